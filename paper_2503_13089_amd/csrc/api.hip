@@ -87,6 +87,13 @@ bool use_pruning(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters)
     return K >= 8192 || (K >= 256 && N >= (1u << 19) && iters >= 5);
 }
 
+// Small problems: two launches per iteration, everything in direct form (small_fit.hip); a fit long and large enough for
+// the windows is better off with them.
+bool use_small(const Ctx& cx, uint64_t N, uint32_t d, uint32_t K, int32_t iters)
+{
+    return cx.mode == CC_ASSIGN_AUTO && !use_pruning(cx, N, K, iters) && cc::small_problem(N, d, K);
+}
+
 // Relative half-width of the guessed windows of the bootstrap pass. The nearest-centroid distance of a vector of
 // norm r is of the order of r * K^(-1/d) when the centroids follow the vectors' own distribution; a window about
 // that wide usually holds a near neighbour and is cheap to score. Capped where (large d) no window would be narrow.
@@ -162,9 +169,12 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
 // One E-step pass: idx (and, if inertia != NULL, the objective) for the given centroids.
 // to_user = false leaves norm-ordered codes in the workspace only (intermediate fit iterations).
 int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx,
-               double* inertia, const cc::Workspace& w, bool pruned, bool have_hint, hipStream_t s)
+               double* inertia, const cc::Workspace& w, bool pruned, bool have_hint, hipStream_t s, bool small)
 {
-    if (use_matrix_cores(cx, K)) {
+    if (small) {
+        cc::ProfileScope scope(cx.prof, cc::kProfEstepDirect, s);
+        CC_TRY_HIP(cc::launch_small_assign(X, N, d, C, K, idx, w.dmin, w, s), "assign (small problem)");
+    } else if (use_matrix_cores(cx, K)) {
         if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, false, pruned, have_hint, s)) return rc;
         if (pruned) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, s), "assign (codes to input order)");
     } else {
@@ -181,9 +191,13 @@ int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const floa
 // idx == NULL (only inside the fit loop, pruned path) skips the copy of the codes to input order.
 int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx,
                    double* inertia, uint32_t* counts, const cc::Workspace& w, bool pruned, bool have_hint, hipStream_t s,
-                   bool sums_follow = false)
+                   bool small, bool sums_follow = false)
 {
-    if (use_matrix_cores(cx, K)) {
+    if (small) {
+        // codes and distances leave the kernel only where somebody reads them
+        cc::ProfileScope scope(cx.prof, cc::kProfEstepDirect, s);
+        CC_TRY_HIP(cc::launch_small_iter(X, N, d, C, K, idx, inertia ? w.dmin : nullptr, counts, w, s), "iteration (small problem)");
+    } else if (use_matrix_cores(cx, K)) {
         // sums_follow (inside a fit, pruned path, after an M-step by buckets of the same fit): the workspace holds the
         // integer sums and counts of the codes in w.idx_sorted. The E-step kernel then flags the vectors that leave
         // those codes (and keeps the code they had), so that the M-step can move just these.
@@ -396,21 +410,22 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * D, w.hdr, s), "input scan");
     if (o.C_work != o.C_in)
         CC_TRY_HIP(cc::launch_copy_f32(o.C_in, o.C_work, size_t(K) * D, s), "centroid copy");
-    const bool pruned = use_matrix_cores(cx, K) && use_pruning(cx, N, K, iters);
+    const bool small = use_small(cx, N, D, K, iters);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, iters);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
     }
     for (int32_t t = 0; t < iters; ++t) {
         // only the matrix-core path can leave its codes in the workspace; the others write idx directly
-        uint32_t* step_idx = pruned ? nullptr : idx;
+        uint32_t* step_idx = pruned || small ? nullptr : idx;
         // from the third iteration on the M-step only moves the vectors whose code changed (the first iterations move
         // too many for that to pay off)
         const bool sums_follow = pruned && w.bucket_ok && t >= 2;
-        if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, sums_follow))
+        if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, small, sums_follow))
             return rc;
     }
-    if (int rc = run_assign(cx, o.X, n, D, o.C_work, K, idx, inertia, w, pruned, iters > 0, s)) return rc;
+    if (int rc = run_assign(cx, o.X, n, D, o.C_work, K, idx, inertia, w, pruned, iters > 0, s, small)) return rc;
     return leave(centroids, d, K, w, s);
 }
 
@@ -436,12 +451,13 @@ int cc_assign_ex(const float* vectors, uint64_t N, uint32_t d, const float* cent
     Operands o;
     if (int rc = enter(vectors, centroids, nullptr, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool pruned = use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
+    const bool small = use_small(cx, N, w.d, K, 1);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, uint32_t(N), w.d, K, w, false, s), "norm ordering");
     }
-    return run_assign(cx, o.X, uint32_t(N), w.d, o.C_in, K, idx, inertia, w, pruned, false, s);
+    return run_assign(cx, o.X, uint32_t(N), w.d, o.C_in, K, idx, inertia, w, pruned, false, s, small);
 }
 
 int cc_lloyd_iter(const float* vectors, uint64_t N, uint32_t d, float* centroids, uint32_t K, uint32_t* idx,
@@ -468,12 +484,13 @@ int cc_lloyd_iter_ex(const float* vectors, uint64_t N, uint32_t d, float* centro
     Operands o;
     if (int rc = enter(vectors, centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool pruned = use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
+    const bool small = use_small(cx, N, w.d, K, 1);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, uint32_t(N), w.d, K, w, false, s), "norm ordering");
     }
-    if (int rc = run_lloyd_iter(cx, o.X, uint32_t(N), w.d, o.C_work, K, idx, inertia, counts, w, pruned, false, s)) return rc;
+    if (int rc = run_lloyd_iter(cx, o.X, uint32_t(N), w.d, o.C_work, K, idx, inertia, counts, w, pruned, false, s, small)) return rc;
     return leave(centroids, d, K, w, s);
 }
 

@@ -10,6 +10,8 @@ namespace cc {
 
 // bytes of the radix sort's histogram buffer for n elements (sort.hip)
 size_t sort_hist_bytes(uint64_t n);
+// per-workgroup cluster sums of a small problem (small_fit.hip); 0 where that form is not used
+size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K);
 
 constexpr uint32_t kMaxK = 1u << 24;
 
@@ -93,6 +95,7 @@ struct Workspace {
     uint32_t* bucket_gtot;     // [groups of kBucketGroup blocks][buckets]
     uint32_t* bucket_base;     // [buckets + 1] first record of each bucket
     bool bucket_ok;
+    char* small_partials;      // small problems: one set of cluster sums per workgroup
     uint32_t refine_cap;
     uint32_t partial_slots;
     uint32_t packed_tiles;     // number of 32-centroid tiles in `packed` (K rounded up, padded)
@@ -176,6 +179,7 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
         w.bucket_gtot = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk / kBucketGroup + 1) * 4));
         w.bucket_base = reinterpret_cast<uint32_t*>(take((buckets + 1) * 4));
     }
+    w.small_partials = take(small_partials_bytes(N, d, K));
     w.bytes = off;
     return w;
 }
@@ -230,6 +234,14 @@ hipError_t launch_assign_mfma_f32(const EStep& e, uint32_t d, const Workspace& w
 // Matrix-core E-step for fp16-representable inputs: centroids split into three fp16 parts so that
 // every product is exact, scored with the fp16 MFMA. Same outputs as the fp32 variant.
 hipError_t launch_assign_mfma_f16(const EStep& e, uint32_t d, const Workspace& w, hipStream_t s);
+
+// Small problems (small_fit.hip): E-step in direct form with the codebook and the cluster sums in LDS. One Lloyd
+// iteration (C updated in place; idx, dmin and counts may be NULL), and the E-step alone.
+bool small_problem(uint64_t N, uint32_t d, uint32_t K);
+hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx, float* dmin,
+                             uint32_t* counts, const Workspace& w, hipStream_t s);
+hipError_t launch_small_assign(const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx, float* dmin,
+                               const Workspace& w, hipStream_t s);
 
 // Norm ordering (pruned E-step): vectors once per call, centroids + per-tile windows once per E-step,
 // and the codes back to input order afterwards.
