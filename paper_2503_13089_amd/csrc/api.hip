@@ -166,6 +166,39 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
     return CC_OK;
 }
 
+// One E-step by cells (cells.hip): near vectors on the lists of their cells, far vectors through the windows. `first`: the
+// first one since the vectors were grouped at all; `track`: as in run_assign_matrix. Codes are left in w.idx_sorted.
+int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint32_t K, const cc::Workspace& w, bool first, bool track,
+                     hipStream_t s)
+{
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, first, s), "assign (centroids and lists of the cells)");
+    }
+    const cc::FarView f = cc::far_view(w, N, d);
+    cc::Workspace wf = w;
+    wf.xsorted = f.x; wf.idx_sorted = f.idx; wf.refine_list = f.refine; wf.refine_cap = N;
+    const uint32_t* far_count = &w.hdr->far_count;
+    {
+        cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
+        CC_TRY_HIP(cc::launch_cells_near(C, N, d, K, w, track, s), "assign (near vectors)");
+        CC_TRY_HIP(cc::launch_windows(C, N, d, K, wf, 0.0f, s, far_count), "assign (windows of the far vectors)");
+        CC_TRY_HIP(cc::launch_cells_far(N, d, K, w, s), "assign (far vectors)");
+    }
+    // inputs that are not fp16 numbers: every vector is far, and the fp32 variant scores it
+    cc::EStep e{};
+    e.X = f.x; e.N = N; e.n_dev = far_count; e.out_pos = f.pos;
+    e.pack_rows = C; e.pack_perm = w.cperm; e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
+    e.packed = w.packed; e.packed_tiles = w.packed_tiles; e.windows = w.windows;
+    e.idx = w.idx_sorted;
+    e.gate = cc::kGateIfNotF16;
+    e.profile = cx.prof;
+    CC_TRY_HIP(cc::launch_assign_mfma_f32(e, d, wf, s), "assign (far vectors, fp32 matrix cores)");
+    cc::ProfileScope refine_scope(cx.prof, cc::kProfRefine, s);
+    CC_TRY_HIP(cc::launch_refine(f.x, N, d, C, K, w.idx_sorted, wf, false, true, s, f.pos), "assign (refinement)");
+    return CC_OK;
+}
+
 // One E-step pass: idx (and, if inertia != NULL, the objective) for the given centroids.
 // to_user = false leaves norm-ordered codes in the workspace only (intermediate fit iterations).
 int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx,
@@ -176,7 +209,7 @@ int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const floa
         CC_TRY_HIP(cc::launch_small_assign(X, N, d, C, K, idx, w.dmin, w, s), "assign (small problem)");
     } else if (use_matrix_cores(cx, K)) {
         if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, false, pruned, have_hint, s)) return rc;
-        if (pruned) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, s), "assign (codes to input order)");
+        if (pruned) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, true, s), "assign (codes to input order)");
     } else {
         CC_TRY_HIP(cc::launch_assign_direct(X, N, d, C, K, idx, w.dmin, nullptr, 0, s, cx.prof), "assign (direct form)");
         CC_TRY_HIP(cc::launch_bump_assign_calls(w.hdr, s), "bookkeeping");
@@ -217,7 +250,7 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
             else
                 CC_TRY_HIP(cc::launch_finalize(C, C, counts, K, d, N, w, true, s), "update (means)");
         }
-        if (pruned && idx != nullptr) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, s), "assign (codes to input order)");
+        if (pruned && idx != nullptr) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, true, s), "assign (codes to input order)");
     } else {
         CC_TRY_HIP(cc::launch_assign_direct(X, N, d, C, K, idx, w.dmin, nullptr, 0, s, cx.prof), "assign (direct form)");
         CC_TRY_HIP(cc::launch_bump_assign_calls(w.hdr, s), "bookkeeping");
@@ -226,6 +259,24 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
     }
     if (inertia)
         CC_TRY_HIP(cc::launch_reduce_dmin(w.dmin, N, w.partials, w.partial_slots, inertia, s), "objective reduction");
+    return CC_OK;
+}
+
+// Iterations of a fit after which the vectors are grouped by their codes (anew): most codes change early.
+bool regroup_at(int32_t t) { return t == 1 || t == 3 || t == 8; }
+
+// Iteration t >= 1 of a fit by cells; the workspace holds the codes, sums and counts of the iteration before.
+int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32_t d_caller, float* C, uint32_t K, cc::Workspace& w,
+                   int32_t t, hipStream_t s)
+{
+    if (regroup_at(t)) {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, t == 1, s), "assign (grouping by code)");
+    }
+    if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1, true, s)) return rc;
+    cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
+    CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed),
+               "update (buckets)");
     return CC_OK;
 }
 
@@ -401,7 +452,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const cc::Workspace w = cc::carve(workspace, N, d, K);
+    cc::Workspace w = cc::carve(workspace, N, d, K);
     const uint32_t n = uint32_t(N), D = w.d;
 
     CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
@@ -416,7 +467,12 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
     }
+    const bool cells = pruned && iters >= 3 && cc::cells_possible(N, D, K);
     for (int32_t t = 0; t < iters; ++t) {
+        if (cells && t > 0) {
+            if (int rc = run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, s)) return rc;
+            continue;
+        }
         // only the matrix-core path can leave its codes in the workspace; the others write idx directly
         uint32_t* step_idx = pruned || small ? nullptr : idx;
         // from the third iteration on the M-step only moves the vectors whose code changed (the first iterations move
@@ -424,6 +480,13 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         const bool sums_follow = pruned && w.bucket_ok && t >= 2;
         if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, small, sums_follow))
             return rc;
+    }
+    if (cells) {
+        if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, false, false, s)) return rc;
+        CC_TRY_HIP(cc::launch_unpermute(n, idx, w, false, s), "assign (codes to input order)");
+        if (inertia)
+            CC_TRY_HIP(cc::launch_reduce_dmin(w.dmin, n, w.partials, w.partial_slots, inertia, s), "objective reduction");
+        return leave(centroids, d, K, w, s);
     }
     if (int rc = run_assign(cx, o.X, n, D, o.C_work, K, idx, inertia, w, pruned, iters > 0, s, small)) return rc;
     return leave(centroids, d, K, w, s);

@@ -90,7 +90,8 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
                                                                uint32_t* counts, const uint2* __restrict__ windows,
                                                                const uint32_t* __restrict__ cperm, int hint_only,
                                                                uint32_t* __restrict__ prev_out,
-                                                               uint32_t* __restrict__ changed)
+                                                               uint32_t* __restrict__ changed,
+                                                               const uint32_t* __restrict__ n_dev, const uint32_t* __restrict__ out_pos)
 {
     constexpr int KS = D / 2;                 // MFMA k-steps per tile
     if (!gate_open(hdr, gate)) return;        // uniform over the grid
@@ -105,6 +106,10 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
     const int h = lane >> 5, n = lane & 31;
     // a windowed launch starts with the last tiles of the norm order, whose windows are the widest (as in the fp16 kernel)
     const uint32_t wg = WINDOWED ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    if (n_dev != nullptr) {  // fewer vectors than the grid was made for (uniform over the workgroup)
+        N = min(N, *n_dev);
+        if (wg * (4 * 32 * VT) >= N) return;
+    }
     const uint32_t vbase = (wg * 4 + wave) * (32 * VT);
 
     // B operands: lane (n, h) supplies -2 * x_n[2 ks + h] for k-step ks
@@ -269,8 +274,9 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
                 moved = old != kstar || !safe;
                 if (moved) prev_out[i] = old;
             }
-            idx[i] = kstar;
-            dmin[i] = dstar;
+            const uint32_t o = out_pos != nullptr ? out_pos[i] : i;
+            idx[o] = kstar;
+            dmin[o] = dstar;
             if (sums != nullptr) accumulate_vector<D>(x, kstar, sums, counts, sum_exp, +1);
             if (!safe) {
                 const uint32_t pos = atomicAdd(&hdr->refine_count, 1u);
@@ -303,7 +309,7 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
                            e.X, e.N, e.rows, e.K, static_cast<const float*>(e.packed), e.packed_tiles, e.idx, w.dmin, w.hdr,
                            w.refine_list, w.refine_cap, e.gate, e.accumulate ? w.sums : nullptr,
                            e.accumulate ? w.counts : nullptr, e.windows, e.row_ids, e.hint_only ? 1 : 0,
-                           e.prev_out, e.changed);
+                           e.prev_out, e.changed, e.n_dev, e.out_pos);
     }
     return hipGetLastError();
 }

@@ -30,56 +30,11 @@
 #include <algorithm>
 
 #include "common.h"
+#include "f16_scores.h"
 
 namespace cc {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 constexpr int kThreads = 256;
-constexpr float kUnit = 5.9604644775390625e-08f;  // 2^-24
-constexpr float kGuardSafety = 1.5f;
-constexpr float kAccumUlps = 8.0f;
-
-template <int D>
-struct F16Shape {
-    static constexpr int kParts = (D == 4) ? 3 : 2;         // fp16 parts per centroid component
-    static constexpr bool kNormInK = (D == 4);              // ||c||^2 rides in spare k slots
-    static constexpr int kSlots = kParts * D + (kNormInK ? 3 : 0);
-    static constexpr int KM = (kSlots + 15) / 16;           // MFMAs per tile
-    static constexpr int kTileBytes = 64 * KM * 16 + (kNormInK ? 0 : 128);
-};
-
-// log2 of the centroid scale sigma: max|c| * sigma <= 2^15 and d * max|c|^2 * sigma <= 2^23
-__device__ __forceinline__ int centroid_scale_log2(uint32_t cmax_bits, int d)
-{
-    if (cmax_bits == 0) return 0;
-    const int ec = int(cmax_bits >> 23) - 127;  // max|c| < 2^(ec+1)
-    const int ld = 32 - __clz(uint32_t(d - 1)); // d <= 2^ld
-    int s = min(14 - ec, 21 - 2 * ec - ld);
-    return max(-100, min(100, s));
-}
-
-// The three fp16 parts of a scaled fp32 value.
-__device__ __forceinline__ void split3(float v, _Float16 (&h)[3])
-{
-    h[0] = _Float16(v);
-    const float r1 = v - float(h[0]);  // exact
-    h[1] = _Float16(r1);
-    const float r2 = r1 - float(h[1]);  // exact
-    h[2] = _Float16(r2);
-}
-
-// sigma*||c||^2 as g0*2^8 + g1*2^-3 + g2*2^-14
-__device__ __forceinline__ void split_norm(float v, _Float16 (&g)[3])
-{
-    g[0] = _Float16(v * 0.00390625f);
-    const float r1 = v - float(g[0]) * 256.0f;
-    g[1] = _Float16(r1 * 8.0f);
-    const float r2 = r1 - float(g[1]) * 0.125f;
-    g[2] = _Float16(r2 * 16384.0f);
-}
-
 __global__ __launch_bounds__(kThreads) void codebook_absmax_kernel(const float4* __restrict__ C4, size_t n4,
                                                                    WsHeader* hdr, int gate)
 {
@@ -201,24 +156,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_f16_kernel(
         const uint32_t i = min(vbase + vt * 32 + n, N - 1);
         float x[D];
         load_row<D>(X + size_t(i) * D, x);
-#pragma unroll
-        for (int mi = 0; mi < KM; ++mi) {
-#pragma unroll
-            for (int q8 = 0; q8 < 8; ++q8) {
-                _Float16 v[2];
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const int q = 16 * mi + 8 * half + q8;
-                    v[half] = _Float16(0.0f);
-                    constexpr int PD = S::kParts * D;
-                    if (q < PD) v[half] = _Float16(-2.0f * x[q % D]);
-                    else if (S::kNormInK && q == PD) v[half] = _Float16(256.0f);
-                    else if (S::kNormInK && q == PD + 1) v[half] = _Float16(0.125f);
-                    else if (S::kNormInK && q == PD + 2) v[half] = _Float16(6.103515625e-05f);  // 2^-14
-                }
-                b[vt][mi][q8] = h ? v[1] : v[0];
-            }
-        }
+        vector_operand<D>(x, h, b[vt]);
     }
     float best[VT], second[VT];
     uint32_t grp[VT];
@@ -363,33 +301,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_f16_kernel(
             if (h == 0 && i_raw < N) idx[i] = kstar;
             continue;
         }
-        float xn = 0.0f, x1 = 0.0f, xlost = 0.0f;
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            xn = __builtin_fmaf(x[j], x[j], xn);
-            x1 += __builtin_fabsf(x[j]);
-            // what the fp16 operand -2 x_j lost: nonzero only below the fp16 normal range, at most 2^-25, exact in fp32
-            const float t = -2.0f * x[j];
-            xlost += __builtin_fabsf(t - float(_Float16(t)));
-        }
-        // accumulation rounding of winner + true nearest (||c||^2 <= 2||x||^2 + 2D for both); what fp16
-        // subnormal factors add to the sum of |terms| (with a = 2^-14: each of the P*D product slots at most
-        // a |2 x_j| + a |part| + a^2, the parts of one centroid summing to <= 1.002 sigma ||c||_1, and the
-        // norm slots at most 2^-6 + 2^-17 + 2^-28); then the split residuals: 2^-25 per component against
-        // |2 x_j|, twice, and the norm residual
-        constexpr float kA = 6.103515625e-05f;  // 2^-14
-        constexpr int P = S::kParts;
-        const float inflation = 2.0f * float(P) * kA * x1 + 1.002f * kA * sigma * __builtin_sqrtf(float(D) * (2.0f * xn + 2.0f * dstar)) +
-                                float(P * D) * kA * kA + (S::kNormInK ? 0.015634f : 0.0f);
-        // two parts leave a relative residual: |c sigma - h1 - h2| <= 2^-22 |c sigma| per component (each part is a
-        // rounding to 11 bits), against |2 x_j|: at most 2^-21 sigma ||x|| ||c|| per score, for the best and for its
-        // competitor (three parts leave 2^-33, which the accumulation term dwarfs)
-        const float split_rel = P == 2 ? 9.5367431640625e-07f * sigma * __builtin_sqrtf(xn * (2.0f * xn + 2.0f * dstar)) : 0.0f;
-        // a lost part of -2 x_j moves every score of this vector by at most |it| * sigma * max|c| * 1.002 (the
-        // parts of a centroid component), the best and its competitor in opposite directions at worst
-        const float operand_loss = 2.0f * 1.002f * sigma_cmax * xlost;
-        const float delta = kGuardSafety * 2.0f * kAccumUlps * kUnit * (sigma * (5.0f * xn + 4.0f * dstar) + inflation) +
-                            kGuardSafety * (2.0f * kUnit * x1 + 1e-11f + operand_loss + split_rel) + 1e-36f;
+        const float delta = f16_guard_band<D>(x, dstar, sigma, sigma_cmax);
         const bool safe = (sstar - bstar) > delta;  // false for NaN as well
         bool moved = false;
         if (h == 0 && i_raw < N) {

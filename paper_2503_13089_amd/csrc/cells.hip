@@ -1,0 +1,1244 @@
+// E-step of a fit by cells (Section 3.1: the codes are the argmin over ALL centroids; a centroid can be skipped for a
+// vector only if it provably cannot be that argmin), for sub-vectors of up to 8 numbers and K <= 65536.
+//
+// After the first iteration the vectors are grouped by the code they have: the group of centroid c is its cell. For a
+// vector x of the cell with previous code h, u = ||x - c_h|| bounds the distance of its nearest centroid c', so
+//     ||c - c'|| <= ||x - c|| + ||x - c'|| <= ||x - c|| + u =: t(x).
+// Once per E-step every centroid gets the list of the centroids within a radius R of it; the vectors of its cell with
+// t(x) <= R ("near") are decided on that list alone. It is 10^2 .. 10^3 times shorter than the codebook where the
+// (norm, cosine) windows of sort.hip leave 3 % (d = 4) or 66 % (d = 8) of it: a ball in d dimensions against a shell.
+// The other vectors ("far", a few per cent) are collected in the norm order and go through the windowed matrix-core
+// E-step. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
+// codes are the same bits as those of every other route, whatever the radius, however old the grouping.
+// Measured, E-step of a later iteration: N = 11 M, d = 4, K = 65536: 0.78 ms with 1 to 4 % far (1.2 ms by windows);
+// N = 29 M, d = 8: 7.5 ms with 2 % far (53 ms).
+//
+// The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
+// against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
+// kTarget centroids per list, and no more than the largest t(x) of the cell.
+#include <algorithm>
+
+#include "common.h"
+#include "f16_scores.h"
+#include "ordering.h"
+
+namespace cc {
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kWaves = kThreads / 64;
+
+// A cell's list: the centroids within r1 of its centroid, then (d = 8) those between r1 and r2.
+template <int D>
+struct Lists {
+    static constexpr uint32_t kCap1 = D == 4 ? 128 : 1024;            // room for entries within r1 ...
+    static constexpr uint32_t kCap2 = D == 4 ? 0 : 5120;              // ... and between r1 and r2
+    static constexpr uint32_t kCap = kCap1 + kCap2;
+    static constexpr float kTarget1 = D == 4 ? 44.0f : 400.0f;        // entries within r1 / r2 that a list should have
+    static constexpr float kTarget2 = D == 4 ? 44.0f : 1500.0f;
+};
+
+}  // namespace
+
+uint32_t cell_list_cap(uint32_t d) { return d == 4 ? Lists<4>::kCap : Lists<8>::kCap; }
+
+namespace {
+
+// Lists and near vectors need numbers that -2 x in fp16 can carry (rounded: bounds cover that): fp16 inputs are, others if
+// they are below 2^14.
+__device__ __forceinline__ bool lists_exist(const WsHeader* hdr)
+{
+    return hdr->x_not_f16 == 0 || max(hdr->cmax_bits, hdr->absmax_bits) < 0x46800000u;
+}
+
+// ---- grouping ---------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kThreads) void cell_keys_kernel(const uint32_t* __restrict__ idx, uint32_t N, uint16_t* __restrict__ keys,
+                                                             uint32_t* __restrict__ ids)
+{
+    const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
+    if (p >= N) return;
+    keys[p] = uint16_t(idx[p]);
+    ids[p] = p;
+}
+
+// New position p holds what stood at order[p]. order is turned into the norm rank of every position (the position in
+// the norm order the fit began with: rank_old == NULL means that the old order is that one).
+__global__ __launch_bounds__(kThreads) void cell_apply_kernel(const uint16_t* __restrict__ sorted_keys, uint32_t N, uint32_t* order,
+                                                              const uint32_t* __restrict__ rank_old,
+                                                              const uint32_t* __restrict__ perm_old, uint32_t* __restrict__ perm_new,
+                                                              uint32_t* __restrict__ position, uint32_t* __restrict__ idx)
+{
+    const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
+    if (p >= N) return;
+    const uint32_t q = order[p];
+    const uint32_t r = rank_old != nullptr ? rank_old[q] : q;
+    order[p] = r;
+    position[r] = p;
+    perm_new[p] = perm_old[q];
+    idx[p] = sorted_keys[p];
+}
+
+// First vector of every cell (codes are sorted: a binary search each).
+__global__ __launch_bounds__(kThreads) void cell_starts_kernel(const uint16_t* __restrict__ sorted_keys, uint32_t N, uint32_t K,
+                                                               CellHead* __restrict__ heads)
+{
+    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+    if (t >= K) return;
+    uint32_t bound[2];
+#pragma unroll
+    for (uint32_t u = 0; u < 2; ++u) {
+        uint32_t a = 0, b = N;
+        while (a < b) {
+            const uint32_t m = a + (b - a) / 2;
+            if (uint32_t(sorted_keys[m]) >= t + u) b = m; else a = m + 1;
+        }
+        bound[u] = a;
+    }
+    heads[t].start = bound[0];
+    heads[t].members = bound[1] - bound[0];
+}
+
+// Work items of at most `item` vectors of one cell: cell c owns the slots [start / item + c, next cell's) of the item
+// table, always enough for its ceil(members / item) items; the slots it does not need are marked empty.
+__global__ __launch_bounds__(kThreads) void cell_items_kernel(const CellHead* __restrict__ heads, uint32_t K, uint32_t slots,
+                                                              uint32_t item, uint32_t* __restrict__ item_cell)
+{
+    const uint32_t c = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (c >= K) return;
+    const uint32_t s0 = heads[c].start, members = heads[c].members;
+    const uint32_t first = s0 / item + c, end = c + 1 < K ? (s0 + members) / item + c + 1 : slots;
+    const uint32_t used = first + (members + item - 1) / item;
+    for (uint32_t s = first + (threadIdx.x & 63); s < end; s += 64) item_cell[s] = s < used ? c : 0xffffffffu;
+}
+
+// ---- radius -----------------------------------------------------------------------------------------------------
+// First radii of a cell: multiples of the mean t(x) of (up to 256 of) its vectors. One wave per cell.
+template <int D>
+__global__ __launch_bounds__(kThreads) void cell_first_radius_kernel(const float* __restrict__ X, const uint32_t* __restrict__ idx,
+                                                                     CellHead* __restrict__ heads, const float* __restrict__ C,
+                                                                     uint32_t K, float factor1, float factor2)
+{
+    const uint32_t c = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (c >= K) return;
+    const uint32_t lane = threadIdx.x & 63, s0 = heads[c].start, n = min(heads[c].members, 256u);
+    float row[D];
+    load_row<D>(C + size_t(c) * D, row);
+    float sum = 0.0f;
+    for (uint32_t i = lane; i < n; i += 64) {
+        float x[D], ch[D];
+        load_row<D>(X + size_t(s0 + i) * D, x);
+        load_row<D>(C + size_t(min(idx[s0 + i], K - 1)) * D, ch);
+        sum += __builtin_sqrtf(direct_sqdist<D>(x, row)) + __builtin_sqrtf(direct_sqdist<D>(x, ch));
+    }
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if (lane == 0) {
+        const float mean = n > 0 ? sum / float(n) : 0.0f;
+        heads[c].r1 = factor1 * mean;
+        heads[c].r2 = factor2 * mean;
+    }
+}
+
+// ---- centroids: order, operands, radii ------------------------------------------------------------------------------
+// Three launches put the centroids into the order of sort.hip's (norm shell, cosine) key with everything the E-step needs
+// of them: keys and histogram; prefix sums (which are the key -> first position table); rows, permutations and operands
+// straight to their places. Unlike the stable radix sort this leaves the order among equal keys to scheduling, which
+// decides nothing but which tile a centroid shares; eight launches of 4 us for a few microseconds of work became three.
+
+// Keys and their histogram, the largest magnitude; and what has to happen once per E-step: the radii follow the lengths
+// of the cell's last list (towards the targets, at most 18 % a step) and never exceed what any vector of the cell needed;
+// the bitmap of changed codes and the counters are cleared.
+template <int D>
+__global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const float* __restrict__ C, uint32_t K, uint32_t words,
+                                                                          int first, uint16_t* __restrict__ keys,
+                                                                          uint32_t* __restrict__ hist, CellHead* __restrict__ heads,
+                                                                          uint32_t* __restrict__ changed, WsHeader* hdr)
+{
+    using L = Lists<D>;
+    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+    if (t == 0) {
+        hdr->far_count = 0;
+        hdr->refine_count = 0;
+    }
+    if (t < words) changed[t] = 0;
+    uint32_t m = 0;
+    if (t < K) {
+        float c[D];
+        load_row<D>(C + size_t(t) * D, c);
+        float s = 0.0f, proj;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            s = __builtin_fmaf(c[j], c[j], s);
+            m = max(m, __float_as_uint(c[j]) & 0x7fffffffu);
+        }
+        const uint32_t key = ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj);
+        keys[t] = uint16_t(key);
+        atomicAdd(&hist[key], 1u);
+        if (!first) {
+            const CellHead h = heads[t];
+            auto next = [&](float r, float target, uint32_t n) {
+                float step = __builtin_sqrtf(__builtin_sqrtf(target / float(max(n, 1u))));
+                if (D == 8) step = __builtin_sqrtf(step);
+                return fminf(r * fminf(fmaxf(step, 0.85f), 1.18f), 1.05f * __uint_as_float(h.tmax));
+            };
+            const float r1 = next(h.r1, L::kTarget1, h.n1);
+            heads[t].r1 = r1;
+            heads[t].r2 = fmaxf(r1, next(h.r2, L::kTarget2, h.n1 + h.n2));
+        }
+        heads[t].tmax = 0;
+        heads[t].mids = 0;
+    }
+    for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
+    if ((threadIdx.x & 63) == 0 && m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
+}
+
+// starts[v] = centroids with a key below v, also the next free position of each key (cursor). One workgroup per
+// 1024 keys; each adds up everything before its own share itself.
+__global__ __launch_bounds__(1024) void cell_key_starts_kernel(const uint32_t* __restrict__ hist, uint32_t* __restrict__ starts, uint32_t* __restrict__ cursor,
+                                                               uint32_t K)
+{
+    __shared__ uint32_t wave_sum[16], wave_before[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lo = blockIdx.x * 1024;
+    uint32_t before = 0;
+    for (uint32_t i = threadIdx.x; i < lo / 4; i += 1024) {
+        const uint4 v = reinterpret_cast<const uint4*>(hist)[i];
+        before += v.x + v.y + v.z + v.w;
+    }
+    const uint32_t own = hist[lo + threadIdx.x];
+    uint32_t incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = uint32_t(__shfl_up(int(incl), off, 64));
+        if (lane >= off) incl += v;
+    }
+    for (int off = 32; off > 0; off >>= 1) before += uint32_t(__shfl_xor(int(before), off, 64));
+    if (lane == 63) wave_sum[wave] = incl;
+    if (lane == 0) wave_before[wave] = before;
+    __syncthreads();
+    uint32_t at = incl - own;
+    for (int w = 0; w < 16; ++w) {
+        at += wave_before[w];
+        if (w < wave) at += wave_sum[w];
+    }
+    starts[lo + threadIdx.x] = at;
+    cursor[lo + threadIdx.x] = at;
+    if (lo == 0 && threadIdx.x == 0) starts[65536] = K;
+}
+
+// Every centroid to its place: permutation and inverse, ordered row, the operand row of the E-step's packed codebook
+// (assign_mfma_f16.hip) and the one of the lists: 8 product slots (the first fp16 part of each component) and
+// 8 for norm and threshold: sigma ||c||^2 in three parts against the multipliers 2^8, 2^-3, 2^-14 of the other side, and
+// those multipliers themselves. Positions past K get operands that never win and never enter a list.
+template <int D>
+__global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __restrict__ C, uint32_t K, uint32_t padded,
+                                                              const uint16_t* __restrict__ keys, uint32_t* __restrict__ cursor,
+                                                              uint32_t* __restrict__ cperm, uint32_t* __restrict__ cinv,
+                                                              float* __restrict__ csorted, char* __restrict__ packed,
+                                                              char* __restrict__ operands, char* __restrict__ flat,
+                                                              const WsHeader* __restrict__ hdr)
+{
+    using S = F16Shape<D>;
+    static_assert(S::KM == 1, "one matrix instruction per tile");
+    const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
+    if (k >= padded) return;
+    const bool valid = k < K;
+    float c[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) c[j] = 0.0f;
+    uint32_t pos = k;
+    if (valid) {
+        load_row<D>(C + size_t(k) * D, c);
+        pos = atomicAdd(&cursor[keys[k]], 1u);
+        cperm[pos] = k;
+        cinv[k] = pos;
+#pragma unroll
+        for (int q = 0; q < D / 4; ++q)
+            reinterpret_cast<float4*>(csorted + size_t(pos) * D)[q] = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+    }
+    if (!lists_exist(hdr)) return;
+    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
+    _Float16 parts[D][3], g[3];
+    double norm = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        norm += double(c[j]) * double(c[j]);
+        split3(c[j] * sigma, parts[j]);
+    }
+    const float scaled_norm = valid ? float(norm * double(sigma)) : INFINITY;
+    if (valid) {
+        split_norm(scaled_norm, g);
+    } else {
+        g[0] = _Float16(INFINITY);
+        g[1] = g[2] = _Float16(0.0f);
+    }
+    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
+    char* tile = packed + size_t(pos >> 5) * S::kTileBytes;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        f16x8 v;
+#pragma unroll
+        for (int q8 = 0; q8 < 8; ++q8) {
+            const int slot = 8 * half + q8;
+            v[q8] = slot < S::kParts * D ? parts[slot % D][slot / D]
+                                         : (S::kNormInK && slot < S::kParts * D + 3 ? g[slot - S::kParts * D] : _Float16(0.0f));
+        }
+        *reinterpret_cast<f16x8*>(tile + (half * 32 + m) * 16) = v;
+    }
+    if (!S::kNormInK) *reinterpret_cast<float*>(tile + 1024 + 4 * q) = scaled_norm;
+    if (flat != nullptr && valid) {  // d = 8: the operand pieces of one centroid side by side, for the near vectors
+        f16x8* to = reinterpret_cast<f16x8*>(flat + size_t(pos) * 64);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            f16x8 v;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = parts[j % D][p];
+            to[p] = v;
+        }
+        const _Float16 o = _Float16(0.0f);
+        to[3] = f16x8{g[0], g[1], g[2], o, o, o, o, o};
+        if (k == 0) {   // row K never wins: a norm of 60000 * 2^8 is above every score (at most 2^23 + 2^24), and finite so
+                        // that a tag leaves it a number
+            f16x8* none = reinterpret_cast<f16x8*>(flat + size_t(K) * 64);
+            none[0] = none[1] = none[2] = f16x8{o, o, o, o, o, o, o, o};
+            none[3] = f16x8{_Float16(60000.0f), o, o, o, o, o, o, o};
+        }
+    }
+    char* op = operands + size_t(pos >> 5) * 1024;
+    f16x8 lo, hi;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) lo[j] = j < D ? parts[j % D][0] : _Float16(0.0f);
+    const _Float16 z = _Float16(0.0f);
+    hi = f16x8{valid ? g[0] : _Float16(60000.0f), g[1], g[2], _Float16(256.0f), _Float16(0.125f), _Float16(6.103515625e-05f), z, z};
+    *reinterpret_cast<f16x8*>(op + m * 16) = lo;
+    *reinterpret_cast<f16x8*>(op + (32 + m) * 16) = hi;
+}
+
+// ---- lists: one workgroup per 32 cells (neighbours in the norm order), its waves taking turns at the codebook ---------
+// One matrix instruction gives sigma (||c'||^2 - 2 c.c' - (R^2 - ||c||^2 + slack)) for 32 x 32 (centroid, cell) pairs;
+// an entry is kept where that is negative. Both sides' coordinates are fp16 (2^-11 relative each), which the slack covers: a
+// list may hold a few centroids beyond R, never fewer than all within. The signs of a lane's 16 results are shifted into
+// one word (with a second instruction for the inner radius into another), the cells' counters are in LDS. Where in a list
+// an entry lands depends on scheduling; no result does.
+// WINDOWED (d = 4): only the runs of the ordered codebook that the shells and cosines of sort.hip allow for the 32 cells;
+// at d = 8 a ball that is 1 % of the codebook touches most of them.
+// Bound: vector instructions, 50 to 80 per 1024 pairs; K = 65536: 4.3 G pairs at d = 8 in 0.54 to 0.97 ms (1.35 with the
+// hits worked off where they were found), 0.14 ms at d = 4.
+constexpr float kListThrMax = 1.5e7f;     // what three fp16 parts against 2^8, 2^-3, 2^-14 can carry
+template <int D, bool WINDOWED>
+__global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
+                                                              uint32_t K, const char* __restrict__ operands, uint32_t ntiles,
+                                                              const uint32_t* __restrict__ key_starts, CellHead* __restrict__ heads,
+                                                              uint32_t N, WsHeader* hdr, uint16_t* __restrict__ lists,
+                                                              uint32_t* __restrict__ hist)
+{
+    using L = Lists<D>;
+    __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32];
+    __shared__ uint2 queues[kWaves][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < 65536; i += gridDim.x * kThreads) hist[i] = 0;  // for the next E-step
+    if (!lists_exist(hdr)) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
+    const uint32_t p0 = blockIdx.x * 32;
+    const uint32_t pos = min(p0 + n, K - 1), c = cperm[pos];
+    if (threadIdx.x < 32) {
+        cnt1[threadIdx.x] = 0;
+        cnt2[threadIdx.x] = 0;
+        cell_ids[threadIdx.x] = c;
+    }
+    __syncthreads();
+    float x[D];
+    load_row<D>(csorted + size_t(pos) * D, x);
+    const CellHead head = heads[c];
+    float xn = 0.0f;
+#pragma unroll
+    for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
+    const float norm = __builtin_sqrtf(xn);
+    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
+    // slack: 2^-9 ||c|| ||c'|| = 1.95e-3 for the rounded operands; everything else (accumulation, the split of norm and
+    // threshold, fp16 subnormals) is far below the difference to 2.2e-3 and the constant term
+    auto threshold = [&](float R) { return sigma * (R * R * 1.0001f - xn + 2.2e-3f * norm * (norm + R)) + 0.05f; };
+    float r2 = L::kCap2 > 0 ? head.r2 : head.r1;
+    if (threshold(r2) > kListThrMax) r2 = head.r1;
+    const bool carried = threshold(head.r1) <= kListThrMax;  // else the cell goes without a list
+    const bool live = p0 + n < K && head.members > 0 && head.r1 > 0.0f && carried;
+    const float thr1 = threshold(head.r1), thr = threshold(r2);
+    auto operand = [&](float threshold) {
+        _Float16 tp[3];
+        split_norm(live ? -threshold : kListThrMax, tp);
+        const _Float16 z = _Float16(0.0f);
+        f16x8 lo;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lo[j] = j < D ? _Float16(-2.0f * x[j % D]) : z;
+        const f16x8 hi = f16x8{_Float16(256.0f), _Float16(0.125f), _Float16(6.103515625e-05f), tp[0], tp[1], tp[2], z, z};
+        return h ? hi : lo;
+    };
+    const f16x8 b = operand(thr), b1 = operand(thr1);
+    f32x16 zero;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) zero[q] = 0.0f;
+
+    // runs of tiles to scan: with windows one per lane (shell), else a single run
+    uint2 run = make_uint2(0, ntiles);
+    uint32_t nruns = 1;
+    if constexpr (WINDOWED) {
+        const uint32_t base = shell_base(hdr->absmax_bits, D);
+        float prj;
+        (void)ordering_key<D>(x, norm, base, prj);
+        float nlo = live ? norm - r2 : INFINITY, nhi = live ? norm + r2 : 0.0f;
+        float plo = live ? prj - r2 : INFINITY, phi = live ? prj + r2 : -INFINITY;
+        for (int off = 16; off > 0; off >>= 1) {
+            nlo = __builtin_fminf(nlo, __shfl_xor(nlo, off, 64));
+            nhi = __builtin_fmaxf(nhi, __shfl_xor(nhi, off, 64));
+            plo = __builtin_fminf(plo, __shfl_xor(plo, off, 64));
+            phi = __builtin_fmaxf(phi, __shfl_xor(phi, off, 64));
+        }
+        const float slack = nhi < 3.0e38f ? 1e-5f * nhi : 0.0f;
+        nlo -= slack; nhi += slack; plo -= slack; phi += slack;
+        const uint32_t smin = shell_of_key(nlo > 0.0f ? norm_key(nlo) : 0u, base);
+        const uint32_t smax = shell_of_key(nhi < 3.0e38f ? norm_key(nhi) : 0xffffu, base);
+        const bool wide = smax - smin + 1 > 64u;
+        nruns = uint32_t(__builtin_amdgcn_readfirstlane(int(wide ? 1u : smax - smin + 1)));
+        uint32_t klo = smin << 7, khi = (smax << 7) | 127u;
+        if (!wide) shell_cosine_run(smin + min(uint32_t(lane), nruns - 1), base, plo, phi, klo, khi);
+        run = make_uint2(0, 0);
+        if (klo <= khi && nlo <= nhi) {
+            const uint32_t first = key_starts[klo], end = key_starts[khi + 1];
+            if (first < end) run = make_uint2(first / 32, (end + 31) / 32);
+        }
+    }
+    // Lanes with a hit push (their rows' bits, tile and lane) onto a queue of their wave; 64 entries at a time are then
+    // taken off it, one per lane. Worked off on the spot, a tile's few hits would keep the wave busy for six times as
+    // many instructions as the rest of the tile.
+    uint2* queue = queues[wave];
+    uint32_t queued = 0;   // wave-uniform
+    auto work_off = [&](uint32_t count) {   // the first `count` <= 64 entries
+        if (uint32_t(lane) < count) {
+            const uint2 q = queue[lane];
+            const uint32_t cell = q.y & 31u, first_pos = (q.y >> 6) * 32 + (q.y & 32u ? 16u : 0u);
+            uint32_t mask = q.x & 0xffffu;
+            const uint32_t inner = L::kCap2 > 0 ? (q.x >> 16) & mask : mask;
+            uint16_t* list = lists + size_t(cell_ids[cell]) * L::kCap;
+            const uint32_t n1 = __popc(inner), n2 = __popc(mask) - n1;
+            uint32_t at1 = n1 ? atomicAdd(&cnt1[cell], n1) : 0u, at2 = n2 ? atomicAdd(&cnt2[cell], n2) : 0u;
+            do {
+                const uint32_t r = uint32_t(__clz(int(mask))) - 16, bit = 0x8000u >> r;
+                mask &= ~bit;
+                const bool in = (inner & bit) != 0;
+                const uint32_t at = in ? at1 : at2;
+                if (at < (in ? L::kCap1 : L::kCap2)) list[(in ? 0u : L::kCap1) + at] = uint16_t(first_pos + r);
+                at1 += in ? 1u : 0u;
+                at2 += in ? 0u : 1u;
+            } while (mask != 0);
+        }
+    };
+    constexpr int U = 4;                        // tiles a wave takes at a time
+    constexpr uint32_t kStep = U * kWaves;
+    uint32_t next = 0;
+    for (uint32_t r = 0; r < nruns; ++r) {
+        const uint32_t r0 = max(uint32_t(__builtin_amdgcn_readlane(int(run.x), int(r))), next);  // a tile on the border of
+        const uint32_t t1 = uint32_t(__builtin_amdgcn_readlane(int(run.y), int(r)));             // two shells is visited once
+        if (r0 >= t1) continue;
+        next = t1;
+        uint32_t t = r0 + wave * U;
+        f16x8 a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + u, t1 - 1)) * 1024 + lane * 16);
+        for (; t < t1; t += kStep) {
+            f16x8 an[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                an[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + kStep + u, t1 - 1)) * 1024 + lane * 16);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (t + u >= t1) break;
+                const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b, zero, 0, 0, 0);
+                if constexpr (WINDOWED) {
+                    float m = INFINITY;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) m = __builtin_fminf(__builtin_fminf(m, acc[2 * q]), acc[2 * q + 1]);
+                    if (!__any(m < 0.0f)) continue;
+                }
+                uint32_t mask = 0;   // bit 15 - q: row q is within the radius
+#pragma unroll
+                for (int q = 0; q < 16; ++q) mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(acc[q]), 31);
+                uint32_t bits = mask;
+                if constexpr (L::kCap2 > 0) {   // upper half: within r1
+                    const f32x16 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b1, zero, 0, 0, 0);
+                    uint32_t inner = 0;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) inner = __builtin_amdgcn_alignbit(inner, __float_as_uint(acc1[q]), 31);
+                    bits = mask | (inner << 16);
+                }
+                const unsigned long long hits = __ballot(mask != 0);
+                if (mask != 0)
+                    queue[__builtin_amdgcn_mbcnt_hi(uint32_t(hits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(hits), queued))] =
+                        make_uint2(bits, ((t + u) << 6) | uint32_t(lane));
+                queued += uint32_t(__popcll(hits));
+                if (queued >= 64) {
+                    __builtin_amdgcn_wave_barrier();
+                    work_off(64);
+                    queued -= 64;
+                    const uint2 rest = queue[64 + lane];
+                    __builtin_amdgcn_wave_barrier();
+                    if (uint32_t(lane) < queued) queue[lane] = rest;
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[u] = an[u];
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    work_off(queued);
+    __syncthreads();
+    if (wave == 0) {
+        float scored = 0.0f;
+        if (h == 0 && p0 + n < K) {
+            heads[c].n1 = carried ? cnt1[n] : 0xffffffffu;
+            heads[c].n2 = cnt2[n];
+            if (r2 != head.r2) heads[c].r2 = r2;
+            if (carried) scored = float(cnt1[n]) * float(head.members);
+        }
+        // statistics: pairs the near vectors look at, in units of (512 vectors x 32 centroids)
+        for (int off = 32; off > 0; off >>= 1) scored += __shfl_xor(scored, off, 64);
+        if (lane == 0) {
+            atomicAdd(&hdr->window_stages, static_cast<unsigned long long>(scored / 16384.0f + 1.0f));
+            if (blockIdx.x == 0)
+                atomicAdd(&hdr->window_total, static_cast<unsigned long long>((N + kWinTile - 1) / kWinTile) * ((K + 31) / 32));
+        }
+    }
+}
+
+// ---- what the near kernels share ---------------------------------------------------------------------------------
+struct NearArgs {
+    const float* X;
+    const float* C;             // centroids by index
+    const float* csorted;       // centroids in the norm order ...
+    const char* flat;           // ... their operand pieces (d = 8) ...
+    const uint32_t* cperm;      // ... and their indices
+    uint32_t K;
+    CellHead* heads;
+    const uint32_t* item_cell;
+    uint32_t slots;
+    const uint16_t* lists;
+    const uint32_t* rank;
+    uint32_t* far_bits;
+    uint32_t* mids;             // d = 8: positions of the vectors between r1 and r2, those of a cell from its start on
+    uint32_t* idx;
+    float* dmin;
+    uint32_t* prev_out;         // NULL: changes are not tracked
+    uint32_t* changed;
+    WsHeader* hdr;
+};
+
+// Sets bit (p0 + lane) of a bitmap for every set bit of `m` (wave-uniform), where the 64 positions start anywhere.
+__device__ __forceinline__ void or_bits(uint32_t* bits, uint32_t p0, unsigned long long m, int lane)
+{
+    if (m == 0) return;
+    const uint32_t sh = p0 & 31u;
+    const uint32_t w = lane == 0 ? uint32_t(m << sh) : (lane == 1 ? uint32_t(m >> (32 - sh)) : (sh ? uint32_t(m >> (64 - sh)) : 0u));
+    if (lane < 3 && w != 0) atomicOr(bits + (p0 >> 5) + lane, w);
+}
+
+__device__ __forceinline__ void or_bit(uint32_t* bits, uint32_t p) { atomicOr(bits + (p >> 5), 1u << (p & 31u)); }
+
+__device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint32_t item, bool mid, uint32_t& c, CellHead& head,
+                                          uint32_t& first, uint32_t& n)
+{
+    if (slot >= a.slots) return false;
+    c = uint32_t(__builtin_amdgcn_readfirstlane(int(a.item_cell[slot])));
+    if (c >= a.K) return false;
+    head = a.heads[c];
+    const uint32_t at = (slot - (head.start / item + c)) * item;
+    first = head.start + at;
+    const uint32_t have = mid ? head.mids : head.members;
+    if (at >= have) return false;
+    n = min(item, have - at);
+    return true;
+}
+
+// t(x), enlarged by more than the rounding of the two distances
+template <int D>
+__device__ __forceinline__ float cell_bound(const float (&x)[D], const float (&centre)[D], const float (&hinted)[D])
+{
+    return (__builtin_sqrtf(direct_sqdist<D>(x, centre)) + __builtin_sqrtf(direct_sqdist<D>(x, hinted)) * 1.001f) * 1.00001f + 1e-30f;
+}
+
+// ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
+// Direct-form distances are final: no guard band and no index recovery. Rows past the list are NaN and never win.
+template <int D, int NV>
+__device__ __forceinline__ void scan_list(const float4* rows, uint32_t L, const float (&x)[4][D], float (&bd)[4], uint32_t (&bp)[4],
+                                          unsigned long long& ties)
+{
+    static_assert(D == 4, "one 16-byte row per centroid");
+    for (uint32_t e = 0; e < L; e += 2) {
+        float c[2][D];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float4 t = rows[e + u];
+            c[u][0] = t.x; c[u][1] = t.y; c[u][2] = t.z; c[u][3] = t.w;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const float d = direct_sqdist<D>(x[v], c[u]);
+                ties |= __ballot(d == bd[v]);
+                if (d < bd[v]) {
+                    bd[v] = d;
+                    bp[v] = e + u;
+                }
+            }
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
+{
+    constexpr int D = 4;
+    using L = Lists<D>;
+    __shared__ float4 rows_all[kWaves][L::kCap + 2];
+    __shared__ uint32_t ids_all[kWaves][L::kCap + 2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t c, first, n;
+    CellHead head;
+    if (!near_item(a, blockIdx.x * kWaves + wave, kCellItem, false, c, head, first, n)) return;  // wave-uniform; no barriers below
+    float4* rows = rows_all[wave];
+    uint32_t* ids = ids_all[wave];
+    // lists are complete unless they ran out of room
+    const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1;
+    const float R = usable ? head.r1 : -1.0f;
+    const uint32_t len = usable ? head.n1 : 0u;
+    const float qnan = __uint_as_float(0x7fc00000u);
+    for (uint32_t e = lane; e < len + 2; e += 64) {
+        float4 row = make_float4(qnan, qnan, qnan, qnan);
+        uint32_t id = 0;
+        if (e < len) {
+            const uint32_t pos = a.lists[size_t(c) * L::kCap + e];
+            row = reinterpret_cast<const float4*>(a.csorted)[pos];
+            id = a.cperm[pos];
+        }
+        rows[e] = row;
+        ids[e] = id;
+    }
+    float cc_row[D];
+    load_row<D>(a.C + size_t(c) * D, cc_row);
+    const uint32_t nv = (n + 63) / 64;
+    float x[4][D], bd[4];
+    uint32_t bp[4], hint[4];
+    bool near[4];
+    float tm = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const uint32_t o = v * 64 + lane;
+        const uint32_t p = first + min(o, n - 1);
+        load_row<D>(a.X + size_t(p) * D, x[v]);
+        hint[v] = a.idx[p];
+        float ch[D];
+        load_row<D>(a.C + size_t(min(hint[v], a.K - 1)) * D, ch);
+        const float t = cell_bound<D>(x[v], cc_row, ch);
+        near[v] = t <= R;
+        if (o < n) tm = __builtin_fmaxf(tm, t);
+        bd[v] = INFINITY;
+        bp[v] = 0;
+    }
+    for (int off = 32; off > 0; off >>= 1) tm = __builtin_fmaxf(tm, __shfl_xor(tm, off, 64));
+    if (lane == 0) atomicMax(&a.heads[c].tmax, __float_as_uint(tm));
+    unsigned long long ties = 0;
+    switch (nv) {
+        case 1: scan_list<D, 1>(rows, len, x, bd, bp, ties); break;
+        case 2: scan_list<D, 2>(rows, len, x, bd, bp, ties); break;
+        case 3: scan_list<D, 3>(rows, len, x, bd, bp, ties); break;
+        default: scan_list<D, 4>(rows, len, x, bd, bp, ties); break;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (uint32_t(v) >= nv) break;
+        const uint32_t o = v * 64 + lane, p = first + o;
+        const bool live = o < n;
+        uint32_t k = ids[bp[v]];
+        if (ties != 0) {  // some lane met an equal distance: among equals the lowest index wins
+            for (uint32_t e = 0; e < len; ++e) {
+                const float4 t = rows[e];
+                const float cr[D] = {t.x, t.y, t.z, t.w};
+                if (direct_sqdist<D>(x[v], cr) == bd[v]) k = min(k, ids[e]);
+            }
+        }
+        if (live && near[v]) {
+            a.idx[p] = k;
+            a.dmin[p] = bd[v];
+        }
+        if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
+        if (a.changed != nullptr) {
+            const bool moved = live && (!near[v] || k != hint[v]);
+            if (moved) a.prev_out[p] = hint[v];
+            or_bits(a.changed, first + v * 64, __ballot(moved), lane);
+        }
+    }
+}
+
+// ---- near vectors, d = 8: matrix cores over the list -----------------------------------------------------------------
+// A workgroup of W waves takes up to 64 W vectors of one cell (W = 8; 1 where the cells are small), each wave 64 of them. The
+// operands of the list's centroids (64 bytes each, one cache line) are laid out for v_mfma_f32_16x16x32_f16: 32 k slots hold
+// the 24 products of d = 8 and sigma ||c||^2, so that scores need no accumulator to start from. With several waves they go
+// through LDS, a wave of its own gathers them straight into registers. Four tiles of 16 centroids are folded two and two row
+// by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
+// instructions per 1024 scores. The winner is then known up to 2 centroids: two direct-form distances. What the tag costs
+// in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction was
+// measured at 5.7 x 2^-24 of the sum of its terms; 16 is assumed); a vector whose second best comes within the band is
+// decided in direct form over the list, 64 centroids at a time.
+// Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
+// Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
+// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 1.9 ms + 2.7 ms per E-step, N = 2.8 M: 0.26 ms +
+// 0.16 ms, where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
+// list, operands, scores, rows), so a wave works alone and keeps 64 vectors at four waves per SIMD: workgroups that shared
+// the list through LDS, 128 vectors per wave, took 6.1 to 7.8 ms for the same.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kVT = 4;                    // tiles of 16 vectors per wave
+constexpr uint32_t kSetVectors = 16 * kVT;
+constexpr uint32_t kGroup = 64;           // list entries folded together: 4 tiles of 16
+constexpr uint32_t kTag = 31;
+
+struct Scores {
+    float best[kVT], second[kVT];
+    uint32_t grp[kVT];
+};
+
+__device__ __forceinline__ void clear_scores(Scores& s)
+{
+#pragma unroll
+    for (int vt = 0; vt < kVT; ++vt) {
+        s.best[vt] = INFINITY;
+        s.second[vt] = INFINITY;
+        s.grp[vt] = 0;
+    }
+}
+
+// One running best / second best: `w` into (best, second)
+__device__ __forceinline__ void take_score(float& best, float& second, float w)
+{
+    second = __builtin_amdgcn_fmed3f(best, second, w);
+    asm("v_min_f32 %0, %1, %2" : "=v"(best) : "v"(best), "v"(w));
+}
+
+// The lane's part of a vector's operand: k slots 8 g .. 8 g + 7 (g = 0 .. 2: the products with parts 0 .. 2 of the centroids'
+// components; g = 3: the multipliers of the norm's parts)
+__device__ __forceinline__ f16x8 near_operand(const float (&x)[8], int g)
+{
+    f16x8 b;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const _Float16 fixed = j == 0 ? _Float16(256.0f) : (j == 1 ? _Float16(0.125f) : (j == 2 ? _Float16(6.103515625e-05f) : _Float16(0.0f)));
+        b[j] = g < 3 ? _Float16(-2.0f * x[j]) : fixed;
+    }
+    return b;
+}
+
+// LOW: the operands' lower parts (64 lanes apart) are added first.
+template <int NVT, bool LOW>
+__device__ __forceinline__ void score_group(const f16x8 (&a)[4], const f16x8 (&b)[kVT], const f16x8* low, uint32_t row0, uint32_t group, float minus_inf,
+                                            Scores& s)
+{
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int vt = 0; vt < NVT; ++vt) {
+        f32x4 r[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            r[t] = zero;
+            if constexpr (LOW) r[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[t], low[vt * 64], zero, 0, 0, 0);
+            r[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[t], b[vt], r[t], 0, 0, 0);
+        }
+        const float before = s.best[vt];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // median with -inf = minimum of two: fminf on fresh matrix results costs two more instructions to quiet them
+            const uint32_t lo = __float_as_uint(__builtin_amdgcn_fmed3f(r[0][i], r[1][i], minus_inf));
+            const uint32_t hi = __float_as_uint(__builtin_amdgcn_fmed3f(r[2][i], r[3][i], minus_inf));
+            take_score(s.best[vt], s.second[vt], __uint_as_float((lo & ~kTag) | (row0 + i)));
+            take_score(s.best[vt], s.second[vt], __uint_as_float((hi & ~kTag) | (row0 + i + 16)));
+        }
+        s.grp[vt] = s.best[vt] < before ? group : s.grp[vt];
+    }
+}
+
+template <bool MID>
+__global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
+{
+    constexpr int D = 8;
+    using L = Lists<D>;
+    const int lane = threadIdx.x & 63, g = lane >> 4, n16 = lane & 15;
+    uint32_t c, first, n;   // MID: `first` is where the positions of the vectors are listed
+    CellHead head;
+    if (!near_item(a, blockIdx.x * kWaves + (threadIdx.x >> 6), kSetVectors, MID, c, head, first, n)) return;  // wave-uniform
+    // lists are complete unless they ran out of room
+    const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
+    const bool whole = usable && head.n2 <= L::kCap2;
+    const float r1 = usable ? head.r1 : -1.0f, r2 = whole ? fmaxf(head.r1, head.r2) : r1;
+    const uint32_t len1 = usable ? head.n1 : 0u, len = MID && whole ? head.n1 + head.n2 : len1;
+    const uint16_t* list = a.lists + size_t(c) * L::kCap;
+    auto entry = [&](uint32_t e) { return uint32_t(list[!MID || e < len1 ? e : L::kCap1 + (e - len1)]); };
+    const uint32_t cmax_bits = a.hdr->cmax_bits;
+    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(cmax_bits, D));
+    const float sigma_cmax = sigma * __uint_as_float(cmax_bits);
+    float minus_inf;   // out of the compiler's sight, which would turn a median with it back into fminf
+    asm("s_mov_b32 %0, 0xff800000" : "=s"(minus_inf));
+    const uint32_t row0 = 4 * g;
+    const bool f16 = a.hdr->x_not_f16 == 0;
+    __shared__ f16x8 lows[kWaves][kVT * 64];   // other inputs: what a vector's operand has below its fp16 part
+    f16x8* low = lows[threadIdx.x >> 6];
+    f16x8 b[kVT];
+    Scores s;
+    clear_scores(s);
+
+    // ---- the vectors: operands, bounds and previous codes (one vector per lane)
+    const bool on = uint32_t(lane) < n;
+    auto position = [&](uint32_t v) { return MID ? a.mids[first + v] : first + v; };
+    const uint32_t p = position(min(uint32_t(lane), n - 1));
+    float x[D];
+    load_row<D>(a.X + size_t(p) * D, x);
+    const uint32_t hint = a.idx[p];
+#pragma unroll
+    for (int vt = 0; vt < kVT; ++vt) {
+        float xo[D];
+        load_row<D>(a.X + size_t(position(min(uint32_t(vt * 16 + n16), n - 1))) * D, xo);
+        b[vt] = near_operand(xo, g);
+        if (!f16) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) xo[j] -= float(_Float16(xo[j]));
+            f16x8 lo = near_operand(xo, g);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) lo[j] = g < 3 ? lo[j] : _Float16(0.0f);
+            low[vt * 64 + lane] = lo;
+        }
+    }
+    bool decided = on;
+    if constexpr (!MID) {
+        float row[D], ch[D];
+        load_row<D>(a.C + size_t(c) * D, row);
+        load_row<D>(a.C + size_t(min(hint, a.K - 1)) * D, ch);
+        const float t = cell_bound<D>(x, row, ch);
+        decided = on && t <= r1;
+        const bool mid = on && !decided && t <= r2, far = on && !decided && !mid;
+        float tm = on ? t : 0.0f;
+        for (int off = 32; off > 0; off >>= 1) tm = __builtin_fmaxf(tm, __shfl_xor(tm, off, 64));
+        if (lane == 0) atomicMax(&a.heads[c].tmax, __float_as_uint(tm));
+        const unsigned long long queued = __ballot(mid);
+        if (queued != 0) {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&a.heads[c].mids, uint32_t(__popcll(queued)));
+            at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
+            if (mid) a.mids[head.start + __builtin_amdgcn_mbcnt_hi(uint32_t(queued >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(queued), at))] = p;
+        }
+        if (far) or_bit(a.far_bits, a.rank[p]);
+        if (a.changed != nullptr) {
+            if (far) a.prev_out[p] = hint;
+            or_bits(a.changed, first, __ballot(far), lane);
+        }
+        if (!__any(decided)) return;
+    }
+    // ---- scores: 64 list entries at a time, the operands of a group gathered while the one before it is scored, its list
+    // entries one group earlier; past the end, the operand that never wins
+    {
+        const uint32_t groups = (len + kGroup - 1) / kGroup, tiles = (n + 15) / 16;
+        uint32_t pos[4];
+        f16x8 av[4];
+        auto positions = [&](uint32_t gr) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t e = gr * kGroup + 16 * t + n16;
+                pos[t] = e < len ? entry(e) : a.K;
+            }
+        };
+        auto gather = [&](f16x8 (&to)[4]) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) to[t] = *reinterpret_cast<const f16x8*>(a.flat + size_t(pos[t]) * 64 + g * 16);
+        };
+        positions(0);
+        gather(av);
+        positions(1);
+        for (uint32_t gr = 0; gr < groups; ++gr) {
+            f16x8 an[4];
+            gather(an);
+            positions(gr + 2);
+            if (!f16) score_group<4, true>(av, b, low + lane, row0, gr, minus_inf, s);
+            else if (tiles <= 2) score_group<2, false>(av, b, low, row0, gr, minus_inf, s);
+            else score_group<4, false>(av, b, low, row0, gr, minus_inf, s);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) av[t] = an[t];
+        }
+    }
+    // ---- best, second best and group over the four lanes that share a vector; lane (n16, g) takes vector n16 of tile g
+    float best = 0.0f, second = 0.0f;
+    uint32_t grp = 0;
+#pragma unroll
+    for (int t = 0; t < kVT; ++t) {
+        float tb = s.best[t], ts = s.second[t];
+        uint32_t tg = s.grp[t];
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            const float ob = __shfl_xor(tb, off, 64), os = __shfl_xor(ts, off, 64);
+            const uint32_t og = uint32_t(__shfl_xor(int(tg), off, 64));
+            ts = __builtin_fminf(__builtin_fminf(ts, os), __builtin_fmaxf(tb, ob));
+            tg = ob < tb ? og : tg;   // scores of different lanes differ in their row number
+            tb = __builtin_fminf(tb, ob);
+        }
+        best = g == t ? tb : best;
+        second = g == t ? ts : second;
+        grp = g == t ? tg : grp;
+    }
+    // ---- the decision
+    const uint32_t tag = __float_as_uint(best) & kTag, e0 = grp * kGroup + (tag & 15u) + 2 * (tag & 16u);
+    const uint32_t p0 = entry(min(e0, len - 1)), p1 = entry(min(e0 + 16, len - 1));
+    float c0[D], c1[D];
+    load_row<D>(a.csorted + size_t(p0) * D, c0);
+    load_row<D>(a.csorted + size_t(p1) * D, c1);
+    const float d0 = direct_sqdist<D>(x, c0), d1 = direct_sqdist<D>(x, c1);
+    float d = __builtin_fminf(d0, d1);
+    uint32_t k = a.cperm[d0 <= d1 ? p0 : p1];
+    if (d0 == d1) k = min(k, a.cperm[p1]);
+    float xn = 0.0f;
+#pragma unroll
+    for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
+    float delta = f16_guard_band<D, 3, true, 16>(x, d, sigma, sigma_cmax) +
+                        3.814697265625e-06f * (__builtin_fabsf(best) + __builtin_fabsf(second));   // the tags: 2^-18
+    if (!f16) delta += 16.0f * sigma_cmax * (2.384185791015625e-07f * __builtin_sqrtf(xn) + 1.6e-07f);   // what x has beyond 22 bits
+    unsigned long long todo = __ballot(decided && !((second - best) > delta));
+    while (todo != 0) {  // direct form over the whole list, one vector at a time
+        const int src = __ffsll(static_cast<long long>(todo)) - 1;
+        todo &= todo - 1;
+        float y[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) y[j] = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(x[j])), src)));
+        unsigned long long key = ~0ull;
+#pragma unroll 4
+        for (uint32_t le = lane; le < len; le += 64) {
+            const uint32_t pos = entry(le);
+            float c2[D];
+            load_row<D>(a.csorted + size_t(pos) * D, c2);
+            const unsigned long long v =
+                (static_cast<unsigned long long>(__float_as_uint(direct_sqdist<D>(y, c2))) << 32) | a.cperm[pos];
+            key = v < key ? v : key;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long v = __shfl_xor(key, off, 64);
+            key = v < key ? v : key;
+        }
+        if (lane == src) {
+            k = uint32_t(key & 0xffffffffull);
+            d = __uint_as_float(uint32_t(key >> 32));
+        }
+    }
+    if (decided) {
+        a.idx[p] = k;
+        a.dmin[p] = d;
+    }
+    if (a.changed != nullptr) {
+        const bool moved = decided && k != hint;
+        if (moved) a.prev_out[p] = hint;
+        if constexpr (MID) {
+            if (moved) or_bit(a.changed, p);
+        } else {
+            or_bits(a.changed, first, __ballot(moved), lane);
+        }
+    }
+}
+
+// ---- far vectors ------------------------------------------------------------------------------------------------------
+// The flagged ranks, in order within a block of 8192 of them, to a dense list with their rows and previous codes; clears
+// the flags. Where a block's share lies in the list depends on scheduling, the results do not.
+template <int D>
+__global__ __launch_bounds__(kThreads) void far_compact_kernel(uint32_t* __restrict__ far_bits, uint32_t words,
+                                                               const uint32_t* __restrict__ position, const float* __restrict__ X,
+                                                               const uint32_t* __restrict__ idx, WsHeader* hdr,
+                                                               uint32_t* __restrict__ far_pos, float* __restrict__ far_x,
+                                                               uint32_t* __restrict__ far_idx)
+{
+    constexpr uint32_t kWords = 1;  // per thread
+    __shared__ uint16_t offsets[kThreads * kWords * 32];
+    __shared__ uint32_t wave_sum[kWaves];
+    __shared__ uint32_t base;
+    const uint32_t w0 = (blockIdx.x * kThreads + threadIdx.x) * kWords;
+    uint32_t word[kWords], cnt = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWords; ++w) {
+        word[w] = w0 + w < words ? far_bits[w0 + w] : 0u;
+        if (word[w]) far_bits[w0 + w] = 0u;
+        cnt += __popc(word[w]);
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = uint32_t(__shfl_up(int(incl), off, 64));
+        if (lane >= off) incl += t;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t total = 0, at = incl - cnt;
+    for (int w = 0; w < kWaves; ++w) {
+        if (w < wave) at += wave_sum[w];
+        total += wave_sum[w];
+    }
+    if (threadIdx.x == 0) base = total ? atomicAdd(&hdr->far_count, total) : 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < kWords; ++w)
+        for (uint32_t bits = word[w]; bits != 0; bits &= bits - 1)
+            offsets[at++] = uint16_t((threadIdx.x * kWords + w) * 32 + uint32_t(__ffs(int(bits)) - 1));
+    __syncthreads();
+    const uint32_t rank0 = blockIdx.x * (kThreads * kWords * 32), b0 = base;
+    for (uint32_t e = threadIdx.x; e < total; e += kThreads) {  // dealt out evenly
+        const uint32_t p = position[rank0 + offsets[e]], to = b0 + e;
+        far_pos[to] = p;
+        far_idx[to] = idx[p];
+#pragma unroll
+        for (int q = 0; q < D / 4; ++q)
+            reinterpret_cast<float4*>(far_x + size_t(to) * D)[q] = reinterpret_cast<const float4*>(X + size_t(p) * D)[q];
+    }
+}
+
+// The far vectors' windowed E-step: 128 vectors (a quarter of a window tile) per workgroup, whose 16 waves take turns at
+// the window's tiles and load operands straight from the packed codebook. The kernel of assign_mfma_f16.hip gives 512
+// vectors to 4 waves and shares every tile through LDS: better with many vectors, but the far ones are outliers, few, with
+// windows that span much of the codebook, and left most of the chip without work (110 workgroups for 0.5 % of 11 M
+// vectors: 540 us, with 4 waves on 128 vectors 176 us).
+constexpr int kFarWaves = 16, kFarVT = 4;
+constexpr uint32_t kFarSet = 32 * kFarVT;
+template <int D>
+__global__ __launch_bounds__(64 * kFarWaves) void far_kernel(const float* __restrict__ X, const float* __restrict__ rows,
+                                                           const uint32_t* __restrict__ cperm, uint32_t K,
+                                                           const char* __restrict__ packed, const uint2* __restrict__ windows,
+                                                           const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx,
+                                                           float* __restrict__ dmin, WsHeader* hdr, uint32_t* __restrict__ refine_list)
+{
+    using S = F16Shape<D>;
+    constexpr int GT = 2;
+    __shared__ float x_best[kFarWaves][kFarVT][64], x_second[kFarWaves][kFarVT][64];
+    __shared__ uint32_t x_grp[kFarWaves][kFarVT][64];
+    const uint32_t N = hdr->far_count;
+    if (hdr->x_not_f16 != 0) return;
+    const uint32_t sets = (N + kFarSet - 1) / kFarSet;
+    for (uint32_t set = blockIdx.x; set < sets; set += gridDim.x) {
+    const uint32_t i0 = (sets - 1 - set) * kFarSet;  // the widest windows first
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
+    f16x8 b[kFarVT][1];
+#pragma unroll
+    for (int vt = 0; vt < kFarVT; ++vt) {
+        float x[D];
+        load_row<D>(X + size_t(min(i0 + vt * 32 + n, N - 1)) * D, x);
+        vector_operand<D>(x, h, b[vt]);
+    }
+    float best_of[kFarVT], second_of[kFarVT];
+    uint32_t grp_of[kFarVT];
+#pragma unroll
+    for (int vt = 0; vt < kFarVT; ++vt) {
+        best_of[vt] = second_of[vt] = INFINITY;
+        grp_of[vt] = 0;
+    }
+    const uint2* wl = windows + size_t(i0 / kWinTile) * kWinStride;
+    const uint32_t nruns = wl[0].x;
+    uint2 my_run = make_uint2(0u, 0u);
+    if (uint32_t(lane) < nruns) my_run = wl[1 + lane];
+    for (uint32_t r = 0; r < nruns; ++r) {
+        const uint32_t t0 = uint32_t(__builtin_amdgcn_readlane(int(my_run.x), int(r)));
+        const uint32_t t1 = uint32_t(__builtin_amdgcn_readlane(int(my_run.y), int(r)));
+        uint32_t g = t0 / GT + wave;
+        f16x8 a[GT];
+#pragma unroll
+        for (int u = 0; u < GT; ++u)
+            a[u] = *reinterpret_cast<const f16x8*>(packed + size_t(min(g * GT + u, t1 - 1)) * S::kTileBytes + lane * 16);
+        for (; g * GT < t1; g += kFarWaves) {
+            f16x8 an[GT];
+#pragma unroll
+            for (int u = 0; u < GT; ++u)
+                an[u] = *reinterpret_cast<const f16x8*>(packed + size_t(min((g + kFarWaves) * GT + u, t1 - 1)) * S::kTileBytes + lane * 16);
+            float m[kFarVT];
+#pragma unroll
+            for (int vt = 0; vt < kFarVT; ++vt) m[vt] = INFINITY;
+#pragma unroll
+            for (int u = 0; u < GT; ++u) {
+                const uint32_t t = g * GT + u;
+                if (t < t0 || t >= t1) continue;  // wave-uniform: outside the run
+                f32x16 cn;
+                if constexpr (S::kNormInK) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) cn[q] = 0.0f;
+                } else {
+                    const char* T = packed + size_t(t) * S::kTileBytes + 1024 + 64 * h;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 v = *reinterpret_cast<const float4*>(T + 16 * q);
+                        cn[4 * q] = v.x; cn[4 * q + 1] = v.y; cn[4 * q + 2] = v.z; cn[4 * q + 3] = v.w;
+                    }
+                }
+#pragma unroll
+                for (int vt = 0; vt < kFarVT; ++vt) {
+                    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b[vt][0], cn, 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) m[vt] = __builtin_fminf(__builtin_fminf(m[vt], acc[2 * q]), acc[2 * q + 1]);
+                }
+            }
+#pragma unroll
+            for (int vt = 0; vt < kFarVT; ++vt) {
+                grp_of[vt] = m[vt] < best_of[vt] ? g : grp_of[vt];
+                take_score(best_of[vt], second_of[vt], m[vt]);
+            }
+#pragma unroll
+            for (int u = 0; u < GT; ++u) a[u] = an[u];
+        }
+    }
+#pragma unroll
+    for (int vt = 0; vt < kFarVT; ++vt) {
+        x_best[wave][vt][lane] = best_of[vt];
+        x_second[wave][vt][lane] = second_of[vt];
+        x_grp[wave][vt][lane] = grp_of[vt];
+    }
+    __syncthreads();
+    if (wave < kFarVT) {  // wave w finishes tile w: index recovery and guard band as in assign_mfma_f16.hip
+    float best = INFINITY, second = INFINITY;
+    uint32_t grp = 0;
+#pragma unroll
+    for (int w = 0; w < kFarWaves; ++w) {
+        const float ob = x_best[w][wave][lane], os = x_second[w][wave][lane];
+        if (ob < best) grp = x_grp[w][wave][lane];
+        second = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
+        best = __builtin_fminf(best, ob);
+    }
+    const uint32_t i_raw = i0 + wave * 32 + n, i = min(i_raw, N - 1);
+    float x[D];
+    load_row<D>(X + size_t(i) * D, x);
+    const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
+    const uint32_t og = uint32_t(__shfl_xor(int(grp), 32, 64));
+    const bool mine = best < ob || (best == ob && h == 0);
+    const float bstar = __builtin_fminf(best, ob);
+    const float sstar = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
+    float bd;
+    uint32_t bk;
+    recover_group<D, GT>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
+    const float od = __shfl_xor(bd, 32, 64);
+    const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
+    const bool take = od < bd || (od == bd && ok < bk);
+    const float dstar = take ? od : bd;
+    const uint32_t cmax_bits = hdr->cmax_bits;
+    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(cmax_bits, D));
+    const bool safe = (sstar - bstar) > f16_guard_band<D>(x, dstar, sigma, sigma * __uint_as_float(cmax_bits));
+    if (h == 0 && i_raw < N) {
+        const uint32_t p = far_pos[i];
+        idx[p] = take ? ok : bk;
+        dmin[p] = dstar;
+        if (!safe) refine_list[atomicAdd(&hdr->refine_count, 1u)] = i;
+    }
+    }
+    __syncthreads();  // the exchange buffers have been read
+    }
+}
+
+uint32_t item_of(uint32_t d) { return d == 4 ? kCellItem : kSetVectors; }
+
+template <int D>
+hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K, Workspace& w, bool first, float factor, hipStream_t s)
+{
+    const dim3 per_vector((N + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL(cell_keys_kernel, per_vector, dim3(kThreads), 0, s, w.idx_sorted, N, w.vkeys, w.cell_order);
+    if (hipError_t e = launch_sort_u16(w.vkeys, w.cell_order, w.vkeys_tmp, w.vperm_tmp, N, w.sort_hist, s); e != hipSuccess) return e;
+    hipLaunchKernelGGL(cell_apply_kernel, per_vector, dim3(kThreads), 0, s, w.vkeys, N, w.cell_order, first ? nullptr : w.cell_rank,
+                       w.vperm, w.vperm_tmp, w.cell_position, w.idx_sorted);
+    std::swap(w.vperm, w.vperm_tmp);
+    std::swap(w.cell_rank, w.cell_order);
+    if (hipError_t e = launch_gather_rows(X, w.vperm, N, D, w.xsorted, s); e != hipSuccess) return e;
+    hipLaunchKernelGGL(cell_starts_kernel, dim3((K + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.vkeys, N, K, w.cell_heads);
+    const uint32_t item = item_of(D), slots = N / item + K;
+    hipLaunchKernelGGL(cell_items_kernel, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.cell_heads, K, slots, item, w.cell_items);
+    if (first) {
+        const float wider = D == 4 ? 1.0f : 1.28f;   // (kTarget2 / kTarget1)^(1/8)
+        hipLaunchKernelGGL(cell_first_radius_kernel<D>, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.xsorted, w.idx_sorted,
+                           w.cell_heads, C, K, factor, factor * wider);
+        if (hipError_t e = launch_fill_u32(w.far_bits, (N + 31) / 32, 0u, s); e != hipSuccess) return e;
+        if (hipError_t e = launch_fill_u32(w.cell_hist, 65536, 0u, s); e != hipSuccess) return e;
+    }
+    return hipGetLastError();
+}
+
+template <int D>
+void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool first, hipStream_t s)
+{
+    const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32;
+    hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
+                       words, first ? 1 : 0, w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.hdr);
+    hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
+    hipLaunchKernelGGL(cell_place_kernel<D>, dim3((tiles * 32 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, tiles * 32, w.ckeys,
+                       w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
+    hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(kThreads), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
+                       w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist);
+}
+
+template <int D>
+void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, hipStream_t s)
+{
+    const uint32_t words = (N + 31) / 32, slots = N / item_of(D) + K;
+    const FarView f = far_view(w, N, D);
+    const NearArgs a{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, slots,
+                     w.cell_lists, w.cell_rank, w.far_bits, f.pos, w.idx_sorted, w.dmin,
+                     track ? w.idx_prev : nullptr, track ? w.changed : nullptr, w.hdr};
+    const dim3 grid((slots + kWaves - 1) / kWaves);
+    if constexpr (D == 4) {
+        hipLaunchKernelGGL(near_direct_kernel, grid, dim3(kThreads), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(near_mfma_kernel<false>, grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(near_mfma_kernel<true>, grid, dim3(kThreads), 0, s, a);
+    }
+    hipLaunchKernelGGL(far_compact_kernel<D>, dim3((words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.far_bits, words,
+                       w.cell_position, w.xsorted, w.idx_sorted, w.hdr, f.pos, f.x, f.idx);
+}
+
+template <int D>
+void cells_far_t(uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
+{
+    const FarView f = far_view(w, N, D);
+    const uint32_t sets = (N + kFarSet - 1) / kFarSet;
+    hipLaunchKernelGGL(far_kernel<D>, dim3(std::min(sets, 4096u)), dim3(64 * kFarWaves), 0, s, f.x, w.csorted, w.cperm, K,
+                       reinterpret_cast<const char*>(w.packed), w.windows, f.pos, w.idx_sorted, w.dmin, w.hdr, f.refine);
+}
+
+}  // namespace
+
+hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
+                              bool first, hipStream_t s)
+{
+    // first radius over mean t: n(R) grows like R^d from about 10 (d = 4) or 150 (d = 8) centroids at the mean
+    const float factor = d_caller <= 4 ? 1.45f : (d_caller <= 6 ? 1.25f : 1.13f);
+    switch (d) {
+        case 4: return cells_order_t<4>(X, C, N, K, w, first, factor, s);
+        case 8: return cells_order_t<8>(X, C, N, K, w, first, factor, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool first, hipStream_t s)
+{
+    switch (d) {
+        case 4: cells_centroids_t<4>(C, N, K, w, first, s); break;
+        case 8: cells_centroids_t<8>(C, N, K, w, first, s); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s)
+{
+    switch (d) {
+        case 4: cells_near_t<4>(C, N, K, w, track, s); break;
+        case 8: cells_near_t<8>(C, N, K, w, track, s); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
+{
+    switch (d) {
+        case 4: cells_far_t<4>(N, K, w, s); break;
+        case 8: cells_far_t<8>(N, K, w, s); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace cc

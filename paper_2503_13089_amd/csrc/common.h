@@ -12,6 +12,25 @@ namespace cc {
 size_t sort_hist_bytes(uint64_t n);
 // per-workgroup cluster sums of a small problem (small_fit.hip); 0 where that form is not used
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K);
+// E-step by cells (cells.hip): room for the entries of a cell's list
+uint32_t cell_list_cap(uint32_t d);
+constexpr uint32_t kCellItem = 256;       // vectors of one wave (d = 4)
+struct CellHead {
+    uint32_t start, members;   // the cell's vectors
+    uint32_t n1, n2;           // list entries within r1, between r1 and r2 (more than there is room for: not all stored)
+    float r1, r2;
+    uint32_t tmax;             // largest t(x) of the last E-step, fp32 bits
+    uint32_t mids;             // d = 8: vectors of the cell between r1 and r2
+};
+// Whether a fit of this shape runs its E-steps by cells (d as padded; codes of 16 bits; the bounds do not prune at
+// d = 16). The line lies where grouping, lists and the extra launches pay: against windows alone, d = 4: 0.90 x the speed at
+// (N, K) = (2 M, 65536), 0.98 at (2 M, 4096), 1.00 at (4 M, 1024), 1.2 at (4 M, 4096), 0.89 at (4 M, 65536, 5 iterations), 1.3 at (11 M, 65536), 0.88 at
+// (16 M, 300); d = 8: 0.93 at (1 M, 32768), 1.03 at (2 M, 4096), 1.16 at (2 M, 16384), 1.0 at (16 M, 300), 3.7 at
+// (29 M, 65536).
+inline bool cells_possible(uint64_t N, uint32_t d, uint32_t K)
+{
+    return d <= 8 && K >= 1024 && K <= 65536 && N >= (d == 4 ? 128ull : 32ull) * K && N >= (d == 4 ? 1u << 22 : 1u << 21) && N < (1ull << 31);
+}
 
 constexpr uint32_t kMaxK = 1u << 24;
 
@@ -45,6 +64,7 @@ struct WsHeader {
     unsigned long long window_total;    // what that sum would be without pruning
     int32_t fixed_point_exp;
     uint32_t x_nonfinite;      // != 0: some input is Inf or NaN (the sums then skip such components)
+    uint32_t far_count;        // E-step by cells: vectors that go through the windowed pass
 };
 
 // Survives between calls on the same workspace (not touched by the per-call header reset): whether the
@@ -95,6 +115,18 @@ struct Workspace {
     uint32_t* bucket_gtot;     // [groups of kBucketGroup blocks][buckets]
     uint32_t* bucket_base;     // [buckets + 1] first record of each bucket
     bool bucket_ok;
+    // E-step by cells
+    uint32_t* cell_order;      // [N]    scratch of the grouping
+    uint32_t* cell_rank;       // [N]    norm rank of the vector at each position
+    uint32_t* cell_position;   // [N]    inverse of cell_rank
+    uint32_t* far_bits;        // [ceil(N/32)] by norm rank
+    CellHead* cell_heads;      // [K]
+    uint32_t* cell_hist;       // [65536] centroids per ordering key; zero between E-steps
+    uint32_t* cell_cursor;     // [65536] next position of each key
+    char* cell_flat;           // [K + 1] x 64 bytes: operand pieces of each ordered centroid (d = 8)
+    char* cell_operands;       // one matrix-core operand per 32 ordered centroids, for the lists
+    uint32_t* cell_items;      // [N / 64 + K] cell of each work item
+    uint16_t* cell_lists;      // [K][cap] positions in the norm order of the centroids
     char* small_partials;      // small problems: one set of cluster sums per workgroup
     uint32_t refine_cap;
     uint32_t partial_slots;
@@ -179,6 +211,19 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
         w.bucket_gtot = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk / kBucketGroup + 1) * 4));
         w.bucket_base = reinterpret_cast<uint32_t*>(take((buckets + 1) * 4));
     }
+    if (cells_possible(N, d, K)) {
+        w.cell_order = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+        w.cell_rank = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+        w.cell_position = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+        w.far_bits = reinterpret_cast<uint32_t*>(take((size_t(N) / 32 + 1) * 4));
+        w.cell_heads = reinterpret_cast<CellHead*>(take(size_t(K) * sizeof(CellHead)));
+        w.cell_hist = reinterpret_cast<uint32_t*>(take(65536 * 4));
+        w.cell_cursor = reinterpret_cast<uint32_t*>(take(65536 * 4));
+        w.cell_operands = take((size_t(K) + 31) / 32 * 1024);
+        w.cell_flat = take((size_t(K) + 1) * 64);
+        w.cell_items = reinterpret_cast<uint32_t*>(take((size_t(N) / 64 + K) * 4));
+        w.cell_lists = reinterpret_cast<uint16_t*>(take(size_t(K) * cell_list_cap(d) * 2));
+    }
     w.small_partials = take(small_partials_bytes(N, d, K));
     w.bytes = off;
     return w;
@@ -224,6 +269,8 @@ struct EStep {
     uint32_t* prev_out;         // with `changed`: where the code that idx held before goes, for every vector flagged there
     uint32_t* changed;          // NULL, or one bit per vector, set where the code differs from what idx held or is not final yet
     int gate;
+    const uint32_t* n_dev;      // NULL, or where the device keeps the number of vectors, at most N (fp32 variant)
+    const uint32_t* out_pos;    // NULL, or the position of each vector in idx and the distances (fp32 variant)
     Profile* profile;           // NULL, or where the scoring kernel's device time is recorded
 };
 
@@ -249,9 +296,41 @@ hipError_t launch_small_assign(const float* X, uint32_t N, uint32_t d, const flo
 hipError_t launch_sort_vectors(const float* X, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool drop_hint,
                                hipStream_t s);
 hipError_t launch_sort_centroids(const float* C, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
+// n_dev: NULL, or where the device keeps the number of vectors (at most N)
 hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
-                          hipStream_t s);
-hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, hipStream_t s);
+                          hipStream_t s, const uint32_t* n_dev = nullptr);
+hipError_t launch_gather_rows(const float* in, const uint32_t* ids, uint32_t n, uint32_t d, float* out, hipStream_t s);
+// norm_order: the codes lie in the norm order, i.e. are a hint for the next call
+hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool norm_order, hipStream_t s);
+
+// E-step by cells inside a fit (cells.hip), after a first E-step in the norm order. launch_cells_order groups the
+// vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order); launch_cells_centroids
+// orders the current centroids and makes their operands and the lists of the cells; launch_cells_near decides the near
+// vectors and leaves the far ones as a list of hdr->far_count entries in the arrays of far_view; launch_cells_far
+// decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
+hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
+                              bool first, hipStream_t s);
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool first, hipStream_t s);
+hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s);
+hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
+hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t value, hipStream_t s);
+struct FarView {
+    float* x;        // [N * d] rows
+    uint32_t* pos;   // [N]     positions
+    uint32_t* idx;   // [N]     previous codes
+    uint32_t* refine;  // [N]   those to be re-decided in direct form
+};
+inline FarView far_view(const Workspace& w, uint32_t N, uint32_t d)   // in the M-step's record buffer, free at that time
+{
+    FarView f;
+    char* p = w.records;
+    auto take = [&](size_t bytes) { char* q = p; p += align256(bytes); return q; };
+    f.x = reinterpret_cast<float*>(take(size_t(N) * d * 4));
+    f.pos = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+    f.idx = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+    f.refine = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
+    return f;
+}
 
 // Re-decides the listed guard-band vectors over all K centroids in direct form; if the list
 // overflowed, re-decides everything in direct form. With fix_sums = true the cluster sums/counts that
@@ -259,8 +338,10 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, hipSt
 // scratch on overflow).
 // With norm_ordered = true (X = w.xsorted, idx = w.idx_sorted) only each vector's window is searched and
 // the codes are flagged as a usable hint for the next call.
+// out_pos != NULL (norm_ordered only): where each of the listed vectors keeps its code and distance; the list then holds
+// everything there is to refine (w.refine_cap vectors at most exist).
 hipError_t launch_refine(const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx,
-                         const Workspace& w, bool fix_sums, bool norm_ordered, hipStream_t s);
+                         const Workspace& w, bool fix_sums, bool norm_ordered, hipStream_t s, const uint32_t* out_pos = nullptr);
 
 // Scans the inputs: max |x| and whether every x is exactly representable in fp16.
 hipError_t launch_scan_inputs(const float* X, uint64_t n_floats, WsHeader* hdr, hipStream_t s);
@@ -393,6 +474,16 @@ hipError_t launch_decode(const float* C, uint32_t K, uint32_t d, const uint32_t*
                          hipStream_t s);
 
 hipError_t launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s);
+
+// log2 of the centroid scale sigma: max|c| * sigma <= 2^15 and d * max|c|^2 * sigma <= 2^23
+__device__ __forceinline__ int centroid_scale_log2(uint32_t cmax_bits, int d)
+{
+    if (cmax_bits == 0) return 0;
+    const int ec = int(cmax_bits >> 23) - 127;  // max|c| < 2^(ec+1)
+    const int ld = 32 - __clz(uint32_t(d - 1)); // d <= 2^ld
+    int s = min(14 - ec, 21 - 2 * ec - ld);
+    return max(-100, min(100, s));
+}
 
 // Fixed-point exponent e of the cluster sums: inputs satisfy |x| < 2^(EM+1) with EM the unbiased
 // exponent of the largest magnitude M, and N < 2^LN, so |sum of N terms| < 2^(EM+1+e+LN) <= 2^62.

@@ -117,6 +117,18 @@ __global__ __launch_bounds__(kThreads) void copy_f32_kernel(const float* __restr
     if (i < n) dst[i] = src[i];
 }
 
+__global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* __restrict__ dst, size_t n, uint32_t value)
+{
+    const size_t i = size_t(blockIdx.x) * kThreads + threadIdx.x;
+    if (i < n) dst[i] = value;
+}
+
+hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t value, hipStream_t s)
+{
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, dst, n, value);
+    return hipGetLastError();
+}
+
 hipError_t launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(copy_f32_kernel, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, src, dst, n);

@@ -10,7 +10,8 @@ namespace cc {
 
 constexpr int kThreads = 256;
 
-// One wave per listed vector: the 64 lanes stride over the candidate range with coalesced row loads,
+// One workgroup per listed vector: its 256 lanes stride over the candidate range with coalesced row loads (a wave per
+// vector left the kernel waiting for the few vectors with the longest ranges: 87 us for 900 of them at K = 65536),
 // each keeps its best (distance, centroid index) as one 64-bit key (distance bits << 32 | index; distances
 // are non-negative, so the integer order is distance first, then the lower index), and a shuffle
 // reduction picks the minimum. The candidate range is the whole codebook, or - for a norm-ordered run -
@@ -22,7 +23,8 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
                                                           WsHeader* hdr, const uint32_t* __restrict__ refine_list,
                                                           uint32_t refine_cap, const uint2* __restrict__ windows,
                                                           uint32_t* __restrict__ idx, float* __restrict__ dmin,
-                                                          long long* sums, uint32_t* counts, WsPersist* persist)
+                                                          long long* sums, uint32_t* counts, WsPersist* persist,
+                                                          const uint32_t* __restrict__ out_pos)
 {
     const uint32_t count = hdr->refine_count;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -32,10 +34,10 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
         if (persist != nullptr) persist->hint_valid = 1;  // idx (norm-ordered) is a usable hint from now on
     }
     if (count > refine_cap) return;  // overflow is handled by the full direct pass
+    __shared__ unsigned long long red[kThreads / 64];
     const int lane = threadIdx.x & 63;
-    const uint32_t wave = (blockIdx.x * kThreads + threadIdx.x) >> 6, waves = gridDim.x * (kThreads / 64);
     const int fpe = fixed_point_exp(hdr->absmax_bits, N);
-    for (uint32_t e = wave; e < count; e += waves) {
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
         const uint32_t i = refine_list[e];
         float x[D];
         load_row<D>(X + size_t(i) * D, x);
@@ -54,12 +56,12 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
                 hi = min(kWinQuad * uint32_t(__builtin_amdgcn_readlane(int(my_run.y), int(r))), K);
             }
             constexpr int U = 4;  // independent row loads in flight per lane
-            for (uint32_t p0 = lo + lane; p0 < hi; p0 += U * 64) {
+            for (uint32_t p0 = lo + threadIdx.x; p0 < hi; p0 += U * kThreads) {
                 float c[U][D];
                 uint32_t k[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const uint32_t pos = min(p0 + u * 64, hi - 1);
+                    const uint32_t pos = min(p0 + u * kThreads, hi - 1);
                     load_row<D>(rows + size_t(pos) * D, c[u]);
                     k[u] = row_ids != nullptr ? row_ids[pos] : pos;
                 }
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
                 for (int u = 0; u < U; ++u) {
                     const unsigned long long v =
                         (static_cast<unsigned long long>(__float_as_uint(direct_sqdist<D>(x, c[u]))) << 32) | k[u];
-                    if (p0 + u * 64 < hi) best = v < best ? v : best;
+                    if (p0 + u * kThreads < hi) best = v < best ? v : best;
                 }
             }
         }
@@ -75,21 +77,27 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
             const unsigned long long o = __shfl_xor(best, off, 64);
             best = o < best ? o : best;
         }
-        if (lane == 0 && best != ~0ull) {
-            const uint32_t k_new = uint32_t(best & 0xffffffffull), k_old = idx[i];
+        __syncthreads();  // the last vector's exchange has been read
+        if (lane == 0) red[threadIdx.x >> 6] = best;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) best = red[w] < best ? red[w] : best;
+        if (threadIdx.x == 0 && best != ~0ull) {
+            const uint32_t k_new = uint32_t(best & 0xffffffffull), k_old = sums != nullptr ? idx[i] : 0u;
             if (sums != nullptr && k_new != k_old) {
                 // the scoring kernel already added this vector to its provisional cluster: move it
                 accumulate_vector<D>(x, k_old, sums, counts, fpe, -1);
                 accumulate_vector<D>(x, k_new, sums, counts, fpe, +1);
             }
-            idx[i] = k_new;
-            dmin[i] = __uint_as_float(uint32_t(best >> 32));
+            const uint32_t o = out_pos != nullptr ? out_pos[i] : i;
+            idx[o] = k_new;
+            dmin[o] = __uint_as_float(uint32_t(best >> 32));
         }
     }
 }
 
 hipError_t launch_refine(const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx,
-                         const Workspace& w, bool fix_sums, bool norm_ordered, hipStream_t s)
+                         const Workspace& w, bool fix_sums, bool norm_ordered, hipStream_t s, const uint32_t* out_pos)
 {
     const float* rows = norm_ordered ? w.csorted : C;
     const uint32_t* row_ids = norm_ordered ? w.cperm : nullptr;
@@ -99,11 +107,12 @@ hipError_t launch_refine(const float* X, uint32_t N, uint32_t d, const float* C,
     WsPersist* persist = norm_ordered ? w.persist : nullptr;
     const dim3 grid(2048), block(kThreads);
     switch (d) {
-        case 4: hipLaunchKernelGGL(refine_kernel<4>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist); break;
-        case 8: hipLaunchKernelGGL(refine_kernel<8>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist); break;
-        case 16: hipLaunchKernelGGL(refine_kernel<16>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist); break;
+        case 4: hipLaunchKernelGGL(refine_kernel<4>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist, out_pos); break;
+        case 8: hipLaunchKernelGGL(refine_kernel<8>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist, out_pos); break;
+        case 16: hipLaunchKernelGGL(refine_kernel<16>, grid, block, 0, s, X, N, rows, row_ids, K, w.hdr, w.refine_list, w.refine_cap, windows, idx, w.dmin, sums, counts, persist, out_pos); break;
         default: return hipErrorInvalidValue;
     }
+    if (out_pos != nullptr) return hipGetLastError();
     // overflow path: more guard-band vectors than the list holds -> decide everything in direct form
     // (and rebuild the cluster sums from those codes)
     hipError_t e = launch_assign_direct(X, N, d, C, K, idx, w.dmin, &w.hdr->refine_count, w.refine_cap, s);

@@ -20,54 +20,13 @@
 #include <algorithm>
 
 #include "common.h"
+#include "ordering.h"
 
 namespace cc {
 
 constexpr int kThreads = 256;
 constexpr int kSortThreads = 512;          // 8 waves
 constexpr uint32_t kSortChunk = 4096;      // elements per block and pass
-
-// 16-bit norm key: the top half of the fp32 pattern of a non-negative float (monotone, 2^-7 relative steps)
-__device__ __forceinline__ uint32_t norm_key(float norm) { return __float_as_uint(norm) >> 16; }
-
-// Shells: 4 norm keys each. `base` places shell 511 at the largest norm any vector can have; everything
-// 511 shells (16 octaves) or more below that shares shell 0, anything above shares shell 511.
-__device__ __forceinline__ uint32_t shell_base(uint32_t absmax_bits, int d)
-{
-    const float top = __uint_as_float(absmax_bits) * __builtin_sqrtf(float(d)) * 1.0001f;
-    const uint32_t tk = norm_key(top) >> 2;
-    return tk > 511u ? tk - 511u : 0u;
-}
-__device__ __forceinline__ uint32_t shell_of_key(uint32_t nkey, uint32_t base)
-{
-    const uint32_t s = nkey >> 2;
-    return s <= base ? 0u : min(s - base, 511u);
-}
-// every norm whose key falls in shell s lies in [shell_rlo, shell_rhi)
-__device__ __forceinline__ float shell_rlo(uint32_t s, uint32_t base)
-{
-    return s == 0 ? 0.0f : __uint_as_float(((s + base) << 2) << 16);
-}
-__device__ __forceinline__ float shell_rhi(uint32_t s, uint32_t base)
-{
-    return s >= 511u ? INFINITY : __uint_as_float(((s + base + 1) << 2) << 16);
-}
-__device__ __forceinline__ uint32_t cos_bucket(float t)
-{
-    const int q = int((t + 1.0f) * 64.0f);
-    return uint32_t(max(0, min(q, 127)));
-}
-// norm, projection on e = (1,..,1)/sqrt(d), and the ordering key of one row
-template <int D>
-__device__ __forceinline__ uint32_t ordering_key(const float (&x)[D], float norm, uint32_t base, float& proj)
-{
-    float sum = 0.0f;
-#pragma unroll
-    for (int j = 0; j < D; ++j) sum += x[j];
-    proj = sum * (D == 4 ? 0.5f : (D == 16 ? 0.25f : 0.35355339059327373f));
-    const float t = norm > 0.0f ? proj / norm : 0.0f;
-    return (shell_of_key(norm_key(norm), base) << 7) | cos_bucket(t);
-}
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void vector_keys_kernel(const float* __restrict__ X, uint32_t N,
@@ -235,8 +194,13 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
                                                           const float* __restrict__ C, uint32_t K,
                                                           const uint32_t* __restrict__ hint, const WsPersist* persist,
                                                           const uint32_t* __restrict__ ckey_starts, float guess,
-                                                          const WsHeader* __restrict__ hdr, uint2* __restrict__ win)
+                                                          const WsHeader* __restrict__ hdr, uint2* __restrict__ win,
+                                                          const uint32_t* __restrict__ n_dev, unsigned long long* stages)
 {
+    if (n_dev != nullptr) {
+        N = min(N, *n_dev);
+        if (blockIdx.x * kWinTile >= N) return;
+    }
     __shared__ float red[4][kThreads / 64];
     __shared__ uint2 runs[kWinSlots];
     const uint32_t quads = (K + kWinQuad - 1) / kWinQuad;
@@ -313,17 +277,7 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
             klo = smin << 7;
             khi = (smax << 7) | 127u;
         } else {
-            // cosine e.c/||c|| of a candidate in shell s: e.c in [plo, phi], ||c|| in [rlo, rhi); 1e-4 of slack for
-            // the two divisions (the centroid's own, when its key was made, and the one here: 1e-7 each)
-            const uint32_t sh = smin + threadIdx.x;
-            const float rlo = shell_rlo(sh, base), rhi = shell_rhi(sh, base);
-            float tlo, thi;
-            if (plo >= 0.0f) tlo = rhi < INFINITY ? plo / rhi : 0.0f; else tlo = rlo > 0.0f ? plo / rlo : -1.0f;
-            if (phi >= 0.0f) thi = rlo > 0.0f ? phi / rlo : 1.0f; else thi = rhi < INFINITY ? phi / rhi : 0.0f;
-            const uint32_t qa = cos_bucket(__builtin_fmaxf(tlo - 1e-4f, -1.0f));
-            const uint32_t qb = cos_bucket(__builtin_fminf(thi + 1e-4f, 1.0f));
-            klo = (sh << 7) | qa;
-            khi = (sh << 7) | qb;
+            shell_cosine_run(smin + threadIdx.x, base, plo, phi, klo, khi);
         }
         uint2 r = make_uint2(0, 0);
         if (klo <= khi) {
@@ -368,7 +322,10 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
     }
     __syncthreads();
     if (threadIdx.x < merged_n) out[1 + threadIdx.x] = merged[threadIdx.x];
-    if (threadIdx.x == 0) out[0] = make_uint2(merged_n, merged_total);
+    if (threadIdx.x == 0) {
+        out[0] = make_uint2(merged_n, merged_total);
+        if (n_dev != nullptr) atomicAdd(stages, static_cast<unsigned long long>(merged_total));  // statistics (few tiles)
+    }
 }
 
 // Sum of the window sizes of the last E-step (statistics only).
@@ -390,13 +347,14 @@ __global__ __launch_bounds__(1024) void window_stats_kernel(const uint2* __restr
     }
 }
 
-// Codes back to input order: idx[ids[p]] = idx_sorted[p]; also records that the sorted codes are a usable hint.
+// Codes back to input order: idx[ids[p]] = idx_sorted[p]; also records whether the codes left behind are a usable hint for
+// the next call (they are if they lie in the norm order).
 __global__ __launch_bounds__(kThreads) void unpermute_kernel(const uint32_t* __restrict__ idx_sorted,
                                                              const uint32_t* __restrict__ ids, uint32_t n,
-                                                             uint32_t* __restrict__ idx, WsPersist* persist)
+                                                             uint32_t* __restrict__ idx, WsPersist* persist, int hint)
 {
     const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
-    if (p == 0) persist->hint_valid = 1;
+    if (p == 0) persist->hint_valid = hint;
     if (p < n) idx[ids[p]] = idx_sorted[p];
 }
 
@@ -460,6 +418,19 @@ static void sort_vectors_t(const float* X, uint32_t N, const Workspace& w, hipSt
                        w.vperm, N, w.xsorted);
 }
 
+hipError_t launch_gather_rows(const float* in, const uint32_t* ids, uint32_t n, uint32_t d, float* out, hipStream_t s)
+{
+    const uint64_t pieces = uint64_t(n) * (d / 4);
+    const dim3 grid(uint32_t((pieces + kThreads - 1) / kThreads));
+    switch (d) {
+        case 4: hipLaunchKernelGGL(gather_rows_kernel<4>, grid, dim3(kThreads), 0, s, in, ids, n, out); break;
+        case 8: hipLaunchKernelGGL(gather_rows_kernel<8>, grid, dim3(kThreads), 0, s, in, ids, n, out); break;
+        case 16: hipLaunchKernelGGL(gather_rows_kernel<16>, grid, dim3(kThreads), 0, s, in, ids, n, out); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_sort_vectors(const float* X, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool drop_hint,
                                hipStream_t s)
 {
@@ -520,10 +491,11 @@ hipError_t launch_sort_centroids(const float* C, uint32_t d, uint32_t K, const W
 }
 
 template <int D>
-static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, float guess, hipStream_t s)
+static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, float guess, hipStream_t s, const uint32_t* n_dev)
 {
     hipLaunchKernelGGL(window_kernel<D>, dim3((N + kWinTile - 1) / kWinTile), dim3(kThreads), 0, s, w.xsorted, N, C, K, w.idx_sorted,
-                       w.persist, w.key_starts, guess, w.hdr, w.windows);
+                       w.persist, w.key_starts, guess, w.hdr, w.windows, n_dev, &w.hdr->window_stages);
+    if (n_dev != nullptr) return;
     hipLaunchKernelGGL(window_stats_kernel, dim3(32), dim3(1024), 0, s, w.windows, (N + kWinTile - 1) / kWinTile, K, w.hdr,
                        guess > 0.0f ? 1 : 0);
 }
@@ -532,21 +504,21 @@ static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w
 // guess > 0: no codes needed - windows of relative half-width `guess` around every vector's own norm and
 // projection, for the bootstrap pass that produces the first codes; does nothing if the workspace holds a hint.
 hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
-                          hipStream_t s)
+                          hipStream_t s, const uint32_t* n_dev)
 {
     switch (d) {
-        case 4: windows_t<4>(C, N, K, w, guess, s); break;
-        case 8: windows_t<8>(C, N, K, w, guess, s); break;
-        case 16: windows_t<16>(C, N, K, w, guess, s); break;
+        case 4: windows_t<4>(C, N, K, w, guess, s, n_dev); break;
+        case 8: windows_t<8>(C, N, K, w, guess, s, n_dev); break;
+        case 16: windows_t<16>(C, N, K, w, guess, s, n_dev); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, hipStream_t s)
+hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool norm_order, hipStream_t s)
 {
     hipLaunchKernelGGL(unpermute_kernel, dim3((N + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.idx_sorted, w.vperm, N,
-                       idx, w.persist);
+                       idx, w.persist, norm_order ? 1 : 0);
     return hipGetLastError();
 }
 

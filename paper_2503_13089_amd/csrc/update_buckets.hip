@@ -339,7 +339,12 @@ __global__ __launch_bounds__(kThreads) void bucket_sum_kernel(const char* __rest
     const int e = fixed_point_exp(hdr->absmax_bits, N);
     const uint32_t p0 = blockIdx.x * kBucketClusters;
     const uint32_t first = base[blockIdx.x], last = base[blockIdx.x + 1];
-    for (uint32_t p = first + threadIdx.x; p < last; p += kThreads) {
+    // A full pass deals the records out in turn. Those of an incremental pass are few and come from vectors that may lie
+    // ordered by cluster (a fit by cells): neighbours would add to one accumulator, so every thread takes a stretch.
+    const uint32_t per = delta ? (last - first + kThreads - 1) / kThreads : 0u;
+    const uint32_t begin = delta ? first + min(threadIdx.x * per, last - first) : first + threadIdx.x;
+    const uint32_t end = delta ? min(begin + per, last) : last, stride = delta ? 1u : uint32_t(kThreads);
+    for (uint32_t p = begin; p < end; p += stride) {
         const char* rec = records + size_t(p) * Record<D>::kBytes;
         const uint2 tag = *reinterpret_cast<const uint2*>(rec + D * 4);
         const uint32_t local = (tag.x - p0) & (kBucketClusters - 1);

@@ -1,0 +1,47 @@
+"""Large fits decide most vectors on a list of the centroids near their last one (Section 3.1: the codes are the argmin over
+all centroids): at the edges of how cells, lists and their tiles are dealt out, every result has the bits of the
+direct-form kernels."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+N4, N8 = 1 << 22, 1 << 21   # the smallest that take the form
+
+
+@pytest.mark.parametrize("N,d,K,iters,kind", [
+    (N4, 4, 1024, 3, "plain"), (N4 + 77, 4, 1055, 9, "plain"), (N4 + 1, 3, 32768, 4, "plain"), (N4, 4, 2048, 4, "fp32"),
+    (N4, 4, 4096, 4, "clumped"),
+    (N8, 8, 1024, 9, "plain"), (N8 + 33, 8, 1025, 3, "plain"), (N8 + 1, 5, 65536, 3, "plain"), (N8 + 63, 6, 65500, 4, "plain"),
+    (N8, 8, 2048, 3, "fp32"), (N8, 8, 4096, 4, "clumped"), (N8, 7, 1500, 4, "one value")])
+def test_fits_by_cells_have_the_bits_of_the_direct_form(N, d, K, iters, kind):
+    import paper_2503_13089_amd as cc
+    from tests import gpu_helpers as g
+
+    X, C0 = workloads.make_small(N, d, K, seed=N + d + K)
+    rng = np.random.default_rng(K)
+    if kind == "fp32":          # no fp16 numbers: every vector goes through the fp32 windows
+        X = (X * np.float32(1.0009)).astype(np.float32)
+    elif kind == "clumped":     # more centroids close together than a list has room for, and exact duplicates
+        C0 = C0.copy()
+        C0[K // 4:] = C0[0] + (rng.standard_normal((K - K // 4, d)) * 1e-4).astype(np.float16).astype(np.float32)
+        C0[-8:] = C0[0]
+    elif kind == "one value":   # one enormous cell
+        X = X.copy()
+        X[: 3 * N // 4] = X[0]
+    Xd, ws = g.dev(X), g.workspace(N, d, K)
+    got = []
+    try:
+        for mode in (0, 1):
+            cc.set_assign_mode(mode)
+            print(f"fit by cells N={N} d={d} K={K} iters={iters} {kind} mode {mode}", flush=True)
+            got.append(g.gpu_fit(X, C0, iters, ws=ws, Xd=Xd))
+    finally:
+        cc.set_assign_mode(0)
+    (C, idx, J, _), (C1, idx1, J1, _) = got
+    assert C.tobytes() == C1.tobytes() and idx.tobytes() == idx1.tobytes()
+    assert J == pytest.approx(J1, rel=1e-12)
