@@ -401,6 +401,11 @@ hipError_t launch_layer_weight(const void* codebook, int dtype, uint32_t K, uint
 // y = x . W(codebook, codes) (+ bias); `partial` holds layer_forward_splits(...) * M * out_features floats if that
 // count is above 1
 uint32_t layer_forward_splits(uint64_t M, uint32_t in_features, uint32_t out_features);
+// few rows, codebook through LDS (layer_forward_book.hip): whether a call takes that route; needs no partial buffer
+bool layer_forward_book(uint64_t M, uint32_t g, uint32_t K, uint32_t in_features, uint32_t out_features);
+hipError_t launch_layer_forward_book(const uint16_t* x, uint32_t M, const uint16_t* codebook, int dtype, uint32_t K,
+                                     const uint16_t* codes, uint32_t in_features, uint32_t out_features, const uint16_t* bias,
+                                     uint16_t* y, hipStream_t s);
 hipError_t launch_layer_forward(const void* x, uint32_t M, const void* codebook, int dtype, uint32_t K, uint32_t g,
                                 const uint16_t* codes, uint32_t in_features, uint32_t out_features, const void* bias,
                                 void* y, float* partial, hipStream_t s);

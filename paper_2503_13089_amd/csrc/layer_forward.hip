@@ -318,6 +318,8 @@ hipError_t launch_layer_forward(const void* x, uint32_t M, const void* codebook,
     const uint16_t* cb = static_cast<const uint16_t*>(codebook);
     const uint16_t* bs = static_cast<const uint16_t*>(bias);
     uint16_t* ys = static_cast<uint16_t*>(y);
+    if (layer_forward_book(M, g, K, in_features, out_features))
+        return launch_layer_forward_book(xs, M, cb, dtype, K, codes, in_features, out_features, bs, ys, s);
     const uint32_t splits = layer_forward_splits(M, in_features, out_features);
     const uint32_t ksteps = (in_features + BK - 1) / BK;
     const uint32_t rows_per_split = (ksteps + splits - 1) / splits * BK;
