@@ -242,7 +242,7 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
         {
             cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
             if (by_buckets && !sums_follow && cc::update_sliced_applies(N, d, K, w))
-                CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, s), "update (slices)");
+                CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, false, s), "update (slices)");
             else if (by_buckets)
                 CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, true, s,
                                                      sums_follow ? w.idx_prev : nullptr, sums_follow ? w.changed : nullptr),
@@ -577,8 +577,14 @@ int cc_update_ex(const float* vectors, uint64_t N, uint32_t d, const uint32_t* i
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const cc::Workspace w = cc::carve(workspace, N, d, K);
-    CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     Operands o;
+    if (cc::update_sliced_applies(uint32_t(N), w.d, K, w)) {
+        if (int rc = enter(vectors, prev_centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
+        cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
+        CC_TRY_HIP(cc::launch_update_sliced(o.X, uint32_t(N), w.d, idx, o.C_in, K, o.C_work, counts, w, true, true, s), "update (slices)");
+        return leave(centroids, d, K, w, s);
+    }
+    CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     if (int rc = enter(vectors, prev_centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
     {
@@ -720,16 +726,15 @@ int cc_layer_codebook_grad(const void* grad_weight, int grad_dtype, uint32_t in_
     if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const cc::Workspace w = cc::carve(workspace, n_ws, g, K);
-    CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     // A large layer with 16-bit gradients whose sub-vectors are whole rows of g numbers: summed in place by cluster
     // slices, no fp32 copy of the gradient (the same fixed-point sums as below, hence the same bits).
     if (grad_dtype != CC_F32 && out_features % g == 0 && !w.padded && aligned(grad_weight, 16) && aligned(codes, 4) &&
         cc::update_sliced_applies(uint32_t(N), w.d, K, w)) {
-        CC_TRY_HIP(cc::launch_scan_inputs16(grad_weight, grad_dtype, N * g, w.hdr, s), "input scan");
         CC_TRY_HIP(cc::launch_sum_rows16_sliced(grad_weight, grad_dtype, uint32_t(N), w.d, codes, K, grad_codebook, w, s),
                    "codebook gradient (slices)");
         return CC_OK;
     }
+    CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     // the ordered-copy buffers of the E-step are free here: vectors in w.xsorted, widened codes in w.idx_sorted
     CC_TRY_HIP(cc::launch_layer_grad_vectors(grad_weight, grad_dtype, in_features, out_features, g, w.d, codes, N, w.xsorted,
                                              w.idx_sorted, s), "gradient vectors");
