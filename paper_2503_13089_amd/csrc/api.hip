@@ -275,7 +275,7 @@ int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32
     }
     if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1, true, s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
-    CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed),
+    CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed, true),
                "update (buckets)");
     return CC_OK;
 }
@@ -475,9 +475,9 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         }
         // only the matrix-core path can leave its codes in the workspace; the others write idx directly
         uint32_t* step_idx = pruned || small ? nullptr : idx;
-        // from the third iteration on the M-step only moves the vectors whose code changed (the first iterations move
-        // too many for that to pay off)
-        const bool sums_follow = pruned && w.bucket_ok && t >= 2;
+        // From the third iteration on the M-step only moves the vectors whose code changed (the first iterations move
+        // too many for that to pay off). Where one pass by one slice will do, finding those takes as long as that pass.
+        const bool sums_follow = pruned && w.bucket_ok && t >= 2 && !(cc::update_one_slice(D, K) && cc::update_sliced_applies(n, D, K, w));
         if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, small, sums_follow))
             return rc;
     }

@@ -367,15 +367,17 @@ hipError_t launch_accumulate(const float* X, uint32_t N, uint32_t d, const uint3
 // counts are left in w.sums / w.counts. prev_idx != NULL: those already hold the sums and counts of the codes
 // prev_idx; only the vectors whose code differs are moved (bit-identical to a recomputation from idx). That needs
 // `changed` too, one bit per vector: prev_idx is only read, and only needs to be valid, where the bit is set, and a
-// vector whose bit is clear must have kept its code.
+// vector whose bit is clear must have kept its code. by_cluster: neighbouring vectors are mostly of one cluster.
 hipError_t launch_update_buckets(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev,
                                  uint32_t K, float* out, uint32_t* counts_out, const Workspace& w, bool norm_order,
                                  bool mean, hipStream_t s, const uint32_t* prev_idx = nullptr,
-                                 const uint32_t* changed = nullptr);
+                                 const uint32_t* changed = nullptr, bool by_cluster = false);
 // M-step by cluster slices (update_sliced.hip): one pass over the codes per slice of the clusters, LDS accumulators,
-// no copy of the vectors; for N >= 2^20 and K <= 65536. Same integer sums (left in w.sums / w.counts) and the same
+// no copy of the vectors; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
 // result bits as the other formulations. `out` may alias `prev`.
 bool update_sliced_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
+// Whether all clusters fit one slice, i.e. the pass needs neither lists nor a second look at a code.
+inline bool update_one_slice(uint32_t d, uint32_t K) { return K <= 16384 / d; }
 // Sums (not means) of 16-bit rows (dtype 1 = fp16, 2 = bf16; 16-byte aligned) by 16-bit code (4-byte aligned), both read
 // in place; needs update_sliced_applies(N, d, K, w). Header as after a reset and a scan of the rows.
 hipError_t launch_sum_rows16_sliced(const void* rows, int dtype, uint32_t N, uint32_t d, const uint16_t* codes, uint32_t K,

@@ -36,6 +36,7 @@ namespace {
 constexpr int kThreads = 1024;            // 16 waves: what hides the latency of the row fetches
 constexpr int kWaves = kThreads / 64;
 constexpr uint32_t kWorkgroups = 256;
+constexpr uint32_t kLeast = 32768;        // vectors; below, few memory-side atomics take no longer (20000 of 16 numbers: 33 and 36 us)
 constexpr int kChunkThreads = 512;        // for a chunk: finer grains than 1024, 4 M vectors are 585 chunks
 constexpr uint32_t kChunk = 7168;         // vectors sorted together
 constexpr uint32_t kPosBits = 13;
@@ -114,20 +115,25 @@ struct Cut {
     size_t sum_bytes, part_bytes, entry_bytes, start_bytes;
 };
 
+// The record buffer (2 N records) holds it all; ranges = 0: not even one range of partial sums fits.
 template <int D>
 Cut cut_of(uint32_t N, uint32_t K)
 {
+    const size_t have = size_t(N) * 2 * (4 * D + 16);
     Cut c;
-    c.listed = K > Slice<D>::kClusters;
+    c.listed = !update_one_slice(D, K);
+    static_assert(Slice<D>::kClusters == 16384 / D);
     c.slices = (K + Slice<D>::kClusters - 1) / Slice<D>::kClusters;
     c.chunks = uint32_t((uint64_t(N) + kChunk - 1) / kChunk);
-    c.ranges = std::max(1u, std::min(kWorkgroups / c.slices, c.chunks));
-    c.sharers = 1;
-    while (c.sharers < uint32_t(kWaves) && c.sharers * 128 < kChunk / c.slices) c.sharers *= 2;
-    c.sum_bytes = align256(size_t(c.slices) * c.ranges * Slice<D>::kLdsBytes);
     c.part_bytes = align256(size_t(c.chunks) * sizeof(ScanPart));
     c.entry_bytes = c.listed ? align256(size_t(c.chunks) * kChunk * 4) : 0;
     c.start_bytes = c.listed ? align256(size_t(c.chunks) * (c.slices + 1) * 4) : 0;
+    const size_t taken = c.part_bytes + c.entry_bytes + c.start_bytes + 256, per_range = size_t(c.slices) * Slice<D>::kLdsBytes;
+    const uint32_t fit = uint32_t(have > taken ? std::min<size_t>((have - taken) / per_range, kWorkgroups) : 0);
+    c.ranges = std::min({std::max(kWorkgroups / c.slices, 1u), c.chunks, fit});
+    c.sharers = 1;
+    while (c.sharers < uint32_t(kWaves) && c.sharers * 128 < kChunk / c.slices) c.sharers *= 2;
+    c.sum_bytes = align256(per_range * c.ranges);
     return c;
 }
 
@@ -404,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t i = min(i0 + u * (64 / P) + which, end - 1);
-            ent[u] = LISTED ? entries[size_t(first) + i] : (code_at<SRC>(idx, size_t(first) + i) << kPosBits) | i;
+            ent[u] = LISTED ? entries[size_t(first) + i] : (min(code_at<SRC>(idx, size_t(first) + i), K) << kPosBits) | i;
         }
     };
     float pending[U][n];
@@ -556,23 +562,14 @@ hipError_t update_sliced_t(const void* X, uint32_t N, const void* idx, const flo
                     : launch_t<D, SRC, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, s);
 }
 
-template <int D>
-size_t sliced_bytes_t(uint32_t N, uint32_t K)
-{
-    const Cut c = cut_of<D>(N, K);
-    return c.sum_bytes + c.part_bytes + c.entry_bytes + c.start_bytes;
-}
-
 }  // namespace
 
-// Whether the M-step by slices applies: enough vectors that one pass per slice over the codes pays, and a workspace
-// whose record buffer (2 N records) holds the per-workgroup partial sums.
+// Whether the M-step by slices applies: not to so few vectors that three launches with a workgroup per 7168 of them take
+// longer than atomics, nor where the record buffer does not hold one range of partial sums (far fewer vectors than centroids).
 bool update_sliced_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w)
 {
-    if (!w.bucket_ok || w.records == nullptr || N < (1u << 20)) return false;
-    const size_t have = size_t(N) * 2 * (4 * d + 16);
-    const size_t need = d == 4 ? sliced_bytes_t<4>(N, K) : (d == 8 ? sliced_bytes_t<8>(N, K) : sliced_bytes_t<16>(N, K));
-    return need <= have;
+    if (!w.bucket_ok || w.records == nullptr || N < kLeast) return false;
+    return (d == 4 ? cut_of<4>(N, K).ranges : (d == 8 ? cut_of<8>(N, K).ranges : cut_of<16>(N, K).ranges)) > 0;
 }
 
 // `out` may alias `prev`; `out` must not alias X. Sums and counts are left in w.sums / w.counts. fresh: no input scan has run

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d,per_slice", [(4, 4096), (8, 2048), (16, 1024)])
 @pytest.mark.parametrize("N,slices,short", [(147 * 7168, 1, 0), (147 * 7168 + 1, 2, 0), (147 * 7168 - 1, 3, 1), (1048576 + 63, 4, 40),
-                                            (1048576 + 65, 5, 1), (1048576 + 4097, 13, 5)])
+                                            (1048576 + 65, 5, 1), (1048576 + 4097, 13, 5),
+                                            (32768, 1, 300), (40000, 2, 3)])
 def test_sums_by_slices_are_the_fixed_point_sums(d, per_slice, N, slices, short):
     K = slices * per_slice - short
     rng = np.random.default_rng(N + K + d)
@@ -19,7 +20,7 @@ def test_sums_by_slices_are_the_fixed_point_sums(d, per_slice, N, slices, short)
     X[5:9] = -0.0
     idx = rng.integers(0, K, size=N).astype(np.uint32)
     idx[N // 2:N // 2 + 9000] = K - 1          # a chunk and more of one cluster
-    idx[[0, 77, N - 1]] = K, 2**32 - 1, K      # no cluster
+    idx[[0, 77, N - 1]] = K, 2**31, 2**32 - 1      # no cluster
     prev = rng.standard_normal((K, d)).astype(np.float32)
     keep = idx < K
     for bad in (False, True):
