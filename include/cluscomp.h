@@ -53,7 +53,7 @@ typedef enum cc_status {
     CC_ERR_SHAPE = -2,     /* N == 0, N >= 2^32, d not in 1..16, K == 0, K > N, K > 2^24 */
     CC_ERR_ITERS = -3,     /* iters < 0 */
     CC_ERR_ALIGN = -4,     /* a pointer violates the alignment stated above */
-    CC_ERR_WORKSPACE = -5, /* workspace_bytes < cc_workspace_bytes(N, d, K) */
+    CC_ERR_WORKSPACE = -5, /* workspace_bytes below what every call needs, see cc_workspace_bytes */
     CC_ERR_HIP = -6        /* the HIP runtime reported an error at launch */
 } cc_status;
 
@@ -74,7 +74,10 @@ typedef enum cc_status {
  *                         whose norm, or whose projection on the fixed direction, differs from a vector's by more than
  *                         a known upper bound of its nearest distance cannot be the nearest. The previous E-step's
  *                         codes on the same workspace - or a bootstrap pass over a guessed neighbourhood of each
- *                         vector - provide that bound; a poor bound costs time, never correctness.
+ *                         vector - provide that bound; a poor bound costs time, never correctness. Inside a large
+ *                         fit (d <= 8, 1024 <= K <= 65536, 2^22 vectors and 128 K for d <= 4, 2^21 and 32 K above;
+ *                         iters >= 3) most vectors are, from the second E-step on, decided on a list of the centroids
+ *                         near their last one.
  *   CC_ASSIGN_DIRECT      direct-form vector-ALU kernel only.
  *   CC_ASSIGN_MFMA_F32    fp32 MFMA kernel always, whole codebook.
  *   CC_ASSIGN_AUTO_WHOLE  as CC_ASSIGN_AUTO but always the whole codebook, and every M-step recomputed.
@@ -120,9 +123,12 @@ int cc_profile_read(cc_profile *profile, double *ms, uint32_t *launches, uint32_
 void cc_profile_destroy(cc_profile *profile);
 
 /* Host-only query: bytes of device workspace that cc_kmeans_fit / cc_assign / cc_lloyd_iter / cc_update
- * need for this problem size (about 12*N*d + 54*N bytes: an ordered copy of the vectors, room for two
- * copies grouped by cluster for the M-step, permutations and sort buffers, with d rounded up to 4, 8 or 16; plus one
- * more padded copy of the vectors if d is not one of those). Returns 0 for an unsupported shape. The
+ * need for this problem size, with d rounded up to 4, 8 or 16. Most of it (about 12*N*d + 60*N bytes for K <= 65536:
+ * an ordered copy of the vectors, room for two copies grouped by cluster for the M-step, permutations and sort buffers;
+ * plus one more padded copy of the vectors if d is not one of those) is needed by every call. The rest serves
+ * the fastest form of a large fit (neighbour lists, see CC_ASSIGN_AUTO: 12 bytes per vector, and where N is less than
+ * about 240 K at d = 5..8 up to 12 KB per centroid) and of a small problem (partial sums, at most 32 MB); a workspace
+ * without room for that is accepted and gives the same results. Returns 0 for an unsupported shape. The
  * first 256 bytes keep a little state between calls (problem shape, "codes of the previous E-step are
  * present"): a workspace that held something else in between is still safe to reuse - stale state can
  * only make a call slower, not wrong. */

@@ -54,7 +54,7 @@ int check_workspace(void* ws, size_t ws_bytes, uint64_t N, uint32_t d, uint32_t 
 {
     if (ws == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
     if (!aligned(ws, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
-    const size_t need = cc::carve(nullptr, N, d, K).bytes;
+    const size_t need = cc::carve(nullptr, N, d, K).least;
     if (ws_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", ws_bytes, need);
     return CC_OK;
 }
@@ -89,9 +89,9 @@ bool use_pruning(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters)
 
 // Small problems: two launches per iteration, everything in direct form (small_fit.hip); a fit long and large enough for
 // the windows is better off with them.
-bool use_small(const Ctx& cx, uint64_t N, uint32_t d, uint32_t K, int32_t iters)
+bool use_small(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters, const cc::Workspace& w)
 {
-    return cx.mode == CC_ASSIGN_AUTO && !use_pruning(cx, N, K, iters) && cc::small_problem(N, d, K);
+    return cx.mode == CC_ASSIGN_AUTO && !use_pruning(cx, N, K, iters) && w.small_partials != nullptr;
 }
 
 // Relative half-width of the guessed windows of the bootstrap pass. The nearest-centroid distance of a vector of
@@ -452,7 +452,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    cc::Workspace w = cc::carve(workspace, N, d, K);
+    cc::Workspace w = cc::carve(workspace, N, d, K, workspace_bytes);
     const uint32_t n = uint32_t(N), D = w.d;
 
     CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
@@ -461,13 +461,13 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * D, w.hdr, s), "input scan");
     if (o.C_work != o.C_in)
         CC_TRY_HIP(cc::launch_copy_f32(o.C_in, o.C_work, size_t(K) * D, s), "centroid copy");
-    const bool small = use_small(cx, N, D, K, iters);
+    const bool small = use_small(cx, N, K, iters, w);
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, iters);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
     }
-    const bool cells = pruned && iters >= 3 && cc::cells_possible(N, D, K);
+    const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr;
     for (int32_t t = 0; t < iters; ++t) {
         if (cells && t > 0) {
             if (int rc = run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, s)) return rc;
@@ -509,12 +509,12 @@ int cc_assign_ex(const float* vectors, uint64_t N, uint32_t d, const float* cent
         return fail(CC_ERR_ALIGN, "vectors/centroids need 16-byte alignment, idx 4, inertia 8");
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const cc::Workspace w = cc::carve(workspace, N, d, K);
+    const cc::Workspace w = cc::carve(workspace, N, d, K, workspace_bytes);
     CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     Operands o;
     if (int rc = enter(vectors, centroids, nullptr, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool small = use_small(cx, N, w.d, K, 1);
+    const bool small = use_small(cx, N, K, 1, w);
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
@@ -542,12 +542,12 @@ int cc_lloyd_iter_ex(const float* vectors, uint64_t N, uint32_t d, float* centro
         return fail(CC_ERR_ALIGN, "vectors/centroids need 16-byte alignment, idx and counts 4, inertia 8");
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const cc::Workspace w = cc::carve(workspace, N, d, K);
+    const cc::Workspace w = cc::carve(workspace, N, d, K, workspace_bytes);
     CC_TRY_HIP(cc::launch_reset_header(w.hdr, s), "bookkeeping");
     Operands o;
     if (int rc = enter(vectors, centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool small = use_small(cx, N, w.d, K, 1);
+    const bool small = use_small(cx, N, K, 1, w);
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
@@ -576,7 +576,7 @@ int cc_update_ex(const float* vectors, uint64_t N, uint32_t d, const uint32_t* i
         return fail(CC_ERR_ALIGN, "vectors/centroids need 16-byte alignment, idx and counts 4");
     if (int rc = check_workspace(workspace, workspace_bytes, N, d, K)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const cc::Workspace w = cc::carve(workspace, N, d, K);
+    const cc::Workspace w = cc::carve(workspace, N, d, K, workspace_bytes);
     Operands o;
     if (cc::update_sliced_applies(uint32_t(N), w.d, K, w)) {
         if (int rc = enter(vectors, prev_centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
@@ -722,10 +722,10 @@ int cc_layer_codebook_grad(const void* grad_weight, int grad_dtype, uint32_t in_
     if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
     // sized like a clustering problem with at least K vectors (a layer may have fewer codes than clusters)
     const uint64_t n_ws = N > K ? N : K;
-    const size_t need = cc::carve(nullptr, n_ws, g, K).bytes;
+    const size_t need = cc::carve(nullptr, n_ws, g, K).least;
     if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const cc::Workspace w = cc::carve(workspace, n_ws, g, K);
+    const cc::Workspace w = cc::carve(workspace, n_ws, g, K, workspace_bytes);
     // A large layer with 16-bit gradients whose sub-vectors are whole rows of g numbers: summed in place by cluster
     // slices, no fp32 copy of the gradient (the same fixed-point sums as below, hence the same bits).
     if (grad_dtype != CC_F32 && out_features % g == 0 && !w.padded && aligned(grad_weight, 16) && aligned(codes, 4) &&
@@ -749,7 +749,7 @@ int cc_layer_codebook_grad(const void* grad_weight, int grad_dtype, uint32_t in_
 // One layer, one call: reshape, seeded start, Lloyd iterations, storage formats.
 namespace {
 struct CompressLayout {
-    size_t vectors, centroids, idx, fit, total;
+    size_t vectors, centroids, idx, fit, least, total;
     uint64_t N;
 };
 CompressLayout compress_layout(uint32_t out_features, uint32_t in_features, uint32_t g, uint32_t K)
@@ -761,8 +761,10 @@ CompressLayout compress_layout(uint32_t out_features, uint32_t in_features, uint
     l.vectors = take(size_t(l.N) * g * 4);
     l.centroids = take(size_t(K) * g * 4);
     l.idx = take(size_t(l.N) * 4);
-    l.fit = take(cc::carve(nullptr, l.N, g, K).bytes);
-    l.total = off;
+    const cc::Workspace w = cc::carve(nullptr, l.N, g, K);
+    l.fit = off;
+    l.least = off + w.least;
+    l.total = off + w.bytes;
     return l;
 }
 }  // namespace
@@ -787,7 +789,7 @@ int cc_layer_compress(const void* weight, int weight_dtype, uint32_t out_feature
     if (int rc = check_shape(l.N, g, K)) return rc;
     if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
     if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
-    if (workspace_bytes < l.total) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, l.total);
+    if (workspace_bytes < l.least) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, l.least);
     char* base = static_cast<char*>(workspace);
     float* vectors = reinterpret_cast<float*>(base + l.vectors);
     float* centroids = reinterpret_cast<float*>(base + l.centroids);

@@ -126,12 +126,13 @@ struct Workspace {
     char* cell_flat;           // [K + 1] x 64 bytes: operand pieces of each ordered centroid (d = 8)
     char* cell_operands;       // one matrix-core operand per 32 ordered centroids, for the lists
     uint32_t* cell_items;      // [N / 64 + K] cell of each work item
-    uint16_t* cell_lists;      // [K][cap] positions in the norm order of the centroids
-    char* small_partials;      // small problems: one set of cluster sums per workgroup
+    uint16_t* cell_lists;      // [K][cap] positions in the norm order of the centroids (an E-step's own); NULL: no room for cells
+    char* small_partials;      // small problems: one set of cluster sums per workgroup; NULL: no room
     uint32_t refine_cap;
     uint32_t partial_slots;
     uint32_t packed_tiles;     // number of 32-centroid tiles in `packed` (K rounded up, padded)
-    size_t bytes;
+    size_t least;              // bytes without which no call runs: cells and the form for small problems go without
+    size_t bytes;              // bytes for the fastest form of every call
 };
 
 constexpr uint32_t kTileCentroids = 32;   // centroids per matrix-core tile
@@ -153,8 +154,13 @@ constexpr uint32_t kDeltaChunk = 16384;   // the same for an incremental pass, w
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Lays the arrays out behind `base` (which may be NULL for a pure size query).
-inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
+// E-step by cells: the far vectors lie at the start of the M-step's record buffer, which is free during an E-step
+inline size_t far_bytes(uint64_t N, uint32_t d) { return align256(size_t(N) * d * 4) + 3 * align256(size_t(N) * 4); }
+
+// Lays the arrays out behind `base` (which may be NULL for a pure size query); `have` bytes are there. Calls take a workspace
+// of w.least bytes; the arrays of cells and of small problems share space with others where those are idle, and are left out
+// (NULL) where `have` does not reach them.
+inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K, size_t have = ~size_t(0))
 {
     Workspace w{};
     const uint32_t d = d_caller <= 4 ? 4u : (d_caller <= 8 ? 8u : 16u);
@@ -173,6 +179,11 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
     w.partial_slots = 1024;
     w.partials = reinterpret_cast<double*>(take(size_t(w.partial_slots) * 8));
     w.dmin = reinterpret_cast<float*>(take(size_t(N) * 4));
+    if (w.padded) {
+        w.xpad = reinterpret_cast<float*>(take(size_t(N) * d * 4));
+        w.cpad = reinterpret_cast<float*>(take(size_t(K) * d * 4));
+    }
+    const size_t small_at = off;   // a small problem uses none of what follows
     const uint32_t stage = kTileCentroids * kStageTilesMax;
     w.packed_tiles = uint32_t((uint64_t(K) + stage - 1) / stage) * kStageTilesMax;
     // per centroid: fp32 operands + norm take 4(d+1) bytes; the fp16-split operands take up to 6d+4 bytes
@@ -197,21 +208,21 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
     // histogram rows + 256 totals, for the vectors' sort and for the centroids' (whose blocks are smaller)
     w.sort_hist = reinterpret_cast<uint32_t*>(take(std::max(sort_hist_bytes(N), sort_hist_bytes(K))));
     w.windows = reinterpret_cast<uint2*>(take((size_t(N) / kWinTile + 1) * kWinStride * 8));
-    if (w.padded) {
-        w.xpad = reinterpret_cast<float*>(take(size_t(N) * d * 4));
-        w.cpad = reinterpret_cast<float*>(take(size_t(K) * d * 4));
-    }
     w.bucket_ok = K <= kMaxBuckets * kBucketClusters && N < (uint64_t(1) << 31);  // record positions are 32-bit
     if (w.bucket_ok) {
         const size_t buckets = (size_t(K) + kBucketClusters - 1) / kBucketClusters;
-        // 2N records: an incremental M-step writes two records (plus, minus) per vector whose code changed, and
-        // nothing bounds how many change in one iteration
-        w.records = take(size_t(N) * 2 * (4 * d + 16));
         w.bucket_hist = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk + 1) * 4));
         w.bucket_gtot = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk / kBucketGroup + 1) * 4));
         w.bucket_base = reinterpret_cast<uint32_t*>(take((buckets + 1) * 4));
+        // 2N records: an incremental M-step writes two records (plus, minus) per vector whose code changed, and
+        // nothing bounds how many change in one iteration
+        w.records = take(size_t(N) * 2 * (4 * d + 16));
     }
+    w.least = w.bytes = off;
     if (cells_possible(N, d, K)) {
+        // the lists live from the start of an E-step to its end: behind the far vectors, past the records' end if need be
+        const size_t lists_at = off - align256(size_t(N) * 2 * (4 * d + 16)) + far_bytes(N, d);
+        off = std::max(off, lists_at + align256(size_t(K) * cell_list_cap(d) * 2));
         w.cell_order = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
         w.cell_rank = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
         w.cell_position = reinterpret_cast<uint32_t*>(take(size_t(N) * 4));
@@ -222,10 +233,14 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K)
         w.cell_operands = take((size_t(K) + 31) / 32 * 1024);
         w.cell_flat = take((size_t(K) + 1) * 64);
         w.cell_items = reinterpret_cast<uint32_t*>(take((size_t(N) / 64 + K) * 4));
-        w.cell_lists = reinterpret_cast<uint16_t*>(take(size_t(K) * cell_list_cap(d) * 2));
+        w.cell_lists = have >= off && p ? reinterpret_cast<uint16_t*>(p + lists_at) : nullptr;
+        w.bytes = off;
     }
-    w.small_partials = take(small_partials_bytes(N, d, K));
-    w.bytes = off;
+    if (const size_t n = small_partials_bytes(N, d, K); n > 0) {
+        const size_t end = small_at + align256(n);
+        w.small_partials = have >= end && p ? p + small_at : nullptr;
+        w.bytes = std::max(w.bytes, end);
+    }
     return w;
 }
 
@@ -320,7 +335,7 @@ struct FarView {
     uint32_t* idx;   // [N]     previous codes
     uint32_t* refine;  // [N]   those to be re-decided in direct form
 };
-inline FarView far_view(const Workspace& w, uint32_t N, uint32_t d)   // in the M-step's record buffer, free at that time
+inline FarView far_view(const Workspace& w, uint32_t N, uint32_t d)   // far_bytes(N, d) bytes
 {
     FarView f;
     char* p = w.records;
