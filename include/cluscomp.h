@@ -127,7 +127,7 @@ void cc_profile_destroy(cc_profile *profile);
  * an ordered copy of the vectors, room for two copies grouped by cluster for the M-step, permutations and sort buffers;
  * plus one more padded copy of the vectors if d is not one of those) is needed by every call. The rest serves
  * the fastest form of a large fit (neighbour lists, see CC_ASSIGN_AUTO: 12 bytes per vector, and where N is less than
- * about 240 K at d = 5..8 up to 12 KB per centroid) and of a small problem (partial sums, at most 32 MB); a workspace
+ * about 150 K at d = 5..8 up to 8 KB per centroid) and of a small problem (partial sums, at most 32 MB); a workspace
  * without room for that is accepted and gives the same results. Returns 0 for an unsupported shape. The
  * first 256 bytes keep a little state between calls (problem shape, "codes of the previous E-step are
  * present"): a workspace that held something else in between is still safe to reuse - stale state can
