@@ -209,7 +209,7 @@ int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const floa
         CC_TRY_HIP(cc::launch_small_assign(X, N, d, C, K, idx, w.dmin, w, s), "assign (small problem)");
     } else if (use_matrix_cores(cx, K)) {
         if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, false, pruned, have_hint, s)) return rc;
-        if (pruned) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, true, s), "assign (codes to input order)");
+        if (pruned) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, false, s), "assign (codes to input order)");
     } else {
         CC_TRY_HIP(cc::launch_assign_direct(X, N, d, C, K, idx, w.dmin, nullptr, 0, s, cx.prof), "assign (direct form)");
         CC_TRY_HIP(cc::launch_bump_assign_calls(w.hdr, s), "bookkeeping");
@@ -250,7 +250,7 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
             else
                 CC_TRY_HIP(cc::launch_finalize(C, C, counts, K, d, N, w, true, s), "update (means)");
         }
-        if (pruned && idx != nullptr) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, true, s), "assign (codes to input order)");
+        if (pruned && idx != nullptr) CC_TRY_HIP(cc::launch_unpermute(N, idx, w, false, s), "assign (codes to input order)");
     } else {
         CC_TRY_HIP(cc::launch_assign_direct(X, N, d, C, K, idx, w.dmin, nullptr, 0, s, cx.prof), "assign (direct form)");
         CC_TRY_HIP(cc::launch_bump_assign_calls(w.hdr, s), "bookkeeping");
@@ -483,7 +483,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     }
     if (cells) {
         if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, false, false, s)) return rc;
-        CC_TRY_HIP(cc::launch_unpermute(n, idx, w, false, s), "assign (codes to input order)");
+        CC_TRY_HIP(cc::launch_unpermute(n, idx, w, true, s), "assign (codes to input order)");
         if (inertia)
             CC_TRY_HIP(cc::launch_reduce_dmin(w.dmin, n, w.partials, w.partial_slots, inertia, s), "objective reduction");
         return leave(centroids, d, K, w, s);

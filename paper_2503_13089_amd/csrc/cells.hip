@@ -1140,6 +1140,7 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
     const dim3 per_vector((N + kThreads - 1) / kThreads);
     hipLaunchKernelGGL(cell_keys_kernel, per_vector, dim3(kThreads), 0, s, w.idx_sorted, N, w.vkeys, w.cell_order);
     if (hipError_t e = launch_sort_u16(w.vkeys, w.cell_order, w.vkeys_tmp, w.vperm_tmp, N, w.sort_hist, s); e != hipSuccess) return e;
+    if (first) std::swap(w.idx_sorted, w.idx_prev);
     hipLaunchKernelGGL(cell_apply_kernel, per_vector, dim3(kThreads), 0, s, w.vkeys, N, w.cell_order, first ? nullptr : w.cell_rank,
                        w.vperm, w.vperm_tmp, w.cell_position, w.idx_sorted);
     std::swap(w.vperm, w.vperm_tmp);

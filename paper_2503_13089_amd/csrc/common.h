@@ -68,12 +68,14 @@ struct WsHeader {
 };
 
 // Survives between calls on the same workspace (not touched by the per-call header reset): whether the
-// norm-ordered codes of the previous E-step may serve as a hint. A hint never affects results, only
+// codes of the previous E-step may serve as a hint, and where they lie. A hint never affects results, only
 // how much of the codebook has to be scored.
+enum Hint : int { kHintNone = 0, kHintByNorm = 1,   // in the norm order, in idx_sorted
+                  kHintByCells = 2 };               // in the order of the cells, in idx_prev; that of norm rank r at cell_position[r]
 struct WsPersist {
     unsigned long long magic;
     uint32_t N, d, K;
-    uint32_t hint_valid;
+    uint32_t hint_valid;       // a Hint
 };
 
 // Carved view of the caller's workspace.
@@ -315,11 +317,12 @@ hipError_t launch_sort_centroids(const float* C, uint32_t d, uint32_t K, const W
 hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
                           hipStream_t s, const uint32_t* n_dev = nullptr);
 hipError_t launch_gather_rows(const float* in, const uint32_t* ids, uint32_t n, uint32_t d, float* out, hipStream_t s);
-// norm_order: the codes lie in the norm order, i.e. are a hint for the next call
-hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool norm_order, hipStream_t s);
+// by_cells: the vectors are grouped by cells
+hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool by_cells, hipStream_t s);
 
 // E-step by cells inside a fit (cells.hip), after a first E-step in the norm order. launch_cells_order groups the
-// vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order); launch_cells_centroids
+// vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order, and the codes change
+// places with w.idx_prev: at the end a next call can put them into the norm order, kHintByCells); launch_cells_centroids
 // orders the current centroids and makes their operands and the lists of the cells; launch_cells_near decides the near
 // vectors and leaves the far ones as a list of hdr->far_count entries in the arrays of far_view; launch_cells_far
 // decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.

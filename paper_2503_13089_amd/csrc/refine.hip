@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
         hdr->refined_vectors += count;
         hdr->assign_calls += 1;
         hdr->cmax_bits = 0;                               // the next E-step scans its own codebook
-        if (persist != nullptr) persist->hint_valid = 1;  // idx (norm-ordered) is a usable hint from now on
+        if (persist != nullptr) persist->hint_valid = kHintByNorm;  // idx (norm-ordered) is a usable hint from now on
     }
     if (count > refine_cap) return;  // overflow is handled by the full direct pass
     __shared__ unsigned long long red[kThreads / 64];

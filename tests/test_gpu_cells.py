@@ -45,3 +45,31 @@ def test_fits_by_cells_have_the_bits_of_the_direct_form(N, d, K, iters, kind):
     (C, idx, J, _), (C1, idx1, J1, _) = got
     assert C.tobytes() == C1.tobytes() and idx.tobytes() == idx1.tobytes()
     assert J == pytest.approx(J1, rel=1e-12)
+
+
+@pytest.mark.parametrize("N,d,K", [(N4 + 77, 4, 8192), (N8 + 33, 6, 8200)])
+def test_a_fit_by_cells_leaves_its_codes_as_the_next_call_s_hint(N, d, K):
+    """An E-step that finds no codes of a previous one scores the whole order of tiles twice, with a bootstrap pass first."""
+    import paper_2503_13089_amd as cc
+    from tests import gpu_helpers as g
+
+    X, C0 = workloads.make_small(N, d, K, seed=N + d + K)
+    Xd, ws = g.dev(X), g.workspace(N, d, K)
+    one_pass = -(-N // 512) * -(-K // 32)
+    for call in ("assign", "lloyd_iter"):
+        print(f"hint after a fit by cells N={N} d={d} K={K} {call}", flush=True)
+        C, idx, _, _ = g.gpu_fit(X, C0, 4, ws=ws, Xd=Xd)
+        Cd, out = g.dev(C), torch.empty(N, dtype=torch.uint32, device="cuda")
+        if call == "assign":
+            cc.assign(Xd, Cd, out, None, ws)
+        else:
+            cc.lloyd_iter(Xd, Cd, out, None, None, ws)
+        torch.cuda.synchronize()
+        st = cc.read_stats(ws)
+        assert st.total_stages == one_pass
+        # ... and the hint is each vector's own code: windows as wide as a converged E-step's
+        assert np.array_equal(out.cpu().numpy(), idx)
+        again = st.scored_stages
+        cc.assign(Xd, g.dev(C), out, None, ws)
+        torch.cuda.synchronize()
+        assert cc.read_stats(ws).scored_stages == again and np.array_equal(out.cpu().numpy(), idx)
