@@ -73,3 +73,41 @@ def test_a_fit_by_cells_leaves_its_codes_as_the_next_call_s_hint(N, d, K):
         cc.assign(Xd, g.dev(C), out, None, ws)
         torch.cuda.synchronize()
         assert cc.read_stats(ws).scored_stages == again and np.array_equal(out.cpu().numpy(), idx)
+
+
+def clumps(N, d, K, seed):
+    """K / 2 clumps, two centroids each: one in the middle of a clump and one so far beyond its end that the first E-step
+    gives it the outermost vector only. That becomes its place, and from the next E-step on it has a quarter of the clump."""
+    rng = np.random.default_rng(seed)
+    m = K // 2
+    centre = rng.uniform(-0.5, 0.5, size=(m, d)).astype(np.float16).astype(np.float32)
+    h = 0.06
+    X = np.repeat(centre, N // m, axis=0).reshape(m, N // m, d)
+    u = rng.uniform(0.0, 0.9, size=(m, N // m))
+    u[:, 0] = 1.0
+    X = X + rng.normal(scale=0.01 * h, size=X.shape)
+    X[:, 0] = centre                    # the outermost vector lies on the axis
+    X[:, :, 0] += h * u
+    C0 = np.repeat(centre, 2, axis=0)
+    C0[0::2, 0] += 0.5 * h
+    C0[1::2, 0] += 1.4 * h
+    X = X.reshape(-1, d)
+    X = X[rng.permutation(len(X))]
+    return X.astype(np.float16).astype(np.float32), C0.astype(np.float32)
+
+
+@pytest.mark.parametrize("N,d,K", [(N4, 4, 2048), (N8, 8, 2048)])
+def test_cells_that_begin_with_one_vector_get_lists_when_they_grow(N, d, K):
+    from tests import gpu_helpers as g
+
+    X, C0 = clumps(N, d, K, seed=d)
+    Xd, ws = g.dev(X), g.workspace(N, d, K)
+    scored = []
+    for iters in (5, 10):
+        print(f"growing cells N={N} d={d} K={K} iters={iters}", flush=True)
+        C, idx, _, st = g.gpu_fit(X, C0, iters, ws=ws, Xd=Xd)
+        scored.append(st.scored_stages)
+    assert 0.4 < np.bincount(idx, minlength=K)[1::2].sum() / N < 0.6     # every second cell has half a clump
+    # tiles of 32 centroids per 512 vectors and E-step: 0.3 to 0.5 where the lists serve them, 2.8 to 3.0 where half of the
+    # vectors go through the windows in every one
+    assert (scored[1] - scored[0]) / 5 < 1.4 * N / 512
