@@ -384,6 +384,15 @@ int cc_layer_forward_q(const void *x, uint64_t M, const void *qbook, int bits, c
 int cc_mfma_f16_probe(const uint16_t *A, const uint16_t *B, const float *C, float *D, uint32_t tiles, uint32_t km,
                       void *stream);
 
+/*
+ * The same for v_mfma_f32_16x16x32_f16, which scores the lists of a large fit's cells at d = 5..8: rows of 32 * km slots, 16 of
+ * A against 16 of B per tile. That guard band assumes 16 * 2^-24 * S; km = 2 chains two instructions, as inputs that are no
+ * fp16 numbers need.
+ *   A, B [tiles * 16 * 32 * km], C [tiles * 16], D [tiles * 16 * 16]
+ */
+int cc_mfma_f16_probe16(const uint16_t *A, const uint16_t *B, const float *C, float *D, uint32_t tiles, uint32_t km,
+                        void *stream);
+
 /* Thread-local description of the last error returned on this thread (host pointer, static storage). */
 const char *cc_last_error(void);
 

@@ -37,6 +37,7 @@ from .binding import (  # noqa: F401
     lloyd_iter,
     load_library,
     mfma_f16_probe,
+    mfma_f16_probe16,
     read_stats,
     set_assign_mode,
     update,

@@ -16,7 +16,7 @@ EXPORTS = (
     "cc_workspace_bytes", "cc_kmeans_fit", "cc_assign", "cc_lloyd_iter", "cc_update", "cc_decode",
     "cc_kmeans_fit_ex", "cc_assign_ex", "cc_lloyd_iter_ex", "cc_update_ex",
     "cc_profile_create", "cc_profile_read", "cc_profile_destroy",
-    "cc_read_stats", "cc_mfma_f16_probe", "cc_last_error", "cc_version",
+    "cc_read_stats", "cc_mfma_f16_probe", "cc_mfma_f16_probe16", "cc_last_error", "cc_version",
     "cc_layer_deficiency", "cc_layer_num_codes", "cc_layer_vectors", "cc_layer_pack", "cc_layer_weight",
     "cc_layer_codebook_grad", "cc_layer_forward", "cc_layer_forward_workspace_bytes",
     "cc_layer_grad_plan_bytes", "cc_layer_grad_plan_workspace_bytes", "cc_layer_grad_plan",
@@ -145,6 +145,8 @@ def load_library():
     lib.cc_layer_codebook_grad.restype = ctypes.c_int
     lib.cc_mfma_f16_probe.argtypes = [vp, vp, vp, vp, u32, u32, vp]
     lib.cc_mfma_f16_probe.restype = ctypes.c_int
+    lib.cc_mfma_f16_probe16.argtypes = [vp, vp, vp, vp, u32, u32, vp]
+    lib.cc_mfma_f16_probe16.restype = ctypes.c_int
     lib.cc_last_error.restype = ctypes.c_char_p
     lib.cc_version.restype = ctypes.c_char_p
     _lib = lib
@@ -327,6 +329,18 @@ def mfma_f16_probe(A, B, C, D) -> None:
     _check(load_library().cc_mfma_f16_probe(_ptr(A, torch.float16, "A"), _ptr(B, torch.float16, "B"),
                                             _ptr(C, torch.float32, "C"), _ptr(D, torch.float32, "D"), tiles, slots // 16,
                                             _stream()))
+
+
+def mfma_f16_probe16(A, B, C, D) -> None:
+    """cc_mfma_f16_probe16: A, B float16 [tiles, 16, 32 * km], C float32 [tiles, 16], D float32 [tiles, 16, 16] (out)."""
+    import torch
+
+    tiles, rows, slots = A.shape
+    if rows != 16 or slots not in (32, 64) or B.shape != A.shape or C.shape != (tiles, 16) or D.shape != (tiles, 16, 16):
+        raise ValueError("A, B: [tiles, 16, 32 or 64]; C: [tiles, 16]; D: [tiles, 16, 16]")
+    _check(load_library().cc_mfma_f16_probe16(_ptr(A, torch.float16, "A"), _ptr(B, torch.float16, "B"),
+                                              _ptr(C, torch.float32, "C"), _ptr(D, torch.float32, "D"), tiles, slots // 32,
+                                              _stream()))
 
 
 # ---- the compressed linear layer ---------------------------------------------------------------------

@@ -715,8 +715,8 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
 // through LDS, a wave of its own gathers them straight into registers. Four tiles of 16 centroids are folded two and two row
 // by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
 // instructions per 1024 scores. The winner is then known up to 2 centroids: two direct-form distances. What the tag costs
-// in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction was
-// measured at 5.7 x 2^-24 of the sum of its terms; 16 is assumed); a vector whose second best comes within the band is
+// in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction is
+// within 4.5 x 2^-24 of the sum of its terms in tests/test_gpu_mfma_bound16.py; 16 is assumed); a vector whose second best comes within the band is
 // decided in direct form over the list, 64 centroids at a time.
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.

@@ -39,6 +39,42 @@ __global__ __launch_bounds__(64) void mfma_f16_probe_kernel(const uint16_t* __re
     for (int r = 0; r < 16; ++r) D[(t * 32 + (r % 4) + 8 * (r / 4) + 4 * h) * 32 + n] = acc[r];
 }
 
+// The same for v_mfma_f32_16x16x32_f16 as the E-step by cells uses it (d = 8): A [tiles][16][32*KM], B [tiles][16][32*KM],
+// C [tiles][16], D [tiles][16][16].
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int KM>
+__global__ __launch_bounds__(64) void mfma_f16_probe16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                              const float* __restrict__ C, float* __restrict__ D)
+{
+    const int lane = threadIdx.x, g = lane >> 4, n = lane & 15;
+    const size_t t = blockIdx.x;
+    f16x8 a[KM], b[KM];
+#pragma unroll
+    for (int mi = 0; mi < KM; ++mi)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            // lane (n, g) supplies k slots 32*mi + 8g .. +7 of A row n and of B row n
+            a[mi][q] = __builtin_bit_cast(_Float16, A[(t * 16 + n) * (32 * KM) + 32 * mi + 8 * g + q]);
+            b[mi][q] = __builtin_bit_cast(_Float16, B[(t * 16 + n) * (32 * KM) + 32 * mi + 8 * g + q]);
+        }
+    f32x4 acc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[r] = C[t * 16 + 4 * g + r];
+#pragma unroll
+    for (int mi = 0; mi < KM; ++mi) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mi], b[mi], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) D[(t * 16 + 4 * g + r) * 16 + n] = acc[r];
+}
+
+hipError_t launch_mfma_f16_probe16(const uint16_t* A, const uint16_t* B, const float* C, float* D, uint32_t tiles, uint32_t km,
+                                   hipStream_t s)
+{
+    if (km == 1) hipLaunchKernelGGL(mfma_f16_probe16_kernel<1>, dim3(tiles), dim3(64), 0, s, A, B, C, D);
+    else if (km == 2) hipLaunchKernelGGL(mfma_f16_probe16_kernel<2>, dim3(tiles), dim3(64), 0, s, A, B, C, D);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 hipError_t launch_mfma_f16_probe(const uint16_t* A, const uint16_t* B, const float* C, float* D, uint32_t tiles, uint32_t km,
                                  hipStream_t s)
 {
