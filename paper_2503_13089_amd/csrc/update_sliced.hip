@@ -528,13 +528,10 @@ hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, co
     ScanPart* parts = reinterpret_cast<ScanPart*>(w.records + c.sum_bytes);
     uint32_t* entries = reinterpret_cast<uint32_t*>(w.records + c.sum_bytes + c.part_bytes);
     uint32_t* starts = reinterpret_cast<uint32_t*>(w.records + c.sum_bytes + c.part_bytes + c.entry_bytes);
-    static bool lds_set = false;
-    if (!lds_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sliced_accumulate_kernel<D, SRC, LISTED>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(S::kLdsBytes));
-        if (e != hipSuccess) return e;
-        lds_set = true;
-    }
+    // per call: the attribute belongs to the current device
+    if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sliced_accumulate_kernel<D, SRC, LISTED>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(S::kLdsBytes)); e != hipSuccess)
+        return e;
     if (fresh)
         hipLaunchKernelGGL((slice_chunk_kernel<D, SRC, true, LISTED>), dim3(c.chunks), dim3(kChunkThreads), 0, s, X, idx, N, K, c.slices, w.hdr,
                            parts, entries, starts);
