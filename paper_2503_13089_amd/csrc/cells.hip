@@ -985,18 +985,12 @@ __global__ __launch_bounds__(kThreads) void far_compact_kernel(uint32_t* __restr
                                                                uint32_t* __restrict__ far_pos, float* __restrict__ far_x,
                                                                uint32_t* __restrict__ far_idx)
 {
-    constexpr uint32_t kWords = 1;  // per thread
-    __shared__ uint16_t offsets[kThreads * kWords * 32];
+    __shared__ uint16_t offsets[kThreads * 32];
     __shared__ uint32_t wave_sum[kWaves];
     __shared__ uint32_t base;
-    const uint32_t w0 = (blockIdx.x * kThreads + threadIdx.x) * kWords;
-    uint32_t word[kWords], cnt = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < kWords; ++w) {
-        word[w] = w0 + w < words ? far_bits[w0 + w] : 0u;
-        if (word[w]) far_bits[w0 + w] = 0u;
-        cnt += __popc(word[w]);
-    }
+    const uint32_t at_word = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t word = at_word < words ? far_bits[at_word] : 0u, cnt = __popc(word);
+    if (word) far_bits[at_word] = 0u;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t incl = cnt;
     for (int off = 1; off < 64; off <<= 1) {
@@ -1011,12 +1005,10 @@ __global__ __launch_bounds__(kThreads) void far_compact_kernel(uint32_t* __restr
         total += wave_sum[w];
     }
     if (threadIdx.x == 0) base = total ? atomicAdd(&hdr->far_count, total) : 0u;
-#pragma unroll
-    for (uint32_t w = 0; w < kWords; ++w)
-        for (uint32_t bits = word[w]; bits != 0; bits &= bits - 1)
-            offsets[at++] = uint16_t((threadIdx.x * kWords + w) * 32 + uint32_t(__ffs(int(bits)) - 1));
+    for (uint32_t bits = word; bits != 0; bits &= bits - 1)
+        offsets[at++] = uint16_t(threadIdx.x * 32 + uint32_t(__ffs(int(bits)) - 1));
     __syncthreads();
-    const uint32_t rank0 = blockIdx.x * (kThreads * kWords * 32), b0 = base;
+    const uint32_t rank0 = blockIdx.x * (kThreads * 32), b0 = base;
     for (uint32_t e = threadIdx.x; e < total; e += kThreads) {  // dealt out evenly
         const uint32_t p = position[rank0 + offsets[e]], to = b0 + e;
         far_pos[to] = p;

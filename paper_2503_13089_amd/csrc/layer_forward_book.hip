@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "half_types.h"
 
 namespace cc {
 
@@ -27,28 +28,10 @@ constexpr uint32_t kXBytes = 28 * 1024;    // x values in LDS
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int DT>
-__device__ __forceinline__ float to_f32(uint32_t v)   // low 16 bits
-{
-    if constexpr (DT == 1) return float(__builtin_bit_cast(_Float16, uint16_t(v)));
-    else return __uint_as_float(v << 16);
-}
-template <int DT>
 __device__ __forceinline__ float hi_to_f32(uint32_t v)   // high 16 bits
 {
     if constexpr (DT == 1) return float(__builtin_bit_cast(_Float16, uint16_t(v >> 16)));
     else return __uint_as_float(v & 0xffff0000u);
-}
-
-template <int DT>
-__device__ __forceinline__ uint16_t from_f32(float v)
-{
-    if constexpr (DT == 1) {
-        return __builtin_bit_cast(uint16_t, _Float16(v));  // round to nearest even
-    } else {
-        const uint32_t b = __float_as_uint(v);
-        if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-        return uint16_t((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
-    }
 }
 
 template <int DT, int MB>
@@ -175,10 +158,10 @@ __global__ __launch_bounds__(kThreads) void layer_forward_book_kernel(const uint
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         const uint2 w = row[u][e];
-                        const float f[4] = {to_f32<DT>(w.x), hi_to_f32<DT>(w.x), to_f32<DT>(w.y), hi_to_f32<DT>(w.y)};
+                        const float f[4] = {to_f32<DT>(uint16_t(w.x)), hi_to_f32<DT>(w.x), to_f32<DT>(uint16_t(w.y)), hi_to_f32<DT>(w.y)};
 #pragma unroll
                         for (int m = 0; m < MB; ++m) {
-                            const float xf = e == 0 ? to_f32<DT>(xw[u][m]) : hi_to_f32<DT>(xw[u][m]);
+                            const float xf = e == 0 ? to_f32<DT>(uint16_t(xw[u][m])) : hi_to_f32<DT>(xw[u][m]);
 #pragma unroll
                             for (int j = 0; j < 4; ++j) acc[m][j] = __builtin_fmaf(xf, f[j], acc[m][j]);
                         }

@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "half_types.h"
 
 namespace cc {
 
@@ -55,25 +56,6 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     else
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-template <int DT>
-__device__ __forceinline__ float to_f32(uint16_t v)
-{
-    if constexpr (DT == 1) return float(__builtin_bit_cast(_Float16, v));
-    else return __uint_as_float(uint32_t(v) << 16);
-}
-
-template <int DT>
-__device__ __forceinline__ uint16_t from_f32(float v)
-{
-    if constexpr (DT == 1) {
-        return __builtin_bit_cast(uint16_t, _Float16(v));  // round to nearest even
-    } else {
-        const uint32_t b = __float_as_uint(v);
-        if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-        return uint16_t((b + 0x7fffu + ((b >> 16) & 1u)) >> 16);
-    }
 }
 
 // ---- 1. rebuild into B-operand fragments: column block nb = n / 32, in-feature block kb = k / 16, fragment

@@ -21,7 +21,6 @@ namespace cc {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kWaves = kThreads / 64;
 constexpr uint32_t kMaxBlocks = 512;      // two workgroups per compute unit
 constexpr uint32_t kMaxLds = 76 * 1024;   // two workgroups per compute unit next to the exchange buffers
 
