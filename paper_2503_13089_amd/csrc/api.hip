@@ -668,15 +668,27 @@ int cc_layer_weight(const void* codebook, int dtype, uint32_t K, uint32_t g, con
     return CC_OK;
 }
 
+namespace {
+// fp32 partial sums of the in-feature slices
+size_t fused_forward_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
+{
+    const uint32_t splits = cc::layer_forward_splits(M, in_features, out_features);
+    return splits > 1 ? cc::align256(size_t(splits) * M * out_features * 4) : 0;
+}
+// the rebuilt 16-bit weight (matrix-core operand layout), then the fp32 partial tiles of a contraction split over workgroups
+size_t dense_forward_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
+{
+    return cc::layer_weight_frag_bytes(in_features, out_features) + cc::layer_gemm_partial_bytes(M, in_features, out_features);
+}
+}  // namespace
+
 size_t cc_layer_forward_workspace_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
     if (M == 0 || M > (1ull << 22) || in_features == 0 || out_features == 0) return 0;
-    const uint32_t splits = cc::layer_forward_splits(M, in_features, out_features);
-    const size_t fused = splits > 1 ? cc::align256(size_t(splits) * M * out_features * 4) : 0;
-    if (!cc::dense_rows(M, in_features, out_features)) return fused;
-    // the rebuilt 16-bit weight (matrix-core operand layout), then the fp32 partial tiles of a contraction split over
-    // workgroups
-    return cc::layer_weight_frag_bytes(in_features, out_features) + cc::layer_gemm_partial_bytes(M, in_features, out_features);
+    // whatever the sub-vector length: from 128 rows on, or 65 of a large layer, room for the rebuilt route, up to 384 for both
+    const bool few = M < 128 && !(M > 64 && uint64_t(in_features) * out_features >= (1ull << 24));
+    const size_t fused = M <= 384 ? fused_forward_bytes(M, in_features, out_features) : 0;
+    return few ? fused : std::max(fused, dense_forward_bytes(M, in_features, out_features));
 }
 
 int cc_layer_forward(const void* x, uint64_t M, const void* codebook, int dtype, uint32_t K, uint32_t g,
@@ -689,14 +701,17 @@ int cc_layer_forward(const void* x, uint64_t M, const void* codebook, int dtype,
     if (in_features % 8 != 0) return fail(CC_ERR_SHAPE, "in_features = %u is not a multiple of 8", in_features);
     if (!aligned(x, 16) || !aligned(y, 16) || !aligned(codebook, 16) || !aligned(codes, 2) || (bias && !aligned(bias, 2)))
         return fail(CC_ERR_ALIGN, "x, y and codebook need 16-byte alignment");
-    const size_t need = cc_layer_forward_workspace_bytes(M, in_features, out_features);
+    const size_t fused_need = fused_forward_bytes(M, in_features, out_features), dense_need = dense_forward_bytes(M, in_features, out_features);
+    // a workspace that holds the rebuilt weight but not the slices' sums is good for the rebuilt route at any M
+    const bool dense = cc::dense_rows(M, g, in_features, out_features) || (workspace_bytes < fused_need && workspace_bytes >= dense_need);
+    const size_t need = dense ? dense_need : fused_need;
     if (need > 0) {
         if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
         if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
         if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (cc::dense_rows(M, in_features, out_features)) {
+    if (dense) {
         char* partial = static_cast<char*>(workspace) + cc::layer_weight_frag_bytes(in_features, out_features);
         CC_TRY_HIP(cc::launch_layer_weight_frag(codebook, K, g, codes, in_features, out_features, workspace, s), "layer weight");
         CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), workspace, dtype, in_features, out_features, nullptr, bias, y,

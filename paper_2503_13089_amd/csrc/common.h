@@ -440,20 +440,27 @@ hipError_t launch_layer_grad_planned(const void* grad, int dtype, uint32_t in_fe
                                      uint32_t g, uint32_t n, const void* plan, float* grad_codebook, void* workspace,
                                      hipStream_t s);
 // ---- prefill-sized batches (layer_gemm.hip): W rebuilt into memory, then one dense product on the matrix cores
-// From where on the rebuilt-weight route is the faster one. The fused kernels repeat their gathers per row tile (32,
-// 64, 96, ... rows), the rebuild costs the same for any number of rows (58 us for 45 M weights). Measured on
-// 4096 x 4096, 4096 x 11008, 11008 x 4096 and 8192 x 8192 (bf16, K = 65536, g = 4; fused / rebuilt + product, us):
-// 16-bit codebook: 4096 x 4096 at 64 rows 40 / 51, at 96 rows 59 / 53; 4096 x 11008 at 32 rows 71 / 94, at 48 rows
-// 108 / 94; 11008 x 4096 at 64 rows 73 / 94, at 96 rows 121 / 97; 8192 x 8192 at 64 rows 99 / 130, at 96 rows 165 / 133.
-// 4-bit codebook (the integer codebook is expanded first, + 5 us): 4096 x 4096 at 32 rows 49 / 55, at 48 rows 58 / 55;
-// 4096 x 11008 at 8 rows 56 / 96, at 16 rows 109 / 97; 11008 x 4096 at 16 rows 85 / 96, at 24 rows 99 / 97, at 32 rows
-// 101 / 97; 8192 x 8192 at 16 rows 112 / 131, at 32 rows 136 / 132, at 48 rows 150 / 134.
-inline bool dense_rows(uint64_t M, uint32_t in_features, uint32_t out_features)
+// From where on the rebuilt-weight route is the faster one: the fused kernel repeats its lookups for every 128 rows of x, the
+// rebuild takes the same for any number of rows, but longer where it moves rows element by element (all lengths but 4 and 8).
+// bf16, K = 65536, us, fused / rebuilt + product:
+//   g = 4: 8192 x 28672 at 128 rows 355 / 481, at 160 581 / 488; 4096 x 11008 96 / 93, 145 / 96; 8192 x 8192 112 / 132,
+//   175 / 136; 11008 x 4096 93 / 101, 136 / 105; 4096 x 4096 at 256 rows 68 / 71, at 384 96 / 68; 3072 x 3072 50 / 45, 67 / 58;
+//   2048 x 2048 37 / 34, 44 / 36; 1024 x 2048 at 384 rows 28 / 34, at 512 36 / 33.
+//   g = 8: 8192 x 28672 at 128 rows 235 / 370, at 160 424 / 378; 4096 x 10997 81 / 82, 107 / 84; 4096 x 4096 at 256 rows 56 / 69,
+//   at 384 81 / 62.
+//   g = 6: 8192 x 28672 at 384 rows 810 / 1170, at 768 1608 / 1322; 4096 x 10997 195 / 247, 347 / 276; 4096 x 4096 91 / 116,
+//   152 / 124. g = 9: 939 / 1161, 1679 / 1330; 233 / 254, 427 / 279; 97 / 116, 164 / 124. g = 5, 7, 12, 16: as 9.
+//   g = 3: 4096 x 10997 at 64 rows 194 / 215, at 128 234 / 218, at 160 388 / 220; 4096 x 4096 at 128 106 / 103. g = 2: 211 / 212, 76 / 99.
+inline bool dense_rows(uint64_t M, uint32_t g, uint32_t in_features, uint32_t out_features)
 {
     const uint64_t weights = uint64_t(in_features) * out_features;
-    if (weights < (1ull << 24)) return M >= 128;
-    return M > 64 || (weights >= (1ull << 25) && M > 32 && out_features >= 2 * uint64_t(in_features));
+    if (g < 4) return M > 128;
+    if (g != 4 && g != 8) return M > 384;
+    return M > (weights >= (1ull << 25) ? 128u : (weights >= (1ull << 22) ? 256u : 384u));
 }
+// The same with the 4-bit codebook (which the rebuild expands first, + 5 us), g = 4: 4096 x 4096 at 32 rows 48 / 49, at 48 57 / 50;
+// 4096 x 11008 at 8 rows 54 / 88, at 16 107 / 87; 11008 x 4096 at 16 rows 85 / 87, at 32 101 / 88, at 48 113 / 90; 8192 x 8192 at
+// 16 rows 111 / 121, at 32 136 / 121, at 48 150 / 125; 2048 x 2048 at 64 rows 26 / 33, at 96 40 / 34.
 inline bool dense_rows_q(uint64_t M, uint32_t in_features, uint32_t out_features)  // quantised codebook
 {
     const uint64_t weights = uint64_t(in_features) * out_features;
