@@ -6,12 +6,14 @@ and an M-step; the fit ends with the E-step and objective of the returned codebo
 iterations, each bracketed by a device synchronisation) and the headline is steps / median wall time, on the
 4096x11008, d=4, K=65536 workload with all inputs resident in HBM.
 
-`roofline` prices the dominant kernel of that same timed region - the E-step's scoring kernel as the fit launches it
-(windowed: it visits only the part of the codebook the triangle-inequality windows leave) - from HIP events that the
-library records around exactly those launches (cc_profile) and the number of (vector, centroid) pairs they scored
-(cc_stats). The whole-codebook kernels, the M-step and decode are measured after the timed region and reported under
-`kernels`; whole fits of the other benchmark configurations under `other_configs`; the CPU oracle timed on this
-box's host cores on a bounded sample of the same workload under `cpu_baseline`.
+`roofline` prices the E-step kernels that take most of that same timed region, from HIP events that the library records
+around exactly their launches (cc_profile) and the number of (vector, centroid) pairs they scored (cc_stats). A large fit
+has two kinds: lists of neighbouring centroids, which decide most vectors from the second E-step on (in direct form on
+the vector ALUs at d = 4), and windows of the codebook on the matrix cores for the first E-step and the vectors that the
+lists do not serve. The kind that takes longer is `roofline`; `kernels` has both. The whole-codebook kernels, the M-step
+and decode are measured after the timed region and reported under `kernels`; whole fits of the other benchmark
+configurations under `other_configs`; the CPU oracle timed on this machine's host cores on a bounded sample of the same
+workload under `cpu_baseline`.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload cfg3] [--repeats R] [--no-cpu-baseline]
                     [--only fit|estep_whole|estep_f32|update|decode|layer_forward|layer_forward_m1|layer_grad]   (one part per process, for counter runs)
@@ -40,9 +42,12 @@ VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4   # wave-instructions/s: 1024 SIMDs, one 64-l
 # reads 44,300 KiB x 2 dispatches on FETCH_SIZE and writes 88,580 KiB x 2 on WRITE_SIZE).
 _KIB = 1024.0
 MEASURED_TRAFFIC_BYTES = {
-    ("cfg3_4096x11008_d4_k65536", "fit_estep"): (147500 * 1.988 + 97360 * 0.994) * _KIB,     # windowed kernel, mean of 44 launches
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_direct"): (168500 * 1.988 + 115000 * 0.994) * _KIB,   # near_direct_kernel, mean of 40 launches
+    # far_kernel (20 a fit) and assign_mfma_f16_kernel (2 a fit)
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_f16"): ((20 * 16570 + 2 * 130100) * 1.988 + (20 * 8710 + 2 * 66370) * 0.994) / 22 * _KIB,
     ("cfg3_4096x11008_d4_k65536", "estep_whole"): (283040 * 1.988 + 88480 * 0.994) * _KIB,
-    ("cfg3_4096x11008_d4_k65536", "update"): ((110200 + 18450) * 1.988 + (36860 + 3328) * 0.994) * _KIB,  # both kernels
+    # slice_chunk_kernel, sliced_accumulate_kernel, sliced_finalize_kernel
+    ("cfg3_4096x11008_d4_k65536", "update"): ((110200 + 125100 + 22270) * 1.988 + (44230 + 37030 + 6294) * 0.994) * _KIB,
     ("cfg3_4096x11008_d4_k65536", "decode"): (26120 * 1.988 + 176100 * 0.994) * _KIB,
 }
 
@@ -239,7 +244,8 @@ def main():
     out = torch.empty_like(Xd)
     C0d = Cd.clone()
     # device time of the E-step scoring kernels inside the timed fits (two event records per launch)
-    prof = cc.Profile(max_records=64 * (args.steps + 4), slots=("estep_f16", "estep_f32", "estep_direct"))
+    slots = ("estep_f32",) if mode == 2 else ("estep_f16", "estep_direct")   # the inputs are fp16 numbers
+    prof = cc.Profile(max_records=64 * (args.steps + 4), slots=slots)
 
     def job(iters, profile=None):
         cc.kmeans_fit(Xd, K, iters, C0d, Cd, idx, J, ws, assign_mode=mode, profile=profile)
@@ -252,7 +258,7 @@ def main():
     if args.warmup > 0:
         job(args.warmup)
     walls, prof_ms, prof_n = [], dict.fromkeys(cc.PROFILE_SLOTS, 0.0), dict.fromkeys(cc.PROFILE_SLOTS, 0)
-    scored = total = refined = assigns = 0
+    scored = total = in_lists = refined = assigns = 0
     for _ in range(max(1, args.repeats)):
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -267,30 +273,53 @@ def main():
             prof_n[k] += launches[k]
         scored += st.scored_stages
         total += st.total_stages
+        in_lists += st.list_stages
         refined += st.refined_vectors
         assigns += st.assign_calls
     wall = statistics.median(walls)
     ms_per_step = wall * 1e3 / args.steps
     final_objective = float(J.item())
 
-    # the dominant kernel of the timed region: the E-step scoring kernel that ran (the other variants return at once)
-    slot = max(("estep_f16", "estep_f32", "estep_direct"), key=lambda k: prof_ms[k])
-    launches_per_job = prof_n[slot] / len(walls)
-    launch_ms = prof_ms[slot] / max(1, prof_n[slot])
-    # (vector, centroid) pairs scored per launch: with windows, the stages (32 centroids) each 512-vector tile scored
-    pairs_per_launch = (scored * 32.0 * 512.0 / prof_n[slot]) if total else float(N) * K
-    flop_per_launch = 2.0 * d * pairs_per_launch
+    # the E-step kernels of the timed region, by kind (a variant whose inputs do not qualify returns at once)
     km = 1 if d <= 8 else 2            # fp16 MFMAs per (32 centroids x 32 vectors) tile: 16 k slots each
-    if slot == "estep_f16":
-        bound, peak, unit = "mfma", F16_MFMA_PEAK_TFLOPS, "TFLOP/s"
-        kernel = "assign_mfma_f16_kernel (E-step scoring, fp16 matrix cores)" + (", windowed" if total else "")
-    elif slot == "estep_f32":
-        bound, peak, unit = "mfma", FP32_PEAK_TFLOPS, "TFLOP/s"
-        kernel = "assign_mfma_kernel (E-step scoring, fp32 matrix cores)" + (", windowed" if total else "")
-    else:
-        bound, peak, unit = "alu", FP32_PEAK_TFLOPS, "TFLOP/s"
-        kernel = "assign_direct_kernel (E-step, direct form on the vector ALUs)"
-    achieved = flop_per_launch / (launch_ms * 1e-3) / 1e12
+    pairs_unit = 32.0 * 512.0          # (vector, centroid) pairs of one stage: 32 centroids x 512 vectors
+    by_lists = in_lists > 0 and prof_n["estep_direct"] > 0    # d = 4: lists and windows are separate records
+
+    def estep(slot):
+        """Roofline entry of one slot's launches in the timed fits."""
+        n = prof_n[slot]
+        ms_ = prof_ms[slot] / n
+        if slot == "estep_direct" and by_lists:
+            pairs, kernel = in_lists * pairs_unit / n, "near_direct_kernel (vectors on the list of their cell, direct form)"
+        elif slot == "estep_direct":
+            pairs, kernel = float(N) * K, "E-step in direct form on the vector ALUs (assign_direct_kernel, or small_iter_kernel with the sums)"
+        else:
+            scored_here = (scored - in_lists) if by_lists else scored
+            pairs = scored_here * pairs_unit / n if total else float(N) * K
+            if slot == "estep_f32":
+                kernel = "assign_mfma_kernel (E-step scoring, fp32 matrix cores)" + (", windowed" if total else "")
+            elif by_lists:
+                kernel = "assign_mfma_f16_kernel (first E-step) and far_kernel (vectors without a list), windows on the fp16 matrix cores"
+            elif in_lists:
+                kernel = "near_mfma_kernel (lists), far_kernel and assign_mfma_f16_kernel (windows), fp16 matrix cores"
+            else:
+                kernel = "assign_mfma_f16_kernel (E-step scoring, fp16 matrix cores)" + (", windowed" if total else "")
+        bound, peak = ("mfma", F16_MFMA_PEAK_TFLOPS) if slot == "estep_f16" else (("mfma", FP32_PEAK_TFLOPS) if slot == "estep_f32"
+                                                                                else ("alu", FP32_PEAK_TFLOPS))
+        flop = 2.0 * d * pairs
+        rate = flop / (ms_ * 1e-3) / 1e12
+        # wave-instructions that the form cannot do without: one v_min3_f32 per two scores of the matrix cores, or the
+        # distance, its comparison and two selects
+        instr = pairs * (2 * d + 3) / 64.0 if slot == "estep_direct" else pairs / 128.0
+        return {"bound": bound, "kernel": kernel, "achieved": rate, "peak": peak, "unit": "TFLOP/s", "frac": rate / peak,
+                "traffic": MEASURED_TRAFFIC_BYTES.get((w.name, "fit_" + slot)) if by_lists else None,
+                "flop_per_launch": flop, "pairs_per_launch": pairs, "avg_ms": ms_, "launches_per_job": n / len(walls),
+                "ms_per_step_in_this_kernel": prof_ms[slot] / len(walls) / args.steps,
+                "work": "2 d flop per (vector, centroid) pair actually scored: scored stages x 32 centroids x 512 vectors, "
+                        "summed over the launches (cc_stats), not the whole N x K"}, instr / (ms_ * 1e-3)
+
+    slot = max(slots, key=lambda k: prof_ms[k])
+    roofline, instr_rate = estep(slot)
 
     def timed(fn, reps=3):
         fn()
@@ -378,23 +407,20 @@ def main():
                    "assign_mode": mode, "final_objective": final_objective,
                    "scored_codebook_fraction": (scored / total if total else 1.0),
                    "refined_vectors_per_assign": refined / max(1, assigns)},
-        # the dominant kernel of the timed region, per launch, averaged over all its launches in the timed fits
-        "roofline": {"bound": bound, "kernel": kernel, "achieved": achieved, "peak": peak, "unit": unit,
-                     "frac": achieved / peak, "traffic": MEASURED_TRAFFIC_BYTES.get((w.name, "fit_estep")),
-                     "flop_per_launch": flop_per_launch, "pairs_per_launch": pairs_per_launch, "avg_ms": launch_ms,
-                     "launches_per_job": launches_per_job,
-                     "ms_per_step_in_this_kernel": launch_ms * launches_per_job / args.steps,
-                     "work": "2 d flop per (vector, centroid) pair actually scored: scored stages x 32 centroids x "
-                             "512 vectors, summed over the launches (cc_stats), not the whole N x K"},
-        # the same launches against the unit that binds the fp16 variant: one v_min3_f32 per two scores on the vector ALUs
-        "roofline_alu": {"bound": "alu", "kernel": kernel, "achieved": pairs_per_launch / 128.0 / (launch_ms * 1e-3) / 1e9,
-                         "peak": VALU_ISSUE_PEAK / 1e9, "unit": "G wave-instr/s",
-                         "frac": pairs_per_launch / 128.0 / (launch_ms * 1e-3) / VALU_ISSUE_PEAK, "traffic": None},
+        # per launch, averaged over all launches of that kind in the timed fits
+        "roofline": roofline,
+        # the same launches against the issue rate of the vector ALUs
+        "roofline_alu": {"bound": "alu", "kernel": roofline["kernel"], "achieved": instr_rate / 1e9,
+                         "peak": VALU_ISSUE_PEAK / 1e9, "unit": "G wave-instr/s", "frac": instr_rate / VALU_ISSUE_PEAK, "traffic": None},
         "standalone_lloyd_iter_ms": iter_ms,
         "kernels": kernels,
     }
-    if slot == "estep_f16":
-        line["roofline"]["issued_mfma_slot_frac"] = 2.0 * 16 * km * pairs_per_launch / (launch_ms * 1e-3) / 1e12 / F16_MFMA_PEAK_TFLOPS
+    if slot == "estep_f16" and (by_lists or not in_lists):   # the lists at d = 8 take another instruction
+        roofline["issued_mfma_slot_frac"] = (2.0 * 16 * km * roofline["pairs_per_launch"] / (roofline["avg_ms"] * 1e-3) / 1e12
+                                             / F16_MFMA_PEAK_TFLOPS)
+    if by_lists:
+        for kind in ("estep_direct", "estep_f16"):
+            kernels["estep_lists" if kind == "estep_direct" else "estep_windows"] = dict(estep(kind)[0], valu_issue_frac=estep(kind)[1] / VALU_ISSUE_PEAK)
     if layer is not None:
         line["layer_kernels"] = layer
     del ws, out, Xd

@@ -100,13 +100,16 @@ typedef struct cc_options {
  * Device time of the library's kernels, measured with HIP events recorded on the stream of the call that the
  * profile is passed to (for benchmarks: the time of the dominant kernel inside a whole fit). Each launch - or short
  * run of launches - named by a slot takes one record:
- *   CC_PROF_ESTEP_F16     the scoring kernel of the E-step on the fp16 matrix cores, one record per launch
+ *   CC_PROF_ESTEP_F16     the scoring kernels of the E-step on the fp16 matrix cores, one record per launch; inside a
+ *                         large fit also the lists of the near vectors at d = 5..8 (two launches, one record) and the
+ *                         windows of the far vectors
  *   CC_PROF_ESTEP_F32     the same on the fp32 matrix cores (both are enqueued; the one whose inputs do not
  *                         qualify returns at once)
- *   CC_PROF_ESTEP_DIRECT  the direct-form E-step kernel
+ *   CC_PROF_ESTEP_DIRECT  the direct-form E-step kernel; inside a large fit the lists of the near vectors at d <= 4
  *   CC_PROF_REFINE        re-decision of the guard-band vectors
  *   CC_PROF_MSTEP         all kernels of one M-step
- *   CC_PROF_ORDER         key ordering of vectors / centroids, window lists
+ *   CC_PROF_ORDER         key ordering of vectors / centroids, grouping by code, neighbour lists, list of the far
+ *                         vectors, window lists
  * cc_profile_create allocates (host memory and max_records pairs of events) and is the only profile call that does;
  * slot_mask selects the slots to record (bit s = slot s) - an event pair costs a few microseconds of stream time.
  * cc_profile_read waits for the recorded events (it synchronises with the work they bracket), adds up ms[slot]
@@ -208,13 +211,14 @@ typedef struct cc_stats {
     uint64_t skipped_vectors;  /* vectors with idx >= K seen by an update */
     uint64_t assign_calls;     /* assign passes run */
     uint64_t scored_stages;    /* window pruning: codebook tiles (32 centroids) scored, summed over the
-                                  512-vector tiles of all assigns; 0 when pruning did not run */
+                                  512-vector tiles of all assigns; 0 when pruning did not run. Inside a large fit: of the
+                                  far vectors' tiles, and the pairs on the lists (d = 5..8: their inner part) in that unit */
     uint64_t total_stages;     /* the same sum if every tile had scored the whole codebook */
     int32_t  fixed_point_exp;  /* e: cluster sums are held as round(x * 2^e) in int64 */
     uint32_t fp16_inputs;      /* 1 if the vectors of the last call qualified for the fp16 matrix-core kernels
                                   (|x| < 2^15 and every |x| >= 2^-14 an fp16 number), else 0 */
     uint32_t nonfinite_inputs; /* 1 if some input of the last call was Inf or NaN (a violated precondition) */
-    uint32_t reserved;
+    uint32_t list_stages;      /* the part of scored_stages on lists (at most 2^32 - 1) */
 } cc_stats;
 int cc_read_stats(const void *workspace, size_t workspace_bytes, cc_stats *host_out, void *stream);
 

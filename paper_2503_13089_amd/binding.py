@@ -35,7 +35,7 @@ class _CStats(ctypes.Structure):
     _fields_ = [("refined_vectors", ctypes.c_uint64), ("skipped_vectors", ctypes.c_uint64),
                 ("assign_calls", ctypes.c_uint64), ("scored_stages", ctypes.c_uint64),
                 ("total_stages", ctypes.c_uint64), ("fixed_point_exp", ctypes.c_int32),
-                ("fp16_inputs", ctypes.c_uint32), ("nonfinite_inputs", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
+                ("fp16_inputs", ctypes.c_uint32), ("nonfinite_inputs", ctypes.c_uint32), ("list_stages", ctypes.c_uint32)]
 
 
 class _COptions(ctypes.Structure):
@@ -55,6 +55,7 @@ class Stats:
     fixed_point_exp: int
     fp16_inputs: int = 0
     nonfinite_inputs: int = 0
+    list_stages: int = 0
 
 
 def lib_path() -> str:
@@ -316,7 +317,7 @@ def read_stats(workspace) -> Stats:
     _check(load_library().cc_read_stats(_ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
                                         ctypes.byref(st), _stream()))
     return Stats(int(st.refined_vectors), int(st.skipped_vectors), int(st.assign_calls), int(st.scored_stages),
-                 int(st.total_stages), int(st.fixed_point_exp), int(st.fp16_inputs), int(st.nonfinite_inputs))
+                 int(st.total_stages), int(st.fixed_point_exp), int(st.fp16_inputs), int(st.nonfinite_inputs), int(st.list_stages))
 
 
 def mfma_f16_probe(A, B, C, D) -> None:

@@ -1,5 +1,6 @@
 // C ABI of libcluscomp: argument validation on the host, then the kernel sequence of each call.
 // See include/cluscomp.h for the contract of every entry point.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -180,12 +181,19 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     wf.xsorted = f.x; wf.idx_sorted = f.idx; wf.refine_list = f.refine; wf.refine_cap = N;
     const uint32_t* far_count = &w.hdr->far_count;
     {
-        cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
+        cc::ProfileScope scope(cx.prof, d == 4 ? cc::kProfEstepDirect : cc::kProfEstepF16, s);
         CC_TRY_HIP(cc::launch_cells_near(C, N, d, K, w, track, s), "assign (near vectors)");
+    }
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_cells_compact(N, d, w, s), "assign (list of the far vectors)");
         CC_TRY_HIP(cc::launch_windows(C, N, d, K, wf, 0.0f, s, far_count), "assign (windows of the far vectors)");
+    }
+    {
+        cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
         CC_TRY_HIP(cc::launch_cells_far(N, d, K, w, s), "assign (far vectors)");
     }
-    // inputs that are not fp16 numbers: every vector is far, and the fp32 variant scores it
+    // inputs that are not fp16 numbers: the fp32 variant scores the far vectors (all of them where no lists can be made)
     cc::EStep e{};
     e.X = f.x; e.N = N; e.n_dev = far_count; e.out_pos = f.pos;
     e.pack_rows = C; e.pack_perm = w.cperm; e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
@@ -994,7 +1002,7 @@ int cc_read_stats(const void* workspace, size_t workspace_bytes, cc_stats* host_
     host_out->fixed_point_exp = h.fixed_point_exp;
     host_out->fp16_inputs = h.x_not_f16 == 0 ? 1u : 0u;
     host_out->nonfinite_inputs = h.x_nonfinite != 0 ? 1u : 0u;
-    host_out->reserved = 0;
+    host_out->list_stages = uint32_t(std::min<unsigned long long>(h.list_stages, 0xffffffffull));
     return CC_OK;
 }
 

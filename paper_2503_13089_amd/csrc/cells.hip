@@ -534,7 +534,9 @@ __global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __res
         // statistics: pairs the near vectors look at, in units of (512 vectors x 32 centroids)
         for (int off = 32; off > 0; off >>= 1) scored += __shfl_xor(scored, off, 64);
         if (lane == 0) {
-            atomicAdd(&hdr->window_stages, static_cast<unsigned long long>(scored / 16384.0f + 1.0f));
+            const auto stages = static_cast<unsigned long long>(scored / 16384.0f + 0.5f);
+            atomicAdd(&hdr->window_stages, stages);
+            atomicAdd(&hdr->list_stages, stages);
             if (blockIdx.x == 0)
                 atomicAdd(&hdr->window_total, static_cast<unsigned long long>((N + kWinTile - 1) / kWinTile) * ((K + 31) / 32));
         }
@@ -1199,7 +1201,7 @@ void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& 
 template <int D>
 void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, hipStream_t s)
 {
-    const uint32_t words = (N + 31) / 32, slots = N / item_of(D) + K;
+    const uint32_t slots = N / item_of(D) + K;
     const FarView f = far_view(w, N, D);
     const NearArgs a{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, slots,
                      w.cell_lists, w.cell_rank, w.far_bits, f.pos, w.idx_sorted, w.dmin,
@@ -1211,6 +1213,13 @@ void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bo
         hipLaunchKernelGGL(near_mfma_kernel<false>, grid, dim3(kThreads), 0, s, a);
         hipLaunchKernelGGL(near_mfma_kernel<true>, grid, dim3(kThreads), 0, s, a);
     }
+}
+
+template <int D>
+void cells_compact_t(uint32_t N, const Workspace& w, hipStream_t s)
+{
+    const uint32_t words = (N + 31) / 32;
+    const FarView f = far_view(w, N, D);
     hipLaunchKernelGGL(far_compact_kernel<D>, dim3((words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.far_bits, words,
                        w.cell_position, w.xsorted, w.idx_sorted, w.hdr, f.pos, f.x, f.idx);
 }
@@ -1253,6 +1262,16 @@ hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K,
     switch (d) {
         case 4: cells_near_t<4>(C, N, K, w, track, s); break;
         case 8: cells_near_t<8>(C, N, K, w, track, s); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s)
+{
+    switch (d) {
+        case 4: cells_compact_t<4>(N, w, s); break;
+        case 8: cells_compact_t<8>(N, w, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -65,6 +65,7 @@ struct WsHeader {
     int32_t fixed_point_exp;
     uint32_t x_nonfinite;      // != 0: some input is Inf or NaN (the sums then skip such components)
     uint32_t far_count;        // E-step by cells: vectors that go through the windowed pass
+    unsigned long long list_stages;     // E-steps by cells: the part of window_stages that was scored on lists
 };
 
 // Survives between calls on the same workspace (not touched by the per-call header reset): whether the
@@ -324,12 +325,13 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool 
 // vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order, and the codes change
 // places with w.idx_prev: at the end a next call can put them into the norm order, kHintByCells); launch_cells_centroids
 // orders the current centroids and makes their operands and the lists of the cells; launch_cells_near decides the near
-// vectors and leaves the far ones as a list of hdr->far_count entries in the arrays of far_view; launch_cells_far
-// decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
+// vectors; launch_cells_compact leaves the far ones as a list of hdr->far_count entries in the arrays of far_view;
+// launch_cells_far decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
                               bool first, hipStream_t s);
 hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool first, hipStream_t s);
 hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s);
+hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t value, hipStream_t s);
 struct FarView {

@@ -29,6 +29,7 @@ __global__ void reset_header_kernel(WsHeader* hdr)
         hdr->window_total = 0;
         hdr->fixed_point_exp = 0;
         hdr->x_nonfinite = 0;
+        hdr->list_stages = 0;
     }
 }
 

@@ -111,3 +111,28 @@ def test_cells_that_begin_with_one_vector_get_lists_when_they_grow(N, d, K):
     # tiles of 32 centroids per 512 vectors and E-step: 0.3 to 0.5 where the lists serve them, 2.8 to 3.0 where half of the
     # vectors go through the windows in every one
     assert (scored[1] - scored[0]) / 5 < 1.4 * N / 512
+
+
+@pytest.mark.parametrize("N,d,K", [(N4, 4, 1024), (N8, 8, 1024)])
+def test_profile_and_statistics_tell_lists_from_windows(N, d, K):
+    import paper_2503_13089_amd as cc
+    from tests import gpu_helpers as g
+
+    X, C0 = workloads.make_small(N, d, K, seed=5)
+    Xd, C0d, ws, iters = g.dev(X), g.dev(C0), g.workspace(N, d, K), 5
+    C, idx = torch.empty_like(C0d), torch.empty(N, dtype=torch.uint32, device="cuda")
+    prof = cc.Profile(max_records=512)
+    print(f"profile of a fit by cells N={N} d={d} K={K}", flush=True)
+    cc.kmeans_fit(Xd, K, iters, C0d, C, idx, None, ws, profile=prof)
+    ms, launches, dropped = prof.read()
+    prof.close()
+    st = cc.read_stats(ws)
+    # a bootstrap and a first E-step by windows, `iters` more by cells: lists (direct form at d = 4), then far vectors
+    assert dropped == 0 and launches["estep_direct"] == (iters if d == 4 else 0)
+    assert launches["estep_f16"] == 2 + (iters if d == 4 else 2 * iters)
+    assert all((ms[k] > 0.0) == (n > 0) for k, n in launches.items())
+    # every vector meets at least its own centroid, none more than there are (pairs in units of 32 x 512; each of the K / 32
+    # workgroups rounds its share)
+    pairs = st.list_stages * 16384.0
+    slack = iters * 16384.0 * K / 32
+    assert iters * N - slack <= pairs <= iters * N * K + slack and st.list_stages <= st.scored_stages
