@@ -293,19 +293,20 @@ int cc_layer_forward(const void *x, uint64_t M, const void *codebook, int dtype,
  * [in_features * out_features] (grad_dtype) over the entries rebuilt from codebook[k][j]. Sums are
  * accumulated in 64-bit fixed point scaled from max |grad|: deterministic, exact for 16-bit gradients, and
  * within 2^-38 * max |grad| per term otherwise. Gradients must be finite.
- * A 16-bit gradient of a layer with at least 2^20 codes, g = 4, 8 or 16 and out_features a multiple of g is read
+ * A 16-bit gradient of a layer with at least 32768 codes, g = 4, 8 or 16 and out_features a multiple of g is read
  * where it lies if grad_weight is 16-byte and codes 4-byte aligned (same bits, about a third of the time);
  * every other case goes through an fp32 copy of the gradient in the workspace.
- * Workspace: cc_workspace_bytes(num_codes, g, K) bytes.
+ * Workspace: cc_workspace_bytes(max(num_codes, K), g, K) bytes.
  */
 int cc_layer_codebook_grad(const void *grad_weight, int grad_dtype, uint32_t in_features, uint32_t out_features,
                            const uint16_t *codes, uint32_t K, uint32_t g, float *grad_codebook,
                            void *workspace, size_t workspace_bytes, void *stream);
 
 /*
- * The same gradient for training loops (Section 3.3: only the codebook is trained, the codes of a layer never
- * change): cc_layer_grad_plan orders the code positions by cluster once; cc_layer_codebook_grad_planned then
- * reads every gradient entry once, straight from grad_weight, and adds each cluster's entries in fp64 in a
+ * The same gradient from an order of the codes prepared once (Section 3.3: only the codebook is trained, the codes of
+ * a layer never change), for gradients that the call above does not read where they lie: cc_layer_grad_plan orders
+ * the code positions by cluster once; cc_layer_codebook_grad_planned then reads every gradient entry once, straight
+ * from grad_weight, and adds each cluster's entries in fp64 in a
  * fixed order (same inputs, same bits; each sum is within count * 2^-53 * sum |terms| of exact before its one
  * rounding to fp32, i.e. the rounded exact sum for 16-bit gradients in practice). Codes >= K are left out.
  *   plan       device memory, cc_layer_grad_plan_bytes(num_codes, K) bytes, 256-byte aligned; written by

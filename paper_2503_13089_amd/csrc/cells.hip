@@ -7,11 +7,15 @@
 // Once per E-step every centroid gets the list of the centroids within a radius R of it; the vectors of its cell with
 // t(x) <= R ("near") are decided on that list alone. It is 10^2 .. 10^3 times shorter than the codebook where the
 // (norm, cosine) windows of sort.hip leave 3 % (d = 4) or 66 % (d = 8) of it: a ball in d dimensions against a shell.
-// The other vectors ("far", a few per cent) are collected in the norm order and go through the windowed matrix-core
-// E-step. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
+// The other vectors ("far", 0.7 to 4 %) are collected and go through a windowed matrix-core E-step, 512 to a window. Those of
+// one run of 8192 norm ranks lie together, in order, but the runs in the order in which workgroups come by: with some 60
+// far vectors a run, a window of the 4096x11008 matrix spans a factor of 3 in norm where 4 % would do. That is what far_kernel
+// takes its time for (4.4 of the 20.5 ms of that fit), and why a fit's time moves by 1 to 2 % with anything that moves the
+// timing of far_compact_kernel. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
-// Measured, E-step of a later iteration: N = 11 M, d = 4, K = 65536: 0.78 ms with 1 to 4 % far (1.2 ms by windows);
-// N = 29 M, d = 8: 7.5 ms with 2 % far (53 ms).
+// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.21, far ones 0.04 to collect and
+// 0.15 to 0.4 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
+// to 3.3, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.09, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
 // against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
@@ -329,8 +333,10 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         }
         const _Float16 o = _Float16(0.0f);
         to[3] = f16x8{g[0], g[1], g[2], o, o, o, o, o};
-        if (k == 0) {   // row K never wins: a norm of 60000 * 2^8 is above every score (at most 2^23 + 2^24), and finite so
-                        // that a tag leaves it a number
+        if (k == 0) {   // row K never wins, and is finite so that a tag leaves it a number. Its score is 60000 * 2^8 = 1.54e7. The
+                        // best of a near vector is below 5.9e6: its cell's centroid and its previous code are both on the list
+                        // and their distances add up to R at most, so one of them is within R / 2; and where there is a list,
+                        // sigma R^2 <= 1.5e7 + sigma ||c||^2 <= 1.5e7 + 2^23.
             f16x8* none = reinterpret_cast<f16x8*>(flat + size_t(K) * 64);
             none[0] = none[1] = none[2] = f16x8{o, o, o, o, o, o, o, o};
             none[3] = f16x8{_Float16(60000.0f), o, o, o, o, o, o, o};
@@ -600,6 +606,8 @@ __device__ __forceinline__ float cell_bound(const float (&x)[D], const float (&c
 
 // ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
 // Direct-form distances are final: no guard band and no index recovery. Rows past the list are NaN and never win.
+// Bound: vector instructions, 19 per 64 (vector, entry) pairs by the counters where the distance, its comparison and two selects
+// are 11; 0.49 G pairs in 0.21 ms (lists of 43 entries, N = 11 M).
 template <int D, int NV>
 __device__ __forceinline__ void scan_list(const float4* rows, uint32_t L, const float (&x)[4][D], float (&bd)[4], uint32_t (&bp)[4],
                                           unsigned long long& ties)
@@ -711,19 +719,18 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
 }
 
 // ---- near vectors, d = 8: matrix cores over the list -----------------------------------------------------------------
-// A workgroup of W waves takes up to 64 W vectors of one cell (W = 8; 1 where the cells are small), each wave 64 of them. The
-// operands of the list's centroids (64 bytes each, one cache line) are laid out for v_mfma_f32_16x16x32_f16: 32 k slots hold
-// the 24 products of d = 8 and sigma ||c||^2, so that scores need no accumulator to start from. With several waves they go
-// through LDS, a wave of its own gathers them straight into registers. Four tiles of 16 centroids are folded two and two row
-// by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
+// A wave takes up to 64 vectors of one cell and works alone. The operands of the list's centroids (64 bytes each, one cache
+// line) are laid out for v_mfma_f32_16x16x32_f16: 32 k slots hold the 24 products of d = 8 and sigma ||c||^2, so that scores
+// need no accumulator to start from; the wave gathers them straight into registers. Four tiles of 16 centroids are folded
+// two and two row by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
 // instructions per 1024 scores. The winner is then known up to 2 centroids: two direct-form distances. What the tag costs
 // in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction is
-// within 4.5 x 2^-24 of the sum of its terms in tests/test_gpu_mfma_bound16.py; 16 is assumed); a vector whose second best comes within the band is
-// decided in direct form over the list, 64 centroids at a time.
+// within 4.5 x 2^-24 of the sum of its terms in tests/test_gpu_mfma_bound16.py; 16 is assumed); a vector whose second best
+// comes within the band is decided in direct form over the list, 64 centroids at a time.
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
-// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 1.9 ms + 2.7 ms per E-step, N = 2.8 M: 0.26 ms +
-// 0.16 ms, where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
+// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.7 ms per E-step, N = 2.8 M: 0.27 ms +
+// 0.14 ms, where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
 // list, operands, scores, rows), so a wave works alone and keeps 64 vectors at four waves per SIMD: workgroups that shared
 // the list through LDS, 128 vectors per wave, took 6.1 to 7.8 ms for the same.
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -392,8 +392,8 @@ hipError_t launch_update_buckets(const float* X, uint32_t N, uint32_t d, const u
                                  uint32_t K, float* out, uint32_t* counts_out, const Workspace& w, bool norm_order,
                                  bool mean, hipStream_t s, const uint32_t* prev_idx = nullptr,
                                  const uint32_t* changed = nullptr, bool by_cluster = false);
-// M-step by cluster slices (update_sliced.hip): one pass over the codes per slice of the clusters, LDS accumulators,
-// no copy of the vectors; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
+// M-step by cluster slices (update_sliced.hip): each chunk's codes sorted by slice, then one LDS accumulation per slice of the
+// clusters, no copy of the vectors; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
 // result bits as the other formulations. `out` may alias `prev`.
 bool update_sliced_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
 // Whether all clusters fit one slice, i.e. the pass needs neither lists nor a second look at a code.

@@ -372,7 +372,8 @@ __global__ void persist_check_kernel(WsPersist* persist, uint32_t N, uint32_t d,
     }
 }
 
-// The codes that a fit by cells left, into the norm order: 4-byte gathers, 103 us for 11 M vectors of 4 (call 2.87 -> 2.15 ms), 0.40 ms for 29 M of 8 (63.8 -> 51.4).
+// The codes that a fit by cells left, into the norm order: 4-byte gathers, 103 us for 11 M vectors of 4 (the call 2.87 -> 2.15
+// ms), 0.40 ms for 29 M of 8 (63.8 -> 51.4).
 // Left to the call that wants them: at the end of the fit it would be 2 % of its time. Whatever the arrays hold, reads stay inside.
 __global__ __launch_bounds__(kThreads) void hint_from_cells_kernel(const WsPersist* persist, const uint32_t* __restrict__ codes,
                                                                    const uint32_t* __restrict__ position, uint32_t N,

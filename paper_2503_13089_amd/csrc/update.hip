@@ -193,7 +193,7 @@ hipError_t launch_update(const float* X, uint32_t N, uint32_t d, const uint32_t*
 {
     hipError_t e;
     if (update_sliced_applies(N, d, K, w)) {
-        // many vectors: one pass over the codes per slice of the clusters, sums in LDS, the vectors are not copied
+        // codes sorted by slice of the clusters, sums in LDS, the vectors are not copied
         return launch_update_sliced(X, N, d, idx, prev, K, out, counts_out, w, mean, false, s);
     } else if (w.bucket_ok && N >= 32768) {
         // memory-side atomics are the bottleneck of the scatter formulation: group by bucket, sum in LDS

@@ -14,10 +14,10 @@
 // of the result.
 //
 // Because the sums are integers they can also be kept up to date instead of recomputed: inside a fit, from
-// the third iteration on, only the vectors whose code changed since the previous iteration go through the
-// four steps (18 % of them in the second iteration of the 4-bit benchmark, 2 % in the twentieth), each as
-// two records - plus for the new cluster, minus for the old one - and step 4 adds the bucket's net change
-// to the sums and counts that the previous iteration left in the workspace. Bit-identical to a recomputation.
+// the third iteration on (the second of a fit by cells), only the vectors whose code changed since the previous
+// iteration go through the four steps (18 % of them in the second iteration of the 4-bit benchmark, 2 % in the
+// twentieth), each as two records - plus for the new cluster, minus for the old one - and step 4 adds the bucket's
+// net change to the sums and counts that the previous iteration left in the workspace. Bit-identical to a recomputation.
 // The E-step kernel that produced the codes leaves a bitmap of the vectors that may have changed (and their
 // previous code), so steps 1 and 3 read one bit per vector instead of two code arrays.
 #include <algorithm>

@@ -24,7 +24,7 @@ def test_fits_by_cells_have_the_bits_of_the_direct_form(N, d, K, iters, kind):
 
     X, C0 = workloads.make_small(N, d, K, seed=N + d + K)
     rng = np.random.default_rng(K)
-    if kind == "fp32":          # no fp16 numbers: every vector goes through the fp32 windows
+    if kind == "fp32":          # no fp16 numbers: lists from their fp16 parts, far vectors on the fp32 matrix cores
         X = (X * np.float32(1.0009)).astype(np.float32)
     elif kind == "clumped":     # more centroids close together than a list has room for, and exact duplicates
         C0 = C0.copy()
