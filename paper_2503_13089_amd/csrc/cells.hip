@@ -14,7 +14,7 @@
 // timing of far_compact_kernel. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
 // Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.21, far ones 0.04 to collect and
-// 0.15 to 0.4 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
+// 0.13 to 0.6 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
 // to 3.3, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.09, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
