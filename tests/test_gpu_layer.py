@@ -294,8 +294,8 @@ FORWARD_CASES = [  # (M, in_features, out_features, g, K, bias)
     (32, 1024, 1024, 8, 65536, True),
     (5, 64, 70, 7, 3, False),
     (200, 4096, 256, 4, 65536, False),
-    # few rows: M <= 4 with g = 4 takes a kernel of its own (one lane per code column, a register block per row count);
-    # the same kind of shape with g = 8 or more rows stays with the tile kernel
+    # few rows: one or two with g = 4 and many codes per codebook row take a kernel of their own (the codebook through LDS in
+    # parts, tests/test_gpu_forward_book.py), the others the tile kernel
     (2, 136, 200, 8, 300, True),      # in_features not a multiple of the 16 rows a round of the 8 waves takes
     (3, 1048, 1000, 4, 65536, False),
     (4, 4096, 1280, 4, 65536, True),  # several slices of in_features
@@ -306,7 +306,8 @@ FORWARD_CASES = [  # (M, in_features, out_features, g, K, bias)
     (9, 264, 333, 4, 1000, True),     # padding columns, ragged last block of code columns
     (12, 72, 68, 4, 50, False),
     (16, 4096, 256, 8, 65536, False),
-    # prefill-sized batches: the weight is rebuilt and multiplied by the library's matrix-core product
+    # larger batches: the weight is rebuilt and multiplied by the library's matrix-core product from 385 rows on at this size
+    # (tests/test_gpu_forward_routes.py), gathered below
     (128, 2048, 2048, 4, 65536, True),
     (256, 512, 768, 4, 65536, True),
     (1000, 1024, 520, 8, 4096, False),
@@ -350,7 +351,7 @@ def test_layer_forward(cc, M, in_features, out_features, g, K, with_bias, dt):
 
 @pytest.mark.parametrize("M", [40, 2048])
 def test_layer_forward_prefill_at_model_size(cc, M):
-    """A prefill batch, and a wide decoding batch, through an MLP-sized layer (the rebuilt-weight route): sampled rows of y against the definition, and the same bits on a second call."""
+    """A prefill batch (the rebuilt-weight route), and a wide decoding batch, through an MLP-sized layer: sampled rows of y against the definition, and the same bits on a second call."""
     rng = np.random.default_rng(77)
     in_features, out_features, g, K = 4096, 11008, 4, 65536
     T = torch.bfloat16
@@ -387,7 +388,7 @@ def test_layer_forward_prefill_at_model_size(cc, M):
                                                             # several row tiles with a ragged last one, column tiles likewise
                                                             (777, 264, 515, 5, 2000)])
 def test_layer_forward_many_rows_meets_the_definition_and_reads_out_weight_rows(cc, M, in_features, out_features, g, K, dt):
-    """The rebuilt-weight route (rebuild into matrix-core operands + the product, the contraction split over workgroups
+    """The rebuilt-weight route where the rows are many enough for it (tests/test_gpu_forward_routes.py; rebuild into matrix-core operands + the product, the contraction split over workgroups
     where the tiles are few, in_features not a multiple of the operand's 16, ragged edges in both directions): every
     output against the definition, the same bits on a second call, and one-hot inputs must return rows of the
     reconstructed weight exactly (no arithmetic error possible)."""
@@ -400,7 +401,7 @@ def test_layer_forward_many_rows_meets_the_definition_and_reads_out_weight_rows(
     codes_np = rng.integers(0, K, size=n).astype(np.uint16)
     codes = _dev(codes_np.view(np.int16)).view(torch.uint16)
     nbytes = cc.layer_forward_workspace_bytes(M, in_features, out_features)
-    assert nbytes >= in_features * out_features * 2   # room for the rebuilt weight: this is the many-rows route
+    assert nbytes >= in_features * out_features * 2   # room for the rebuilt weight
     ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     print(f"layer_forward (many rows) M={M} {in_features}->{out_features} g={g} K={K} {dt} ws={nbytes}", flush=True)
     y = torch.full((M, out_features), 9.0, dtype=T, device="cuda")
