@@ -693,9 +693,9 @@ size_t dense_forward_bytes(uint64_t M, uint32_t in_features, uint32_t out_featur
 size_t cc_layer_forward_workspace_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
     if (M == 0 || M > (1ull << 22) || in_features == 0 || out_features == 0) return 0;
-    // whatever the sub-vector length: from 128 rows on, or 65 of a large layer, room for the rebuilt route, up to 384 for both
+    // whatever the sub-vector length: from 128 rows on, or 65 of a large layer, room for the rebuilt route, up to 384 for the others
     const bool few = M < 128 && !(M > 64 && uint64_t(in_features) * out_features >= (1ull << 24));
-    const size_t fused = M <= 384 ? fused_forward_bytes(M, in_features, out_features) : 0;
+    const size_t fused = M <= 384 ? fused_forward_bytes(M, in_features, out_features) + cc::layer_forward_columns_room(M, in_features) : 0;
     return few ? fused : std::max(fused, dense_forward_bytes(M, in_features, out_features));
 }
 
@@ -711,7 +711,7 @@ int cc_layer_forward(const void* x, uint64_t M, const void* codebook, int dtype,
         return fail(CC_ERR_ALIGN, "x, y and codebook need 16-byte alignment");
     const size_t fused_need = fused_forward_bytes(M, in_features, out_features), dense_need = dense_forward_bytes(M, in_features, out_features);
     // a workspace that holds the rebuilt weight but not the slices' sums is good for the rebuilt route at any M
-    const bool dense = cc::dense_rows(M, g, in_features, out_features) || (workspace_bytes < fused_need && workspace_bytes >= dense_need);
+    const bool dense = cc::dense_rows(M, g) || (workspace_bytes < fused_need && workspace_bytes >= dense_need);
     const size_t need = dense ? dense_need : fused_need;
     if (need > 0) {
         if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
@@ -724,6 +724,12 @@ int cc_layer_forward(const void* x, uint64_t M, const void* codebook, int dtype,
         CC_TRY_HIP(cc::launch_layer_weight_frag(codebook, K, g, codes, in_features, out_features, workspace, s), "layer weight");
         CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), workspace, dtype, in_features, out_features, nullptr, bias, y,
                                          reinterpret_cast<float*>(partial), s), "dense product");
+        return CC_OK;
+    }
+    if (cc::layer_forward_columns(g)) {
+        CC_TRY_HIP(cc::launch_layer_forward_columns(x, uint32_t(M), codebook, 16, nullptr, K, g, codes, in_features, out_features, bias, y, dtype,
+                                                    workspace, workspace_bytes, cc::layer_forward_splits(M, in_features, out_features), s),
+                   "layer forward (by columns)");
         return CC_OK;
     }
     CC_TRY_HIP(cc::launch_layer_forward(x, uint32_t(M), codebook, dtype, K, g, codes, in_features, out_features, bias, y,
@@ -914,17 +920,27 @@ namespace {
 constexpr size_t kIntegerBookBytes = size_t(65536) * 16 * 2;  // K <= 65536 codes of g <= 16 entries, 16 bits each
 }
 
+namespace {
+size_t fused_forward_q_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
+{
+    const uint32_t splits = cc::layer_forward_q_max_splits(M, in_features, out_features);
+    return splits > 1 ? cc::align256(size_t(splits) * M * out_features * 4) : 0;
+}
+// the integer weight in 16 bits (matrix-core operand layout), the integer codebook in 16 bits (at most 65536 x 16
+// entries), then the fp32 partial tiles of the product
+size_t dense_forward_q_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
+{
+    return cc::layer_weight_frag_bytes(in_features, out_features) + kIntegerBookBytes + cc::layer_gemm_partial_bytes(M, in_features, out_features);
+}
+}  // namespace
+
 size_t cc_layer_forward_q_workspace_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
     if (M == 0 || M > (1ull << 22) || in_features == 0 || out_features == 0) return 0;
-    const uint32_t splits = cc::layer_forward_q_max_splits(M, in_features, out_features);
-    const size_t fused = splits > 1 ? cc::align256(size_t(splits) * M * out_features * 4) : 0;
-    if (!cc::dense_rows_q(M, in_features, out_features)) return fused;
-    // the integer weight in 16 bits (matrix-core operand layout), the integer codebook in 16 bits (at most 65536 x 16
-    // entries), then the fp32 partial tiles of the product
-    const size_t dense = cc::layer_weight_frag_bytes(in_features, out_features) + kIntegerBookBytes +
-                         cc::layer_gemm_partial_bytes(M, in_features, out_features);
-    return dense > fused ? dense : fused;
+    // whatever the sub-vector length
+    size_t bytes = fused_forward_q_bytes(M, in_features, out_features);
+    if (M <= 384) bytes += cc::layer_forward_columns_room(M, in_features);
+    return cc::dense_rows_q(M, 1, in_features, out_features) ? std::max(bytes, dense_forward_q_bytes(M, in_features, out_features)) : bytes;
 }
 
 int cc_layer_forward_q(const void* x, uint64_t M, const void* qbook, int bits, const float* scale, uint32_t K, uint32_t g,
@@ -939,14 +955,15 @@ int cc_layer_forward_q(const void* x, uint64_t M, const void* qbook, int bits, c
     if (!aligned(x, 16) || !aligned(y, 16) || !aligned(qbook, 16) || !aligned(codes, 2) || !aligned(scale, 4) ||
         (bias && !aligned(bias, 2)))
         return fail(CC_ERR_ALIGN, "x, y and qbook need 16-byte alignment");
-    const size_t need = cc_layer_forward_q_workspace_bytes(M, in_features, out_features);
+    const bool dense = cc::dense_rows_q(M, g, in_features, out_features);
+    const size_t need = dense ? dense_forward_q_bytes(M, in_features, out_features) : fused_forward_q_bytes(M, in_features, out_features);
     if (need > 0) {
         if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
         if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
         if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (cc::dense_rows_q(M, in_features, out_features)) {
+    if (dense) {
         // the integers q themselves as a 16-bit codebook (exact), gathered into the operand layout and multiplied into
         // fp32 sums; scale and bias meet the finished sum
         char* wf = static_cast<char*>(workspace);
@@ -956,6 +973,12 @@ int cc_layer_forward_q(const void* x, uint64_t M, const void* qbook, int bits, c
         CC_TRY_HIP(cc::launch_layer_weight_frag(book16, K, g, codes, in_features, out_features, wf, s), "integer weight");
         CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), wf, dtype, in_features, out_features, scale, bias, y, sums, s),
                    "dense product");
+        return CC_OK;
+    }
+    if (cc::layer_forward_columns(g)) {
+        CC_TRY_HIP(cc::launch_layer_forward_columns(x, uint32_t(M), qbook, bits, scale, K, g, codes, in_features, out_features, bias, y, dtype,
+                                                    workspace, workspace_bytes, cc::layer_forward_q_max_splits(M, in_features, out_features), s),
+                   "layer forward (quantised codebook, by columns)");
         return CC_OK;
     }
     CC_TRY_HIP(cc::launch_layer_forward_q(x, uint32_t(M), qbook, bits, scale, K, g, codes, in_features, out_features, bias, y,

@@ -423,11 +423,20 @@ hipError_t launch_layer_weight(const void* codebook, int dtype, uint32_t K, uint
 // y = x . W(codebook, codes) (+ bias); `partial` holds layer_forward_splits(...) * M * out_features floats if that
 // count is above 1
 uint32_t layer_forward_splits(uint64_t M, uint32_t in_features, uint32_t out_features);
-// few rows, codebook through LDS (layer_forward_book.hip): whether a call takes that route; needs no partial buffer
-bool layer_forward_book(uint64_t M, uint32_t g, uint32_t K, uint32_t in_features, uint32_t out_features);
-hipError_t launch_layer_forward_book(const uint16_t* x, uint32_t M, const uint16_t* codebook, int dtype, uint32_t K,
-                                     const uint16_t* codes, uint32_t in_features, uint32_t out_features, const uint16_t* bias,
-                                     uint16_t* y, hipStream_t s);
+// The sum of slices (times a scale if it is not NULL) + bias
+hipError_t launch_layer_forward_reduce(const float* partial, uint32_t M, uint32_t out_features, uint32_t splits, const float* scale,
+                                       const uint16_t* bias, uint16_t* y, int dtype, hipStream_t s);
+// Rows of 4 .. 9 elements of 16, 8 or 4 bits, each column of the codebook through LDS (layer_forward_columns.hip). The workspace
+// holds most_slices * M * out_features floats (none are needed if that is 1); what it has beyond the slices in use, up to
+// layer_forward_columns_room bytes, holds copies of codebook and x in the layout of the kernel, without which it is slower.
+// `scale` multiplies the sum if it is not NULL.
+constexpr uint32_t kLeastColumns = 4, kMostColumns = 9;
+inline bool layer_forward_columns(uint32_t g) { return g >= kLeastColumns && g <= kMostColumns; }
+size_t layer_forward_columns_room(uint64_t M, uint32_t in_features);
+hipError_t launch_layer_forward_columns(const void* x, uint32_t M, const void* book, int bits, const float* scale, uint32_t K, uint32_t g,
+                                        const uint16_t* codes, uint32_t in_features, uint32_t out_features, const void* bias, void* y,
+                                        int dtype, void* workspace, size_t workspace_bytes, uint32_t most_slices, hipStream_t s);
+// The other lengths: rows gathered from memory tile by tile (layer_forward.hip)
 hipError_t launch_layer_forward(const void* x, uint32_t M, const void* codebook, int dtype, uint32_t K, uint32_t g,
                                 const uint16_t* codes, uint32_t in_features, uint32_t out_features, const void* bias,
                                 void* y, float* partial, hipStream_t s);
@@ -442,29 +451,26 @@ hipError_t launch_layer_grad_planned(const void* grad, int dtype, uint32_t in_fe
                                      uint32_t g, uint32_t n, const void* plan, float* grad_codebook, void* workspace,
                                      hipStream_t s);
 // ---- prefill-sized batches (layer_gemm.hip): W rebuilt into memory, then one dense product on the matrix cores
-// From where on the rebuilt-weight route is the faster one: the fused kernel repeats its lookups for every 128 rows of x, the
-// rebuild takes the same for any number of rows, but longer where it moves rows element by element (all lengths but 4 and 8).
-// bf16, K = 65536, us, fused / rebuilt + product:
-//   g = 4: 8192 x 28672 at 128 rows 355 / 481, at 160 581 / 488; 4096 x 11008 96 / 93, 145 / 96; 8192 x 8192 112 / 132,
-//   175 / 136; 11008 x 4096 93 / 101, 136 / 105; 4096 x 4096 at 256 rows 68 / 71, at 384 96 / 68; 3072 x 3072 50 / 45, 67 / 58;
-//   2048 x 2048 37 / 34, 44 / 36; 1024 x 2048 at 384 rows 28 / 34, at 512 36 / 33.
-//   g = 8: 8192 x 28672 at 128 rows 235 / 370, at 160 424 / 378; 4096 x 10997 81 / 82, 107 / 84; 4096 x 4096 at 256 rows 56 / 69,
-//   at 384 81 / 62.
-//   g = 6: 8192 x 28672 at 384 rows 810 / 1170, at 768 1608 / 1322; 4096 x 10997 195 / 247, 347 / 276; 4096 x 4096 91 / 116,
-//   152 / 124. g = 9: 939 / 1161, 1679 / 1330; 233 / 254, 427 / 279; 97 / 116, 164 / 124. g = 5, 7, 12, 16: as 9.
-//   g = 3: 4096 x 10997 at 64 rows 194 / 215, at 128 234 / 218, at 160 388 / 220; 4096 x 4096 at 128 106 / 103. g = 2: 211 / 212, 76 / 99.
-inline bool dense_rows(uint64_t M, uint32_t g, uint32_t in_features, uint32_t out_features)
+// From where on the rebuilt-weight route is the faster one: the others repeat their lookups for every 64 (by columns) or 128 rows
+// of x, the rebuild takes the same for any number of rows, but longer where it moves rows element by element (all lengths but 4
+// and 8). bf16, us, by columns / rebuilt + product:
+//   g = 4, K = 65536: 4096 x 11008 at 256 rows 93 / 116, at 384 157 / 130; 8192 x 28672 372 / 490, 527 / 540; 4096 x 4096 39 / 67,
+//   62 / 65; 2048 x 2048 20 / 37, 26 / 36.  g = 8, K = 4096: 4096 x 11008 87 / 92, 142 / 107; 4096 x 4096 37 / 49, 59 / 56.
+//   g = 6, K = 65500: 4096 x 11008 at 256 rows 100 / 249, at 384 166 / 253; 8192 x 28672 427 / 1165, 658 / 1170. g = 9: 96 / 252,
+//   163 / 254; 420 / 1160, 688 / 1161.
+// Rows by row: g = 3: 4096 x 10997 at 64 rows 194 / 215, at 128 234 / 218, at 160 388 / 220; 4096 x 4096 at 128 106 / 103. g = 2: 211 /
+// 212, 76 / 99. g = 12, 16: 4096 x 10997 at 384 rows 233 / 254, at 768 427 / 279.
+inline bool dense_rows(uint64_t M, uint32_t g)
 {
-    const uint64_t weights = uint64_t(in_features) * out_features;
     if (g < 4) return M > 128;
-    if (g != 4 && g != 8) return M > 384;
-    return M > (weights >= (1ull << 25) ? 128u : (weights >= (1ull << 22) ? 256u : 384u));
+    return M > (g == 4 || g == 8 ? 256u : 384u);
 }
-// The same with the 4-bit codebook (which the rebuild expands first, + 5 us), g = 4: 4096 x 4096 at 32 rows 48 / 49, at 48 57 / 50;
-// 4096 x 11008 at 8 rows 54 / 88, at 16 107 / 87; 11008 x 4096 at 16 rows 85 / 87, at 32 101 / 88, at 48 113 / 90; 8192 x 8192 at
-// 16 rows 111 / 121, at 32 136 / 121, at 48 150 / 125; 2048 x 2048 at 64 rows 26 / 33, at 96 40 / 34.
-inline bool dense_rows_q(uint64_t M, uint32_t in_features, uint32_t out_features)  // quantised codebook
+// The same with the quantised codebook (which the rebuild expands first, + 5 us), 4 bits: g = 4, K = 65536: 4096 x 11008 at 192 rows
+// 111 / 110, at 256 111 / 120, at 384 179 / 132; g = 6: 142 / 235 at 256, 212 / 251 at 384. Row by row: 2048 x 2048 at 64 rows
+// 26 / 33, at 96 40 / 34; 4096 x 11008 at 8 rows 54 / 88, at 16 107 / 87; 11008 x 4096 at 16 rows 85 / 87, at 32 101 / 88.
+inline bool dense_rows_q(uint64_t M, uint32_t g, uint32_t in_features, uint32_t out_features)
 {
+    if (layer_forward_columns(g)) return dense_rows(M, g);
     const uint64_t weights = uint64_t(in_features) * out_features;
     if (weights < (1ull << 24)) return M > 64;
     if (weights >= (1ull << 25) && out_features >= 2 * uint64_t(in_features)) return M >= 16;

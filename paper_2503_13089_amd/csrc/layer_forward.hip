@@ -11,13 +11,10 @@
 // The in-feature slices of different workgroups (there to fill the chip when M is small) go to an fp32
 // partial buffer and are added in a fixed order by a second kernel: the result does not depend on scheduling.
 //
-// Bound: one codebook lookup per code per M-tile (random rows from L2 come at 3 clocks each per compute unit), not HBM: the
-// codes are in*out/g*2 bytes. Hence whole code columns per tile, rows in one load (two if g is odd) and the codes of the
-// next step under way meanwhile. 4096 x 10997, g = 6, K = 65500, M = 23: 89 -> 49 us; 4096 x 11008, g = 9, M = 4: 157 -> 52 us;
-// 4096 x 4096, g = 4, M = 4 .. 32: 22 us and 4 us for the slices' sum, within 5 % of a kernel for few rows without
-// matrix cores.
+// This is the route for rows of 1 .. 3 and 10 .. 16 elements; those of 4 .. 9 go through LDS column by column
+// (layer_forward_columns.hip). Bound: one codebook lookup per code per M-tile (random rows from L2 come at 3 clocks each per
+// compute unit), not HBM: the codes are in*out/g*2 bytes. 4096 x 11008, g = 3, K = 65536, M = 16: 211 us, g = 12: 46 us.
 #include <algorithm>
-#include <type_traits>
 
 #include "common.h"
 #include "half_types.h"
@@ -44,30 +41,11 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Row `k` of a codebook of 16-bit elements as 32-bit words (element j in word j/2, half j%2). G: the row length if it is
-// 4 .. 9, else 0. Rows of 4 .. 9 elements come in one load of 8, 12 or 16 bytes and, where G is odd, one of 2 (loads need no
-// alignment beyond an element's): what bounds the kernel is one L1 lookup per load instruction and lane.
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-typedef uint32_t u32x3_any __attribute__((ext_vector_type(3), aligned(2)));
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-
-template <int G>
+// Row `k` of a codebook of 16-bit elements as 32-bit words (element j in word j/2, half j%2).
 __device__ __forceinline__ void load_row_words(const uint16_t* __restrict__ codebook, uint32_t k, uint32_t g, uint32_t (&w)[8])
 {
-    const uint16_t* row = codebook + size_t(k) * (G ? G : g);
-    if constexpr (G == 4 || G == 5) {
-        const u32x2_any t = *reinterpret_cast<const u32x2_any*>(row);
-        w[0] = t[0]; w[1] = t[1];
-        if (G == 5) w[2] = row[4];
-    } else if constexpr (G == 6 || G == 7) {
-        const u32x3_any t = *reinterpret_cast<const u32x3_any*>(row);
-        w[0] = t[0]; w[1] = t[1]; w[2] = t[2];
-        if (G == 7) w[3] = row[6];
-    } else if constexpr (G == 8 || G == 9) {
-        const u32x4_any t = *reinterpret_cast<const u32x4_any*>(row);
-        w[0] = t[0]; w[1] = t[1]; w[2] = t[2]; w[3] = t[3];
-        if (G == 9) w[4] = row[8];
-    } else if (g == 16) {
+    const uint16_t* row = codebook + size_t(k) * g;
+    if (g == 16) {
         const uint4 t = reinterpret_cast<const uint4*>(row)[0], u = reinterpret_cast<const uint4*>(row)[1];
         w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w; w[4] = u.x; w[5] = u.y; w[6] = u.z; w[7] = u.w;
     } else if ((g & 1) == 0) {
@@ -87,9 +65,9 @@ __device__ __forceinline__ void load_row_words(const uint16_t* __restrict__ code
 
 // grid.x = n_tiles * splits (remapped so that one XCD works on neighbouring column tiles, which share the
 // cache lines of the codes), grid.y = M tiles.
-template <int DT, int MT, int G>
+template <int DT, int MT>
 __global__ __launch_bounds__(kThreads) void layer_forward_kernel(
-    const uint16_t* __restrict__ x, uint32_t M, const uint16_t* __restrict__ codebook, uint32_t K, uint32_t any_g,
+    const uint16_t* __restrict__ x, uint32_t M, const uint16_t* __restrict__ codebook, uint32_t K, uint32_t g,
     const uint16_t* __restrict__ codes, uint32_t per_row, uint32_t in_features, uint32_t out_features,
     const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, float* __restrict__ partial, uint32_t n_tiles,
     uint32_t splits, uint32_t rows_per_split)
@@ -97,7 +75,6 @@ __global__ __launch_bounds__(kThreads) void layer_forward_kernel(
     __shared__ __attribute__((aligned(16))) float red[4][16][64];
     uint32_t* Wt = reinterpret_cast<uint32_t*>(red);   // [BN][S], until the sums
     static_assert(sizeof(uint32_t) * BN * S <= sizeof(float) * 4 * 16 * 64, "the tile fits");
-    const uint32_t g = G ? uint32_t(G) : any_g;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
 
     // column tile and in-feature slice of this workgroup: consecutive workgroup ids go to different XCDs,
@@ -131,71 +108,33 @@ __global__ __launch_bounds__(kThreads) void layer_forward_kernel(
             if (m < M && kk < k_end) a[mt] = *reinterpret_cast<const u32x4*>(x + size_t(m) * in_features + kk);
         }
     };
-    // items of a thread: a row pair and a column each. With G known there are NI at most, worked on together; else one by one
-    // (NI = 1). The codes of a step are requested during the step before, the lines of x before its rows are waited for.
-    constexpr int NI = G ? ((BK / 2) * (BN / (G ? G : 1)) + kThreads - 1) / kThreads : 1;
-    constexpr uint32_t kMost = G ? G : 16;
-    uint32_t rps[NI], cs[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const uint32_t it = threadIdx.x + i * kThreads;
-        rps[i] = it / cpr;
-        cs[i] = it % cpr;
-    }
+    const uint32_t rp0 = threadIdx.x / cpr, c0 = threadIdx.x % cpr;
     auto load_code = [&](uint32_t r, uint32_t c) {
         return r < k_end ? uint32_t(codes[size_t(r) * per_row + min(cn_lo + c, per_row - 1)]) : 0u;
     };
-    auto put = [&](const uint32_t (&w0)[8], const uint32_t (&w1)[8], uint32_t r0, uint32_t rp, uint32_t c) {
-        const bool live0 = r0 < k_end, live1 = r0 + 1 < k_end;
-#pragma unroll
-        for (uint32_t j = 0; j < kMost; ++j) {
-            if (!G && j >= g) break;
-            const uint32_t n = c * g + j;
-            const uint32_t e0 = live0 ? (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
-            const uint32_t e1 = live1 ? (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
-            Wt[n * S + rp] = e0 | (e1 << 16);
-        }
-    };
-    uint32_t code[NI][2];
-    if constexpr (G != 0) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) code[i][e] = rps[i] < BK / 2 ? load_code(k_begin + 2 * rps[i] + e, cs[i]) : 0u;
-    }
     for (uint32_t k0 = k_begin; k0 < k_end; k0 += BK) {
         // ---- gather the W piece: Wt[n - n_lo][k - k0], two k per 32-bit word
-        const uint32_t kk = k0 + 16 * wave + 8 * h;  // first of this lane's 8 in-features
         u32x4 a[MT];
-        if constexpr (G != 0) {
-            uint32_t w[NI][2][8];
+        load_x(a, k0 + 16 * wave + 8 * h);   // this lane's 8 in-features
+        uint32_t rp = rp0, c = c0;
+        for (uint32_t it = threadIdx.x; it < items; it += kThreads) {
+            const uint32_t r0 = k0 + 2 * rp;
+            const bool live0 = r0 < k_end, live1 = r0 + 1 < k_end;
+            uint32_t w0[8], w1[8];  // up to 16 elements each, two per word
+            load_row_words(codebook, min(load_code(r0, c), K - 1), g, w0);
+            load_row_words(codebook, min(load_code(r0 + 1, c), K - 1), g, w1);
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) load_row_words<G>(codebook, min(code[i][e], K - 1), g, w[i][e]);
-            load_x(a, kk);
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) code[i][e] = rps[i] < BK / 2 ? load_code(k0 + BK + 2 * rps[i] + e, cs[i]) : 0u;
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-                if (rps[i] < BK / 2) put(w[i][0], w[i][1], k0 + 2 * rps[i], rps[i], cs[i]);
-        } else {
-            load_x(a, kk);
-            uint32_t rp = rps[0], c = cs[0];
-            for (uint32_t it = threadIdx.x; it < items; it += kThreads) {
-                const uint32_t r0 = k0 + 2 * rp;
-                uint32_t w0[8], w1[8];  // up to 16 elements each, two per word
-                load_row_words<G>(codebook, min(load_code(r0, c), K - 1), g, w0);
-                load_row_words<G>(codebook, min(load_code(r0 + 1, c), K - 1), g, w1);
-                put(w0, w1, r0, rp, c);
-                rp += step_rp;
-                c += step_c;
-                if (c >= cpr) {
-                    c -= cpr;
-                    ++rp;
-                }
+            for (uint32_t j = 0; j < 16; ++j) {
+                if (j >= g) break;
+                const uint32_t e0 = live0 ? (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
+                const uint32_t e1 = live1 ? (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
+                Wt[(c * g + j) * S + rp] = e0 | (e1 << 16);
+            }
+            rp += step_rp;
+            c += step_c;
+            if (c >= cpr) {
+                c -= cpr;
+                ++rp;
             }
         }
         __syncthreads();
@@ -243,6 +182,7 @@ __global__ __launch_bounds__(kThreads) void layer_forward_kernel(
 template <int DT>
 __global__ __launch_bounds__(kThreads) void layer_forward_reduce_kernel(const float* __restrict__ partial, uint64_t n,
                                                                         uint32_t out_features, uint32_t splits,
+                                                                        const float* __restrict__ scale,
                                                                         const uint16_t* __restrict__ bias,
                                                                         uint16_t* __restrict__ y)
 {
@@ -257,11 +197,12 @@ __global__ __launch_bounds__(kThreads) void layer_forward_reduce_kernel(const fl
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) v += p[u];  // fixed order
     }
+    if (scale) v *= *scale;
     if (bias) v += to_f32<DT>(bias[t % out_features]);
     y[t] = from_f32<DT>(v);
 }
 
-template <int DT, int MT, int G>
+template <int DT, int MT>
 void forward_t(const uint16_t* x, uint32_t M, const uint16_t* codebook, uint32_t K, uint32_t g, const uint16_t* codes,
                uint32_t in_features, uint32_t out_features, const uint16_t* bias, uint16_t* y, float* partial,
                uint32_t splits, uint32_t rows_per_split, hipStream_t s)
@@ -269,16 +210,21 @@ void forward_t(const uint16_t* x, uint32_t M, const uint16_t* codebook, uint32_t
     const uint32_t per_row = (out_features + g - 1) / g;
     const uint32_t n_tiles = (per_row + BN / g - 1) / (BN / g);
     const dim3 grid(n_tiles * splits, (M + 32 * MT - 1) / (32 * MT));
-    hipLaunchKernelGGL((layer_forward_kernel<DT, MT, G>), grid, dim3(kThreads), 0, s, x, M, codebook, K, g, codes, per_row,
+    hipLaunchKernelGGL((layer_forward_kernel<DT, MT>), grid, dim3(kThreads), 0, s, x, M, codebook, K, g, codes, per_row,
                        in_features, out_features, bias, y, partial, n_tiles, splits, rows_per_split);
-    if (splits > 1) {
-        const uint64_t n = uint64_t(M) * out_features;
-        hipLaunchKernelGGL(layer_forward_reduce_kernel<DT>, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           partial, n, out_features, splits, bias, y);
-    }
+    if (splits > 1) (void)launch_layer_forward_reduce(partial, M, out_features, splits, nullptr, bias, y, DT, s);
 }
 
 }  // namespace
+
+hipError_t launch_layer_forward_reduce(const float* partial, uint32_t M, uint32_t out_features, uint32_t splits, const float* scale,
+                                       const uint16_t* bias, uint16_t* y, int dtype, hipStream_t s)
+{
+    const uint64_t n = uint64_t(M) * out_features;
+    const auto kernel = dtype == 1 ? layer_forward_reduce_kernel<1> : layer_forward_reduce_kernel<2>;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, partial, n, out_features, splits, scale, bias, y);
+    return hipGetLastError();
+}
 
 // How many in-feature slices a call uses (also sizes the partial buffer): enough workgroups to fill the chip.
 uint32_t layer_forward_splits(uint64_t M, uint32_t in_features, uint32_t out_features)
@@ -300,32 +246,19 @@ hipError_t launch_layer_forward(const void* x, uint32_t M, const void* codebook,
     const uint16_t* cb = static_cast<const uint16_t*>(codebook);
     const uint16_t* bs = static_cast<const uint16_t*>(bias);
     uint16_t* ys = static_cast<uint16_t*>(y);
-    if (layer_forward_book(M, g, K, in_features, out_features))
-        return launch_layer_forward_book(xs, M, cb, dtype, K, codes, in_features, out_features, bs, ys, s);
     const uint32_t splits = layer_forward_splits(M, in_features, out_features);
     const uint32_t ksteps = (in_features + BK - 1) / BK;
     const uint32_t rows_per_split = (ksteps + splits - 1) / splits * BK;
     const uint32_t used = (in_features + rows_per_split - 1) / rows_per_split;  // slices that are not empty
     const int mt = M > 64 ? 4 : (M > 32 ? 2 : 1);
-#define CC_FWD(DT, MT, G) forward_t<DT, MT, G>(xs, M, cb, K, g, codes, in_features, out_features, bs, ys, partial, used, rows_per_split, s)
-#define CC_FWD_G(DT, MT)                        \
-    switch (g) {                                \
-        case 4: CC_FWD(DT, MT, 4); break;       \
-        case 5: CC_FWD(DT, MT, 5); break;       \
-        case 6: CC_FWD(DT, MT, 6); break;       \
-        case 7: CC_FWD(DT, MT, 7); break;       \
-        case 8: CC_FWD(DT, MT, 8); break;       \
-        case 9: CC_FWD(DT, MT, 9); break;       \
-        default: CC_FWD(DT, MT, 0); break;      \
-    }
+#define CC_FWD(DT, MT) forward_t<DT, MT>(xs, M, cb, K, g, codes, in_features, out_features, bs, ys, partial, used, rows_per_split, s)
     if (dtype == 1) {
-        if (mt == 4) { CC_FWD_G(1, 4) } else if (mt == 2) { CC_FWD_G(1, 2) } else { CC_FWD_G(1, 1) }
+        if (mt == 4) CC_FWD(1, 4); else if (mt == 2) CC_FWD(1, 2); else CC_FWD(1, 1);
     } else if (dtype == 2) {
-        if (mt == 4) { CC_FWD_G(2, 4) } else if (mt == 2) { CC_FWD_G(2, 2) } else { CC_FWD_G(2, 1) }
+        if (mt == 4) CC_FWD(2, 4); else if (mt == 2) CC_FWD(2, 2); else CC_FWD(2, 1);
     } else {
         return hipErrorInvalidValue;
     }
-#undef CC_FWD_G
 #undef CC_FWD
     return hipGetLastError();
 }

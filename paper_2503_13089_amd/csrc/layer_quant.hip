@@ -375,352 +375,6 @@ __global__ __launch_bounds__(kThreads) void layer_forward_q_kernel(
     }
 }
 
-// Row k of the quantised codebook as floats with the offset left in: f[j] = q[j] + 2^(BITS-1), an unsigned byte
-// that converts to float in one instruction (the offset is removed once per wave, see the kernel).
-template <int BITS, int G>
-__device__ __forceinline__ void biased_row(const uint8_t* book, uint32_t k, float (&f)[G])
-{
-    uint32_t packed[G / 4];  // byte i of word v: element order given by `lane_of`
-    if constexpr (BITS == 8) {
-#pragma unroll
-        for (int v = 0; v < G / 4; ++v)
-            packed[v] = reinterpret_cast<const uint32_t*>(book + size_t(k) * G)[v] ^ 0x80808080u;
-#pragma unroll
-        for (int j = 0; j < G; ++j) f[j] = float((packed[j / 4] >> (8 * (j % 4))) & 0xffu);
-    } else {
-        // 4 nibbles n3 n2 n1 n0 -> bytes (n0, n2, n1, n3), each xor 8
-#pragma unroll
-        for (int v = 0; v < G / 4; ++v) {
-            const uint32_t r = reinterpret_cast<const uint16_t*>(book + size_t(k) * (G / 2))[v];
-            packed[v] = ((r & 0x0f0fu) | (((r >> 4) & 0x0f0fu) << 16)) ^ 0x08080808u;
-        }
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const int e = j % 4;
-            const int byte = e == 0 ? 0 : (e == 1 ? 2 : (e == 2 ? 1 : 3));
-            f[j] = float((packed[j / 4] >> (8 * byte)) & 0xffu);
-        }
-    }
-}
-
-// ---- fused forward on the matrix cores with the codebook in LDS, g = 4 or 8, up to 64 rows of x ---------------
-// The tiling of the kernel above with everything the compiler needs to know at compile time: with g fixed, a
-// step of 64 in-features x 64 columns is exactly NI items (two codebook rows each) per thread, so the codes and
-// the x operands of the next step sit in a fixed number of registers while the current step is gathered from
-// LDS, written to the transposed tile and multiplied. B holds the integers q (exact in bf16 and fp16).
-// Measured: 43 us for a 4096 x 4096 layer whatever M <= 32 (58 us for M <= 64): the four waves of the one
-// workgroup a CU can hold spend most of their time waiting (a three-step-deep operand ring did not help), so
-// this kernel only takes over where the few-rows kernel's M * g multiply-adds per code cost more (M > 16).
-template <int BITS, int G>
-__device__ __forceinline__ void signed_row(const uint8_t* book, uint32_t k, float (&f)[G])
-{
-    biased_row<BITS, G>(book, k, f);
-#pragma unroll
-    for (int j = 0; j < G; ++j) f[j] -= float(1 << (BITS - 1));
-}
-
-template <int DT, int BITS, int G, int MT>
-__global__ __launch_bounds__(kThreads) void layer_forward_q_mfma_kernel(
-    const uint16_t* __restrict__ x, uint32_t M, const uint8_t* __restrict__ qbook, uint32_t book_bytes,
-    const float* __restrict__ scale, uint32_t K, const uint16_t* __restrict__ codes, uint32_t per_row,
-    uint32_t in_features, uint32_t out_features, const uint16_t* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ partial, uint32_t n_tiles, uint32_t splits, uint32_t rows_per_split)
-{
-    constexpr int CPR = BN / G;                        // code columns of a tile
-    constexpr int NI = (BK / 2) * CPR / kThreads;      // items per thread and step
-    static_assert((BK / 2) * CPR % kThreads == 0, "whole items per thread");
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    uint32_t* Wt = reinterpret_cast<uint32_t*>(smem);
-    float (*red)[16][64] = reinterpret_cast<float (*)[16][64]>(smem);  // [2][16][64], used between k loops only
-    uint8_t* book = smem + kTileBytes;
-    stage_book(qbook, book_bytes, book);
-    const float s = *scale;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5;
-    const uint32_t jobs = n_tiles * splits;
-
-    // item i of this thread: row pair rp[i] of the step, code column cc[i] of the tile
-    uint32_t rp[NI], cc[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const uint32_t it = threadIdx.x + i * kThreads;
-        rp[i] = it / CPR;
-        cc[i] = it % CPR;
-    }
-    auto fetch_codes = [&](uint32_t n_lo, uint32_t k0, uint32_t k_end, uint32_t (&pc)[NI]) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const uint32_t cn = n_lo / G + cc[i];
-            const uint32_t r0 = k0 + 2 * rp[i];
-            const bool on = cn < per_row && r0 < k_end;  // k_end is even: the pair is in or out as a whole
-            const uint32_t c0 = on ? codes[size_t(r0) * per_row + cn] : 0u;
-            const uint32_t c1 = on ? codes[size_t(r0 + 1) * per_row + cn] : 0u;
-            pc[i] = c0 | (c1 << 16) | 0u;
-        }
-    };
-    auto fetch_x = [&](uint32_t k0, uint32_t k_end, u32x4 (&a)[MT]) {
-        const uint32_t kk = k0 + 16 * wave + 8 * h;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const uint32_t m = 32 * mt + (lane & 31);
-            a[mt] = u32x4{0u, 0u, 0u, 0u};
-            if (m < M && kk < k_end) a[mt] = *reinterpret_cast<const u32x4*>(x + size_t(m) * in_features + kk);
-        }
-    };
-    auto span = [&](uint32_t job, uint32_t& n_lo, uint32_t& split, uint32_t& k_begin, uint32_t& k_end) {
-        n_lo = (job % n_tiles) * BN;
-        split = job / n_tiles;
-        k_begin = split * rows_per_split;
-        k_end = min(k_begin + rows_per_split, in_features);
-    };
-
-    uint32_t job = blockIdx.x;
-    if (job >= jobs) return;
-    uint32_t n_lo, split, k_begin, k_end;
-    span(job, n_lo, split, k_begin, k_end);
-    uint32_t pc[NI];
-    u32x4 a[MT];
-    fetch_codes(n_lo, k_begin, k_end, pc);
-    fetch_x(k_begin, k_end, a);
-
-    while (true) {
-        f32x16 acc[MT][2];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.0f;
-        const uint32_t next_job = job + gridDim.x;
-        const bool more = next_job < jobs;
-        uint32_t nn_lo = n_lo, nsplit = split, nk_begin = k_begin, nk_end = k_end;
-        if (more) span(next_job, nn_lo, nsplit, nk_begin, nk_end);
-
-        for (uint32_t k0 = k_begin; k0 < k_end; k0 += BK) {
-            // request the operands of the step after this one (same job, or the first step of the next job)
-            uint32_t nc[NI];
-            u32x4 na[MT];
-            const bool last = k0 + BK >= k_end;
-            if (!last) {
-                fetch_codes(n_lo, k0 + BK, k_end, nc);
-                fetch_x(k0 + BK, k_end, na);
-            } else {
-                fetch_codes(nn_lo, nk_begin, more ? nk_end : 0u, nc);
-                fetch_x(nk_begin, more ? nk_end : 0u, na);
-            }
-            // gather this step's piece of W from LDS into the transposed tile
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const uint32_t cn = n_lo / G + cc[i];
-                const bool on = cn < per_row && k0 + 2 * rp[i] < k_end;
-                float f0[G], f1[G];
-                signed_row<BITS, G>(book, min(pc[i] & 0xffffu, K - 1), f0);
-                signed_row<BITS, G>(book, min(pc[i] >> 16, K - 1), f1);
-#pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    const uint32_t lo16 = on ? to_bits16<DT>(f0[e]) : 0u, hi16 = on ? to_bits16<DT>(f1[e]) : 0u;
-                    Wt[(cc[i] * G + e) * S + rp[i]] = lo16 | (hi16 << 16);
-                }
-            }
-            __syncthreads();
-            u32x4 b[2];
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-                b[nb] = *reinterpret_cast<const u32x4*>(&Wt[(32 * nb + (lane & 31)) * S + 8 * wave + 4 * h]);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[mt][nb] = mma<DT>(a[mt], b[nb], acc[mt][nb]);
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < NI; ++i) pc[i] = nc[i];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) a[mt] = na[mt];
-        }
-
-        // add the four k slices: (w0 + w2) + (w1 + w3), through the 8 KB buffer that aliases the tile; wave 0 stores
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                if (wave >= 2) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) red[wave - 2][r][lane] = acc[mt][nb][r];
-                }
-                __syncthreads();
-                if (wave < 2) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[mt][nb][r] += red[wave][r][lane];
-                }
-                __syncthreads();
-                if (wave == 1) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) red[0][r][lane] = acc[mt][nb][r];
-                }
-                __syncthreads();
-                if (wave == 0) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float v = (acc[mt][nb][r] + red[0][r][lane]) * (splits == 1 ? s : 1.0f);
-                        const uint32_t m = 32 * mt + (r & 3) + 8 * (r >> 2) + 4 * h;
-                        const uint32_t n = n_lo + 32 * nb + (lane & 31);
-                        if (m < M && n < out_features) {
-                            if (splits == 1) {
-                                y[size_t(m) * out_features + n] =
-                                    uint16_t(to_bits16<DT>(bias ? v + from_bits16<DT>(bias[n]) : v));
-                            } else {
-                                partial[(size_t(split) * M + m) * out_features + n] = v;
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        if (!more) break;
-        job = next_job;
-        n_lo = nn_lo; split = nsplit; k_begin = nk_begin; k_end = nk_end;
-    }
-}
-
-// ---- fused forward for few rows of x (decode-time M <= 16), codebook in LDS, g = 4 or 8 ------------------
-// No matrix cores and no transposition: a lane owns one code column (g outputs) and walks down the
-// in-features of its slice; per code it looks the row up in LDS, dequantises it, and does MB * g fused
-// multiply-adds against x values that are uniform over the wave (scalar loads). 8 waves of a workgroup share
-// 64 code columns and take every 8th pair of in-features; their partial sums meet in LDS at the end.
-// The sum runs over x * q with the integers q (exact products); the scale multiplies the finished sum.
-constexpr int kGemvThreads = 512, kGemvWaves = 8, kGemvCols = 64;
-
-
-template <int DT, int BITS, int G, int MB>
-__global__ __launch_bounds__(kGemvThreads) void layer_forward_q_gemv_kernel(
-    const uint16_t* __restrict__ x, uint32_t M, const uint8_t* __restrict__ qbook, uint32_t book_bytes,
-    const float* __restrict__ scale, uint32_t K, const uint16_t* __restrict__ codes, uint32_t per_row,
-    uint32_t in_features, uint32_t out_features, const uint16_t* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ partial, uint32_t col_blocks, uint32_t splits, uint32_t rows_per_split)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    constexpr int MC = G == 4 ? 2 : 1;                           // rows of x per reduction round (16 KB of LDS)
-    float* red = reinterpret_cast<float*>(smem);                 // [kGemvWaves][MC][kGemvCols * G]
-    constexpr uint32_t kRedBytes = kGemvWaves * MC * kGemvCols * G * 4;
-    uint8_t* book = smem + kRedBytes;
-    stage_book(qbook, book_bytes, book);
-    const float s = *scale;
-    const int lane = threadIdx.x & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t jobs = col_blocks * splits;
-
-    for (uint32_t job = blockIdx.x; job < jobs; job += gridDim.x) {
-        const uint32_t cb = job % col_blocks, split = job / col_blocks;
-        const uint32_t cn = cb * kGemvCols + lane;
-        const bool live = cn < per_row;
-        const uint32_t k_begin = split * rows_per_split, k_end = min(k_begin + rows_per_split, in_features);
-        float acc[MB][G], xsum[MB];
-#pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            xsum[m] = 0.0f;
-#pragma unroll
-            for (int j = 0; j < G; ++j) acc[m][j] = 0.0f;
-        }
-
-        // pairs of in-features (rows 2p, 2p + 1): this wave takes p = k_begin/2 + wave, + 8, ...; the codes of
-        // U pairs are requested before any is used
-        constexpr int U = MB >= 16 ? 4 : 8;
-        uint32_t c0[U], c1[U];
-        auto fetch = [&](uint32_t p0, uint32_t (&a0)[U], uint32_t (&a1)[U]) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t p = p0 + u * kGemvWaves;
-                const bool on = live && 2 * p < k_end;
-                a0[u] = on ? uint32_t(codes[size_t(2 * p) * per_row + cn]) : 0u;
-                a1[u] = on ? uint32_t(codes[size_t(2 * p + 1) * per_row + cn]) : 0u;
-            }
-        };
-        uint32_t p0 = k_begin / 2 + wave;
-        fetch(p0, c0, c1);
-        for (; 2 * p0 < k_end; p0 += kGemvWaves * U) {
-            // the next batch is requested before this one is used: its latency hides behind the arithmetic
-            uint32_t n0[U], n1[U];
-            fetch(p0 + kGemvWaves * U, n0, n1);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t p = p0 + u * kGemvWaves;
-                if (2 * p >= k_end) break;  // wave-uniform
-                float f0[G], f1[G];
-                biased_row<BITS, G>(book, min(c0[u], K - 1), f0);
-                biased_row<BITS, G>(book, min(c1[u], K - 1), f1);
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    // both x values of the pair in one (wave-uniform) 32-bit load
-                    const uint32_t xw = m < int(M) ? reinterpret_cast<const uint32_t*>(x + size_t(m) * in_features)[p] : 0u;
-                    const float x0 = from_bits16<DT>(uint16_t(xw & 0xffffu)), x1 = from_bits16<DT>(uint16_t(xw >> 16));
-                    xsum[m] += x0 + x1;
-#pragma unroll
-                    for (int j = 0; j < G; ++j) {
-                        acc[m][j] = __builtin_fmaf(x0, f0[j], acc[m][j]);
-                        acc[m][j] = __builtin_fmaf(x1, f1[j], acc[m][j]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                c0[u] = n0[u];
-                c1[u] = n1[u];
-            }
-        }
-        // the stored integers were taken with their offset (q + 2^(BITS-1)): remove offset * sum of this wave's x
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int j = 0; j < G; ++j) acc[m][j] = __builtin_fmaf(-float(1 << (BITS - 1)), xsum[m], acc[m][j]);
-
-        // sum over the 8 waves, MC rows of x per round: thread t finishes element t of the round
-#pragma unroll
-        for (int m0 = 0; m0 < MB; m0 += MC) {
-            __syncthreads();
-#pragma unroll
-            for (int mc = 0; mc < MC; ++mc)
-#pragma unroll
-                for (int j = 0; j < G; ++j)
-                    if (m0 + mc < MB) red[((wave * MC + mc) * kGemvCols + lane) * G + j] = acc[(m0 + mc) % MB][j];
-            __syncthreads();
-            constexpr int kRound = MC * kGemvCols * G;  // elements per round
-            for (int t = threadIdx.x; t < kRound; t += kGemvThreads) {
-                const int mc = t / (kGemvCols * G), rest = t % (kGemvCols * G);
-                float v = 0.0f;
-#pragma unroll
-                for (int w = 0; w < kGemvWaves; ++w) v += red[(w * MC + mc) * kGemvCols * G + rest];
-                if (splits == 1) v *= s;
-                const uint32_t m = m0 + mc;
-                const uint32_t n = cb * kGemvCols * G + rest;
-                if (m < M && m < MB && n < out_features) {
-                    if (splits == 1) {
-                        y[size_t(m) * out_features + n] = uint16_t(to_bits16<DT>(bias ? v + from_bits16<DT>(bias[n]) : v));
-                    } else {
-                        partial[(size_t(split) * M + m) * out_features + n] = v;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
-template <int DT>
-__global__ __launch_bounds__(kThreads) void forward_q_reduce_kernel(const float* __restrict__ partial, uint64_t n,
-                                                                    uint32_t out_features, uint32_t splits,
-                                                                    const float* __restrict__ scale,
-                                                                    const uint16_t* __restrict__ bias,
-                                                                    uint16_t* __restrict__ y)
-{
-    const uint64_t t = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (t >= n) return;
-    float v = partial[t];
-    for (uint32_t s = 1; s < splits; ++s) v += partial[uint64_t(s) * n + t];  // fixed order
-    v *= *scale;
-    if (bias) v += from_bits16<DT>(bias[t % out_features]);
-    y[t] = uint16_t(to_bits16<DT>(v));
-}
-
 int g_cus = 0;
 int compute_units()
 {
@@ -802,74 +456,6 @@ hipError_t launch_layer_weight_q(const void* qbook, int bits, const float* scale
     return hipErrorInvalidValue;
 }
 
-// The few-rows kernel: 64 code columns per job; slices of in_features so that every CU gets a job or two.
-static uint32_t gemv_splits(uint32_t in_features, uint32_t per_row)
-{
-    const uint32_t col_blocks = (per_row + kGemvCols - 1) / kGemvCols;
-    uint32_t splits = (2 * 256 + col_blocks - 1) / col_blocks;
-    splits = std::min<uint32_t>(splits, std::max<uint32_t>(1, in_features / (2 * kGemvWaves * 4)));  // >= 4 pairs per wave
-    return std::max<uint32_t>(1, std::min<uint32_t>(splits, 64));
-}
-
-template <int DT, int BITS, int G, int MB>
-static hipError_t forward_q_gemv_t(const uint16_t* x, uint32_t M, const uint8_t* qbook, uint32_t book_bytes,
-                                   const float* scale, uint32_t K, const uint16_t* codes, uint32_t in_features,
-                                   uint32_t out_features, const uint16_t* bias, uint16_t* y, float* partial, hipStream_t s)
-{
-    const uint32_t per_row = (out_features + G - 1) / G;
-    const uint32_t col_blocks = (per_row + kGemvCols - 1) / kGemvCols;
-    const uint32_t req = gemv_splits(in_features, per_row);
-    // slices hold whole groups of 16 in-features (one pair per wave), so that every slice starts at wave 0's pair
-    const uint32_t groups = (in_features + 2 * kGemvWaves - 1) / (2 * kGemvWaves);
-    const uint32_t rows_per_split = (groups + req - 1) / req * (2 * kGemvWaves);
-    const uint32_t splits = (in_features + rows_per_split - 1) / rows_per_split;
-    auto kernel = layer_forward_q_gemv_kernel<DT, BITS, G, MB>;
-    const uint32_t lds = kGemvWaves * (G == 4 ? 2 : 1) * kGemvCols * G * 4 + ((book_bytes + 15) & ~15u);
-    hipError_t e = allow_lds(kernel, lds);
-    if (e != hipSuccess) return e;
-    const dim3 grid(std::min<uint32_t>(uint32_t(compute_units()), col_blocks * splits));
-    hipLaunchKernelGGL(kernel, grid, dim3(kGemvThreads), lds, s, x, M, qbook, book_bytes, scale, K, codes, per_row, in_features,
-                       out_features, bias, y, partial, col_blocks, splits, rows_per_split);
-    if (splits > 1) {
-        const uint64_t n = uint64_t(M) * out_features;
-        hipLaunchKernelGGL(forward_q_reduce_kernel<DT>, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           partial, n, out_features, splits, scale, bias, y);
-    }
-    return hipGetLastError();
-}
-
-static bool lds_book_applies(uint32_t K, uint32_t g, int bits)
-{
-    return (g == 4 || g == 8) && (uint64_t(K) * g * bits + 7) / 8 <= kMaxLdsBook;
-}
-
-template <int DT, int BITS, int G, int MT>
-static hipError_t forward_q_mfma_t(const uint16_t* x, uint32_t M, const uint8_t* qbook, uint32_t book_bytes,
-                                   const float* scale, uint32_t K, const uint16_t* codes, uint32_t in_features,
-                                   uint32_t out_features, const uint16_t* bias, uint16_t* y, float* partial, hipStream_t s)
-{
-    const uint32_t per_row = (out_features + G - 1) / G;
-    const uint32_t n_tiles = (out_features + BN - 1) / BN;
-    const uint32_t ksteps = (in_features + BK - 1) / BK;
-    uint32_t req = (2 * 256 + n_tiles - 1) / n_tiles;
-    req = std::max<uint32_t>(1, std::min<uint32_t>(std::min<uint32_t>(req, 64), std::max<uint32_t>(1, ksteps / 4)));
-    const uint32_t rows_per_split = (ksteps + req - 1) / req * BK;
-    const uint32_t splits = (in_features + rows_per_split - 1) / rows_per_split;
-    auto kernel = layer_forward_q_mfma_kernel<DT, BITS, G, MT>;
-    const uint32_t lds = kTileBytes + ((book_bytes + 15) & ~15u);
-    hipError_t e = allow_lds(kernel, lds);
-    if (e != hipSuccess) return e;
-    const dim3 grid(std::min<uint32_t>(uint32_t(compute_units()), n_tiles * splits));
-    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, s, x, M, qbook, book_bytes, scale, K, codes, per_row, in_features,
-                       out_features, bias, y, partial, n_tiles, splits, rows_per_split);
-    if (splits > 1) {
-        const uint64_t n = uint64_t(M) * out_features;
-        hipLaunchKernelGGL(forward_q_reduce_kernel<DT>, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           partial, n, out_features, splits, scale, bias, y);
-    }
-    return hipGetLastError();
-}
-
 // Slices of in_features per column tile: enough jobs for two rounds over the chip.
 uint32_t layer_forward_q_splits(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
@@ -916,11 +502,7 @@ static hipError_t forward_q_t(const uint16_t* x, uint32_t M, const uint8_t* qboo
                            book_bytes, scale, K, g, codes, per_row, in_features, out_features, bias, y, partial, n_tiles, splits,
                            rows_per_split, m_tiles);
     }
-    if (splits > 1) {
-        const uint64_t n = uint64_t(M) * out_features;
-        hipLaunchKernelGGL(forward_q_reduce_kernel<DT>, dim3(uint32_t((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                           partial, n, out_features, splits, scale, bias, y);
-    }
+    if (splits > 1) return launch_layer_forward_reduce(partial, M, out_features, splits, scale, bias, y, DT, s);
     return hipGetLastError();
 }
 
@@ -933,32 +515,6 @@ hipError_t launch_layer_forward_q(const void* x, uint32_t M, const void* qbook, 
     const uint8_t* qb = static_cast<const uint8_t*>(qbook);
     const uint16_t* bs = static_cast<const uint16_t*>(bias);
     uint16_t* ys = static_cast<uint16_t*>(y);
-    if (lds_book_applies(K, g, bits) && M > 16 && M <= 64) {
-#define CC_MQ(DT, BITS, G, MT) return forward_q_mfma_t<DT, BITS, G, MT>(xs, M, qb, book_bytes, scale, K, codes, in_features, out_features, bs, ys, partial, s)
-#define CC_MQ_MT(DT, BITS, G) do { if (M <= 32) CC_MQ(DT, BITS, G, 1); else CC_MQ(DT, BITS, G, 2); } while (0)
-#define CC_MQ_G(DT, BITS) do { if (g == 4) CC_MQ_MT(DT, BITS, 4); else CC_MQ_MT(DT, BITS, 8); } while (0)
-        if (dtype == 1 && bits == 4) CC_MQ_G(1, 4);
-        if (dtype == 1 && bits == 8) CC_MQ_G(1, 8);
-        if (dtype == 2 && bits == 4) CC_MQ_G(2, 4);
-        if (dtype == 2 && bits == 8) CC_MQ_G(2, 8);
-#undef CC_MQ_G
-#undef CC_MQ_MT
-#undef CC_MQ
-        return hipErrorInvalidValue;
-    }
-    if (lds_book_applies(K, g, bits) && M <= 16) {
-#define CC_GV(DT, BITS, G, MB) return forward_q_gemv_t<DT, BITS, G, MB>(xs, M, qb, book_bytes, scale, K, codes, in_features, out_features, bs, ys, partial, s)
-#define CC_GV_MB(DT, BITS, G) do { if (M <= 1) CC_GV(DT, BITS, G, 1); else if (M <= 4) CC_GV(DT, BITS, G, 4); else if (M <= 8) CC_GV(DT, BITS, G, 8); else CC_GV(DT, BITS, G, 16); } while (0)
-#define CC_GV_G(DT, BITS) do { if (g == 4) CC_GV_MB(DT, BITS, 4); else CC_GV_MB(DT, BITS, 8); } while (0)
-        if (dtype == 1 && bits == 4) CC_GV_G(1, 4);
-        if (dtype == 1 && bits == 8) CC_GV_G(1, 8);
-        if (dtype == 2 && bits == 4) CC_GV_G(2, 4);
-        if (dtype == 2 && bits == 8) CC_GV_G(2, 8);
-#undef CC_GV_G
-#undef CC_GV_MB
-#undef CC_GV
-        return hipErrorInvalidValue;
-    }
     const int mt = M > 64 ? 4 : (M > 32 ? 2 : 1);
 #define CC_FQ(DT, MT, BITS) return forward_q_t<DT, MT, BITS>(xs, M, qb, book_bytes, scale, K, g, codes, in_features, out_features, bs, ys, partial, s)
 #define CC_FQ_MT(DT, BITS) do { if (mt == 4) CC_FQ(DT, 4, BITS); else if (mt == 2) CC_FQ(DT, 2, BITS); else CC_FQ(DT, 1, BITS); } while (0)
