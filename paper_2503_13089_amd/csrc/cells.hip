@@ -7,11 +7,8 @@
 // Once per E-step every centroid gets the list of the centroids within a radius R of it; the vectors of its cell with
 // t(x) <= R ("near") are decided on that list alone. It is 10^2 .. 10^3 times shorter than the codebook where the
 // (norm, cosine) windows of sort.hip leave 3 % (d = 4) or 66 % (d = 8) of it: a ball in d dimensions against a shell.
-// The other vectors ("far", 0.7 to 4 %) are collected and go through a windowed matrix-core E-step, 512 to a window. Those of
-// one run of 8192 norm ranks lie together, in order, but the runs in the order in which workgroups come by: with some 60
-// far vectors a run, a window of the 4096x11008 matrix spans a factor of 3 in norm where 4 % would do. That is what far_kernel
-// takes its time for (4.4 of the 20.5 ms of that fit), and why a fit's time moves by 1 to 2 % with anything that moves the
-// timing of far_compact_kernel. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
+// The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, 512
+// neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
 // Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.21, far ones 0.04 to collect and
 // 0.13 to 0.6 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
@@ -184,20 +181,20 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
 
 // Keys and their histogram, the largest magnitude; and what has to happen once per E-step: the radii follow the lengths
 // of the cell's last list (towards the targets, at most 18 % a step) and never exceed what any vector of the cell needed;
-// the bitmap of changed codes and the counters are cleared.
+// the bitmaps of changed codes and far vectors and the refine counter are cleared.
 template <int D>
 __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const float* __restrict__ C, uint32_t K, uint32_t words,
                                                                           int first, uint16_t* __restrict__ keys,
                                                                           uint32_t* __restrict__ hist, CellHead* __restrict__ heads,
-                                                                          uint32_t* __restrict__ changed, WsHeader* hdr)
+                                                                          uint32_t* __restrict__ changed, uint32_t* __restrict__ far_bits, WsHeader* hdr)
 {
     using L = Lists<D>;
     const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
-    if (t == 0) {
-        hdr->far_count = 0;
-        hdr->refine_count = 0;
+    if (t == 0) hdr->refine_count = 0;
+    if (t < words) {
+        changed[t] = 0;
+        far_bits[t] = 0;
     }
-    if (t < words) changed[t] = 0;
     uint32_t m = 0;
     if (t < K) {
         float c[D];
@@ -985,46 +982,68 @@ __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
 }
 
 // ---- far vectors ------------------------------------------------------------------------------------------------------
-// The flagged ranks, in order within a block of 8192 of them, to a dense list with their rows and previous codes; clears
-// the flags. Where a block's share lies in the list depends on scheduling, the results do not.
+// Far vectors among every 8192 norm ranks, and among the pieces of 2048 of them before each.
+constexpr uint32_t kFarPiece = 64;                     // words of the bitmap
+constexpr uint32_t kFarPieces = kThreads / kFarPiece;  // to a run of 8192 ranks
+__global__ __launch_bounds__(kThreads) void far_count_kernel(const uint32_t* __restrict__ far_bits, uint32_t words, uint32_t* __restrict__ runs,
+                                                             uint32_t* __restrict__ before)
+{
+    __shared__ uint32_t piece[kFarPieces];
+    const uint32_t at_word = blockIdx.x * kThreads + threadIdx.x;
+    uint32_t cnt = at_word < words ? uint32_t(__popc(far_bits[at_word])) : 0u;
+    for (int off = kFarPiece / 2; off > 0; off >>= 1) cnt += uint32_t(__shfl_xor(int(cnt), off, 64));
+    if (threadIdx.x % kFarPiece == 0) piece[threadIdx.x / kFarPiece] = cnt;
+    __syncthreads();
+    if (threadIdx.x > kFarPieces) return;
+    uint32_t sum = 0;
+    for (uint32_t i = 0; i < threadIdx.x; ++i) sum += piece[i];
+    if (threadIdx.x < kFarPieces) before[blockIdx.x * kFarPieces + threadIdx.x] = sum;
+    else runs[blockIdx.x] = sum;
+}
+
+// The flagged ranks, in order, to a dense list with their rows and previous codes, a piece per workgroup: far vectors are outliers
+// and lie close together in the norm order (a workgroup per 8192 ranks: 17 to 24 us where 40 to 90 thousand of 4 M are far).
+// Neighbours in the list are neighbours in norm, so the 512 of a window need little more than each of them: the 4096 x 11008 fit
+// spends 1.8 ms on its far vectors, 4.4 when runs of 8192 ranks lay in the order of their workgroups' arrival.
 template <int D>
-__global__ __launch_bounds__(kThreads) void far_compact_kernel(uint32_t* __restrict__ far_bits, uint32_t words,
+__global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* __restrict__ far_bits, uint32_t words,
+                                                               const uint32_t* __restrict__ runs, const uint32_t* __restrict__ before,
                                                                const uint32_t* __restrict__ position, const float* __restrict__ X,
                                                                const uint32_t* __restrict__ idx, WsHeader* hdr,
                                                                uint32_t* __restrict__ far_pos, float* __restrict__ far_x,
                                                                uint32_t* __restrict__ far_idx)
 {
-    __shared__ uint16_t offsets[kThreads * 32];
-    __shared__ uint32_t wave_sum[kWaves];
-    __shared__ uint32_t base;
-    const uint32_t at_word = blockIdx.x * kThreads + threadIdx.x;
-    const uint32_t word = at_word < words ? far_bits[at_word] : 0u, cnt = __popc(word);
-    if (word) far_bits[at_word] = 0u;
+    __shared__ uint16_t offsets[kFarPiece * 32];
+    __shared__ uint32_t total, wave_before[kWaves];
+    const uint32_t run = blockIdx.x / kFarPieces;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = cnt;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = uint32_t(__shfl_up(int(incl), off, 64));
-        if (lane >= off) incl += t;
+    uint32_t b = 0;
+    for (uint32_t r = threadIdx.x; r < run; r += kThreads) b += runs[r];
+    for (int off = 32; off > 0; off >>= 1) b += uint32_t(__shfl_xor(int(b), off, 64));
+    if (lane == 0) wave_before[wave] = b;
+    if (wave == 0) {
+        const uint32_t at_word = blockIdx.x * kFarPiece + lane;
+        const uint32_t word = uint32_t(lane) < kFarPiece && at_word < words ? far_bits[at_word] : 0u, cnt = __popc(word);
+        uint32_t incl = cnt;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t t = uint32_t(__shfl_up(int(incl), off, 64));
+            if (lane >= off) incl += t;
+        }
+        if (lane == 63) total = incl;
+        uint32_t at = incl - cnt;
+        for (uint32_t bits = word; bits != 0; bits &= bits - 1) offsets[at++] = uint16_t(lane * 32 + (__ffs(int(bits)) - 1));
     }
-    if (lane == 63) wave_sum[wave] = incl;
     __syncthreads();
-    uint32_t total = 0, at = incl - cnt;
-    for (int w = 0; w < kWaves; ++w) {
-        if (w < wave) at += wave_sum[w];
-        total += wave_sum[w];
-    }
-    if (threadIdx.x == 0) base = total ? atomicAdd(&hdr->far_count, total) : 0u;
-    for (uint32_t bits = word; bits != 0; bits &= bits - 1)
-        offsets[at++] = uint16_t(threadIdx.x * 32 + uint32_t(__ffs(int(bits)) - 1));
-    __syncthreads();
-    const uint32_t rank0 = blockIdx.x * (kThreads * 32), b0 = base;
-    for (uint32_t e = threadIdx.x; e < total; e += kThreads) {  // dealt out evenly
-        const uint32_t p = position[rank0 + offsets[e]], to = b0 + e;
-        far_pos[to] = p;
-        far_idx[to] = idx[p];
+    uint32_t to = before[blockIdx.x];
+    for (int w = 0; w < kWaves; ++w) to += wave_before[w];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) hdr->far_count = to + total;
+    for (uint32_t e = threadIdx.x; e < total; e += kThreads) {
+        const uint32_t p = position[blockIdx.x * (kFarPiece * 32) + offsets[e]];
+        far_pos[to + e] = p;
+        far_idx[to + e] = idx[p];
 #pragma unroll
         for (int q = 0; q < D / 4; ++q)
-            reinterpret_cast<float4*>(far_x + size_t(to) * D)[q] = reinterpret_cast<const float4*>(X + size_t(p) * D)[q];
+            reinterpret_cast<float4*>(far_x + size_t(to + e) * D)[q] = reinterpret_cast<const float4*>(X + size_t(p) * D)[q];
     }
 }
 
@@ -1186,7 +1205,6 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
     if (first) {
         hipLaunchKernelGGL(cell_first_radius_kernel<D>, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.xsorted, w.idx_sorted,
                            w.cell_heads, C, K, factor, factor * wider);
-        if (hipError_t e = launch_fill_u32(w.far_bits, (N + 31) / 32, 0u, s); e != hipSuccess) return e;
         if (hipError_t e = launch_fill_u32(w.cell_hist, 65536, 0u, s); e != hipSuccess) return e;
     }
     return hipGetLastError();
@@ -1197,7 +1215,7 @@ void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& 
 {
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32;
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
-                       words, first ? 1 : 0, w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.hdr);
+                       words, first ? 1 : 0, w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr);
     hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((tiles * 32 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, tiles * 32, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
@@ -1227,8 +1245,11 @@ void cells_compact_t(uint32_t N, const Workspace& w, hipStream_t s)
 {
     const uint32_t words = (N + 31) / 32;
     const FarView f = far_view(w, N, D);
-    hipLaunchKernelGGL(far_compact_kernel<D>, dim3((words + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.far_bits, words,
-                       w.cell_position, w.xsorted, w.idx_sorted, w.hdr, f.pos, f.x, f.idx);
+    const uint32_t blocks = (words + kThreads - 1) / kThreads;
+    uint32_t *runs = w.sort_hist, *before = runs + blocks;   // no sort runs during an E-step
+    hipLaunchKernelGGL(far_count_kernel, dim3(blocks), dim3(kThreads), 0, s, w.far_bits, words, runs, before);
+    hipLaunchKernelGGL(far_compact_kernel<D>, dim3(blocks * kFarPieces), dim3(kThreads), 0, s, w.far_bits, words, runs, before, w.cell_position,
+                       w.xsorted, w.idx_sorted, w.hdr, f.pos, f.x, f.idx);
 }
 
 template <int D>
