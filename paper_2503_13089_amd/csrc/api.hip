@@ -104,6 +104,26 @@ float guess_width(uint32_t K, uint32_t d)
     return std::min(0.1f, std::max(0.04f, w));
 }
 
+// Bootstrap (only runs on the device when the workspace holds no hint): the nearest centroid inside a guessed window around
+// each vector's own norm and projection. Its codes are only the upper bounds that size what the exact pass looks at, so a
+// poor guess costs time, never correctness. `e` says where vectors and codes lie; the centroids must have been ordered.
+int run_bootstrap(const Ctx& cx, const cc::EStep& e, uint32_t N, uint32_t d, const float* C, uint32_t K, const cc::Workspace& w, hipStream_t s)
+{
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_windows(C, N, d, K, w, guess_width(K, d), s), "assign (guessed windows)");
+    }
+    cc::EStep b = e;
+    b.pack_rows = C; b.pack_perm = w.cperm; b.rows = w.csorted; b.row_ids = w.cperm; b.K = K;
+    b.packed = w.packed; b.packed_tiles = w.packed_tiles; b.windows = w.windows;
+    b.accumulate = false; b.hint_only = true;
+    b.gate = cc::kGateIfF16 | cc::kGateNoHint;
+    CC_TRY_HIP(cc::launch_assign_mfma_f16(b, d, w, s), "assign (bootstrap, fp16 matrix cores)");
+    b.gate = cc::kGateIfNotF16 | cc::kGateNoHint;
+    CC_TRY_HIP(cc::launch_assign_mfma_f32(b, d, w, s), "assign (bootstrap, fp32 matrix cores)");
+    return CC_OK;
+}
+
 // Scoring + refinement on the matrix cores. The input scan (WsHeader::x_not_f16) must have run on this
 // workspace since the last header reset; with pruned = true the vectors must have been norm-ordered
 // (launch_sort_vectors) and the codes are left in norm order in w.idx_sorted.
@@ -124,23 +144,8 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
             cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
             CC_TRY_HIP(cc::launch_sort_centroids(C, d, K, w, s), "assign (centroid norm order)");
         }
-        // Bootstrap (only runs on the device when the workspace holds no hint): the nearest centroid inside a
-        // guessed window around each vector's own norm and projection. Its codes are only the upper bounds that
-        // size the real windows below, so a poor guess costs time, never correctness.
-        if (!have_hint) {
-            {
-                cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-                CC_TRY_HIP(cc::launch_windows(C, N, d, K, w, guess_width(K, d), s), "assign (guessed windows)");
-            }
-            cc::EStep b = e;
-            b.pack_rows = C; b.pack_perm = w.cperm; b.rows = w.csorted; b.row_ids = w.cperm; b.K = K;
-            b.packed = w.packed; b.packed_tiles = w.packed_tiles; b.windows = w.windows;
-            b.accumulate = false; b.hint_only = true;
-            b.gate = cc::kGateIfF16 | cc::kGateNoHint;
-            CC_TRY_HIP(cc::launch_assign_mfma_f16(b, d, w, s), "assign (bootstrap, fp16 matrix cores)");
-            b.gate = cc::kGateIfNotF16 | cc::kGateNoHint;
-            CC_TRY_HIP(cc::launch_assign_mfma_f32(b, d, w, s), "assign (bootstrap, fp32 matrix cores)");
-        }
+        if (!have_hint)
+            if (int rc = run_bootstrap(cx, e, N, d, C, K, w, s)) return rc;
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_windows(C, N, d, K, w, 0.0f, s), "assign (norm windows)");
     }
@@ -167,14 +172,13 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
     return CC_OK;
 }
 
-// One E-step by cells (cells.hip): near vectors on the lists of their cells, far vectors through the windows. `first`: the
-// first one since the vectors were grouped at all; `track`: as in run_assign_matrix. Codes are left in w.idx_sorted.
-int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint32_t K, const cc::Workspace& w, bool first, bool track,
-                     hipStream_t s)
+// One E-step by cells (cells.hip): near vectors on the lists of their cells, far vectors through the windows. `track`: as in run_assign_matrix. Codes are left in w.idx_sorted.
+int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint32_t K, const cc::Workspace& w, cc::Radii radii,
+                     bool track, hipStream_t s)
 {
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, first, s), "assign (centroids and lists of the cells)");
+        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, radii, s), "assign (centroids and lists of the cells)");
     }
     const cc::FarView f = cc::far_view(w, N, d);
     cc::Workspace wf = w;
@@ -270,18 +274,62 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
     return CC_OK;
 }
 
-// Iterations of a fit after which the vectors are grouped by their codes (anew): most codes change early.
-bool regroup_at(int32_t t) { return t == 1 || t == 3 || t == 8; }
+// Whether a fit by cells takes its first E-step by cells too, or by windows. At d = 8 those hold 66 % of the codebook (20 % with rows
+// of different scale), time that grows like N * K; the first way takes two more groupings and lists. 10 iterations, K = 65536, windows /
+// cells: N = 29 M 149.5 / 120.2 ms, with rows of different scale 151.0 / 138.0; 20 M, such rows 112.2 / 109.7; 15 M 82.8 / 74.3 and 87.0 /
+// 88.1; 8 M 53.6 / 50.7 and (20 iterations) 86.3 / 89.2; 2.8 M 28.1 / 29.0. At d = 4 the windows take 1.5 of 18 ms and the fit is no faster
+// without.
+bool cells_from_first(uint64_t N, uint32_t d, uint32_t K) { return d == 8 && N * K >= 1200000000000ull; }
+
+// Iterations of a fit by cells that begin with grouping the vectors by their codes (anew): most codes change early. (29 M vectors
+// of 8 from the first iteration on: after 2 and 5 iterations 120.4 ms, 3 and 8 123.4, 1, 3 and 8 132.8.)
+bool regroup_at(int32_t t, bool from_first) { return from_first ? t == 2 || t == 5 : t == 1 || t == 3 || t == 8; }
+
+// First iteration of a fit by cells (d = 8). The bootstrap's codes are among the nearest few hundred of their vector's cell rather than
+// the nearest: one look at the cell's list makes most of them so, the vectors are grouped again, and the lengths of the lists
+// say what radii the exact ones take.
+int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32_t d_caller, float* C, uint32_t K, cc::Workspace& w,
+                         hipStream_t s)
+{
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_sort_centroids(C, d, K, w, s), "assign (centroid norm order)");
+    }
+    cc::EStep e{};
+    e.profile = cx.prof;
+    e.X = w.xsorted; e.N = N; e.idx = w.idx_sorted;
+    if (int rc = run_bootstrap(cx, e, N, d, C, K, w, s)) return rc;
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, true, s), "assign (grouping by code)");
+        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, cc::kRadiiStay, s), "assign (centroids and lists of the cells)");
+    }
+    {
+        cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
+        CC_TRY_HIP(cc::launch_cells_hints(C, N, d, K, w, s), "assign (best of the lists)");
+    }
+    {
+        cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, false, s), "assign (grouping by code)");
+    }
+    if (int rc = run_assign_cells(cx, N, d, C, K, w, cc::kRadiiJump, false, s)) return rc;
+    cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
+    if (cc::update_sliced_applies(N, d, K, w))
+        CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, false, s), "update (slices)");
+    else
+        CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s), "update (buckets)");
+    return CC_OK;
+}
 
 // Iteration t >= 1 of a fit by cells; the workspace holds the codes, sums and counts of the iteration before.
 int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32_t d_caller, float* C, uint32_t K, cc::Workspace& w,
-                   int32_t t, hipStream_t s)
+                   int32_t t, bool from_first, hipStream_t s)
 {
-    if (regroup_at(t)) {
+    if (regroup_at(t, from_first)) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, t == 1, s), "assign (grouping by code)");
     }
-    if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1, true, s)) return rc;
+    if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1 && !from_first ? cc::kRadiiStay : cc::kRadiiFollow, true, s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
     CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed, true),
                "update (buckets)");
@@ -475,10 +523,12 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
     }
-    const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr;
+    const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr, from_first = cells && cells_from_first(N, D, K);
     for (int32_t t = 0; t < iters; ++t) {
-        if (cells && t > 0) {
-            if (int rc = run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, s)) return rc;
+        if (cells && (t > 0 || from_first)) {
+            if (int rc = t == 0 ? run_cells_first_iter(cx, o.X, n, D, d, o.C_work, K, w, s)
+                                : run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, from_first, s))
+                return rc;
             continue;
         }
         // only the matrix-core path can leave its codes in the workspace; the others write idx directly
@@ -490,7 +540,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
             return rc;
     }
     if (cells) {
-        if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, false, false, s)) return rc;
+        if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, cc::kRadiiFollow, false, s)) return rc;
         CC_TRY_HIP(cc::launch_unpermute(n, idx, w, true, s), "assign (codes to input order)");
         if (inertia)
             CC_TRY_HIP(cc::launch_reduce_dmin(w.dmin, n, w.partials, w.partial_slots, inertia, s), "objective reduction");

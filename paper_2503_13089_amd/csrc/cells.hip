@@ -1,7 +1,8 @@
 // E-step of a fit by cells (Section 3.1: the codes are the argmin over ALL centroids; a centroid can be skipped for a
 // vector only if it provably cannot be that argmin), for sub-vectors of up to 8 numbers and K <= 65536.
 //
-// After the first iteration the vectors are grouped by the code they have: the group of centroid c is its cell. For a
+// After the first iteration, or from a bootstrap's codes on (cells_from_first in api.hip), the vectors are grouped by the code they
+// have: the group of centroid c is its cell. For a
 // vector x of the cell with previous code h, u = ||x - c_h|| bounds the distance of its nearest centroid c', so
 //     ||c - c'|| <= ||x - c|| + ||x - c'|| <= ||x - c|| + u =: t(x).
 // Once per E-step every centroid gets the list of the centroids within a radius R of it; the vectors of its cell with
@@ -180,11 +181,12 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
 // decides nothing but which tile a centroid shares; eight launches of 4 us for a few microseconds of work became three.
 
 // Keys and their histogram, the largest magnitude; and what has to happen once per E-step: the radii follow the lengths
-// of the cell's last list (towards the targets, at most 18 % a step) and never exceed what any vector of the cell needed;
+// of the cell's last list (towards the targets, at most 18 % a step unless the centroids stayed) and never exceed what any vector
+// of the cell needed;
 // the bitmaps of changed codes and far vectors and the refine counter are cleared.
 template <int D>
 __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const float* __restrict__ C, uint32_t K, uint32_t words,
-                                                                          int first, uint16_t* __restrict__ keys,
+                                                                          int radii, uint16_t* __restrict__ keys,
                                                                           uint32_t* __restrict__ hist, CellHead* __restrict__ heads,
                                                                           uint32_t* __restrict__ changed, uint32_t* __restrict__ far_bits, WsHeader* hdr)
 {
@@ -208,16 +210,20 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
         const uint32_t key = ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj);
         keys[t] = uint16_t(key);
         atomicAdd(&hist[key], 1u);
-        if (!first) {
+        if (radii != kRadiiStay) {
             const CellHead h = heads[t];
+            // vectors need longer lists in the first E-step, whose centroids are vectors themselves (29 M, K = 65536: 124 ms with
+            // the targets as they are, 122.5 with 1.6 times as much, 123 with twice)
+            const float longer = radii == kRadiiJump ? 1.6f : 1.0f, most = radii == kRadiiJump ? 2.0f : 1.18f;
             auto next = [&](float r, float target, uint32_t n) {
                 float step = __builtin_sqrtf(__builtin_sqrtf(target / float(max(n, 1u))));
                 if (D == 8) step = __builtin_sqrtf(step);
-                return fminf(r * fminf(fmaxf(step, 0.85f), 1.18f), 1.05f * __uint_as_float(h.tmax));
+                const float to = r * fminf(fmaxf(step, radii == kRadiiJump ? 0.5f : 0.85f), most);
+                return radii == kRadiiJump ? to : fminf(to, 1.05f * __uint_as_float(h.tmax));
             };
-            const float r1 = next(h.r1, L::kTarget1, h.n1);
+            const float r1 = next(h.r1, longer * L::kTarget1, h.n1);
             heads[t].r1 = r1;
-            heads[t].r2 = fmaxf(r1, next(h.r2, L::kTarget2, h.n1 + h.n2));
+            heads[t].r2 = fmaxf(r1, next(h.r2, longer * L::kTarget2, h.n1 + h.n2));
         }
         heads[t].tmax = 0;
         heads[t].mids = 0;
@@ -799,9 +805,12 @@ __device__ __forceinline__ void score_group(const f16x8 (&a)[4], const f16x8 (&b
     }
 }
 
-template <bool MID>
+enum NearMode : int { kNear, kMid, kHint };   // kHint: the best of the list within r1 (or what of it there is room for) for every vector of
+                                              // the cell, no matter whether that is its nearest centroid
+template <int MODE>
 __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
 {
+    constexpr bool MID = MODE == kMid;
     constexpr int D = 8;
     using L = Lists<D>;
     const int lane = threadIdx.x & 63, g = lane >> 4, n16 = lane & 15;
@@ -812,7 +821,9 @@ __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
     const bool whole = usable && head.n2 <= L::kCap2;
     const float r1 = usable ? head.r1 : -1.0f, r2 = whole ? fmaxf(head.r1, head.r2) : r1;
-    const uint32_t len1 = usable ? head.n1 : 0u, len = MID && whole ? head.n1 + head.n2 : len1;
+    const uint32_t len1 = MODE == kHint ? (lists_exist(a.hdr) && head.n1 != 0xffffffffu ? min(head.n1, L::kCap1) : 0u) : (usable ? head.n1 : 0u);
+    const uint32_t len = MID && whole ? head.n1 + head.n2 : len1;
+    if (MODE == kHint && len == 0) return;
     const uint16_t* list = a.lists + size_t(c) * L::kCap;
     auto entry = [&](uint32_t e) { return uint32_t(list[!MID || e < len1 ? e : L::kCap1 + (e - len1)]); };
     const uint32_t cmax_bits = a.hdr->cmax_bits;
@@ -850,7 +861,7 @@ __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
         }
     }
     bool decided = on;
-    if constexpr (!MID) {
+    if constexpr (MODE == kNear) {
         float row[D], ch[D];
         load_row<D>(a.C + size_t(c) * D, row);
         load_row<D>(a.C + size_t(min(hint, a.K - 1)) * D, ch);
@@ -934,6 +945,10 @@ __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
     float d = __builtin_fminf(d0, d1);
     uint32_t k = a.cperm[d0 <= d1 ? p0 : p1];
     if (d0 == d1) k = min(k, a.cperm[p1]);
+    if constexpr (MODE == kHint) {
+        if (decided) a.idx[p] = k;
+        return;
+    }
     float xn = 0.0f;
 #pragma unroll
     for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
@@ -1211,11 +1226,11 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
 }
 
 template <int D>
-void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool first, hipStream_t s)
+void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, hipStream_t s)
 {
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32;
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
-                       words, first ? 1 : 0, w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr);
+                       words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr);
     hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((tiles * 32 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, tiles * 32, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
@@ -1223,20 +1238,23 @@ void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& 
                        w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist);
 }
 
+NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track)
+{
+    return NearArgs{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, N / item_of(d) + K,
+                    w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos, w.idx_sorted, w.dmin,
+                    track ? w.idx_prev : nullptr, track ? w.changed : nullptr, w.hdr};
+}
+
 template <int D>
 void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, hipStream_t s)
 {
-    const uint32_t slots = N / item_of(D) + K;
-    const FarView f = far_view(w, N, D);
-    const NearArgs a{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, slots,
-                     w.cell_lists, w.cell_rank, w.far_bits, f.pos, w.idx_sorted, w.dmin,
-                     track ? w.idx_prev : nullptr, track ? w.changed : nullptr, w.hdr};
-    const dim3 grid((slots + kWaves - 1) / kWaves);
+    const NearArgs a = near_args(C, N, D, K, w, track);
+    const dim3 grid((a.slots + kWaves - 1) / kWaves);
     if constexpr (D == 4) {
         hipLaunchKernelGGL(near_direct_kernel, grid, dim3(kThreads), 0, s, a);
     } else {
-        hipLaunchKernelGGL(near_mfma_kernel<false>, grid, dim3(kThreads), 0, s, a);
-        hipLaunchKernelGGL(near_mfma_kernel<true>, grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(near_mfma_kernel<kNear>, grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(near_mfma_kernel<kMid>, grid, dim3(kThreads), 0, s, a);
     }
 }
 
@@ -1275,11 +1293,11 @@ hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32
     }
 }
 
-hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool first, hipStream_t s)
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, hipStream_t s)
 {
     switch (d) {
-        case 4: cells_centroids_t<4>(C, N, K, w, first, s); break;
-        case 8: cells_centroids_t<8>(C, N, K, w, first, s); break;
+        case 4: cells_centroids_t<4>(C, N, K, w, radii, s); break;
+        case 8: cells_centroids_t<8>(C, N, K, w, radii, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1292,6 +1310,14 @@ hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K,
         case 8: cells_near_t<8>(C, N, K, w, track, s); break;
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
+{
+    if (d != 8) return hipErrorInvalidValue;
+    const NearArgs a = near_args(C, N, d, K, w, false);
+    hipLaunchKernelGGL(near_mfma_kernel<kHint>, dim3((a.slots + kWaves - 1) / kWaves), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -329,8 +329,10 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool 
 // launch_cells_far decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
                               bool first, hipStream_t s);
-hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool first, hipStream_t s);
+enum Radii : int { kRadiiStay, kRadiiFollow, kRadiiJump };   // towards the lists' target lengths: not, a step, all the way (same centroids)
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, hipStream_t s);
 hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s);
+hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t value, hipStream_t s);
