@@ -11,8 +11,8 @@
 // The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, 512
 // neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
-// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.21, far ones 0.04 to collect and
-// 0.13 to 0.6 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
+// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.15, far ones 0.02 to collect and
+// 0.05 to 0.3 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
 // to 3.3, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.09, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
@@ -600,17 +600,20 @@ __device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint
     return true;
 }
 
-// t(x), enlarged by more than the rounding of the two distances
+// t(x), enlarged by more than the rounding of the two distances (the roots are within 1 ulp, those of subnormal numbers zero)
 template <int D>
 __device__ __forceinline__ float cell_bound(const float (&x)[D], const float (&centre)[D], const float (&hinted)[D])
 {
-    return (__builtin_sqrtf(direct_sqdist<D>(x, centre)) + __builtin_sqrtf(direct_sqdist<D>(x, hinted)) * 1.001f) * 1.00001f + 1e-30f;
+    return (__builtin_amdgcn_sqrtf(direct_sqdist<D>(x, centre)) + __builtin_amdgcn_sqrtf(direct_sqdist<D>(x, hinted)) * 1.001f) * 1.00001f + 3e-19f;
 }
 
 // ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
 // Direct-form distances are final: no guard band and no index recovery. Rows past the list are NaN and never win.
 // Bound: vector instructions, 19 per 64 (vector, entry) pairs by the counters where the distance, its comparison and two selects
-// are 11; 0.49 G pairs in 0.21 ms (lists of 43 entries, N = 11 M).
+// are 11; 0.49 G pairs in 0.15 ms (lists of 43 entries, N = 11 M). A workgroup is one wave, as in the kernels for d = 8: two in five
+// items are empty or short, and in a workgroup of four the room of those waves waits for the longest (0.21 ms).
+// Tried: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest
+// t(x): a third fewer instructions in all, 0.20 ms.
 template <int D, int NV>
 __device__ __forceinline__ void scan_list(const float4* rows, uint32_t L, const float (&x)[4][D], float (&bd)[4], uint32_t (&bp)[4],
                                           unsigned long long& ties)
@@ -637,18 +640,21 @@ __device__ __forceinline__ void scan_list(const float4* rows, uint32_t L, const 
     }
 }
 
-__global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
+__global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 {
     constexpr int D = 4;
     using L = Lists<D>;
-    __shared__ float4 rows_all[kWaves][L::kCap + 2];
-    __shared__ uint32_t ids_all[kWaves][L::kCap + 2];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float4 rows[L::kCap + 2];
+    __shared__ uint32_t ids[L::kCap + 2];
+    const int lane = threadIdx.x;
     uint32_t c, first, n;
     CellHead head;
-    if (!near_item(a, blockIdx.x * kWaves + wave, kCellItem, false, c, head, first, n)) return;  // wave-uniform; no barriers below
-    float4* rows = rows_all[wave];
-    uint32_t* ids = ids_all[wave];
+    if (!near_item(a, blockIdx.x, kCellItem, false, c, head, first, n)) return;
+    // of this item, by place within it
+    const float4* X = reinterpret_cast<const float4*>(a.X) + first;
+    uint32_t* idx = a.idx + first;
+    float* dmin = a.dmin + first;
+    const uint16_t* list = a.lists + size_t(c) * L::kCap;
     // lists are complete unless they ran out of room
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1;
     const float R = usable ? head.r1 : -1.0f;
@@ -658,7 +664,7 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
         float4 row = make_float4(qnan, qnan, qnan, qnan);
         uint32_t id = 0;
         if (e < len) {
-            const uint32_t pos = a.lists[size_t(c) * L::kCap + e];
+            const uint32_t pos = list[e];
             row = reinterpret_cast<const float4*>(a.csorted)[pos];
             id = a.cperm[pos];
         }
@@ -675,9 +681,10 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const uint32_t o = v * 64 + lane;
-        const uint32_t p = first + min(o, n - 1);
-        load_row<D>(a.X + size_t(p) * D, x[v]);
-        hint[v] = a.idx[p];
+        const uint32_t i = min(o, n - 1);
+        const float4 t4 = X[i];
+        x[v][0] = t4.x; x[v][1] = t4.y; x[v][2] = t4.z; x[v][3] = t4.w;
+        hint[v] = idx[i];
         float ch[D];
         load_row<D>(a.C + size_t(min(hint[v], a.K - 1)) * D, ch);
         const float t = cell_bound<D>(x[v], cc_row, ch);
@@ -709,8 +716,8 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
             }
         }
         if (live && near[v]) {
-            a.idx[p] = k;
-            a.dmin[p] = bd[v];
+            idx[o] = k;
+            dmin[o] = bd[v];
         }
         if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
         if (a.changed != nullptr) {
@@ -732,8 +739,8 @@ __global__ __launch_bounds__(kThreads) void near_direct_kernel(NearArgs a)
 // comes within the band is decided in direct form over the list, 64 centroids at a time.
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
-// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.7 ms per E-step, N = 2.8 M: 0.27 ms +
-// 0.14 ms, where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
+// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.4 ms per E-step, N = 2.8 M: 0.21 ms +
+// 0.10 ms (0.27 + 0.14 with four waves to a workgroup), where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
 // list, operands, scores, rows), so a wave works alone and keeps 64 vectors at four waves per SIMD: workgroups that shared
 // the list through LDS, 128 vectors per wave, took 6.1 to 7.8 ms for the same.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -808,15 +815,15 @@ __device__ __forceinline__ void score_group(const f16x8 (&a)[4], const f16x8 (&b
 enum NearMode : int { kNear, kMid, kHint };   // kHint: the best of the list within r1 (or what of it there is room for) for every vector of
                                               // the cell, no matter whether that is its nearest centroid
 template <int MODE>
-__global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
+__global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
 {
     constexpr bool MID = MODE == kMid;
     constexpr int D = 8;
     using L = Lists<D>;
-    const int lane = threadIdx.x & 63, g = lane >> 4, n16 = lane & 15;
+    const int lane = threadIdx.x, g = lane >> 4, n16 = lane & 15;
     uint32_t c, first, n;   // MID: `first` is where the positions of the vectors are listed
     CellHead head;
-    if (!near_item(a, blockIdx.x * kWaves + (threadIdx.x >> 6), kSetVectors, MID, c, head, first, n)) return;  // wave-uniform
+    if (!near_item(a, blockIdx.x, kSetVectors, MID, c, head, first, n)) return;
     // lists are complete unless they ran out of room
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
     const bool whole = usable && head.n2 <= L::kCap2;
@@ -833,8 +840,7 @@ __global__ __launch_bounds__(kThreads, 4) void near_mfma_kernel(NearArgs a)
     asm("s_mov_b32 %0, 0xff800000" : "=s"(minus_inf));
     const uint32_t row0 = 4 * g;
     const bool f16 = a.hdr->x_not_f16 == 0;
-    __shared__ f16x8 lows[kWaves][kVT * 64];   // other inputs: what a vector's operand has below its fp16 part
-    f16x8* low = lows[threadIdx.x >> 6];
+    __shared__ f16x8 low[kVT * 64];   // other inputs: what a vector's operand has below its fp16 part
     f16x8 b[kVT];
     Scores s;
     clear_scores(s);
@@ -1249,12 +1255,12 @@ template <int D>
 void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, hipStream_t s)
 {
     const NearArgs a = near_args(C, N, D, K, w, track);
-    const dim3 grid((a.slots + kWaves - 1) / kWaves);
+    const dim3 grid(a.slots), wave(64);
     if constexpr (D == 4) {
-        hipLaunchKernelGGL(near_direct_kernel, grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(near_direct_kernel, grid, wave, 0, s, a);
     } else {
-        hipLaunchKernelGGL(near_mfma_kernel<kNear>, grid, dim3(kThreads), 0, s, a);
-        hipLaunchKernelGGL(near_mfma_kernel<kMid>, grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(near_mfma_kernel<kNear>, grid, wave, 0, s, a);
+        hipLaunchKernelGGL(near_mfma_kernel<kMid>, grid, wave, 0, s, a);
     }
 }
 
@@ -1317,7 +1323,7 @@ hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K
 {
     if (d != 8) return hipErrorInvalidValue;
     const NearArgs a = near_args(C, N, d, K, w, false);
-    hipLaunchKernelGGL(near_mfma_kernel<kHint>, dim3((a.slots + kWaves - 1) / kWaves), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(near_mfma_kernel<kHint>, dim3(a.slots), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
