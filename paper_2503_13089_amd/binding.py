@@ -11,6 +11,7 @@ from dataclasses import dataclass
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libcluscomp.so")
 _lib = None
+torch = None  # the module, from load_library() on: every call below evaluates that before its arguments
 
 EXPORTS = (
     "cc_workspace_bytes", "cc_kmeans_fit", "cc_assign", "cc_lloyd_iter", "cc_update", "cc_decode",
@@ -64,7 +65,7 @@ def lib_path() -> str:
 
 def load_library():
     """Loads the built HIP library; raises if it has not been built (there is no fallback)."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -73,7 +74,9 @@ def load_library():
             "(or __graft_entry__.build()); this package has no CPU fallback")
     # PyTorch ships a HIP runtime of its own, and the tensors passed in live in that runtime's context: it has
     # to be the one this process loads first, so that the library binds to it and not to a second copy
-    import torch  # noqa: F401
+    import torch as module
+
+    torch = module
 
     lib = ctypes.CDLL(_LIB_PATH)
     u64, u32, i32, vp, sz = ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t
@@ -169,8 +172,6 @@ def _check(status: int):
 
 def _ptr(t, dtype, what):
     """Device pointer of a contiguous CUDA(HIP) tensor of the expected dtype, or None."""
-    import torch
-
     if t is None:
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
@@ -179,18 +180,18 @@ def _ptr(t, dtype, what):
         raise TypeError(f"{what}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{what}: must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    import torch
-
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device. The public way builds a Stream object: 2.9 us of a call's 13."""
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _idx_dtype():
-    import torch
-
     return torch.uint32
 
 
@@ -254,8 +255,6 @@ def kmeans_fit(vectors, K: int, iters: int, init_centroids, centroids, idx, iner
                profile=None) -> None:
     """cc_kmeans_fit_ex on the current stream. vectors [N,d] f32, init/centroids [K,d] f32, idx [N] uint32,
     inertia [1] f64 or None, workspace uint8 [>= workspace_bytes]. Asynchronous."""
-    import torch
-
     N, d = vectors.shape
     lib = load_library()
     _check(lib.cc_kmeans_fit_ex(_ptr(vectors, torch.float32, "vectors"), N, d, K, iters,
@@ -266,8 +265,6 @@ def kmeans_fit(vectors, K: int, iters: int, init_centroids, centroids, idx, iner
 
 
 def assign(vectors, centroids, idx, inertia, workspace, assign_mode=None, profile=None) -> None:
-    import torch
-
     N, d = vectors.shape
     K = centroids.shape[0]
     _check(load_library().cc_assign_ex(_ptr(vectors, torch.float32, "vectors"), N, d,
@@ -278,8 +275,6 @@ def assign(vectors, centroids, idx, inertia, workspace, assign_mode=None, profil
 
 def lloyd_iter(vectors, centroids, idx, inertia, counts, workspace, assign_mode=None, profile=None) -> None:
     """cc_lloyd_iter_ex: one E-step + M-step; `centroids` is updated in place."""
-    import torch
-
     N, d = vectors.shape
     K = centroids.shape[0]
     _check(load_library().cc_lloyd_iter_ex(_ptr(vectors, torch.float32, "vectors"), N, d,
@@ -290,8 +285,6 @@ def lloyd_iter(vectors, centroids, idx, inertia, counts, workspace, assign_mode=
 
 
 def update(vectors, idx, prev_centroids, centroids, counts, workspace, profile=None) -> None:
-    import torch
-
     N, d = vectors.shape
     K = prev_centroids.shape[0]
     _check(load_library().cc_update_ex(_ptr(vectors, torch.float32, "vectors"), N, d, _ptr(idx, _idx_dtype(), "idx"),
@@ -302,8 +295,6 @@ def update(vectors, idx, prev_centroids, centroids, counts, workspace, profile=N
 
 
 def decode(centroids, idx, out) -> None:
-    import torch
-
     K, d = centroids.shape
     N = idx.shape[0]
     _check(load_library().cc_decode(_ptr(centroids, torch.float32, "centroids"), K, d, _ptr(idx, _idx_dtype(), "idx"),
@@ -311,8 +302,6 @@ def decode(centroids, idx, out) -> None:
 
 
 def read_stats(workspace) -> Stats:
-    import torch
-
     st = _CStats()
     _check(load_library().cc_read_stats(_ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
                                         ctypes.byref(st), _stream()))
@@ -322,8 +311,6 @@ def read_stats(workspace) -> Stats:
 
 def mfma_f16_probe(A, B, C, D) -> None:
     """cc_mfma_f16_probe: A, B float16 [tiles, 32, 16 * km], C float32 [tiles, 32], D float32 [tiles, 32, 32] (out)."""
-    import torch
-
     tiles, rows, slots = A.shape
     if rows != 32 or slots not in (16, 32) or B.shape != A.shape or C.shape != (tiles, 32) or D.shape != (tiles, 32, 32):
         raise ValueError("A, B: [tiles, 32, 16 or 32]; C: [tiles, 32]; D: [tiles, 32, 32]")
@@ -334,8 +321,6 @@ def mfma_f16_probe(A, B, C, D) -> None:
 
 def mfma_f16_probe16(A, B, C, D) -> None:
     """cc_mfma_f16_probe16: A, B float16 [tiles, 16, 32 * km], C float32 [tiles, 16], D float32 [tiles, 16, 16] (out)."""
-    import torch
-
     tiles, rows, slots = A.shape
     if rows != 16 or slots not in (32, 64) or B.shape != A.shape or C.shape != (tiles, 16) or D.shape != (tiles, 16, 16):
         raise ValueError("A, B: [tiles, 16, 32 or 64]; C: [tiles, 16]; D: [tiles, 16, 16]")
@@ -348,8 +333,6 @@ def mfma_f16_probe16(A, B, C, D) -> None:
 
 def _dtype_code(t) -> int:
     """cc_dtype of a tensor's element type."""
-    import torch
-
     codes = {torch.float32: 0, torch.float16: 1, torch.bfloat16: 2}
     if t.dtype not in codes:
         raise TypeError(f"unsupported element type {t.dtype}")
@@ -369,8 +352,6 @@ def layer_num_codes(in_features: int, out_features: int, g: int) -> int:
 
 
 def layer_vectors(weight, g: int, vectors) -> None:
-    import torch
-
     out_features, in_features = weight.shape
     _check(load_library().cc_layer_vectors(_any_ptr(weight, "weight"), _dtype_code(weight), out_features, in_features, g,
                                            _ptr(vectors, torch.float32, "vectors"), _stream()))
@@ -378,8 +359,6 @@ def layer_vectors(weight, g: int, vectors) -> None:
 
 def layer_pack(centroids, codebook, idx, codes, K: int | None = None) -> None:
     """Either pair (centroids, codebook) / (idx, codes) may be None; K is needed when only codes are packed."""
-    import torch
-
     K, g = (centroids.shape if centroids is not None else (K, 1))
     _check(load_library().cc_layer_pack(_ptr(centroids, torch.float32, "centroids"), K, g, _any_ptr(codebook, "codebook"),
                                         _dtype_code(codebook) if codebook is not None else 1,
@@ -388,8 +367,6 @@ def layer_pack(centroids, codebook, idx, codes, K: int | None = None) -> None:
 
 
 def layer_weight(codebook, codes, in_features: int, out_features: int, weight) -> None:
-    import torch
-
     K, g = codebook.shape
     if weight.dtype != codebook.dtype:
         raise TypeError("weight and codebook must share one element type")
@@ -399,8 +376,6 @@ def layer_weight(codebook, codes, in_features: int, out_features: int, weight) -
 
 
 def layer_codebook_grad(grad_weight, codes, K: int, g: int, grad_codebook, workspace) -> None:
-    import torch
-
     in_features, out_features = grad_weight.shape
     _check(load_library().cc_layer_codebook_grad(_any_ptr(grad_weight, "grad_weight"), _dtype_code(grad_weight), in_features,
                                                  out_features, _ptr(codes, torch.uint16, "codes"), K, g,
@@ -418,8 +393,6 @@ def layer_grad_plan_workspace_bytes(num_codes: int) -> int:
 
 def layer_grad_plan(codes, K: int, plan, workspace) -> None:
     """Orders the code positions by cluster into `plan` (uint8 device tensor), once per layer."""
-    import torch
-
     _check(load_library().cc_layer_grad_plan(_ptr(codes, torch.uint16, "codes"), codes.numel(), K,
                                              _ptr(plan, torch.uint8, "plan"), plan.numel(),
                                              _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
@@ -430,8 +403,6 @@ def layer_codebook_grad_planned_workspace_bytes(num_codes: int, K: int, g: int) 
 
 
 def layer_codebook_grad_planned(grad_weight, K: int, g: int, plan, grad_codebook, workspace) -> None:
-    import torch
-
     in_features, out_features = grad_weight.shape
     _check(load_library().cc_layer_codebook_grad_planned(_any_ptr(grad_weight, "grad_weight"), _dtype_code(grad_weight),
                                                          in_features, out_features, K, g, _ptr(plan, torch.uint8, "plan"),
@@ -445,8 +416,6 @@ def layer_forward_workspace_bytes(M: int, in_features: int, out_features: int) -
 
 
 def layer_forward(x, codebook, codes, out_features: int, bias, y, workspace) -> None:
-    import torch
-
     M, in_features = x.shape
     K, g = codebook.shape
     if x.dtype != codebook.dtype or y.dtype != codebook.dtype or (bias is not None and bias.dtype != codebook.dtype):
@@ -463,8 +432,6 @@ def layer_compress_workspace_bytes(out_features: int, in_features: int, g: int, 
 
 
 def layer_compress(weight, g: int, iters: int, init_ids, codebook, codes, inertia, workspace) -> None:
-    import torch
-
     out_features, in_features = weight.shape
     K = codebook.shape[0]
     _check(load_library().cc_layer_compress(_any_ptr(weight, "weight"), _dtype_code(weight), out_features, in_features, g, K,
@@ -478,8 +445,6 @@ def layer_compress(weight, g: int, iters: int, init_ids, codebook, codes, inerti
 
 def codebook_quantize(centroids, bits: int, qbook, scale, scratch) -> None:
     """qbook: uint8 tensor of K*g (8 bits) or ceil(K*g/2) (4 bits) bytes; scale: 1 float32; scratch: >= 4 bytes."""
-    import torch
-
     K, g = centroids.shape
     _check(load_library().cc_codebook_quantize(_ptr(centroids, torch.float32, "centroids"), K, g, bits,
                                                _ptr(qbook, torch.uint8, "qbook"), _ptr(scale, torch.float32, "scale"),
@@ -487,8 +452,6 @@ def codebook_quantize(centroids, bits: int, qbook, scale, scratch) -> None:
 
 
 def layer_weight_q(qbook, bits: int, scale, K: int, g: int, codes, in_features: int, out_features: int, weight) -> None:
-    import torch
-
     _check(load_library().cc_layer_weight_q(_ptr(qbook, torch.uint8, "qbook"), bits, _ptr(scale, torch.float32, "scale"), K, g,
                                             _ptr(codes, torch.uint16, "codes"), in_features, out_features,
                                             _dtype_code(weight), _any_ptr(weight, "weight"), _stream()))
@@ -499,8 +462,6 @@ def layer_forward_q_workspace_bytes(M: int, in_features: int, out_features: int)
 
 
 def layer_forward_q(x, qbook, bits: int, scale, K: int, g: int, codes, out_features: int, bias, y, workspace) -> None:
-    import torch
-
     M, in_features = x.shape
     if y.dtype != x.dtype or (bias is not None and bias.dtype != x.dtype):
         raise TypeError("x, bias and y must share one element type")
