@@ -12,11 +12,12 @@
 // (g = 4 as fast, g = 6: 60 us where this takes 27); rows gathered from L2 straight into the operands (67 us).
 //
 // Measured, us a call, before (rows from L2 through LDS tiles; the codebook in four parts through LDS; integers by plain
-// multiply-adds) and now. K = 65536, 16 bits: 4096 x 4096, g = 4, M = 1 22.6 / 14.0, M = 16 24.2 / 15.4; 4096 x 11008, M = 1 39.1 / 22.5,
+// multiply-adds) and now. K = 65536, 16 bits: 4096 x 4096, g = 4, M = 1 22.6 / 13.3, M = 16 24.2 / 13.9; 4096 x 11008, M = 1 39.1 / 22.5,
 // M = 16 59.1 / 24.2, M = 64 69.8 / 37.8, M = 256 116 / 93; 4096 x 10997, g = 6, M = 23 49.1 / 27.2; 8192 x 28672, M = 1 144 / 69; g = 9,
-// 4096 x 11008, M = 4 52.3 / 25.2. 4 bits: 8192 x 8192, g = 4, M = 4 42.7 / 18.2, M = 16 113 / 19.3; 4096 x 11008, g = 6, M = 9 210 / 25.6.
-// A call of 4096 x 4096, M = 1: 3 us for the copies, then 2.5 us until the codes are requested (their loads, 8 of 2 bytes a step,
-// take the address unit 10 clocks each), 2 for the column, 3 for the lookups, 1.5 for the sums.
+// 4096 x 11008, M = 4 52.3 / 25.2. K = 4096, g = 8: 4096 x 4096, M = 16 15.8 / 13.2, 2048 x 2048, M = 64 14.6 / 12.6. 4 bits: 8192 x 8192, g = 4,
+// M = 4 42.7 / 17.6, M = 16 113 / 19.3; 4096 x 11008, g = 6, M = 9 210 / 25.6.
+// A call of 4096 x 4096, M = 1: 2.8 us for the copies, then 2.5 us until the codes are requested (their loads, 8 of 2 bytes a step,
+// take the address unit 10 clocks each), 2 for the column, 3 for the lookups, 1 for the sums.
 #include <algorithm>
 #include <type_traits>
 
@@ -31,6 +32,7 @@ constexpr uint32_t kStep = 32;             // in-features of a matrix instructio
 constexpr uint32_t kLds = 160 * 1024;
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr uint32_t kUnits = 256;           // compute units
+constexpr int kSumFloats = 4 * 64 + 8;     // sums of a matrix instruction, and 8 for lanes that read 8 of them to meet 64 banks
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -61,14 +63,15 @@ __device__ __forceinline__ uint64_t make_entry(const uint8_t* __restrict__ book,
     if constexpr (BITS == 16) {
         const uint16_t* row = reinterpret_cast<const uint16_t*>(book) + size_t(k) * g + j0;
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-            if (j0 + j < g) e |= uint64_t(row[j]) << (16 * j);
+        for (uint32_t j = 0; j < J; ++j) {   // loads without a branch: all of them in flight
+            const uint64_t v = row[min(j, g - 1 - j0)];
+            e |= (j0 + j < g ? v : 0ull) << (16 * j);
+        }
     } else {
         const uint64_t bit = (uint64_t(k) * g + j0) * BITS;
         const uint32_t at = uint32_t(bit / 8), shift = uint32_t(bit % 8);   // shift: 0 or 4
 #pragma unroll
-        for (int b = 0; b <= kEntryBytes<BITS, J>; ++b)
-            if (at + b < book_bytes) e |= uint64_t(book[at + b]) << (8 * b);
+        for (uint32_t b = 0; b <= kEntryBytes<BITS, J>; ++b) e |= uint64_t(book[min(at + b, book_bytes - 1)]) << (8 * b);   // past the end: not used
         e = (e >> shift) ^ (BITS == 8 ? 0x8080808080808080ull : 0x8888888888888888ull);
     }
     return e;
@@ -101,10 +104,8 @@ __global__ __launch_bounds__(256) void forward_columns_layout_kernel(const uint8
                                                                      uint32_t MT, uint32_t in_features, u32x4* __restrict__ x_out)
 {
     if (blockIdx.x < book_blocks) {
-        const uint32_t k = blockIdx.x * 256 + threadIdx.x;
-        if (k >= K) return;
-        for (uint32_t set = 0; set < sets; ++set)
-            put_entry<BITS, J>(out + size_t(set) * stride, k, make_entry<BITS, J>(book, book_bytes, g, k, set * J));
+        const uint32_t set = blockIdx.x % sets, k = blockIdx.x / sets * 256 + threadIdx.x;
+        if (k < K) put_entry<BITS, J>(out + size_t(set) * stride, k, make_entry<BITS, J>(book, book_bytes, g, k, set * J));
         return;
     }
     const uint32_t t = (blockIdx.x - book_blocks) * 256 + threadIdx.x;   // read in the order of x
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
     };
     if (steps > 0) {
         request(0, 0);
-        request(1, 1);
+        if (steps > 1) request(1, 1);
     }
     // ---- the columns into LDS. Every workgroup starts at another place, so that they do not all ask the same cache channels
     if (p.laid != nullptr || (p.sets == 1 && uint32_t(E) * 8 == p.g * BITS)) {
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
 
     // ---- the waves of a column group are added and stored, as many rows at a time as there is room for
     constexpr int Q = NC * J, T = MT * Q > 8 ? MT / 2 : MT;
-    float (*red)[Q][4][64] = reinterpret_cast<float (*)[Q][4][64]>(smem);   // [kWaves * T]
+    float (*red)[Q][kSumFloats] = reinterpret_cast<float (*)[Q][kSumFloats]>(smem);   // [kWaves * T], [4][64] each
     const float scale = p.scale != nullptr && p.slices == 1 ? *p.scale : 1.0f;
 #pragma unroll
     for (int t0 = 0; t0 < MT; t0 += T) {
@@ -342,16 +343,16 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) red[wave * T + mt][q][i][lane] = acc[t0 + mt][q / J][q % J][i];
+                for (int i = 0; i < 4; ++i) red[wave * T + mt][q][64 * i + lane] = acc[t0 + mt][q / J][q % J][i];
         __syncthreads();
         const uint32_t width = CW * 16 * Q, here = min(rows > uint32_t(16 * t0) ? rows - 16 * t0 : 0u, uint32_t(16 * T)), count = here * width;
 #pragma unroll 1
         for (uint32_t e = threadIdx.x; e < count; e += kThreads) {
             const uint32_t mm = e / width, rest = e % width, q = rest % Q, c16 = rest / Q % 16, cg = rest / (16 * Q), mt = mm / 16, m = row0 + 16 * t0 + mm;
-            const uint32_t at = 16 * (mm % 16 / 4) + c16, i = mm % 4;
+            const uint32_t at = 64 * (mm % 4) + 16 * (mm % 16 / 4) + c16;
             float part[kWaves], v = 0.0f;
 #pragma unroll
-            for (uint32_t s = 0; s < kWaves; ++s) part[s] = red[min(s * CW + cg, uint32_t(kWaves - 1)) * T + mt][q][i][at];
+            for (uint32_t s = 0; s < kWaves; ++s) part[s] = red[min(s * CW + cg, uint32_t(kWaves - 1)) * T + mt][q][at];
 #pragma unroll
             for (uint32_t s = 0; s < kWaves; ++s) v += s < KW ? part[s] : 0.0f;
             const uint32_t j = set * J + q % J, n = p.g * (column(cg, c16) + q / J) + j;
@@ -385,7 +386,7 @@ Cut choose_cut(uint32_t M, uint32_t in_features, uint32_t out_features, uint32_t
             const uint32_t sl = std::max<uint32_t>(1, std::min({full * kUnits / (tiles * jobs), most_slices, steps}));
             const uint32_t rounds = (tiles * sl * jobs + kUnits - 1) / kUnits, per_slice = (steps + sl - 1) / sl, per_wave = (per_slice + kw - 1) / kw;
             const float clocks = rounds * (fixed + per_wave * std::max(float(kw * cw) * step_clocks, 900.0f)) +
-                                 (sl > 1 ? 9000.0f + float(sl) * M * out_features * 0.003f : 0.0f);
+                                 (sl > 1 ? 6000.0f + float(sl) * M * out_features * 0.003f : 0.0f);
             if (clocks < best.clocks) best = Cut{cw, tiles, (steps + per_slice - 1) / per_slice, per_slice * kStep, clocks};
         }
     }
@@ -396,7 +397,7 @@ template <int DT, int BITS, int J, int MT, int NC>
 hipError_t launch_t(ColumnArgs p, const Cut& c, hipStream_t s)
 {
     p.CW = c.CW; p.tiles = c.tiles; p.slices = c.slices; p.slice_rows = c.slice_rows;
-    const uint32_t lds = std::max<uint32_t>(p.K * kEntryBytes<BITS, J>, kWaves * std::min(MT * NC * J, 8) * 4 * 64 * 4);
+    const uint32_t lds = std::max<uint32_t>(p.K * kEntryBytes<BITS, J>, kWaves * std::min(MT * NC * J, 8) * kSumFloats * 4);
     const auto kernel = layer_forward_columns_kernel<DT, BITS, J, MT, NC>;
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
@@ -447,7 +448,7 @@ hipError_t launch_entries(ColumnArgs p, int dtype, uint32_t most_slices, size_t 
         p.laid = laid ? at : nullptr;
         p.laid_stride = stride;
         p.x_laid = x_laid ? reinterpret_cast<const u32x4*>(at + align256(book_bytes)) : nullptr;
-        const uint32_t book_blocks = laid ? (p.K + 255) / 256 : 0, x_blocks = x_laid ? uint32_t((uint64_t(steps) * 4 * 16 * mt * p.row_tiles + 255) / 256) : 0;
+        const uint32_t book_blocks = laid ? (p.K + 255) / 256 * p.sets : 0, x_blocks = x_laid ? uint32_t((uint64_t(steps) * 4 * 16 * mt * p.row_tiles + 255) / 256) : 0;
         hipLaunchKernelGGL((forward_columns_layout_kernel<BITS, J>), dim3(book_blocks + x_blocks), dim3(256), 0, s, p.book, p.book_bytes, p.g, p.K,
                            p.sets, stride, at, book_blocks, p.x, p.M, mt, p.in_features, const_cast<u32x4*>(p.x_laid));
     }
