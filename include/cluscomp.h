@@ -267,8 +267,8 @@ int cc_layer_weight(const void *codebook, int dtype, uint32_t K, uint32_t g, con
  * Forward pass of the layer (layer listing): y [M * out_features] = x [M * in_features] . W (+ bias), with W
  * as rebuilt by cc_layer_weight. x, codebook, bias (may be NULL) and y share one 16-bit dtype (CC_F16 or
  * CC_BF16); products are exact, accumulation is fp32, y is rounded once (to nearest even). in_features must be
- * a multiple of 8, M <= 2^22; x, y and codebook 16-byte aligned. Two routes, chosen by the shape alone (the
- * second for g = 4 and 8 from M = 257 on, for g = 1, 2, 3 from M = 129, for every other g from M = 385):
+ * a multiple of 8, M <= 2^22; x, y and codebook 16-byte aligned. Two routes, chosen by shape
+ * and workspace alone (the faster one of those there is room for; from M = 385 on always the second):
  *   few rows (decoding): W is never written to memory: what is looked up goes straight into matrix-core operands (g = 4 .. 9:
  *     from LDS, which holds a column of the codebook or a few; else codebook rows gathered from memory, tile by tile). The
  *     summation order is fixed: same inputs, same bits. Workspace: fp32 partial sums of the in-feature slices that fill
@@ -279,7 +279,9 @@ int cc_layer_weight(const void *codebook, int dtype, uint32_t K, uint32_t g, con
  *     finished sum, one rounding. Tiles that do not fill a round of the chip are also split along the contraction
  *     and their fp32 partial tiles added in a fixed order by a second kernel. Workspace: W plus those partial tiles.
  * cc_layer_forward_workspace_bytes(M, in_features, out_features) bytes, 256-byte aligned; may be NULL where the route
- * needs no partial sums. A workspace with room for W and its partial tiles but not for the slices' sums takes the second route at any M.
+ * needs no partial sums. Needed: for g = 1 .. 3 from M = 129 on, for g = 4 and 8 from M = 129, 257 or 385 on (2^25 weights or more, 2^22
+ * or more, fewer) and for every other g from M = 385 on the room of the second route; for fewer rows that of the slices' sums, or that
+ * of the second route.
  */
 size_t cc_layer_forward_workspace_bytes(uint64_t M, uint32_t in_features, uint32_t out_features);
 int cc_layer_forward(const void *x, uint64_t M, const void *codebook, int dtype, uint32_t K, uint32_t g,
@@ -366,7 +368,7 @@ int cc_layer_weight_q(const void *qbook, int bits, const float *scale, uint32_t 
  * weight rebuilt from the integers q themselves. The products x * q are exact, the sum is fp32, the scale
  * multiplies the finished sum, and y is rounded once - so this is slightly more accurate than a product with
  * the 16-bit weight of cc_layer_weight_q, whose entries are each rounded to 16 bits. Same contract otherwise,
- * both routes included (g = 4 .. 9: from the same M on; else the second from M = 65 on, from M = 33 on for layers of 2^24
+ * both routes included (the second one's room is needed from M = 65 on, from M = 33 on for layers of 2^24
  * weights or more, from M = 16 on for layers of 2^25 weights or more with out_features >= 2 * in_features): there the integers q become a 16-bit
  * codebook (exact), the weight is rebuilt from it into the matrix cores' operand layout, and the same matrix-core
  * kernel applies scale and bias to the finished fp32 sum and rounds once.

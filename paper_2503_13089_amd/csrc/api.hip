@@ -738,6 +738,12 @@ size_t dense_forward_bytes(uint64_t M, uint32_t in_features, uint32_t out_featur
 {
     return cc::layer_weight_frag_bytes(in_features, out_features) + cc::layer_gemm_partial_bytes(M, in_features, out_features);
 }
+// The faster route that there is room for; past 384 rows always the rebuilt one
+bool takes_rebuilt(uint64_t M, uint32_t g, int bits, uint32_t in_features, uint32_t out_features, size_t room, size_t fused_need, size_t dense_need)
+{
+    if (room < dense_need) return false;
+    return M > 384 || room < fused_need || cc::rebuild_pays(M, g, bits, in_features, out_features);
+}
 }  // namespace
 
 size_t cc_layer_forward_workspace_bytes(uint64_t M, uint32_t in_features, uint32_t out_features)
@@ -761,24 +767,28 @@ int cc_layer_forward(const void* x, uint64_t M, const void* codebook, int dtype,
         return fail(CC_ERR_ALIGN, "x, y and codebook need 16-byte alignment");
     const size_t fused_need = fused_forward_bytes(M, in_features, out_features), dense_need = dense_forward_bytes(M, in_features, out_features);
     // a workspace that holds the rebuilt weight but not the slices' sums is good for the rebuilt route at any M
-    const bool dense = cc::dense_rows(M, g) || (workspace_bytes < fused_need && workspace_bytes >= dense_need);
-    const size_t need = dense ? dense_need : fused_need;
+    const bool brings = cc::brings_rebuilt(M, g, in_features, out_features) || (workspace_bytes < fused_need && workspace_bytes >= dense_need);
+    const size_t need = brings ? dense_need : fused_need;
     if (need > 0) {
         if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
         if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
         if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (dense) {
-        char* partial = static_cast<char*>(workspace) + cc::layer_weight_frag_bytes(in_features, out_features);
-        CC_TRY_HIP(cc::launch_layer_weight_frag(codebook, K, g, codes, in_features, out_features, workspace, s), "layer weight");
+    const size_t room = workspace != nullptr && aligned(workspace, 256) ? workspace_bytes : 0;
+    if (takes_rebuilt(M, g, 16, in_features, out_features, room, fused_need, dense_need)) {
+        // (the partial sums' room holds the codebook by columns until the product)
+        const size_t frag_bytes = cc::layer_weight_frag_bytes(in_features, out_features);
+        char* partial = static_cast<char*>(workspace) + frag_bytes;
+        CC_TRY_HIP(cc::launch_layer_weight_frag(codebook, 16, dtype, K, g, codes, in_features, out_features, workspace, partial,
+                                                room - frag_bytes, s), "layer weight");
         CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), workspace, dtype, in_features, out_features, nullptr, bias, y,
-                                         reinterpret_cast<float*>(partial), s), "dense product");
+                                         reinterpret_cast<float*>(partial), g, s), "dense product");
         return CC_OK;
     }
     if (cc::layer_forward_columns(g)) {
         CC_TRY_HIP(cc::launch_layer_forward_columns(x, uint32_t(M), codebook, 16, nullptr, K, g, codes, in_features, out_features, bias, y, dtype,
-                                                    workspace, workspace_bytes, cc::layer_forward_splits(M, in_features, out_features), s),
+                                                    workspace, room, cc::layer_forward_splits(M, in_features, out_features), s),
                    "layer forward (by columns)");
         return CC_OK;
     }
@@ -990,7 +1000,7 @@ size_t cc_layer_forward_q_workspace_bytes(uint64_t M, uint32_t in_features, uint
     // whatever the sub-vector length
     size_t bytes = fused_forward_q_bytes(M, in_features, out_features);
     if (M <= 384) bytes += cc::layer_forward_columns_room(M, in_features);
-    return cc::dense_rows_q(M, 1, in_features, out_features) ? std::max(bytes, dense_forward_q_bytes(M, in_features, out_features)) : bytes;
+    return cc::brings_rebuilt_q(M, in_features, out_features) ? std::max(bytes, dense_forward_q_bytes(M, in_features, out_features)) : bytes;
 }
 
 int cc_layer_forward_q(const void* x, uint64_t M, const void* qbook, int bits, const float* scale, uint32_t K, uint32_t g,
@@ -1005,29 +1015,30 @@ int cc_layer_forward_q(const void* x, uint64_t M, const void* qbook, int bits, c
     if (!aligned(x, 16) || !aligned(y, 16) || !aligned(qbook, 16) || !aligned(codes, 2) || !aligned(scale, 4) ||
         (bias && !aligned(bias, 2)))
         return fail(CC_ERR_ALIGN, "x, y and qbook need 16-byte alignment");
-    const bool dense = cc::dense_rows_q(M, g, in_features, out_features);
-    const size_t need = dense ? dense_forward_q_bytes(M, in_features, out_features) : fused_forward_q_bytes(M, in_features, out_features);
+    const size_t fused_need = fused_forward_q_bytes(M, in_features, out_features), dense_need = dense_forward_q_bytes(M, in_features, out_features);
+    const size_t need = cc::brings_rebuilt_q(M, in_features, out_features) ? std::max(fused_need, dense_need) : fused_need;
     if (need > 0) {
         if (workspace == nullptr) return fail(CC_ERR_NULL, "workspace is NULL");
         if (!aligned(workspace, 256)) return fail(CC_ERR_ALIGN, "workspace must be 256-byte aligned");
         if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (dense) {
+    const size_t room = workspace != nullptr && aligned(workspace, 256) ? workspace_bytes : 0;
+    if (takes_rebuilt(M, g, bits, in_features, out_features, room, fused_need, dense_need)) {
         // the integers q themselves as a 16-bit codebook (exact), gathered into the operand layout and multiplied into
         // fp32 sums; scale and bias meet the finished sum
         char* wf = static_cast<char*>(workspace);
         char* book16 = wf + cc::layer_weight_frag_bytes(in_features, out_features);
         float* sums = reinterpret_cast<float*>(book16 + kIntegerBookBytes);
-        CC_TRY_HIP(cc::launch_codebook_integers16(qbook, bits, K, g, dtype, book16, s), "integer codebook");
-        CC_TRY_HIP(cc::launch_layer_weight_frag(book16, K, g, codes, in_features, out_features, wf, s), "integer weight");
-        CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), wf, dtype, in_features, out_features, scale, bias, y, sums, s),
+        CC_TRY_HIP(cc::launch_layer_weight_frag(qbook, bits, dtype, K, g, codes, in_features, out_features, wf, book16, kIntegerBookBytes, s),
+                   "integer weight");
+        CC_TRY_HIP(cc::launch_layer_gemm(x, uint32_t(M), wf, dtype, in_features, out_features, scale, bias, y, sums, g, s),
                    "dense product");
         return CC_OK;
     }
     if (cc::layer_forward_columns(g)) {
         CC_TRY_HIP(cc::launch_layer_forward_columns(x, uint32_t(M), qbook, bits, scale, K, g, codes, in_features, out_features, bias, y, dtype,
-                                                    workspace, workspace_bytes, cc::layer_forward_q_max_splits(M, in_features, out_features), s),
+                                                    workspace, room, cc::layer_forward_q_max_splits(M, in_features, out_features), s),
                    "layer forward (quantised codebook, by columns)");
         return CC_OK;
     }

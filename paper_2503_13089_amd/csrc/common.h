@@ -453,42 +453,55 @@ hipError_t launch_layer_grad_planned(const void* grad, int dtype, uint32_t in_fe
                                      uint32_t g, uint32_t n, const void* plan, float* grad_codebook, void* workspace,
                                      hipStream_t s);
 // ---- prefill-sized batches (layer_gemm.hip): W rebuilt into memory, then one dense product on the matrix cores
-// From where on the rebuilt-weight route is the faster one: the others repeat their lookups for every 64 (by columns) or 128 rows
-// of x, the rebuild takes the same for any number of rows, but longer where it moves rows element by element (all lengths but 4
-// and 8). bf16, us, by columns / rebuilt + product:
-//   g = 4, K = 65536: 4096 x 11008 at 256 rows 93 / 116, at 384 157 / 130; 8192 x 28672 372 / 490, 527 / 540; 4096 x 4096 39 / 67,
-//   62 / 65; 2048 x 2048 20 / 37, 26 / 36.  g = 8, K = 4096: 4096 x 11008 87 / 92, 142 / 107; 4096 x 4096 37 / 49, 59 / 56.
-//   g = 6, K = 65500: 4096 x 11008 at 256 rows 100 / 249, at 384 166 / 253; 8192 x 28672 427 / 1165, 658 / 1170. g = 9: 96 / 252,
-//   163 / 254; 420 / 1160, 688 / 1161.
-// Rows by row: g = 3: 4096 x 10997 at 64 rows 194 / 215, at 128 234 / 218, at 160 388 / 220; 4096 x 4096 at 128 106 / 103. g = 2: 211 /
-// 212, 76 / 99. g = 12, 16: 4096 x 10997 at 384 rows 233 / 254, at 768 427 / 279.
-inline bool dense_rows(uint64_t M, uint32_t g)
+// Rows from which on a call brings room for the rebuilt weight: what a workspace is checked against. Which route a call takes is
+// decided by rebuild_pays where the room allows both.
+inline bool brings_rebuilt(uint64_t M, uint32_t g, uint32_t in_features, uint32_t out_features)
 {
+    const uint64_t weights = uint64_t(in_features) * out_features;
     if (g < 4) return M > 128;
-    return M > (g == 4 || g == 8 ? 256u : 384u);
+    if (g != 4 && g != 8) return M > 384;
+    return M > (weights >= (1ull << 25) ? 128u : (weights >= (1ull << 22) ? 256u : 384u));
 }
-// The same with the quantised codebook (which the rebuild expands first, + 5 us), 4 bits: g = 4, K = 65536: 4096 x 11008 at 192 rows
-// 111 / 110, at 256 111 / 120, at 384 179 / 132; g = 6: 142 / 235 at 256, 212 / 251 at 384. Row by row: 2048 x 2048 at 64 rows
-// 26 / 33, at 96 40 / 34; 4096 x 11008 at 8 rows 54 / 88, at 16 107 / 87; 11008 x 4096 at 16 rows 85 / 87, at 32 101 / 88.
-inline bool dense_rows_q(uint64_t M, uint32_t g, uint32_t in_features, uint32_t out_features)
+inline bool brings_rebuilt_q(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
-    if (layer_forward_columns(g)) return dense_rows(M, g);
     const uint64_t weights = uint64_t(in_features) * out_features;
     if (weights < (1ull << 24)) return M > 64;
     if (weights >= (1ull << 25) && out_features >= 2 * uint64_t(in_features)) return M >= 16;
     return M > 32;
 }
+// From where on the rebuilt-weight route is the faster one: the others repeat their lookups for every 64 (by columns) or 128 rows
+// of x, the rebuild takes the same for any number of rows. bf16, K = 65536, us, by columns / rebuilt + product:
+//   g = 4, 4096 x 4096 at 256 rows 39 / 62, at 320 56 / 59, at 384 63 / 62; 4096 x 11008 at 256 90 / 91, at 320 117 / 107; 8192 x 16384 at 256
+//   208 / 208, at 320 290 / 235; 8192 x 28672 at 128 226 / 317, at 192 367 / 320. g = 8: the same within 5 %. g = 6: 4096 x 11008 at 256 100 /
+//   94, at 320 129 / 112; 2048 x 2048 at 384 26 / 37; 512 x 28672 at 256 60 / 53, at 320
+//   77 / 44. g = 9: 4096 x 11008 97 / 96, 121 / 113; 8192 x 8192 at 128 91 / 119, at 160 141 / 123.
+//   8 bits: g = 4, 4096 x 4096 at 384 63 / 61; 8192 x 28672 at 128 237 / 310, at 192 374 / 330.
+//   4 bits (more arithmetic a lookup): 4096 x 4096 at 192 48 / 54, at 320 83 / 59; 8192 x 8192 at 128 91 / 111, at 192 153 / 121; g = 6, 2048 x
+//   5000 at 128 30 / 38, at 192 49 / 40; g = 9, 4096 x 4096 at 128 47 / 48, at 192 82 / 57; 2048 x 2048 at 384 29 / 39.
+// Row by row: g = 12, 4096 x 4096 at 64 rows 39 / 48, at 96 59 / 50; g = 16, 4096 x 11008 62 / 85, 101 / 88; g = 2, 4096 x 4096 at 4 rows 40 / 36, at
+// 48 46 / 42; integers: g = 12 at 4 rows 71 / 43, g = 3, 2048 x 2048 30 / 25, g = 12, 1024 x 4096 at 32 26 / 27, at 48 32 / 27.
+inline bool rebuild_pays(uint64_t M, uint32_t g, int bits, uint32_t in_features, uint32_t out_features)
+{
+    const uint64_t weights = uint64_t(in_features) * out_features;
+    if (!layer_forward_columns(g)) {
+        if (bits != 16) return M > 32 || weights >= (1ull << 22);
+        return M > (g < 4 ? 32u : 64u);
+    }
+    if (bits == 4) return M > (weights <= (1ull << 22) ? 384u : 128u);
+    if (weights <= (1ull << 24) && out_features <= 8192) return M > 384;
+    return M > (weights < (1ull << 26) || (weights <= (1ull << 27) && (g == 4 || g == 8)) ? 256u : 128u);
+}
 // layer_gemm.hip: the weight rebuilt in the register layout of the matrix cores' B operand (layer_weight_frag_bytes
-// bytes), the integers of a quantised codebook as a 16-bit codebook for that rebuild, and y [M][out] = x [M][in] . W
+// bytes; codebook of 16, 8 or 4 bits, the integers themselves in `dtype`; room: for the codebook as 16-bit numbers, needed for
+// integers only, K * g * 2 bytes, and one more 16-byte piece per column to spare) and y [M][out] = x [M][in] . W
 // (scale: device pointer or NULL, multiplies the finished sum; partial: layer_gemm_partial_bytes(...) bytes of fp32
 // tiles for the tiles whose contraction is cut into slices)
 size_t layer_gemm_partial_bytes(uint64_t M, uint32_t in_features, uint32_t out_features);
 size_t layer_weight_frag_bytes(uint32_t in_features, uint32_t out_features);
-hipError_t launch_layer_weight_frag(const void* codebook, uint32_t K, uint32_t g, const uint16_t* codes, uint32_t in_features,
-                                    uint32_t out_features, void* wf, hipStream_t s);
-hipError_t launch_codebook_integers16(const void* qbook, int bits, uint32_t K, uint32_t g, int dtype, void* book16, hipStream_t s);
+hipError_t launch_layer_weight_frag(const void* codebook, int bits, int dtype, uint32_t K, uint32_t g, const uint16_t* codes, uint32_t in_features,
+                                    uint32_t out_features, void* wf, void* room, size_t room_bytes, hipStream_t s);
 hipError_t launch_layer_gemm(const void* x, uint32_t M, const void* wf, int dtype, uint32_t in_features, uint32_t out_features,
-                             const float* scale, const void* bias, void* y, float* partial, hipStream_t s);
+                             const float* scale, const void* bias, void* y, float* partial, uint32_t g, hipStream_t s);
 // ---- uniformly quantised codebook (layer_quant.hip); bits = 8 or 4
 hipError_t launch_codebook_quantize(const float* centroids, size_t n, int bits, void* qbook, float* scale,
                                     uint32_t* absmax_scratch, hipStream_t s);

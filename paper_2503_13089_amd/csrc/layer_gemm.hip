@@ -1,11 +1,10 @@
 // Forward pass of the compressed linear layer at prefill-sized batches (the paper's layer listing: rebuild the
 // weight from (codebook, codes), then y = x . W + bias), as two hand-written kernels:
 //
-//   1. layer_weight_frag_kernel: the listing's gather, written straight into the register layout of the matrix
-//      cores' B operand. One fragment = 32 output columns x 16 in-features = 64 lanes x 8 consecutive k = 1 KB, lane
-//      (n % 32) + 32 ((k % 16) / 8); fragments of one column block are contiguous along k. 64 x 64 tiles through LDS:
-//      codes are read along a row of W, fragments leave in whole cache lines. Padding (columns past out_features,
-//      in-features past the end of the last fragment) is written as zeros.
+//   1. layer_weight_frag_columns_kernel (small matrices: layer_weight_frag_kernel): the listing's gather, written straight into
+//      the register layout of the matrix cores' B operand. One fragment = 32 output columns x 16 in-features = 64 lanes
+//      x 8 consecutive k = 1 KB; fragments of one column block are contiguous along k. Padding in-features past the
+//      end of the last fragment are zeros; columns past out_features are anything, nothing is stored of their sums.
 //   2. gemm_frag_kernel: y[M][N] = x[M][K] . W on v_mfma_f32_32x32x16_{bf16,f16}. A workgroup of 8 waves owns a
 //      256 x 256 tile of y, each wave 128 x 64 of it (4 x 2 accumulator tiles of 32 x 32, in registers for the whole
 //      contraction), and steps through K in slices of 32. Only x goes through LDS (double-buffered, rows padded to 40
@@ -24,9 +23,8 @@
 // product takes 189 us = 0.98 PFLOP/s. The same loop with every memory instruction taken out (matrix instructions
 // only) takes 130 us: under sustained matrix work the chip clocks near 1.7 GHz instead of 2.4, and the 344 tiles take
 // 1.5 rounds on 256 compute units where 1.34 would do - that, not 2.5 PFLOP/s, is the ceiling of this tile schedule.
-// The rebuild is bound by one codebook row lookup per code, a cache line fill each (58 us for 45 M weights), not by
-// the 2 bytes it writes per weight.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "half_types.h"
@@ -58,8 +56,27 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The columns of a block of 32 lie in the order of n % g first, then the even ones and the odd ones of those: what a column of
+// the codebook fills is together, and so is what one store of the rebuild by columns writes (two code columns a lane; a cache
+// line at g = 4, its two halves of 8 in-features side by side). place and column are each other's inverse.
+__device__ __forceinline__ uint32_t block_place(uint32_t column, uint32_t g)
+{
+    const uint32_t i = column * (1024 / g + 1) >> 10, r = column - i * g;   // column / g, column % g: column < 32, g <= 16
+    const uint32_t count = 32 / g + (r < 32 % g ? 1 : 0);                   // columns with this remainder
+    return r * (32 / g) + min(r, 32 % g) + i / 2 + (i % 2) * ((count + 1) / 2);
+}
+__device__ __forceinline__ uint32_t block_column(uint32_t place, uint32_t g)
+{
+    const uint32_t per = 32 / g, more = 32 % g * (per + 1);   // the first 32 % g remainders have per + 1 columns
+    const uint32_t r = place < more ? place / (per + 1) : (place - more) / per + 32 % g;
+    const uint32_t i = place - r * per - min(r, 32 % g), even = (per + (r < 32 % g ? 2 : 1)) / 2;
+    return r + (i < even ? 2 * i : 2 * (i - even) + 1) * g;
+}
+// 16-byte piece of a fragment with in-features 8 h .. + 7 of the column at a place
+__device__ __forceinline__ uint32_t frag_piece(uint32_t place, uint32_t h) { return place / 4 * 8 + 4 * h + place % 4; }
+
 // ---- 1. rebuild into B-operand fragments: column block nb = n / 32, in-feature block kb = k / 16, fragment
-// (nb * KB + kb) with KB = ceil(in_features / 16) blocks per column block, lane (n % 32) + 32 ((k % 16) / 8), 8 halves
+// (nb * KB + kb) with KB = ceil(in_features / 16) blocks per column block, 16-byte piece frag_piece(block_place(n % 32), (k % 16) / 8)
 // Three steps per 64 x 64 tile: the tile's codes (64 rows of W, the code columns that touch the tile) go to LDS with
 // reads along the rows of the code matrix; then a wave takes one code column and its 64 lanes the 64 rows, so that
 // the elements they write into the transposed tile are neighbours in LDS (lanes along n would hit the same banks);
@@ -120,30 +137,198 @@ __global__ __launch_bounds__(kThreads) void layer_weight_frag_kernel(const uint1
     }
     __syncthreads();
     // fragment q = 4 (column block within the tile) + (in-feature block within the tile): a wave writes one, 1 KB
-    const uint32_t lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
+    const uint32_t lane = threadIdx.x & 63, half = lane / 4 % 2, column = block_column(lane / 8 * 4 + lane % 4, g);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const uint32_t q = pass * 4 + threadIdx.x / 64;
         const uint32_t nb = n_lo / 32 + q / 4, kb = k0 / 16 + q % 4;
         if (nb < NB && kb < KB)
             *reinterpret_cast<uint4*>(wf + (size_t(nb) * KB + kb) * kFragHalves + lane * 8) =
-                *reinterpret_cast<const uint4*>(&tile[((q / 4) * 32 + l32) * LT + (q % 4) * 16 + 8 * h]);
+                *reinterpret_cast<const uint4*>(&tile[((q / 4) * 32 + column) * LT + (q % 4) * 16 + 8 * half]);
     }
 }
 
-// The integers of a quantised codebook (8 bits: signed bytes; 4 bits: two's-complement nibbles, element e in byte
-// e / 2, low nibble first) as 16-bit floats, exact in both formats: the codebook the rebuild above gathers from when
-// the product runs over the integers themselves.
+// The same by columns of the codebook. Row by row, every code is a codebook row from L2, one line each, 0.3 to 0.4 a clock and compute
+// unit; here a workgroup (one per compute unit, 16 waves) keeps J columns of all rows in LDS, an entry of 2 J bytes per row, and writes
+// the elements of the matrix that come from them. What a lane looks up - 8 codes below one another, 2 side by side - are pieces of 16
+// bytes of the fragments, so nothing is transposed. g / J workgroups read the same codes, side by side on one XCD.
+// Measured for 4096 x 11008 (45 M weights; a fill of the 90 MB takes 15 us), us, row by row and now: K = 65536, g = 4 65 / 33,
+// g = 6 192 / 39, g = 8 46 / 36; 8192 x 28672, g = 4 361 / 176. Without the stores 24 us at g = 4, without the
+// lookups 41, without the codes 27, without the columns 33: codes and stores share the way to L2.
+// Tried and no faster: 3, 4 or 6 items' codes ahead; codes 16 columns apart (whole 128-byte stores at g = 8, twice the loads);
+// items along the rows; stores past L2 (20 us slower at g = 6 and 8).
+constexpr int kColumnThreads = 1024;
+constexpr uint32_t kBand = 2;               // code column groups of 32: 128 bytes of a row of codes
+constexpr uint32_t kColumnLds = 160 * 1024;
+constexpr uint32_t kUnits = 256;            // compute units
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32_2 __attribute__((aligned(2)));
+
+template <int J>
+__global__ __launch_bounds__(kColumnThreads, 4) void layer_weight_frag_columns_kernel(
+    const uint16_t* __restrict__ codebook, const uint8_t* __restrict__ laid, uint32_t stride, uint32_t K, uint32_t g, const uint16_t* __restrict__ codes, uint32_t per_row,
+    uint32_t in_features, uint32_t out_features, uint32_t NB, uint32_t KB, uint16_t* __restrict__ wf, uint32_t sets, uint32_t jobs, uint32_t k_steps,
+    uint32_t items, uint32_t per_job)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    constexpr uint32_t E = 2 * J, NC = 2, kWaves = kColumnThreads / 64;
+    const uint32_t lane = threadIdx.x & 63, n16 = lane & 15, kg = lane >> 4;
+    const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+    const uint32_t job = blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8;   // the sets of the same codes on one XCD
+    if (job >= jobs) return;
+    const uint32_t set = job % sets, begin = job / sets * per_job, end = min(begin + per_job, items);
+    // A job's items, 16 NC code columns by 32 in-features: kBand side by side, then down the matrix, then the next kBand. Every 16th
+    // is this wave's.
+    uint32_t code[2][8];
+    struct Item {
+        uint32_t k0, group;
+    };
+    auto item = [&](uint32_t t) {
+        const uint32_t band = t / kBand / k_steps;
+        return Item{(t / kBand - band * k_steps) * 32, band * kBand + t % kBand};
+    };
+    auto next = [&](Item i) {
+        i.k0 += kWaves / kBand * 32;
+        while (i.k0 >= 32 * k_steps) {
+            i.k0 -= 32 * k_steps;
+            i.group += kBand;
+        }
+        return i;
+    };
+    const uint32_t lane_row = 8 * kg * per_row, last_k0 = (k_steps - 1) * 32;
+    const uint32_t lane_row_last = (min(last_k0 + 8 * kg, in_features - 8) - last_k0) * per_row;   // rows past the end: the last 8 again
+    auto column = [&](const Item& i) { return min(i.group * (16 * NC) + n16 * NC, per_row - NC); };
+    auto request = [&](const Item& i, uint32_t (&c)[8]) {
+        const char* from = reinterpret_cast<const char*>(codes + size_t(i.k0) * per_row);
+        const uint32_t at = 2 * ((i.k0 == last_k0 ? lane_row_last : lane_row) + column(i));
+#pragma unroll
+        for (uint32_t r = 0; r < 8; ++r) {
+            const char* q = from + size_t(2 * r) * per_row + at;
+            c[r] = *reinterpret_cast<const u32_2*>(q);
+        }
+    };
+    const uint32_t first = begin + wave, steps = first < end ? (end - first + kWaves - 1) / kWaves : 0u;
+    Item now = item(first), ahead = now;
+    uint32_t asked = 0;
+    auto request_next = [&](uint32_t (&c)[8]) {   // of the wave's last item again where there is none left
+        if (asked > 0 && asked < steps) ahead = next(ahead);
+        ++asked;
+        request(ahead, c);
+    };
+    if (steps > 0) {
+        request_next(code[0]);
+        request_next(code[1]);
+    }
+    // ---- the columns into LDS, each workgroup from another place on
+    if (laid != nullptr) {
+        constexpr int U = 8;
+        const uint8_t* src = laid + size_t(set) * stride;
+        const uint32_t pieces = stride / 16, turn = (blockIdx.x / 8 * 331u + blockIdx.x) % pieces;
+        for (uint32_t i0 = threadIdx.x; i0 < pieces; i0 += U * kColumnThreads) {
+            u32x4 e[U];
+            uint32_t at[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                at[u] = min(i0 + u * kColumnThreads, pieces - 1) + turn;
+                at[u] = at[u] >= pieces ? at[u] - pieces : at[u];
+                e[u] = *reinterpret_cast<const u32x4*>(src + 16 * size_t(at[u]));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) *reinterpret_cast<u32x4*>(smem + 16 * at[u]) = e[u];
+        }
+    } else {
+        constexpr int U = 8;
+        const uint32_t turn = (blockIdx.x / 8 * 331u + blockIdx.x) * 64u % K;
+        for (uint32_t i0 = threadIdx.x; i0 < K; i0 += U * kColumnThreads) {
+            uint16_t e[U][J];
+            uint32_t at[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                at[u] = min(i0 + u * kColumnThreads, K - 1) + turn;
+                at[u] = at[u] >= K ? at[u] - K : at[u];
+#pragma unroll
+                for (uint32_t j = 0; j < J; ++j) e[u][j] = codebook[size_t(at[u]) * g + min(set * J + j, g - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (uint32_t j = 0; j < J; ++j) reinterpret_cast<uint16_t*>(smem)[at[u] * J + j] = e[u][j];
+        }
+    }
+    __syncthreads();
+    const u16x2 last = {uint16_t(K - 1), uint16_t(K - 1)};
+    auto step = [&](uint32_t (&c)[8], auto more) {
+        const uint32_t k = now.k0 + 8 * kg, col = column(now);
+        uint32_t w[NC][4 * J];
+#pragma unroll
+        for (uint32_t v = 0; v < NC; ++v)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const u16x2 both = __builtin_elementwise_min(__builtin_bit_cast(u16x2, c[r]), last);   // never outside the codebook
+                const uint32_t from = uint32_t(both[v]) * E;
+                if constexpr (J == 1) {
+                    u16x2 pair = __builtin_bit_cast(u16x2, w[v][r / 2]);
+                    pair[r % 2] = *reinterpret_cast<const uint16_t*>(smem + from);
+                    w[v][r / 2] = __builtin_bit_cast(uint32_t, pair);
+                } else if constexpr (J == 2) {
+                    w[v][r] = *reinterpret_cast<const uint32_t*>(smem + from);
+                } else {
+                    const uint2 x = *reinterpret_cast<const uint2*>(smem + from);
+                    w[v][2 * r] = x.x; w[v][2 * r + 1] = x.y;
+                }
+            }
+        if constexpr (more) {
+            request_next(c);
+            __builtin_amdgcn_sched_barrier(0);   // not behind the stores
+        }
+        // stores without a branch, so that the wait for the next codes does not become one for everything: what is not part of
+        // the matrix goes to an offset past the end, which the store leaves out
+        const uint32_t nb = min(now.group * (16 * NC), per_row - NC) * g / 32;
+        const size_t left = (size_t(NB) - nb) * KB * (kFragHalves * 2);
+        const auto block = __builtin_amdgcn_make_buffer_rsrc(wf + size_t(nb) * KB * kFragHalves, 0, int(min(left, size_t(0x7fffffff))), 0x00020000);
+#pragma unroll
+        for (uint32_t v = 0; v < NC; ++v)
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const uint32_t e = set * J + j, n = (col + v) * g + e;
+                const bool part = (J == 1 || e < g) && n < out_features && k / 16 < KB;
+                u32x4 b;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (J == 1) b[i] = w[v][i];
+                    else b[i] = __builtin_amdgcn_perm(w[v][(2 * i + 1) * (J / 2) + j / 2], w[v][2 * i * (J / 2) + j / 2], j % 2 ? 0x07060302u : 0x05040100u);
+                    b[i] = k < in_features ? b[i] : 0u;
+                }
+                const uint32_t at = (__umul24(n / 32 - nb, KB) + k / 16) * (kFragHalves * 2) + frag_piece(block_place(n % 32, g), kg & 1) * 16;
+                __builtin_amdgcn_raw_buffer_store_b128(b, block, part ? at : 0x80000000u, 0, 0);
+            }
+        now = next(now);
+    };
+    if (steps == 0) return;
+    uint32_t i = 0;
+    for (; i + 2 < steps; i += 2) {
+        step(code[0], std::true_type{});
+        step(code[1], std::true_type{});
+    }
+    step(code[0], std::false_type{});
+    if (i + 1 < steps) step(code[1], std::false_type{});
+}
+
+// The codebook as 16-bit numbers by sets of J columns, `stride` of them a set (J = g: as it was). Integers of a quantised codebook
+// (8 bits: signed bytes; 4 bits: two's-complement nibbles, element e in byte e / 2, low nibble first) are exact in both formats: the
+// rebuilt matrix and the product hold the integers themselves.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void codebook_integers16_kernel(const uint8_t* __restrict__ qbook, int bits, uint32_t n,
-                                                                       uint16_t* __restrict__ out)
+__global__ __launch_bounds__(kThreads) void codebook_columns_kernel(const uint8_t* __restrict__ book, int bits, uint32_t n, uint32_t g, uint32_t J,
+                                                                    uint32_t stride, uint16_t* __restrict__ out)
 {
     const uint32_t e = blockIdx.x * kThreads + threadIdx.x;
     if (e >= n) return;
-    int q;
-    if (bits == 8) q = int(static_cast<int8_t>(qbook[e]));
-    else q = int(((uint32_t(qbook[e >> 1]) >> (4 * (e & 1))) & 0xFu) ^ 8u) - 8;
-    out[e] = from_f32<DT>(float(q));
+    uint16_t v;
+    if (bits == 16) v = reinterpret_cast<const uint16_t*>(book)[e];
+    else if (bits == 8) v = from_f32<DT>(float(int(static_cast<int8_t>(book[e]))));
+    else v = from_f32<DT>(float(int(((uint32_t(book[e >> 1]) >> (4 * (e & 1))) & 0xFu) ^ 8u) - 8));
+    const uint32_t k = e / g, j = e % g;
+    out[size_t(j / J) * stride + k * J + j % J] = v;
 }
 
 // ---- 2. the product
@@ -155,7 +340,7 @@ template <int DT>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wf, uint32_t M, uint32_t N, uint32_t K, uint32_t NB, uint32_t KB,
     const float* __restrict__ scale, const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, float* __restrict__ partial,
-    uint32_t m_tiles, uint32_t whole, uint32_t f, uint32_t k_per_split, uint32_t jobs)
+    uint32_t m_tiles, uint32_t whole, uint32_t f, uint32_t k_per_split, uint32_t jobs, uint32_t g)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, l32 = lane & 31;
@@ -203,7 +388,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     const uint16_t* b_src[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-        b_src[j] = wf + size_t(min(n0 / 32 + wn * 2 + j, NB - 1)) * KB * kFragHalves + lane * 8;
+        b_src[j] = wf + size_t(min(n0 / 32 + wn * 2 + j, NB - 1)) * KB * kFragHalves + frag_piece(l32, h) * 8;
     auto request = [](u32x4& r, const uint16_t* p) { asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(r) : "v"(p)); };
     auto a_addr = [&](int i, uint32_t k0) { return a_src[i] + (k0 + pk < k_end ? k0 + pk : K - 8); };
     auto b_addr = [&](int j, uint32_t k) { return b_src[j] + size_t(min(k / 16, KB - 1)) * kFragHalves; };
@@ -314,12 +499,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
 
     // ---- epilogue: accumulator register r of lane (l32, h) is row r % 4 + 8 (r / 4) + 4 h, column l32 of its tile
     const float sc = (direct && scale != nullptr) ? *scale : 1.0f;
+    const uint32_t l_column = block_column(l32, g);
     float* ptile = partial + (size_t(cut) * f + split) * (BM * BN);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const uint32_t nl = wn * 64 + 32 * j + l32, n = n0 + nl;
+            const uint32_t nl = wn * 64 + 32 * j + l_column, n = n0 + nl;
             if (n >= N) continue;
             const float bv = (direct && bias != nullptr) ? to_f32<DT>(bias[n]) : 0.0f;
 #pragma unroll
@@ -401,37 +587,52 @@ size_t layer_weight_frag_bytes(uint32_t in_features, uint32_t out_features)
     return align256(size_t((out_features + 31) / 32) * ((in_features + 15) / 16) * kFragHalves * 2);
 }
 
-hipError_t launch_layer_weight_frag(const void* codebook, uint32_t K, uint32_t g, const uint16_t* codes, uint32_t in_features,
-                                    uint32_t out_features, void* wf, hipStream_t s)
+hipError_t launch_layer_weight_frag(const void* codebook, int bits, int dtype, uint32_t K, uint32_t g, const uint16_t* codes, uint32_t in_features,
+                                    uint32_t out_features, void* wf, void* room, size_t room_bytes, hipStream_t s)
 {
-    const uint32_t per_row = (out_features + g - 1) / g;
+    if (dtype != 1 && dtype != 2) return hipErrorInvalidValue;
+    const uint32_t per_row = (out_features + g - 1) / g, KB = (in_features + 15) / 16, NB = (out_features + 31) / 32;
+    const uint32_t J = K * 8 <= kColumnLds ? 4 : (K * 4 <= kColumnLds ? 2 : 1), sets = (g + J - 1) / J;
+    // By columns, unless the matrix is small: the columns' way into LDS costs more than it saves. us a call of 520 rows, row by row / by columns: 512 x 512, g = 4
+    // 23.8 / 25.5, 1024 x 1024 26.4 / 27.9, 2048 x 2048 39.5 / 39.2, 4096 x 4096 70.7 / 62.8; g = 8: 2048 x 2048 37.6 / 39.8, 4096 x 4096 64.9 / 63.2.
+    // Other lengths (rows that no single load fetches): g = 6, 1024 x 1024 29.2 / 28.5, g = 9, 2048 x 2048 51.6 / 41.2.
+    const uint64_t weights = uint64_t(in_features) * out_features;
+    const bool columns = weights > (g == 4 || g == 8 ? 1u << 22 : 1u << 19) && in_features % 8 == 0 && in_features <= (1u << 20) && per_row >= 2;
+    const uint16_t* book = static_cast<const uint16_t*>(codebook);
+    const uint32_t stride = columns ? (K * 2 * J + 15) / 16 * 16 : 0;   // bytes
+    const bool laid = columns && (K >= 8192 || bits != 16) && size_t(sets) * stride <= room_bytes;   // a small one is as soon read row by row
+    if (bits != 16 || laid) {
+        const uint32_t n = K * g;
+        const auto lay = dtype == 1 ? codebook_columns_kernel<1> : codebook_columns_kernel<2>;
+        hipLaunchKernelGGL(lay, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, s, static_cast<const uint8_t*>(codebook), bits, n, g,
+                           laid ? J : g, stride / 2, static_cast<uint16_t*>(room));
+        book = static_cast<const uint16_t*>(room);
+    }
+    if (columns) {
+        const uint32_t k_steps = (in_features + 31) / 32, items = (per_row + 32 * kBand - 1) / (32 * kBand) * kBand * k_steps;
+        const uint32_t parts = std::min(std::max(1u, kUnits / sets), items), per_job = (items + parts - 1) / parts;
+        const uint32_t jobs = (items + per_job - 1) / per_job * sets, lds = std::max(stride, K * 2 * J);
+        auto go = [&](auto kernel) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kernel, dim3((jobs + 7) / 8 * 8), dim3(kColumnThreads), lds, s, book,
+                               laid ? static_cast<const uint8_t*>(room) : static_cast<const uint8_t*>(nullptr), stride, K, g, codes, per_row, in_features,
+                               out_features, NB, KB, static_cast<uint16_t*>(wf), sets, jobs, k_steps, items, per_job);
+            return hipGetLastError();
+        };
+        return J == 4 ? go(layer_weight_frag_columns_kernel<4>) : (J == 2 ? go(layer_weight_frag_columns_kernel<2>) : go(layer_weight_frag_columns_kernel<1>));
+    }
     const dim3 grid((out_features + 63) / 64, (in_features + 63) / 64);
     if (grid.y > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(layer_weight_frag_kernel, grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(codebook), K, g, codes,
-                       per_row, in_features, out_features, (out_features + 31) / 32, (in_features + 15) / 16,
+    hipLaunchKernelGGL(layer_weight_frag_kernel, grid, dim3(kThreads), 0, s, book, K, g, codes, per_row, in_features, out_features, NB, KB,
                        static_cast<uint16_t*>(wf));
-    return hipGetLastError();
-}
-
-hipError_t launch_codebook_integers16(const void* qbook, int bits, uint32_t K, uint32_t g, int dtype, void* book16, hipStream_t s)
-{
-    const uint32_t n = K * g;
-    const dim3 grid((n + kThreads - 1) / kThreads);
-    if (dtype == 1)
-        hipLaunchKernelGGL(codebook_integers16_kernel<1>, grid, dim3(kThreads), 0, s, static_cast<const uint8_t*>(qbook), bits, n,
-                           static_cast<uint16_t*>(book16));
-    else if (dtype == 2)
-        hipLaunchKernelGGL(codebook_integers16_kernel<2>, grid, dim3(kThreads), 0, s, static_cast<const uint8_t*>(qbook), bits, n,
-                           static_cast<uint16_t*>(book16));
-    else
-        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 // y [M][out] = x [M][in] . W, W as written by launch_layer_weight_frag; scale (device, may be NULL) multiplies the
 // finished sum; `partial` holds layer_gemm_partial_bytes(...) bytes
 hipError_t launch_layer_gemm(const void* x, uint32_t M, const void* wf, int dtype, uint32_t in_features, uint32_t out_features,
-                             const float* scale, const void* bias, void* y, float* partial, hipStream_t s)
+                             const float* scale, const void* bias, void* y, float* partial, uint32_t group, hipStream_t s)
 {
     const GemmShape g = gemm_shape(M, in_features, out_features);
     const dim3 grid(8 * ((g.whole + 7) / 8) + 8 * ((g.jobs - g.whole + 7) / 8));
@@ -443,10 +644,10 @@ hipError_t launch_layer_gemm(const void* x, uint32_t M, const void* wf, int dtyp
     if (dtype != 1 && dtype != 2) return hipErrorInvalidValue;
     if (dtype == 1)
         hipLaunchKernelGGL(gemm_frag_kernel<1>, grid, dim3(kGemmThreads), kGemmLdsBytes, s, xs, ws, M, out_features, in_features, NB,
-                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs);
+                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs, group);
     else
         hipLaunchKernelGGL(gemm_frag_kernel<2>, grid, dim3(kGemmThreads), kGemmLdsBytes, s, xs, ws, M, out_features, in_features, NB,
-                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs);
+                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs, group);
     if (g.cut_tiles > 0) {
         const dim3 fgrid(BM * BN / kThreads, g.cut_tiles);
         if (dtype == 1)
