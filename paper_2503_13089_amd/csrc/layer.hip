@@ -7,6 +7,8 @@ namespace cc {
 
 constexpr int kThreads = 256;
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 // ---- element conversions -----------------------------------------------------------------------
 // bf16 is the upper half of the fp32 pattern; rounding to nearest even adds 0x7fff + (lowest kept bit).
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float v)
@@ -102,29 +104,84 @@ hipError_t launch_layer_pack_codes(const uint32_t* idx, uint64_t n, uint32_t K, 
     return hipGetLastError();
 }
 
-// ---- reconstruction: one lane per code; its g elements go to weight[r][c .. c + g) minus the padding.
-// T is the element's storage type (2 or 4 bytes). Lanes of a wave write neighbouring pieces of one row.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void layer_weight_kernel(const T* __restrict__ codebook, uint32_t K, uint32_t g,
-                                                                const uint16_t* __restrict__ codes, uint64_t num_codes,
-                                                                uint32_t per_row, uint32_t out_features,
-                                                                T* __restrict__ weight)
+// ---- reconstruction: weight[r][c .. c + g) = codebook[code of (r, c / g)] minus the padding.
+// Consecutive codes fill consecutive elements, across the ends of rows too: element j of code v goes to v g + j less the padding of
+// the rows before. A wave takes 64 P codes, puts their rows (one load of up to 16 bytes, or two) side by side in LDS where the
+// 16-byte pieces of the output begin, and stores whole pieces; up to 7 elements at either end singly. G is the row in 16-bit units
+// (fp32: 2 g), `padding` and out_features too. No wave needs another one.
+// Element by element the loads and stores are what counts (2 G + 1 an instruction each). 4096 x 11005, K = 65536, us, before and
+// now: g = 4 108 / 49, g = 5 (K = 35000) 119 / 45, g = 6 105 / 38, g = 8 109 / 31, g = 9 121 / 39; 512 x 700 9.3 / 6.6.
+// Now bound by a codebook line from L2 per code (0.3 to 0.4 a clock and compute unit) where K = 65536; K = 4096, g = 4 28.
+template <int G>
+constexpr int kCodesPerLane = G <= 9 ? 4 : (G <= 18 ? 2 : 1);
+
+template <int G>
+struct CodeRow {
+    uint16_t e[G];
+    __device__ __forceinline__ void load(const uint16_t* p)
+    {
+        constexpr int A = G % 8 == 0 ? 16 : (G % 4 == 0 ? 8 : (G % 2 == 0 ? 4 : 2));   // of every row: the codebook begins at 16 bytes
+        __builtin_memcpy(e, __builtin_assume_aligned(p, A), G * 2);
+    }
+};
+
+template <int G, bool EVEN>
+__global__ __launch_bounds__(kThreads) void layer_weight_kernel(const uint16_t* __restrict__ codebook, uint32_t K, const uint16_t* __restrict__ codes,
+                                                                uint64_t num_codes, uint32_t per_row, uint32_t padding, uint16_t* __restrict__ weight)
 {
-    const uint64_t v = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (v >= num_codes) return;
-    const uint32_t r = uint32_t(v / per_row), c = uint32_t(v % per_row) * g;
-    const uint32_t k = min(uint32_t(codes[v]), K - 1);  // never read outside the codebook
-    const T* row = codebook + size_t(k) * g;
-    T* dst = weight + size_t(r) * out_features + c;
-    const uint32_t n = min(g, out_features - c);  // c < out_features always: at most g - 1 padding columns
-    for (uint32_t j = 0; j < n; ++j) dst[j] = row[j];
+    constexpr int P = kCodesPerLane<G>;
+    constexpr uint32_t C = 64 * P;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[kThreads / 64][C * G + 8];
+    const uint32_t lane = threadIdx.x & 63, wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+    const uint64_t first = (uint64_t(blockIdx.x) * (kThreads / 64) + wave) * C;
+    if (first >= num_codes) return;
+    const uint32_t n = uint32_t(min(num_codes - first, uint64_t(C)));
+    const uint64_t r0 = first / per_row;
+    const uint32_t c0 = uint32_t(first - r0 * per_row);
+    uint32_t code[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) code[p] = codes[first + min(lane + 64 * p, n - 1)];
+    CodeRow<G> row[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) row[p].load(codebook + size_t(min(code[p], K - 1)) * G);   // never read outside the codebook
+    const uint64_t begin = first * G - r0 * padding;        // of the wave's elements
+    const uint32_t shift = uint32_t(begin % 8);
+    uint16_t* out = lds[wave];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint32_t i = lane + 64 * p, c = c0 + i;
+        const uint32_t ends = per_row >= C ? (c >= per_row ? 1u : 0u) : c / per_row;   // rows that end before this code
+        const uint32_t keep = c - ends * per_row == per_row - 1 ? G - padding : uint32_t(G);
+        uint16_t* at = out + shift + i * G - ends * padding;
+        if (i < n) {
+            if (EVEN) {
+#pragma unroll
+                for (int j = 0; j < G / 2; ++j)
+                    if (uint32_t(2 * j) < keep)
+                        reinterpret_cast<uint32_t*>(at)[j] = uint32_t(row[p].e[2 * j]) | uint32_t(row[p].e[2 * j + 1]) << 16;
+            } else {
+#pragma unroll
+                for (int j = 0; j < G; ++j)
+                    if (uint32_t(j) < keep) at[j] = row[p].e[j];
+            }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // one wave's LDS accesses are served in order: nothing to wait for
+    const uint32_t last_c = c0 + n - 1, rows_ended = last_c / per_row + (last_c % per_row == per_row - 1 ? 1 : 0);
+    const uint32_t end = shift + n * G - rows_ended * padding;
+    uint16_t* to = weight + (begin - shift);
+    const uint32_t whole_begin = (shift + 7) / 8, whole_end = end / 8;   // pieces
+    for (uint32_t t = whole_begin + lane; t < whole_end; t += 64)
+        __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(out)[t], reinterpret_cast<u32x4*>(to) + t);
+    // the ends, lanes 0 .. 7 and 8 .. 15; one piece may be both
+    const uint32_t e = lane < 8 ? lane : end / 8 * 8 + lane - 8;
+    const bool mine = lane < 8 ? e >= shift && e < min(8 * whole_begin, end) : lane < 16 && e >= max(8 * whole_begin, shift) && e < end;
+    if (mine) to[e] = out[e];
 }
 
-// g = 4 or 8 with no padding and 16-bit elements: whole rows as one 8- or 16-byte piece
-template <typename V>
-__global__ __launch_bounds__(kThreads) void layer_weight_vec_kernel(const V* __restrict__ codebook, uint32_t K,
-                                                                    const uint16_t* __restrict__ codes,
-                                                                    uint64_t num_codes, V* __restrict__ weight)
+// g = 8 with no padding and 16-bit elements: whole rows as one piece
+__global__ __launch_bounds__(kThreads) void layer_weight_vec_kernel(const u32x4* __restrict__ codebook, uint32_t K, const uint16_t* __restrict__ codes,
+                                                                    uint64_t num_codes, u32x4* __restrict__ weight)
 {
     const uint64_t v = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
     if (v >= num_codes) return;
@@ -132,8 +189,22 @@ __global__ __launch_bounds__(kThreads) void layer_weight_vec_kernel(const V* __r
     __builtin_nontemporal_store(codebook[k], &weight[v]);
 }
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <int G>
+hipError_t launch_weight(uint32_t units, const void* codebook, uint32_t K, const uint16_t* codes, uint64_t num_codes, uint32_t per_row, uint32_t padding,
+                         void* weight, hipStream_t s)
+{
+    if constexpr (G <= 32) {
+        if (units != G) return launch_weight<(G < 16 ? G + 1 : G + 2)>(units, codebook, K, codes, num_codes, per_row, padding, weight, s);
+        constexpr uint32_t kCodes = kThreads * kCodesPerLane<G>;
+        const bool even = G % 2 == 0 && padding % 2 == 0;   // every row of the codebook and of the weight begins at 4 bytes
+        const auto kernel = even || G > 16 ? layer_weight_kernel<G, G % 2 == 0> : layer_weight_kernel<(G <= 16 ? G : 16), false>;
+        hipLaunchKernelGGL(kernel, dim3(uint32_t((num_codes + kCodes - 1) / kCodes)), dim3(kThreads), 0, s, static_cast<const uint16_t*>(codebook), K,
+                           codes, num_codes, per_row, padding, static_cast<uint16_t*>(weight));
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_layer_weight(const void* codebook, int dtype, uint32_t K, uint32_t g, const uint16_t* codes,
                                uint32_t in_features, uint32_t out_features, void* weight, hipStream_t s)
@@ -142,20 +213,13 @@ hipError_t launch_layer_weight(const void* codebook, int dtype, uint32_t K, uint
     const uint64_t num_codes = uint64_t(in_features) * per_row;
     const dim3 grid(uint32_t((num_codes + kThreads - 1) / kThreads));
     const bool whole = out_features % g == 0;
-    if (dtype != 0 && whole && g == 4) {
-        hipLaunchKernelGGL(layer_weight_vec_kernel<u32x2>, grid, dim3(kThreads), 0, s, static_cast<const u32x2*>(codebook), K,
-                           codes, num_codes, static_cast<u32x2*>(weight));
-    } else if (dtype != 0 && whole && g == 8) {
-        hipLaunchKernelGGL(layer_weight_vec_kernel<u32x4>, grid, dim3(kThreads), 0, s, static_cast<const u32x4*>(codebook), K,
-                           codes, num_codes, static_cast<u32x4*>(weight));
-    } else if (dtype == 0) {
-        hipLaunchKernelGGL(layer_weight_kernel<uint32_t>, grid, dim3(kThreads), 0, s, static_cast<const uint32_t*>(codebook),
-                           K, g, codes, num_codes, per_row, out_features, static_cast<uint32_t*>(weight));
-    } else {
-        hipLaunchKernelGGL(layer_weight_kernel<uint16_t>, grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(codebook),
-                           K, g, codes, num_codes, per_row, out_features, static_cast<uint16_t*>(weight));
+    if (dtype != 0 && whole && g == 8) {   // 28.2 us at 4096 x 11008, K = 65536, where the general kernel takes 30.5
+        hipLaunchKernelGGL(layer_weight_vec_kernel, grid, dim3(kThreads), 0, s, static_cast<const u32x4*>(codebook), K, codes, num_codes,
+                           static_cast<u32x4*>(weight));
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    const uint32_t unit = dtype == 0 ? 2 : 1;
+    return launch_weight<1>(g * unit, codebook, K, codes, num_codes, per_row, (per_row * g - out_features) * unit, weight, s);
 }
 
 // ---- codebook gradient, first step: the gradient of the weight as fp32 vectors in the layout of the
