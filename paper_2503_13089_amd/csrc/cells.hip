@@ -12,13 +12,14 @@
 // neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
 // Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.15, far ones 0.02 to collect and
-// 0.05 to 0.3 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 2.0
-// to 3.3, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.09, 0.03.
+// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 1.6
+// to 2.4, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.05, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
 // against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
 // kTarget centroids per list, and no more than the largest t(x) of the cell.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "f16_scores.h"
@@ -173,6 +174,13 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
         heads[c].tmax = 0x7f800000u;
     }
 }
+
+constexpr int kFarGroup = 2;   // tiles of 32 centroids that the far vectors score together
+// Up to so many far vectors, 32, 64 and 128 of them share a workgroup: the first two give each of 256 compute units one, and 256 vectors
+// (d = 8), whose operand loads and start values serve twice the products (27.3 instead of 31.8 ms of the 29 M fit), take four rounds
+// to be worth it (2.8 M: 26.7 ms with 256 at any number, 25.5 with 128, 25.0 with this rule).
+constexpr uint32_t kFarFew1 = 32 * 256, kFarFew2 = 64 * 256, kFarFew4 = 4 * 128 * 256;
+static_assert(kStageTiles % kFarGroup == 0 && kStageTilesMax % kFarGroup == 0, "runs share no group, the packed codebook has room for whole ones");
 
 // ---- centroids: order, operands, radii ------------------------------------------------------------------------------
 // Three launches put the centroids into the order of sort.hip's (norm shell, cosine) key with everything the E-step needs
@@ -345,6 +353,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
             none[3] = f16x8{_Float16(60000.0f), o, o, o, o, o, o, o};
         }
     }
+    if (pos >= (K + 31) / 32 * 32) return;   // lists go tile by tile
     char* op = operands + size_t(pos >> 5) * 1024;
     f16x8 lo, hi;
 #pragma unroll
@@ -1025,7 +1034,7 @@ __global__ __launch_bounds__(kThreads) void far_count_kernel(const uint32_t* __r
 // The flagged ranks, in order, to a dense list with their rows and previous codes, a piece per workgroup: far vectors are outliers
 // and lie close together in the norm order (a workgroup per 8192 ranks: 17 to 24 us where 40 to 90 thousand of 4 M are far).
 // Neighbours in the list are neighbours in norm, so the 512 of a window need little more than each of them: the 4096 x 11008 fit
-// spends 1.8 ms on its far vectors, 4.4 when runs of 8192 ranks lay in the order of their workgroups' arrival.
+// spent 1.8 ms on its far vectors with them, 4.4 when runs of 8192 ranks lay in the order of their workgroups' arrival.
 template <int D>
 __global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* __restrict__ far_bits, uint32_t words,
                                                                const uint32_t* __restrict__ runs, const uint32_t* __restrict__ before,
@@ -1068,140 +1077,207 @@ __global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* _
     }
 }
 
-// The far vectors' windowed E-step: 128 vectors (a quarter of a window tile) per workgroup, whose 16 waves take turns at
-// the window's tiles and load operands straight from the packed codebook. The kernel of assign_mfma_f16.hip gives 512
+// The far vectors' windowed E-step: a workgroup takes 32 VT vectors (a part of a window tile), its waves take turns at the
+// window's tiles and load operands straight from the packed codebook. The kernel of assign_mfma_f16.hip gives 512
 // vectors to 4 waves and shares every tile through LDS: better with many vectors, but the far ones are outliers, few, with
-// windows that span much of the codebook, and left most of the chip without work (110 workgroups for 0.5 % of 11 M
-// vectors: 540 us, with 4 waves on 128 vectors 176 us).
-constexpr int kFarWaves = 16, kFarVT = 4;
-constexpr uint32_t kFarSet = 32 * kFarVT;
+// windows that span much of the codebook, and left most of the chip without work.
+// Bound: matrix cores and vector ALUs together, which hardly overlap: 32 and 46 (8 of the 11.5 instructions take the minimum of 16
+// scores) of 82 cycles per 1024 pairs by the counters. Operands are loaded a group ahead across the ends of runs, and the norms of d = 8
+// pass through LDS, loaded by one lane each: 64 lanes that fetch 64 bytes each when their product needs them waited for L2 at every tile
+// (96 cycles). Kernel time of a fit: 29 M vectors of 8 (1.0 to 2 M of them far, 10 iterations) 38.0 -> 27.3 ms, 11 M of 4 1.74 -> 1.28,
+// 2.8 M of 6 (4 to 11 thousand far) 1.78 -> 1.02.
 template <int D>
-__global__ __launch_bounds__(64 * kFarWaves) void far_kernel(const float* __restrict__ X, const float* __restrict__ rows,
-                                                           const uint32_t* __restrict__ cperm, uint32_t K,
-                                                           const char* __restrict__ packed, const uint2* __restrict__ windows,
-                                                           const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx,
-                                                           float* __restrict__ dmin, WsHeader* hdr, uint32_t* __restrict__ refine_list)
+struct FarShape {
+    static constexpr int kWaves = 8, kMostVT = D == 4 ? 4 : 8;
+    static constexpr int kLds = kWaves * kMostVT * 64;
+};
+
+template <int D, int VT>
+__device__ __forceinline__ void far_sets(const float* __restrict__ X, const float* __restrict__ rows, const uint32_t* __restrict__ cperm,
+                                         uint32_t N, uint32_t K, const char* __restrict__ packed, const uint2* __restrict__ windows,
+                                         const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx, float* __restrict__ dmin,
+                                         WsHeader* hdr, uint32_t* __restrict__ refine_list, float* x_best, float* x_second,
+                                         uint32_t* x_grp, float* lds_norms)
 {
     using S = F16Shape<D>;
-    constexpr int GT = 2;
-    __shared__ float x_best[kFarWaves][kFarVT][64], x_second[kFarWaves][kFarVT][64];
-    __shared__ uint32_t x_grp[kFarWaves][kFarVT][64];
-    const uint32_t N = hdr->far_count;
-    if (hdr->x_not_f16 != 0) return;
-    const uint32_t sets = (N + kFarSet - 1) / kFarSet;
+    constexpr int GT = kFarGroup, W = FarShape<D>::kWaves;
+    constexpr uint32_t kSet = 32 * VT;
+    static_assert(GT == 2, "a lane of each half to a tile's norms");
+    static_assert(kWinSlots <= 64, "a lane to a run");
+    static_assert(kWinTile % kSet == 0 && VT <= W, "a set has one window, a wave finishes a tile");
+    const int lane = threadIdx.x & 63, h = lane >> 5, n = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    float* const norms = lds_norms + wave * (32 * GT);
+    const uint32_t sets = (N + kSet - 1) / kSet;
     for (uint32_t set = blockIdx.x; set < sets; set += gridDim.x) {
-    const uint32_t i0 = (sets - 1 - set) * kFarSet;  // the widest windows first
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
-    f16x8 b[kFarVT][1];
+        const uint32_t i0 = (sets - 1 - set) * kSet;  // the widest windows first
+        f16x8 b[VT][1];
 #pragma unroll
-    for (int vt = 0; vt < kFarVT; ++vt) {
-        float x[D];
-        load_row<D>(X + size_t(min(i0 + vt * 32 + n, N - 1)) * D, x);
-        vector_operand<D>(x, h, b[vt]);
-    }
-    float best_of[kFarVT], second_of[kFarVT];
-    uint32_t grp_of[kFarVT];
+        for (int vt = 0; vt < VT; ++vt) {
+            float x[D];
+            load_row<D>(X + size_t(min(i0 + vt * 32 + n, N - 1)) * D, x);
+            vector_operand<D>(x, h, b[vt]);
+        }
+        float best_of[VT], second_of[VT];
+        uint32_t grp_of[VT];
 #pragma unroll
-    for (int vt = 0; vt < kFarVT; ++vt) {
-        best_of[vt] = second_of[vt] = INFINITY;
-        grp_of[vt] = 0;
-    }
-    const uint2* wl = windows + size_t(i0 / kWinTile) * kWinStride;
-    const uint32_t nruns = wl[0].x;
-    uint2 my_run = make_uint2(0u, 0u);
-    if (uint32_t(lane) < nruns) my_run = wl[1 + lane];
-    for (uint32_t r = 0; r < nruns; ++r) {
-        const uint32_t t0 = uint32_t(__builtin_amdgcn_readlane(int(my_run.x), int(r)));
-        const uint32_t t1 = uint32_t(__builtin_amdgcn_readlane(int(my_run.y), int(r)));
-        uint32_t g = t0 / GT + wave;
-        f16x8 a[GT];
+        for (int vt = 0; vt < VT; ++vt) {
+            best_of[vt] = second_of[vt] = INFINITY;
+            grp_of[vt] = 0;
+        }
+        // The window's groups of GT tiles in one sequence (runs share none), the waves taking every W-th: lane r holds where
+        // run r ends in it and what turns a place in the sequence into a group. Tiles of a group beside the run are scored with it.
+        const uint2* wl = windows + size_t(i0 / kWinTile) * kWinStride;
+        uint32_t g0 = 0, count = 0;
+        if (uint32_t(lane) < wl[0].x) {
+            const uint2 run = wl[1 + lane];
+            g0 = run.x / GT;
+            count = (run.y + GT - 1) / GT - g0;
+        }
+        uint32_t run_end = count;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t before = uint32_t(__shfl_up(int(run_end), off, 64));
+            if (lane >= off) run_end += before;
+        }
+        const uint32_t shift = g0 - (run_end - count);
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(run_end), 63));
+        uint32_t r = 0;
+        auto group_at = [&](uint32_t at) {   // ascending places; past the end the last one
+            const uint32_t f = min(at, total - 1);
+            while (f >= uint32_t(__builtin_amdgcn_readlane(int(run_end), int(r)))) ++r;
+            return f + uint32_t(__builtin_amdgcn_readlane(int(shift), int(r)));
+        };
+        float norm = 0.0f;   // d = 8: lane (u, row) loads the norm of a row of tile u, a group ahead
+        auto load = [&](uint32_t group, f16x8 (&to)[GT]) {   // a scalar base and one offset per lane
+            const char* tiles = packed + size_t(group) * (GT * S::kTileBytes);
 #pragma unroll
-        for (int u = 0; u < GT; ++u)
-            a[u] = *reinterpret_cast<const f16x8*>(packed + size_t(min(g * GT + u, t1 - 1)) * S::kTileBytes + lane * 16);
-        for (; g * GT < t1; g += kFarWaves) {
-            f16x8 an[GT];
+            for (int u = 0; u < GT; ++u) to[u] = *reinterpret_cast<const f16x8*>(tiles + (uint32_t(lane) * 16 + u * S::kTileBytes));
+            if constexpr (!S::kNormInK) norm = *reinterpret_cast<const float*>(tiles + (uint32_t(h) * S::kTileBytes + 1024 + 4 * n));
+        };
+        f16x8 from[GT], to[GT];
+        uint32_t at = uint32_t(wave), g = 0;
+        if (at < total) {
+            g = group_at(at);
+            load(g, from);
+        }
+        for (; at < total; at += W) {
+            f32x16 cn[S::kNormInK ? 1 : GT];
+            if constexpr (S::kNormInK) {
 #pragma unroll
-            for (int u = 0; u < GT; ++u)
-                an[u] = *reinterpret_cast<const f16x8*>(packed + size_t(min((g + kFarWaves) * GT + u, t1 - 1)) * S::kTileBytes + lane * 16);
-            float m[kFarVT];
+                for (int q = 0; q < 16; ++q) cn[0][q] = 0.0f;
+            } else {   // rows 16 h .. 16 h + 15 of every tile
+                __builtin_amdgcn_wave_barrier();   // what the group before had there has been read
+                norms[lane] = norm;
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int vt = 0; vt < kFarVT; ++vt) m[vt] = INFINITY;
-#pragma unroll
-            for (int u = 0; u < GT; ++u) {
-                const uint32_t t = g * GT + u;
-                if (t < t0 || t >= t1) continue;  // wave-uniform: outside the run
-                f32x16 cn;
-                if constexpr (S::kNormInK) {
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) cn[q] = 0.0f;
-                } else {
-                    const char* T = packed + size_t(t) * S::kTileBytes + 1024 + 64 * h;
+                for (int u = 0; u < GT; ++u)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float4 v = *reinterpret_cast<const float4*>(T + 16 * q);
-                        cn[4 * q] = v.x; cn[4 * q + 1] = v.y; cn[4 * q + 2] = v.z; cn[4 * q + 3] = v.w;
+                        const float4 v = reinterpret_cast<const float4*>(norms + 32 * u + 16 * h)[q];
+                        cn[u][4 * q] = v.x; cn[u][4 * q + 1] = v.y; cn[u][4 * q + 2] = v.z; cn[u][4 * q + 3] = v.w;
                     }
-                }
+            }
+            const uint32_t next = group_at(at + W);
+            load(next, to);
+            __builtin_amdgcn_sched_barrier(0);   // else the compiler would put the loads behind the products
+            // the products of one tile run while the minima of the one before it are taken
+            float m[VT];
 #pragma unroll
-                for (int vt = 0; vt < kFarVT; ++vt) {
-                    const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b[vt][0], cn, 0, 0, 0);
+            for (int vt = 0; vt < VT; ++vt) m[vt] = INFINITY;
+            f32x16 acc[2];
+            auto product = [&](int i) {
+                acc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(from[i / VT], b[i % VT][0], cn[S::kNormInK ? 0 : i / VT], 0, 0, 0);
+            };
+            product(0);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) m[vt] = __builtin_fminf(__builtin_fminf(m[vt], acc[2 * q]), acc[2 * q + 1]);
-                }
+            for (int i = 0; i < GT * VT; ++i) {
+                if (i + 1 < GT * VT) product(i + 1);
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    m[i % VT] = __builtin_fminf(__builtin_fminf(m[i % VT], acc[i & 1][2 * q]), acc[i & 1][2 * q + 1]);
+            }
+            __builtin_amdgcn_sched_group_barrier(8, 1, 0);
+#pragma unroll
+            for (int i = 0; i < GT * VT; ++i) {   // a product, the eight instructions of the minimum before it, the next product ...
+                __builtin_amdgcn_sched_group_barrier(8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(2, 8, 0);
             }
 #pragma unroll
-            for (int vt = 0; vt < kFarVT; ++vt) {
+            for (int vt = 0; vt < VT; ++vt) {
                 grp_of[vt] = m[vt] < best_of[vt] ? g : grp_of[vt];
                 take_score(best_of[vt], second_of[vt], m[vt]);
             }
+            g = next;
 #pragma unroll
-            for (int u = 0; u < GT; ++u) a[u] = an[u];
+            for (int u = 0; u < GT; ++u) from[u] = to[u];
         }
-    }
+        auto exchange = [&](int w, int vt) { return (w * VT + vt) * 64 + lane; };
 #pragma unroll
-    for (int vt = 0; vt < kFarVT; ++vt) {
-        x_best[wave][vt][lane] = best_of[vt];
-        x_second[wave][vt][lane] = second_of[vt];
-        x_grp[wave][vt][lane] = grp_of[vt];
-    }
-    __syncthreads();
-    if (wave < kFarVT) {  // wave w finishes tile w: index recovery and guard band as in assign_mfma_f16.hip
-    float best = INFINITY, second = INFINITY;
-    uint32_t grp = 0;
+        for (int vt = 0; vt < VT; ++vt) {
+            x_best[exchange(wave, vt)] = best_of[vt];
+            x_second[exchange(wave, vt)] = second_of[vt];
+            x_grp[exchange(wave, vt)] = grp_of[vt];
+        }
+        __syncthreads();
+        if (wave < VT) {  // wave w finishes tile w: index recovery and guard band as in assign_mfma_f16.hip
+            float best = INFINITY, second = INFINITY;
+            uint32_t grp = 0;
 #pragma unroll
-    for (int w = 0; w < kFarWaves; ++w) {
-        const float ob = x_best[w][wave][lane], os = x_second[w][wave][lane];
-        if (ob < best) grp = x_grp[w][wave][lane];
-        second = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
-        best = __builtin_fminf(best, ob);
+            for (int w = 0; w < W; ++w) {
+                const float ob = x_best[exchange(w, wave)], os = x_second[exchange(w, wave)];
+                if (ob < best) grp = x_grp[exchange(w, wave)];
+                second = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
+                best = __builtin_fminf(best, ob);
+            }
+            const uint32_t i_raw = i0 + wave * 32 + n, i = min(i_raw, N - 1);
+            float x[D];
+            load_row<D>(X + size_t(i) * D, x);
+            const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
+            const uint32_t og = uint32_t(__shfl_xor(int(grp), 32, 64));
+            const bool mine = best < ob || (best == ob && h == 0);
+            const float bstar = __builtin_fminf(best, ob);
+            const float sstar = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
+            float bd;
+            uint32_t bk;
+            recover_group<D, GT>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
+            const float od = __shfl_xor(bd, 32, 64);
+            const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
+            const bool take = od < bd || (od == bd && ok < bk);
+            const float dstar = take ? od : bd;
+            const uint32_t cmax_bits = hdr->cmax_bits;
+            const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(cmax_bits, D));
+            const bool safe = (sstar - bstar) > f16_guard_band<D>(x, dstar, sigma, sigma * __uint_as_float(cmax_bits));
+            if (h == 0 && i_raw < N) {
+                const uint32_t p = far_pos[i];
+                idx[p] = take ? ok : bk;
+                dmin[p] = dstar;
+                if (!safe) refine_list[atomicAdd(&hdr->refine_count, 1u)] = i;
+            }
+        }
+        __syncthreads();  // the exchange buffers have been read
     }
-    const uint32_t i_raw = i0 + wave * 32 + n, i = min(i_raw, N - 1);
-    float x[D];
-    load_row<D>(X + size_t(i) * D, x);
-    const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
-    const uint32_t og = uint32_t(__shfl_xor(int(grp), 32, 64));
-    const bool mine = best < ob || (best == ob && h == 0);
-    const float bstar = __builtin_fminf(best, ob);
-    const float sstar = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
-    float bd;
-    uint32_t bk;
-    recover_group<D, GT>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
-    const float od = __shfl_xor(bd, 32, 64);
-    const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
-    const bool take = od < bd || (od == bd && ok < bk);
-    const float dstar = take ? od : bd;
-    const uint32_t cmax_bits = hdr->cmax_bits;
-    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(cmax_bits, D));
-    const bool safe = (sstar - bstar) > f16_guard_band<D>(x, dstar, sigma, sigma * __uint_as_float(cmax_bits));
-    if (h == 0 && i_raw < N) {
-        const uint32_t p = far_pos[i];
-        idx[p] = take ? ok : bk;
-        dmin[p] = dstar;
-        if (!safe) refine_list[atomicAdd(&hdr->refine_count, 1u)] = i;
-    }
-    }
-    __syncthreads();  // the exchange buffers have been read
-    }
+}
+
+template <int D>
+__global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const float* __restrict__ X, const float* __restrict__ rows,
+                                                                       const uint32_t* __restrict__ cperm, uint32_t K,
+                                                                       const char* __restrict__ packed, const uint2* __restrict__ windows,
+                                                                       const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx,
+                                                                       float* __restrict__ dmin, WsHeader* hdr, uint32_t* __restrict__ refine_list)
+{
+    using F = FarShape<D>;
+    __shared__ float x_best[F::kLds], x_second[F::kLds];
+    __shared__ uint32_t x_grp[F::kLds];
+    __shared__ __attribute__((aligned(16))) float norms[F::kWaves * 32 * kFarGroup];
+    const uint32_t N = hdr->far_count;
+    if (hdr->x_not_f16 != 0) return;
+    auto sets = [&](auto vt) {
+        far_sets<D, decltype(vt)::value>(X, rows, cperm, N, K, packed, windows, far_pos, idx, dmin, hdr, refine_list, x_best, x_second, x_grp, norms);
+    };
+    if (N <= kFarFew1) sets(std::integral_constant<int, 1>{});
+    else if (N <= kFarFew2) sets(std::integral_constant<int, 2>{});
+    else if (F::kMostVT == 4 || N <= kFarFew4) sets(std::integral_constant<int, 4>{});
+    else sets(std::integral_constant<int, F::kMostVT>{});
 }
 
 uint32_t item_of(uint32_t d) { return d == 4 ? kCellItem : kSetVectors; }
@@ -1234,11 +1310,11 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
 template <int D>
 void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, hipStream_t s)
 {
-    const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32;
+    const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = (K + 32 * kFarGroup - 1) / (32 * kFarGroup) * (32 * kFarGroup);
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
                        words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr);
     hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
-    hipLaunchKernelGGL(cell_place_kernel<D>, dim3((tiles * 32 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, tiles * 32, w.ckeys,
+    hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
     hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(kThreads), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
                        w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist);
@@ -1280,8 +1356,8 @@ template <int D>
 void cells_far_t(uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
 {
     const FarView f = far_view(w, N, D);
-    const uint32_t sets = (N + kFarSet - 1) / kFarSet;
-    hipLaunchKernelGGL(far_kernel<D>, dim3(std::min(sets, 4096u)), dim3(64 * kFarWaves), 0, s, f.x, w.csorted, w.cperm, K,
+    const uint32_t sets = (N + 31) / 32;
+    hipLaunchKernelGGL(far_kernel<D>, dim3(std::min(sets, 4096u)), dim3(64 * FarShape<D>::kWaves), 0, s, f.x, w.csorted, w.cperm, K,
                        reinterpret_cast<const char*>(w.packed), w.windows, f.pos, w.idx_sorted, w.dmin, w.hdr, f.refine);
 }
 
