@@ -173,12 +173,13 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
 }
 
 // One E-step by cells (cells.hip): near vectors on the lists of their cells, far vectors through the windows. `track`: as in run_assign_matrix. Codes are left in w.idx_sorted.
+// bounded: the E-step before was one by cells with the grouping as it is.
 int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint32_t K, const cc::Workspace& w, cc::Radii radii,
-                     bool track, hipStream_t s)
+                     bool track, bool bounded, hipStream_t s)
 {
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, radii, s), "assign (centroids and lists of the cells)");
+        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, radii, bounded, s), "assign (centroids and lists of the cells)");
     }
     const cc::FarView f = cc::far_view(w, N, d);
     cc::Workspace wf = w;
@@ -186,7 +187,7 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     const uint32_t* far_count = &w.hdr->far_count;
     {
         cc::ProfileScope scope(cx.prof, d == 4 ? cc::kProfEstepDirect : cc::kProfEstepF16, s);
-        CC_TRY_HIP(cc::launch_cells_near(C, N, d, K, w, track, s), "assign (near vectors)");
+        CC_TRY_HIP(cc::launch_cells_near(C, N, d, K, w, track, bounded, s), "assign (near vectors)");
     }
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
@@ -302,7 +303,7 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, true, s), "assign (grouping by code)");
-        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, cc::kRadiiStay, s), "assign (centroids and lists of the cells)");
+        CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, cc::kRadiiStay, false, s), "assign (centroids and lists of the cells)");
     }
     {
         cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
@@ -312,7 +313,7 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, false, s), "assign (grouping by code)");
     }
-    if (int rc = run_assign_cells(cx, N, d, C, K, w, cc::kRadiiJump, false, s)) return rc;
+    if (int rc = run_assign_cells(cx, N, d, C, K, w, cc::kRadiiJump, false, false, s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
     if (cc::update_sliced_applies(N, d, K, w))
         CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, false, s), "update (slices)");
@@ -329,7 +330,7 @@ int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, t == 1, s), "assign (grouping by code)");
     }
-    if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1 && !from_first ? cc::kRadiiStay : cc::kRadiiFollow, true, s)) return rc;
+    if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1 && !from_first ? cc::kRadiiStay : cc::kRadiiFollow, true, !regroup_at(t, from_first), s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
     CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed, true),
                "update (buckets)");
@@ -540,7 +541,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
             return rc;
     }
     if (cells) {
-        if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, cc::kRadiiFollow, false, s)) return rc;
+        if (int rc = run_assign_cells(cx, n, D, o.C_work, K, w, cc::kRadiiFollow, false, true, s)) return rc;
         CC_TRY_HIP(cc::launch_unpermute(n, idx, w, true, s), "assign (codes to input order)");
         if (inertia)
             CC_TRY_HIP(cc::launch_reduce_dmin(w.dmin, n, w.partials, w.partial_slots, inertia, s), "objective reduction");

@@ -12,8 +12,8 @@
 // neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
 // Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.15, far ones 0.02 to collect and
-// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.8, 3.8, 0.2, 1.6
-// to 2.4, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.05, 0.03.
+// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.9, 2.7
+// to 3.6, 0.2, 1.6 to 2.4, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.05, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
 // against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
@@ -56,6 +56,11 @@ __device__ __forceinline__ bool lists_exist(const WsHeader* hdr)
 {
     return hdr->x_not_f16 == 0 || max(hdr->cmax_bits, hdr->absmax_bits) < 0x46800000u;
 }
+
+// What bounds are kept as, towards more and towards less: the upper half of the fp32 number.
+__device__ __forceinline__ uint16_t upper_half(float v) { return uint16_t((__float_as_uint(v) + 0xffffu) >> 16); }   // v >= 0
+__device__ __forceinline__ uint16_t lower_half(float v) { return uint16_t(__float_as_uint(__builtin_fmaxf(v, 0.0f)) >> 16); }
+__device__ __forceinline__ float from_half(uint32_t v) { return __uint_as_float(v << 16); }
 
 // ---- grouping ---------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void cell_keys_kernel(const uint32_t* __restrict__ idx, uint32_t N, uint16_t* __restrict__ keys,
@@ -196,7 +201,9 @@ template <int D>
 __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const float* __restrict__ C, uint32_t K, uint32_t words,
                                                                           int radii, uint16_t* __restrict__ keys,
                                                                           uint32_t* __restrict__ hist, CellHead* __restrict__ heads,
-                                                                          uint32_t* __restrict__ changed, uint32_t* __restrict__ far_bits, WsHeader* hdr)
+                                                                          uint32_t* __restrict__ changed, uint32_t* __restrict__ far_bits, WsHeader* hdr,
+                                                                          const float* __restrict__ csorted, const uint32_t* __restrict__ cinv,
+                                                                          float* __restrict__ drift)
 {
     using L = Lists<D>;
     const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
@@ -218,6 +225,11 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
         const uint32_t key = ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj);
         keys[t] = uint16_t(key);
         atomicAdd(&hist[key], 1u);
+        if (drift != nullptr) {   // how far it can have moved since the E-step before
+            float before[D];
+            load_row<D>(csorted + size_t(cinv[t]) * D, before);
+            drift[t] = __builtin_sqrtf(direct_sqdist<D>(c, before)) * 1.00001f + 3e-19f;
+        }
         if (radii != kRadiiStay) {
             const CellHead h = heads[t];
             // vectors need longer lists in the first E-step, whose centroids are vectors themselves (29 M, K = 65536: 124 ms with
@@ -283,7 +295,8 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
                                                               uint32_t* __restrict__ cperm, uint32_t* __restrict__ cinv,
                                                               float* __restrict__ csorted, char* __restrict__ packed,
                                                               char* __restrict__ operands, char* __restrict__ flat,
-                                                              const WsHeader* __restrict__ hdr)
+                                                              const WsHeader* __restrict__ hdr, const float* __restrict__ drift,
+                                                              uint16_t* __restrict__ moves)
 {
     using S = F16Shape<D>;
     static_assert(S::KM == 1, "one matrix instruction per tile");
@@ -299,6 +312,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         pos = atomicAdd(&cursor[keys[k]], 1u);
         cperm[pos] = k;
         cinv[k] = pos;
+        if (drift != nullptr) moves[pos] = upper_half(drift[k]);
 #pragma unroll
         for (int q = 0; q < D / 4; ++q)
             reinterpret_cast<float4*>(csorted + size_t(pos) * D)[q] = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
@@ -380,12 +394,15 @@ __global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __res
                                                               uint32_t K, const char* __restrict__ operands, uint32_t ntiles,
                                                               const uint32_t* __restrict__ key_starts, CellHead* __restrict__ heads,
                                                               uint32_t N, WsHeader* hdr, uint16_t* __restrict__ lists,
-                                                              uint32_t* __restrict__ hist)
+                                                              uint32_t* __restrict__ hist, uint32_t* __restrict__ queued_near)
 {
     using L = Lists<D>;
     __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32];
     __shared__ uint2 queues[kWaves][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
-    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < 65536; i += gridDim.x * kThreads) hist[i] = 0;  // for the next E-step
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < 65536; i += gridDim.x * kThreads) {
+        hist[i] = 0;  // for the next E-step
+        if (D == 8) queued_near[i] = 0;
+    }
     if (!lists_exist(hdr)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
     const uint32_t p0 = blockIdx.x * 32;
@@ -575,9 +592,14 @@ struct NearArgs {
     const uint16_t* lists;
     const uint32_t* rank;
     uint32_t* far_bits;
-    uint32_t* mids;             // d = 8: positions of the vectors between r1 and r2, those of a cell from its start on
+    uint32_t* queues;           // d = 8: positions of vectors to be scored, in their cell's places: those within r1 from its first on,
+                                // those between r1 and r2 from its last backwards
+    uint32_t* queued_near;      // [K] how many of the former (the latter: CellHead::mids)
+    const uint32_t* moved;      // [K] most that a centroid of the list within r1 / of the whole list has moved: upper halves, low / high
+    uint16_t* bound;            // by position: no centroid but the code's is nearer than that (lower_half); NULL: nobody asks
+    bool bounded;               // the E-step before was one by cells, of this grouping
     uint32_t* idx;
-    float* dmin;
+    float* dmin;                // NULL: nobody reads the distances
     uint32_t* prev_out;         // NULL: changes are not tracked
     uint32_t* changed;
     WsHeader* hdr;
@@ -594,7 +616,10 @@ __device__ __forceinline__ void or_bits(uint32_t* bits, uint32_t p0, unsigned lo
 
 __device__ __forceinline__ void or_bit(uint32_t* bits, uint32_t p) { atomicOr(bits + (p >> 5), 1u << (p & 31u)); }
 
-__device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint32_t item, bool mid, uint32_t& c, CellHead& head,
+// What a work item is a part of: the vectors of a cell, or one of its queues.
+enum ItemOf : int { kMembers, kQueuedNear, kQueuedMid };
+// first: of the vectors (kMembers), else the place in the queue of the first of them.
+__device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint32_t item, ItemOf of, uint32_t& c, CellHead& head,
                                           uint32_t& first, uint32_t& n)
 {
     if (slot >= a.slots) return false;
@@ -602,18 +627,22 @@ __device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint
     if (c >= a.K) return false;
     head = a.heads[c];
     const uint32_t at = (slot - (head.start / item + c)) * item;
-    first = head.start + at;
-    const uint32_t have = mid ? head.mids : head.members;
+    first = of == kQueuedMid ? head.start + head.members - 1 - at : head.start + at;
+    const uint32_t have = of == kMembers ? head.members : (of == kQueuedMid ? head.mids : a.queued_near[c]);
     if (at >= have) return false;
     n = min(item, have - at);
     return true;
 }
 
 // t(x), enlarged by more than the rounding of the two distances (the roots are within 1 ulp, those of subnormal numbers zero)
-template <int D>
-__device__ __forceinline__ float cell_bound(const float (&x)[D], const float (&centre)[D], const float (&hinted)[D])
+__device__ __forceinline__ float cell_bound(float to_centre, float to_hinted)
 {
-    return (__builtin_amdgcn_sqrtf(direct_sqdist<D>(x, centre)) + __builtin_amdgcn_sqrtf(direct_sqdist<D>(x, hinted)) * 1.001f) * 1.00001f + 3e-19f;
+    return (to_centre + to_hinted * 1.001f) * 1.00001f + 3e-19f;
+}
+template <int D>
+__device__ __forceinline__ float rough_distance(const float (&x)[D], const float (&c)[D])
+{
+    return __builtin_amdgcn_sqrtf(direct_sqdist<D>(x, c));
 }
 
 // ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
@@ -658,11 +687,11 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
     const int lane = threadIdx.x;
     uint32_t c, first, n;
     CellHead head;
-    if (!near_item(a, blockIdx.x, kCellItem, false, c, head, first, n)) return;
+    if (!near_item(a, blockIdx.x, kCellItem, kMembers, c, head, first, n)) return;
     // of this item, by place within it
     const float4* X = reinterpret_cast<const float4*>(a.X) + first;
     uint32_t* idx = a.idx + first;
-    float* dmin = a.dmin + first;
+    float* dmin = a.dmin != nullptr ? a.dmin + first : nullptr;
     const uint16_t* list = a.lists + size_t(c) * L::kCap;
     // lists are complete unless they ran out of room
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1;
@@ -696,7 +725,7 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
         hint[v] = idx[i];
         float ch[D];
         load_row<D>(a.C + size_t(min(hint[v], a.K - 1)) * D, ch);
-        const float t = cell_bound<D>(x[v], cc_row, ch);
+        const float t = cell_bound(rough_distance<D>(x[v], cc_row), rough_distance<D>(x[v], ch));
         near[v] = t <= R;
         if (o < n) tm = __builtin_fmaxf(tm, t);
         bd[v] = INFINITY;
@@ -726,7 +755,7 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
         }
         if (live && near[v]) {
             idx[o] = k;
-            dmin[o] = bd[v];
+            if (dmin != nullptr) dmin[o] = bd[v];
         }
         if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
         if (a.changed != nullptr) {
@@ -748,7 +777,8 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 // comes within the band is decided in direct form over the list, 64 centroids at a time.
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
-// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.4 ms per E-step, N = 2.8 M: 0.21 ms +
+// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.4 ms per E-step that scores every vector, 1.1 to 2.0
+// + 1.2 to 1.6 ms with 0.38 to sort out those that need not be and 0.07 for the moves of the lists; N = 2.8 M: 0.21 ms +
 // 0.10 ms (0.27 + 0.14 with four waves to a workgroup), where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
 // list, operands, scores, rows), so a wave works alone and keeps 64 vectors at four waves per SIMD: workgroups that shared
 // the list through LDS, 128 vectors per wave, took 6.1 to 7.8 ms for the same.
@@ -821,18 +851,135 @@ __device__ __forceinline__ void score_group(const f16x8 (&a)[4], const f16x8 (&b
     }
 }
 
-enum NearMode : int { kNear, kMid, kHint };   // kHint: the best of the list within r1 (or what of it there is room for) for every vector of
+// Most that a centroid of a cell's list has moved since the E-step before: within r1, and on the whole list. One wave per cell, the moves of
+// all centroids in LDS.
+constexpr int kMovedThreads = 1024;
+__global__ __launch_bounds__(kMovedThreads) void cell_moved_kernel(const uint16_t* __restrict__ moves, uint32_t K, const CellHead* __restrict__ heads,
+                                                                   const uint16_t* __restrict__ lists, uint32_t* __restrict__ moved,
+                                                                   const WsHeader* __restrict__ hdr)
+{
+    using L = Lists<8>;
+    extern __shared__ __attribute__((aligned(16))) uint16_t by_position[];
+    if (!lists_exist(hdr)) return;
+    for (uint32_t i = threadIdx.x; i < (K + 7) / 8; i += kMovedThreads)   // (the buffer is a whole number of 256 bytes)
+        reinterpret_cast<uint4*>(by_position)[i] = reinterpret_cast<const uint4*>(moves)[i];
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63, waves = gridDim.x * (kMovedThreads / 64);
+    for (uint32_t c = blockIdx.x * (kMovedThreads / 64) + (threadIdx.x >> 6); c < K; c += waves) {
+        const uint32_t all1 = heads[c].n1, n1 = all1 != 0xffffffffu ? min(all1, L::kCap1) : 0u, n2 = min(heads[c].n2, L::kCap2);   // (a cell without a list: ~0)
+        const uint16_t* list = lists + size_t(c) * L::kCap;
+        auto most = [&](const uint16_t* from, uint32_t n) {
+            uint32_t m = 0;
+            for (uint32_t e0 = lane * 8; e0 < n; e0 += 512) {
+                const uint4 v = *reinterpret_cast<const uint4*>(from + e0);
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (uint32_t q = 0; q < 8; ++q) {
+                    const uint32_t pos = (w[q / 2] >> (16 * (q & 1))) & 0xffffu;
+                    if (e0 + q < n) m = max(m, uint32_t(by_position[pos]));
+                }
+            }
+            for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
+            return m;
+        };
+        const uint32_t m1 = most(list, n1), m2 = most(list + L::kCap1, n2);
+        if (lane == 0) moved[c] = m1 | (max(m1, m2) << 16);
+    }
+}
+
+// Codes that cannot change. An E-step leaves for every vector x it decided on its cell's list, with nearest centroid k, a bound on the
+// distance of all others: what else is on the list is no nearer than the second best, what is not on it lies beyond R from the cell's
+// centroid c, hence beyond R - ||x - c|| from x. Until the next E-step the centroids move; of those that can be nearest then (the cell's new
+// list) none has come nearer by more than the largest move among them. Where the bound less that move is above the new ||x - c_k||, k stays,
+// its distance is known, and the new bound is the smaller of what is left of the old one and R - ||x - c||.
+// Every bound gives way by more than its rounding (1e-5 of the distances behind it, 3e-19 for squares among the subnormal numbers), so the
+// others' distances are larger in fp32 as well: no tie, the same code.
+__device__ __forceinline__ float bound_of(float others, float R, float to_centre)
+{
+    return __builtin_fminf(others, R * 0.99999f - to_centre * 1.00001f) - 3e-19f;
+}
+
+// The vectors of an item, one lane each: which are near (returned), to the mid queue, to the far ones, or done.
+__device__ __forceinline__ bool sort_out(const NearArgs& a, uint32_t c, const CellHead& head, uint32_t first, uint32_t n, int lane,
+                                         const float (&x)[8], uint32_t hint)
+{
+    constexpr int D = 8;
+    using L = Lists<D>;
+    const bool on = uint32_t(lane) < n;
+    const uint32_t p = first + min(uint32_t(lane), n - 1);
+    float row[D], ch[D];
+    const float was = a.bounded ? from_half(a.bound[p]) : 0.0f;
+    const uint32_t moved = a.bounded ? a.moved[c] : 0u;
+    load_row<D>(a.C + size_t(c) * D, row);
+    load_row<D>(a.C + size_t(min(hint, a.K - 1)) * D, ch);
+    // lists are complete unless they ran out of room
+    const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
+    const float r1 = usable ? head.r1 : -1.0f, r2 = usable && head.n2 <= L::kCap2 ? fmaxf(head.r1, head.r2) : r1;
+    const float sq = direct_sqdist<D>(x, ch), to_hinted = __builtin_amdgcn_sqrtf(sq), to_centre = rough_distance<D>(x, row);
+    const float t = cell_bound(to_centre, to_hinted);
+    bool near = on && t <= r1, mid = on && !near && t <= r2;
+    const bool far = on && !near && !mid;
+    if (a.bounded) {
+        const float others = was - from_half(near ? moved & 0xffffu : moved >> 16) - 2e-7f * was;
+        if ((near || mid) && to_hinted * 1.00002f + 6e-19f < others) {
+            if (a.dmin != nullptr) a.dmin[p] = sq;
+            a.bound[p] = lower_half(bound_of(others, near ? r1 : r2, to_centre));
+            near = mid = false;
+        }
+    }
+    float tm = on ? t : 0.0f;
+    for (int off = 32; off > 0; off >>= 1) tm = __builtin_fmaxf(tm, __shfl_xor(tm, off, 64));
+    if (lane == 0) atomicMax(&a.heads[c].tmax, __float_as_uint(tm));
+    const unsigned long long mids = __ballot(mid);
+    if (mids != 0) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&a.heads[c].mids, uint32_t(__popcll(mids)));
+        at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
+        if (mid) a.queues[head.start + head.members - 1 - __builtin_amdgcn_mbcnt_hi(uint32_t(mids >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mids), at))] = p;
+    }
+    if (far) {
+        or_bit(a.far_bits, a.rank[p]);
+        if (a.bound != nullptr) a.bound[p] = 0;
+    }
+    if (a.changed != nullptr) {
+        if (far) a.prev_out[p] = hint;
+        or_bits(a.changed, first, __ballot(far), lane);
+    }
+    return near;
+}
+
+// Near vectors that have to be scored, to their cell's queue: 64 of them then share a gather of the list.
+__global__ __launch_bounds__(kThreads) void near_sort_out_kernel(NearArgs a)
+{
+    constexpr int D = 8;
+    const int lane = threadIdx.x & 63;
+    uint32_t c, first, n;
+    CellHead head;
+    if (!near_item(a, blockIdx.x * kWaves + (threadIdx.x >> 6), kSetVectors, kMembers, c, head, first, n)) return;
+    const uint32_t p = first + min(uint32_t(lane), n - 1), hint = a.idx[p];
+    float x[D];
+    load_row<D>(a.X + size_t(p) * D, x);
+    const bool near = sort_out(a, c, head, first, n, lane, x, hint);
+    const unsigned long long some = __ballot(near);
+    if (some == 0) return;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&a.queued_near[c], uint32_t(__popcll(some)));
+    at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
+    if (near) a.queues[head.start + __builtin_amdgcn_mbcnt_hi(uint32_t(some >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(some), at))] = p;
+}
+
+enum NearMode : int { kNear, kQueued, kMid, kHint };   // kNear: sorts its vectors out itself; kQueued: the near ones of near_sort_out_kernel; kHint: the best of the list within r1 (or what of it there is room for) for every vector of
                                               // the cell, no matter whether that is its nearest centroid
 template <int MODE>
 __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
 {
-    constexpr bool MID = MODE == kMid;
+    constexpr bool MID = MODE == kMid, QUEUED = MID || MODE == kQueued;
     constexpr int D = 8;
     using L = Lists<D>;
     const int lane = threadIdx.x, g = lane >> 4, n16 = lane & 15;
-    uint32_t c, first, n;   // MID: `first` is where the positions of the vectors are listed
+    uint32_t c, first, n;
     CellHead head;
-    if (!near_item(a, blockIdx.x, kSetVectors, MID, c, head, first, n)) return;
+    if (!near_item(a, blockIdx.x, kSetVectors, MID ? kQueuedMid : (QUEUED ? kQueuedNear : kMembers), c, head, first, n)) return;
     // lists are complete unless they ran out of room
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
     const bool whole = usable && head.n2 <= L::kCap2;
@@ -855,8 +1002,8 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     clear_scores(s);
 
     // ---- the vectors: operands, bounds and previous codes (one vector per lane)
-    const bool on = uint32_t(lane) < n;
-    auto position = [&](uint32_t v) { return MID ? a.mids[first + v] : first + v; };
+    bool on = uint32_t(lane) < n;
+    auto position = [&](uint32_t v) { return QUEUED ? a.queues[MID ? first - v : first + v] : first + v; };
     const uint32_t p = position(min(uint32_t(lane), n - 1));
     float x[D];
     load_row<D>(a.X + size_t(p) * D, x);
@@ -875,30 +1022,9 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
             low[vt * 64 + lane] = lo;
         }
     }
-    bool decided = on;
     if constexpr (MODE == kNear) {
-        float row[D], ch[D];
-        load_row<D>(a.C + size_t(c) * D, row);
-        load_row<D>(a.C + size_t(min(hint, a.K - 1)) * D, ch);
-        const float t = cell_bound<D>(x, row, ch);
-        decided = on && t <= r1;
-        const bool mid = on && !decided && t <= r2, far = on && !decided && !mid;
-        float tm = on ? t : 0.0f;
-        for (int off = 32; off > 0; off >>= 1) tm = __builtin_fmaxf(tm, __shfl_xor(tm, off, 64));
-        if (lane == 0) atomicMax(&a.heads[c].tmax, __float_as_uint(tm));
-        const unsigned long long queued = __ballot(mid);
-        if (queued != 0) {
-            uint32_t at = 0;
-            if (lane == 0) at = atomicAdd(&a.heads[c].mids, uint32_t(__popcll(queued)));
-            at = uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
-            if (mid) a.mids[head.start + __builtin_amdgcn_mbcnt_hi(uint32_t(queued >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(queued), at))] = p;
-        }
-        if (far) or_bit(a.far_bits, a.rank[p]);
-        if (a.changed != nullptr) {
-            if (far) a.prev_out[p] = hint;
-            or_bits(a.changed, first, __ballot(far), lane);
-        }
-        if (!__any(decided)) return;
+        on = sort_out(a, c, head, first, n, lane, x, hint);
+        if (!__any(on)) return;
     }
     // ---- scores: 64 list entries at a time, the operands of a group gathered while the one before it is scored, its list
     // entries one group earlier; past the end, the operand that never wins
@@ -961,16 +1087,17 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     uint32_t k = a.cperm[d0 <= d1 ? p0 : p1];
     if (d0 == d1) k = min(k, a.cperm[p1]);
     if constexpr (MODE == kHint) {
-        if (decided) a.idx[p] = k;
+        if (on) a.idx[p] = k;
         return;
     }
     float xn = 0.0f;
 #pragma unroll
     for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
-    float delta = f16_guard_band<D, 3, true, 16>(x, d, sigma, sigma_cmax) +
-                        3.814697265625e-06f * (__builtin_fabsf(best) + __builtin_fabsf(second));   // the tags: 2^-18
-    if (!f16) delta += 16.0f * sigma_cmax * (2.384185791015625e-07f * __builtin_sqrtf(xn) + 1.6e-07f);   // what x has beyond 22 bits
-    unsigned long long todo = __ballot(decided && !((second - best) > delta));
+    float slack = 3.814697265625e-06f * (__builtin_fabsf(best) + __builtin_fabsf(second));   // the tags: 2^-18
+    if (!f16) slack += 16.0f * sigma_cmax * (2.384185791015625e-07f * __builtin_sqrtf(xn) + 1.6e-07f);   // what x has beyond 22 bits
+    const float delta = f16_guard_band<D, 3, true, 16>(x, d, sigma, sigma_cmax) + slack;
+    const bool clear = (second - best) > delta;
+    unsigned long long todo = __ballot(on && !clear);
     while (todo != 0) {  // direct form over the whole list, one vector at a time
         const int src = __ffsll(static_cast<long long>(todo)) - 1;
         todo &= todo - 1;
@@ -996,14 +1123,24 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
             d = __uint_as_float(uint32_t(key >> 32));
         }
     }
-    if (decided) {
+    if (on) {
         a.idx[p] = k;
-        a.dmin[p] = d;
+        if (a.dmin != nullptr) a.dmin[p] = d;
+    }
+    if (on && a.bound != nullptr) {
+        // others: the partner of the winner's pair, and whatever scored no better than the second best pair. The band is the one of a
+        // centroid twice as far as the winner, which is as much as is made of the scores of those beyond.
+        float row[D];
+        load_row<D>(a.C + size_t(c) * D, row);
+        const float scored = (second - f16_guard_band<D, 3, true, 16>(x, 4.0f * d, sigma, sigma_cmax) - slack) / sigma + xn * 0.999999f;
+        const float sq = __builtin_fminf(__builtin_fminf(scored, 4.0f * d), __builtin_fmaxf(d0, d1));
+        const float others = clear ? __builtin_sqrtf(__builtin_fmaxf(0.0f, sq)) * 0.99999f : 0.0f;
+        a.bound[p] = lower_half(bound_of(others, MID ? r2 : r1, rough_distance<D>(x, row)));
     }
     if (a.changed != nullptr) {
-        const bool moved = decided && k != hint;
+        const bool moved = on && k != hint;
         if (moved) a.prev_out[p] = hint;
-        if constexpr (MID) {
+        if constexpr (QUEUED) {
             if (moved) or_bit(a.changed, p);
         } else {
             or_bits(a.changed, first, __ballot(moved), lane);
@@ -1280,6 +1417,13 @@ __global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const flo
     else sets(std::integral_constant<int, F::kMostVT>{});
 }
 
+// Whether the codes that cannot change are left out (d = 8): where that leaves fewer sets of 64 to a cell, which share a gather of its list
+// (where a cell has one set at most, the gather stays). Fits, ms, without / with: N = 29 M, K = 65536 (447 vectors per centroid) 109.8 / 104.8;
+// 4.2 M, K = 4096 (1024), 20 iterations 15.7 / 14.4, K = 16384 (256) 13.9 / 13.65, K = 32768 (128), 20 iterations 32.6 / 32.2; 4.9 M of 5,
+// K = 35000 (140) 18.8 / 19.1; 2.8 M of 6, K = 65500 (43) 24.8 / 25.8. At d = 4 it cost more than it saved (near_direct_kernel of the
+// 11 M fit: 40 % fewer vector instructions, 3.0 -> 3.4 ms, for the bounds and the second pass over what is left).
+bool cells_bounded(uint64_t N, uint32_t d, uint32_t K) { return d == 8 && N >= 192ull * K; }
+
 uint32_t item_of(uint32_t d) { return d == 4 ? kCellItem : kSetVectors; }
 
 template <int D>
@@ -1308,34 +1452,53 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
 }
 
 template <int D>
-void cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, hipStream_t s)
+hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s)
 {
+    // buffers of the centroids' sort, which does not run during an E-step by cells
+    float* drift = cells_bounded(N, D, K) && bounded ? reinterpret_cast<float*>(w.cperm_tmp) : nullptr;
+    uint16_t* moves = w.ckeys_tmp;
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = (K + 32 * kFarGroup - 1) / (32 * kFarGroup) * (32 * kFarGroup);
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
-                       words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr);
+                       words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr, w.csorted, w.cinv, drift);
     hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
-                       w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
+                       w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr,
+                       drift, moves);
     hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(kThreads), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
-                       w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist);
+                       w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist, w.cell_cursor);
+    if (drift != nullptr) {   // (by cell where the moves were by centroid: those are in their places now)
+        const uint32_t lds = (K + 7) / 8 * 16;
+        if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cell_moved_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 65536 * 2);
+            e != hipSuccess) return e;
+        hipLaunchKernelGGL(cell_moved_kernel, dim3(std::min((K + 15) / 16, 256u)), dim3(kMovedThreads), lds, s, moves, K, w.cell_heads, w.cell_lists,
+                           w.cperm_tmp, w.hdr);
+    }
+    return hipGetLastError();
 }
 
-NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track)
+NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded)
 {
     return NearArgs{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, N / item_of(d) + K,
-                    w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos, w.idx_sorted, w.dmin,
+                    w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos,
+                    w.cell_cursor, w.cperm_tmp, cells_bounded(N, d, K) ? reinterpret_cast<uint16_t*>(w.cell_order) /* idle between groupings */ : nullptr,
+                    cells_bounded(N, d, K) && bounded, w.idx_sorted, track ? nullptr : w.dmin /* track: an iteration's */,
                     track ? w.idx_prev : nullptr, track ? w.changed : nullptr, w.hdr};
 }
 
 template <int D>
-void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, hipStream_t s)
+void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bool track, bool bounded, hipStream_t s)
 {
-    const NearArgs a = near_args(C, N, D, K, w, track);
+    const NearArgs a = near_args(C, N, D, K, w, track, bounded);
     const dim3 grid(a.slots), wave(64);
     if constexpr (D == 4) {
         hipLaunchKernelGGL(near_direct_kernel, grid, wave, 0, s, a);
     } else {
-        hipLaunchKernelGGL(near_mfma_kernel<kNear>, grid, wave, 0, s, a);
+        if (cells_bounded(N, D, K)) {
+            hipLaunchKernelGGL(near_sort_out_kernel, dim3((a.slots + kWaves - 1) / kWaves), dim3(kThreads), 0, s, a);
+            hipLaunchKernelGGL(near_mfma_kernel<kQueued>, grid, wave, 0, s, a);
+        } else {
+            hipLaunchKernelGGL(near_mfma_kernel<kNear>, grid, wave, 0, s, a);
+        }
         hipLaunchKernelGGL(near_mfma_kernel<kMid>, grid, wave, 0, s, a);
     }
 }
@@ -1375,21 +1538,20 @@ hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32
     }
 }
 
-hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, hipStream_t s)
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s)
 {
     switch (d) {
-        case 4: cells_centroids_t<4>(C, N, K, w, radii, s); break;
-        case 8: cells_centroids_t<8>(C, N, K, w, radii, s); break;
+        case 4: return cells_centroids_t<4>(C, N, K, w, radii, bounded, s);
+        case 8: return cells_centroids_t<8>(C, N, K, w, radii, bounded, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
-hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s)
+hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded, hipStream_t s)
 {
     switch (d) {
-        case 4: cells_near_t<4>(C, N, K, w, track, s); break;
-        case 8: cells_near_t<8>(C, N, K, w, track, s); break;
+        case 4: cells_near_t<4>(C, N, K, w, track, bounded, s); break;
+        case 8: cells_near_t<8>(C, N, K, w, track, bounded, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1398,7 +1560,7 @@ hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K,
 hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
 {
     if (d != 8) return hipErrorInvalidValue;
-    const NearArgs a = near_args(C, N, d, K, w, false);
+    const NearArgs a = near_args(C, N, d, K, w, false, false);
     hipLaunchKernelGGL(near_mfma_kernel<kHint>, dim3(a.slots), dim3(64), 0, s, a);
     return hipGetLastError();
 }

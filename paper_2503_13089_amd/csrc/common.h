@@ -330,8 +330,8 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool 
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
                               bool first, hipStream_t s);
 enum Radii : int { kRadiiStay, kRadiiFollow, kRadiiJump };   // towards the lists' target lengths: not, a step, all the way (same centroids)
-hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, hipStream_t s);
-hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, hipStream_t s);
+hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s);
+hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded, hipStream_t s);
 hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
