@@ -390,7 +390,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
 // hits worked off where they were found), 0.14 ms at d = 4.
 constexpr float kListThrMax = 1.5e7f;     // what three fp16 parts against 2^8, 2^-3, 2^-14 can carry
 template <int D, bool WINDOWED>
-__global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
+__global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
                                                               uint32_t K, const char* __restrict__ operands, uint32_t ntiles,
                                                               const uint32_t* __restrict__ key_starts, CellHead* __restrict__ heads,
                                                               uint32_t N, WsHeader* hdr, uint16_t* __restrict__ lists,
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __res
         if (D == 8) queued_near[i] = 0;
     }
     if (!lists_exist(hdr)) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, n = lane & 31;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), h = lane >> 5, n = lane & 31;
     const uint32_t p0 = blockIdx.x * 32;
     const uint32_t pos = min(p0 + n, K - 1), c = cperm[pos];
     if (threadIdx.x < 32) {
@@ -482,20 +482,20 @@ __global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __res
         if (uint32_t(lane) < count) {
             const uint2 q = queue[lane];
             const uint32_t cell = q.y & 31u, first_pos = (q.y >> 6) * 32 + (q.y & 32u ? 16u : 0u);
-            uint32_t mask = q.x & 0xffffu;
-            const uint32_t inner = L::kCap2 > 0 ? (q.x >> 16) & mask : mask;
-            uint16_t* list = lists + size_t(cell_ids[cell]) * L::kCap;
-            const uint32_t n1 = __popc(inner), n2 = __popc(mask) - n1;
-            uint32_t at1 = n1 ? atomicAdd(&cnt1[cell], n1) : 0u, at2 = n2 ? atomicAdd(&cnt2[cell], n2) : 0u;
-            do {
-                const uint32_t r = uint32_t(__clz(int(mask))) - 16, bit = 0x8000u >> r;
-                mask &= ~bit;
-                const bool in = (inner & bit) != 0;
-                const uint32_t at = in ? at1 : at2;
-                if (at < (in ? L::kCap1 : L::kCap2)) list[(in ? 0u : L::kCap1) + at] = uint16_t(first_pos + r);
-                at1 += in ? 1u : 0u;
-                at2 += in ? 0u : 1u;
-            } while (mask != 0);
+            const uint32_t inner = L::kCap2 > 0 ? q.x & (q.x << 16) & 0xffff0000u : q.x << 16, outer = (q.x << 16) ^ inner;
+            const uint32_t n1 = __popc(inner), n2 = __popc(outer);
+            const uint32_t at1 = n1 ? atomicAdd(&cnt1[cell], n1) : 0u, at2 = n2 ? atomicAdd(&cnt2[cell], n2) : 0u;
+            auto put = [&](uint32_t mask, uint32_t at, uint32_t end) {   // in entries of the whole table
+                while (mask != 0) {
+                    const uint32_t r = uint32_t(__builtin_clz(mask));
+                    mask ^= 0x80000000u >> r;
+                    if (at < end) lists[at] = uint16_t(first_pos + r);
+                    ++at;
+                }
+            };
+            const uint32_t list = cell_ids[cell] * L::kCap;
+            put(inner, list + at1, list + L::kCap1);
+            if constexpr (L::kCap2 > 0) put(outer, list + L::kCap1 + at2, list + L::kCap);
         }
     };
     constexpr int U = 4;                        // tiles a wave takes at a time
@@ -509,12 +509,12 @@ __global__ __launch_bounds__(kThreads) void cell_lists_kernel(const float* __res
         uint32_t t = r0 + wave * U;
         f16x8 a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + u, t1 - 1)) * 1024 + lane * 16);
+        for (int u = 0; u < U; ++u) a[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + u, t1 - 1)) * 1024 + uint32_t(lane * 16));
         for (; t < t1; t += kStep) {
             f16x8 an[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                an[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + kStep + u, t1 - 1)) * 1024 + lane * 16);
+                an[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + kStep + u, t1 - 1)) * 1024 + uint32_t(lane * 16));
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (t + u >= t1) break;
