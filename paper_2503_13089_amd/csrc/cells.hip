@@ -11,9 +11,9 @@
 // The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, 512
 // neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
-// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.10 ms, near vectors 0.15, far ones 0.02 to collect and
-// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.9, 2.7
-// to 3.6, 0.2, 1.6 to 2.4, 0.05 (53 ms). At 2.8 M, d = 8, the lists are the longest part: 0.5, 0.42, 0.02, 0.05, 0.03.
+// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.08 ms, near vectors 0.15, far ones 0.02 to collect and
+// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.6, 2.7
+// to 3.6, 0.2, 1.6 to 2.4, 0.05 (53 ms). At 2.8 M, d = 8: 0.3, 0.33, 0.02, 0.05, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
 // against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
@@ -382,12 +382,14 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
 // One matrix instruction gives sigma (||c'||^2 - 2 c.c' - (R^2 - ||c||^2 + slack)) for 32 x 32 (centroid, cell) pairs;
 // an entry is kept where that is negative. Both sides' coordinates are fp16 (2^-11 relative each), which the slack covers: a
 // list may hold a few centroids beyond R, never fewer than all within. The signs of a lane's 16 results are shifted into
-// one word (with a second instruction for the inner radius into another), the cells' counters are in LDS. Where in a list
-// an entry lands depends on scheduling; no result does.
+// one word, at d = 8 with the upper bit of their exponents: a cell's side is scaled so that what lies within the inner radius scores -2
+// or less. The cells' counters are in LDS. Where in a list an entry lands depends on scheduling; no result does.
 // WINDOWED (d = 4): only the runs of the ordered codebook that the shells and cosines of sort.hip allow for the 32 cells;
 // at d = 8 a ball that is 1 % of the codebook touches most of them.
-// Bound: vector instructions, 50 to 80 per 1024 pairs; K = 65536: 4.3 G pairs at d = 8 in 0.54 to 0.97 ms (1.35 with the
-// hits worked off where they were found), 0.14 ms at d = 4.
+// Bound: vector instructions, 16 for a tile's bits and as many again for its hits; K = 65536: 4.3 G pairs at d = 8 in 0.3 to 0.52 ms
+// (lists of 2.8 M vectors; 0.48 to 0.76 with a second product for the inner radius and every product copied out of accumulation
+// registers, which the launch bound prevents, 0.37 to 0.57 with the second product alone; 29 M vectors 0.6 to 1.4, its first lists are
+// longer), 0.08 to 0.15 ms at d = 4 (0.095 to 0.21).
 constexpr float kListThrMax = 1.5e7f;     // what three fp16 parts against 2^8, 2^-3, 2^-14 can carry
 template <int D, bool WINDOWED>
 __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
                                                               uint32_t* __restrict__ hist, uint32_t* __restrict__ queued_near)
 {
     using L = Lists<D>;
-    __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32];
+    __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32], all_inner[32];
     __shared__ uint2 queues[kWaves][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
     for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < 65536; i += gridDim.x * kThreads) {
         hist[i] = 0;  // for the next E-step
@@ -412,7 +414,6 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
         cnt2[threadIdx.x] = 0;
         cell_ids[threadIdx.x] = c;
     }
-    __syncthreads();
     float x[D];
     load_row<D>(csorted + size_t(pos) * D, x);
     const CellHead head = heads[c];
@@ -423,23 +424,37 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
     const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
     // slack: 2^-9 ||c|| ||c'|| = 1.95e-3 for the rounded operands; everything else (accumulation, the split of norm and
     // threshold, fp16 subnormals) is far below the difference to 2.2e-3 and the constant term
-    auto threshold = [&](float R) { return sigma * (R * R * 1.0001f - xn + 2.2e-3f * norm * (norm + R)) + 0.05f; };
+    auto reach = [&](float R) { return sigma * (R * R * 1.0001f - xn + 2.2e-3f * norm * (norm + R)); };
     float r2 = L::kCap2 > 0 ? head.r2 : head.r1;
-    if (threshold(r2) > kListThrMax) r2 = head.r1;
-    const bool carried = threshold(head.r1) <= kListThrMax;  // else the cell goes without a list
+    if (reach(r2) + 0.05f > kListThrMax) r2 = head.r1;
+    // The cell's side times f: what lies within r1 then scores -2 or less, and sign and upper exponent bit say both. f has 11 bits, so that
+    // its products with the multipliers are exact (where 2^-3 f and 2^-14 f are subnormal numbers, what they lose is below 2^-18 of the norm),
+    // and is at least 2 / gap after its rounding. What f < 1 does not scale is the error of a cell's operand among the
+    // subnormal numbers, at most 2^-25 against every component of the other side.
+    _Float16 f = _Float16(1.0f);
+    bool apart = false;   // else everything within r2 counts as within r1
+    if constexpr (L::kCap2 > 0) {
+        const float gap = sigma * ((r2 * r2 - head.r1 * head.r1) * 1.0001f + 2.2e-3f * norm * (r2 - head.r1)), want = 2.004f / gap;
+        apart = gap > 0.0f && want > 6.2e-5f && want < 255.0f && want * 2.0f * norm < 60000.0f &&
+                want * __builtin_fabsf(reach(r2)) < 0.99f * kListThrMax;
+        if (apart) f = _Float16(want);
+    }
+    const float scale = float(f), thr = L::kCap2 > 0 ? scale * (reach(r2) + 0.05f) + (3e-7f * sigma * __uint_as_float(hdr->cmax_bits) + 1e-3f) : reach(r2) + 0.05f;
+    const bool carried = thr <= kListThrMax;  // else the cell goes without a list
     const bool live = p0 + n < K && head.members > 0 && head.r1 > 0.0f && carried;
-    const float thr1 = threshold(head.r1), thr = threshold(r2);
-    auto operand = [&](float threshold) {
+    if (threadIdx.x < 32) all_inner[threadIdx.x] = apart ? 0u : 0xffffffffu;
+    f16x8 b;
+    {
         _Float16 tp[3];
-        split_norm(live ? -threshold : kListThrMax, tp);
+        split_norm(live ? -thr : kListThrMax, tp);
         const _Float16 z = _Float16(0.0f);
         f16x8 lo;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) lo[j] = j < D ? _Float16(-2.0f * x[j % D]) : z;
-        const f16x8 hi = f16x8{_Float16(256.0f), _Float16(0.125f), _Float16(6.103515625e-05f), tp[0], tp[1], tp[2], z, z};
-        return h ? hi : lo;
-    };
-    const f16x8 b = operand(thr), b1 = operand(thr1);
+        for (int j = 0; j < 8; ++j) lo[j] = j < D ? _Float16(-2.0f * scale * x[j % D]) : z;
+        const f16x8 hi = f16x8{_Float16(256.0f * scale), _Float16(0.125f * scale), _Float16(6.103515625e-05f * scale), tp[0], tp[1], tp[2], z, z};
+        b = h ? hi : lo;
+    }
+    __syncthreads();
     f32x16 zero;
 #pragma unroll
     for (int q = 0; q < 16; ++q) zero[q] = 0.0f;
@@ -482,14 +497,15 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
         if (uint32_t(lane) < count) {
             const uint2 q = queue[lane];
             const uint32_t cell = q.y & 31u, first_pos = (q.y >> 6) * 32 + (q.y & 32u ? 16u : 0u);
-            const uint32_t inner = L::kCap2 > 0 ? q.x & (q.x << 16) & 0xffff0000u : q.x << 16, outer = (q.x << 16) ^ inner;
+            const uint32_t all = L::kCap2 > 0 ? q.x & 0xaaaaaaaau : q.x << 16;
+            const uint32_t inner = L::kCap2 > 0 ? all & ((q.x << 1) | all_inner[cell]) : all, outer = all ^ inner;
             const uint32_t n1 = __popc(inner), n2 = __popc(outer);
             const uint32_t at1 = n1 ? atomicAdd(&cnt1[cell], n1) : 0u, at2 = n2 ? atomicAdd(&cnt2[cell], n2) : 0u;
             auto put = [&](uint32_t mask, uint32_t at, uint32_t end) {   // in entries of the whole table
                 while (mask != 0) {
-                    const uint32_t r = uint32_t(__builtin_clz(mask));
-                    mask ^= 0x80000000u >> r;
-                    if (at < end) lists[at] = uint16_t(first_pos + r);
+                    const uint32_t bit = uint32_t(__builtin_clz(mask));
+                    mask ^= 0x80000000u >> bit;
+                    if (at < end) lists[at] = uint16_t(first_pos + bit / (L::kCap2 > 0 ? 2 : 1));
                     ++at;
                 }
             };
@@ -525,17 +541,11 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
                     for (int q = 0; q < 8; ++q) m = __builtin_fminf(__builtin_fminf(m, acc[2 * q]), acc[2 * q + 1]);
                     if (!__any(m < 0.0f)) continue;
                 }
-                uint32_t mask = 0;   // bit 15 - q: row q is within the radius
+                constexpr int kBits = L::kCap2 > 0 ? 2 : 1;   // of a row: within the (outer) radius, within r1
+                uint32_t bits = 0;   // row 0 uppermost
 #pragma unroll
-                for (int q = 0; q < 16; ++q) mask = __builtin_amdgcn_alignbit(mask, __float_as_uint(acc[q]), 31);
-                uint32_t bits = mask;
-                if constexpr (L::kCap2 > 0) {   // upper half: within r1
-                    const f32x16 acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b1, zero, 0, 0, 0);
-                    uint32_t inner = 0;
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) inner = __builtin_amdgcn_alignbit(inner, __float_as_uint(acc1[q]), 31);
-                    bits = mask | (inner << 16);
-                }
+                for (int q = 0; q < 16; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(acc[q]), 32 - kBits);
+                const uint32_t mask = kBits == 2 ? bits & 0xaaaaaaaau : bits;
                 const unsigned long long hits = __ballot(mask != 0);
                 if (mask != 0)
                     queue[__builtin_amdgcn_mbcnt_hi(uint32_t(hits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(hits), queued))] =
