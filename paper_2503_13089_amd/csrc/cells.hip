@@ -248,8 +248,14 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
         heads[t].tmax = 0;
         heads[t].mids = 0;
     }
+    // one look at the running maximum per workgroup that has centroids: one per wave of the whole grid, all at one address, took 16 of 27 us
+    __shared__ uint32_t wave_most[kWaves];
     for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
-    if ((threadIdx.x & 63) == 0 && m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
+    if ((threadIdx.x & 63) == 0) wave_most[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x != 0 || t >= K) return;
+    for (int v = 1; v < kWaves; ++v) m = max(m, wave_most[v]);
+    if (m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
 }
 
 // starts[v] = centroids with a key below v, also the next free position of each key (cursor). One workgroup per

@@ -153,24 +153,42 @@ struct Cut {
     int slices;
 };
 
-// Workgroups of at least 64 vectors, at most kMaxBlocks; with fewer vectors per workgroup than threads the waves split
+// Workgroups of at least 64 vectors, at most `most`; with fewer vectors per workgroup than threads the waves split
 // the codebook (8, 4 or 2 ways) instead of idling.
-Cut cut_of(uint32_t N)
+Cut cut_into(uint32_t N, uint32_t most)
 {
     Cut c;
     const uint32_t groups = (N + 63) / 64;
-    const uint32_t per = (groups + kMaxBlocks - 1) / kMaxBlocks;   // groups of 64 vectors per workgroup
+    const uint32_t per = (groups + most - 1) / most;   // groups of 64 vectors per workgroup
     c.per_block = per * 64;
     c.blocks = (groups + per - 1) / per;
     c.slices = per >= 8 ? 1 : (per >= 4 ? 2 : (per >= 2 ? 4 : 8));
     return c;
 }
 
+// us of an iteration: distances on the vector ALUs (2.7 clocks per instruction with two workgroups on a compute unit, 3.5 with one), and
+// the workgroups' sums out and in again at 3 TB/s.
+double cost_of(const Cut& c, uint32_t d, uint32_t K)
+{
+    const uint32_t at_once = 8 / uint32_t(c.slices), groups = c.per_block / 64;   // groups of 64 vectors
+    const double instructions = double(c.blocks) * 8 / 1024 * ((groups + at_once - 1) / at_once) * ((K + c.slices - 1) / c.slices) * (2 * d + 4);
+    return instructions * (c.blocks <= 256 ? 3.5 : 2.7) / 2200 + double(c.blocks) * 2 * double(partial_bytes(d, K)) / 3e6;
+}
+
+// One or two workgroups per compute unit: two hide each other's latencies, one leaves half as many partial sums to add. Fits of 10
+// iterations, us, two / one: N = 65536, K = 256, d = 4 168 / 153; N = 32768, K = 300, d = 16 334 / 290; N = 512000, K = 100, d = 4 301 / 333;
+// N = 76800, K = 1000, d = 4 520 / 566.
+Cut cut_of(uint32_t N, uint32_t d, uint32_t K)
+{
+    const Cut two = cut_into(N, kMaxBlocks), one = cut_into(N, kMaxBlocks / 2);
+    return cost_of(one, d, K) < cost_of(two, d, K) ? one : two;
+}
+
 template <int D, bool SUMS>
 hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K, uint32_t* idx, float* dmin, const Workspace& w,
                          hipStream_t s)
 {
-    const Cut c = cut_of(N);
+    const Cut c = SUMS ? cut_of(N, D, K) : cut_into(N, kMaxBlocks);
     const uint32_t lds = uint32_t(SUMS ? lds_bytes(D, K) : size_t(K) * D * 4), stride = uint32_t(partial_bytes(D, K));
 #define CC_SMALL(S)                                                                                                       \
     do {                                                                                                                  \
@@ -198,7 +216,7 @@ hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K,
 {
     if (hipError_t e = launch_iter_t<D, true>(X, N, C, K, idx, dmin, w, s); e != hipSuccess) return e;
     hipLaunchKernelGGL(small_means_kernel<D>, dim3((K * D + 15) / 16), dim3(kFinThreads), 0, s, w.small_partials,
-                       uint32_t(partial_bytes(D, K)), cut_of(N).blocks, C, counts, K, N, w.hdr);
+                       uint32_t(partial_bytes(D, K)), cut_of(N, D, K).blocks, C, counts, K, N, w.hdr);
     return hipGetLastError();
 }
 
@@ -219,7 +237,7 @@ bool small_problem(uint64_t N, uint32_t d, uint32_t K)
 
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K)
 {
-    return small_problem(N, d, K) ? size_t(cut_of(uint32_t(N)).blocks) * partial_bytes(d, K) : 0;
+    return small_problem(N, d, K) ? size_t(cut_into(uint32_t(N), kMaxBlocks).blocks) * partial_bytes(d, K) : 0;
 }
 
 hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx, float* dmin,
