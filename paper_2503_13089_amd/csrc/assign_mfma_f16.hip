@@ -212,59 +212,73 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_f16_kernel(
             float m[VT];
 #pragma unroll
             for (int vt = 0; vt < VT; ++vt) m[vt] = INFINITY;
-            auto operands = [&](int g, f16x8 (&a)[KM], f32x16& cn) {
-                const char* T = L + (tt + g) * S::kTileBytes;
+            if constexpr (S::kNormInK) {
+                static_assert(KM == 1, "d = 4");
+                f32x16 zero;
 #pragma unroll
-                for (int mi = 0; mi < KM; ++mi) a[mi] = *reinterpret_cast<const f16x8*>(T + (lane * KM + mi) * 16);
-                if constexpr (S::kNormInK) {
+                for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) cn[r] = 0.0f;
-                } else {
+                for (int g = 0; g < GT; ++g) {
+                    if (WINDOWED && (tt + g < g_lo || tt + g >= g_hi)) continue;  // wave-uniform: tile outside the run
+                    const f16x8 a = *reinterpret_cast<const f16x8*>(L + (tt + g) * S::kTileBytes + lane * 16);
+#pragma unroll
+                    for (int vt = 0; vt < VT; ++vt) {
+                        const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[vt][0], zero, 0, 0, 0);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) m[vt] = __builtin_fminf(__builtin_fminf(m[vt], acc[2 * q]), acc[2 * q + 1]);
+                    }
+                }
+            } else {
+                // Inside a run the minima of one product are taken while the next one runs: fits of 16 numbers, 5 iterations of 2.8 M vectors,
+                // K = 65536, 62.0 to 63.4 -> 59.7 to 61.2 ms (left to the compiler's order 70), layer_compress of 2168 x 549, g = 7, K = 42818 9.0 -> 7.8.
+                // At d = 4, two tiles to a group, that is 2 % slower.
+                auto operands = [&](int g, f16x8 (&a)[KM], f32x16& cn) {
+                    const char* T = L + (tt + g) * S::kTileBytes;
+#pragma unroll
+                    for (int mi = 0; mi < KM; ++mi) a[mi] = *reinterpret_cast<const f16x8*>(T + (lane * KM + mi) * 16);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const float4 t = *reinterpret_cast<const float4*>(T + 64 * KM * 16 + (16 * h + 4 * q) * 4);
                         cn[4 * q + 0] = t.x; cn[4 * q + 1] = t.y; cn[4 * q + 2] = t.z; cn[4 * q + 3] = t.w;
                     }
-                }
-            };
-            auto product = [&](const f16x8 (&a)[KM], const f32x16& cn, int vt) {
-                f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[vt][0], cn, 0, 0, 0);
+                };
+                auto product = [&](const f16x8 (&a)[KM], const f32x16& cn, int vt) {
+                    f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[vt][0], cn, 0, 0, 0);
 #pragma unroll
-                for (int mi = 1; mi < KM; ++mi) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[mi], b[vt][mi], acc, 0, 0, 0);
-                return acc;
-            };
-            auto minimum = [&](const f32x16& acc, int vt) {
+                    for (int mi = 1; mi < KM; ++mi) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[mi], b[vt][mi], acc, 0, 0, 0);
+                    return acc;
+                };
+                auto minimum = [&](const f32x16& acc, int vt) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q) m[vt] = __builtin_fminf(__builtin_fminf(m[vt], acc[2 * q]), acc[2 * q + 1]);
-            };
-            if (D >= 8 && (!WINDOWED || (tt >= g_lo && tt + GT <= g_hi))) {
-                // The minima of one product are taken while the next one runs (16 numbers: 5 iterations of 2.8 M vectors, K = 65536,
-                // 62.0 -> 59.7 ms; left to the compiler's order 70). At d = 4, two tiles to a group, that is 2 % slower.
-                f16x8 a[GT][KM];
-                f32x16 cn[GT], acc[2];
+                    for (int q = 0; q < 8; ++q) m[vt] = __builtin_fminf(__builtin_fminf(m[vt], acc[2 * q]), acc[2 * q + 1]);
+                };
+                if (!WINDOWED || (tt >= g_lo && tt + GT <= g_hi)) {
+                    f16x8 a[GT][KM];
+                    f32x16 cn[GT], acc[2];
 #pragma unroll
-                for (int g = 0; g < GT; ++g) operands(g, a[g], cn[g]);
-                acc[0] = product(a[0], cn[0], 0);
+                    for (int g = 0; g < GT; ++g) operands(g, a[g], cn[g]);
+                    acc[0] = product(a[0], cn[0], 0);
 #pragma unroll
-                for (int i = 0; i < GT * VT; ++i) {
-                    if (i + 1 < GT * VT) acc[(i + 1) & 1] = product(a[(i + 1) / VT], cn[(i + 1) / VT], (i + 1) % VT);
-                    minimum(acc[i & 1], i % VT);
-                }
-                __builtin_amdgcn_sched_group_barrier(8, KM, 0);
-#pragma unroll
-                for (int i = 0; i < GT * VT; ++i) {   // a product, the eight instructions of the minimum before it, the next product ...
+                    for (int i = 0; i < GT * VT; ++i) {
+                        if (i + 1 < GT * VT) acc[(i + 1) & 1] = product(a[(i + 1) / VT], cn[(i + 1) / VT], (i + 1) % VT);
+                        minimum(acc[i & 1], i % VT);
+                    }
                     __builtin_amdgcn_sched_group_barrier(8, KM, 0);
-                    __builtin_amdgcn_sched_group_barrier(2, 8, 0);
-                }
-            } else {
 #pragma unroll
-                for (int g = 0; g < GT; ++g) {
-                    if (WINDOWED && (tt + g < g_lo || tt + g >= g_hi)) continue;  // wave-uniform: tile outside the run
-                    f16x8 a[KM];
-                    f32x16 cn;
-                    operands(g, a, cn);
+                    for (int i = 0; i < GT * VT; ++i) {   // a product, the eight instructions of the minimum before it, the next product ...
+                        __builtin_amdgcn_sched_group_barrier(8, KM, 0);
+                        __builtin_amdgcn_sched_group_barrier(2, 8, 0);
+                    }
+                } else {
 #pragma unroll
-                    for (int vt = 0; vt < VT; ++vt) minimum(product(a, cn, vt), vt);
+                    for (int g = 0; g < GT; ++g) {
+                        if (WINDOWED && (tt + g < g_lo || tt + g >= g_hi)) continue;  // wave-uniform: tile outside the run
+                        f16x8 a[KM];
+                        f32x16 cn;
+                        operands(g, a, cn);
+#pragma unroll
+                        for (int vt = 0; vt < VT; ++vt) minimum(product(a, cn, vt), vt);
+                    }
                 }
             }
             const uint32_t gid = (s * ST + tt) / GT;
