@@ -1234,8 +1234,9 @@ __global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* _
 // window's tiles and load operands straight from the packed codebook. The kernel of assign_mfma_f16.hip gives 512
 // vectors to 4 waves and shares every tile through LDS: better with many vectors, but the far ones are outliers, few, with
 // windows that span much of the codebook, and left most of the chip without work.
-// Bound: matrix cores and vector ALUs together, which hardly overlap: 32 and 46 (8 of the 11.5 instructions take the minimum of 16
-// scores) of 82 cycles per 1024 pairs by the counters. Operands are loaded a group ahead across the ends of runs, and the norms of d = 8
+// Bound: instructions. By the counters (d = 8, 29 M) 82 clocks per 1024 pairs at 1.9 GHz: 32 of the matrix cores, 11.2 vector instructions,
+// 8 of which take the minimum of 16 scores; 4 or 16 waves, 128 or 256 vectors and the order of instructions changed that by 10 %. Operands
+// are loaded a group ahead across the ends of runs, and the norms of d = 8
 // pass through LDS, loaded by one lane each: 64 lanes that fetch 64 bytes each when their product needs them waited for L2 at every tile
 // (96 cycles). Kernel time of a fit: 29 M vectors of 8 (1.0 to 2 M of them far, 10 iterations) 38.0 -> 27.3 ms, 11 M of 4 1.74 -> 1.28,
 // 2.8 M of 6 (4 to 11 thousand far) 1.78 -> 1.02.
