@@ -15,7 +15,7 @@
 // multiply-adds) and now. K = 65536, 16 bits: 4096 x 4096, g = 4, M = 1 22.6 / 13.3, M = 16 24.2 / 13.9; 4096 x 11008, M = 1 39.1 / 22.5,
 // M = 16 59.1 / 24.2, M = 64 69.8 / 37.8, M = 256 116 / 93; 4096 x 10997, g = 6, M = 23 49.1 / 27.2; 8192 x 28672, M = 1 144 / 69; g = 9,
 // 4096 x 11008, M = 4 52.3 / 25.2. K = 4096, g = 8: 4096 x 4096, M = 16 15.8 / 13.2, 2048 x 2048, M = 64 14.6 / 12.6. 4 bits: 8192 x 8192, g = 4,
-// M = 4 42.7 / 17.6, M = 16 113 / 19.3; 4096 x 11008, g = 6, M = 9 210 / 25.6.
+// M = 4 42.7 / 16.3, M = 16 113 / 18.2; 4096 x 11008, g = 6, M = 9 210 / 25.6.
 // A call of 4096 x 4096, M = 1: 2.8 us for the copies, then 2.5 us until the codes are requested (their loads, 8 of 2 bytes a step,
 // take the address unit 10 clocks each), 2 for the column, 3 for the lookups, 1 for the sums.
 #include <algorithm>
@@ -51,7 +51,7 @@ __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c)
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// J elements of BITS bits: an entry. Integers carry their offset 2^(BITS-1).
+// J elements of BITS bits: an entry. Integers of 4 bits are held as q + 8.
 template <int BITS, int J>
 constexpr int kEntryBytes = BITS * J / 8;
 
@@ -72,7 +72,7 @@ __device__ __forceinline__ uint64_t make_entry(const uint8_t* __restrict__ book,
         const uint32_t at = uint32_t(bit / 8), shift = uint32_t(bit % 8);   // shift: 0 or 4
 #pragma unroll
         for (uint32_t b = 0; b <= kEntryBytes<BITS, J>; ++b) e |= uint64_t(book[min(at + b, book_bytes - 1)]) << (8 * b);   // past the end: not used
-        e = (e >> shift) ^ (BITS == 8 ? 0x8080808080808080ull : 0x8888888888888888ull);
+        e = (e >> shift) ^ (BITS == 8 ? 0ull : 0x8888888888888888ull);
     }
     return e;
 }
@@ -137,13 +137,11 @@ struct ColumnArgs {
     uint32_t slices, slice_rows; // of the in-features, in multiples of kStep
 };
 
-// Integers of 4 bits for up to 16 rows of x keep their offset of 8 in the operands (one instruction in three less); 8 times the
-// sum of x is taken off at the end.
-template <int BITS, int MT>
-constexpr bool kOffset = BITS == 4 && MT == 1;
-
-// The operand of element j from the words of 8 entries (two entries a word where they are of 2 bytes)
-template <int DT, int BITS, int J, int RW, bool OFFSET>
+// The operand of element j from the words of 8 entries (two entries a word where they are of 2 bytes). Integers become operands with
+// their sign: with an offset left in and taken off the finished sum, the fp32 sum would round at the size of the offset's
+// share, several times its own. Signed bytes convert in one instruction, as unsigned ones do; nibbles become signed bytes four at a
+// time (8192 x 8192, g = 4, M = 4: 16.3 us, with an offset of 8 for up to 16 rows 17.5).
+template <int DT, int BITS, int J, int RW>
 __device__ __forceinline__ u32x4 operand(const uint32_t (&w)[RW], int j)
 {
     u32x4 b;
@@ -159,9 +157,12 @@ __device__ __forceinline__ u32x4 operand(const uint32_t (&w)[RW], int j)
             for (int e = 0; e < 2; ++e) {
                 const uint32_t v = kEntryBytes<BITS, J> == 2 ? w[i] : w[2 * i + e];
                 const int first = kEntryBytes<BITS, J> == 2 ? 2 * e : 0;   // byte
-                if constexpr (BITS == 8) f[e] = float((v >> (8 * (first + j))) & 0xffu);
-                else f[e] = float((((j % 2 ? v >> 4 : v) & 0x0f0f0f0fu) >> (8 * (first + j / 2))) & 0xffu);
-                if constexpr (!OFFSET) f[e] -= float(1 << (BITS - 1));
+                if constexpr (BITS == 8) {
+                    f[e] = float(int8_t(v >> (8 * (first + j))));
+                } else {   // 0 .. 15 + 0x78 carries into no other byte
+                    const uint32_t q = (((j % 2 ? v >> 4 : v) & 0x0f0f0f0fu) + 0x78787878u) ^ 0x80808080u;
+                    f[e] = float(int8_t(q >> (8 * (first + j / 2))));
+                }
             }
             if constexpr (DT == 1) b[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));   // exact, as
             else b[i] = __builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u);         // is this
@@ -197,9 +198,6 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int j = 0; j < J; ++j) acc[mt][c][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    f32x4 x_sum = {0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr uint32_t kOne = DT == 1 ? 0x3c003c00u : 0x3f803f80u;
 
     const uint32_t stride = KW * kStep, k_first = k_begin + ks * kStep;
     const uint32_t steps = ks < KW && k_first < k_end ? (k_end - k_first + stride - 1) / stride : 0u;   // of this wave
@@ -237,7 +235,7 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
     // ---- the columns into LDS. Every workgroup starts at another place, so that they do not all ask the same cache channels
     if (p.laid != nullptr || (p.sets == 1 && uint32_t(E) * 8 == p.g * BITS)) {
         const uint8_t* src = p.laid != nullptr ? p.laid + size_t(set) * p.laid_stride : p.book;
-        const uint32_t offset = p.laid != nullptr || BITS == 16 ? 0u : (BITS == 8 ? 0x80808080u : 0x88888888u);
+        const uint32_t offset = p.laid != nullptr || BITS != 4 ? 0u : 0x88888888u;   // to q + 8
         const uint32_t bytes = p.K * E, pieces = bytes / 16, turn = pieces > 0 ? (blockIdx.x / 8 * 331u + blockIdx.x) % pieces : 0u;
         constexpr int U = 8;
         for (uint32_t i0 = threadIdx.x; i0 < pieces; i0 += U * kThreads) {
@@ -306,12 +304,11 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
                         for (int r = 0; r < RW; ++r) w[v][r] = dead ? 0u : w[v][r];
                 }
             }
-            if constexpr (kOffset<BITS, MT>) x_sum = mma<DT>(a[0], u32x4{kOne, kOne, kOne, kOne}, x_sum);
 #pragma unroll
             for (int v = 0; v < NC; ++v)
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
-                    const u32x4 b = operand<DT, BITS, J, RW, kOffset<BITS, MT>>(w[v], j);
+                    const u32x4 b = operand<DT, BITS, J, RW>(w[v], j);
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) acc[mt][v][j] = mma<DT>(a[mt], b, acc[mt][v][j]);
                 }
@@ -323,12 +320,6 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
         }
         step(at, 0, std::false_type{});
         if (at + 1 < steps) step(at + 1, 1, std::false_type{});
-        if constexpr (kOffset<BITS, MT>) {
-#pragma unroll
-            for (int v = 0; v < NC; ++v)
-#pragma unroll
-                for (int j = 0; j < J; ++j) acc[0][v][j] -= 8.0f * x_sum;
-        }
     }
 
     // ---- the waves of a column group are added and stored, as many rows at a time as there is room for

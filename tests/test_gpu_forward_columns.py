@@ -21,13 +21,23 @@ def _inputs(M, i, o, g, K, dt):
     return gen, x, codes, bias
 
 
+def _integers(n, bits, gen):
+    return torch.randint(-(1 << (bits - 1)), 1 << (bits - 1), (n,), device="cuda", generator=gen, dtype=torch.int32)
+
+
+def _stored(q, bits):
+    """The codebook of these integers as it is stored."""
+    if bits == 8:
+        return q.to(torch.int8).view(torch.uint8)
+    even = torch.nn.functional.pad(q & 15, (0, q.numel() % 2))
+    return (even[0::2] | (even[1::2] << 4)).to(torch.uint8)
+
+
 def _check(call, x, weight, scale, bias, dt, workspaces):
-    """y against x . weight * scale + bias: half a unit of the format, and the accumulation of in_features terms in fp32 (twice
-    that many where 4-bit integers carry an offset of 8: |q + 8| <= |q| + 8, |8 sum x| on top)."""
+    """y against x . weight * scale + bias: half a unit of the format, and the accumulation of in_features terms in fp32."""
     M, o = x.shape[0], bias.shape[0]
-    terms = weight.abs() + (16.0 if scale is not None else 0.0)
     s = scale if scale is not None else 1.0
-    want, size = (x.double() @ weight) * s + bias.double(), (x.double().abs() @ terms) * s
+    want, size = (x.double() @ weight) * s + bias.double(), (x.double().abs() @ weight.abs()) * s
     tol = DTYPES[dt][1] * want.abs() + x.shape[1] * 2.0 ** -24 * size + 2.0 ** -24
     first = None
     for nbytes in workspaces:
@@ -64,12 +74,8 @@ def test_forward_by_columns_with_the_quantised_codebook(M, i, o, g, K, dt, bits)
     import paper_2503_13089_amd as cc
 
     gen, x, codes, bias = _inputs(M, i, o, g, K, dt)
-    q = torch.randint(-(1 << (bits - 1)), 1 << (bits - 1), (K * g,), device="cuda", generator=gen, dtype=torch.int32)
-    if bits == 8:
-        qbook = q.to(torch.int8).view(torch.uint8)
-    else:
-        even = torch.nn.functional.pad(q & 15, (0, K * g % 2))
-        qbook = (even[0::2] | (even[1::2] << 4)).to(torch.uint8)
+    q = _integers(K * g, bits, gen)
+    qbook = _stored(q, bits)
     weight = q.double().reshape(K, g)[codes].reshape(i, -1)[:, :o].contiguous()
     scale = torch.full((1,), 0.0078125, device="cuda")
     full, least = cc.layer_forward_q_workspace_bytes(M, i, o), 64 * M * o * 4
@@ -79,19 +85,52 @@ def test_forward_by_columns_with_the_quantised_codebook(M, i, o, g, K, dt, bits)
            (full, min(full, least)))
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("dt", list(DTYPES))
+@pytest.mark.parametrize("M,g,K", [(1, 4, 65536), (16, 5, 65536), (3, 6, 4096), (16, 8, 20480), (2, 8, 65536), (17, 9, 65536)])
+def test_a_weight_of_zero_rounds_nothing(M, g, K, dt, bits):
+    """Large inputs that meet integers of zero: their products are zero, so that the bound of the small terms' sum holds
+    (2e-4 here; half a unit of fp32 at 8 times a large input would be 1.6e-2)."""
+    import paper_2503_13089_amd as cc
+
+    i, o = 264, 515
+    gen, x, codes, bias = _inputs(M, i, o, g, K, dt)
+    x, bias = x / 64, torch.zeros_like(bias)
+    x[:, 5::32] = 32768.0 + 32.0 * torch.arange(M, device="cuda", dtype=torch.float32)[:, None]
+    q = _integers(K * g, bits, gen).reshape(K, g)
+    q[K // 2] = 0
+    codes = codes.reshape(i, -1)
+    codes[5::32] = K // 2
+    codes = codes.reshape(-1)
+    weight = q.double()[codes].reshape(i, -1)[:, :o].contiguous()
+    qbook, scale = _stored(q.reshape(-1), bits), torch.ones(1, device="cuda")
+    codes16 = codes.to(torch.int32).to(torch.int16).view(torch.uint16)
+    _check(lambda y, ws: cc.layer_forward_q(x, qbook, bits, scale, K, g, codes16, o, bias, y, ws), x, weight, 1.0, bias, dt,
+           (cc.layer_forward_q_workspace_bytes(M, i, o),))
+
+
+@pytest.mark.parametrize("bits", [16, 8, 4])
 @pytest.mark.parametrize("M", [1, 3, 40])
-def test_infinite_inputs_reach_their_own_outputs_only(M):
+def test_infinite_inputs_reach_their_own_outputs_only(M, bits):
     import paper_2503_13089_amd as cc
 
     i, o, g, K = 264, 515, 6, 4096
     gen, x, codes, bias = _inputs(M, i, o, g, K, "bf16")
-    book = (torch.randn(K, g, device="cuda", generator=gen) * 0.05).bfloat16()
-    x[M - 1, i - 3], book[7, 2] = float("inf"), float("inf")
+    x[M - 1, i - 3] = float("inf")
+    codes16 = codes.to(torch.int32).to(torch.int16).view(torch.uint16)
+    y = torch.empty(M, o, dtype=torch.bfloat16, device="cuda")
+    if bits == 16:
+        book = (torch.randn(K, g, device="cuda", generator=gen) * 0.05).bfloat16()
+        book[7, 2] = float("inf")
+        ws = torch.empty(cc.layer_forward_workspace_bytes(M, i, o), dtype=torch.uint8, device="cuda")
+        cc.layer_forward(x, book, codes16, o, bias, y, ws)
+    else:
+        book = _integers(K * g, bits, gen)
+        ws = torch.empty(cc.layer_forward_q_workspace_bytes(M, i, o), dtype=torch.uint8, device="cuda")
+        cc.layer_forward_q(x, _stored(book, bits), bits, torch.ones(1, device="cuda"), K, g, codes16, o, bias, y, ws)
+        book = book.reshape(K, g)
     weight = book.double()[codes].reshape(i, -1)[:, :o].contiguous()
     want = (x.double().cpu() @ weight.cpu() + bias.double().cpu()).numpy()
-    y = torch.empty(M, o, dtype=torch.bfloat16, device="cuda")
-    ws = torch.empty(cc.layer_forward_workspace_bytes(M, i, o), dtype=torch.uint8, device="cuda")
-    cc.layer_forward(x, book, codes.to(torch.int32).to(torch.int16).view(torch.uint16), o, bias, y, ws)
     got = y.double().cpu().numpy()
     odd = ~np.isfinite(want)
     assert odd.any() and (M == 1 or not odd.all())
