@@ -40,7 +40,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32_2 __attribute__((aligned(2)));
-typedef uint32_t u32_1 __attribute__((aligned(1)));
+typedef uint64_t u64_2 __attribute__((aligned(2)));
+typedef uint64_t u64_1 __attribute__((aligned(1)));
 
 template <int DT>
 __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c)
@@ -55,23 +56,36 @@ __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c)
 template <int BITS, int J>
 constexpr int kEntryBytes = BITS * J / 8;
 
-// The entry of row k that begins with element j0; elements from g on are zero (16 bits) or anything.
+// The entry of row k that begins with element j0; elements from g on are zero (16 bits) or anything. One load each, of bytes of
+// the codebook only: loads of 2 bytes 16 apart take 24 clocks a wave, whole rows of 16 bytes 16.
 template <int BITS, int J>
 __device__ __forceinline__ uint64_t make_entry(const uint8_t* __restrict__ book, uint32_t book_bytes, uint32_t g, uint32_t k, uint32_t j0)
 {
     uint64_t e = 0;
-    if constexpr (BITS == 16) {
-        const uint16_t* row = reinterpret_cast<const uint16_t*>(book) + size_t(k) * g + j0;
-#pragma unroll
-        for (uint32_t j = 0; j < J; ++j) {   // loads without a branch: all of them in flight
-            const uint64_t v = row[min(j, g - 1 - j0)];
-            e |= (j0 + j < g ? v : 0ull) << (16 * j);
+    if constexpr (BITS == 16 && J == 1) {
+        if (g == 8) {   // (j0 is the same for every lane)
+            const u32x4 row = reinterpret_cast<const u32x4*>(book)[k];
+            const uint32_t w = j0 < 4 ? (j0 < 2 ? row[0] : row[1]) : (j0 < 6 ? row[2] : row[3]);
+            e = uint16_t(w >> (16 * (j0 % 2)));
+        } else {
+            e = reinterpret_cast<const uint16_t*>(book)[size_t(k) * g + j0];
         }
+    } else if constexpr (BITS == 16) {
+        const uint32_t j1 = min(j0, g - J);   // the row's last J elements, moved down: J <= 4 <= g
+        const uint16_t* from = reinterpret_cast<const uint16_t*>(book) + size_t(k) * g + j1;
+        if constexpr (J == 2) e = *reinterpret_cast<const u32_2*>(from);
+        else e = *reinterpret_cast<const u64_2*>(from);
+        e >>= 16 * (j0 - j1);
     } else {
         const uint64_t bit = (uint64_t(k) * g + j0) * BITS;
         const uint32_t at = uint32_t(bit / 8), shift = uint32_t(bit % 8);   // shift: 0 or 4
+        if (book_bytes >= 8) {
+            const uint32_t at1 = min(at, book_bytes - 8);   // what the codebook ends before is not used
+            e = *reinterpret_cast<const u64_1*>(book + at1) >> (8 * (at - at1));
+        } else {
 #pragma unroll
-        for (uint32_t b = 0; b <= kEntryBytes<BITS, J>; ++b) e |= uint64_t(book[min(at + b, book_bytes - 1)]) << (8 * b);   // past the end: not used
+            for (uint32_t b = 0; b <= kEntryBytes<BITS, J>; ++b) e |= uint64_t(book[min(at + b, book_bytes - 1)]) << (8 * b);
+        }
         e = (e >> shift) ^ (BITS == 8 ? 0ull : 0x8888888888888888ull);
     }
     return e;
@@ -432,6 +446,10 @@ hipError_t launch_entries(ColumnArgs p, int dtype, uint32_t most_slices, size_t 
     }
     // behind the partial sums, if there is room
     const size_t partial_bytes = best.slices > 1 ? align256(size_t(best.slices) * p.M * p.out_features * 4) : 0;
+    // Without room for the codebook's copy (one row or a few through a workspace of the sums' size) every workgroup takes its columns
+    // out of whole rows: 16 bits, M = 1, us with room / without / rows gathered tile by tile, as every length was before: K = 65536, g = 4, 1024 x 1024
+    // 9.0 / 12.0 / 12.2, 2048 x 2048 9.7 / 13.5 / 12.1, 4096 x 4096 12.3 / 16.4 / 21.9; g = 6, 4096 x 4096 16.5 / 20.1 / 19.2; g = 8, 1024 x 1024 9.7 / 15.2 / 11.9,
+    // 4096 x 4096 13.1 / 19.5 / 15.3, 4096 x 11008 21.3 / 27.3 / 34.3; g = 9, 2048 x 2048 10.9 / 14.6 / 12.0. K = 20000, g = 9, 4096 x 4096 12.6 / 12.2 / 21.0.
     if (room < partial_bytes + align256(book_bytes) + x_bytes) x_laid = false;
     const bool laid = !as_it_is && room >= partial_bytes + book_bytes;
     if (laid || x_laid) {

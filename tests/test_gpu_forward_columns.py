@@ -85,6 +85,29 @@ def test_forward_by_columns_with_the_quantised_codebook(M, i, o, g, K, dt, bits)
            (full, min(full, least)))
 
 
+@pytest.mark.parametrize("bits", [16, 8, 4])
+@pytest.mark.parametrize("g", [4, 5, 6, 7, 8, 9])
+@pytest.mark.parametrize("M,K", [(1, 1), (2, 3), (1, 65536), (3, 20480), (33, 40960)])
+def test_columns_straight_from_the_codebook(M, K, g, bits):
+    """The least workspace (none for 16 bits, sums of 64 slices for integers): every workgroup takes its columns out of rows of any
+    alignment, the last entry of a row and the last row of the codebook among them."""
+    import paper_2503_13089_amd as cc
+
+    i, o, dt = 128, 70, "bf16"
+    gen, x, codes, bias = _inputs(M, i, o, g, K, dt)
+    codes16 = codes.to(torch.int32).to(torch.int16).view(torch.uint16)
+    if bits == 16:
+        book = (torch.randn(K, g, device="cuda", generator=gen) * 0.05).to(x.dtype)
+        weight = book.double()[codes].reshape(i, -1)[:, :o].contiguous()
+        _check(lambda y, ws: cc.layer_forward(x, book, codes16, o, bias, y, ws), x, weight, None, bias, dt, (cc.layer_forward_workspace_bytes(M, i, o), 0))
+        return
+    q = _integers(K * g, bits, gen)
+    qbook, scale = _stored(q, bits), torch.full((1,), 0.125, device="cuda")
+    weight = q.double().reshape(K, g)[codes].reshape(i, -1)[:, :o].contiguous()
+    _check(lambda y, ws: cc.layer_forward_q(x, qbook, bits, scale, K, g, codes16, o, bias, y, ws), x, weight, 0.125, bias, dt,
+           (cc.layer_forward_q_workspace_bytes(M, i, o), 64 * M * o * 4))
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("dt", list(DTYPES))
 @pytest.mark.parametrize("M,g,K", [(1, 4, 65536), (16, 5, 65536), (3, 6, 4096), (16, 8, 20480), (2, 8, 65536), (17, 9, 65536)])
