@@ -32,6 +32,14 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
+// Between what lanes of one wave write to LDS and what other lanes of it read: its LDS accesses are served in order, so there is
+// nothing to wait for, but the compiler has to keep them in order.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A cell's list: the centroids within r1 of its centroid, then (d = 8) those between r1 and r2. Room in all for 4096 entries
 // where 1500 are aimed at: the vectors of a longer one are far. 29 M vectors, K = 65536, 10 iterations: room for 6144
 // 152.7 ms, 4096 153.4, 2560 157.5; 2.8 M vectors 28.4, 28.3 and 28.3 ms with 805, 537 and 335 MB of lists.
@@ -558,20 +566,20 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
                         make_uint2(bits, ((t + u) << 6) | uint32_t(lane));
                 queued += uint32_t(__popcll(hits));
                 if (queued >= 64) {
-                    __builtin_amdgcn_wave_barrier();
+                    wave_order();
                     work_off(64);
                     queued -= 64;
                     const uint2 rest = queue[64 + lane];
-                    __builtin_amdgcn_wave_barrier();
+                    wave_order();
                     if (uint32_t(lane) < queued) queue[lane] = rest;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_order();
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) a[u] = an[u];
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_order();
     work_off(queued);
     __syncthreads();
     if (wave == 0) {
@@ -725,6 +733,7 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
         rows[e] = row;
         ids[e] = id;
     }
+    wave_order();
     float cc_row[D];
     load_row<D>(a.C + size_t(c) * D, cc_row);
     const uint32_t nv = (n + 63) / 64;
@@ -1320,9 +1329,9 @@ __device__ __forceinline__ void far_sets(const float* __restrict__ X, const floa
 #pragma unroll
                 for (int q = 0; q < 16; ++q) cn[0][q] = 0.0f;
             } else {   // rows 16 h .. 16 h + 15 of every tile
-                __builtin_amdgcn_wave_barrier();   // what the group before had there has been read
+                wave_order();   // what the group before had there has been read
                 norms[lane] = norm;
-                __builtin_amdgcn_wave_barrier();
+                wave_order();
 #pragma unroll
                 for (int u = 0; u < GT; ++u)
 #pragma unroll
