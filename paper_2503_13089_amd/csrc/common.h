@@ -478,7 +478,8 @@ inline bool brings_rebuilt_q(uint64_t M, uint32_t in_features, uint32_t out_feat
 //   8 bits: g = 4, 4096 x 4096 at 384 63 / 61; 8192 x 28672 at 128 237 / 310, at 192 374 / 330.
 //   4 bits (more arithmetic a lookup): 4096 x 4096 at 192 48 / 54, at 320 83 / 59; 8192 x 8192 at 128 91 / 111, at 192 153 / 121; g = 6, 2048 x
 //   5000 at 128 30 / 38, at 192 49 / 40; g = 9, 4096 x 4096 at 128 47 / 48, at 192 82 / 57; 2048 x 2048 at 384 29 / 39.
-// Row by row: g = 12, 4096 x 4096 at 64 rows 39 / 48, at 96 59 / 50; g = 16, 4096 x 11008 62 / 85, 101 / 88; g = 2, 4096 x 4096 at 4 rows 40 / 36, at
+// Row by row (up to 127 rows of smaller layers the query asks for the sums' room only: the rebuilt weight is taken where that holds it or the
+// caller brings more): g = 12, 4096 x 4096 at 64 rows 39 / 48, at 96 59 / 50; g = 16, 4096 x 11008 62 / 85, 101 / 88; g = 2, 4096 x 4096 at 4 rows 40 / 36, at
 // 48 46 / 42; integers: g = 12 at 4 rows 71 / 43, g = 3, 2048 x 2048 30 / 25, g = 12, 1024 x 4096 at 32 26 / 27, at 48 32 / 27.
 inline bool rebuild_pays(uint64_t M, uint32_t g, int bits, uint32_t in_features, uint32_t out_features)
 {

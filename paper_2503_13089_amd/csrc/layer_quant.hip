@@ -3,11 +3,11 @@
 // up inference).
 //
 // Why it is faster here: a 16-bit codebook of 65536 x 4 entries (512 KB) lives in L2, and every code costs
-// one L1 miss (a 128-byte line fill), which caps reconstruction and the fused forward pass at ~0.4 codes
+// one L1 miss (a 128-byte line fill), which caps reconstruction at ~0.4 codes
 // per clock and CU. At 4 bits the same codebook is 128 KB and fits the 160 KB of LDS of one CU: persistent
 // workgroups (one per CU) copy it into LDS once and then serve every code from there, dequantising on the
 // fly (q * s in fp32, rounded to the 16-bit format of the layer). Codebooks too large for LDS are read from
-// global memory with the same code.
+// global memory with the same code. The forward pass is here for row lengths that do not go by columns.
 //
 // Quantisation rule (one scale per codebook): s = max|c| / (2^(b-1) - 1), q = clamp(rint(c / s)), both in
 // fp32; 4-bit values are two's-complement nibbles, element e in byte e/2, low nibble first.
@@ -89,8 +89,29 @@ __device__ __forceinline__ uint32_t dequant_pair(int q0, int q1, float s)
 __device__ __forceinline__ int nibble(uint32_t raw, int i) { return int(((raw >> (4 * i)) & 0xFu) ^ 8u) - 8; }
 __device__ __forceinline__ int byte_of(uint32_t raw, int i) { return int(int8_t((raw >> (8 * i)) & 0xFFu)); }
 
+// Any g, a byte or nibble at a time
 template <int DT, int BITS>
 __device__ __forceinline__ void dequant_row_words(const uint8_t* book, uint32_t k, uint32_t g, float s, uint32_t (&w)[8])
+{
+    const size_t e0 = size_t(k) * g;
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+        if (2 * q >= g) break;
+        int v[2] = {0, 0};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const size_t e = e0 + 2 * q + i;
+            if (2 * q + i >= g) continue;
+            if constexpr (BITS == 4) v[i] = nibble(book[e >> 1], int(e & 1));
+            else v[i] = int(int8_t(book[e]));
+        }
+        w[q] = dequant_pair<DT, BITS>(v[0], v[1], s);
+    }
+}
+
+// Rows of 4 or 8 in one load
+template <int DT, int BITS>
+__device__ __forceinline__ void dequant_row_fast(const uint8_t* book, uint32_t k, uint32_t g, float s, uint32_t (&w)[8])
 {
     if (g == 4) {
         if constexpr (BITS == 4) {
@@ -118,20 +139,7 @@ __device__ __forceinline__ void dequant_row_words(const uint8_t* book, uint32_t 
         for (int q = 0; q < 4; ++q) w[q] = dequant_pair<DT, BITS>(nibble(raw, 2 * q), nibble(raw, 2 * q + 1), s);
         return;
     }
-    const size_t e0 = size_t(k) * g;
-#pragma unroll
-    for (uint32_t q = 0; q < 8; ++q) {
-        if (2 * q >= g) break;
-        int v[2] = {0, 0};
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const size_t e = e0 + 2 * q + i;
-            if (2 * q + i >= g) continue;
-            if constexpr (BITS == 4) v[i] = nibble(book[e >> 1], int(e & 1));
-            else v[i] = int(int8_t(book[e]));
-        }
-        w[q] = dequant_pair<DT, BITS>(v[0], v[1], s);
-    }
+    dequant_row_words<DT, BITS>(book, k, g, s, w);
 }
 
 // Copies the codebook into LDS: whole 16-byte pieces, then the last few bytes one by one. Every workgroup of
@@ -191,7 +199,7 @@ __global__ __launch_bounds__(1024) void layer_weight_q_kernel(const uint8_t* __r
             const uint64_t v = v0 + u * stride;
             if (v >= num_codes) break;
             uint32_t w[8];
-            dequant_row_words<DT, BITS>(book, ks[u], g, s, w);
+            dequant_row_fast<DT, BITS>(book, ks[u], g, s, w);
             if (whole4) {
                 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 __builtin_nontemporal_store(u32x2{w[0], w[1]}, reinterpret_cast<u32x2*>(weight) + v);
@@ -228,11 +236,11 @@ __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c)
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Same tiling as the 16-bit forward kernel (32*MT rows x 64 columns x a slice of in-features per job, 4 waves
-// each owning a 16-wide k slice of every 64-wide step), but the workgroups are persistent: each copies the
-// codebook into LDS once and then walks its jobs. It serves g other than 4 and 8, M above 16, and codebooks too
-// large for LDS (then read from global memory by four workgroups per CU); decode-time shapes take the few-rows
-// kernel below.
+// Same tiling as the 16-bit forward kernel of layer_forward.hip (32*MT rows x 64 columns x a slice of in-features per job, 4
+// waves each owning a 16-wide k slice of every 64-wide step), but the workgroups are persistent: each copies the
+// codebook into LDS once and then walks its jobs (codebooks too large for LDS are read from global memory by four
+// workgroups per CU). It serves g = 1 .. 3 and 10 .. 16 where rebuilding the weight does not pay (rebuild_pays in common.h) or has no
+// room; g = 4 .. 9 go by columns (layer_forward_columns.hip).
 template <int DT, int MT, int BITS, bool IN_LDS>
 __global__ __launch_bounds__(kThreads) void layer_forward_q_kernel(
     const uint16_t* __restrict__ x, uint32_t M, const uint8_t* __restrict__ qbook, uint32_t book_bytes,
@@ -468,7 +476,7 @@ uint32_t layer_forward_q_splits(uint64_t M, uint32_t in_features, uint32_t out_f
     return uint32_t(std::max<uint64_t>(1, std::min<uint64_t>(splits, 64)));
 }
 
-// Upper bound over both kernels (the few-rows kernel may use up to 64 slices): sizes the partial buffer.
+// Slices that sums have room for: those of this file's kernel, or up to 64 for few rows by columns (layer_forward_columns.hip).
 uint32_t layer_forward_q_max_splits(uint64_t M, uint32_t in_features, uint32_t out_features)
 {
     return M <= 64 ? 64u : layer_forward_q_splits(M, in_features, out_features);

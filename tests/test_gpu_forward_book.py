@@ -1,5 +1,6 @@
-"""Few rows through a layer whose codebook passes through LDS in parts (g = 4, Section 3.2's layer listing): at the edges of
-parts, columns per workgroup and chunks of in-features, against the product with the rebuilt weight in float64."""
+"""One to four rows through a layer with g = 4 (Section 3.2's layer listing), a column of the codebook in LDS or two or four of them
+(up to 40960 and 20480 rows): in-features that leave a matrix-core step unfilled, fewer steps than waves, a padding column, infinite
+inputs and entries, against the product with the rebuilt weight in float64."""
 import numpy as np
 import pytest
 
@@ -10,8 +11,8 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("dt", ["float16", "bfloat16"])
 @pytest.mark.parametrize("M,in_features,out_features,K,kind", [
-    (1, 8, 4096, 200, ""), (2, 4096, 1029, 16384, ""),    # fewer pairs than slots; a padding column, 2 columns a workgroup
-    (1, 14344, 600, 16385, ""), (2, 7176, 1000, 32769, ""),  # one chunk and a bit; a part of one row
+    (1, 8, 4096, 200, ""), (2, 4096, 1029, 16384, ""),    # less than a step; a padding column, four columns
+    (1, 14344, 600, 16385, ""), (2, 7176, 1000, 32769, ""),  # a last step of 8 in-features; two columns
     (4, 3592, 1200, 32768, ""), (3, 4096, 512, 10001, ""), (1, 8192, 8202, 65536, ""),
     (2, 4096, 1032, 20000, "x"), (1, 4096, 1032, 20000, "book")])
 def test_few_rows_with_the_codebook_in_parts(M, in_features, out_features, K, kind, dt):

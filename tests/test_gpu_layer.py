@@ -294,14 +294,13 @@ FORWARD_CASES = [  # (M, in_features, out_features, g, K, bias)
     (32, 1024, 1024, 8, 65536, True),
     (5, 64, 70, 7, 3, False),
     (200, 4096, 256, 4, 65536, False),
-    # few rows: one or two with g = 4 and many codes per codebook row take a kernel of their own (the codebook through LDS in
-    # parts, tests/test_gpu_forward_book.py), the others the tile kernel
-    (2, 136, 200, 8, 300, True),      # in_features not a multiple of the 16 rows a round of the 8 waves takes
+    # few rows (by columns of the codebook, as all of g = 4 .. 9)
+    (2, 136, 200, 8, 300, True),      # in_features not a multiple of the 32 of a step
     (3, 1048, 1000, 4, 65536, False),
     (4, 4096, 1280, 4, 65536, True),  # several slices of in_features
     (2, 24, 516, 4, 300, False),
     (3, 40, 250, 4, 900, True),       # padding columns in the last code column
-    (4, 8, 12, 4, 7, True),           # fewer pairs of in-features than waves
+    (4, 8, 12, 4, 7, True),           # fewer in-features than a step
     (8, 520, 516, 8, 4096, True),     # padding columns (516 = 64 * 8 + 4)
     (9, 264, 333, 4, 1000, True),     # padding columns, ragged last block of code columns
     (12, 72, 68, 4, 50, False),
