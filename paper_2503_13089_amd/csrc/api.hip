@@ -285,7 +285,8 @@ bool cells_from_first(uint64_t N, uint32_t d, uint32_t K) { return d == 8 && N *
 // Iterations of a fit by cells that begin with grouping the vectors by their codes (anew): most codes change early, and a grouping costs
 // what one or two E-steps of that size do. 29 M vectors of 8 from the first iteration on: after 2 and 5 iterations 102 ms, 2 102, 4 104, 3 and
 // 8 105. Else 1 and 5; 11 M of 4, 20 iterations / K = 20000, 10 iterations / 4.2 M of 4 / 4.2 M of 8 / 2.8 M of 6: 15.3 / 9.1 / 5.98 / 14.1 / 21.1 ms,
-// with 1, 3 and 8 15.8 / 9.9 / 6.25 / 14.4 / 21.0, with 1 alone 16.8 / 8.6 / 5.9 / 13.8 / 22.4.
+// with 1, 3 and 8 15.8 / 9.9 / 6.25 / 14.4 / 21.0, with 1 alone 16.8 / 8.6 / 5.9 / 13.8 / 22.4. So 1 and 5 suits
+// the benchmark's fit and the padded lengths; the three between would be 1 to 5 % faster with 1 alone.
 bool regroup_at(int32_t t, bool from_first) { return from_first ? t == 2 || t == 5 : t == 1 || t == 5; }
 
 // First iteration of a fit by cells (d = 8). The bootstrap's codes are among the nearest few hundred of their vector's cell rather than

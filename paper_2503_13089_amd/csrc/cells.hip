@@ -671,7 +671,7 @@ __device__ __forceinline__ float rough_distance(const float (&x)[D], const float
 
 // ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
 // Direct-form distances are final: no guard band and no index recovery. Rows past the list are NaN and never win.
-// Bound: vector instructions, 19 per 64 (vector, entry) pairs by the counters where the distance, its comparison and two selects
+// Bound: vector instructions, 17 per 64 (vector, entry) pairs by the counters where the distance, its comparison and two selects
 // are 11; 0.49 G pairs in 0.15 ms (lists of 43 entries, N = 11 M). A workgroup is one wave, as in the kernels for d = 8: two in five
 // items are empty or short, and in a workgroup of four the room of those waves waits for the longest (0.21 ms).
 // Tried: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest

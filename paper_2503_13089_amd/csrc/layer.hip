@@ -111,7 +111,7 @@ hipError_t launch_layer_pack_codes(const uint32_t* idx, uint64_t n, uint32_t K, 
 // (fp32: 2 g), `padding` and out_features too. No wave needs another one.
 // Element by element the loads and stores are what counts (2 G + 1 an instruction each). 4096 x 11005, K = 65536, us, before and
 // now: g = 4 108 / 49, g = 5 (K = 35000) 119 / 45, g = 6 105 / 38, g = 8 109 / 31, g = 9 121 / 39; 512 x 700 9.3 / 6.6.
-// Now bound by a codebook line from L2 per code (0.3 to 0.4 a clock and compute unit) where K = 65536; K = 4096, g = 4 28.
+// Now bound by a codebook line from L2 per code (0.3 to 0.4 a clock and compute unit) where K = 65536; K = 4096, g = 4 26.
 template <int G>
 constexpr int kCodesPerLane = G <= 9 ? 4 : (G <= 18 ? 2 : 1);
 
