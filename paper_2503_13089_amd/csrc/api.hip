@@ -819,11 +819,10 @@ int cc_layer_codebook_grad(const void* grad_weight, int grad_dtype, uint32_t in_
     if (workspace_bytes < need) return fail(CC_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const cc::Workspace w = cc::carve(workspace, n_ws, g, K, workspace_bytes);
-    // A large layer with 16-bit gradients whose sub-vectors are whole rows of g numbers: summed in place by cluster
-    // slices, no fp32 copy of the gradient (the same fixed-point sums as below, hence the same bits).
-    if (grad_dtype != CC_F32 && out_features % g == 0 && !w.padded && aligned(grad_weight, 16) && aligned(codes, 4) &&
-        cc::update_sliced_applies(uint32_t(N), w.d, K, w)) {
-        CC_TRY_HIP(cc::launch_sum_rows16_sliced(grad_weight, grad_dtype, uint32_t(N), w.d, codes, K, grad_codebook, w, s),
+    // A large layer with 16-bit gradients: summed in place by cluster slices, no fp32 copy of the gradient (the same fixed-point
+    // sums as below, hence the same bits).
+    if (grad_dtype != CC_F32 && cc::sum_rows16_applies(uint32_t(N), w.d, K, w)) {
+        CC_TRY_HIP(cc::launch_sum_rows16(grad_weight, grad_dtype, uint32_t(N), out_features, g, codes, K, grad_codebook, w, s),
                    "codebook gradient (slices)");
         return CC_OK;
     }

@@ -400,10 +400,11 @@ hipError_t launch_update_buckets(const float* X, uint32_t N, uint32_t d, const u
 bool update_sliced_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
 // Whether all clusters fit one slice, i.e. the pass needs neither lists nor a second look at a code.
 inline bool update_one_slice(uint32_t d, uint32_t K) { return K <= 16384 / d; }
-// Sums (not means) of 16-bit rows (dtype 1 = fp16, 2 = bf16; 16-byte aligned) by 16-bit code (4-byte aligned), both read
-// in place; needs update_sliced_applies(N, d, K, w). Header as after a reset and a scan of the rows.
-hipError_t launch_sum_rows16_sliced(const void* rows, int dtype, uint32_t N, uint32_t d, const uint16_t* codes, uint32_t K,
-                                    float* out, const Workspace& w, hipStream_t s);
+// Sums (not means) of the sub-vectors of a 16-bit gradient [in][out_features] (dtype 1 = fp16, 2 = bf16) by 16-bit code, both read in
+// place; out [K][g]. Header as after a reset and a scan of the rows.
+bool sum_rows16_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
+hipError_t launch_sum_rows16(const void* grad, int dtype, uint32_t N, uint32_t out_features, uint32_t g, const uint16_t* codes, uint32_t K,
+                             float* out, const Workspace& w, hipStream_t s);
 // fresh: instead of launch_reset_header and launch_scan_inputs too
 hipError_t launch_update_sliced(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev, uint32_t K,
                                 float* out, uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, hipStream_t s);

@@ -18,12 +18,20 @@
 // entries rebuilt from each codebook entry): there the rows are 16-bit numbers and the codes the layer's stored 16-bit
 // codes, both read in place and converted as they are fetched (SRC below).
 //
-// Bound: with many slices, one 8/16/32/64-byte row fetch per vector from a different cache line each - the L1 fill rate
-// (about 0.35 lines per clock and compute unit); with few, the two passes over the rows (5 TB/s). The former form had every
-// slice look at every code, with packed positions in an LDS queue, after a reset, a scan and an fp64 conversion per number.
-// Before and after, a whole call: 11.3 M vectors of 4 at K = 65536 159 -> 134 us (53 chunks, 68 sums, 10 means); 28 M of 8
-// 845 -> 484; 1.1 M of 4 at K = 300 106 -> 26; 6 M of 16 at K = 3000 206 -> 181; bf16 gradient of a 4096x11008 layer
-// 142 -> 108. 28 M of 8 at K = 6000 pay for writing and reading the entries: 420 -> 435.
+// Rows of 8 to 32 bytes go along (record_chunk_kernel): what a chunk leaves for a slice are its rows as 16-bit numbers, read back in
+// sequence, instead of entries that name rows to be fetched from a line each. Taken for 16-bit gradients and for fp32 vectors of 4
+// whose chunk holds fp16 or bf16 numbers only (a compressed model's weights do); a chunk of other numbers leaves entries. fp32 vectors
+// of 8 and 16 keep the entries: at 32 bytes a row the second read costs less than writing the rows (28 M of 8 500 us with entries, 526
+// with rows).
+//
+// Bound, rows along: the passes over memory (chunk kernel 5.6 TB/s, 40 us for the gradient of 4096x11008, 61 for the vectors of 4), then
+// 14 vector instructions per number for its fixed-point term (26 us) beside the records from memory (25 us) and the LDS atomics
+// (11 clocks a wave, 14 us). Slices of 2048 clusters at d = 4 then, half the partial sums of 4096. By entries: one row fetch per
+// vector from a different cache line each - the L1 fill rate - or, with few slices, the two passes over the rows.
+// By entries / rows along, a whole call: 11.3 M vectors of 4 at K = 65536 133 -> 109 us, K = 8192 (20 M) 199 -> 179, 1 M 35 -> 27; numbers that are
+// neither 134 -> 126 (20 M at K = 8192 200, as before, at 15000 219 -> 228); bf16 gradient of 4096x11008 108 -> 82, g = 8 85 -> 82, 1000x1111 41 -> 25. Through an fp32 copy / rows along: g = 6
+// 344 -> 143 us, g = 9 458 -> 187.
+// By entries only: 28 M of 8 at K = 65536 500 us, 6 M of 16 at K = 3000 189; one slice: 11.5 M of 4 at K = 300 106.
 #include <algorithm>
 #include <type_traits>
 
@@ -38,7 +46,11 @@ constexpr int kWaves = kThreads / 64;
 constexpr uint32_t kWorkgroups = 256;
 constexpr uint32_t kLeast = 32768;        // vectors; below, few memory-side atomics take no longer (20000 of 16 numbers: 33 and 36 us)
 constexpr int kChunkThreads = 512;        // for a chunk: finer grains than 1024, 4 M vectors are 585 chunks
-constexpr uint32_t kChunk = 7168;         // vectors sorted together
+// Vectors sorted together. Records hold 10 (d = 4) to 34 bytes each in LDS, and this leaves room for two to four chunks on a compute unit.
+template <int D, bool RECORDS>
+constexpr uint32_t kChunkOf = RECORDS ? (D == 16 ? 1792 : 3584) : 7168;
+template <int D, bool RECORDS>
+constexpr int kChunkThreadsOf = RECORDS ? int(kChunkOf<D, true> / 7) : kChunkThreads;
 constexpr uint32_t kPosBits = 13;
 constexpr uint32_t kCounters = 512;       // of a chunk: slices x 8 groups of positions x what is left for the lanes, so that
 constexpr uint32_t kGroups = 8;           // few of them take turns at one counter
@@ -92,9 +104,9 @@ __device__ __forceinline__ uint32_t code_at(const void* idx, size_t i)
 }
 
 // As many clusters as LDS holds, one workgroup per compute unit.
-template <int D>
+template <int D, bool RECORDS = false>
 struct Slice {
-    static constexpr uint32_t kBits = D == 4 ? 12u : (D == 8 ? 11u : 10u);
+    static constexpr uint32_t kBits = D == 4 ? (RECORDS ? 11u : 12u) : (D == 8 ? 11u : 10u);
     static constexpr uint32_t kClusters = 1u << kBits;
     // sums of one component lie side by side; the two extra keep the lanes that share a row off one bank
     static constexpr uint32_t kPitch = kClusters + 2;
@@ -105,8 +117,17 @@ struct Slice {
 
 // What the input scan found in one chunk, and its codes >= K.
 struct ScanPart {
-    uint32_t absmax, flags, skipped, pad;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input
+    uint32_t absmax, flags, skipped;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input
+    uint32_t kind;                     // what lies in the chunk's part of the entry buffer: a Kind
 };
+// Entries (32 bits each), or the rows themselves as fp16 or bf16 numbers by slice, followed by their clusters within the slice (16 bits).
+enum Kind : uint32_t { kEntries = 0, kRowsF16 = 1, kRowsBf16 = 2 };
+template <int D>
+constexpr uint32_t kRecordBytes = 2 * D + 2;
+template <int D>
+constexpr int kRecordRows = 2;   // a lane has under way twice
+template <int D>
+constexpr uint32_t kRecordStep = kRecordRows<D> * (D == 16 ? 32 : 64);   // rows of a wave at once
 
 struct Cut {
     bool listed;
@@ -116,23 +137,25 @@ struct Cut {
 };
 
 // The record buffer (2 N records) holds it all; ranges = 0: not even one range of partial sums fits.
-template <int D>
+template <int D, bool RECORDS = false>
 Cut cut_of(uint32_t N, uint32_t K)
 {
+    constexpr uint32_t kChunk = kChunkOf<D, RECORDS>;
     const size_t have = size_t(N) * 2 * (4 * D + 16);
     Cut c;
-    c.listed = !update_one_slice(D, K);
+    c.listed = RECORDS || !update_one_slice(D, K);
+    using S = Slice<D, RECORDS>;
     static_assert(Slice<D>::kClusters == 16384 / D);
-    c.slices = (K + Slice<D>::kClusters - 1) / Slice<D>::kClusters;
+    c.slices = (K + S::kClusters - 1) / S::kClusters;
     c.chunks = uint32_t((uint64_t(N) + kChunk - 1) / kChunk);
     c.part_bytes = align256(size_t(c.chunks) * sizeof(ScanPart));
-    c.entry_bytes = c.listed ? align256(size_t(c.chunks) * kChunk * 4) : 0;
+    c.entry_bytes = c.listed ? align256(size_t(c.chunks) * kChunk * (RECORDS ? kRecordBytes<D> : 4)) : 0;
     c.start_bytes = c.listed ? align256(size_t(c.chunks) * (c.slices + 1) * 4) : 0;
-    const size_t taken = c.part_bytes + c.entry_bytes + c.start_bytes + 256, per_range = size_t(c.slices) * Slice<D>::kLdsBytes;
+    const size_t taken = c.part_bytes + c.entry_bytes + c.start_bytes + 256, per_range = size_t(c.slices) * S::kLdsBytes;
     const uint32_t fit = uint32_t(have > taken ? std::min<size_t>((have - taken) / per_range, kWorkgroups) : 0);
     c.ranges = std::min({std::max(kWorkgroups / c.slices, 1u), c.chunks, fit});
     c.sharers = 1;
-    while (c.sharers < uint32_t(kWaves) && c.sharers * 128 < kChunk / c.slices) c.sharers *= 2;
+    while (c.sharers < uint32_t(kWaves) && c.sharers * (RECORDS ? kRecordStep<D> : 128u) < kChunk / c.slices) c.sharers *= 2;
     c.sum_bytes = align256(per_range * c.ranges);
     return c;
 }
@@ -165,6 +188,57 @@ struct Scan {
     }
 };
 
+// The same in fewer instructions, of numbers that are all finite: otherwise flag 1 is set and Scan has to look again. fp32 numbers
+// come with their fp16 neighbour; flag 2: one is no fp16 number, flag 3: one is no bf16 number.
+template <int SRC>
+struct RowScan {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    uint32_t m = 0, strange = 0, bits = 0;   // largest magnitude, that of those that are no fp16 numbers, the OR of all
+    __device__ __forceinline__ void look(uint32_t w, float back)
+    {
+        if constexpr (SRC == 0) {
+            const uint32_t a = w & 0x7fffffffu;
+            m = max(m, a);
+            strange = max(strange, back != __uint_as_float(w) ? a : 0u);
+            bits |= w;
+        } else {   // both halves at once
+            const uint32_t a = w & 0x7fff7fffu;
+            m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, a)));
+        }
+    }
+    __device__ __forceinline__ uint32_t largest() const { return SRC == 0 ? m : max(m & 0xffffu, m >> 16); }
+    __device__ __forceinline__ uint32_t flags() const
+    {
+        if constexpr (SRC != 0) return largest() < (SRC == 1 ? 0x7c00u : 0x7f80u) ? 0u : 2u;
+        return uint32_t(strange >= 0x38800000u || m >= 0x47000000u) | (m < 0x7f800000u ? 0u : 2u) | (strange != 0 ? 4u : 0u) |
+               ((bits & 0xffffu) != 0 ? 8u : 0u);
+    }
+};
+
+// Counts to places, by one wave, eight counters per lane.
+__device__ __forceinline__ void counts_to_places(uint32_t* count, uint32_t& total)
+{
+    constexpr uint32_t kEach = kCounters / 64;
+    uint32_t c[kEach], sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
+        c[q] = count[threadIdx.x * kEach + q];
+        sum += c[q];
+    }
+    uint32_t upto = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = uint32_t(__shfl_up(int(upto), off, 64));
+        if (int(threadIdx.x) >= off) upto += o;
+    }
+    uint32_t at = upto - sum;
+    if (threadIdx.x == 63) total = upto;
+#pragma unroll
+    for (uint32_t q = 0; q < kEach; ++q) {
+        count[threadIdx.x * kEach + q] = at;
+        at += c[q];
+    }
+}
+
 // One chunk. FRESH: the input scan of its rows and codes. LISTED: its entries by slice, entries[chunk][..], the slices'
 // starts within it in starts[chunk][slices + 1]; the order within a slice depends on scheduling, the sums do not. Codes >= K
 // belong to no slice.
@@ -174,6 +248,7 @@ __global__ __launch_bounds__(kChunkThreads) void slice_chunk_kernel(const void* 
                                                                uint32_t* __restrict__ entries, uint32_t* __restrict__ starts)
 {
     using S = Slice<D>;
+    constexpr uint32_t kChunk = kChunkOf<D, false>;
     constexpr int U = kChunk / kChunkThreads;
     static_assert(kChunk % kChunkThreads == 0, "whole rounds");
     __shared__ uint32_t count[kCounters];
@@ -267,30 +342,10 @@ __global__ __launch_bounds__(kChunkThreads) void slice_chunk_kernel(const void* 
     __syncthreads();
     if (FRESH && threadIdx.x == 0) {
         scan.m = red[0];
-        parts[blockIdx.x] = ScanPart{scan.absmax(), red[1], red[2], 0u};
+        parts[blockIdx.x] = ScanPart{scan.absmax(), red[1], red[2], kEntries};
     }
     if constexpr (LISTED) {
-        if (threadIdx.x < 64) {   // counts to places, eight counters per lane
-            constexpr uint32_t kEach = kCounters / 64;
-            uint32_t c[kEach], sum = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < kEach; ++q) {
-                c[q] = count[threadIdx.x * kEach + q];
-                sum += c[q];
-            }
-            uint32_t upto = sum;
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t o = uint32_t(__shfl_up(int(upto), off, 64));
-                if (int(threadIdx.x) >= off) upto += o;
-            }
-            uint32_t at = upto - sum;
-            if (threadIdx.x == 63) total = upto;
-#pragma unroll
-            for (uint32_t q = 0; q < kEach; ++q) {
-                count[threadIdx.x * kEach + q] = at;
-                at += c[q];
-            }
-        }
+        if (threadIdx.x < 64) counts_to_places(count, total);
         __syncthreads();
         if (threadIdx.x <= slices)
             starts[size_t(blockIdx.x) * (slices + 1) + threadIdx.x] = threadIdx.x < slices ? count[(threadIdx.x * kGroups) << log_lanes] : total;
@@ -303,6 +358,193 @@ __global__ __launch_bounds__(kChunkThreads) void slice_chunk_kernel(const void* 
         __syncthreads();
         for (uint32_t t = threadIdx.x; t < total; t += kChunkThreads) entries[size_t(first) + t] = sorted[t];
     }
+}
+
+// Where the rows of a layer's gradient lie: row v = (r, c) of codes [in][per_row] at r * out_features + c * g, the last of every
+// r less `padding` numbers. per_row = 0: whole rows of D numbers side by side.
+struct RowPlace {
+    uint32_t per_row, g, padding;
+};
+
+// One chunk whose rows go along: as slice_chunk_kernel<FRESH, LISTED>, but what it leaves for a slice are the rows themselves,
+// 16-bit numbers, and their clusters. fp32 rows (SRC 0) do where all numbers of the chunk are fp16 numbers, or all of them bf16 ones;
+// a chunk of others leaves entries. The rows are read once, coalesced, and held in registers until their places are known.
+template <int D, int SRC, bool WHOLE>
+__global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void record_chunk_kernel(const void* __restrict__ X, const void* __restrict__ idx, uint32_t N,
+                                                                                uint32_t K, uint32_t slices, RowPlace place,
+                                                                                ScanPart* __restrict__ parts, char* __restrict__ records,
+                                                                                uint32_t* __restrict__ starts)
+{
+    using S = Slice<D, true>;
+    constexpr uint32_t kChunk = kChunkOf<D, true>, T = kChunkThreadsOf<D, true>;
+    constexpr int U = kChunk / T;
+    static_assert(kChunk % T == 0 && (SRC != 0 || WHOLE), "whole rounds");
+    typedef uint32_t Words __attribute__((ext_vector_type(D == 4 ? 2 : 4)));   // a piece of a record
+    constexpr int kPieces = D == 16 ? 2 : 1;
+    __shared__ uint32_t count[kCounters];
+    __shared__ __attribute__((aligned(16))) char sorted[kChunk * kRecordBytes<D>];
+    __shared__ uint32_t total, red[3];
+    const uint32_t first = blockIdx.x * kChunk, n = min(kChunk, N - first);
+    const uint32_t log_lanes = slices == 1 ? 6u : 6 - (32 - __clz(slices - 1)), sub = threadIdx.x & ((1u << log_lanes) - 1);
+    uint32_t code[U], rank[U], raw[U][D / 2];   // 16-bit numbers: of fp32 rows the fp16 ones
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t p = u * T + threadIdx.x;
+        code[u] = p < n ? code_at<SRC>(idx, size_t(first) + p) : 0xffffffffu;
+    }
+    for (uint32_t t = threadIdx.x; t < kCounters; t += T) count[t] = 0;
+    if (threadIdx.x < 3) red[threadIdx.x] = 0;
+    // past the end the last row once more, which finds nothing new and belongs to no slice
+    auto row_at = [&](int u) { return size_t(first) + min(uint32_t(u * T + threadIdx.x), n - 1); };
+    RowScan<SRC> scan;
+    if constexpr (SRC == 0) {
+        constexpr int kAtOnce = D == 4 ? U : 4;   // rows in registers as they are
+#pragma unroll
+        for (int u0 = 0; u0 < U; u0 += kAtOnce) {
+            uint4 t[kAtOnce][D / 4];
+#pragma unroll
+            for (int v = 0; v < kAtOnce && u0 + v < U; ++v)
+#pragma unroll
+                for (int q = 0; q < D / 4; ++q) t[v][q] = static_cast<const uint4*>(X)[row_at(u0 + v) * (D / 4) + q];
+#pragma unroll
+            for (int v = 0; v < kAtOnce && u0 + v < U; ++v) {
+#pragma unroll
+                for (int q = 0; q < D / 4; ++q) {
+                    const uint32_t w[4] = {t[v][q].x, t[v][q].y, t[v][q].z, t[v][q].w};
+                    uint16_t h[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const _Float16 half = _Float16(__uint_as_float(w[j]));
+                        h[j] = __builtin_bit_cast(uint16_t, half);
+                        scan.look(w[j], float(half));
+                    }
+                    raw[u0 + v][2 * q] = uint32_t(h[0]) | uint32_t(h[1]) << 16;
+                    raw[u0 + v][2 * q + 1] = uint32_t(h[2]) | uint32_t(h[3]) << 16;
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (WHOLE) {
+                constexpr int A = D * 2 < 16 ? D * 2 : 16;
+                __builtin_memcpy(raw[u], __builtin_assume_aligned(static_cast<const uint32_t*>(X) + row_at(u) * (D / 2), A), D * 2);
+            } else {
+                const uint32_t v = uint32_t(row_at(u)), r = v / place.per_row;
+                const uint32_t keep = v - r * place.per_row == place.per_row - 1 ? place.g - place.padding : place.g;
+                const uint16_t* from = static_cast<const uint16_t*>(X) + (size_t(v) * place.g - size_t(r) * place.padding);
+#pragma unroll
+                for (int j = 0; j < D; ++j) {
+                    const uint32_t half = uint32_t(j) < place.g ? from[min(uint32_t(j), keep - 1)] : 0u;
+                    const uint32_t kept = uint32_t(j) < keep ? half : 0u;
+                    raw[u][j / 2] = j & 1 ? raw[u][j / 2] | kept << 16 : kept;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < D / 2; ++q) scan.look(raw[u][q], 0.0f);
+    }
+    __syncthreads();   // counters and reductions are clear
+    uint32_t m = scan.largest(), flags = scan.flags();
+    if (flags & 2u) {   // what is not finite has no magnitude
+        Scan<SRC> again;
+        if constexpr (SRC == 0) {
+#pragma unroll 1
+            for (int u = 0; u < U; ++u)
+                for (int q = 0; q < D; ++q) again.look(static_cast<const uint32_t*>(X)[row_at(u) * D + q]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < D / 2; ++q) {
+                    again.look(raw[u][q]);
+                    constexpr uint32_t kInf = SRC == 1 ? 0x7c00u : 0x7f80u;   // such numbers add nothing
+                    raw[u][q] &= ((raw[u][q] & kInf) == kInf ? 0u : 0xffffu) | (((raw[u][q] >> 16) & kInf) == kInf ? 0u : 0xffff0000u);
+                }
+        }
+        m = again.m;
+        flags |= again.flags;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
+        flags |= uint32_t(__shfl_xor(int(flags), off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&red[0], m);
+        if (flags) atomicOr(&red[1], flags);
+    }
+    __syncthreads();
+    const uint32_t found = red[1];
+    const uint32_t kind = SRC != 0 ? uint32_t(SRC) : ((found & 2u) ? kEntries : (!(found & 4u) ? kRowsF16 : (!(found & 8u) ? kRowsBf16 : kEntries)));
+    // As in slice_chunk_kernel the entries of few slices stay in the order of the rows.
+    const bool keep_order = SRC == 0 && kind == kEntries && slices <= 8;
+    static_assert(SRC != 0 || (kChunk / 64 <= 64 && kCounters == 8 * 64), "a count per slice and 64 positions");
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto counter = [&](uint32_t code, int u) {
+        const uint32_t slice = code >> S::kBits;
+        return keep_order ? (slice << 6) | (u * (T / 64) + wave) : (((slice << 3) | (u * kGroups / U)) << log_lanes) | sub;
+    };
+    uint32_t bad = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        rank[u] = 0;
+        if (keep_order) {
+            const uint32_t slice = code[u] >> S::kBits;
+            const unsigned long long valid = __ballot(code[u] < K), b0 = __ballot(slice & 1), b1 = __ballot(slice & 2), b2 = __ballot(slice & 4);
+            auto members = [&](uint32_t q) { return valid & (q & 1 ? b0 : ~b0) & (q & 2 ? b1 : ~b1) & (q & 4 ? b2 : ~b2); };
+            const unsigned long long same = members(slice);
+            rank[u] = __builtin_amdgcn_mbcnt_hi(uint32_t(same >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0u));
+            if (lane < 8) count[(lane << 6) | (u * (T / 64) + wave)] = uint32_t(__popcll(members(lane)));
+        } else if (code[u] < K) {
+            rank[u] = atomicAdd(&count[counter(code[u], u)], 1u);
+        }
+        if (code[u] >= K && u * T + threadIdx.x < n) ++bad;
+    }
+    if (bad) atomicAdd(&red[2], bad);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Scan<SRC> whole;
+        whole.m = red[0];
+        parts[blockIdx.x] = ScanPart{whole.absmax(), found & 3u, red[2], kind};
+    }
+    if (threadIdx.x < 64) counts_to_places(count, total);
+    __syncthreads();
+    const uint32_t members = total;
+    if (threadIdx.x <= slices)   // the first counter of a slice
+        starts[size_t(blockIdx.x) * (slices + 1) + threadIdx.x] =
+            threadIdx.x < slices ? count[keep_order ? threadIdx.x << 6 : (threadIdx.x * kGroups) << log_lanes] : members;
+    char* out = records + size_t(blockIdx.x) * (kChunk * kRecordBytes<D>);
+    uint16_t* clusters = reinterpret_cast<uint16_t*>(sorted + kChunk * (2 * D));
+    if (SRC == 0 && kind == kEntries) {
+        uint32_t* at = reinterpret_cast<uint32_t*>(sorted);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (code[u] < K) at[count[counter(code[u], u)] + rank[u]] = ((code[u] & (S::kClusters - 1)) << kPosBits) | (u * T + threadIdx.x);
+        __syncthreads();
+        for (uint32_t t = threadIdx.x; t < members; t += T) reinterpret_cast<uint32_t*>(out)[t] = at[t];
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (code[u] >= K) continue;
+        const uint32_t at = count[counter(code[u], u)] + rank[u];
+        if (SRC == 0 && kind == kRowsBf16) {   // the fp32 row once more, from L2
+#pragma unroll
+            for (int q = 0; q < D / 2; ++q) {
+                const uint2 t = static_cast<const uint2*>(X)[row_at(u) * (D / 2) + q];
+                raw[u][q] = (t.x >> 16) | (t.y & 0xffff0000u);
+            }
+        }
+        __builtin_memcpy(__builtin_assume_aligned(sorted + at * (2 * D), D == 4 ? 8 : 16), raw[u], 2 * D);
+        clusters[at] = uint16_t(code[u] & (S::kClusters - 1));
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < members * kPieces; t += T)
+        reinterpret_cast<Words*>(out)[t] = reinterpret_cast<const Words*>(sorted)[t];
+    for (uint32_t t = threadIdx.x; t < (members + 1) / 2; t += T)   // the last one may bring a number that nobody reads
+        reinterpret_cast<uint32_t*>(out + kChunk * (2 * D))[t] = reinterpret_cast<const uint32_t*>(clusters)[t];
 }
 
 // (slice, range) of a workgroup. Workgroups are dealt to the 8 XCDs in turn; XCD q takes the q-th contiguous share of
@@ -318,8 +560,117 @@ __device__ __forceinline__ bool job_of_workgroup(uint32_t slices, uint32_t range
     return job < jobs && blockIdx.x / 8 < per_xcd;
 }
 
-// LISTED: by entry lists; otherwise (one slice) the codes themselves, in their order.
-template <int D, int SRC, bool LISTED>
+// The records of a slice in the chunks of a range, added into the accumulators. A unit of a wave is its share of one chunk's run;
+// where the runs begin is loaded for 64 units at once, a lane each, and the records of the next step (kStep rows) before those of
+// this one are added.
+template <int D, int SRC>
+__device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* cnt, int e, uint32_t slice, uint32_t slices,
+                                            uint32_t range, uint32_t ranges, uint32_t chunks, uint32_t sharers,
+                                            const ScanPart* __restrict__ parts, const char* __restrict__ records,
+                                            const uint32_t* __restrict__ starts)
+{
+    using S = Slice<D, true>;
+    constexpr uint32_t kChunk = kChunkOf<D, true>;
+    constexpr int n = D < 8 ? D : 8, P = D / n, U = kRecordRows<D>;   // numbers of a lane, lanes of a row, rows of a lane
+    constexpr uint32_t R = 64 / P, kStep = U * R;
+    static_assert(kStep == kRecordStep<D>);
+    typedef uint32_t Words __attribute__((ext_vector_type(n / 2)));
+    const uint32_t lane = threadIdx.x & 63, wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+    const uint32_t piece = lane % P, which = lane / P;
+    unsigned long long* mine = sum + piece * (n * S::kPitch);
+    const uint32_t share = wave % sharers, per_round = ranges * (kWaves / sharers);   // chunks that all waves take in one round
+    uint32_t upto = range + ranges * (wave / sharers);   // chunks above the current one
+    // the runs of the next 64 chunks of this wave, a lane each
+    uint32_t run_begin = 0, run_end = 0, run_kind = 0, left = 64;
+    auto look_ahead = [&]() {
+        const uint64_t mine_done = uint64_t(upto) + uint64_t(per_round) * lane;
+        run_begin = run_end = 0;
+        if (mine_done < chunks) {
+            const uint32_t chunk = chunks - 1 - uint32_t(mine_done);
+            const uint32_t* at = starts + size_t(chunk) * (slices + 1) + slice;
+            run_kind = parts[chunk].kind;
+            run_begin = at[0];
+            run_end = run_kind == kEntries ? run_begin : at[1];
+        }
+    };
+    look_ahead();
+    uint32_t at = 0, end = 0, kind = 0, chunk = 0;   // the next rows of this wave's share: at, at + sharers kStep, ..
+    uint32_t last_at = 0, last_end = 0;
+    auto next = [&]() {   // false: no rows left
+        last_at = at;
+        last_end = end;
+        at += sharers * kStep;
+        while (at >= end) {
+            if (left == 0) {
+                look_ahead();
+                left = 64;
+            }
+            if (upto >= chunks) {   // the rows of before stay the ones to look at
+                at = last_at;
+                end = last_end;
+                return false;
+            }
+            const int l = int(64 - left);
+            chunk = uint32_t(__builtin_amdgcn_readfirstlane(int(chunks - 1 - upto)));
+            at = uint32_t(__builtin_amdgcn_readlane(int(run_begin), l)) + share * kStep;
+            end = uint32_t(__builtin_amdgcn_readlane(int(run_end), l));
+            kind = uint32_t(__builtin_amdgcn_readlane(int(run_kind), l));
+            --left;
+            upto = chunks - upto > per_round ? upto + per_round : chunks;
+        }
+        return true;
+    };
+    struct Step {
+        Words w[U];
+        uint32_t cluster[U], rows, kind;
+    };
+    // Always four (2 U) requests, of the last rows once more where none are left: the counts of the waits then hold on every path.
+    auto load = [&](Step& s, bool more) {
+        const char* base = records + size_t(chunk) * (kChunk * kRecordBytes<D>);
+        s.rows = more ? min(end - at, kStep) : 0u;
+        s.kind = kind;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = min(at + u * R + which, end - 1);
+            s.w[u] = reinterpret_cast<const Words*>(base)[i * P + piece];
+            s.cluster[u] = reinterpret_cast<const uint16_t*>(base + kChunk * (2 * D))[i];
+        }
+    };
+    auto add_kind = [&](const Step& s, auto bf16) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u * R + which >= s.rows) continue;
+#pragma unroll
+            for (int j = 0; j < n; ++j) {
+                const uint32_t w = s.w[u][j / 2];
+                const float x = decltype(bf16)::value ? __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16)
+                                                      : float(__builtin_bit_cast(_Float16, uint16_t(j & 1 ? w >> 16 : w)));
+                atomicAdd(&mine[j * S::kPitch + s.cluster[u]], static_cast<unsigned long long>(fixed_point_finite(x, e)));
+            }
+            if (SRC == 0 && piece == 0) atomicAdd(&cnt[s.cluster[u]], 1u);
+        }
+    };
+    auto add = [&](const Step& s) {
+        if (SRC == 2 || (SRC == 0 && s.kind == kRowsBf16)) add_kind(s, std::true_type{});
+        else add_kind(s, std::false_type{});
+    };
+    end = 0;
+    at = 0u - sharers * kStep;   // next() begins with a step
+    if (!next()) return;
+    Step a, b;
+    load(a, true);
+    for (bool more = true; more;) {
+        more = next();
+        load(b, more);
+        add(a);
+        more = more && next();
+        load(a, more);
+        add(b);
+    }
+}
+
+// LISTED: by entry lists; otherwise (one slice) the codes themselves, in their order. RECORDS: by what record_chunk_kernel left.
+template <int D, int SRC, bool LISTED, bool RECORDS>
 __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void* __restrict__ X, uint32_t N, const void* __restrict__ idx,
                                                                      uint32_t K, uint32_t slices, uint32_t chunks, uint32_t ranges,
                                                                      uint32_t sharers, WsHeader* hdr, const ScanPart* __restrict__ parts,
@@ -328,7 +679,9 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
                                                                      unsigned long long* __restrict__ part_sums,
                                                                      uint32_t* __restrict__ part_counts)
 {
-    using S = Slice<D>;
+    using S = Slice<D, RECORDS>;
+    constexpr uint32_t kChunk = kChunkOf<D, RECORDS>;
+    constexpr bool kCounted = SRC == 0;   // the gradient's sums need no numbers of members
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned long long* sum = reinterpret_cast<unsigned long long*>(smem);              // [D][kPitch]
     uint32_t* cnt = reinterpret_cast<uint32_t*>(smem + S::kSumBytes);                   // [kClusters]
@@ -377,7 +730,11 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
     const int e = fixed_point_exp(absmax, N);
     const bool finite = (flags & 2u) == 0;   // otherwise every number is looked at
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (RECORDS)
+        add_records<D, SRC>(sum, cnt, e, slice, slices, range, ranges, chunks, sharers, parts,
+                            reinterpret_cast<const char*>(entries), starts);
     uint32_t bad = 0;
+    auto add_entries = [&](auto all_finite) {
     constexpr int n = Piece<D, SRC>::kNumbers, P = Piece<D, SRC>::kLanes;
     constexpr int U = SRC == 0 && (D >= 8 || !LISTED) ? 2 : 1;   // rows a lane has under way: what measured better
     const uint32_t piece = lane % P, which = lane / P;   // this lane's part of a row, its row within a batch of 64 / P
@@ -385,22 +742,26 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
     auto add = [&](const float (&x)[n], uint32_t c) {
 #pragma unroll
         for (int j = 0; j < n; ++j) {
-            const long long v = finite ? fixed_point_finite(x[j], e) : fixed_point_term(x[j], e);
+            const long long v = decltype(all_finite)::value ? fixed_point_finite(x[j], e) : fixed_point_term(x[j], e);
             atomicAdd(&mine[j * S::kPitch + c], static_cast<unsigned long long>(v));
         }
-        if (piece == 0) atomicAdd(&cnt[c], 1u);
+        if (kCounted && piece == 0) atomicAdd(&cnt[c], 1u);
     };
     // Range r takes every ranges-th chunk, from the last one down - what the previous kernel read last is still in the
     // memory-side cache - kWaves / sharers of them at a time: the workgroups of all slices of a range then work within a
     // window of X that their L2 holds. The entries of a wave's next batch are requested before the rows of this one, and
     // those before the ones of the last are added.
     uint32_t done = range + ranges * (wave / sharers), first = 0, i0 = 0, end = 0;   // chunks above the current one
+    size_t entries_at = 0;
+    constexpr uint32_t kEntryPitch = RECORDS ? kChunk * kRecordBytes<D> / 4 : kChunk;
     const uint32_t step = ranges * (kWaves / sharers);
     auto open = [&]() {   // first batch at or after `done`
         for (; done < chunks; done += step) {
             const uint32_t chunk = chunks - 1 - done;
+            if (RECORDS && parts[chunk].kind != kEntries) continue;
             const uint32_t* at = starts + size_t(chunk) * (slices + 1) + slice;
             first = chunk * kChunk;
+            entries_at = size_t(chunk) * kEntryPitch;
             end = LISTED ? at[1] : min(kChunk, N - first);
             i0 = (LISTED ? at[0] : 0u) + wave % sharers * (U * 64 / P);
             if (i0 < end) return;
@@ -410,7 +771,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t i = min(i0 + u * (64 / P) + which, end - 1);
-            ent[u] = LISTED ? entries[size_t(first) + i] : (min(code_at<SRC>(idx, size_t(first) + i), K) << kPosBits) | i;
+            ent[u] = LISTED ? entries[entries_at + i] : (min(code_at<SRC>(idx, size_t(first) + i), K) << kPosBits) | i;
         }
     };
     float pending[U][n];
@@ -458,6 +819,11 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
         }
     }
     commit();
+    };
+    if constexpr (!RECORDS || SRC == 0) {
+        if (finite) add_entries(std::true_type{});   // a branch per number otherwise
+        else add_entries(std::false_type{});
+    }
     if (bad && parts == nullptr) atomicAdd(&hdr->skipped_vectors, static_cast<unsigned long long>(bad));
     __syncthreads();
     const size_t job = size_t(slice) * ranges + range;
@@ -466,21 +832,22 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
 #pragma unroll
     for (int j = 0; j < D; ++j)
         for (uint32_t t = threadIdx.x; t < k_n; t += kThreads) ps[j * S::kPitch + t] = sum[j * S::kPitch + t];
-    for (uint32_t t = threadIdx.x; t < k_n; t += kThreads) pc[t] = cnt[t];
+    if (kCounted)
+        for (uint32_t t = threadIdx.x; t < k_n; t += kThreads) pc[t] = cnt[t];
 }
 
 // Adds the ranges of every cluster (integers: any order gives the same bits; this one is fixed anyway), leaves the
 // totals in the workspace and writes the means (or, mean = 0, the plain sums). An empty cluster keeps prev. A workgroup
 // finishes 64 neighbouring clusters of one component, its waves take turns at the ranges (one thread per cluster and
 // component waited 75 us for 256 ranges at K = 1024).
-template <int D, int W>
+template <int D, int W, bool RECORDS>
 __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned long long* __restrict__ part_sums,
                                                                    const uint32_t* __restrict__ part_counts, uint32_t ranges,
                                                                    const float* prev, float* out, uint32_t* counts_out, uint32_t K,
                                                                    uint32_t N, WsHeader* hdr, int mean, long long* __restrict__ sums_ws,
-                                                                   uint32_t* __restrict__ counts_ws)
+                                                                   uint32_t* __restrict__ counts_ws, uint32_t width)
 {
-    using S = Slice<D>;
+    using S = Slice<D, RECORDS>;
     __shared__ long long red_sum[W][64];
     __shared__ uint32_t red_count[W][64];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, groups = (K + 63) / 64;
@@ -495,7 +862,7 @@ __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned 
         for (uint32_t r = wave; r < ranges; r += W) {
             const size_t job = size_t(slice) * ranges + r;
             isum += static_cast<long long>(part_sums[job * (S::kPitch * D) + j * S::kPitch + local]);
-            n += part_counts[job * S::kClusters + local];
+            if (part_counts != nullptr) n += part_counts[job * S::kClusters + local];
         }
     }
     red_sum[wave][lane] = isum;
@@ -507,9 +874,9 @@ __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned 
         isum += red_sum[v][lane];
         n += red_count[v][lane];
     }
-    const size_t o = size_t(k) * D + j;
-    sums_ws[o] = isum;
-    if (j == 0) {
+    sums_ws[size_t(k) * D + j] = isum;
+    const size_t o = size_t(k) * width + j;
+    if (j == 0 && part_counts != nullptr) {
         counts_ws[k] = n;
         if (counts_out != nullptr) counts_out[k] = n;
     }
@@ -517,46 +884,70 @@ __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned 
     out[o] = !mean ? float(total) : (n > 0 ? float(total / double(n)) : prev[o]);
 }
 
-template <int D, int SRC, bool LISTED>
-hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, const float* prev, uint32_t K, float* out,
-                    uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, hipStream_t s)
+// Whether the rows go along (the head of this file says what it gives): there has to be room for as many ranges, or for the 8 that
+// one per XCD takes.
+template <int D, int SRC>
+bool records_pay(uint32_t N, uint32_t K, bool fresh)
 {
-    using S = Slice<D>;
+    if (!fresh || update_one_slice(D, K)) return false;
+    return cut_of<D, true>(N, K).ranges >= std::min(cut_of<D>(N, K).ranges, 8u);
+}
+
+template <int D, int SRC, bool LISTED, bool RECORDS>
+hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, const float* prev, uint32_t K, float* out,
+                    uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, const RowPlace& place, hipStream_t s)
+{
+    using S = Slice<D, RECORDS>;
     const uint32_t jobs = c.slices * c.ranges;
     unsigned long long* part_sums = reinterpret_cast<unsigned long long*>(w.records);
-    uint32_t* part_counts = reinterpret_cast<uint32_t*>(w.records + size_t(jobs) * S::kSumBytes);
+    uint32_t* part_counts = SRC == 0 ? reinterpret_cast<uint32_t*>(w.records + size_t(jobs) * S::kSumBytes) : nullptr;
     ScanPart* parts = reinterpret_cast<ScanPart*>(w.records + c.sum_bytes);
     uint32_t* entries = reinterpret_cast<uint32_t*>(w.records + c.sum_bytes + c.part_bytes);
     uint32_t* starts = reinterpret_cast<uint32_t*>(w.records + c.sum_bytes + c.part_bytes + c.entry_bytes);
     // per call: the attribute belongs to the current device
-    if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sliced_accumulate_kernel<D, SRC, LISTED>),
+    if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sliced_accumulate_kernel<D, SRC, LISTED, RECORDS>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(S::kLdsBytes)); e != hipSuccess)
         return e;
-    if (fresh)
+    if constexpr (RECORDS) {
+        const dim3 threads(kChunkThreadsOf<D, true>);
+        char* records = reinterpret_cast<char*>(entries);
+        if constexpr (SRC != 0) {
+            if (place.per_row != 0)
+                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, false>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+            else
+                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+        } else {
+            hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+        }
+    } else if (fresh)
         hipLaunchKernelGGL((slice_chunk_kernel<D, SRC, true, LISTED>), dim3(c.chunks), dim3(kChunkThreads), 0, s, X, idx, N, K, c.slices, w.hdr,
                            parts, entries, starts);
     else if constexpr (LISTED && SRC == 0)
         hipLaunchKernelGGL((slice_chunk_kernel<D, SRC, false, true>), dim3(c.chunks), dim3(kChunkThreads), 0, s, X, idx, N, K, c.slices, w.hdr,
                            parts, entries, starts);
-    hipLaunchKernelGGL((sliced_accumulate_kernel<D, SRC, LISTED>), dim3(8 * ((jobs + 7) / 8)), dim3(kThreads), S::kLdsBytes, s, X, N, idx,
+    hipLaunchKernelGGL((sliced_accumulate_kernel<D, SRC, LISTED, RECORDS>), dim3(8 * ((jobs + 7) / 8)), dim3(kThreads), S::kLdsBytes, s, X, N, idx,
                        K, c.slices, c.chunks, c.ranges, c.sharers, w.hdr, fresh ? parts : nullptr, entries, starts, part_sums, part_counts);
-    const dim3 done((K + 63) / 64 * D);
+    const uint32_t width = place.per_row != 0 ? place.g : D;   // of a row of the result
+    const dim3 done((K + 63) / 64 * width);
     if (c.ranges > 32)
-        hipLaunchKernelGGL((sliced_finalize_kernel<D, 16>), done, dim3(1024), 0, s, part_sums, part_counts, c.ranges, prev, out,
-                           counts_out, K, N, w.hdr, mean ? 1 : 0, w.sums, w.counts);
+        hipLaunchKernelGGL((sliced_finalize_kernel<D, 16, RECORDS>), done, dim3(1024), 0, s, part_sums, part_counts, c.ranges, prev, out,
+                           counts_out, K, N, w.hdr, mean ? 1 : 0, w.sums, w.counts, width);
     else
-        hipLaunchKernelGGL((sliced_finalize_kernel<D, 4>), done, dim3(256), 0, s, part_sums, part_counts, c.ranges, prev, out,
-                           counts_out, K, N, w.hdr, mean ? 1 : 0, w.sums, w.counts);
+        hipLaunchKernelGGL((sliced_finalize_kernel<D, 4, RECORDS>), done, dim3(256), 0, s, part_sums, part_counts, c.ranges, prev, out,
+                           counts_out, K, N, w.hdr, mean ? 1 : 0, w.sums, w.counts, width);
     return hipGetLastError();
 }
 
 template <int D, int SRC>
 hipError_t update_sliced_t(const void* X, uint32_t N, const void* idx, const float* prev, uint32_t K, float* out,
-                           uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, hipStream_t s)
+                           uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, hipStream_t s, const RowPlace& place = RowPlace{})
 {
     const Cut c = cut_of<D>(N, K);
-    return c.listed ? launch_t<D, SRC, true>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, s)
-                    : launch_t<D, SRC, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, s);
+    if constexpr (SRC != 0 || D == 4)
+        if (place.per_row != 0 || records_pay<D, SRC>(N, K, fresh))
+            return launch_t<D, SRC, true, true>(cut_of<D, true>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+    if (c.listed) return launch_t<D, SRC, true, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+    return launch_t<D, SRC, false, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
 }
 
 }  // namespace
@@ -583,21 +974,35 @@ hipError_t launch_update_sliced(const float* X, uint32_t N, uint32_t d, const ui
     }
 }
 
-// The sums (not the means) of 16-bit rows by 16-bit code, read in place: rows [N * d] fp16 (dtype 1) or bf16 (2),
-// 16-byte aligned; codes [N], 4-byte aligned. Leaves the header as a reset and a
-// scan of the rows would. Same fixed-point sums as launch_update on the converted rows: same bits.
-hipError_t launch_sum_rows16_sliced(const void* rows, int dtype, uint32_t N, uint32_t d, const uint16_t* codes, uint32_t K,
-                                    float* out, const Workspace& w, hipStream_t s)
+// The sums (not the means) of the sub-vectors of a layer's 16-bit gradient (dtype 1 = fp16, 2 = bf16) by their 16-bit codes, read in
+// place. Leaves the header as a reset and a scan of the rows would. Same fixed-point sums as launch_update on the converted rows:
+// same bits. Rows at aligned places are loaded as they are; others (g other than 4, 8, 16, a padded last one, a gradient that does not
+// begin at 16 bytes) number by number: 92 of 143 us at 4096 x 11008, g = 6.
+template <int D>
+hipError_t sum_rows16_t(const void* grad, int dtype, uint32_t N, uint32_t out_features, uint32_t g, const uint16_t* codes, uint32_t K, float* out,
+                        const Workspace& w, hipStream_t s)
 {
-    if (!update_sliced_applies(N, d, K, w) || (dtype != 1 && dtype != 2)) return hipErrorInvalidValue;
-    const bool bf = dtype == 2;
-    switch (d) {
-        case 4: return bf ? update_sliced_t<4, 2>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s)
-                          : update_sliced_t<4, 1>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s);
-        case 8: return bf ? update_sliced_t<8, 2>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s)
-                          : update_sliced_t<8, 1>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s);
-        case 16: return bf ? update_sliced_t<16, 2>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s)
-                           : update_sliced_t<16, 1>(rows, N, codes, nullptr, K, out, nullptr, w, false, true, s);
+    const uint32_t per_row = (out_features + g - 1) / g;
+    const bool whole = g == D && out_features % g == 0 && reinterpret_cast<uintptr_t>(grad) % 16 == 0;
+    const RowPlace place = whole ? RowPlace{0, 0, 0} : RowPlace{per_row, g, per_row * g - out_features};
+    return dtype == 2 ? update_sliced_t<D, 2>(grad, N, codes, nullptr, K, out, nullptr, w, false, true, s, place)
+                      : update_sliced_t<D, 1>(grad, N, codes, nullptr, K, out, nullptr, w, false, true, s, place);
+}
+
+bool sum_rows16_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w)
+{
+    if (!update_sliced_applies(N, d, K, w)) return false;
+    return (d == 4 ? cut_of<4, true>(N, K).ranges : (d == 8 ? cut_of<8, true>(N, K).ranges : cut_of<16, true>(N, K).ranges)) > 0;
+}
+
+hipError_t launch_sum_rows16(const void* grad, int dtype, uint32_t N, uint32_t out_features, uint32_t g, const uint16_t* codes, uint32_t K,
+                             float* out, const Workspace& w, hipStream_t s)
+{
+    if (!sum_rows16_applies(N, w.d, K, w) || (dtype != 1 && dtype != 2)) return hipErrorInvalidValue;
+    switch (w.d) {
+        case 4: return sum_rows16_t<4>(grad, dtype, N, out_features, g, codes, K, out, w, s);
+        case 8: return sum_rows16_t<8>(grad, dtype, N, out_features, g, codes, K, out, w, s);
+        case 16: return sum_rows16_t<16>(grad, dtype, N, out_features, g, codes, K, out, w, s);
         default: return hipErrorInvalidValue;
     }
 }
