@@ -401,16 +401,17 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
         constexpr int kAtOnce = D == 4 ? U : 4;   // rows in registers as they are
 #pragma unroll
         for (int u0 = 0; u0 < U; u0 += kAtOnce) {
-            uint4 t[kAtOnce][D / 4];
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            u32x4 t[kAtOnce][D / 4];
 #pragma unroll
             for (int v = 0; v < kAtOnce && u0 + v < U; ++v)
 #pragma unroll
-                for (int q = 0; q < D / 4; ++q) t[v][q] = static_cast<const uint4*>(X)[row_at(u0 + v) * (D / 4) + q];
+                for (int q = 0; q < D / 4; ++q) t[v][q] = __builtin_nontemporal_load(static_cast<const u32x4*>(X) + row_at(u0 + v) * (D / 4) + q);
 #pragma unroll
             for (int v = 0; v < kAtOnce && u0 + v < U; ++v) {
 #pragma unroll
                 for (int q = 0; q < D / 4; ++q) {
-                    const uint32_t w[4] = {t[v][q].x, t[v][q].y, t[v][q].z, t[v][q].w};
+                    const u32x4 w = t[v][q];
                     uint16_t h[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -542,7 +543,7 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     }
     __syncthreads();
     for (uint32_t t = threadIdx.x; t < members * kPieces; t += T)
-        reinterpret_cast<Words*>(out)[t] = reinterpret_cast<const Words*>(sorted)[t];
+        __builtin_nontemporal_store(reinterpret_cast<const Words*>(sorted)[t], reinterpret_cast<Words*>(out) + t);   // 112 MB, 20 M vectors 190 -> 179 us
     for (uint32_t t = threadIdx.x; t < (members + 1) / 2; t += T)   // the last one may bring a number that nobody reads
         reinterpret_cast<uint32_t*>(out + kChunk * (2 * D))[t] = reinterpret_cast<const uint32_t*>(clusters)[t];
 }
