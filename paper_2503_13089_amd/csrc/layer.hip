@@ -1,6 +1,8 @@
 // Data movement of the compressed linear layer (Section 3.1 footnote, Section 3.2, the paper's layer
 // listing): the reshape that produces the vectors to cluster, the 16-bit storage formats, and the
 // reconstruction of the weight from (codebook, codes) with the padding columns cut off.
+#include <type_traits>
+
 #include "common.h"
 
 namespace cc {
@@ -189,6 +191,104 @@ __global__ __launch_bounds__(kThreads) void layer_weight_vec_kernel(const u32x4*
     __builtin_nontemporal_store(codebook[k], &weight[v]);
 }
 
+// g = 4, no padding, 16-bit elements, by parts of the codebook. What bounds the general kernel is a line from L2 per code. Here a
+// workgroup (16 waves, one per compute unit) holds up to 44 codes and their rows per thread in registers; the parts of the codebook pass
+// through its LDS one after the other, every thread picks the rows that are there, and whole rows leave at the end, past the caches (plain
+// stores of more than the memory-side cache holds run at 2 TB/s). Bound: the parts' way into LDS (512 KB a workgroup and round at K = 65536) and
+// the lookups, 10 us of 35 each at 4096 x 11008, then the stores.
+// Tried: a workgroup per part that stores the 8 bytes of each of its codes (L2 puts the lines together): 47 us there, as the general kernel.
+constexpr int kPartThreads = 1024;
+constexpr uint32_t kPartRows = 160 * 1024 / 8 - 16;
+constexpr int kLeastPairs = 4, kMostPairs = 19;   // of codes of a thread: 76 registers of rows, 19 of codes; at 22 it spills, and one round for two gains nothing
+typedef uint32_t u32_2 __attribute__((aligned(2)));
+
+template <int PAIRS>
+__global__ __launch_bounds__(kPartThreads, 4) void layer_weight_parts_kernel(const u32x4* __restrict__ codebook, uint32_t K, const uint16_t* __restrict__ codes,
+                                                                          uint64_t num_codes, u32x4* __restrict__ weight, uint32_t parts,
+                                                                          uint32_t part_rows, uint64_t per_share)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u32x2* table = reinterpret_cast<const u32x2*>(smem);
+    const uint32_t lane = threadIdx.x & 63, wave = uint32_t(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+    const uint64_t begin = blockIdx.x * per_share, end = min(begin + per_share, num_codes);   // per_share and num_codes are even
+    const u16x2 last = {uint16_t(K - 1), uint16_t(K - 1)};
+    constexpr uint64_t round = PAIRS * 2 * kPartThreads;
+    for (uint64_t at = begin; at < end; at += round) {
+        const uint32_t n = uint32_t(min(end - at, uint64_t(round)));
+        uint32_t code[PAIRS];
+        u32x4 row[PAIRS];
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            const uint32_t i = min(2 * (q * kPartThreads + threadIdx.x), n - 2);   // past the end the last pair again
+            const uint32_t pair = *reinterpret_cast<const u32_2*>(codes + at + i);
+            code[q] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, pair), last));   // never outside the codebook
+        }
+        for (uint32_t part = 0; part < parts; ++part) {
+            const uint32_t low = part * part_rows, rows = min(part_rows, K - low);   // part_rows is even
+            // into LDS, each workgroup from another place on; a row of zeros behind
+            const u32x4* from = codebook + low / 2;
+            const uint32_t pieces = rows / 2, chunks = (pieces + 63) / 64, turn = (blockIdx.x / 8 * 7u + blockIdx.x) % chunks;   // of 1 KB
+            if (part > 0 || at > begin) __syncthreads();
+            for (uint32_t i = wave; i < chunks; i += kPartThreads / 64) {
+                uint32_t chunk = i + turn;
+                chunk = chunk >= chunks ? chunk - chunks : chunk;
+                if (chunk * 64 + lane < pieces)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(from + chunk * 64 + lane),
+                                                     (__attribute__((address_space(3))) void*)(smem + chunk * 1024), 16, 0, 0);
+            }
+            if (threadIdx.x == 0) {
+                if (rows % 2 != 0) reinterpret_cast<u32x2*>(smem)[rows - 1] = reinterpret_cast<const u32x2*>(from)[rows - 1];
+                reinterpret_cast<u32x2*>(smem)[rows] = u32x2{0u, 0u};
+            }
+            __syncthreads();
+            auto look = [&](auto first) {
+#pragma unroll
+                for (int q = 0; q < PAIRS; ++q) {
+                    asm volatile("" : "+v"(code[q]));   // its halves are not kept over the parts: registers
+                    const u32x2 x = table[min((code[q] & 0xffffu) - low, rows)], y = table[min((code[q] >> 16) - low, rows)];
+                    const u32x4 here = {x[0], x[1], y[0], y[1]};
+                    row[q] = decltype(first)::value ? here : row[q] | here;
+                    if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // few reads at a time: registers
+                }
+            };
+            if (part == 0) look(std::true_type{});
+            else look(std::false_type{});
+        }
+        uint32_t thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));   // nor are the places of the loads
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            const uint32_t i = q * kPartThreads + thread;
+            if (2 * i < n) __builtin_nontemporal_store(row[q], weight + at / 2 + i);
+        }
+    }
+}
+
+template <int PAIRS>
+hipError_t launch_weight_parts(int pairs, uint32_t shares, const u32x4* codebook, uint32_t K, const uint16_t* codes, uint64_t num_codes, u32x4* weight,
+                               uint32_t parts, uint32_t part_rows, uint64_t per_share, hipStream_t s)
+{
+    if constexpr (PAIRS <= kMostPairs) {
+        if (pairs > PAIRS) return launch_weight_parts<PAIRS + 1>(pairs, shares, codebook, K, codes, num_codes, weight, parts, part_rows, per_share, s);
+        if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_weight_parts_kernel<PAIRS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(kPartRows + 16) * 8);
+            e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(layer_weight_parts_kernel<PAIRS>, dim3(shares), dim3(kPartThreads), size_t(part_rows + 1) * 8, s, codebook, K, codes, num_codes,
+                           weight, parts, part_rows, per_share);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
+// us, general kernel / by parts, 16-bit, g = 4. K = 65536 (4 parts): 1024 x 8192 11.1 / 11.4, 2048 x 11008 25.8 / 19.4, 4096 x 11008 47 / 35, 8192 x 14336
+// 117 / 72. K = 50000 (3): 10.5 / 9.2, 25 / 17, 47 / 30, 116 / 64. K = 20000 (1): 1024 x 4096 6.1 / 6.4, 1024 x 8192 9.7 / 6.4, 4096 x 11008 42 / 20; K = 4096
+// 25.5 / 20, and where the general kernel's rows lie in L1, 21 / 20 at K = 2000 and 6.7 / 6.9 for 1024 x 8192.
+bool weight_parts_pay(uint32_t K, uint64_t num_codes) { return K >= 4096 && num_codes >= (K > 3 * kPartRows ? 3u << 20 : 1u << 21); }
+
 template <int G>
 hipError_t launch_weight(uint32_t units, const void* codebook, uint32_t K, const uint16_t* codes, uint64_t num_codes, uint32_t per_row, uint32_t padding,
                          void* weight, hipStream_t s)
@@ -217,6 +317,16 @@ hipError_t launch_layer_weight(const void* codebook, int dtype, uint32_t K, uint
         hipLaunchKernelGGL(layer_weight_vec_kernel, grid, dim3(kThreads), 0, s, static_cast<const u32x4*>(codebook), K, codes, num_codes,
                            static_cast<u32x4*>(weight));
         return hipGetLastError();
+    }
+    if (dtype != 0 && whole && g == 4 && num_codes % 2 == 0 && weight_parts_pay(K, num_codes)) {
+        const uint32_t parts = (K + kPartRows - 1) / kPartRows, part_rows = ((K + parts - 1) / parts + 1) & ~1u;
+        const uint64_t per_share = (num_codes + 511) / 512 * 2;
+        const uint32_t shares = uint32_t((num_codes + per_share - 1) / per_share);
+        constexpr uint64_t kUnit = 2 * kPartThreads;
+        const uint64_t rounds = (per_share + kMostPairs * kUnit - 1) / (kMostPairs * kUnit);   // of equal length
+        const int pairs = int((per_share + rounds * kUnit - 1) / (rounds * kUnit));
+        return launch_weight_parts<kLeastPairs>(pairs, shares, static_cast<const u32x4*>(codebook), K, codes, num_codes, static_cast<u32x4*>(weight), parts,
+                                                part_rows, per_share, s);
     }
     const uint32_t unit = dtype == 0 ? 2 : 1;
     return launch_weight<1>(g * unit, codebook, K, codes, num_codes, per_row, (per_row * g - out_features) * unit, weight, s);
