@@ -256,10 +256,10 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
             cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
             if (by_buckets && !sums_follow && cc::update_sliced_applies(N, d, K, w))
                 CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, false, s), "update (slices)");
+            else if (by_buckets && sums_follow && cc::update_delta_applies(N, d, K, w))
+                CC_TRY_HIP(cc::launch_update_delta(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, s), "update (changes)");
             else if (by_buckets)
-                CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, true, s,
-                                                     sums_follow ? w.idx_prev : nullptr, sums_follow ? w.changed : nullptr),
-                           "update (buckets)");
+                CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, true, s), "update (buckets)");
             else
                 CC_TRY_HIP(cc::launch_finalize(C, C, counts, K, d, N, w, true, s), "update (means)");
         }
@@ -335,8 +335,7 @@ int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32
     }
     if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1 && !from_first ? cc::kRadiiStay : cc::kRadiiFollow, true, !regroup_at(t, from_first), s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
-    CC_TRY_HIP(cc::launch_update_buckets(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, true, true, s, w.idx_prev, w.changed, true),
-               "update (buckets)");
+    CC_TRY_HIP(cc::launch_update_delta(w.xsorted, N, d, w.idx_sorted, C, K, C, nullptr, w, s), "update (changes)");
     return CC_OK;
 }
 

@@ -386,14 +386,16 @@ hipError_t launch_accumulate(const float* X, uint32_t N, uint32_t d, const uint3
 // not NULL) in one go. Codes >= K are skipped and counted in WsHeader::skipped_vectors. norm_order = true
 // buckets the clusters by their position in the norm order left by launch_sort_centroids (w.cinv, w.cperm).
 // mean = false writes the plain sums (0 for an empty cluster) instead of the means. The integer sums and the
-// counts are left in w.sums / w.counts. prev_idx != NULL: those already hold the sums and counts of the codes
-// prev_idx; only the vectors whose code differs are moved (bit-identical to a recomputation from idx). That needs
-// `changed` too, one bit per vector: prev_idx is only read, and only needs to be valid, where the bit is set, and a
-// vector whose bit is clear must have kept its code. by_cluster: neighbouring vectors are mostly of one cluster.
+// counts are left in w.sums / w.counts.
 hipError_t launch_update_buckets(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev,
                                  uint32_t K, float* out, uint32_t* counts_out, const Workspace& w, bool norm_order,
-                                 bool mean, hipStream_t s, const uint32_t* prev_idx = nullptr,
-                                 const uint32_t* changed = nullptr, bool by_cluster = false);
+                                 bool mean, hipStream_t s);
+// Incremental M-step (update_delta.hip): w.sums and w.counts hold the sums and counts of the codes w.idx_prev; only the vectors whose code
+// differs are moved (bit-identical to a recomputation from idx). w.changed has one bit per vector: w.idx_prev is only read, and only
+// needs to be valid, where the bit is set, and a vector whose bit is clear must have kept its code. Needs update_delta_applies.
+bool update_delta_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
+hipError_t launch_update_delta(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev, uint32_t K, float* out,
+                               uint32_t* counts_out, const Workspace& w, hipStream_t s);
 // M-step by cluster slices (update_sliced.hip): each chunk's codes sorted by slice, then one LDS accumulation per slice of the
 // clusters, no copy of the vectors; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
 // result bits as the other formulations. `out` may alias `prev`.

@@ -13,13 +13,7 @@
 // records land inside a bucket - the only thing here that depends on scheduling - cannot change a bit
 // of the result.
 //
-// Because the sums are integers they can also be kept up to date instead of recomputed: inside a fit, from
-// the third iteration on (the second of a fit by cells), only the vectors whose code changed since the previous
-// iteration go through the four steps (18 % of them in the second iteration of the 4-bit benchmark, 2 % in the
-// twentieth), each as two records - plus for the new cluster, minus for the old one - and step 4 adds the bucket's
-// net change to the sums and counts that the previous iteration left in the workspace. Bit-identical to a recomputation.
-// The E-step kernel that produced the codes leaves a bitmap of the vectors that may have changed (and their
-// previous code), so steps 1 and 3 read one bit per vector instead of two code arrays.
+// Inside a fit the later iterations move only the vectors whose code changed (update_delta.hip).
 #include <algorithm>
 
 #include "common.h"
@@ -57,30 +51,6 @@ __device__ __forceinline__ uint32_t slot_of_code(uint32_t k, const uint32_t* __r
     return cinv != nullptr ? cinv[k] : k;
 }
 
-// Calls f(i) for every flagged vector of the chunk of kDeltaChunk vectors starting at lo (bits beyond N are never
-// set). Each thread reads the 64 flags of its own stretch (two words of the `changed` bitmap), the flagged offsets
-// are packed into `list` (LDS, kDeltaChunk entries) and then dealt out evenly: with a few per cent of the flags set,
-// a thread working through its own stretch alone would wait for the unluckiest lane of its wave.
-template <typename F>
-__device__ __forceinline__ void for_each_flagged(const uint32_t* __restrict__ changed, uint32_t lo, uint32_t N,
-                                                 uint16_t* list, uint32_t* wave_sum, F f)
-{
-    static_assert(kDeltaChunk == 64 * kThreads && kDeltaChunk <= 65536, "two bitmap words per thread, 16-bit offsets");
-    const uint32_t first = lo + 64 * threadIdx.x;
-    uint32_t word[2] = {0u, 0u};
-#pragma unroll
-    for (uint32_t w = 0; w < 2; ++w)
-        if (first + 32 * w < N) word[w] = changed[(first >> 5) + w];
-    uint32_t total;
-    uint32_t pos = block_exclusive_scan(uint32_t(__popc(word[0]) + __popc(word[1])), wave_sum, total);
-#pragma unroll
-    for (uint32_t w = 0; w < 2; ++w)
-        for (uint32_t bits = word[w]; bits != 0; bits &= bits - 1)
-            list[pos++] = uint16_t(64 * threadIdx.x + 32 * w + uint32_t(__ffs(int(bits)) - 1));
-    __syncthreads();
-    for (uint32_t e = threadIdx.x; e < total; e += kThreads) f(lo + list[e]);
-}
-
 // Which chunk of vectors a workgroup takes. Workgroups are dealt to the 8 XCDs in turn, and the records of
 // neighbouring chunks are neighbours in every bucket's range: with chunk = workgroup id, each cache line on the
 // border of two runs would be written in part by two XCDs, i.e. from two L2s that cannot merge the halves.
@@ -93,35 +63,19 @@ __device__ __forceinline__ uint32_t chunk_of_workgroup()
 }
 
 // ---- 1. bucket histogram of one block of vectors: row `block` of hist[blocks][nbuckets]
-__global__ __launch_bounds__(kThreads) void bucket_count_kernel(const uint32_t* __restrict__ idx,
-                                                                const uint32_t* __restrict__ prev,
-                                                                const uint32_t* __restrict__ changed, uint32_t N, uint32_t K,
+__global__ __launch_bounds__(kThreads) void bucket_count_kernel(const uint32_t* __restrict__ idx, uint32_t N, uint32_t K,
                                                                 const uint32_t* __restrict__ cinv, uint32_t nbuckets,
                                                                 uint32_t* __restrict__ hist, WsHeader* hdr)
 {
     __shared__ uint32_t h[kMaxBuckets];
     __shared__ uint32_t bad_total;
-    __shared__ uint16_t flagged[kDeltaChunk];
-    __shared__ uint32_t wave_sum[kThreads / 64];
     for (uint32_t b = threadIdx.x; b < nbuckets; b += kThreads) h[b] = 0;
     if (threadIdx.x == 0) bad_total = 0;
     __syncthreads();
-    // a full pass works on chunks of kBucketChunk vectors; an incremental one (changed != NULL) on chunks of
-    // kDeltaChunk, looks only at the flagged vectors, and counts one record for the new cluster and one for the old
-    const uint32_t chunk = changed != nullptr ? kDeltaChunk : kBucketChunk;
     const uint32_t blk = chunk_of_workgroup();
-    const uint32_t lo = blk * chunk, hi = min(lo + chunk, N);
+    const uint32_t lo = blk * kBucketChunk, hi = min(lo + kBucketChunk, N);
     uint32_t bad = 0;
-    if (changed != nullptr) {
-        for_each_flagged(changed, lo, N, flagged, wave_sum, [&](uint32_t i) {
-            const uint32_t k = idx[i], kp = prev[i];
-            if (k != kp && k < K && kp < K) {
-                atomicAdd(&h[slot_of_code(k, cinv) / kBucketClusters], 1u);
-                atomicAdd(&h[slot_of_code(kp, cinv) / kBucketClusters], 1u);
-            }
-        });
-    }
-    for (uint32_t i = lo + threadIdx.x; changed == nullptr && i < hi; i += kThreads) {
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += kThreads) {
         const uint32_t k = idx[i];
         if (k < K) atomicAdd(&h[slot_of_code(k, cinv) / kBucketClusters], 1u);
         else ++bad;
@@ -281,57 +235,15 @@ __global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(const float* _
     }
 }
 
-// ---- 3'. the changed vectors only: two records each (third trailer word: 0 = add to the new cluster, 1 = take
-// from the old one). Few records, so each lane writes its own straight to where its bucket's cursor points.
-template <int D>
-__global__ __launch_bounds__(kThreads) void bucket_scatter_delta_kernel(const float* __restrict__ X, uint32_t N,
-                                                                        const uint32_t* __restrict__ idx,
-                                                                        const uint32_t* __restrict__ prev,
-                                                                        const uint32_t* __restrict__ changed, uint32_t K,
-                                                                        const uint32_t* __restrict__ cinv,
-                                                                        uint32_t nbuckets,
-                                                                        const uint32_t* __restrict__ hist,
-                                                                        const uint32_t* __restrict__ gtot,
-                                                                        const uint32_t* __restrict__ base,
-                                                                        char* __restrict__ records)
-{
-    __shared__ uint32_t cursor[kMaxBuckets];  // next free record of (bucket, this block)
-    __shared__ uint16_t flagged[kDeltaChunk];
-    __shared__ uint32_t wave_sum[kThreads / 64];
-    const uint32_t blk = chunk_of_workgroup();
-    for (uint32_t b = threadIdx.x; b < nbuckets; b += kThreads)
-        cursor[b] = base[b] + gtot[size_t(blk / kBucketGroup) * nbuckets + b] + hist[size_t(blk) * nbuckets + b];
-    __syncthreads();
-    const uint32_t lo = blk * kDeltaChunk;
-    for_each_flagged(changed, lo, N, flagged, wave_sum, [&](uint32_t i) {
-        const uint32_t k_new = idx[i], k_old = prev[i];
-        if (k_new == k_old || k_new >= K || k_old >= K) return;
-        float4 row[D / 4];
-#pragma unroll
-        for (int q = 0; q < D / 4; ++q) row[q] = reinterpret_cast<const float4*>(X + size_t(i) * D)[q];
-#pragma unroll
-        for (uint32_t minus = 0; minus < 2; ++minus) {  // a record for the new cluster, one for the old
-            const uint32_t slot = slot_of_code(minus ? k_old : k_new, cinv);
-            const uint32_t pos = atomicAdd(&cursor[slot / kBucketClusters], 1u);
-            char* rec = records + size_t(pos) * Record<D>::kBytes;
-#pragma unroll
-            for (int q = 0; q < D / 4; ++q) reinterpret_cast<float4*>(rec)[q] = row[q];
-            *reinterpret_cast<uint4*>(rec + D * 4) = make_uint4(slot, i, minus, 0u);
-        }
-    });
-}
-
 // ---- 4. one workgroup per bucket: sums in LDS (component-major, so that the clusters of a bucket spread over
-// all banks), then the means. An incremental pass over few buckets shares each among gridDim.y workgroups, which add
-// their net change to the running totals; the means are then a launch of their own. (17 buckets of 10.6 M vectors
-// of 4, K = 1067: the sums 34 us a pass; with one workgroup per bucket the whole fit of 10 iterations took 12.2 ms, now 9.0.)
+// all banks), then the means.
 template <int D>
 __global__ __launch_bounds__(kThreads) void bucket_sum_kernel(const char* __restrict__ records,
                                                               const uint32_t* __restrict__ base, uint32_t N, uint32_t K,
                                                               const uint32_t* __restrict__ cperm, const float* prev,
                                                               float* out, uint32_t* counts_out, WsHeader* hdr, int mean,
                                                               long long* __restrict__ sums_ws,
-                                                              uint32_t* __restrict__ counts_ws, int delta, int by_cluster)
+                                                              uint32_t* __restrict__ counts_ws)
 {
     __shared__ unsigned long long sum[D][kBucketClusters];
     __shared__ uint32_t cnt[kBucketClusters];
@@ -340,57 +252,29 @@ __global__ __launch_bounds__(kThreads) void bucket_sum_kernel(const char* __rest
     __syncthreads();
     const int e = fixed_point_exp(hdr->absmax_bits, N);
     const uint32_t p0 = blockIdx.x * kBucketClusters;
-    const uint32_t share = (base[blockIdx.x + 1] - base[blockIdx.x] + gridDim.y - 1) / gridDim.y;
-    const uint32_t first = min(base[blockIdx.x] + blockIdx.y * share, base[blockIdx.x + 1]), last = min(first + share, base[blockIdx.x + 1]);
-    // Records are dealt out in turn. Where the vectors lie ordered by cluster (a fit by cells) neighbours would add to one
-    // accumulator, so every thread takes a stretch.
-    const uint32_t per = by_cluster ? (last - first + kThreads - 1) / kThreads : 0u;
-    const uint32_t begin = by_cluster ? first + min(threadIdx.x * per, last - first) : first + threadIdx.x;
-    const uint32_t end = by_cluster ? min(begin + per, last) : last, stride = by_cluster ? 1u : uint32_t(kThreads);
-    for (uint32_t p = begin; p < end; p += stride) {
+    for (uint32_t p = base[blockIdx.x] + threadIdx.x; p < base[blockIdx.x + 1]; p += kThreads) {
         const char* rec = records + size_t(p) * Record<D>::kBytes;
-        const uint2 tag = *reinterpret_cast<const uint2*>(rec + D * 4);
-        const uint32_t local = (tag.x - p0) & (kBucketClusters - 1);
-        const uint32_t minus = *reinterpret_cast<const uint32_t*>(rec + D * 4 + 8);  // 1: a vector that left the cluster
+        const uint32_t local = (*reinterpret_cast<const uint32_t*>(rec + D * 4) - p0) & (kBucketClusters - 1);
         float x[D];
         load_row<D>(reinterpret_cast<const float*>(rec), x);
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const long long v = fixed_point_term(x[j], e);
-            atomicAdd(&sum[j][local], static_cast<unsigned long long>(minus ? -v : v));  // two's complement: wraps like int64
-        }
-        atomicAdd(&cnt[local], minus ? 0xffffffffu : 1u);
+        for (int j = 0; j < D; ++j) atomicAdd(&sum[j][local], static_cast<unsigned long long>(fixed_point_term(x[j], e)));
+        atomicAdd(&cnt[local], 1u);
     }
     __syncthreads();
-    if (gridDim.y > 1) {
-        for (uint32_t t = threadIdx.x; t < kBucketClusters * D; t += kThreads) {
-            const uint32_t local = t / D, j = t % D;
-            if (p0 + local >= K) continue;
-            const uint32_t k = cperm != nullptr ? cperm[p0 + local] : p0 + local;
-            if (sum[j][local] != 0) atomicAdd(reinterpret_cast<unsigned long long*>(sums_ws) + size_t(k) * D + j, sum[j][local]);
-            if (j == 0 && cnt[local] != 0) atomicAdd(&counts_ws[k], cnt[local]);
-        }
-        return;
-    }
     if (blockIdx.x == 0 && threadIdx.x == 0) hdr->fixed_point_exp = e;
-    // cluster sizes first (one thread per cluster): the running totals stay in the workspace, where a later
-    // iteration of the same fit adds its net change to them
+    // the totals stay in the workspace, where a later iteration of the same fit adds its net change to them
     if (threadIdx.x < kBucketClusters && p0 + threadIdx.x < K) {
         const uint32_t k = cperm != nullptr ? cperm[p0 + threadIdx.x] : p0 + threadIdx.x;
-        uint32_t n = cnt[threadIdx.x];
-        if (delta) n += counts_ws[k];
-        counts_ws[k] = n;
-        cnt[threadIdx.x] = n;
-        if (counts_out != nullptr) counts_out[k] = n;
+        counts_ws[k] = cnt[threadIdx.x];
+        if (counts_out != nullptr) counts_out[k] = cnt[threadIdx.x];
     }
-    __syncthreads();
     for (uint32_t t = threadIdx.x; t < kBucketClusters * D; t += kThreads) {
         const uint32_t local = t / D, j = t % D;
         if (p0 + local >= K) continue;
         const uint32_t k = cperm != nullptr ? cperm[p0 + local] : p0 + local;
         const size_t o = size_t(k) * D + j;
-        long long isum = static_cast<long long>(sum[j][local]);
-        if (delta) isum += sums_ws[o];
+        const long long isum = static_cast<long long>(sum[j][local]);
         sums_ws[o] = isum;
         const uint32_t n = cnt[local];
         const double total = ldexp(double(isum), -e);
@@ -400,47 +284,35 @@ __global__ __launch_bounds__(kThreads) void bucket_sum_kernel(const char* __rest
 }
 
 template <int D>
-static hipError_t update_buckets_t(const float* X, uint32_t N, const uint32_t* idx, const uint32_t* prev_idx,
-                             const uint32_t* changed, const float* prev, uint32_t K, float* out, uint32_t* counts_out,
-                             const Workspace& w, bool norm_order, bool mean, hipStream_t s, bool by_cluster)
+static hipError_t update_buckets_t(const float* X, uint32_t N, const uint32_t* idx, const float* prev, uint32_t K, float* out, uint32_t* counts_out,
+                                   const Workspace& w, bool norm_order, bool mean, hipStream_t s)
 {
     const uint32_t nbuckets = (K + kBucketClusters - 1) / kBucketClusters;
-    const bool delta = prev_idx != nullptr && changed != nullptr;
-    const uint32_t chunk = delta ? kDeltaChunk : kBucketChunk;
-    const uint32_t blocks = (N + chunk - 1) / chunk;
+    const uint32_t blocks = (N + kBucketChunk - 1) / kBucketChunk;
     const uint32_t* cinv = norm_order ? w.cinv : nullptr;
     const uint32_t* cperm = norm_order ? w.cperm : nullptr;
-    hipLaunchKernelGGL(bucket_count_kernel, dim3(blocks), dim3(kThreads), 0, s, idx, delta ? prev_idx : nullptr, delta ? changed : nullptr, N, K,
-                       cinv, nbuckets, w.bucket_hist, w.hdr);
+    hipLaunchKernelGGL(bucket_count_kernel, dim3(blocks), dim3(kThreads), 0, s, idx, N, K, cinv, nbuckets, w.bucket_hist, w.hdr);
     const uint32_t groups = (blocks + kBucketGroup - 1) / kBucketGroup;
     const uint32_t bwg = (nbuckets + kThreads - 1) / kThreads;
     hipLaunchKernelGGL(bucket_groupscan_kernel, dim3(bwg, groups), dim3(kThreads), 0, s, w.bucket_hist, blocks, nbuckets,
                        w.bucket_gtot);
     hipLaunchKernelGGL(bucket_base_kernel, dim3(1), dim3(kMaxBuckets), 0, s, w.bucket_gtot, groups, nbuckets, w.bucket_base);
-    if (delta)
-        hipLaunchKernelGGL(bucket_scatter_delta_kernel<D>, dim3(blocks), dim3(kThreads), 0, s, X, N, idx, prev_idx, changed, K,
-                           cinv, nbuckets, w.bucket_hist, w.bucket_gtot, w.bucket_base, w.records);
-    else
-        hipLaunchKernelGGL(bucket_scatter_kernel<D>, dim3(blocks), dim3(kThreads), 0, s, X, N, idx, K, cinv, nbuckets,
-                           w.bucket_hist, w.bucket_gtot, w.bucket_base, w.records);
-    // two workgroups per compute unit; from half a one on, the launch for the means costs what sharing gains
-    const uint32_t parts = delta && nbuckets <= 128 ? 512 / nbuckets : 1;
-    hipLaunchKernelGGL(bucket_sum_kernel<D>, dim3(nbuckets, parts), dim3(kThreads), 0, s, w.records, w.bucket_base, N, K, cperm,
-                       prev, out, counts_out, w.hdr, mean ? 1 : 0, w.sums, w.counts, delta ? 1 : 0, by_cluster ? 1 : 0);
-    return parts > 1 ? launch_finalize(prev, out, counts_out, K, D, N, w, mean, s) : hipGetLastError();
+    hipLaunchKernelGGL(bucket_scatter_kernel<D>, dim3(blocks), dim3(kThreads), 0, s, X, N, idx, K, cinv, nbuckets,
+                       w.bucket_hist, w.bucket_gtot, w.bucket_base, w.records);
+    hipLaunchKernelGGL(bucket_sum_kernel<D>, dim3(nbuckets), dim3(kThreads), 0, s, w.records, w.bucket_base, N, K, cperm,
+                       prev, out, counts_out, w.hdr, mean ? 1 : 0, w.sums, w.counts);
+    return hipGetLastError();
 }
 
 hipError_t launch_update_buckets(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev,
                                  uint32_t K, float* out, uint32_t* counts_out, const Workspace& w, bool norm_order,
-                                 bool mean, hipStream_t s, const uint32_t* prev_idx, const uint32_t* changed,
-                                 bool by_cluster)
+                                 bool mean, hipStream_t s)
 {
-    if (K > kMaxBuckets * kBucketClusters || w.records == nullptr || (prev_idx != nullptr) != (changed != nullptr))
-        return hipErrorInvalidValue;
+    if (K > kMaxBuckets * kBucketClusters || w.records == nullptr) return hipErrorInvalidValue;
     switch (d) {
-        case 4: return update_buckets_t<4>(X, N, idx, prev_idx, changed, prev, K, out, counts_out, w, norm_order, mean, s, by_cluster);
-        case 8: return update_buckets_t<8>(X, N, idx, prev_idx, changed, prev, K, out, counts_out, w, norm_order, mean, s, by_cluster);
-        case 16: return update_buckets_t<16>(X, N, idx, prev_idx, changed, prev, K, out, counts_out, w, norm_order, mean, s, by_cluster);
+        case 4: return update_buckets_t<4>(X, N, idx, prev, K, out, counts_out, w, norm_order, mean, s);
+        case 8: return update_buckets_t<8>(X, N, idx, prev, K, out, counts_out, w, norm_order, mean, s);
+        case 16: return update_buckets_t<16>(X, N, idx, prev, K, out, counts_out, w, norm_order, mean, s);
         default: return hipErrorInvalidValue;
     }
 }
