@@ -203,6 +203,7 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     e.X = f.x; e.N = N; e.n_dev = far_count; e.out_pos = f.pos;
     e.pack_rows = C; e.pack_perm = w.cperm; e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
     e.packed = w.packed; e.packed_tiles = w.packed_tiles; e.windows = w.windows;
+    e.packed_already = true;   // with the centroids' order
     e.idx = w.idx_sorted;
     e.gate = cc::kGateIfNotF16;
     e.profile = cx.prof;

@@ -39,7 +39,7 @@ constexpr float kUnit = 5.9604644775390625e-08f;  // 2^-24
 constexpr float kGuardSafety = 1.5f;
 
 // ---------------------------------------------------------------------------------------------
-// Packed codebook: per 32-centroid tile, [64 lanes][KS] A-operand values, then 32 x ||c||^2.
+// Packed codebook: per 32-centroid tile, [64 lanes][KS] A-operand values, then 32 x ||c||^2 (put_f32_operand writes the same by centroid).
 // Rows past K are padded with c = 0 and ||c||^2 = +inf, which can never win.
 template <int D>
 __global__ __launch_bounds__(kThreads) void pack_codebook_kernel(const float* __restrict__ C, uint32_t K,
@@ -296,9 +296,10 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     constexpr int GT = int(kGroupTiles);
     constexpr uint32_t TF = 64 * (D / 2) + 32;
     const size_t packed_floats = size_t(e.packed_tiles) * TF;
-    hipLaunchKernelGGL(pack_codebook_kernel<D>, dim3(uint32_t((packed_floats + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<float*>(e.packed), w.hdr, e.gate,
-                       e.pack_perm);
+    if (!e.packed_already)
+        hipLaunchKernelGGL(pack_codebook_kernel<D>, dim3(uint32_t((packed_floats + kThreads - 1) / kThreads)),
+                           dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<float*>(e.packed), w.hdr, e.gate,
+                           e.pack_perm);
     constexpr int VTW = VT * 128 > int(kWinTile) ? int(kWinTile) / 128 : VT;
     const uint32_t per_block = 4 * 32 * (e.windows != nullptr ? VTW : VT);
     const auto kernel = e.windows != nullptr ? assign_mfma_kernel<D, VTW, int(kStageTiles), GT, true>

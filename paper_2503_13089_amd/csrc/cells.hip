@@ -275,10 +275,14 @@ __global__ __launch_bounds__(1024) void cell_key_starts_kernel(const uint32_t* _
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t lo = blockIdx.x * 1024;
     uint32_t before = 0;
-    for (uint32_t i = threadIdx.x; i < lo / 4; i += 1024) {
-        const uint4 v = reinterpret_cast<const uint4*>(hist)[i];
-        before += v.x + v.y + v.z + v.w;
+    uint4 v[16];   // requested together: one at a time the last workgroups waited 16 times
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) {
+        const uint32_t i = q * 1024 + threadIdx.x;
+        v[q] = i < lo / 4 ? reinterpret_cast<const uint4*>(hist)[i] : make_uint4(0u, 0u, 0u, 0u);
     }
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) before += v[q].x + v[q].y + v[q].z + v[q].w;
     const uint32_t own = hist[lo + threadIdx.x];
     uint32_t incl = own;
     for (int off = 1; off < 64; off <<= 1) {
@@ -302,7 +306,8 @@ __global__ __launch_bounds__(1024) void cell_key_starts_kernel(const uint32_t* _
 // Every centroid to its place: permutation and inverse, ordered row, the operand row of the E-step's packed codebook
 // (assign_mfma_f16.hip) and the one of the lists: 8 product slots (the first fp16 part of each component) and
 // 8 for norm and threshold: sigma ||c||^2 in three parts against the multipliers 2^8, 2^-3, 2^-14 of the other side, and
-// those multipliers themselves. Positions past K get operands that never win and never enter a list.
+// those multipliers themselves. Positions past K get operands that never win and never enter a list. Inputs that are not fp16 numbers have
+// their far vectors scored on fp32 operands (assign_mfma.hip), which take the packed codebook's place.
 template <int D>
 __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __restrict__ C, uint32_t K, uint32_t padded,
                                                               const uint16_t* __restrict__ keys, uint32_t* __restrict__ cursor,
@@ -331,15 +336,17 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         for (int q = 0; q < D / 4; ++q)
             reinterpret_cast<float4*>(csorted + size_t(pos) * D)[q] = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
     }
+    double norm = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) norm += double(c[j]) * double(c[j]);
+    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
+    const bool f16 = hdr->x_not_f16 == 0;
+    if (!f16) put_f32_operand<D>(reinterpret_cast<float*>(packed), pos, c, valid ? float(norm) : INFINITY);
     if (!lists_exist(hdr)) return;
     const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
     _Float16 parts[D][3], g[3];
-    double norm = 0.0;
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-        norm += double(c[j]) * double(c[j]);
-        split3(c[j] * sigma, parts[j]);
-    }
+    for (int j = 0; j < D; ++j) split3(c[j] * sigma, parts[j]);
     const float scaled_norm = valid ? float(norm * double(sigma)) : INFINITY;
     if (valid) {
         split_norm(scaled_norm, g);
@@ -347,20 +354,21 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         g[0] = _Float16(INFINITY);
         g[1] = g[2] = _Float16(0.0f);
     }
-    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
-    char* tile = packed + size_t(pos >> 5) * S::kTileBytes;
+    if (f16) {
+        char* tile = packed + size_t(pos >> 5) * S::kTileBytes;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        f16x8 v;
+        for (int half = 0; half < 2; ++half) {
+            f16x8 v;
 #pragma unroll
-        for (int q8 = 0; q8 < 8; ++q8) {
-            const int slot = 8 * half + q8;
-            v[q8] = slot < S::kParts * D ? parts[slot % D][slot / D]
-                                         : (S::kNormInK && slot < S::kParts * D + 3 ? g[slot - S::kParts * D] : _Float16(0.0f));
+            for (int q8 = 0; q8 < 8; ++q8) {
+                const int slot = 8 * half + q8;
+                v[q8] = slot < S::kParts * D ? parts[slot % D][slot / D]
+                                             : (S::kNormInK && slot < S::kParts * D + 3 ? g[slot - S::kParts * D] : _Float16(0.0f));
+            }
+            *reinterpret_cast<f16x8*>(tile + (half * 32 + m) * 16) = v;
         }
-        *reinterpret_cast<f16x8*>(tile + (half * 32 + m) * 16) = v;
+        if (!S::kNormInK) *reinterpret_cast<float*>(tile + 1024 + 4 * q) = scaled_norm;
     }
-    if (!S::kNormInK) *reinterpret_cast<float*>(tile + 1024 + 4 * q) = scaled_norm;
     if (flat != nullptr && valid) {  // d = 8: the operand pieces of one centroid side by side, for the near vectors
         f16x8* to = reinterpret_cast<f16x8*>(flat + size_t(pos) * 64);
 #pragma unroll
@@ -1483,7 +1491,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
     // buffers of the centroids' sort, which does not run during an E-step by cells
     float* drift = cells_bounded(N, D, K) && bounded ? reinterpret_cast<float*>(w.cperm_tmp) : nullptr;
     uint16_t* moves = w.ckeys_tmp;
-    const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = (K + 32 * kFarGroup - 1) / (32 * kFarGroup) * (32 * kFarGroup);
+    const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = w.packed_tiles * 32;
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
                        words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr, w.csorted, w.cinv, drift);
     hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);

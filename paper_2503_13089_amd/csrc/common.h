@@ -278,7 +278,8 @@ struct EStep {
     const float* rows;          // centroid rows in packed order, for the direct-form index recovery ...
     const uint32_t* row_ids;    // ... and the centroid index of each packed position (NULL = identity)
     uint32_t K;                 // rows in this codebook
-    void* packed;               // operand tiles
+    void* packed;               // operand tiles ...
+    bool packed_already;        // ... which hold the codebook (fp32 variant; nothing is left on the refine list then)
     uint32_t packed_tiles;
     const uint2* windows;       // per 512-vector tile window list (NULL = whole codebook)
     uint32_t* idx;              // codes out
@@ -571,6 +572,20 @@ __device__ __forceinline__ long long fixed_point_finite(float x, int e)
 __device__ __forceinline__ long long fixed_point_term(float x, int e)
 {
     return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u ? 0ll : fixed_point_finite(x, e);
+}
+
+// One centroid (c = 0 and norm = +inf past K) at position `pos` of the fp32 variant's packed codebook.
+template <int D>
+__device__ __forceinline__ void put_f32_operand(float* packed, uint32_t pos, const float (&c)[D], float norm)
+{
+    constexpr uint32_t KS = D / 2, TF = 64 * KS + 32;
+    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);   // the operand row whose results lie at q
+    float* tile = packed + size_t(pos >> 5) * TF;
+#pragma unroll
+    for (uint32_t h = 0; h < 2; ++h)
+#pragma unroll
+        for (uint32_t ks = 0; ks < KS; ++ks) tile[(32 * h + m) * KS + ks] = c[2 * ks + h];
+    tile[64 * KS + q] = norm;
 }
 
 // Adds (sign = +1) or removes (sign = -1) one vector to/from cluster k's fixed-point sums and count.
