@@ -116,6 +116,7 @@ int run_bootstrap(const Ctx& cx, const cc::EStep& e, uint32_t N, uint32_t d, con
     cc::EStep b = e;
     b.pack_rows = C; b.pack_perm = w.cperm; b.rows = w.csorted; b.row_ids = w.cperm; b.K = K;
     b.packed = w.packed; b.packed_tiles = w.packed_tiles; b.windows = w.windows;
+    b.packed_already = true;
     b.accumulate = false; b.hint_only = true;
     b.gate = cc::kGateIfF16 | cc::kGateNoHint;
     CC_TRY_HIP(cc::launch_assign_mfma_f16(b, d, w, s), "assign (bootstrap, fp16 matrix cores)");
@@ -142,7 +143,7 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
     if (pruned) {
         {
             cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-            CC_TRY_HIP(cc::launch_sort_centroids(C, d, K, w, s), "assign (centroid norm order)");
+            CC_TRY_HIP(cc::launch_sort_centroids(C, N, d, K, w, s), "assign (centroid norm order)");
         }
         if (!have_hint)
             if (int rc = run_bootstrap(cx, e, N, d, C, K, w, s)) return rc;
@@ -157,6 +158,8 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
     // (incremental M-step) the kernel notes which vectors leave the code that e.idx held on entry, and that code
     if (track_changes) { e.prev_out = w.idx_prev; e.changed = w.changed; }
     if (both) {
+        if (!pruned) CC_TRY_HIP(cc::launch_pack_codebook(C, d, K, w, accumulate, s), "assign (operands)");
+        e.packed_already = true;
         e.gate = cc::kGateIfF16;
         CC_TRY_HIP(cc::launch_assign_mfma_f16(e, d, w, s), "assign (fp16 matrix cores)");
         e.gate = cc::kGateIfNotF16;
@@ -251,7 +254,8 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
         // A pruned E-step is shorter than the atomic traffic of the fused accumulation (which then becomes the
         // bottleneck), so there the M-step groups the vectors by bucket of clusters and sums in LDS instead.
         const bool by_buckets = pruned && w.bucket_ok;
-        if (!by_buckets) CC_TRY_HIP(cc::launch_zero_accumulators(w, K, d, nullptr, 0, s), "update (clear)");
+        if (!by_buckets && (pruned || cx.mode == CC_ASSIGN_MFMA_F32))   // otherwise with the operands
+            CC_TRY_HIP(cc::launch_zero_accumulators(w, K, d, nullptr, 0, s), "update (clear)");
         if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, !by_buckets, pruned, have_hint, s, sums_follow)) return rc;
         {
             cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
@@ -298,7 +302,7 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
 {
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_sort_centroids(C, d, K, w, s), "assign (centroid norm order)");
+        CC_TRY_HIP(cc::launch_sort_centroids(C, N, d, K, w, s), "assign (centroid norm order)");
     }
     cc::EStep e{};
     e.profile = cx.prof;

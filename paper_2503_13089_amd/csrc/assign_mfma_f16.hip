@@ -35,91 +35,6 @@
 namespace cc {
 
 constexpr int kThreads = 256;
-__global__ __launch_bounds__(kThreads) void codebook_absmax_kernel(const float4* __restrict__ C4, size_t n4,
-                                                                   WsHeader* hdr, int gate)
-{
-    if (!gate_open(hdr, gate)) return;
-    uint32_t m = 0;
-    for (size_t i = size_t(blockIdx.x) * kThreads + threadIdx.x; i < n4; i += size_t(gridDim.x) * kThreads) {
-        const float4 t = C4[i];
-        m = max(max(m, __float_as_uint(t.x) & 0x7fffffffu), __float_as_uint(t.y) & 0x7fffffffu);
-        m = max(max(m, __float_as_uint(t.z) & 0x7fffffffu), __float_as_uint(t.w) & 0x7fffffffu);
-    }
-    for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
-    if ((threadIdx.x & 63) == 0 && m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
-    if (blockIdx.x == 0 && threadIdx.x == 0) hdr->refine_count = 0;
-}
-
-// Packed codebook: per 32-centroid tile, [64 lanes][KM] x 8 fp16 A-operand values (lane (m, h) holds
-// k slots 16*mi + 8h .. +7 of MFMA mi for output row m), then for d = 16 the 32 scaled norms (fp32).
-// Output row m of a tile is centroid 32*tile + 16*((m/4)%2) + (m%4) + 4*(m/8), so that lane-half h,
-// accumulator register r is centroid 32*tile + 16h + r. Rows past K: all-zero parts, norm = +inf.
-template <int D>
-__global__ __launch_bounds__(kThreads) void pack_codebook_f16_kernel(const float* __restrict__ C, uint32_t K,
-                                                                     uint32_t ntiles, char* __restrict__ packed,
-                                                                     const WsHeader* __restrict__ hdr, int gate,
-                                                                     const uint32_t* __restrict__ cperm)
-{
-    using S = F16Shape<D>;
-    if (!gate_open(hdr, gate)) return;
-    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
-    const uint32_t tile = t / 64, lane = t % 64;
-    if (tile >= ntiles) return;
-    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
-    const uint32_t h = lane >> 5, m = lane & 31;
-    const uint32_t pos = 32 * tile + 16 * ((m >> 2) & 1) + (m & 3) + 4 * (m >> 3);
-    const bool valid = pos < K;
-    const uint32_t k = (cperm != nullptr && valid) ? cperm[pos] : pos;  // norm order when pruning
-    _Float16 parts[D][3];  // the first S::kParts are used
-    double norm = 0.0;
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const float c = valid ? C[size_t(k) * D + j] : 0.0f;
-        norm += double(c) * double(c);
-        split3(c * sigma, parts[j]);
-    }
-    _Float16 g[3];
-    if (valid) {
-        split_norm(float(norm * double(sigma)), g);  // one rounding of the exact norm
-    } else {
-        g[0] = _Float16(INFINITY);  // times the 2^8 multiplier: a score of +inf, never the minimum
-        g[1] = _Float16(0.0f);
-        g[2] = _Float16(0.0f);
-    }
-    char* tile_base = packed + size_t(tile) * S::kTileBytes;
-#pragma unroll
-    for (int mi = 0; mi < S::KM; ++mi) {
-        f16x8 lo, hi;  // the slots of half 0 and of half 1
-#pragma unroll
-        for (int q8 = 0; q8 < 8; ++q8) {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int q = 16 * mi + 8 * half + q8;
-                _Float16 v = _Float16(0.0f);
-                if (q < S::kParts * D) v = parts[q % D][q / D];
-                else if (S::kNormInK && q < S::kParts * D + 3) v = g[q - S::kParts * D];
-                if (half == 0) lo[q8] = v; else hi[q8] = v;
-            }
-        }
-        *reinterpret_cast<f16x8*>(tile_base + (size_t(lane) * S::KM + mi) * 16) = h ? hi : lo;
-    }
-    if (!S::kNormInK && lane < 32) {
-        // norms in centroid order 32*tile + lane (this thread's own k is a permuted row, so recompute)
-        const uint32_t pc = 32 * tile + lane;
-        const uint32_t kc = (cperm != nullptr && pc < K) ? cperm[pc] : pc;
-        float v = INFINITY;
-        if (pc < K) {
-            double s = 0.0;
-            for (int j = 0; j < D; ++j) {
-                const double c = double(C[size_t(kc) * D + j]);
-                s += c * c;
-            }
-            v = float(s * double(sigma));
-        }
-        *reinterpret_cast<float*>(tile_base + 64 * S::KM * 16 + 4 * lane) = v;
-    }
-}
-
 // WINDOWED = false: the whole packed codebook in stages of ST tiles. WINDOWED = true: the runs of the
 // workgroup's window list (stages of kStageTiles tiles, tiles outside a run skipped).
 template <int D, int VT, int ST, int GT, bool WINDOWED>
@@ -379,12 +294,6 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     // At d = 8 and 16 a window still holds most of the codebook (the bands narrow like K^(-1/d)), the loop dominates again
     // and 4-tile groups pay (8192 x 28672, d = 8, K = 65536: 10 iterations in 531 instead of 545 ms).
     constexpr int GT = 4, GT_WIDE = ST >= 8 ? 8 : 4, GT_WINDOWED = D >= 8 ? 4 : 2;
-    const size_t n4 = size_t(e.K) * D / 4;
-    hipLaunchKernelGGL(codebook_absmax_kernel, dim3(uint32_t(std::min<size_t>((n4 + kThreads - 1) / kThreads, 64))),
-                       dim3(kThreads), 0, s, reinterpret_cast<const float4*>(e.pack_rows), n4, w.hdr, e.gate);
-    hipLaunchKernelGGL(pack_codebook_f16_kernel<D>, dim3((e.packed_tiles * 64 + kThreads - 1) / kThreads),
-                       dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<char*>(e.packed), w.hdr, e.gate,
-                       e.pack_perm);
     // a windowed workgroup scores the vectors of one window list (or a part of them)
     constexpr int VTW = VT * 128 > int(kWinTile) ? int(kWinTile) / 128 : VT;
     const uint32_t per_block = 4 * 32 * (e.windows != nullptr ? VTW : VT);

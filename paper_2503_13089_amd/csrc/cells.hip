@@ -266,43 +266,6 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
     if (m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
 }
 
-// starts[v] = centroids with a key below v, also the next free position of each key (cursor). One workgroup per
-// 1024 keys; each adds up everything before its own share itself.
-__global__ __launch_bounds__(1024) void cell_key_starts_kernel(const uint32_t* __restrict__ hist, uint32_t* __restrict__ starts, uint32_t* __restrict__ cursor,
-                                                               uint32_t K)
-{
-    __shared__ uint32_t wave_sum[16], wave_before[16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t lo = blockIdx.x * 1024;
-    uint32_t before = 0;
-    uint4 v[16];   // requested together: one at a time the last workgroups waited 16 times
-#pragma unroll
-    for (uint32_t q = 0; q < 16; ++q) {
-        const uint32_t i = q * 1024 + threadIdx.x;
-        v[q] = i < lo / 4 ? reinterpret_cast<const uint4*>(hist)[i] : make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < 16; ++q) before += v[q].x + v[q].y + v[q].z + v[q].w;
-    const uint32_t own = hist[lo + threadIdx.x];
-    uint32_t incl = own;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = uint32_t(__shfl_up(int(incl), off, 64));
-        if (lane >= off) incl += v;
-    }
-    for (int off = 32; off > 0; off >>= 1) before += uint32_t(__shfl_xor(int(before), off, 64));
-    if (lane == 63) wave_sum[wave] = incl;
-    if (lane == 0) wave_before[wave] = before;
-    __syncthreads();
-    uint32_t at = incl - own;
-    for (int w = 0; w < 16; ++w) {
-        at += wave_before[w];
-        if (w < wave) at += wave_sum[w];
-    }
-    starts[lo + threadIdx.x] = at;
-    cursor[lo + threadIdx.x] = at;
-    if (lo == 0 && threadIdx.x == 0) starts[65536] = K;
-}
-
 // Every centroid to its place: permutation and inverse, ordered row, the operand row of the E-step's packed codebook
 // (assign_mfma_f16.hip) and the one of the lists: 8 product slots (the first fp16 part of each component) and
 // 8 for norm and threshold: sigma ||c||^2 in three parts against the multipliers 2^8, 2^-3, 2^-14 of the other side, and
@@ -339,7 +302,6 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
     double norm = 0.0;
 #pragma unroll
     for (int j = 0; j < D; ++j) norm += double(c[j]) * double(c[j]);
-    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
     const bool f16 = hdr->x_not_f16 == 0;
     if (!f16) put_f32_operand<D>(reinterpret_cast<float*>(packed), pos, c, valid ? float(norm) : INFINITY);
     if (!lists_exist(hdr)) return;
@@ -354,21 +316,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         g[0] = _Float16(INFINITY);
         g[1] = g[2] = _Float16(0.0f);
     }
-    if (f16) {
-        char* tile = packed + size_t(pos >> 5) * S::kTileBytes;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            f16x8 v;
-#pragma unroll
-            for (int q8 = 0; q8 < 8; ++q8) {
-                const int slot = 8 * half + q8;
-                v[q8] = slot < S::kParts * D ? parts[slot % D][slot / D]
-                                             : (S::kNormInK && slot < S::kParts * D + 3 ? g[slot - S::kParts * D] : _Float16(0.0f));
-            }
-            *reinterpret_cast<f16x8*>(tile + (half * 32 + m) * 16) = v;
-        }
-        if (!S::kNormInK) *reinterpret_cast<float*>(tile + 1024 + 4 * q) = scaled_norm;
-    }
+    if (f16) put_f16_operand<D>(packed, pos, parts, g, scaled_norm);
     if (flat != nullptr && valid) {  // d = 8: the operand pieces of one centroid side by side, for the near vectors
         f16x8* to = reinterpret_cast<f16x8*>(flat + size_t(pos) * 64);
 #pragma unroll
@@ -390,6 +338,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         }
     }
     if (pos >= (K + 31) / 32 * 32) return;   // lists go tile by tile
+    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
     char* op = operands + size_t(pos >> 5) * 1024;
     f16x8 lo, hi;
 #pragma unroll
@@ -1494,7 +1443,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = w.packed_tiles * 32;
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
                        words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr, w.csorted, w.cinv, drift);
-    hipLaunchKernelGGL(cell_key_starts_kernel, dim3(64), dim3(1024), 0, s, w.cell_hist, w.key_starts, w.cell_cursor, K);
+    if (hipError_t e = launch_key_starts(w.cell_hist, w.key_starts, w.cell_cursor, K, s); e != hipSuccess) return e;
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr,
                        drift, moves);

@@ -279,7 +279,7 @@ struct EStep {
     const uint32_t* row_ids;    // ... and the centroid index of each packed position (NULL = identity)
     uint32_t K;                 // rows in this codebook
     void* packed;               // operand tiles ...
-    bool packed_already;        // ... which hold the codebook (fp32 variant; nothing is left on the refine list then)
+    bool packed_already;        // ... which hold the codebook (the fp16 variant's always do)
     uint32_t packed_tiles;
     const uint2* windows;       // per 512-vector tile window list (NULL = whole codebook)
     uint32_t* idx;              // codes out
@@ -314,7 +314,11 @@ hipError_t launch_small_assign(const float* X, uint32_t N, uint32_t d, const flo
 // drop_hint = true forgets the codes a previous call left in the workspace (a fit starts cold).
 hipError_t launch_sort_vectors(const float* X, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool drop_hint,
                                hipStream_t s);
-hipError_t launch_sort_centroids(const float* C, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
+// the centroids in the norm order (w.cperm, w.cinv, w.csorted, w.key_starts) and as operands (w.packed); after launch_sort_vectors
+hipError_t launch_sort_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
+// the centroids as operands where they are; zero_sums: the cluster sums are cleared too
+hipError_t launch_pack_codebook(const float* C, uint32_t d, uint32_t K, const Workspace& w, bool zero_sums, hipStream_t s);
+hipError_t launch_key_starts(const uint32_t* hist, uint32_t* starts, uint32_t* cursor, uint32_t K, hipStream_t s);
 // n_dev: NULL, or where the device keeps the number of vectors (at most N)
 hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
                           hipStream_t s, const uint32_t* n_dev = nullptr);

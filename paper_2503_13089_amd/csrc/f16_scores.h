@@ -41,6 +41,32 @@ __device__ __forceinline__ void split_norm(float v, _Float16 (&g)[3])
     g[2] = _Float16(r2 * 16384.0f);
 }
 
+// One centroid at position `pos` of the packed codebook: its scaled components in parts, sigma ||c||^2 (past K: parts 0, norm +inf, which
+// never wins). Per 32-centroid tile [64 lanes][KM] x 8 fp16 A-operand values (lane (m, h) holds k slots 16 mi + 8 h .. + 7 of MFMA mi for
+// output row m), then, where the norm has no slot, the 32 scaled norms. Output row m of a tile is centroid 32 tile + 16 ((m / 4) % 2) + (m % 4) +
+// 4 (m / 8), so that lane half h, accumulator register r is centroid 32 tile + 16 h + r.
+template <int D>
+__device__ __forceinline__ void put_f16_operand(char* packed, uint32_t pos, const _Float16 (&parts)[D][3], const _Float16 (&g)[3], float scaled_norm)
+{
+    using S = F16Shape<D>;
+    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
+    char* tile = packed + size_t(pos >> 5) * S::kTileBytes;
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int mi = 0; mi < S::KM; ++mi) {
+            f16x8 v;
+#pragma unroll
+            for (int q8 = 0; q8 < 8; ++q8) {
+                const int slot = 16 * mi + 8 * half + q8;
+                v[q8] = slot < S::kParts * D ? parts[slot % D][slot / D]
+                                             : (S::kNormInK && slot < S::kParts * D + 3 ? g[slot - S::kParts * D] : _Float16(0.0f));
+            }
+            *reinterpret_cast<f16x8*>(tile + (size_t(half * 32 + m) * S::KM + mi) * 16) = v;
+        }
+    if (!S::kNormInK) *reinterpret_cast<float*>(tile + 64 * S::KM * 16 + 4 * q) = scaled_norm;
+}
+
 // B operands of one vector: lane (n, h) supplies k slots 16 mi + 8 h .. + 7: -2 x_j for the product slots, the fixed
 // multipliers for the norm slots, 0 for unused ones.
 template <int D>

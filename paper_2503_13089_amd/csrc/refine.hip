@@ -9,6 +9,7 @@
 namespace cc {
 
 constexpr int kThreads = 256;
+constexpr uint32_t kStatBlocks = 64;   // of the 2048 workgroups
 
 // One workgroup per listed vector: its 256 lanes stride over the candidate range with coalesced row loads (a wave per
 // vector left the kernel waiting for the few vectors with the longest ranges: 87 us for 900 of them at K = 65536),
@@ -27,6 +28,21 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
                                                           const uint32_t* __restrict__ out_pos)
 {
     const uint32_t count = hdr->refine_count;
+    __shared__ unsigned long long red[kThreads / 64];
+    if (windows != nullptr && out_pos == nullptr && blockIdx.x < kStatBlocks) {   // how much of the codebook the windows held
+        const uint32_t tiles = (N + kWinTile - 1) / kWinTile;
+        unsigned long long held = 0;
+        for (uint32_t t = blockIdx.x * kThreads + threadIdx.x; t < tiles; t += kStatBlocks * kThreads) held += windows[size_t(t) * kWinStride].y;
+        for (int off = 32; off > 0; off >>= 1) held += __shfl_xor(held, off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = held;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kThreads / 64; ++w) held += red[w];
+            atomicAdd(&hdr->window_stages, held);
+            if (blockIdx.x == 0) atomicAdd(&hdr->window_total, static_cast<unsigned long long>(tiles) * ((K + kWinQuad - 1) / kWinQuad));
+        }
+        __syncthreads();
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         hdr->refined_vectors += count;
         hdr->assign_calls += 1;
@@ -34,7 +50,6 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
         if (persist != nullptr) persist->hint_valid = kHintByNorm;  // idx (norm-ordered) is a usable hint from now on
     }
     if (count > refine_cap) return;  // overflow is handled by the full direct pass
-    __shared__ unsigned long long red[kThreads / 64];
     const int lane = threadIdx.x & 63;
     const int fpe = fixed_point_exp(hdr->absmax_bits, N);
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {

@@ -20,6 +20,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "f16_scores.h"
 #include "ordering.h"
 
 namespace cc {
@@ -158,20 +159,150 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(const float* __re
     reinterpret_cast<float4*>(out)[t] = reinterpret_cast<const float4*>(in)[size_t(ids[p]) * Q + q];
 }
 
+// ---- centroids: order and operands ----------------------------------------------------------------------------------
+// Three launches: keys, their histogram, every centroid's rank among those of its key, the largest magnitude; prefix sums, which are the
+// key -> first position table; rows, permutations and operands straight to their places. Unlike a stable radix sort this leaves the order
+// among equal keys to scheduling, which decides nothing but which tile a centroid shares. (With the sort, the tables, the maximum and
+// the packing for either kind of inputs it were eleven launches of 4 to 6 us: XXX.)
 template <int D>
-__global__ __launch_bounds__(kThreads) void centroid_keys_kernel(const float* __restrict__ C, uint32_t K,
-                                                                 uint16_t* __restrict__ keys, uint32_t* __restrict__ ids,
-                                                                 const WsHeader* __restrict__ hdr)
+__global__ __launch_bounds__(kThreads) void centroid_keys_kernel(const float* __restrict__ C, uint32_t K, uint16_t* __restrict__ keys,
+                                                                 uint32_t* __restrict__ ranks, uint32_t* __restrict__ hist, WsHeader* hdr)
 {
     const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
-    if (k >= K) return;
-    float c[D];
-    load_row<D>(C + size_t(k) * D, c);
-    float s = 0.0f, proj;
+    if (k == 0) hdr->refine_count = 0;
+    uint32_t m = 0;
+    if (k < K) {
+        float c[D];
+        load_row<D>(C + size_t(k) * D, c);
+        float s = 0.0f, proj;
 #pragma unroll
-    for (int j = 0; j < D; ++j) s = __builtin_fmaf(c[j], c[j], s);
-    keys[k] = uint16_t(ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj));
-    ids[k] = k;
+        for (int j = 0; j < D; ++j) {
+            s = __builtin_fmaf(c[j], c[j], s);
+            m = max(m, __float_as_uint(c[j]) & 0x7fffffffu);
+        }
+        const uint32_t key = ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj);
+        keys[k] = uint16_t(key);
+        ranks[k] = atomicAdd(&hist[key], 1u);
+    }
+    __shared__ uint32_t wave_most[kThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
+    if ((threadIdx.x & 63) == 0) wave_most[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int v = 1; v < kThreads / 64; ++v) m = max(m, wave_most[v]);
+    if (m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
+}
+
+// starts[v] = centroids with a key below v, also the next free position of each key (cursor, may be NULL). One workgroup per
+// 1024 keys; each adds up everything before its own share itself.
+__global__ __launch_bounds__(1024) void key_starts_kernel(const uint32_t* __restrict__ hist, uint32_t* __restrict__ starts, uint32_t* __restrict__ cursor,
+                                                               uint32_t K)
+{
+    __shared__ uint32_t wave_sum[16], wave_before[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t lo = blockIdx.x * 1024;
+    uint32_t before = 0;
+    uint4 v[16];   // requested together: one at a time the last workgroups waited 16 times
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) {
+        const uint32_t i = q * 1024 + threadIdx.x;
+        v[q] = i < lo / 4 ? reinterpret_cast<const uint4*>(hist)[i] : make_uint4(0u, 0u, 0u, 0u);
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 16; ++q) before += v[q].x + v[q].y + v[q].z + v[q].w;
+    const uint32_t own = hist[lo + threadIdx.x];
+    uint32_t incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t v = uint32_t(__shfl_up(int(incl), off, 64));
+        if (lane >= off) incl += v;
+    }
+    for (int off = 32; off > 0; off >>= 1) before += uint32_t(__shfl_xor(int(before), off, 64));
+    if (lane == 63) wave_sum[wave] = incl;
+    if (lane == 0) wave_before[wave] = before;
+    __syncthreads();
+    uint32_t at = incl - own;
+    for (int w = 0; w < 16; ++w) {
+        at += wave_before[w];
+        if (w < wave) at += wave_sum[w];
+    }
+    starts[lo + threadIdx.x] = at;
+    if (cursor != nullptr) cursor[lo + threadIdx.x] = at;
+    if (lo == 0 && threadIdx.x == 0) starts[65536] = K;
+}
+
+hipError_t launch_key_starts(const uint32_t* hist, uint32_t* starts, uint32_t* cursor, uint32_t K, hipStream_t s)
+{
+    hipLaunchKernelGGL(key_starts_kernel, dim3(64), dim3(1024), 0, s, hist, starts, cursor, K);
+    return hipGetLastError();
+}
+
+// The codebook's operands for the kind of inputs the scan found (fp16 numbers or not), at the centroids' places in the norm order, or
+// (ORDERED = false) where they are. hist: NULL, or the histogram, to be zero for the next E-step.
+template <int D, bool ORDERED>
+__global__ __launch_bounds__(kThreads) void centroid_place_kernel(const float* __restrict__ C, uint32_t K, uint32_t padded, const uint16_t* __restrict__ keys,
+                                                                  const uint32_t* __restrict__ ranks, const uint32_t* __restrict__ starts,
+                                                                  uint32_t* __restrict__ cperm, uint32_t* __restrict__ cinv, float* __restrict__ csorted,
+                                                                  char* __restrict__ packed, const WsHeader* __restrict__ hdr, uint32_t* __restrict__ hist)
+{
+    const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
+    if (ORDERED && hist != nullptr)
+        for (uint32_t i = k; i < 65536u; i += gridDim.x * kThreads) hist[i] = 0;
+    if (k >= padded) return;
+    const bool valid = k < K;
+    float c[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) c[j] = 0.0f;
+    uint32_t pos = k;
+    if (valid) {
+        load_row<D>(C + size_t(k) * D, c);
+        if constexpr (ORDERED) {
+            pos = starts[keys[k]] + ranks[k];
+            cperm[pos] = k;
+            cinv[k] = pos;
+#pragma unroll
+            for (int q = 0; q < D / 4; ++q)
+                reinterpret_cast<float4*>(csorted + size_t(pos) * D)[q] = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
+        }
+    }
+    double norm = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) norm += double(c[j]) * double(c[j]);
+    if (hdr->x_not_f16 != 0) {
+        put_f32_operand<D>(reinterpret_cast<float*>(packed), pos, c, valid ? float(norm) : INFINITY);
+        return;
+    }
+    const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(hdr->cmax_bits, D));
+    _Float16 parts[D][3], g[3];   // the first F16Shape::kParts are used
+#pragma unroll
+    for (int j = 0; j < D; ++j) split3(c[j] * sigma, parts[j]);
+    const float scaled_norm = valid ? float(norm * double(sigma)) : INFINITY;   // one rounding of the exact norm
+    if (valid) {
+        split_norm(scaled_norm, g);
+    } else {
+        g[0] = _Float16(INFINITY);   // times the 2^8 multiplier: a score of +inf, never the minimum
+        g[1] = g[2] = _Float16(0.0f);
+    }
+    put_f16_operand<D>(packed, pos, parts, g, scaled_norm);
+}
+
+// Ahead of an E-step over the whole codebook: the largest magnitude, an empty refine list, and (sums != NULL) cluster sums of zero.
+__global__ __launch_bounds__(kThreads) void codebook_absmax_kernel(const float4* __restrict__ C4, size_t n4, WsHeader* hdr, long long* __restrict__ sums,
+                                                                   uint32_t* __restrict__ counts, uint32_t K)
+{
+    uint32_t m = 0;
+    for (size_t i = size_t(blockIdx.x) * kThreads + threadIdx.x; i < n4; i += size_t(gridDim.x) * kThreads) {
+        const float4 t = C4[i];
+        m = max(max(m, __float_as_uint(t.x) & 0x7fffffffu), __float_as_uint(t.y) & 0x7fffffffu);
+        m = max(max(m, __float_as_uint(t.z) & 0x7fffffffu), __float_as_uint(t.w) & 0x7fffffffu);
+        if (sums != nullptr) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sums[4 * i + j] = 0;
+            if (i < K) counts[i] = 0;   // K rows are at least K pieces
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
+    if ((threadIdx.x & 63) == 0 && m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
+    if (blockIdx.x == 0 && threadIdx.x == 0) hdr->refine_count = 0;
 }
 
 // Window list of one 512-vector tile: the runs of the ordered codebook (in units of kWinQuad = 32
@@ -328,11 +459,11 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
     }
 }
 
-// Sum of the window sizes of the last E-step (statistics only).
+// Sum of the guessed windows' sizes (statistics only).
 __global__ __launch_bounds__(1024) void window_stats_kernel(const uint2* __restrict__ win, uint32_t tiles, uint32_t K,
-                                                            WsHeader* hdr, int only_without_hint)
+                                                            WsHeader* hdr)
 {
-    if (only_without_hint && !gate_open(hdr, kGateAlways | kGateNoHint)) return;
+    if (!gate_open(hdr, kGateAlways | kGateNoHint)) return;
     __shared__ unsigned long long red[16];
     unsigned long long s = 0;
     for (uint32_t t = blockIdx.x * 1024 + threadIdx.x; t < tiles; t += gridDim.x * 1024) s += win[size_t(t) * kWinStride].y;
@@ -456,53 +587,60 @@ hipError_t launch_sort_vectors(const float* X, uint32_t N, uint32_t d, uint32_t 
         case 16: sort_vectors_t<16>(X, N, w, s); break;
         default: return hipErrorInvalidValue;
     }
+    return N >= 65536u ? launch_fill_u32(w.vperm_tmp, 65536, 0u, s) : hipGetLastError();   // the histogram of the centroids' keys
+}
+
+// The histogram of the keys lies where the vectors' sort had its second buffer, and stays zero between the E-steps of a call; a call of few
+// vectors (with many centroids) has it in the packed codebook, which is written after it, and clears it each time.
+static uint32_t* order_hist(uint32_t N, const Workspace& w) { return N >= 65536u ? w.vperm_tmp : reinterpret_cast<uint32_t*>(w.packed); }
+
+template <int D>
+static hipError_t sort_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
+{
+    uint32_t* hist = order_hist(N, w);
+    const bool kept = hist == w.vperm_tmp;
+    if (!kept)
+        if (hipError_t e = launch_fill_u32(hist, 65536, 0u, s); e != hipSuccess) return e;
+    hipLaunchKernelGGL(centroid_keys_kernel<D>, dim3((K + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, w.ckeys, w.cperm_tmp, hist, w.hdr);
+    if (hipError_t e = launch_key_starts(hist, w.key_starts, nullptr, K, s); e != hipSuccess) return e;
+    const uint32_t padded = w.packed_tiles * kTileCentroids;
+    hipLaunchKernelGGL((centroid_place_kernel<D, true>), dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
+                       w.cperm_tmp, w.key_starts, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.hdr, kept ? hist : nullptr);
     return hipGetLastError();
 }
 
-// What the E-step needs from the ordered centroids, in one launch: the key -> first position table (starts[v] for
-// v = 0 .. 65536), the inverse permutation (cinv[cperm[p]] = p) and the ordered copy of the rows.
-template <int D>
-__global__ __launch_bounds__(kThreads) void centroid_tables_kernel(const uint16_t* __restrict__ sorted_keys,
-                                                                   const uint32_t* __restrict__ perm, uint32_t K,
-                                                                   const float* __restrict__ C, uint32_t* __restrict__ starts,
-                                                                   uint32_t* __restrict__ inv, float* __restrict__ csorted)
+hipError_t launch_sort_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
 {
-    constexpr int Q = D / 4;
-    const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
-    if (t <= 65536u) {
-        uint32_t a = 0, b = K;
-        while (a < b) {
-            const uint32_t m = (a + b) / 2;
-            if (sorted_keys[m] >= t) b = m; else a = m + 1;
-        }
-        starts[t] = a;
-    }
-    if (t < K) inv[perm[t]] = t;
-    if (uint64_t(t) < uint64_t(K) * Q)
-        reinterpret_cast<float4*>(csorted)[t] = reinterpret_cast<const float4*>(C)[size_t(perm[t / Q]) * Q + t % Q];
-}
-
-template <int D>
-static void sort_centroids_t(const float* C, uint32_t K, const Workspace& w, hipStream_t s)
-{
-    hipLaunchKernelGGL(centroid_keys_kernel<D>, dim3((K + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, w.ckeys,
-                       w.cperm, w.hdr);
-    radix_sort16(w.ckeys, w.cperm, w.ckeys_tmp, w.cperm_tmp, K, w.sort_hist, s);
-    const uint64_t pieces = uint64_t(K) * (D / 4);
-    const uint32_t threads = uint32_t(std::max<uint64_t>(pieces, 65537));
-    hipLaunchKernelGGL(centroid_tables_kernel<D>, dim3((threads + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.ckeys,
-                       w.cperm, K, C, w.key_starts, w.cinv, w.csorted);
-}
-
-hipError_t launch_sort_centroids(const float* C, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
-{
+    static_assert(8192 * (6 * 4 + 16) >= 65536 * 4, "the packed codebook holds the histogram");
+    if (N < 65536u && K < 8192u) return hipErrorInvalidValue;
     switch (d) {
-        case 4: sort_centroids_t<4>(C, K, w, s); break;
-        case 8: sort_centroids_t<8>(C, K, w, s); break;
-        case 16: sort_centroids_t<16>(C, K, w, s); break;
+        case 4: return sort_centroids_t<4>(C, N, K, w, s);
+        case 8: return sort_centroids_t<8>(C, N, K, w, s);
+        case 16: return sort_centroids_t<16>(C, N, K, w, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+template <int D>
+static hipError_t pack_codebook_t(const float* C, uint32_t K, const Workspace& w, bool zero_sums, hipStream_t s)
+{
+    const size_t n4 = size_t(K) * D / 4;
+    hipLaunchKernelGGL(codebook_absmax_kernel, dim3(uint32_t(std::min<size_t>((n4 + kThreads - 1) / kThreads, zero_sums ? 512 : 64))), dim3(kThreads), 0, s,
+                       reinterpret_cast<const float4*>(C), n4, w.hdr, zero_sums ? w.sums : nullptr, w.counts, K);
+    const uint32_t padded = w.packed_tiles * kTileCentroids;
+    hipLaunchKernelGGL((centroid_place_kernel<D, false>), dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, nullptr, nullptr,
+                       nullptr, nullptr, nullptr, nullptr, reinterpret_cast<char*>(w.packed), w.hdr, nullptr);
     return hipGetLastError();
+}
+
+hipError_t launch_pack_codebook(const float* C, uint32_t d, uint32_t K, const Workspace& w, bool zero_sums, hipStream_t s)
+{
+    switch (d) {
+        case 4: return pack_codebook_t<4>(C, K, w, zero_sums, s);
+        case 8: return pack_codebook_t<8>(C, K, w, zero_sums, s);
+        case 16: return pack_codebook_t<16>(C, K, w, zero_sums, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int D>
@@ -510,9 +648,8 @@ static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w
 {
     hipLaunchKernelGGL(window_kernel<D>, dim3((N + kWinTile - 1) / kWinTile), dim3(kThreads), 0, s, w.xsorted, N, C, K, w.idx_sorted,
                        w.persist, w.key_starts, guess, w.hdr, w.windows, n_dev, &w.hdr->window_stages);
-    if (n_dev != nullptr) return;
-    hipLaunchKernelGGL(window_stats_kernel, dim3(32), dim3(1024), 0, s, w.windows, (N + kWinTile - 1) / kWinTile, K, w.hdr,
-                       guess > 0.0f ? 1 : 0);
+    if (guess > 0.0f)   // those of the exact pass are counted by the refinement
+        hipLaunchKernelGGL(window_stats_kernel, dim3(32), dim3(1024), 0, s, w.windows, (N + kWinTile - 1) / kWinTile, K, w.hdr);
 }
 
 // guess = 0: windows from the codes in w.idx_sorted (which must be valid codes of these vectors, however stale).
