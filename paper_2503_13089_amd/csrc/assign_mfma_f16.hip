@@ -31,6 +31,7 @@
 
 #include "common.h"
 #include "f16_scores.h"
+#include "score_sets.h"
 
 namespace cc {
 
@@ -283,6 +284,69 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_f16_kernel(
     }
 }
 
+// The same for few vectors: a workgroup of 8 waves takes 32 VT of them, the waves take turns at the tiles.
+constexpr int kFewWaves = 8;
+template <int D, int VT, bool WINDOWED>
+__global__ __launch_bounds__(64 * kFewWaves, VT <= 2 || (VT == 4 && D <= 8) ? 4 : 2) void assign_few_f16_kernel(
+    const float* __restrict__ X, uint32_t N, const float* __restrict__ C, uint32_t K, const char* __restrict__ packed, uint32_t* __restrict__ idx,
+    float* __restrict__ dmin, WsHeader* hdr, uint32_t* __restrict__ refine_list, uint32_t refine_cap, int gate, long long* sums, uint32_t* counts,
+    const uint2* __restrict__ windows, const uint32_t* __restrict__ cperm, int hint_only, uint32_t* __restrict__ prev_out, uint32_t* __restrict__ changed)
+{
+    if (!gate_open(hdr, gate)) return;  // uniform over the grid
+    constexpr int kLds = kFewWaves * VT * 64;
+    __shared__ float x_best[kLds], x_second[kLds];
+    __shared__ uint32_t x_grp[kLds];
+    __shared__ __attribute__((aligned(16))) float norms[kFewWaves * 32 * kSetGroup];
+    const int sum_exp = sums != nullptr ? fixed_point_exp(hdr->absmax_bits, N) : 0;
+    score_sets<D, VT, kFewWaves, WINDOWED>(
+        X, C, cperm, N, K, packed, (K + 31) / 32, windows, hdr->cmax_bits, x_best, x_second, x_grp, norms,
+        [&](uint32_t i, bool mine, const float (&x)[D], uint32_t k, float distance, bool safe) {
+            bool moved = false;
+            if (mine) {
+                if (hint_only) {
+                    idx[i] = k;
+                    return;
+                }
+                if (changed != nullptr) {   // as in assign_mfma_f16_kernel
+                    const uint32_t old = idx[i];
+                    moved = old != k || !safe;
+                    if (moved) prev_out[i] = old;
+                }
+                idx[i] = k;
+                dmin[i] = distance;
+                if (sums != nullptr) accumulate_vector<D>(x, k, sums, counts, sum_exp, +1);
+                if (!safe) {
+                    const uint32_t pos = atomicAdd(&hdr->refine_count, 1u);
+                    if (pos < refine_cap) refine_list[pos] = i;
+                }
+            }
+            if (changed != nullptr && !hint_only) {   // lanes 0..31 hold 32 consecutive vectors
+                const unsigned long long m = __ballot(moved);
+                if ((threadIdx.x & 63) == 0 && i < N) changed[i >> 5] = uint32_t(m);
+            }
+        });
+}
+
+template <int D, int VT>
+static hipError_t launch_few(const EStep& e, const Workspace& w, hipStream_t s)
+{
+    const auto kernel = e.windows != nullptr ? assign_few_f16_kernel<D, VT, true> : assign_few_f16_kernel<D, VT, false>;
+    ProfileScope scope(e.profile, kProfEstepF16, s);
+    hipLaunchKernelGGL(kernel, dim3((e.N + 32 * VT - 1) / (32 * VT)), dim3(64 * kFewWaves), 0, s, e.X, e.N, e.rows, e.K,
+                       static_cast<const char*>(e.packed), e.idx, w.dmin, w.hdr, w.refine_list, w.refine_cap, e.gate,
+                       e.accumulate ? w.sums : nullptr, e.accumulate ? w.counts : nullptr, e.windows, e.row_ids, e.hint_only ? 1 : 0, e.prev_out, e.changed);
+    return hipGetLastError();
+}
+
+// Up to how many vectors. A workgroup of the kernel above takes 512 through the codebook one stage of LDS after the other: 130000 vectors are one
+// workgroup per compute unit, and 17000 are 33 in all. Fits of 10 iterations, us, that kernel / 64 to a workgroup (VT = 2) / 128 (4) / 256 (8), d, K, N:
+// 4, 2600, 17000 696 / 341 / 420 / 419, 90000 807 / 593 / 571 / 642, 450000 1937 / 1668 / 1633 / 1724; 4, 20000 (windows), 200000 1594 / 1288 /
+// 1120 / 1192, 450000 1750 / 2004 / 1622 / 1774, 800000 1999 / 2992 / 2306 / 2558; 8, 2600, 90000 1166 / 843 / 867 / 929, 800000 (windows) 3099 / 3364 / 2923 /
+// 2941; 8, 20000, 200000 2872 / 2426 / 2212 / 2244, 1.6 M 12126 / 14428 / 12472 / 12509; 16, 2600, 17000 1422 / 581 / 640 / 666, 450000 5626 / 4786 / 5088 /
+// 4935, 1.6 M (windows) 10241 / 9803 / 10797 / 8781; 16, 20000, 90000 4102 / 2387 / 2680 / 2447, 450000 8312 / 8190 / 9375 / 7359, 1.6 M 22308 / 25825 / 24050 /
+// 21851. 32 to a workgroup: never better from 17000 on.
+constexpr uint32_t few_most(int d, bool windowed) { return d == 4 ? 1u << 19 : (d == 8 ? 1u << 20 : (windowed ? 1u << 21 : 1u << 19)); }
+
 template <int D, int VT, int ST>
 static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
 {
@@ -294,6 +358,11 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     // At d = 8 and 16 a window still holds most of the codebook (the bands narrow like K^(-1/d)), the loop dominates again
     // and 4-tile groups pay (8192 x 28672, d = 8, K = 65536: 10 iterations in 531 instead of 545 ms).
     constexpr int GT = 4, GT_WIDE = ST >= 8 ? 8 : 4, GT_WINDOWED = D >= 8 ? 4 : 2;
+    if (e.N <= few_most(D, e.windows != nullptr)) {
+        if (e.N <= 8192u) return launch_few<D, 1>(e, w, s);
+        if (e.N <= (D == 4 ? 49152u : (D == 8 ? 98304u : (e.windows != nullptr ? 131072u : 0xffffffffu)))) return launch_few<D, 2>(e, w, s);
+        return launch_few<D, (D == 16 ? 8 : 4)>(e, w, s);
+    }
     // a windowed workgroup scores the vectors of one window list (or a part of them)
     constexpr int VTW = VT * 128 > int(kWinTile) ? int(kWinTile) / 128 : VT;
     const uint32_t per_block = 4 * 32 * (e.windows != nullptr ? VTW : VT);

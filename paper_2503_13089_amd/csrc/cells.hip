@@ -24,6 +24,7 @@
 #include "common.h"
 #include "f16_scores.h"
 #include "ordering.h"
+#include "score_sets.h"
 
 namespace cc {
 
@@ -31,14 +32,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-
-// Between what lanes of one wave write to LDS and what other lanes of it read: its LDS accesses are served in order, so there is
-// nothing to wait for, but the compiler has to keep them in order.
-__device__ __forceinline__ void wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // A cell's list: the centroids within r1 of its centroid, then (d = 8) those between r1 and r2. Room in all for 4096 entries
 // where 1500 are aimed at: the vectors of a longer one are far. 29 M vectors, K = 65536, 10 iterations: room for 6144
@@ -188,12 +181,11 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
     }
 }
 
-constexpr int kFarGroup = 2;   // tiles of 32 centroids that the far vectors score together
 // Up to so many far vectors, 32, 64 and 128 of them share a workgroup: the first two give each of 256 compute units one, and 256 vectors
 // (d = 8), whose operand loads and start values serve twice the products (27.3 instead of 31.8 ms of the 29 M fit), take four rounds
 // to be worth it (2.8 M: 26.7 ms with 256 at any number, 25.5 with 128, 25.0 with this rule).
 constexpr uint32_t kFarFew1 = 32 * 256, kFarFew2 = 64 * 256, kFarFew4 = 4 * 128 * 256;
-static_assert(kStageTiles % kFarGroup == 0 && kStageTilesMax % kFarGroup == 0, "runs share no group, the packed codebook has room for whole ones");
+static_assert(kStageTiles % kSetGroup == 0 && kStageTilesMax % kSetGroup == 0, "runs share no group, the packed codebook has room for whole ones");
 
 // ---- centroids: order, operands, radii ------------------------------------------------------------------------------
 // Three launches put the centroids into the order of sort.hip's (norm shell, cosine) key with everything the E-step needs
@@ -785,13 +777,6 @@ __device__ __forceinline__ void clear_scores(Scores& s)
     }
 }
 
-// One running best / second best: `w` into (best, second)
-__device__ __forceinline__ void take_score(float& best, float& second, float w)
-{
-    second = __builtin_amdgcn_fmed3f(best, second, w);
-    asm("v_min_f32 %0, %1, %2" : "=v"(best) : "v"(best), "v"(w));
-}
-
 // The lane's part of a vector's operand: k slots 8 g .. 8 g + 7 (g = 0 .. 2: the products with parts 0 .. 2 of the centroids'
 // components; g = 3: the multipliers of the norm's parts)
 __device__ __forceinline__ f16x8 near_operand(const float (&x)[8], int g)
@@ -1212,172 +1197,6 @@ struct FarShape {
     static constexpr int kLds = kWaves * kMostVT * 64;
 };
 
-template <int D, int VT>
-__device__ __forceinline__ void far_sets(const float* __restrict__ X, const float* __restrict__ rows, const uint32_t* __restrict__ cperm,
-                                         uint32_t N, uint32_t K, const char* __restrict__ packed, const uint2* __restrict__ windows,
-                                         const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx, float* __restrict__ dmin,
-                                         WsHeader* hdr, uint32_t* __restrict__ refine_list, float* x_best, float* x_second,
-                                         uint32_t* x_grp, float* lds_norms)
-{
-    using S = F16Shape<D>;
-    constexpr int GT = kFarGroup, W = FarShape<D>::kWaves;
-    constexpr uint32_t kSet = 32 * VT;
-    static_assert(GT == 2, "a lane of each half to a tile's norms");
-    static_assert(kWinSlots <= 64, "a lane to a run");
-    static_assert(kWinTile % kSet == 0 && VT <= W, "a set has one window, a wave finishes a tile");
-    const int lane = threadIdx.x & 63, h = lane >> 5, n = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    float* const norms = lds_norms + wave * (32 * GT);
-    const uint32_t sets = (N + kSet - 1) / kSet;
-    for (uint32_t set = blockIdx.x; set < sets; set += gridDim.x) {
-        const uint32_t i0 = (sets - 1 - set) * kSet;  // the widest windows first
-        f16x8 b[VT][1];
-#pragma unroll
-        for (int vt = 0; vt < VT; ++vt) {
-            float x[D];
-            load_row<D>(X + size_t(min(i0 + vt * 32 + n, N - 1)) * D, x);
-            vector_operand<D>(x, h, b[vt]);
-        }
-        float best_of[VT], second_of[VT];
-        uint32_t grp_of[VT];
-#pragma unroll
-        for (int vt = 0; vt < VT; ++vt) {
-            best_of[vt] = second_of[vt] = INFINITY;
-            grp_of[vt] = 0;
-        }
-        // The window's groups of GT tiles in one sequence (runs share none), the waves taking every W-th: lane r holds where
-        // run r ends in it and what turns a place in the sequence into a group. Tiles of a group beside the run are scored with it.
-        const uint2* wl = windows + size_t(i0 / kWinTile) * kWinStride;
-        uint32_t g0 = 0, count = 0;
-        if (uint32_t(lane) < wl[0].x) {
-            const uint2 run = wl[1 + lane];
-            g0 = run.x / GT;
-            count = (run.y + GT - 1) / GT - g0;
-        }
-        uint32_t run_end = count;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t before = uint32_t(__shfl_up(int(run_end), off, 64));
-            if (lane >= off) run_end += before;
-        }
-        const uint32_t shift = g0 - (run_end - count);
-        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(run_end), 63));
-        uint32_t r = 0;
-        auto group_at = [&](uint32_t at) {   // ascending places; past the end the last one
-            const uint32_t f = min(at, total - 1);
-            while (f >= uint32_t(__builtin_amdgcn_readlane(int(run_end), int(r)))) ++r;
-            return f + uint32_t(__builtin_amdgcn_readlane(int(shift), int(r)));
-        };
-        float norm = 0.0f;   // d = 8: lane (u, row) loads the norm of a row of tile u, a group ahead
-        auto load = [&](uint32_t group, f16x8 (&to)[GT]) {   // a scalar base and one offset per lane
-            const char* tiles = packed + size_t(group) * (GT * S::kTileBytes);
-#pragma unroll
-            for (int u = 0; u < GT; ++u) to[u] = *reinterpret_cast<const f16x8*>(tiles + (uint32_t(lane) * 16 + u * S::kTileBytes));
-            if constexpr (!S::kNormInK) norm = *reinterpret_cast<const float*>(tiles + (uint32_t(h) * S::kTileBytes + 1024 + 4 * n));
-        };
-        f16x8 from[GT], to[GT];
-        uint32_t at = uint32_t(wave), g = 0;
-        if (at < total) {
-            g = group_at(at);
-            load(g, from);
-        }
-        for (; at < total; at += W) {
-            f32x16 cn[S::kNormInK ? 1 : GT];
-            if constexpr (S::kNormInK) {
-#pragma unroll
-                for (int q = 0; q < 16; ++q) cn[0][q] = 0.0f;
-            } else {   // rows 16 h .. 16 h + 15 of every tile
-                wave_order();   // what the group before had there has been read
-                norms[lane] = norm;
-                wave_order();
-#pragma unroll
-                for (int u = 0; u < GT; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = reinterpret_cast<const float4*>(norms + 32 * u + 16 * h)[q];
-                        cn[u][4 * q] = v.x; cn[u][4 * q + 1] = v.y; cn[u][4 * q + 2] = v.z; cn[u][4 * q + 3] = v.w;
-                    }
-            }
-            const uint32_t next = group_at(at + W);
-            load(next, to);
-            __builtin_amdgcn_sched_barrier(0);   // else the compiler would put the loads behind the products
-            // the products of one tile run while the minima of the one before it are taken
-            float m[VT];
-#pragma unroll
-            for (int vt = 0; vt < VT; ++vt) m[vt] = INFINITY;
-            f32x16 acc[2];
-            auto product = [&](int i) {
-                acc[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(from[i / VT], b[i % VT][0], cn[S::kNormInK ? 0 : i / VT], 0, 0, 0);
-            };
-            product(0);
-#pragma unroll
-            for (int i = 0; i < GT * VT; ++i) {
-                if (i + 1 < GT * VT) product(i + 1);
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    m[i % VT] = __builtin_fminf(__builtin_fminf(m[i % VT], acc[i & 1][2 * q]), acc[i & 1][2 * q + 1]);
-            }
-            __builtin_amdgcn_sched_group_barrier(8, 1, 0);
-#pragma unroll
-            for (int i = 0; i < GT * VT; ++i) {   // a product, the eight instructions of the minimum before it, the next product ...
-                __builtin_amdgcn_sched_group_barrier(8, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(2, 8, 0);
-            }
-#pragma unroll
-            for (int vt = 0; vt < VT; ++vt) {
-                grp_of[vt] = m[vt] < best_of[vt] ? g : grp_of[vt];
-                take_score(best_of[vt], second_of[vt], m[vt]);
-            }
-            g = next;
-#pragma unroll
-            for (int u = 0; u < GT; ++u) from[u] = to[u];
-        }
-        auto exchange = [&](int w, int vt) { return (w * VT + vt) * 64 + lane; };
-#pragma unroll
-        for (int vt = 0; vt < VT; ++vt) {
-            x_best[exchange(wave, vt)] = best_of[vt];
-            x_second[exchange(wave, vt)] = second_of[vt];
-            x_grp[exchange(wave, vt)] = grp_of[vt];
-        }
-        __syncthreads();
-        if (wave < VT) {  // wave w finishes tile w: index recovery and guard band as in assign_mfma_f16.hip
-            float best = INFINITY, second = INFINITY;
-            uint32_t grp = 0;
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float ob = x_best[exchange(w, wave)], os = x_second[exchange(w, wave)];
-                if (ob < best) grp = x_grp[exchange(w, wave)];
-                second = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
-                best = __builtin_fminf(best, ob);
-            }
-            const uint32_t i_raw = i0 + wave * 32 + n, i = min(i_raw, N - 1);
-            float x[D];
-            load_row<D>(X + size_t(i) * D, x);
-            const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
-            const uint32_t og = uint32_t(__shfl_xor(int(grp), 32, 64));
-            const bool mine = best < ob || (best == ob && h == 0);
-            const float bstar = __builtin_fminf(best, ob);
-            const float sstar = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
-            float bd;
-            uint32_t bk;
-            recover_group<D, GT>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
-            const float od = __shfl_xor(bd, 32, 64);
-            const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
-            const bool take = od < bd || (od == bd && ok < bk);
-            const float dstar = take ? od : bd;
-            const uint32_t cmax_bits = hdr->cmax_bits;
-            const float sigma = __builtin_ldexpf(1.0f, centroid_scale_log2(cmax_bits, D));
-            const bool safe = (sstar - bstar) > f16_guard_band<D>(x, dstar, sigma, sigma * __uint_as_float(cmax_bits));
-            if (h == 0 && i_raw < N) {
-                const uint32_t p = far_pos[i];
-                idx[p] = take ? ok : bk;
-                dmin[p] = dstar;
-                if (!safe) refine_list[atomicAdd(&hdr->refine_count, 1u)] = i;
-            }
-        }
-        __syncthreads();  // the exchange buffers have been read
-    }
-}
-
 template <int D>
 __global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const float* __restrict__ X, const float* __restrict__ rows,
                                                                        const uint32_t* __restrict__ cperm, uint32_t K,
@@ -1388,11 +1207,19 @@ __global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const flo
     using F = FarShape<D>;
     __shared__ float x_best[F::kLds], x_second[F::kLds];
     __shared__ uint32_t x_grp[F::kLds];
-    __shared__ __attribute__((aligned(16))) float norms[F::kWaves * 32 * kFarGroup];
+    __shared__ __attribute__((aligned(16))) float norms[F::kWaves * 32 * kSetGroup];
     const uint32_t N = hdr->far_count;
     if (hdr->x_not_f16 != 0) return;
     auto sets = [&](auto vt) {
-        far_sets<D, decltype(vt)::value>(X, rows, cperm, N, K, packed, windows, far_pos, idx, dmin, hdr, refine_list, x_best, x_second, x_grp, norms);
+        score_sets<D, decltype(vt)::value, F::kWaves, true>(
+            X, rows, cperm, N, K, packed, 0u, windows, hdr->cmax_bits, x_best, x_second, x_grp, norms,
+            [&](uint32_t i, bool mine, const float (&)[D], uint32_t k, float distance, bool safe) {
+                if (!mine) return;
+                const uint32_t p = far_pos[i];
+                idx[p] = k;
+                dmin[p] = distance;
+                if (!safe) refine_list[atomicAdd(&hdr->refine_count, 1u)] = i;
+            });
     };
     if (N <= kFarFew1) sets(std::integral_constant<int, 1>{});
     else if (N <= kFarFew2) sets(std::integral_constant<int, 2>{});

@@ -163,7 +163,8 @@ __global__ __launch_bounds__(kThreads) void gather_rows_kernel(const float* __re
 // Three launches: keys, their histogram, every centroid's rank among those of its key, the largest magnitude; prefix sums, which are the
 // key -> first position table; rows, permutations and operands straight to their places. Unlike a stable radix sort this leaves the order
 // among equal keys to scheduling, which decides nothing but which tile a centroid shares. (With the sort, the tables, the maximum and
-// the packing for either kind of inputs it were eleven launches of 4 to 6 us: XXX.)
+// the packing for either kind of inputs it were eleven launches of 4 to 6 us each:
+// 10 iterations of 528000 vectors of 4, K = 17172, 2.03 ms, now 1.58; 20 of 261000 of 8, K = 28292, 6.47, now 5.72.)
 template <int D>
 __global__ __launch_bounds__(kThreads) void centroid_keys_kernel(const float* __restrict__ C, uint32_t K, uint16_t* __restrict__ keys,
                                                                  uint32_t* __restrict__ ranks, uint32_t* __restrict__ hist, WsHeader* hdr)
