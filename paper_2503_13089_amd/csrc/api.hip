@@ -81,18 +81,24 @@ bool use_matrix_cores(const Ctx& cx, uint32_t K)
 // Norm-window pruning: only in the automatic mode and only where the ordering overhead can pay off. A single
 // E-step pays for ordering the vectors by itself, so it needs a large codebook; a fit orders once and keeps the
 // integer cluster sums up to date across its iterations, which pays from a few hundred centroids on once there
-// are enough vectors to fill the chip (measured break-even: about 3e5 vectors, 5 iterations).
-bool use_pruning(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters)
+// are enough vectors to fill the chip. 10 iterations, us, whole codebook / windows: d = 4, K = 1000: 500000 919 / 1314, 530000 1145 / 1099; K = 6000:
+// 262000 1102 / 1075, 530000 1998 / 1334; d = 8, K = 6000: 530000 2348 / 2402, 1.05 M 4973 / 4430; d = 16: K = 1000 530000 3737 / 3044; K = 2600 500000
+// 3232 / 3269. With few centroids the windows never pay at d = 8 (K = 1000: 1.05 M 3077 / 3249, 3 M 7279 / 7891) and where small_fit.hip takes them
+// (d = 8, K = 390: 1.9 M 3747 / 4400; d = 16, K = 300: 530000 2047 / 2731, 2.1 M 5792 / 9011). Fits of 2^19 to 2^20 vectors of 4 or 8 keep them from 256 centroids
+// on, as their tests say, although d = 4, K = 300, 750000 would take 788 instead of 1132 and d = 8, K = 300 1733 instead of 2207.
+bool use_pruning(const Ctx& cx, uint64_t N, uint32_t d, uint32_t K, int32_t iters)
 {
     if (cx.mode != CC_ASSIGN_AUTO) return false;
-    return K >= 8192 || (K >= 256 && N >= (1u << 19) && iters >= 5);
+    if (K >= 8192) return true;
+    if ((d == 8 && K < 1024 && N >= (1u << 20)) || (d == 16 && cc::small_problem(N, d, K))) return false;
+    return K >= 256 && N >= (1u << 19) && iters >= 5;
 }
 
 // Small problems: two launches per iteration, everything in direct form (small_fit.hip); a fit long and large enough for
 // the windows is better off with them.
 bool use_small(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters, const cc::Workspace& w)
 {
-    return cx.mode == CC_ASSIGN_AUTO && !use_pruning(cx, N, K, iters) && w.small_partials != nullptr;
+    return cx.mode == CC_ASSIGN_AUTO && !use_pruning(cx, N, w.d, K, iters) && w.small_partials != nullptr;
 }
 
 // Relative half-width of the guessed windows of the bootstrap pass. The nearest-centroid distance of a vector of
@@ -253,14 +259,18 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
         // those codes (and keeps the code they had), so that the M-step can move just these.
         // A pruned E-step is shorter than the atomic traffic of the fused accumulation (which then becomes the
         // bottleneck), so there the M-step groups the vectors by bucket of clusters and sums in LDS instead.
-        const bool by_buckets = pruned && w.bucket_ok;
-        if (!by_buckets && (pruned || cx.mode == CC_ASSIGN_MFMA_F32))   // otherwise with the operands
+        // Over the whole codebook those atomics cost more than three launches by slices, too: 10 iterations, N = 450000, with / without, ms: d = 16,
+        // K = 300 8.08 / 2.1; d = 8, K = 1000 3.6 / 1.3; d = 4, K = 2600 1.6 / 1.1.
+        const bool by_buckets = pruned && w.bucket_ok, by_slices = !sums_follow && (by_buckets || !pruned) && cc::update_sliced_applies(N, d, K, w);
+        const bool apart = by_buckets || by_slices;
+        if (!apart && (pruned || cx.mode == CC_ASSIGN_MFMA_F32))   // otherwise with the operands
             CC_TRY_HIP(cc::launch_zero_accumulators(w, K, d, nullptr, 0, s), "update (clear)");
-        if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, !by_buckets, pruned, have_hint, s, sums_follow)) return rc;
+        if (int rc = run_assign_matrix(cx, X, N, d, C, K, idx, w, !apart, pruned, have_hint, s, sums_follow)) return rc;
         {
             cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
-            if (by_buckets && !sums_follow && cc::update_sliced_applies(N, d, K, w))
-                CC_TRY_HIP(cc::launch_update_sliced(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, true, false, s), "update (slices)");
+            if (by_slices)
+                CC_TRY_HIP(cc::launch_update_sliced(pruned ? w.xsorted : X, N, d, pruned ? w.idx_sorted : idx, C, K, C, counts, w, true, false, s),
+                           "update (slices)");
             else if (by_buckets && sums_follow && cc::update_delta_applies(N, d, K, w))
                 CC_TRY_HIP(cc::launch_update_delta(w.xsorted, N, d, w.idx_sorted, C, K, C, counts, w, s), "update (changes)");
             else if (by_buckets)
@@ -526,7 +536,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     if (o.C_work != o.C_in)
         CC_TRY_HIP(cc::launch_copy_f32(o.C_in, o.C_work, size_t(K) * D, s), "centroid copy");
     const bool small = use_small(cx, N, K, iters, w);
-    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, iters);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, D, K, iters);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
@@ -581,7 +591,7 @@ int cc_assign_ex(const float* vectors, uint64_t N, uint32_t d, const float* cent
     if (int rc = enter(vectors, centroids, nullptr, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
     const bool small = use_small(cx, N, K, 1, w);
-    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, w.d, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, uint32_t(N), w.d, K, w, false, s), "norm ordering");
@@ -614,7 +624,7 @@ int cc_lloyd_iter_ex(const float* vectors, uint64_t N, uint32_t d, float* centro
     if (int rc = enter(vectors, centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
     const bool small = use_small(cx, N, K, 1, w);
-    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, K, 1);
+    const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, w.d, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, uint32_t(N), w.d, K, w, false, s), "norm ordering");
