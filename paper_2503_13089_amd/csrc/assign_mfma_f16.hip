@@ -345,7 +345,13 @@ static hipError_t launch_few(const EStep& e, const Workspace& w, hipStream_t s)
 // 2941; 8, 20000, 200000 2872 / 2426 / 2212 / 2244, 1.6 M 12126 / 14428 / 12472 / 12509; 16, 2600, 17000 1422 / 581 / 640 / 666, 450000 5626 / 4786 / 5088 /
 // 4935, 1.6 M (windows) 10241 / 9803 / 10797 / 8781; 16, 20000, 90000 4102 / 2387 / 2680 / 2447, 450000 8312 / 8190 / 9375 / 7359, 1.6 M 22308 / 25825 / 24050 /
 // 21851. 32 to a workgroup: never better from 17000 on.
-constexpr uint32_t few_most(int d, bool windowed) { return d == 4 ? 1u << 19 : (d == 8 ? 1u << 20 : (windowed ? 1u << 21 : 1u << 19)); }
+// Whole codebook, 2 iterations, us, that kernel / this one: 4, 4096, 1 M 656 / 664, 4.2 M 2074 / 2324; 8, 1000, 1 M 786 / 690, 8000, 4 M 4898 / 4698; 16, 8000, 2 M
+// 5373 / 4258.
+constexpr uint32_t few_most(int d, bool windowed)
+{
+    if (windowed) return d == 4 ? 1u << 19 : (d == 8 ? 1u << 20 : 1u << 21);
+    return d == 4 ? 1u << 20 : (d == 8 ? 1u << 23 : 1u << 22);
+}
 
 template <int D, int VT, int ST>
 static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
@@ -360,7 +366,7 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     constexpr int GT = 4, GT_WIDE = ST >= 8 ? 8 : 4, GT_WINDOWED = D >= 8 ? 4 : 2;
     if (e.N <= few_most(D, e.windows != nullptr)) {
         if (e.N <= 8192u) return launch_few<D, 1>(e, w, s);
-        if (e.N <= (D == 4 ? 49152u : (D == 8 ? 98304u : (e.windows != nullptr ? 131072u : 0xffffffffu)))) return launch_few<D, 2>(e, w, s);
+        if (e.N <= (D == 4 ? 49152u : (D == 8 ? 98304u : (e.windows != nullptr ? 131072u : 229376u)))) return launch_few<D, 2>(e, w, s);
         return launch_few<D, (D == 16 ? 8 : 4)>(e, w, s);
     }
     // a windowed workgroup scores the vectors of one window list (or a part of them)

@@ -225,13 +225,14 @@ hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K,
 // Where this form is the fastest: the accumulators fit LDS, and the distances cost less in direct form than what the
 // matrix-core form pays in launches, latency and the M-step. Below 128 centroids the E-step is in direct form anyway. Fits of 10
 // iterations, us, matrix-core form (its own choice of windows) / this one: d = 4: K = 140: N = 260000 515 / 236, 10 M 6766 / 4023; K = 250: 10 M 8997 /
-// 6899; K = 500: 260000 570 / 509, 520000 863 / 852; K = 900: 33000 389 / 269, 40000 368 / 323, 66000 428 / 463; d = 8: K = 140: 4 M 5596 / 2853; K = 390:
-// 4.5 M 9297 / 8250; K = 500: 260000 852 / 779; d = 16: K = 250: 2.5 M 9608 / 5412; K = 300: 430000 2072 / 1424.
+// 6899; K = 500: 260000 570 / 509, 520000 863 / 852; K = 700: 132000 481 / 606, 330000 693 / 1042; K = 900: 33000 389 / 269, 40000
+// 368 / 323, 66000 428 / 463; d = 8: K = 140: 4 M 5596 / 2853; K = 390:
+// 4.5 M 9297 / 8250; K = 500: 260000 852 / 779; K = 700: 66000 516 / 595, 132000 678 / 955; d = 16: K = 250: 2.5 M 9608 / 5412; K = 300: 430000 2072 / 1424.
 bool small_problem(uint64_t N, uint32_t d, uint32_t K)
 {
     if (lds_bytes(d, K) > kMaxLds || N >= (1ull << 31)) return false;
     if (K < (d == 4 ? 256u : 400u)) return true;
-    const uint64_t limit = d == 4 ? (K <= 768 ? 1ull << 28 : 3ull << 24) : 1ull << 27;
+    const uint64_t limit = d == 4 ? (K <= 512 ? 1ull << 28 : 3ull << 24) : (d == 8 && K > 512 ? 1ull << 25 : 1ull << 27);
     return N * K <= limit;
 }
 
