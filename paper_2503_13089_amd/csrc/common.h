@@ -23,13 +23,17 @@ struct CellHead {
     uint32_t mids;             // d = 8: vectors of the cell between r1 and r2
 };
 // Whether a fit of this shape runs its E-steps by cells (d as padded; codes of 16 bits; the bounds do not prune at
-// d = 16). The line lies where grouping, lists and the extra launches pay: against windows alone, d = 4: 0.90 x the speed at
-// (N, K) = (2 M, 65536), 0.98 at (2 M, 4096), 1.00 at (4 M, 1024), 1.2 at (4 M, 4096), 0.89 at (4 M, 65536, 5 iterations), 1.3 at (11 M, 65536), 0.88 at
-// (16 M, 300); d = 8: 0.93 at (1 M, 32768), 1.03 at (2 M, 4096), 1.16 at (2 M, 16384), 1.0 at (16 M, 300), 3.7 at
-// (29 M, 65536).
+// d = 16). The line lies where grouping, lists and the extra launches pay, with few iterations as with many. Times with
+// windows alone over times by cells, random weights, after 3 / 5 / 20 iterations:
+//   d = 4: (N, K) = (1.6 M, 4096) 1.01 / 1.01 / 1.2, (1.6 M, 65500) 1.01 / 1.06 / 1.2, (2 M, 20000) 1.04 / 1.13 / 1.3,
+//     (3.5 M, 65500) 1.1 / 1.2 / 1.5, (11 M, 65536, 20) 1.3; one side below: (1.06 M, 4096) 1.01 / 0.91 / 1.1
+//   d = 8: (1.6 M, 1100) 1.00 / 1.12 / 1.4, (1.6 M, 12000) 1.15 / 1.23 / 1.5, (1.6 M, 65500) 1.29 / 1.40 / 1.7; and below:
+//     (0.8 M, 12000) 0.93 / 0.96 / 1.0
+// Rows of differing scales (0.3 in the logarithm) move both sides: (0.8 M, 12000) 0.76 / 0.79 / 0.81 after 10,
+// (1.1 M, 65500) 0.90 / 0.94 / 1.02, but (1.6 M, 65500) 1.03 / 1.10 / 1.19 and (1.6 M, 12000) 0.96 / 1.03 / 1.11.
 inline bool cells_possible(uint64_t N, uint32_t d, uint32_t K)
 {
-    return d <= 8 && K >= 1024 && K <= 65536 && N >= (d == 4 ? 128ull : 32ull) * K && N >= (d == 4 ? 1u << 22 : 1u << 21) && N < (1ull << 31);
+    return d <= 8 && K >= 1024 && K <= 65536 && N >= 24ull * K && N >= (3u << 19) && N < (1ull << 31);
 }
 
 constexpr uint32_t kMaxK = 1u << 24;

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-N4, N8 = 1 << 22, 1 << 21   # the smallest that take the form
+N4, N8 = 1 << 22, 1 << 21   # cells of many vectors; the fewest are in test_gpu_cells_fewest.py
 
 
 @pytest.mark.parametrize("N,d,K,iters,kind", [

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-N4, N8 = 1 << 22, 1 << 21   # the smallest that take the form
+N4, N8 = 1 << 22, 1 << 21   # cells of many vectors
 
 
 def fits(X, C0, iters, ws, modes=(0, 1)):
