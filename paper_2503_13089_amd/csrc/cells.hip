@@ -349,13 +349,17 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
 // or less. The cells' counters are in LDS. Where in a list an entry lands depends on scheduling; no result does.
 // WINDOWED (d = 4): only the runs of the ordered codebook that the shells and cosines of sort.hip allow for the 32 cells;
 // at d = 8 a ball that is 1 % of the codebook touches most of them.
-// Bound: vector instructions, 16 for a tile's bits and as many again for its hits; K = 65536: 4.3 G pairs at d = 8 in 0.3 to 0.52 ms
-// (lists of 2.8 M vectors; 0.48 to 0.76 with a second product for the inner radius and every product copied out of accumulation
-// registers, which the launch bound prevents, 0.37 to 0.57 with the second product alone; 29 M vectors 0.6 to 1.4, its first lists are
-// longer), 0.08 to 0.15 ms at d = 4 (0.095 to 0.21).
+// Bound: vector instructions, 16 for a tile's bits and as many again for its hits, and L2 (a KB of operands per product, 2 bytes per
+// entry written on their own: the channels are busy nine clocks of ten). K = 65536: 4.3 G pairs at d = 8 in 0.26 ms (lists of 2.8 M vectors) and 0.49
+// (29 M, the first lists are longer), 0.06 at d = 4 (11 M); 0.32, 0.79 and 0.08 with 4 waves to a workgroup, 4 tiles at a time and the inner shells first.
+// Two products per tile (64 cells to a workgroup) halve the loads and lose: 0.32 -> 0.39.
 constexpr float kListThrMax = 1.5e7f;     // what three fp16 parts against 2^8, 2^-3, 2^-14 can carry
+// Waves of a workgroup. With 4 the whole launch is on the chip at once and ends on the few workgroups of the outer shells, whose lists are the longest;
+// with 8 or 16 those start first and are shared by more.
+template <int D> constexpr int kListWaves = D == 4 ? 8 : 16;
+
 template <int D, bool WINDOWED>
-__global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
+__global__ __launch_bounds__(64 * kListWaves<D>, 4) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
                                                               uint32_t K, const char* __restrict__ operands, uint32_t ntiles,
                                                               const uint32_t* __restrict__ key_starts, CellHead* __restrict__ heads,
                                                               uint32_t N, WsHeader* hdr, uint16_t* __restrict__ lists,
@@ -363,14 +367,14 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
 {
     using L = Lists<D>;
     __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32], all_inner[32];
-    __shared__ uint2 queues[kWaves][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
-    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < 65536; i += gridDim.x * kThreads) {
+    __shared__ uint2 queues[kListWaves<D>][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
+    for (uint32_t i = blockIdx.x * (64 * kListWaves<D>) + threadIdx.x; i < 65536; i += gridDim.x * (64 * kListWaves<D>)) {
         hist[i] = 0;  // for the next E-step
         if (D == 8) queued_near[i] = 0;
     }
     if (!lists_exist(hdr)) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), h = lane >> 5, n = lane & 31;
-    const uint32_t p0 = blockIdx.x * 32;
+    const uint32_t p0 = (gridDim.x - 1 - blockIdx.x) * 32;
     const uint32_t pos = min(p0 + n, K - 1), c = cperm[pos];
     if (threadIdx.x < 32) {
         cnt1[threadIdx.x] = 0;
@@ -477,8 +481,8 @@ __global__ __launch_bounds__(kThreads, 4) void cell_lists_kernel(const float* __
             if constexpr (L::kCap2 > 0) put(outer, list + L::kCap1 + at2, list + L::kCap);
         }
     };
-    constexpr int U = 4;                        // tiles a wave takes at a time
-    constexpr uint32_t kStep = U * kWaves;
+    constexpr int U = D == 4 ? 1 : 2;           // tiles a wave takes at a time: at d = 4 a run has a few
+    constexpr uint32_t kStep = U * kListWaves<D>;
     uint32_t next = 0;
     for (uint32_t r = 0; r < nruns; ++r) {
         const uint32_t r0 = max(uint32_t(__builtin_amdgcn_readlane(int(run.x), int(r))), next);  // a tile on the border of
@@ -1274,7 +1278,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr,
                        drift, moves);
-    hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(kThreads), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
+    hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(64 * kListWaves<D>), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
                        w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist, w.cell_cursor);
     if (drift != nullptr) {   // (by cell where the moves were by centroid: those are in their places now)
         const uint32_t lds = (K + 7) / 8 * 16;
