@@ -747,7 +747,7 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 // ---- near vectors, d = 8: matrix cores over the list -----------------------------------------------------------------
 // A wave takes up to 64 vectors of one cell and works alone. The operands of the list's centroids (64 bytes each, one cache
 // line) are laid out for v_mfma_f32_16x16x32_f16: 32 k slots hold the 24 products of d = 8 and sigma ||c||^2, so that scores
-// need no accumulator to start from; the wave gathers them straight into registers. Four tiles of 16 centroids are folded
+// need no accumulator to start from; the wave gathers them through LDS. Four tiles of 16 centroids are folded
 // two and two row by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
 // instructions per 1024 scores. The winner is then known up to 2 centroids: two direct-form distances. What the tag costs
 // in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction is
@@ -968,6 +968,7 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     const uint32_t row0 = 4 * g;
     const bool f16 = a.hdr->x_not_f16 == 0;
     __shared__ f16x8 low[kVT * 64];   // other inputs: what a vector's operand has below its fp16 part
+    __shared__ f16x8 turn[4 * 64];   // the operands of a group of list entries
     f16x8 b[kVT];
     Scores s;
     clear_scores(s);
@@ -1001,31 +1002,38 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     // entries one group earlier; past the end, the operand that never wins
     {
         const uint32_t groups = (len + kGroup - 1) / kGroup, tiles = (n + 15) / 16;
-        uint32_t pos[4];
+        // Four neighbouring lanes to an operand of 64 bytes, which L1 serves at once, and through LDS to the lanes where the product wants the pieces, those of
+        // row r rotated so that eight lanes meet no bank twice. L1 was the bound while every lane loaded its piece of a row of its own: 56
+        // accesses a load, one each clock of the kernel. 29 M vectors, K = 65536: 1.40 and 1.43 ms (near and between r1 and r2) -> 1.27 and
+        // 1.27, 2.8 M 0.221 and 0.131 -> 0.204 and 0.112; of that, a half for one load of list entries per group in place of four.
+        const uint32_t row = lane >> 2, from = (lane ^ (row + (row >> 2))) & 3u, to_row = 4 * n16 + ((g ^ (n16 + (n16 >> 2))) & 3);
+        uint32_t pos = 0;   // of entry `lane` of a group
         f16x8 av[4];
         auto positions = [&](uint32_t gr) {
+            const uint32_t e = gr * kGroup + lane, at = entry(min(e, max(len, 1u) - 1u));
+            pos = e < len ? at : a.K;
+        };
+        auto gather = [&]() {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const uint32_t e = gr * kGroup + 16 * t + n16;
-                pos[t] = e < len ? entry(e) : a.K;
+                const char* operand = a.flat + size_t(uint32_t(__shfl(int(pos), 16 * t + int(row), 64))) * 64 + from * 16;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)operand, (__attribute__((address_space(3))) void*)(turn + t * 64), 16, 0,
+                                                 0);
             }
         };
-        auto gather = [&](f16x8 (&to)[4]) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) to[t] = *reinterpret_cast<const f16x8*>(a.flat + size_t(pos[t]) * 64 + g * 16);
-        };
         positions(0);
-        gather(av);
+        gather();
         positions(1);
         for (uint32_t gr = 0; gr < groups; ++gr) {
-            f16x8 an[4];
-            gather(an);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the operands have landed
+#pragma unroll
+            for (int t = 0; t < 4; ++t) av[t] = turn[t * 64 + to_row];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and are read before the next ones land there
+            gather();
             positions(gr + 2);
             if (!f16) score_group<4, true>(av, b, low + lane, row0, gr, minus_inf, s);
             else if (tiles <= 2) score_group<2, false>(av, b, low, row0, gr, minus_inf, s);
             else score_group<4, false>(av, b, low, row0, gr, minus_inf, s);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) av[t] = an[t];
         }
     }
     // ---- best, second best and group over the four lanes that share a vector; lane (n16, g) takes vector n16 of tile g
