@@ -291,11 +291,15 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
 }
 
 // Whether a fit by cells takes its first E-step by cells too, or by windows. At d = 8 those hold 66 % of the codebook (20 % with rows
-// of different scale), time that grows like N * K; the first way takes two more groupings and lists. 10 iterations, K = 65536, windows /
-// cells: N = 29 M 149.5 / 120.2 ms, with rows of different scale 151.0 / 138.0; 20 M, such rows 112.2 / 109.7; 15 M 82.8 / 74.3 and 87.0 /
-// 88.1; 8 M 53.6 / 50.7 and (20 iterations) 86.3 / 89.2; 2.8 M 28.1 / 29.0. At d = 4 the windows take 1.5 of 18 ms and the fit is no faster
-// without.
-bool cells_from_first(uint64_t N, uint32_t d, uint32_t K) { return d == 8 && N * K >= 1200000000000ull; }
+// of different scale), time that grows like N * K; the first way takes two more groupings and lists, time that grows like N and K * K. Windows / cells, ms,
+// K = 65536 unless said, the second pair with rows of different scale (0.3): N = 29 M, 10 iterations 149.5 / 120.2, 151.0 / 138.0 (with slower lists than now);
+// 15 M, 10 66.8 / 63.9; 5.4 M, 5 22.8 / 19.6, 10 31.9 / 32.0; 22 M, K = 16400, 5 36.2 / 32.5, 10 50.9 / 50.6; d = 7, 5.5 M, 5 18.7 / 14.8, 10
+// 24.8 / 23.0; d = 5, 15 M, K = 30000 18.0 / 17.1, 24.1 / 23.5. Below: 4.2 M, 5 18.9 / 16.9, 10 27.2 / 27.6 and 3 14.7 / 15.2; 27 M, K = 10000 38.9 / 37.9, 56.0 /
+// 57.9; d = 5, 5.5 M 9.2 / 9.2, 13.1 / 13.3. At d = 4 the windows take 1.5 of 18 ms and the fit is no faster without.
+bool cells_from_first(uint64_t N, uint32_t d, uint32_t d_caller, uint32_t K)
+{
+    return d == 8 && K >= 16384 && N * K >= (d_caller == 5 ? 450000000000ull : 350000000000ull);
+}
 
 // Iterations of a fit by cells that begin with grouping the vectors by their codes (anew): most codes change early, and a grouping costs
 // what one or two E-steps of that size do. 29 M vectors of 8 from the first iteration on: after 2 and 5 iterations 102 ms, 2 102, 4 104, 3 and
@@ -541,7 +545,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, n, D, K, w, true, s), "norm ordering");
     }
-    const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr, from_first = cells && cells_from_first(N, D, K);
+    const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr, from_first = cells && cells_from_first(N, D, d, K);
     for (int32_t t = 0; t < iters; ++t) {
         if (cells && (t > 0 || from_first)) {
             if (int rc = t == 0 ? run_cells_first_iter(cx, o.X, n, D, d, o.C_work, K, w, s)
