@@ -42,12 +42,12 @@ VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4   # wave-instructions/s: 1024 SIMDs, one 64-l
 # reads 44,300 KiB x 2 dispatches on FETCH_SIZE and writes 88,580 KiB x 2 on WRITE_SIZE).
 _KIB = 1024.0
 MEASURED_TRAFFIC_BYTES = {
-    ("cfg3_4096x11008_d4_k65536", "fit_estep_direct"): (180439 * 1.988 + 75087 * 0.994) * _KIB,   # near_direct_kernel, mean of 20 launches
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_direct"): (180173 * 1.988 + 74734 * 0.994) * _KIB,   # near_direct_kernel, mean of 20 launches
     # far_kernel (20 a fit) and assign_mfma_f16_kernel (2 a fit)
-    ("cfg3_4096x11008_d4_k65536", "fit_estep_f16"): ((20 * 15633 + 2 * 138677) * 1.988 + (20 * 10547 + 2 * 66377) * 0.994) / 22 * _KIB,
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_f16"): ((20 * 15476 + 2 * 132275) * 1.988 + (20 * 10073 + 2 * 66374) * 0.994) / 22 * _KIB,
     ("cfg3_4096x11008_d4_k65536", "estep_whole"): (283040 * 1.988 + 88480 * 0.994) * _KIB,
-    # slice_chunk_kernel, sliced_accumulate_kernel, sliced_finalize_kernel
-    ("cfg3_4096x11008_d4_k65536", "update"): ((110200 + 125100 + 22270) * 1.988 + (44230 + 37030 + 6294) * 0.994) * _KIB,
+    # record_chunk_kernel, sliced_accumulate_kernel, sliced_finalize_kernel
+    ("cfg3_4096x11008_d4_k65536", "update"): ((110152 + 55902 + 11032) * 1.988 + (110685 + 18489 + 4185) * 0.994) * _KIB,
     ("cfg3_4096x11008_d4_k65536", "decode"): (26120 * 1.988 + 176100 * 0.994) * _KIB,
 }
 

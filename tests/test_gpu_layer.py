@@ -153,7 +153,7 @@ def test_codebook_grad(cc, out_features, in_features, g, K, dt):
 def test_codebook_grad_of_a_large_16_bit_layer_is_summed_in_place(cc, out_features, in_features, g, K, dt):
     """From 2^20 sub-vectors on, a 16-bit gradient whose sub-vectors are whole runs of g numbers is read where it lies
     (no fp32 copy): the exact sums, rounded once, as for every other layer - also with codes beyond K (left out), with
-    a code array that is only 2-byte aligned (the copying route takes over) and on a second call."""
+    a code array that is only 2-byte aligned and on a second call."""
     rng = np.random.default_rng(out_features + in_features + g + K)
     G = _dev(rng.standard_normal((in_features, out_features)).astype(np.float32) * 1e-3, TORCH_DT[dt])
     n = L.num_codes(in_features, out_features, g)
@@ -184,7 +184,7 @@ def test_codebook_grad_of_a_large_16_bit_layer_is_summed_in_place(cc, out_featur
     # the same codes one element further on: 2-byte aligned only
     buf[1:] = torch.from_numpy(codes_np.view(np.int16)).cuda()
     out3 = torch.empty_like(out)
-    print("  the same through the copying route", flush=True)
+    print("  the same with 2-byte aligned codes", flush=True)
     cc.layer_codebook_grad(G, buf[1:].view(torch.uint16), K, g, out3, ws)
     assert torch.equal(out.view(torch.int32), out3.view(torch.int32))
 
