@@ -1,5 +1,6 @@
 // Internal declarations shared by the translation units of libcluscomp (not part of the public ABI).
 #pragma once
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -630,44 +631,74 @@ __device__ __forceinline__ float direct_sqdist(const float (&x)[D], const float 
 template <int D>
 __device__ __forceinline__ void load_row(const float* __restrict__ p, float (&v)[D]);
 
+// The value of lane V of a lane's four neighbours
+template <int V>
+__device__ __forceinline__ uint32_t of_quad(uint32_t v) { return uint32_t(__builtin_amdgcn_mov_dpp(int(v), V * 0x55, 0xf, 0xf, true)); }
+template <int V>
+__device__ __forceinline__ float of_quad(float v) { return __uint_as_float(of_quad<V>(__float_as_uint(v))); }
+
 // Index recovery of the matrix-core E-step: direct-form argmin over the codebook positions
 // 32*(group*GT+g) + 16*h + r, g in [g_begin, g_end), r in [0, 16), of a winning group (the two lanes that
 // share a vector split the group's tiles between them). `rows` holds the centroids in packed
 // order (the codebook itself, or its norm-ordered copy together with `cperm`, which maps a position
-// to the centroid index). Among exactly equal distances the lowest centroid index wins.
-// Rows are fetched U at a time so that U independent loads are in flight.
+// to the centroid index). Among exactly equal distances the lowest centroid index wins. Called by whole waves; neighbouring lanes have the same
+// range of tiles. Four lanes take the candidates of their four vectors one vector after the other, four neighbouring rows at a time, which are one or two accesses
+// of L1: with a lane to a vector every lane was one, and the windowed kernels, whose bound they were, made 0.9 per clock. Fits, ms: 29 M x 8, K = 65536
+// 92.0 -> 88.9; 1.7 M x 8, K = 2000 6.56 -> 6.16; 3 M x 16, K = 20000, 3 iterations 16.4 -> 14.7; 11 M x 4, K = 65536 13.1 -> 12.9.
 template <int D, int GT>
 __device__ __forceinline__ void recover_group(const float (&x)[D], const float* __restrict__ rows,
                                               const uint32_t* __restrict__ cperm, uint32_t K, uint32_t group, int h,
                                               int g_begin, int g_end, float& best_d, uint32_t& best_k)
 {
-    constexpr int U = D <= 8 ? 8 : 4;
-    float bd = INFINITY;
-    uint32_t bpos = 0;
-    for (int g = g_begin; g < g_end; ++g) {
-        const uint32_t k0 = 32 * (group * GT + g) + 16 * h;
+    const uint32_t in_quad = threadIdx.x & 3u, first = 32 * GT * group + 16 * uint32_t(h);
+    auto before = [&](uint32_t pos, uint32_t other) { return cperm != nullptr ? cperm[pos] < cperm[other] : pos < other; };   // among equal distances
+    float best = INFINITY;
+    uint32_t at = 0;
+    auto vector = [&](auto of) {
+        constexpr int V = decltype(of)::value;
+        float y[D];
 #pragma unroll
-        for (int r0 = 0; r0 < 16; r0 += U) {
-            float c[U][D];
+        for (int j = 0; j < D; ++j) y[j] = of_quad<V>(x[j]);
+        const uint32_t k0 = of_quad<V>(first) + in_quad;
+        float bd = INFINITY;
+        uint32_t bpos = 0;
+        for (int g = g_begin; g < g_end; ++g) {
+            float c[4][D];
 #pragma unroll
-            for (int u = 0; u < U; ++u) load_row<D>(rows + size_t(min(k0 + r0 + u, K - 1)) * D, c[u]);
+            for (int u = 0; u < 4; ++u) load_row<D>(rows + size_t(min(k0 + 32 * g + 4 * u, K - 1)) * D, c[u]);
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t pos = k0 + r0 + u;
-                const float dk = direct_sqdist<D>(x, c[u]);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t pos = k0 + 32 * g + 4 * u;
+                const float dk = direct_sqdist<D>(y, c[u]);
                 if (pos < K) {
                     if (dk < bd) {
                         bd = dk;
                         bpos = pos;
-                    } else if (dk == bd && cperm != nullptr && cperm[pos] < cperm[bpos]) {
+                    } else if (dk == bd && before(pos, bpos)) {
                         bpos = pos;  // exact tie in norm order: keep the lower centroid index
                     }
                 }
             }
         }
-    }
-    best_d = bd;
-    best_k = (cperm != nullptr && bd < INFINITY) ? cperm[min(bpos, K - 1)] : bpos;
+        auto meet = [&](auto ctrl) {   // with a neighbour's
+            const float od = __uint_as_float(uint32_t(__builtin_amdgcn_mov_dpp(int(__float_as_uint(bd)), decltype(ctrl)::value, 0xf, 0xf, true)));
+            const uint32_t opos = uint32_t(__builtin_amdgcn_mov_dpp(int(bpos), decltype(ctrl)::value, 0xf, 0xf, true));
+            if (od < bd || (od == bd && opos != bpos && before(opos, bpos))) {
+                bd = od;
+                bpos = opos;
+            }
+        };
+        meet(std::integral_constant<int, 0xb1>{});   // 1 0 3 2
+        meet(std::integral_constant<int, 0x4e>{});   // 2 3 0 1
+        best = in_quad == uint32_t(V) ? bd : best;
+        at = in_quad == uint32_t(V) ? bpos : at;
+    };
+    vector(std::integral_constant<int, 0>{});
+    vector(std::integral_constant<int, 1>{});
+    vector(std::integral_constant<int, 2>{});
+    vector(std::integral_constant<int, 3>{});
+    best_d = best;
+    best_k = (cperm != nullptr && best < INFINITY) ? cperm[min(at, K - 1)] : at;
 }
 
 template <int D>

@@ -30,3 +30,26 @@ def test_few_vectors_have_the_bits_of_the_direct_form(d, N, K, kind):
         torch.cuda.synchronize()
         out.append((c, idx.view(torch.int32), counts.view(torch.int32)))
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("d,N,K", [(4, 5003, 999), (4, 1200003, 9001), (6, 1100003, 1027), (8, 70001, 8195), (16, 40003, 515), (16, 2200003, 1000)])
+@pytest.mark.parametrize("apart", [1, 2, 4, 7])
+def test_among_equal_neighbours_the_lowest_index_wins(d, N, K, apart):
+    """Index recovery shares a group's candidates among four lanes: equal centroids in one lane's rows and in its neighbours'."""
+    import paper_2503_13089_amd as cc
+
+    gen = torch.Generator(device="cuda").manual_seed(N + K + apart)
+    x = torch.randn(N, d, device="cuda", generator=gen).mul_(0.02).half().float()
+    c = torch.randn(K, d, device="cuda", generator=gen).mul_(0.02).half().float()
+    n = (K - apart) // (2 * apart) * (2 * apart)
+    pairs = c[:n].view(-1, 2, apart, d)
+    pairs[:, 1] = pairs[:, 0]
+    ws = torch.empty(cc.workspace_bytes(N, d, K), dtype=torch.uint8, device="cuda")
+    out = []
+    for mode in (0, 1):
+        idx, j = torch.empty(N, dtype=torch.uint32, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+        print(f"equal neighbours d={d} N={N} K={K} apart={apart} mode={mode}", flush=True)
+        cc.assign(x, c, idx, j, ws, assign_mode=mode)
+        torch.cuda.synchronize()
+        out.append(idx.view(torch.int32))
+    assert torch.equal(*out)
