@@ -755,9 +755,9 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 // comes within the band is decided in direct form over the list, 64 centroids at a time.
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
-// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 2.1 ms + 1.4 ms per E-step that scores every vector, 1.1 to 2.0
-// + 1.2 to 1.6 ms with 0.38 to sort out those that need not be and 0.07 for the moves of the lists; N = 2.8 M: 0.21 ms +
-// 0.10 ms (0.27 + 0.14 with four waves to a workgroup), where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
+// Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 1.9 ms per E-step that scores every vector, 0.9 to 1.9
+// + 1.0 to 1.8 ms with 0.36 to sort out those that need not be and 0.07 for the moves of the lists; N = 2.8 M: 0.20 ms +
+// 0.09 ms, where the windowed kernel takes 53 ms and 1.6 ms. What bounds it is the chain of dependent loads of a wave (cell,
 // list, operands, scores, rows), so a wave works alone and keeps 64 vectors at four waves per SIMD: workgroups that shared
 // the list through LDS, 128 vectors per wave, took 6.1 to 7.8 ms for the same.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
