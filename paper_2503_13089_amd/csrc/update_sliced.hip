@@ -887,7 +887,7 @@ __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned 
 
 // Whether the rows go along (the head of this file says what it gives): there has to be room for as many ranges, or for the 8 that
 // one per XCD takes.
-template <int D, int SRC>
+template <int D>
 bool records_pay(uint32_t N, uint32_t K, bool fresh)
 {
     if (!fresh || update_one_slice(D, K)) return false;
@@ -945,7 +945,7 @@ hipError_t update_sliced_t(const void* X, uint32_t N, const void* idx, const flo
 {
     const Cut c = cut_of<D>(N, K);
     if constexpr (SRC != 0 || D == 4)
-        if (place.per_row != 0 || records_pay<D, SRC>(N, K, fresh))
+        if (place.per_row != 0 || records_pay<D>(N, K, fresh))
             return launch_t<D, SRC, true, true>(cut_of<D, true>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
     if (c.listed) return launch_t<D, SRC, true, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
     return launch_t<D, SRC, false, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
