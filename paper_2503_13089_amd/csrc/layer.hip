@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void layer_weight_vec_kernel(const u32x4*
 }
 
 // g = 4, no padding, 16-bit elements, by parts of the codebook. What bounds the general kernel is a line from L2 per code. Here a
-// workgroup (16 waves, one per compute unit) holds up to 44 codes and their rows per thread in registers; the parts of the codebook pass
+// workgroup (16 waves, one per compute unit) holds up to 38 codes and their rows per thread in registers; the parts of the codebook pass
 // through its LDS one after the other, every thread picks the rows that are there, and whole rows leave at the end, past the caches (plain
 // stores of more than the memory-side cache holds run at 2 TB/s). Bound: the parts' way into LDS (512 KB a workgroup and round at K = 65536) and
 // the lookups, 10 us of 35 each at 4096 x 11008, then the stores.
@@ -242,6 +242,7 @@ __global__ __launch_bounds__(kPartThreads, 4) void layer_weight_parts_kernel(con
                 if (rows % 2 != 0) reinterpret_cast<u32x2*>(smem)[rows - 1] = reinterpret_cast<const u32x2*>(from)[rows - 1];
                 reinterpret_cast<u32x2*>(smem)[rows] = u32x2{0u, 0u};
             }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what this wave requested has landed: the others read it behind the barrier
             __syncthreads();
             auto look = [&](auto first) {
 #pragma unroll
