@@ -1,5 +1,5 @@
 // M-step by cluster slices (Section 3.1: c_k <- mean of the vectors assigned to cluster k), for many vectors and
-// K <= 65536: two passes over the codes, no copy of the vectors.
+// K <= 65536: two passes over the codes; no copy of the vectors but the 16-bit one below.
 //
 // The K x (d sums + count) accumulators do not fit one workgroup's LDS, but a slice of them does (4096 clusters at
 // d = 4, 2048 at d = 8, 1024 at d = 16: 64-bit fixed-point sums, about 144 KB). So the clusters are cut into slices and
@@ -19,18 +19,17 @@
 // codes, both read in place and converted as they are fetched (SRC below).
 //
 // Rows of 8 to 32 bytes go along (record_chunk_kernel): what a chunk leaves for a slice are its rows as 16-bit numbers, read back in
-// sequence, instead of entries that name rows to be fetched from a line each. Taken for 16-bit gradients and for fp32 vectors of 4
+// sequence, instead of entries that name rows to be fetched from a line each. Taken for 16-bit gradients (records_pay says which) and for fp32 vectors of 4
 // whose chunk holds fp16 or bf16 numbers only (a compressed model's weights do); a chunk of other numbers leaves entries. fp32 vectors
 // of 8 and 16 keep the entries: at 32 bytes a row the second read costs less than writing the rows (28 M of 8 500 us with entries, 526
 // with rows).
 //
-// Bound, rows along: the passes over memory (chunk kernel 5.6 TB/s, 40 us for the gradient of 4096x11008, 61 for the vectors of 4), then
+// Bound, rows along: the passes over memory (chunk kernel 5.6 TB/s, 40 us for the gradient of 4096x11008, 55 for 11.3 M vectors of 4), then
 // 14 vector instructions per number for its fixed-point term (26 us) beside the records from memory (25 us) and the LDS atomics
 // (11 clocks a wave, 14 us). Slices of 2048 clusters at d = 4 then, half the partial sums of 4096. By entries: one row fetch per
 // vector from a different cache line each - the L1 fill rate - or, with few slices, the two passes over the rows.
-// By entries / rows along, a whole call: 11.3 M vectors of 4 at K = 65536 133 -> 109 us, K = 8192 (20 M) 199 -> 179, 1 M 35 -> 27; numbers that are
-// neither 134 -> 126 (20 M at K = 8192 200, as before, at 15000 219 -> 228); bf16 gradient of 4096x11008 108 -> 82, g = 8 85 -> 82, 1000x1111 41 -> 25. Through an fp32 copy / rows along: g = 6
-// 344 -> 143 us, g = 9 458 -> 187.
+// By entries / rows along, us a call, fp32 vectors of 4; numbers of fp16 or bf16 / of neither: 2 M, K = 12000 46 / 36 / 38; 11.3 M, K = 65536 123 / 103 / 118;
+// 20 M, K = 8192 181 / 158 / 188, K = 65536 229 / 172 / 224. 16-bit gradients through an fp32 copy / rows along: 4096x11008 g = 6 344 / 143, g = 9 458 / 187.
 // By entries only: 28 M of 8 at K = 65536 500 us, 6 M of 16 at K = 3000 189; one slice: 11.5 M of 4 at K = 300 106.
 #include <algorithm>
 #include <type_traits>
@@ -47,11 +46,16 @@ constexpr uint32_t kWorkgroups = 256;
 constexpr uint32_t kLeast = 32768;        // vectors; below, few memory-side atomics take no longer (20000 of 16 numbers: 33 and 36 us)
 constexpr int kChunkThreads = 512;        // for a chunk: finer grains than 1024, 4 M vectors are 585 chunks
 // Vectors sorted together. Records hold 10 (d = 4) to 34 bytes each in LDS, and this leaves room for two to four chunks on a compute unit.
-template <int D, bool RECORDS>
+template <int D, int RECORDS>
 constexpr uint32_t kChunkOf = RECORDS ? (D == 16 ? 1792 : 3584) : 7168;
-template <int D, bool RECORDS>
-constexpr int kChunkThreadsOf = RECORDS ? int(kChunkOf<D, true> / 7) : kChunkThreads;
+template <int D, int RECORDS>
+constexpr int kChunkThreadsOf = RECORDS ? int(kChunkOf<D, 1> / 7) : kChunkThreads;
 constexpr uint32_t kPosBits = 13;
+constexpr uint32_t kKindShift = 16, kStartMask = 0xffffu;   // where a slice starts in a chunk, and above it what the chunk left
+// Rows of fp32 with this many bytes of vectors ahead, or less, are read through the caches: where they do not go along, the second kernel begins with them.
+// All others are read past the caches, which leaves them to the records. 16-bit numbers / others, us a call, with 0, 128 MB and all through the caches: 11.3 M
+// vectors, K = 65536 102 / 140, 103 / 121, 103 / 118; 20 M 164 / 237, 172 / 224, 181 / 225.
+constexpr uint64_t kKeptRows = 128u << 20;
 constexpr uint32_t kCounters = 512;       // of a chunk: slices x 8 groups of positions x what is left for the lanes, so that
 constexpr uint32_t kGroups = 8;           // few of them take turns at one counter
 
@@ -104,9 +108,9 @@ __device__ __forceinline__ uint32_t code_at(const void* idx, size_t i)
 }
 
 // As many clusters as LDS holds, one workgroup per compute unit.
-template <int D, bool RECORDS = false>
+template <int D, int RECORDS = 0>
 struct Slice {
-    static constexpr uint32_t kBits = D == 4 ? (RECORDS ? 11u : 12u) : (D == 8 ? 11u : 10u);
+    static constexpr uint32_t kBits = D == 4 ? (RECORDS == 1 ? 11u : 12u) : (D == 8 ? 11u : 10u);
     static constexpr uint32_t kClusters = 1u << kBits;
     // sums of one component lie side by side; the two extra keep the lanes that share a row off one bank
     static constexpr uint32_t kPitch = kClusters + 2;
@@ -117,10 +121,10 @@ struct Slice {
 
 // What the input scan found in one chunk, and its codes >= K.
 struct ScanPart {
-    uint32_t absmax, flags, skipped;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input
-    uint32_t kind;                     // what lies in the chunk's part of the entry buffer: a Kind
+    uint32_t absmax, flags, skipped, pad;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input
 };
-// Entries (32 bits each), or the rows themselves as fp16 or bf16 numbers by slice, followed by their clusters within the slice (16 bits).
+// What lies in a chunk's part of the entry buffer, told beside where its slices start: entries (32 bits each), or the rows themselves as fp16
+// or bf16 numbers by slice, followed by their clusters within the slice (16 bits).
 enum Kind : uint32_t { kEntries = 0, kRowsF16 = 1, kRowsBf16 = 2 };
 template <int D>
 constexpr uint32_t kRecordBytes = 2 * D + 2;
@@ -132,12 +136,13 @@ constexpr uint32_t kRecordStep = kRecordRows<D> * (D == 16 ? 32 : 64);   // rows
 struct Cut {
     bool listed;
     uint32_t slices, chunks, ranges;
-    uint32_t sharers;   // waves that share a chunk's entries
+    uint32_t sharers;         // waves that share a chunk's entries, or rows
+    uint32_t entry_sharers;   // entries of a chunk whose rows could not go along
     size_t sum_bytes, part_bytes, entry_bytes, start_bytes;
 };
 
 // The record buffer (2 N records) holds it all; ranges = 0: not even one range of partial sums fits.
-template <int D, bool RECORDS = false>
+template <int D, int RECORDS = 0>
 Cut cut_of(uint32_t N, uint32_t K)
 {
     constexpr uint32_t kChunk = kChunkOf<D, RECORDS>;
@@ -156,6 +161,10 @@ Cut cut_of(uint32_t N, uint32_t K)
     c.ranges = std::min({std::max(kWorkgroups / c.slices, 1u), c.chunks, fit});
     c.sharers = 1;
     while (c.sharers < uint32_t(kWaves) && c.sharers * (RECORDS ? kRecordStep<D> : 128u) < kChunk / c.slices) c.sharers *= 2;
+    // With as many waves to the entries of these shorter chunks as to their rows each had one batch of 64, and waited for where they begin as often as
+    // for them (11.3 M vectors, K = 12000: the sums 65 us instead of 55).
+    c.entry_sharers = RECORDS ? 1 : c.sharers;
+    while (RECORDS && c.entry_sharers < uint32_t(kWaves) && c.entry_sharers * 512 < kChunk / c.slices) c.entry_sharers *= 2;
     c.sum_bytes = align256(per_range * c.ranges);
     return c;
 }
@@ -342,7 +351,7 @@ __global__ __launch_bounds__(kChunkThreads) void slice_chunk_kernel(const void* 
     __syncthreads();
     if (FRESH && threadIdx.x == 0) {
         scan.m = red[0];
-        parts[blockIdx.x] = ScanPart{scan.absmax(), red[1], red[2], kEntries};
+        parts[blockIdx.x] = ScanPart{scan.absmax(), red[1], red[2], 0u};
     }
     if constexpr (LISTED) {
         if (threadIdx.x < 64) counts_to_places(count, total);
@@ -369,14 +378,14 @@ struct RowPlace {
 // One chunk whose rows go along: as slice_chunk_kernel<FRESH, LISTED>, but what it leaves for a slice are the rows themselves,
 // 16-bit numbers, and their clusters. fp32 rows (SRC 0) do where all numbers of the chunk are fp16 numbers, or all of them bf16 ones;
 // a chunk of others leaves entries. The rows are read once, coalesced, and held in registers until their places are known.
-template <int D, int SRC, bool WHOLE>
-__global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void record_chunk_kernel(const void* __restrict__ X, const void* __restrict__ idx, uint32_t N,
+template <int D, int SRC, bool WHOLE, int RECORDS>
+__global__ __launch_bounds__((kChunkThreadsOf<D, 1>), (D == 8 ? 4 : 1)) void record_chunk_kernel(const void* __restrict__ X, const void* __restrict__ idx, uint32_t N,
                                                                                 uint32_t K, uint32_t slices, RowPlace place,
                                                                                 ScanPart* __restrict__ parts, char* __restrict__ records,
                                                                                 uint32_t* __restrict__ starts)
 {
-    using S = Slice<D, true>;
-    constexpr uint32_t kChunk = kChunkOf<D, true>, T = kChunkThreadsOf<D, true>;
+    using S = Slice<D, RECORDS>;
+    constexpr uint32_t kChunk = kChunkOf<D, 1>, T = kChunkThreadsOf<D, 1>;
     constexpr int U = kChunk / T;
     static_assert(kChunk % T == 0 && (SRC != 0 || WHOLE), "whole rounds");
     typedef uint32_t Words __attribute__((ext_vector_type(D == 4 ? 2 : 4)));   // a piece of a record
@@ -386,7 +395,8 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     __shared__ uint32_t total, red[3];
     const uint32_t first = blockIdx.x * kChunk, n = min(kChunk, N - first);
     const uint32_t log_lanes = slices == 1 ? 6u : 6 - (32 - __clz(slices - 1)), sub = threadIdx.x & ((1u << log_lanes) - 1);
-    uint32_t code[U], rank[U], raw[U][D / 2];   // 16-bit numbers: of fp32 rows the fp16 ones
+    constexpr int kWords = SRC == 0 ? D : D / 2;
+    uint32_t code[U], rank[U], raw[U][kWords];   // the numbers as they are
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t p = u * T + threadIdx.x;
@@ -398,32 +408,28 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     auto row_at = [&](int u) { return size_t(first) + min(uint32_t(u * T + threadIdx.x), n - 1); };
     RowScan<SRC> scan;
     if constexpr (SRC == 0) {
-        constexpr int kAtOnce = D == 4 ? U : 4;   // rows in registers as they are
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        auto rows = [&](auto load) {
 #pragma unroll
-        for (int u0 = 0; u0 < U; u0 += kAtOnce) {
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            u32x4 t[kAtOnce][D / 4];
-#pragma unroll
-            for (int v = 0; v < kAtOnce && u0 + v < U; ++v)
-#pragma unroll
-                for (int q = 0; q < D / 4; ++q) t[v][q] = __builtin_nontemporal_load(static_cast<const u32x4*>(X) + row_at(u0 + v) * (D / 4) + q);
-#pragma unroll
-            for (int v = 0; v < kAtOnce && u0 + v < U; ++v) {
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int q = 0; q < D / 4; ++q) {
-                    const u32x4 w = t[v][q];
-                    uint16_t h[4];
+                    const u32x4 t = load(static_cast<const u32x4*>(X) + row_at(u) * (D / 4) + q);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const _Float16 half = _Float16(__uint_as_float(w[j]));
-                        h[j] = __builtin_bit_cast(uint16_t, half);
-                        scan.look(w[j], float(half));
-                    }
-                    raw[u0 + v][2 * q] = uint32_t(h[0]) | uint32_t(h[1]) << 16;
-                    raw[u0 + v][2 * q + 1] = uint32_t(h[2]) | uint32_t(h[3]) << 16;
+                    for (int j = 0; j < 4; ++j) raw[u][4 * q + j] = t[j];
                 }
-            }
+        };
+        if ((N - first) * uint64_t(D * 4) > kKeptRows) {
+            asm volatile("");   // else the compiler makes one plain load of the two
+            rows([](const u32x4* p) { return __builtin_nontemporal_load(p); });
+            asm volatile("");
+        } else {
+            rows([](const u32x4* p) { return *p; });
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < D; ++j) scan.look(raw[u][j], float(_Float16(__uint_as_float(raw[u][j]))));
     } else {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -452,9 +458,10 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     if (flags & 2u) {   // what is not finite has no magnitude
         Scan<SRC> again;
         if constexpr (SRC == 0) {
-#pragma unroll 1
+#pragma unroll
             for (int u = 0; u < U; ++u)
-                for (int q = 0; q < D; ++q) again.look(static_cast<const uint32_t*>(X)[row_at(u) * D + q]);
+#pragma unroll
+                for (int j = 0; j < D; ++j) again.look(raw[u][j]);
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -508,14 +515,14 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     if (threadIdx.x == 0) {
         Scan<SRC> whole;
         whole.m = red[0];
-        parts[blockIdx.x] = ScanPart{whole.absmax(), found & 3u, red[2], kind};
+        parts[blockIdx.x] = ScanPart{whole.absmax(), found & 3u, red[2], 0u};
     }
     if (threadIdx.x < 64) counts_to_places(count, total);
     __syncthreads();
     const uint32_t members = total;
     if (threadIdx.x <= slices)   // the first counter of a slice
         starts[size_t(blockIdx.x) * (slices + 1) + threadIdx.x] =
-            threadIdx.x < slices ? count[keep_order ? threadIdx.x << 6 : (threadIdx.x * kGroups) << log_lanes] : members;
+            (threadIdx.x < slices ? count[keep_order ? threadIdx.x << 6 : (threadIdx.x * kGroups) << log_lanes] : members) | kind << kKindShift;
     char* out = records + size_t(blockIdx.x) * (kChunk * kRecordBytes<D>);
     uint16_t* clusters = reinterpret_cast<uint16_t*>(sorted + kChunk * (2 * D));
     if (SRC == 0 && kind == kEntries) {
@@ -531,14 +538,19 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, true>), (D == 8 ? 4 : 1)) void 
     for (int u = 0; u < U; ++u) {
         if (code[u] >= K) continue;
         const uint32_t at = count[counter(code[u], u)] + rank[u];
-        if (SRC == 0 && kind == kRowsBf16) {   // the fp32 row once more, from L2
+        uint32_t row[D / 2];
 #pragma unroll
-            for (int q = 0; q < D / 2; ++q) {
-                const uint2 t = static_cast<const uint2*>(X)[row_at(u) * (D / 2) + q];
-                raw[u][q] = (t.x >> 16) | (t.y & 0xffff0000u);
+        for (int q = 0; q < D / 2; ++q) {
+            if constexpr (SRC != 0) {
+                row[q] = raw[u][q];
+            } else if (kind == kRowsBf16) {
+                row[q] = (raw[u][2 * q] >> 16) | (raw[u][2 * q + 1] & 0xffff0000u);
+            } else {
+                const _Float16 lo = _Float16(__uint_as_float(raw[u][2 * q])), hi = _Float16(__uint_as_float(raw[u][2 * q + 1]));
+                row[q] = uint32_t(__builtin_bit_cast(uint16_t, lo)) | uint32_t(__builtin_bit_cast(uint16_t, hi)) << 16;
             }
         }
-        __builtin_memcpy(__builtin_assume_aligned(sorted + at * (2 * D), D == 4 ? 8 : 16), raw[u], 2 * D);
+        __builtin_memcpy(__builtin_assume_aligned(sorted + at * (2 * D), D == 4 ? 8 : 16), row, 2 * D);
         clusters[at] = uint16_t(code[u] & (S::kClusters - 1));
     }
     __syncthreads();
@@ -564,14 +576,13 @@ __device__ __forceinline__ bool job_of_workgroup(uint32_t slices, uint32_t range
 // The records of a slice in the chunks of a range, added into the accumulators. A unit of a wave is its share of one chunk's run;
 // where the runs begin is loaded for 64 units at once, a lane each, and the records of the next step (kStep rows) before those of
 // this one are added.
-template <int D, int SRC>
+template <int D, int SRC, int RECORDS>
 __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* cnt, int e, uint32_t slice, uint32_t slices,
                                             uint32_t range, uint32_t ranges, uint32_t chunks, uint32_t sharers,
-                                            const ScanPart* __restrict__ parts, const char* __restrict__ records,
-                                            const uint32_t* __restrict__ starts)
+                                            const char* __restrict__ records, const uint32_t* __restrict__ starts)
 {
-    using S = Slice<D, true>;
-    constexpr uint32_t kChunk = kChunkOf<D, true>;
+    using S = Slice<D, RECORDS>;
+    constexpr uint32_t kChunk = kChunkOf<D, 1>;
     constexpr int n = D < 8 ? D : 8, P = D / n, U = kRecordRows<D>;   // numbers of a lane, lanes of a row, rows of a lane
     constexpr uint32_t R = 64 / P, kStep = U * R;
     static_assert(kStep == kRecordStep<D>);
@@ -589,9 +600,9 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
         if (mine_done < chunks) {
             const uint32_t chunk = chunks - 1 - uint32_t(mine_done);
             const uint32_t* at = starts + size_t(chunk) * (slices + 1) + slice;
-            run_kind = parts[chunk].kind;
-            run_begin = at[0];
-            run_end = run_kind == kEntries ? run_begin : at[1];
+            run_kind = at[0] >> kKindShift;
+            run_begin = at[0] & kStartMask;
+            run_end = run_kind == kEntries ? run_begin : at[1] & kStartMask;
         }
     };
     look_ahead();
@@ -670,12 +681,12 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
     }
 }
 
-// LISTED: by entry lists; otherwise (one slice) the codes themselves, in their order. RECORDS: by what record_chunk_kernel left.
-template <int D, int SRC, bool LISTED, bool RECORDS>
+// LISTED: by entry lists; otherwise (one slice) the codes themselves, in their order. RECORDS: by what record_chunk_kernel left (2: in wide slices).
+template <int D, int SRC, bool LISTED, int RECORDS>
 __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void* __restrict__ X, uint32_t N, const void* __restrict__ idx,
                                                                      uint32_t K, uint32_t slices, uint32_t chunks, uint32_t ranges,
-                                                                     uint32_t sharers, WsHeader* hdr, const ScanPart* __restrict__ parts,
-                                                                     const uint32_t* __restrict__ entries,
+                                                                     uint32_t sharers, uint32_t entry_sharers, WsHeader* hdr,
+                                                                     const ScanPart* __restrict__ parts, const uint32_t* __restrict__ entries,
                                                                      const uint32_t* __restrict__ starts,
                                                                      unsigned long long* __restrict__ part_sums,
                                                                      uint32_t* __restrict__ part_counts)
@@ -732,7 +743,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
     const bool finite = (flags & 2u) == 0;   // otherwise every number is looked at
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (RECORDS)
-        add_records<D, SRC>(sum, cnt, e, slice, slices, range, ranges, chunks, sharers, parts,
+        add_records<D, SRC, RECORDS>(sum, cnt, e, slice, slices, range, ranges, chunks, sharers,
                             reinterpret_cast<const char*>(entries), starts);
     uint32_t bad = 0;
     auto add_entries = [&](auto all_finite) {
@@ -749,22 +760,23 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
         if (kCounted && piece == 0) atomicAdd(&cnt[c], 1u);
     };
     // Range r takes every ranges-th chunk, from the last one down - what the previous kernel read last is still in the
-    // memory-side cache - kWaves / sharers of them at a time: the workgroups of all slices of a range then work within a
+    // memory-side cache - kWaves / entry_sharers of them at a time: the workgroups of all slices of a range then work within a
     // window of X that their L2 holds. The entries of a wave's next batch are requested before the rows of this one, and
     // those before the ones of the last are added.
-    uint32_t done = range + ranges * (wave / sharers), first = 0, i0 = 0, end = 0;   // chunks above the current one
+    uint32_t done = range + ranges * (wave / entry_sharers), first = 0, i0 = 0, end = 0;   // chunks above the current one
     size_t entries_at = 0;
     constexpr uint32_t kEntryPitch = RECORDS ? kChunk * kRecordBytes<D> / 4 : kChunk;
-    const uint32_t step = ranges * (kWaves / sharers);
+    const uint32_t step = ranges * (kWaves / entry_sharers);
     auto open = [&]() {   // first batch at or after `done`
         for (; done < chunks; done += step) {
             const uint32_t chunk = chunks - 1 - done;
-            if (RECORDS && parts[chunk].kind != kEntries) continue;
             const uint32_t* at = starts + size_t(chunk) * (slices + 1) + slice;
             first = chunk * kChunk;
             entries_at = size_t(chunk) * kEntryPitch;
             end = LISTED ? at[1] : min(kChunk, N - first);
-            i0 = (LISTED ? at[0] : 0u) + wave % sharers * (U * 64 / P);
+            i0 = LISTED ? at[0] : 0u;
+            if (RECORDS && i0 >> kKindShift != kEntries) continue;
+            i0 += wave % entry_sharers * (U * 64 / P);
             if (i0 < end) return;
         }
     };
@@ -801,7 +813,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
                 if (piece == 0) ++bad;
             }
         }
-        i0 += sharers * (U * 64 / P);
+        i0 += entry_sharers * (U * 64 / P);
         if (i0 >= end) {
             done += step;
             open();
@@ -842,7 +854,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
 // finishes 64 neighbouring clusters of one component, its waves take turns at the ranges (one thread per cluster and
 // component waited 75 us for 256 ranges at K = 1024). COUNTED is known to the compiler: with a branch around each count the loads
 // of a wave went out one by one (256 ranges of one slice 8.3 us instead of 5.6).
-template <int D, int W, bool RECORDS, bool COUNTED>
+template <int D, int W, int RECORDS, bool COUNTED>
 __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned long long* __restrict__ part_sums,
                                                                    const uint32_t* __restrict__ part_counts, uint32_t ranges,
                                                                    const float* prev, float* out, uint32_t* counts_out, uint32_t K,
@@ -892,10 +904,17 @@ template <int D>
 bool records_pay(uint32_t N, uint32_t K, bool fresh)
 {
     if (!fresh || update_one_slice(D, K)) return false;
-    return cut_of<D, true>(N, K).ranges >= std::min(cut_of<D>(N, K).ranges, 8u);
+    return cut_of<D, 1>(N, K).ranges >= std::min(cut_of<D>(N, K).ranges, 8u);
 }
 
-template <int D, int SRC, bool LISTED, bool RECORDS>
+// Rows that go along take slices as wide as entries do (RECORDS = 2) for many fp32 vectors of 6 to 8 narrow slices: where a chunk's numbers turn out to
+// have no 16 bits, every line is fetched by as many workgroups as there are slices. us a call by entries / narrow / wide, numbers without 16 bits: K = 15000:
+// 11.3 M 118 / 119 / 114, 14 M 144 / 148 / 140, 28 M 282 / 302 / 276; K = 12000: 20 M 193 / 204 / 197. 16-bit numbers pay for twice the partial sums: K = 15000:
+// 11.3 M 117 / 99 / 104, 20 M 201 / 162 / 169, 28 M 282 / 223 / 226. Beside these K the others lose little or nothing: 20 M, K = 5000 207 / 194 / 219, K = 8192
+// 181 / 188 / 187, K = 9000 210 / 211 / 214, K = 20000 226 / 214 / 207 (16-bit ones 226 / 173 / 180).
+bool wide_records_pay(uint32_t N, uint32_t K) { return N > 3u << 22 && K > 5 * Slice<4, 1>::kClusters && K <= 8 * Slice<4, 1>::kClusters; }
+
+template <int D, int SRC, bool LISTED, int RECORDS>
 hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, const float* prev, uint32_t K, float* out,
                     uint32_t* counts_out, const Workspace& w, bool mean, bool fresh, const RowPlace& place, hipStream_t s)
 {
@@ -911,15 +930,15 @@ hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, co
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(S::kLdsBytes)); e != hipSuccess)
         return e;
     if constexpr (RECORDS) {
-        const dim3 threads(kChunkThreadsOf<D, true>);
+        const dim3 threads(kChunkThreadsOf<D, 1>);
         char* records = reinterpret_cast<char*>(entries);
         if constexpr (SRC != 0) {
             if (place.per_row != 0)
-                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, false>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, false, RECORDS>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
             else
-                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+                hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true, RECORDS>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
         } else {
-            hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
+            hipLaunchKernelGGL((record_chunk_kernel<D, SRC, true, RECORDS>), dim3(c.chunks), threads, 0, s, X, idx, N, K, c.slices, place, parts, records, starts);
         }
     } else if (fresh)
         hipLaunchKernelGGL((slice_chunk_kernel<D, SRC, true, LISTED>), dim3(c.chunks), dim3(kChunkThreads), 0, s, X, idx, N, K, c.slices, w.hdr,
@@ -928,7 +947,7 @@ hipError_t launch_t(const Cut& c, const void* X, uint32_t N, const void* idx, co
         hipLaunchKernelGGL((slice_chunk_kernel<D, SRC, false, true>), dim3(c.chunks), dim3(kChunkThreads), 0, s, X, idx, N, K, c.slices, w.hdr,
                            parts, entries, starts);
     hipLaunchKernelGGL((sliced_accumulate_kernel<D, SRC, LISTED, RECORDS>), dim3(8 * ((jobs + 7) / 8)), dim3(kThreads), S::kLdsBytes, s, X, N, idx,
-                       K, c.slices, c.chunks, c.ranges, c.sharers, w.hdr, fresh ? parts : nullptr, entries, starts, part_sums, part_counts);
+                       K, c.slices, c.chunks, c.ranges, c.sharers, c.entry_sharers, w.hdr, fresh ? parts : nullptr, entries, starts, part_sums, part_counts);
     const uint32_t width = place.per_row != 0 ? place.g : D;   // of a row of the result
     const dim3 done((K + 63) / 64 * width);
     if (c.ranges > 32)
@@ -946,10 +965,14 @@ hipError_t update_sliced_t(const void* X, uint32_t N, const void* idx, const flo
 {
     const Cut c = cut_of<D>(N, K);
     if constexpr (SRC != 0 || D == 4)
-        if (place.per_row != 0 || records_pay<D>(N, K, fresh))
-            return launch_t<D, SRC, true, true>(cut_of<D, true>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
-    if (c.listed) return launch_t<D, SRC, true, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
-    return launch_t<D, SRC, false, false>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+        if (place.per_row != 0 || records_pay<D>(N, K, fresh)) {
+            if constexpr (SRC == 0)
+                if (wide_records_pay(N, K))
+                    return launch_t<D, SRC, true, 2>(cut_of<D, 2>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+            return launch_t<D, SRC, true, 1>(cut_of<D, 1>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+        }
+    if (c.listed) return launch_t<D, SRC, true, 0>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
+    return launch_t<D, SRC, false, 0>(c, X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);
 }
 
 }  // namespace
@@ -994,7 +1017,7 @@ hipError_t sum_rows16_t(const void* grad, int dtype, uint32_t N, uint32_t out_fe
 bool sum_rows16_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w)
 {
     if (!update_sliced_applies(N, d, K, w)) return false;
-    return (d == 4 ? cut_of<4, true>(N, K).ranges : (d == 8 ? cut_of<8, true>(N, K).ranges : cut_of<16, true>(N, K).ranges)) > 0;
+    return (d == 4 ? cut_of<4, 1>(N, K).ranges : (d == 8 ? cut_of<8, 1>(N, K).ranges : cut_of<16, 1>(N, K).ranges)) > 0;
 }
 
 hipError_t launch_sum_rows16(const void* grad, int dtype, uint32_t N, uint32_t out_features, uint32_t g, const uint16_t* codes, uint32_t K,
