@@ -899,12 +899,17 @@ __global__ __launch_bounds__(64 * W) void sliced_finalize_kernel(const unsigned 
 }
 
 // Whether the rows go along (the head of this file says what it gives): there has to be room for as many ranges, or for the 8 that
-// one per XCD takes.
-template <int D>
+// one per XCD takes. 16-bit rows of 8 and 16 at aligned places: up to 2^24 numbers, and at 8 with slices of which an XCD does not hold whole ranges (entries
+// of one range then come through two L2s). bf16, by entries / rows along, us: g = 16: 4096x6144, K = 4096 49 / 52, 4096x8192 55 / 62 to 75 / 82, 8192x14336
+// 124 / 171 to 167 / 204 (up to 4096x4096, by entries with the last kernel of before: 46 / 43, 63 / 62); g = 8: 4096x11008, K = 4096 69 / 73, K = 20000 75 / 79,
+// K = 35000 78 / 81, 8192x14336, K = 4096 129 / 172, K = 20000 172 / 180, K = 35000 181 / 178; with that last kernel K = 50000 212 / 198, K = 45000 194 / 188.
+template <int D, int SRC>
 bool records_pay(uint32_t N, uint32_t K, bool fresh)
 {
     if (!fresh || update_one_slice(D, K)) return false;
-    return cut_of<D, 1>(N, K).ranges >= std::min(cut_of<D>(N, K).ranges, 8u);
+    const Cut c = cut_of<D, 1>(N, K);
+    if (D >= 8 && SRC != 0 && uint64_t(N) * D > 1u << 24 && !(D == 8 && c.slices > 20 && c.slices < 32)) return false;
+    return c.ranges >= std::min(cut_of<D>(N, K).ranges, 8u);
 }
 
 // Rows that go along take slices as wide as entries do (RECORDS = 2) for many fp32 vectors of 6 to 8 narrow slices: where a chunk's numbers turn out to
@@ -965,7 +970,7 @@ hipError_t update_sliced_t(const void* X, uint32_t N, const void* idx, const flo
 {
     const Cut c = cut_of<D>(N, K);
     if constexpr (SRC != 0 || D == 4)
-        if (place.per_row != 0 || records_pay<D>(N, K, fresh)) {
+        if (place.per_row != 0 || records_pay<D, SRC>(N, K, fresh)) {
             if constexpr (SRC == 0)
                 if (wide_records_pay(N, K))
                     return launch_t<D, SRC, true, 2>(cut_of<D, 2>(N, K), X, N, idx, prev, K, out, counts_out, w, mean, fresh, place, s);

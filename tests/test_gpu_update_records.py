@@ -85,3 +85,22 @@ def test_rows_past_the_caches_and_in_wide_slices(N, K):
     want = torch.ldexp(sums.double(), torch.tensor(float(-e), device="cuda")) / n.clamp(min=1)[:, None]
     assert torch.equal(counts.view(torch.int32).long(), n)
     assert torch.equal(out.cpu(), torch.where((n > 0)[:, None], want, prev.double()).float().cpu())
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("in_features,out_features,gl,K", [(1024, 16384, 16, 4096), (1024, 16400, 16, 4096), (2049, 8192, 16, 65536), (2048, 8192, 8, 4097), (2049, 8192, 8, 4097),
+                                                           (2049, 8192, 8, 40960), (2049, 8192, 8, 40961), (2049, 8192, 8, 63489)])
+def test_16_bit_gradients_on_either_side_of_2_24_numbers(dt, in_features, out_features, gl, K):
+    """Rows of 8 and 16 go along up to 2^24 numbers, and at 8 with 21 to 31 slices; otherwise entries are left. Numbers whose sums are exact in fp32."""
+    import paper_2503_13089_amd as cc
+
+    gen = torch.Generator(device="cuda").manual_seed(out_features + K)
+    n = L.num_codes(in_features, out_features, gl)
+    G = torch.randint(-127, 128, (in_features, out_features), device="cuda", generator=gen).double().mul_(2.0 ** -18)
+    idx = torch.randint(0, K, (n,), device="cuda", generator=gen)
+    codes = idx.to(torch.int32).to(torch.int16).view(torch.uint16)
+    out, ws = torch.full((K, gl), 3.0, device="cuda"), torch.empty(cc.workspace_bytes(max(n, K), gl, K), dtype=torch.uint8, device="cuda")
+    print(f"gradient at 2^24 numbers {in_features}x{out_features} g={gl} K={K} {dt}", flush=True)
+    cc.layer_codebook_grad(G.to(dt), codes, K, gl, out, ws)
+    want = torch.zeros(K, gl, dtype=torch.float64, device="cuda").index_add_(0, idx, G.view(n, gl))
+    assert torch.equal(out.cpu(), want.float().cpu())
