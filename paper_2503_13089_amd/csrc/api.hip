@@ -296,6 +296,8 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
 // 15 M, 10 66.8 / 63.9; 5.4 M, 5 22.8 / 19.6, 10 31.9 / 32.0; 22 M, K = 16400, 5 36.2 / 32.5, 10 50.9 / 50.6; d = 7, 5.5 M, 5 18.7 / 14.8, 10
 // 24.8 / 23.0; d = 5, 15 M, K = 30000 18.0 / 17.1, 24.1 / 23.5. Below: 4.2 M, 5 18.9 / 16.9, 10 27.2 / 27.6 and 3 14.7 / 15.2; 27 M, K = 10000 38.9 / 37.9, 56.0 /
 // 57.9; d = 5, 5.5 M 9.2 / 9.2, 13.1 / 13.3. At d = 4 the windows take 1.5 of 18 ms and the fit is no faster without.
+// Inputs that are no fp16 numbers have their far vectors scored on the fp32 matrix cores: d = 5, 15 M, K = 30000, 10 74.7 / 79.3, 22 M, K = 45000 127.1 / 136.3 (fp16
+// numbers 33.1 / 31.4); d = 6, 15 M, K = 30000 and with slower lists 109 / 88, d = 8 153 / 122.
 bool cells_from_first(uint64_t N, uint32_t d, uint32_t d_caller, uint32_t K)
 {
     return d == 8 && K >= 16384 && N * K >= (d_caller == 5 ? 450000000000ull : 350000000000ull);
@@ -594,7 +596,7 @@ int cc_assign_ex(const float* vectors, uint64_t N, uint32_t d, const float* cent
     Operands o;
     if (int rc = enter(vectors, centroids, nullptr, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool small = use_small(cx, N, K, 1, w);
+    const bool small = use_small(cx, N, K, 1, w) && cc::small_assign_pays(N, w.d, K);
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, w.d, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);

@@ -224,17 +224,24 @@ hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K,
 
 // Where this form is the fastest: the accumulators fit LDS, and the distances cost less in direct form than what the
 // matrix-core form pays in launches, latency and the M-step. Below 128 centroids the E-step is in direct form anyway. Fits of 10
-// iterations, us, matrix-core form (its own choice of windows) / this one: d = 4: K = 140: N = 260000 515 / 236, 10 M 6766 / 4023; K = 250: 10 M 8997 /
-// 6899; K = 500: 260000 570 / 509, 520000 863 / 852; K = 700: 132000 481 / 606, 330000 693 / 1042; K = 900: 33000 389 / 269, 40000
-// 368 / 323, 66000 428 / 463; d = 8: K = 140: 4 M 5596 / 2853; K = 390:
-// 4.5 M 9297 / 8250; K = 500: 260000 852 / 779; K = 700: 66000 516 / 595, 132000 678 / 955; d = 16: K = 250: 2.5 M 9608 / 5412; K = 300: 430000 2072 / 1424.
+// iterations, us, matrix-core form (its own choice of windows) / this one, inputs that are fp16 numbers: d = 4: K = 140: N = 260000 515 / 236, 10 M 6766 / 4023;
+// K = 250: 10 M 8997 / 6899; K = 500: 260000 570 / 509, 520000 863 / 852; d = 8: K = 140: 4 M 5596 / 2853; K = 390: 4.5 M 9297 / 8250; K = 500: 260000 852 / 779;
+// d = 16: K = 250: 2.5 M 9608 / 5412; K = 300: 430000 2072 / 1424. From 512 centroids on what counts is how N falls into groups of 64 for 512
+// workgroups, and the kind of the inputs, which nobody knows here: those that are no fp16 numbers go through the fp32 matrix cores. fp16 numbers / others: d = 4:
+// K = 513: 131072 396 / 331, 529 / 338, 230000 512 / 501, 615 / 511; K = 600: 131072 399 / 376, 530 / 382, 131200 428 / 530, 587 / 536, 230000 514 / 571,
+// 613 / 581; K = 800: 131072 405 / 444, 561 / 452; K = 900: 60000 367 / 326, 548 / 329, 131072 408 / 503, 563 / 509; K = 1000: 60000 365 / 357, 547 / 359; d = 8:
+// K = 513: 131072 510 / 505, 694 / 519, 160000 571 / 770, 842 / 791; K = 600: 110000 505 / 554, 685 / 563; K = 700: 55000 439 / 398, 672 / 402, 131072 518 / 622,
+// 703 / 637.
 bool small_problem(uint64_t N, uint32_t d, uint32_t K)
 {
     if (lds_bytes(d, K) > kMaxLds || N >= (1ull << 31)) return false;
     if (K < (d == 4 ? 256u : 400u)) return true;
-    const uint64_t limit = d == 4 ? (K <= 512 ? 1ull << 28 : 3ull << 24) : (d == 8 && K > 512 ? 1ull << 25 : 1ull << 27);
-    return N * K <= limit;
+    if (K <= (d == 4 ? 560u : 512u)) return N * K <= (d == 4 ? 1ull << 28 : 1ull << 27);
+    return (N <= (1u << 16) && N * K <= (1ull << 26)) || (N <= (1u << 17) && K <= (d == 4 ? 832u : 608u));
 }
+
+// An E-step alone (us, fp16 numbers, others): d = 8, K = 340: 4 M 688 / 556, 578 / 595; K = 370: 720 / 604, 584 / 644; K = 399: 731 / 648, 587 / 690.
+bool small_assign_pays(uint64_t N, uint32_t d, uint32_t K) { return d != 8 || K <= 368 || N * K <= (1ull << 27); }
 
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K)
 {
