@@ -67,17 +67,17 @@ typedef enum cc_status {
  *   CC_ASSIGN_AUTO        for K >= 128 the matrix cores - the fp16 MFMA with the centroids split into fp16 parts
  *                         (exact products, fp32 accumulation) when every input is an fp16 number, the fp32 MFMA
  *                         otherwise, both with a rounding guard band + direct-form refinement - and the direct form
- *                         on the vector ALUs for smaller K. For K >= 8192 (inside cc_kmeans_fit already for K >= 256
- *                         when N >= 2^19 and iters >= 5, where the ordering is paid once) vectors and centroids are
- *                         additionally visited in the order of a (norm, cosine to a fixed direction) key and a
- *                         workgroup skips the parts of the codebook that the triangle inequality rules out: a centroid
- *                         whose norm, or whose projection on the fixed direction, differs from a vector's by more than
- *                         a known upper bound of its nearest distance cannot be the nearest. The previous E-step's
- *                         codes on the same workspace - or a bootstrap pass over a guessed neighbourhood of each
- *                         vector - provide that bound; a poor bound costs time, never correctness. Inside a large
- *                         fit (d <= 8, 1024 <= K <= 65536, 2^22 vectors and 128 K for d <= 4, 2^21 and 32 K above;
- *                         iters >= 3) most vectors are, from the second E-step on, decided on a list of the centroids
- *                         near their last one.
+ *                         on the vector ALUs for smaller K and small problems. For K >= 8192 (inside cc_kmeans_fit
+ *                         already for K >= 256 when N >= 2^19 and iters >= 5, where the ordering is paid once; not
+ *                         for d = 5 .. 8, K < 1024, N >= 2^20) vectors and centroids are additionally visited in the
+ *                         order of a (norm, cosine to a fixed direction) key and a workgroup skips the parts of the
+ *                         codebook that the triangle inequality rules out: a centroid whose norm, or whose projection
+ *                         on the fixed direction, differs from a vector's by more than a known upper bound of its
+ *                         nearest distance cannot be the nearest. The previous E-step's codes on the same workspace -
+ *                         or a bootstrap pass over a guessed neighbourhood of each vector - provide that bound; a
+ *                         poor bound costs time, never correctness. Inside a large fit (d <= 8, 1024 <= K <= 65536,
+ *                         3 * 2^19 vectors and 24 K, iters >= 3) most vectors are, from the second E-step on (for
+ *                         d > 4 in the largest from the first), decided on a list of the centroids near their last one.
  *   CC_ASSIGN_DIRECT      direct-form vector-ALU kernel only.
  *   CC_ASSIGN_MFMA_F32    fp32 MFMA kernel always, whole codebook.
  *   CC_ASSIGN_AUTO_WHOLE  as CC_ASSIGN_AUTO but always the whole codebook, and every M-step recomputed.

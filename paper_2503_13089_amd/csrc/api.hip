@@ -120,7 +120,7 @@ int run_bootstrap(const Ctx& cx, const cc::EStep& e, uint32_t N, uint32_t d, con
         CC_TRY_HIP(cc::launch_windows(C, N, d, K, w, guess_width(K, d), s), "assign (guessed windows)");
     }
     cc::EStep b = e;
-    b.pack_rows = C; b.pack_perm = w.cperm; b.rows = w.csorted; b.row_ids = w.cperm; b.K = K;
+    b.rows = w.csorted; b.row_ids = w.cperm; b.K = K;
     b.packed = w.packed; b.packed_tiles = w.packed_tiles; b.windows = w.windows;
     b.packed_already = true;
     b.accumulate = false; b.hint_only = true;
@@ -156,7 +156,7 @@ int run_assign_matrix(const Ctx& cx, const float* X, uint32_t N, uint32_t d, con
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_windows(C, N, d, K, w, 0.0f, s), "assign (norm windows)");
     }
-    e.pack_rows = C; e.pack_perm = pruned ? w.cperm : nullptr;
+    e.pack_rows = C;
     e.rows = pruned ? w.csorted : C; e.row_ids = pruned ? w.cperm : nullptr;
     e.K = K; e.packed = w.packed; e.packed_tiles = w.packed_tiles;
     e.windows = pruned ? w.windows : nullptr;
@@ -210,7 +210,7 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     // inputs that are not fp16 numbers: the fp32 variant scores the far vectors (all of them where no lists can be made)
     cc::EStep e{};
     e.X = f.x; e.N = N; e.n_dev = far_count; e.out_pos = f.pos;
-    e.pack_rows = C; e.pack_perm = w.cperm; e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
+    e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
     e.packed = w.packed; e.packed_tiles = w.packed_tiles; e.windows = w.windows;
     e.packed_already = true;   // with the centroids' order
     e.idx = w.idx_sorted;

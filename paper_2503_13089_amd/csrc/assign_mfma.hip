@@ -44,8 +44,7 @@ constexpr float kGuardSafety = 1.5f;
 template <int D>
 __global__ __launch_bounds__(kThreads) void pack_codebook_kernel(const float* __restrict__ C, uint32_t K,
                                                                  uint32_t ntiles, float* __restrict__ packed,
-                                                                 WsHeader* hdr, int gate,
-                                                                 const uint32_t* __restrict__ cperm)
+                                                                 WsHeader* hdr, int gate)
 {
     constexpr uint32_t KS = D / 2, TF = 64 * KS + 32;
     if (!gate_open(hdr, gate)) return;
@@ -58,15 +57,13 @@ __global__ __launch_bounds__(kThreads) void pack_codebook_kernel(const float* __
         const uint32_t lane = r / KS, ks = r % KS, h = lane >> 5, m = lane & 31;
         // MFMA output row m lives in half (m/4)%2, register (m%4) + 4*(m/8): give it centroid 16*half + register
         const uint32_t pos = 32 * tile + 16 * ((m >> 2) & 1) + (m & 3) + 4 * (m >> 3);
-        const uint32_t k = (cperm != nullptr && pos < K) ? cperm[pos] : pos;  // norm order when pruning
-        val = pos < K ? C[size_t(k) * D + 2 * ks + h] : 0.0f;
+        val = pos < K ? C[size_t(pos) * D + 2 * ks + h] : 0.0f;
     } else {
         const uint32_t pos = 32 * tile + (r - 64 * KS);
-        const uint32_t k = (cperm != nullptr && pos < K) ? cperm[pos] : pos;
         if (pos < K) {
             double s = 0.0;
             for (int j = 0; j < D; ++j) {
-                const double c = double(C[size_t(k) * D + j]);
+                const double c = double(C[size_t(pos) * D + j]);
                 s += c * c;
             }
             val = float(s);  // one rounding
@@ -298,8 +295,7 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     const size_t packed_floats = size_t(e.packed_tiles) * TF;
     if (!e.packed_already)
         hipLaunchKernelGGL(pack_codebook_kernel<D>, dim3(uint32_t((packed_floats + kThreads - 1) / kThreads)),
-                           dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<float*>(e.packed), w.hdr, e.gate,
-                           e.pack_perm);
+                           dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<float*>(e.packed), w.hdr, e.gate);
     constexpr int VTW = VT * 128 > int(kWinTile) ? int(kWinTile) / 128 : VT;
     const uint32_t per_block = 4 * 32 * (e.windows != nullptr ? VTW : VT);
     const auto kernel = e.windows != nullptr ? assign_mfma_kernel<D, VTW, int(kStageTiles), GT, true>

@@ -330,7 +330,8 @@ __global__ __launch_bounds__(64 * kFewWaves, VT <= 2 || (VT == 4 && D <= 8) ? 4 
 template <int D, int VT>
 static hipError_t launch_few(const EStep& e, const Workspace& w, hipStream_t s)
 {
-    const auto kernel = e.windows != nullptr ? assign_few_f16_kernel<D, VT, true> : assign_few_f16_kernel<D, VT, false>;
+    constexpr bool kWindowed = VT > 1;   // up to 8192 vectors: never
+    const auto kernel = kWindowed && e.windows != nullptr ? assign_few_f16_kernel<D, VT, kWindowed> : assign_few_f16_kernel<D, VT, false>;
     ProfileScope scope(e.profile, kProfEstepF16, s);
     hipLaunchKernelGGL(kernel, dim3((e.N + 32 * VT - 1) / (32 * VT)), dim3(64 * kFewWaves), 0, s, e.X, e.N, e.rows, e.K,
                        static_cast<const char*>(e.packed), e.idx, w.dmin, w.hdr, w.refine_list, w.refine_cap, e.gate,
@@ -365,7 +366,7 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
     // and 4-tile groups pay (8192 x 28672, d = 8, K = 65536: 10 iterations in 531 instead of 545 ms).
     constexpr int GT = 4, GT_WIDE = ST >= 8 ? 8 : 4, GT_WINDOWED = D >= 8 ? 4 : 2;
     if (e.N <= few_most(D, e.windows != nullptr)) {
-        if (e.N <= 8192u) return launch_few<D, 1>(e, w, s);
+        if (e.N <= 8192u && e.windows == nullptr) return launch_few<D, 1>(e, w, s);
         if (e.N <= (D == 4 ? 49152u : (D == 8 ? 98304u : (e.windows != nullptr ? 131072u : 229376u)))) return launch_few<D, 2>(e, w, s);
         return launch_few<D, (D == 16 ? 8 : 4)>(e, w, s);
     }

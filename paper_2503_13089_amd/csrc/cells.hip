@@ -1283,7 +1283,7 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
 template <int D>
 hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s)
 {
-    // buffers of the centroids' sort, which does not run during an E-step by cells
+    // buffers of the centroids' order by norm alone, which no E-step by cells asks for
     float* drift = cells_bounded(N, D, K) && bounded ? reinterpret_cast<float*>(w.cperm_tmp) : nullptr;
     uint16_t* moves = w.ckeys_tmp;
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = w.packed_tiles * 32;

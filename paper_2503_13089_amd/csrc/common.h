@@ -110,12 +110,12 @@ struct Workspace {
     uint16_t* vkeys_tmp;       // [N]
     float* csorted;            // [K*d]  the centroids in ascending-norm order
     uint32_t* cperm;           // [K]    centroid index of the p-th centroid in norm order
-    uint32_t* cperm_tmp;       // [K]
+    uint32_t* cperm_tmp;       // [K]    rank of each centroid among those of its key; moves (cells)
     uint32_t* cinv;            // [K]    position of centroid k in norm order (inverse of cperm)
     uint16_t* ckeys;           // [K]
-    uint16_t* ckeys_tmp;       // [K]
+    uint16_t* ckeys_tmp;       // [K]    moves (cells)
     uint32_t* key_starts;      // [65537] first norm-ordered centroid position with ordering key >= v
-    uint32_t* sort_hist;       // [256 * sort blocks]
+    uint32_t* sort_hist;       // [256 * sort blocks of the vectors]
     uint2* windows;            // [ceil(N/512)][kWinStride] window list (runs of codebook stages) per 512-vector tile
     // M-step by buckets (K <= kMaxBuckets * kBucketClusters)
     char* records;             // [2N] x (4d + 16) bytes: the vectors, each with its code, grouped by bucket
@@ -213,8 +213,8 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K, si
     w.ckeys = reinterpret_cast<uint16_t*>(take(size_t(K) * 2));
     w.ckeys_tmp = reinterpret_cast<uint16_t*>(take(size_t(K) * 2));
     w.key_starts = reinterpret_cast<uint32_t*>(take(size_t(65537) * 4));
-    // histogram rows + 256 totals, for the vectors' sort and for the centroids' (whose blocks are smaller)
-    w.sort_hist = reinterpret_cast<uint32_t*>(take(std::max(sort_hist_bytes(N), sort_hist_bytes(K))));
+    // histogram rows + 256 totals of the vectors' sort
+    w.sort_hist = reinterpret_cast<uint32_t*>(take(sort_hist_bytes(N)));
     w.windows = reinterpret_cast<uint2*>(take((size_t(N) / kWinTile + 1) * kWinStride * 8));
     w.bucket_ok = K <= kMaxBuckets * kBucketClusters && N < (uint64_t(1) << 31);  // record positions are 32-bit
     if (w.bucket_ok) {
@@ -222,8 +222,8 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K, si
         w.bucket_hist = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk + 1) * 4));
         w.bucket_gtot = reinterpret_cast<uint32_t*>(take(buckets * (size_t(N) / kBucketChunk / kBucketGroup + 1) * 4));
         w.bucket_base = reinterpret_cast<uint32_t*>(take((buckets + 1) * 4));
-        // 2N records: an incremental M-step writes two records (plus, minus) per vector whose code changed, and
-        // nothing bounds how many change in one iteration
+        // 2N records: every vector with a trailer needs N, an incremental M-step 8 bytes a vector and its runs, the far vectors of a fit by cells and
+        // the lists behind them what is there; the rest is room for more ranges of partial sums, of which small calls want many
         w.records = take(size_t(N) * 2 * (4 * d + 16));
     }
     w.least = w.bytes = off;
@@ -278,8 +278,7 @@ __device__ __forceinline__ bool gate_open(const WsHeader* hdr, int gate)
 struct EStep {
     const float* X;             // vectors to score (input order, or the norm-ordered copy)
     uint32_t N;
-    const float* pack_rows;     // centroid rows the packed codebook is built from ...
-    const uint32_t* pack_perm;  // ... through this position -> row map (NULL = identity)
+    const float* pack_rows;     // centroid rows, where the packed codebook is not there already
     const float* rows;          // centroid rows in packed order, for the direct-form index recovery ...
     const uint32_t* row_ids;    // ... and the centroid index of each packed position (NULL = identity)
     uint32_t K;                 // rows in this codebook
@@ -408,7 +407,7 @@ bool update_delta_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w
 hipError_t launch_update_delta(const float* X, uint32_t N, uint32_t d, const uint32_t* idx, const float* prev, uint32_t K, float* out,
                                uint32_t* counts_out, const Workspace& w, hipStream_t s);
 // M-step by cluster slices (update_sliced.hip): each chunk's codes sorted by slice, then one LDS accumulation per slice of the
-// clusters, no copy of the vectors; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
+// clusters; for K <= 65536 and not too few N. Same integer sums (left in w.sums / w.counts) and the same
 // result bits as the other formulations. `out` may alias `prev`.
 bool update_sliced_applies(uint32_t N, uint32_t d, uint32_t K, const Workspace& w);
 // Whether all clusters fit one slice, i.e. the pass needs neither lists nor a second look at a code.

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(kThreads) void hint_from_cells_kernel(const WsPersi
 
 // ---------------------------------------------------------------------------------------------------
 // Elements per block and pass: a large array streams through 4096-element chunks (8 rounds of the scatter's
-// ranking per block); a small one (the centroids, every iteration) is latency-bound, so it is spread over as many
+// ranking per block); a small one is latency-bound, so it is spread over as many
 // blocks as it has rounds.
 static uint32_t sort_chunk(uint64_t n) { return n <= (1u << 18) ? uint32_t(kSortThreads) : kSortChunk; }
 

@@ -1,5 +1,5 @@
-"""Incremental M-step of a fit at the edges of its chunks (16384 vectors) and slices (at most 512, of 4 clusters at least): centroids and
-codes are the bits of the same iterations made one call at a time, each of which sums every vector anew."""
+"""Incremental M-step of a fit at the edges of its chunks (16384 vectors), slices (at most 512, of 4 clusters at least) and rounds (2048 chunks): centroids are the
+bits of the same iterations made one call at a time, each of which sums every vector anew, and codes those of an E-step for them."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -7,9 +7,10 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("N,d,K", [(32 * 16384, 4, 256), (32 * 16384 + 1, 4, 2049), (33 * 16384 - 1, 8, 8193), (32 * 16384 + 33, 16, 4097), (600_000, 6, 259),
-                                   (16384 * 3 + 5, 4, 8192), (9000, 4, 8200), (4_300_000, 4, 33000), (2_200_000, 8, 1024)])
-def test_a_fit_is_its_iterations_one_by_one(N, d, K):
+@pytest.mark.parametrize("N,d,K,by_cells", [(3 << 19, 4, 2048, True), ((3 << 19) + 1, 4, 2049, True), ((3 << 19) + 16383, 6, 1025, True), (33 * 16384 - 1, 8, 8193, False),
+                                            (32 * 16384 + 33, 16, 4097, False), (16384 * 3 + 5, 4, 8192, False), (9000, 4, 8200, False), (4_300_000, 4, 33000, True),
+                                            (2_200_000, 8, 1024, True), (2048 * 16384, 4, 1030, True), (2049 * 16384 + 77, 4, 1030, True)])
+def test_a_fit_is_its_iterations_one_by_one(N, d, K, by_cells):
     import paper_2503_13089_amd as cc
 
     gen = torch.Generator(device="cuda").manual_seed(N + K)
@@ -22,8 +23,10 @@ def test_a_fit_is_its_iterations_one_by_one(N, d, K):
     print(f"fit and its iterations N={N} d={d} K={K}", flush=True)
     c, idx, j = torch.empty_like(c0), torch.empty(N, dtype=torch.uint32, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
     cc.kmeans_fit(x, K, iters, c0, c, idx, j, ws)
-    one = c0.clone()
+    assert (cc.read_stats(ws).list_stages > 0) == by_cells   # one slice holds few clusters: only a fit by cells then sums incrementally
+    one, codes = c0.clone(), torch.empty_like(idx)
     for _ in range(iters):
-        cc.lloyd_iter(x, one, idx.clone(), None, None, ws)
+        cc.lloyd_iter(x, one, codes, None, None, ws)
+    cc.assign(x, one, codes, None, ws)
     torch.cuda.synchronize()
-    assert torch.equal(c, one)
+    assert torch.equal(c, one) and torch.equal(idx.view(torch.int32), codes.view(torch.int32))
