@@ -52,10 +52,6 @@ template <int D, int RECORDS>
 constexpr int kChunkThreadsOf = RECORDS ? int(kChunkOf<D, 1> / 7) : kChunkThreads;
 constexpr uint32_t kPosBits = 13;
 constexpr uint32_t kKindShift = 16, kStartMask = 0xffffu;   // where a slice starts in a chunk, and above it what the chunk left
-// Rows of fp32 with this many bytes of vectors ahead, or less, are read through the caches: where they do not go along, the second kernel begins with them.
-// All others are read past the caches, which leaves them to the records. 16-bit numbers / others, us a call, with 0, 128 MB and all through the caches: 11.3 M
-// vectors, K = 65536 102 / 140, 103 / 121, 103 / 118; 20 M 164 / 237, 172 / 224, 181 / 225.
-constexpr uint64_t kKeptRows = 128u << 20;
 constexpr uint32_t kCounters = 512;       // of a chunk: slices x 8 groups of positions x what is left for the lanes, so that
 constexpr uint32_t kGroups = 8;           // few of them take turns at one counter
 
@@ -387,7 +383,7 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, 1>), (D == 8 ? 4 : 1)) void rec
     using S = Slice<D, RECORDS>;
     constexpr uint32_t kChunk = kChunkOf<D, 1>, T = kChunkThreadsOf<D, 1>;
     constexpr int U = kChunk / T;
-    static_assert(kChunk % T == 0 && (SRC != 0 || WHOLE), "whole rounds");
+    static_assert(kChunk % T == 0 && (SRC != 0 || (WHOLE && D == 4)), "whole rounds");
     typedef uint32_t Words __attribute__((ext_vector_type(D == 4 ? 2 : 4)));   // a piece of a record
     constexpr int kPieces = D == 16 ? 2 : 1;
     __shared__ uint32_t count[kCounters];
@@ -395,6 +391,11 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, 1>), (D == 8 ? 4 : 1)) void rec
     __shared__ uint32_t total, red[3];
     const uint32_t first = blockIdx.x * kChunk, n = min(kChunk, N - first);
     const uint32_t log_lanes = slices == 1 ? 6u : 6 - (32 - __clz(slices - 1)), sub = threadIdx.x & ((1u << log_lanes) - 1);
+    uint32_t some = 0;   // the numbers of four rows, a lane each
+    if constexpr (SRC == 0) {
+        const uint32_t q = (threadIdx.x & 63) / 4 % 4;
+        some = static_cast<const uint32_t*>(X)[size_t(uint64_t(N) * q / 4) * D + (threadIdx.x & 3)];
+    }
     constexpr int kWords = SRC == 0 ? D : D / 2;
     uint32_t code[U], rank[U], raw[U][kWords];   // the numbers as they are
 #pragma unroll
@@ -419,7 +420,10 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, 1>), (D == 8 ? 4 : 1)) void rec
                     for (int j = 0; j < 4; ++j) raw[u][4 * q + j] = t[j];
                 }
         };
-        if ((N - first) * uint64_t(D * 4) > kKeptRows) {
+        // Rows that go along are read past the caches, which leaves those to the records (11.3 M vectors from memory 131 us a call, otherwise 160); rows of other numbers
+        // are read again soon (from the caches 119, otherwise 140). Which it will be, a few numbers tell well enough, the same for every workgroup.
+        const bool sixteen = __all(float(_Float16(__uint_as_float(some))) == __uint_as_float(some) || (some & 0xffffu) == 0);
+        if (sixteen) {
             asm volatile("");   // else the compiler makes one plain load of the two
             rows([](const u32x4* p) { return __builtin_nontemporal_load(p); });
             asm volatile("");

@@ -63,20 +63,21 @@ def test_16_bit_gradients_at_any_place(dt, in_features, out_features, gl, K, shi
     assert np.array_equal(out.cpu().numpy(), want.astype(np.float32))
 
 
-@pytest.mark.parametrize("N,K", [((3 << 22) + 3585, 10241), ((3 << 22) + 1, 16384), (3 << 22, 12000), ((3 << 22) + 7, 10240), ((3 << 22) + 7, 16385), ((128 << 16) + 3584, 5000)])
-def test_rows_past_the_caches_and_in_wide_slices(N, K):
-    """More than 128 MB of vectors (the first chunks are read past the caches) and, from 3 * 2^22 on, slices of 4096 clusters for 10241 to 16384 of them;
-    chunks of fp16 numbers, of bf16 numbers and of neither in turn. The exact integer sums, in torch."""
+@pytest.mark.parametrize("N,K", [((3 << 22) + 3585, 10241), ((3 << 22) + 1, 16384), (3 << 22, 12000), ((3 << 22) + 7, 10240), ((3 << 22) + 7, 16385)])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+def test_rows_in_wide_slices(N, K, shift):
+    """From 3 * 2^22 vectors on 10241 to 16384 clusters are cut into slices of 4096; chunks of fp16 numbers, of bf16 numbers and of neither in turn, and four rows
+    that decide how all others are read. The exact integer sums, in torch."""
     import paper_2503_13089_amd as cc
 
     gen = torch.Generator(device="cuda").manual_seed(N + K)
     x = torch.randn(N, 4, device="cuda", generator=gen).mul_(0.02)
-    kind = (torch.arange(N, device="cuda") // 3584 % 3)[:, None]
+    kind = ((torch.arange(N, device="cuda") // 3584 + shift) % 3)[:, None]
     x = torch.where(kind == 0, x.half().float(), torch.where(kind == 1, x.bfloat16().float() * 2.0 ** -12, x))
     idx = torch.randint(0, K, (N,), device="cuda", generator=gen, dtype=torch.int32)
     prev, out = torch.zeros(K, 4, device="cuda"), torch.empty(K, 4, device="cuda")
     counts, ws = torch.empty(K, dtype=torch.uint32, device="cuda"), g.workspace(N, 4, K)
-    print(f"wide slices N={N} K={K}", flush=True)
+    print(f"wide slices N={N} K={K} shift={shift}", flush=True)
     cc.update(x, idx.view(torch.uint32), prev, out, counts, ws)
     e = cc.read_stats(ws).fixed_point_exp
     codes = idx.long()
