@@ -604,9 +604,10 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
         if (mine_done < chunks) {
             const uint32_t chunk = chunks - 1 - uint32_t(mine_done);
             const uint32_t* at = starts + size_t(chunk) * (slices + 1) + slice;
-            run_kind = at[0] >> kKindShift;
-            run_begin = at[0] & kStartMask;
-            run_end = run_kind == kEntries ? run_begin : at[1] & kStartMask;
+            const uint32_t from = at[0], to = at[1];
+            run_kind = from >> kKindShift;
+            run_begin = from & kStartMask;
+            run_end = run_kind == kEntries ? run_begin : to & kStartMask;
         }
     };
     look_ahead();
