@@ -240,7 +240,9 @@ bool small_problem(uint64_t N, uint32_t d, uint32_t K)
     return (N <= (1u << 16) && N * K <= (1ull << 26)) || (N <= (1u << 17) && K <= (d == 4 ? 832u : 608u));
 }
 
-// An E-step alone (us, fp16 numbers, others): d = 8, K = 340: 4 M 688 / 556, 578 / 595; K = 370: 720 / 604, 584 / 644; K = 399: 731 / 648, 587 / 690.
+// An E-step alone (matrix cores / this form, us, fp16 numbers, others): d = 8, K = 340: 4 M 688 / 556, 578 / 595; K = 370: 720 / 604, 584 / 644; K = 399: 731 / 648,
+// 587 / 690. Lines that would cost the first more than they give the others are not drawn: d = 4, K = 240: 4 M 332 / 253, 263 / 279; d = 16, K = 340: 280000 169 / 147,
+// 152 / 175, 420000 217 / 146, 187 / 175.
 bool small_assign_pays(uint64_t N, uint32_t d, uint32_t K) { return d != 8 || K <= 368 || N * K <= (1ull << 27); }
 
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K)
