@@ -28,8 +28,8 @@
 // 14 vector instructions per number for its fixed-point term (26 us) beside the records from memory (25 us) and the LDS atomics
 // (11 clocks a wave, 14 us). Slices of 2048 clusters at d = 4 then, half the partial sums of 4096. By entries: one row fetch per
 // vector from a different cache line each - the L1 fill rate - or, with few slices, the two passes over the rows.
-// By entries / rows along, us a call, fp32 vectors of 4; numbers of fp16 or bf16 / of neither: 2 M, K = 12000 46 / 36 / 38; 11.3 M, K = 65536 123 / 103 / 118;
-// 20 M, K = 8192 181 / 158 / 188, K = 65536 229 / 172 / 224. 16-bit gradients through an fp32 copy / rows along: 4096x11008 g = 6 344 / 143, g = 9 458 / 187.
+// By entries / rows along, us a call, fp32 vectors of 4; numbers of fp16 or bf16 / of neither: 2 M, K = 12000 46 / 39 / 38; 11.3 M, K = 65536 126 / 105 / 120;
+// 20 M, K = 8192 182 / 154 / 188, K = 65536 231 / 159 / 226. 16-bit gradients through an fp32 copy / rows along: 4096x11008 g = 6 344 / 143, g = 9 458 / 187.
 // By entries only: 28 M of 8 at K = 65536 500 us, 6 M of 16 at K = 3000 189; one slice: 11.5 M of 4 at K = 300 106.
 #include <algorithm>
 #include <type_traits>
@@ -117,8 +117,9 @@ struct Slice {
 
 // What the input scan found in one chunk, and its codes >= K.
 struct ScanPart {
-    uint32_t absmax, flags, skipped, pad;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input
+    uint32_t absmax, flags, skipped, pad;   // flags: bit 0 = not fit for the fp16 kernels, bit 1 = a non-finite input, kLeftEntries
 };
+constexpr uint32_t kLeftEntries = 4;   // the rows of this chunk could not go along
 // What lies in a chunk's part of the entry buffer, told beside where its slices start: entries (32 bits each), or the rows themselves as fp16
 // or bf16 numbers by slice, followed by their clusters within the slice (16 bits).
 enum Kind : uint32_t { kEntries = 0, kRowsF16 = 1, kRowsBf16 = 2 };
@@ -519,7 +520,7 @@ __global__ __launch_bounds__((kChunkThreadsOf<D, 1>), (D == 8 ? 4 : 1)) void rec
     if (threadIdx.x == 0) {
         Scan<SRC> whole;
         whole.m = red[0];
-        parts[blockIdx.x] = ScanPart{whole.absmax(), found & 3u, red[2], 0u};
+        parts[blockIdx.x] = ScanPart{whole.absmax(), (found & 3u) | (kind == kEntries ? kLeftEntries : 0u), red[2], 0u};
     }
     if (threadIdx.x < 64) counts_to_places(count, total);
     __syncthreads();
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
             WsHeader h{};
             h.absmax_bits = absmax;
             h.x_not_f16 = flags & 1u;
-            h.x_nonfinite = flags >> 1;
+            h.x_nonfinite = flags >> 1 & 1u;
             h.skipped_vectors = found[2];
             *hdr = h;
         }
@@ -838,9 +839,11 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
     }
     commit();
     };
+    // Where no chunk left entries none is asked for them, which is a chain of 25 loads a wave (11.3 M vectors, K = 65536: a call 108.7 -> 105.3 us, 20 M 169 -> 159).
     if constexpr (!RECORDS || SRC == 0) {
-        if (finite) add_entries(std::true_type{});   // a branch per number otherwise
-        else add_entries(std::false_type{});
+        const bool any = !RECORDS || (flags & kLeftEntries) != 0;
+        if (any && finite) add_entries(std::true_type{});   // a branch per number otherwise
+        else if (any) add_entries(std::false_type{});
     }
     if (bad && parts == nullptr) atomicAdd(&hdr->skipped_vectors, static_cast<unsigned long long>(bad));
     __syncthreads();
@@ -919,9 +922,9 @@ bool records_pay(uint32_t N, uint32_t K, bool fresh)
 
 // Rows that go along take slices as wide as entries do (RECORDS = 2) for many fp32 vectors of 6 to 8 narrow slices: where a chunk's numbers turn out to
 // have no 16 bits, every line is fetched by as many workgroups as there are slices. us a call by entries / narrow / wide, numbers without 16 bits: K = 15000:
-// 11.3 M 118 / 119 / 114, 14 M 144 / 148 / 140, 28 M 282 / 302 / 276; K = 12000: 20 M 193 / 204 / 197. 16-bit numbers pay for twice the partial sums: K = 15000:
-// 11.3 M 117 / 99 / 104, 20 M 201 / 162 / 169, 28 M 282 / 223 / 226. Beside these K the others lose little or nothing: 20 M, K = 5000 207 / 194 / 219, K = 8192
-// 181 / 188 / 187, K = 9000 210 / 211 / 214, K = 20000 226 / 214 / 207 (16-bit ones 226 / 173 / 180).
+// 11.3 M 120 / 116 / 114, 14 M 145 / 150 / 140, 28 M 282 / 298 / 271; K = 12000: 20 M 194 / 202 / 195. 16-bit numbers pay for twice the partial sums: K = 15000:
+// 11.3 M 119 / 105 / 109, 20 M 201 / 158 / 162, 28 M 282 / 217 / 220. Beside these K the others lose little or nothing: 20 M, K = 5000 207 / 196 / 219, K = 8192
+// 182 / 187 / 186, K = 9000 211 / 208 / 214, K = 20000 227 / 217 / 205 (16-bit ones 227 / 166 / 175).
 bool wide_records_pay(uint32_t N, uint32_t K) { return N > 3u << 22 && K > 5 * Slice<4, 1>::kClusters && K <= 8 * Slice<4, 1>::kClusters; }
 
 template <int D, int SRC, bool LISTED, int RECORDS>
