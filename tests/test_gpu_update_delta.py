@@ -9,7 +9,8 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("N,d,K,by_cells", [(3 << 19, 4, 2048, True), ((3 << 19) + 1, 4, 2049, True), ((3 << 19) + 16383, 6, 1025, True), (33 * 16384 - 1, 8, 8193, False),
                                             (32 * 16384 + 33, 16, 4097, False), (16384 * 3 + 5, 4, 8192, False), (9000, 4, 8200, False), (4_300_000, 4, 33000, True),
-                                            (2_200_000, 8, 1024, True), (2048 * 16384, 4, 1030, True), (2049 * 16384 + 77, 4, 1030, True)])
+                                            (2_200_000, 8, 1024, True), (32 * 16384, 4, 256, False),
+                                            (32 * 16384 + 1, 4, 2049, False), (600_000, 6, 259, False), (2048 * 16384, 4, 1030, True), (2049 * 16384 + 77, 4, 1030, True)])
 def test_a_fit_is_its_iterations_one_by_one(N, d, K, by_cells):
     import paper_2503_13089_amd as cc
 
