@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
         const float sstar = __builtin_fminf(__builtin_fminf(second[vt], os), __builtin_fmaxf(best[vt], ob));
         float bd;
         uint32_t bk;
-        recover_group<D, GT>(x, C, cperm, K, wgrp, wh, h * (GT / 2), (h + 1) * (GT / 2), bd, bk);
+        recover_group<D, GT, (D == 16 ? 2 : 4)>(x, C, cperm, K, wgrp, wh, h * (GT / 2), (h + 1) * (GT / 2), bd, bk);
         const float od = __shfl_xor(bd, 32, 64);
         const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
         const bool take = od < bd || (od == bd && ok < bk);

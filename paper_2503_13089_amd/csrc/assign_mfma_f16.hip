@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_f16_kernel(
         const float sstar = __builtin_fminf(__builtin_fminf(second[vt], os), __builtin_fmaxf(best[vt], ob));
         float bd;
         uint32_t bk;
-        recover_group<D, GT>(x, C, cperm, K, wgrp, wh, h * (GT / 2), (h + 1) * (GT / 2), bd, bk);
+        recover_group<D, GT, (D == 16 && WINDOWED ? 2 : 4)>(x, C, cperm, K, wgrp, wh, h * (GT / 2), (h + 1) * (GT / 2), bd, bk);
         const float od = __shfl_xor(bd, 32, 64);
         const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
         const bool take = od < bd || (od == bd && ok < bk);
@@ -345,7 +345,10 @@ static hipError_t launch_few(const EStep& e, const Workspace& w, hipStream_t s)
 // 1120 / 1192, 450000 1750 / 2004 / 1622 / 1774, 800000 1999 / 2992 / 2306 / 2558; 8, 2600, 90000 1166 / 843 / 867 / 929, 800000 (windows) 3099 / 3364 / 2923 /
 // 2941; 8, 20000, 200000 2872 / 2426 / 2212 / 2244, 1.6 M 12126 / 14428 / 12472 / 12509; 16, 2600, 17000 1422 / 581 / 640 / 666, 450000 5626 / 4786 / 5088 /
 // 4935, 1.6 M (windows) 10241 / 9803 / 10797 / 8781; 16, 20000, 90000 4102 / 2387 / 2680 / 2447, 450000 8312 / 8190 / 9375 / 7359, 1.6 M 22308 / 25825 / 24050 /
-// 21851. 32 to a workgroup: never better from 17000 on.
+// 21851. 32 to a workgroup: never better from 17000 on. (d = 16, 64 to a workgroup: with index recovery four rows at once; two take 522 instead of 609 at K = 2600,
+// 17000 and 2309 instead of 2635 at K = 20000, 90000.) The lines between 64 and 256 to a workgroup at d = 16 with that, an E-step, 64 / 256: by windows K = 9811, 183000 277 / 266, K = 32070,
+// 168000 512 / 476; K = 1787, 233000 122 / 113, K = 889, 353000 173 / 163. At d = 8, 128 to a workgroup, fewer waves per SIMD instead of 40 to 60 bytes of
+// scratch a lane: K = 1137, 322000 129 instead of 108, K = 12705, 377000 350 instead of 300.
 // Whole codebook, 2 iterations, us, that kernel / this one: 4, 4096, 1 M 656 / 664, 4.2 M 2074 / 2324; 8, 1000, 1 M 786 / 690, 8000, 4 M 4898 / 4698; 16, 8000, 2 M
 // 5373 / 4258.
 constexpr uint32_t few_most(int d, bool windowed)

@@ -645,7 +645,10 @@ __device__ __forceinline__ float of_quad(float v) { return __uint_as_float(of_qu
 // range of tiles. Four lanes take the candidates of their four vectors one vector after the other, four neighbouring rows at a time, which are one or two accesses
 // of L1: with a lane to a vector every lane was one, and the windowed kernels, whose bound they were, made 0.9 per clock. Fits, ms: 29 M x 8, K = 65536
 // 92.0 -> 88.9; 1.7 M x 8, K = 2000 6.56 -> 6.16; 3 M x 16, K = 20000, 3 iterations 16.4 -> 14.7; 11 M x 4, K = 65536 13.1 -> 12.9.
-template <int D, int GT>
+// ROWS of a lane at once: four, or at D = 16 two where four (64 registers) cost a kernel its fourth wave per SIMD or make it spill. Four / two, us, d = 16: fp32 numbers,
+// 450000, K = 20000, 10 iterations 26062 / 24968, one iteration of 4.4 M, K = 8068 9138 / 8705; fp16 numbers, 90000, K = 2600, 10 1095 / 822; by windows 3 M, K = 20000, 3
+// 16172 / 15732. Elsewhere two are slower: whole codebook, 4.2 M, K = 7872, 2 iterations 8623 / 9102.
+template <int D, int GT, int ROWS>
 __device__ __forceinline__ void recover_group(const float (&x)[D], const float* __restrict__ rows,
                                               const uint32_t* __restrict__ cperm, uint32_t K, uint32_t group, int h,
                                               int g_begin, int g_end, float& best_d, uint32_t& best_k)
@@ -663,19 +666,22 @@ __device__ __forceinline__ void recover_group(const float (&x)[D], const float* 
         float bd = INFINITY;
         uint32_t bpos = 0;
         for (int g = g_begin; g < g_end; ++g) {
-            float c[4][D];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) load_row<D>(rows + size_t(min(k0 + 32 * g + 4 * u, K - 1)) * D, c[u]);
+            for (int u0 = 0; u0 < 4; u0 += ROWS) {
+                float c[ROWS][D];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t pos = k0 + 32 * g + 4 * u;
-                const float dk = direct_sqdist<D>(y, c[u]);
-                if (pos < K) {
-                    if (dk < bd) {
-                        bd = dk;
-                        bpos = pos;
-                    } else if (dk == bd && before(pos, bpos)) {
-                        bpos = pos;  // exact tie in norm order: keep the lower centroid index
+                for (int u = 0; u < ROWS; ++u) load_row<D>(rows + size_t(min(k0 + 32 * g + 4 * (u0 + u), K - 1)) * D, c[u]);
+#pragma unroll
+                for (int u = 0; u < ROWS; ++u) {
+                    const uint32_t pos = k0 + 32 * g + 4 * (u0 + u);
+                    const float dk = direct_sqdist<D>(y, c[u]);
+                    if (pos < K) {
+                        if (dk < bd) {
+                            bd = dk;
+                            bpos = pos;
+                        } else if (dk == bd && before(pos, bpos)) {
+                            bpos = pos;  // exact tie in norm order: keep the lower centroid index
+                        }
                     }
                 }
             }

@@ -182,7 +182,7 @@ __device__ __forceinline__ void score_sets(const float* __restrict__ X, const fl
             const float sstar = __builtin_fminf(__builtin_fminf(second, os), __builtin_fmaxf(best, ob));
             float bd;
             uint32_t bk;
-            recover_group<D, GT>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
+            recover_group<D, GT, (D == 16 && VT <= 2 ? 2 : 4)>(x, rows, cperm, K, mine ? grp : og, mine ? h : 1 - h, h, h + 1, bd, bk);
             const float od = __shfl_xor(bd, 32, 64);
             const uint32_t ok = uint32_t(__shfl_xor(int(bk), 32, 64));
             const bool take = od < bd || (od == bd && ok < bk);
