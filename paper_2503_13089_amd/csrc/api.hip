@@ -200,8 +200,7 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     }
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_compact(N, d, w, s), "assign (list of the far vectors)");
-        CC_TRY_HIP(cc::launch_windows(C, N, d, K, wf, 0.0f, s, far_count), "assign (windows of the far vectors)");
+        CC_TRY_HIP(cc::launch_cells_compact(C, N, d, K, w, s), "assign (list of the far vectors)");
     }
     {
         cc::ProfileScope scope(cx.prof, cc::kProfEstepF16, s);
@@ -211,7 +210,7 @@ int run_assign_cells(const Ctx& cx, uint32_t N, uint32_t d, const float* C, uint
     cc::EStep e{};
     e.X = f.x; e.N = N; e.n_dev = far_count; e.out_pos = f.pos;
     e.rows = w.csorted; e.row_ids = w.cperm; e.K = K;
-    e.packed = w.packed; e.packed_tiles = w.packed_tiles; e.windows = w.windows;
+    e.packed = w.packed; e.packed_tiles = w.packed_tiles; e.windows = cc::far_windows(w);
     e.packed_already = true;   // with the centroids' order
     e.idx = w.idx_sorted;
     e.gate = cc::kGateIfNotF16;

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
     // ntiles is a multiple of ST (padding rows carry ||c||^2 = +inf), so every stage is whole
     const float4* P4 = reinterpret_cast<const float4*>(packed);
     // Stages to score: the whole packed codebook, or the runs of this workgroup's 512-vector tile.
-    const uint2* wl = WINDOWED ? windows + size_t((wg * (4 * 32 * VT)) / kWinTile) * kWinStride : nullptr;
+    const uint2* wl = WINDOWED ? windows + size_t((wg * (4 * 32 * VT)) / kWinTile) * (n_dev != nullptr ? kFarWinStride : kWinStride) : nullptr;
     const uint32_t nruns = WINDOWED ? wl[0].x : 1u;
     uint32_t run = 0;
     uint2 cur_run = WINDOWED ? wl[1] : make_uint2(0, ntiles);  // [first tile, end tile)

@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64 * kFewWaves, VT <= 2 || (VT == 4 && D <= 8) ? 4 
     __shared__ __attribute__((aligned(16))) float norms[kFewWaves * 32 * kSetGroup];
     const int sum_exp = sums != nullptr ? fixed_point_exp(hdr->absmax_bits, N) : 0;
     score_sets<D, VT, kFewWaves, WINDOWED>(
-        X, C, cperm, N, K, packed, (K + 31) / 32, windows, hdr->cmax_bits, x_best, x_second, x_grp, norms,
+        X, C, cperm, N, K, packed, (K + 31) / 32, windows, kWinTile, uint32_t(kWinStride), hdr->cmax_bits, x_best, x_second, x_grp, norms,
         [&](uint32_t i, bool mine, const float (&x)[D], uint32_t k, float distance, bool safe) {
             bool moved = false;
             if (mine) {

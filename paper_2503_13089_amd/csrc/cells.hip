@@ -8,8 +8,8 @@
 // Once per E-step every centroid gets the list of the centroids within a radius R of it; the vectors of its cell with
 // t(x) <= R ("near") are decided on that list alone. It is 10^2 .. 10^3 times shorter than the codebook where the
 // (norm, cosine) windows of sort.hip leave 3 % (d = 4) or 66 % (d = 8) of it: a ball in d dimensions against a shell.
-// The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, 512
-// neighbours to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
+// The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, the
+// 32 to 256 neighbours of a workgroup to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
 // Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.08 ms, near vectors 0.15, far ones 0.02 to collect and
 // 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.6, 2.7
@@ -181,10 +181,6 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
     }
 }
 
-// Up to so many far vectors, 32, 64 and 128 of them share a workgroup: the first two give each of 256 compute units one, and 256 vectors
-// (d = 8), whose operand loads and start values serve twice the products (27.3 instead of 31.8 ms of the 29 M fit), take four rounds
-// to be worth it (2.8 M: 26.7 ms with 256 at any number, 25.5 with 128, 25.0 with this rule).
-constexpr uint32_t kFarFew1 = 32 * 256, kFarFew2 = 64 * 256, kFarFew4 = 4 * 128 * 256;
 static_assert(kStageTiles % kSetGroup == 0 && kStageTilesMax % kSetGroup == 0, "runs share no group, the packed codebook has room for whole ones");
 
 // ---- centroids: order, operands, radii ------------------------------------------------------------------------------
@@ -1156,7 +1152,7 @@ __global__ __launch_bounds__(kThreads) void far_count_kernel(const uint32_t* __r
 
 // The flagged ranks, in order, to a dense list with their rows and previous codes, a piece per workgroup: far vectors are outliers
 // and lie close together in the norm order (a workgroup per 8192 ranks: 17 to 24 us where 40 to 90 thousand of 4 M are far).
-// Neighbours in the list are neighbours in norm, so the 512 of a window need little more than each of them: the 4096 x 11008 fit
+// Neighbours in the list are neighbours in norm, so those of a window need little more than each of them: the 4096 x 11008 fit
 // spent 1.8 ms on its far vectors with them, 4.4 when runs of 8192 ranks lay in the order of their workgroups' arrival.
 template <int D>
 __global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* __restrict__ far_bits, uint32_t words,
@@ -1200,6 +1196,79 @@ __global__ __launch_bounds__(kThreads) void far_compact_kernel(const uint32_t* _
     }
 }
 
+// Windows of the far vectors, a wave to each: the hull of what their distances to the previous codes leave of norms and projections, as in sort.hip, one
+// lane to a shell. Runs that share a tracking group of the kernel that scores them become one, so that none is visited twice.
+template <int D>
+__global__ __launch_bounds__(kThreads) void far_window_kernel(const float* __restrict__ X, const uint32_t* __restrict__ hint, const float* __restrict__ C,
+                                                              uint32_t N, uint32_t K, const uint32_t* __restrict__ key_starts, WsHeader* hdr,
+                                                              uint2* __restrict__ windows)
+{
+    __shared__ uint32_t held[kWaves];
+    const uint32_t far = hdr->far_count, tile = far_window_tile(hdr, D, N), base = shell_base(hdr->absmax_bits, D);
+    const uint32_t whole = hdr->x_not_f16 != 0 ? kStageTiles : uint32_t(kSetGroup), lane = threadIdx.x & 63;
+    uint32_t scored = 0;   // tiles, times vectors
+    for (uint32_t w = blockIdx.x * kWaves + (threadIdx.x >> 6); w < (far + tile - 1) / tile; w += gridDim.x * kWaves) {
+        float nlo = INFINITY, nhi = 0.0f, plo = INFINITY, phi = -INFINITY;
+        for (uint32_t v = lane; v < tile; v += 64) {
+            const uint32_t i = min(w * tile + v, far - 1);
+            float x[D], c[D], s = 0.0f, prj;
+            load_row<D>(X + size_t(i) * D, x);
+            load_row<D>(C + size_t(min(hint[i], K - 1)) * D, c);
+#pragma unroll
+            for (int j = 0; j < D; ++j) s = __builtin_fmaf(x[j], x[j], s);
+            const float nrm = __builtin_sqrtf(s), u = __builtin_sqrtf(direct_sqdist<D>(x, c)) * 1.001f + 1e-30f;
+            (void)ordering_key<D>(x, nrm, base, prj);
+            nlo = __builtin_fminf(nlo, nrm - u);
+            nhi = __builtin_fmaxf(nhi, nrm + u);
+            plo = __builtin_fminf(plo, prj - u);
+            phi = __builtin_fmaxf(phi, prj + u);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            nlo = __builtin_fminf(nlo, __shfl_xor(nlo, off, 64));
+            nhi = __builtin_fmaxf(nhi, __shfl_xor(nhi, off, 64));
+            plo = __builtin_fminf(plo, __shfl_xor(plo, off, 64));
+            phi = __builtin_fmaxf(phi, __shfl_xor(phi, off, 64));
+        }
+        const float slack = nhi < 3.0e38f ? 1e-5f * nhi : 0.0f;   // as in sort.hip
+        nlo -= slack; nhi += slack; plo -= slack; phi += slack;
+        const uint32_t smin = shell_of_key(nlo > 0.0f ? norm_key(nlo) : 0u, base), smax = shell_of_key(nhi < 3.0e38f ? norm_key(nhi) : 0xffffu, base);
+        const bool wide = smax - smin + 1 > uint32_t(kFarWinSlots);
+        uint32_t klo = smin << 7, khi = (smax << 7) | 127u, x = 0, y = 0;   // the run of this lane's shell, in tiles
+        if (!wide) shell_cosine_run(smin + lane, base, plo, phi, klo, khi);
+        if (lane <= (wide ? 0u : smax - smin) && klo <= khi) {
+            const uint32_t first = key_starts[klo], end = key_starts[khi + 1];   // keys are ascending
+            if (first < end) { x = first / 32; y = (end + 31) / 32; }
+        }
+        if (!__any(x < y)) {   // cannot happen: a hinted centroid lies inside its own runs
+            x = 0;
+            y = lane == 0 ? (K + 31) / 32 : 0u;
+        }
+        uint32_t reach = y;   // the furthest end of the runs up to this one
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = uint32_t(__shfl_up(int(reach), off, 64));
+            if (lane >= uint32_t(off)) reach = max(reach, o);
+        }
+        const uint32_t before = uint32_t(__shfl_up(int(reach), 1, 64));
+        const unsigned long long starts = __ballot(x < y && (lane == 0 || before == 0 || x / whole > (before - 1) / whole));
+        const uint32_t n = uint32_t(__popcll(starts)), nth = uint32_t(__popcll(starts & ((2ull << lane) - 1)));   // runs up to this lane's
+        uint2* out = windows + size_t(w) * kFarWinStride;
+        const bool last = lane == 63 || ((starts >> (lane + 1)) & 1) != 0;   // of its run
+        if ((starts >> lane) & 1) out[nth].x = x;
+        if (last && nth > 0) out[nth].y = reach;
+        uint32_t total = ((starts >> lane) & 1 ? 0u - x : 0u) + (last && nth > 0 ? reach : 0u);
+        for (int off = 32; off > 0; off >>= 1) total += uint32_t(__shfl_xor(int(total), off, 64));
+        if (lane == 0) out[0] = make_uint2(n, total);
+        scored += total * min(tile, far - w * tile);
+    }
+    // statistics, in units of (512 vectors x 32 centroids)
+    if (lane == 0) held[threadIdx.x >> 6] = scored;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long all = 0;
+    for (int v = 0; v < kWaves; ++v) all += held[v];
+    if (all != 0) atomicAdd(&hdr->window_stages, (all + kWinTile / 2) / kWinTile);
+}
+
 // The far vectors' windowed E-step: a workgroup takes 32 VT vectors (a part of a window tile), its waves take turns at the
 // window's tiles and load operands straight from the packed codebook. The kernel of assign_mfma_f16.hip gives 512
 // vectors to 4 waves and shares every tile through LDS: better with many vectors, but the far ones are outliers, few, with
@@ -1218,7 +1287,7 @@ struct FarShape {
 
 template <int D>
 __global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const float* __restrict__ X, const float* __restrict__ rows,
-                                                                       const uint32_t* __restrict__ cperm, uint32_t K,
+                                                                       const uint32_t* __restrict__ cperm, uint32_t all, uint32_t K,
                                                                        const char* __restrict__ packed, const uint2* __restrict__ windows,
                                                                        const uint32_t* __restrict__ far_pos, uint32_t* __restrict__ idx,
                                                                        float* __restrict__ dmin, WsHeader* hdr, uint32_t* __restrict__ refine_list)
@@ -1229,9 +1298,10 @@ __global__ __launch_bounds__(64 * FarShape<D>::kWaves) void far_kernel(const flo
     __shared__ __attribute__((aligned(16))) float norms[F::kWaves * 32 * kSetGroup];
     const uint32_t N = hdr->far_count;
     if (hdr->x_not_f16 != 0) return;
+    const uint32_t tile = far_window_tile(hdr, D, all);
     auto sets = [&](auto vt) {
         score_sets<D, decltype(vt)::value, F::kWaves, true>(
-            X, rows, cperm, N, K, packed, 0u, windows, hdr->cmax_bits, x_best, x_second, x_grp, norms,
+            X, rows, cperm, N, K, packed, 0u, windows, tile, uint32_t(kFarWinStride), hdr->cmax_bits, x_best, x_second, x_grp, norms,
             [&](uint32_t i, bool mine, const float (&)[D], uint32_t k, float distance, bool safe) {
                 if (!mine) return;
                 const uint32_t p = far_pos[i];
@@ -1333,7 +1403,7 @@ void cells_near_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, bo
 }
 
 template <int D>
-void cells_compact_t(uint32_t N, const Workspace& w, hipStream_t s)
+void cells_compact_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
 {
     const uint32_t words = (N + 31) / 32;
     const FarView f = far_view(w, N, D);
@@ -1342,6 +1412,7 @@ void cells_compact_t(uint32_t N, const Workspace& w, hipStream_t s)
     hipLaunchKernelGGL(far_count_kernel, dim3(blocks), dim3(kThreads), 0, s, w.far_bits, words, runs, before);
     hipLaunchKernelGGL(far_compact_kernel<D>, dim3(blocks * kFarPieces), dim3(kThreads), 0, s, w.far_bits, words, runs, before, w.cell_position,
                        w.xsorted, w.idx_sorted, w.hdr, f.pos, f.x, f.idx);
+    hipLaunchKernelGGL(far_window_kernel<D>, dim3(1024), dim3(kThreads), 0, s, f.x, f.idx, C, N, K, w.key_starts, w.hdr, far_windows(w));
 }
 
 template <int D>
@@ -1349,8 +1420,8 @@ void cells_far_t(uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
 {
     const FarView f = far_view(w, N, D);
     const uint32_t sets = (N + 31) / 32;
-    hipLaunchKernelGGL(far_kernel<D>, dim3(std::min(sets, 4096u)), dim3(64 * FarShape<D>::kWaves), 0, s, f.x, w.csorted, w.cperm, K,
-                       reinterpret_cast<const char*>(w.packed), w.windows, f.pos, w.idx_sorted, w.dmin, w.hdr, f.refine);
+    hipLaunchKernelGGL(far_kernel<D>, dim3(std::min(sets, 4096u)), dim3(64 * FarShape<D>::kWaves), 0, s, f.x, w.csorted, w.cperm, N, K,
+                       reinterpret_cast<const char*>(w.packed), far_windows(w), f.pos, w.idx_sorted, w.dmin, w.hdr, f.refine);
 }
 
 }  // namespace
@@ -1394,11 +1465,11 @@ hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K
     return hipGetLastError();
 }
 
-hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s)
+hipError_t launch_cells_compact(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s)
 {
     switch (d) {
-        case 4: cells_compact_t<4>(N, w, s); break;
-        case 8: cells_compact_t<8>(N, w, s); break;
+        case 4: cells_compact_t<4>(C, N, K, w, s); break;
+        case 8: cells_compact_t<8>(C, N, K, w, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

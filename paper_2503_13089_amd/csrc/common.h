@@ -154,6 +154,9 @@ constexpr int kWinSlots = 32;             // most runs a window list can hold (o
 // measured 29.0 -> 31.9 ms per cfg3 fit.
 constexpr uint32_t kWinTile = 512;
 constexpr int kWinStride = kWinSlots + 1; // uint2 entries per 512-vector tile: (count, -), then the runs
+// The far vectors of an E-step by cells have windows of their own: up to two octaves of shells, for those that share a workgroup.
+constexpr int kFarWinSlots = 64;
+constexpr int kFarWinStride = kFarWinSlots + 1;
 constexpr uint32_t kBucketClusters = 64;  // M-step by buckets: consecutive clusters summed by one workgroup
 constexpr uint32_t kMaxBuckets = 1024;    // so K <= 65536 for that path
 constexpr uint32_t kBucketGroup = 64;     // blocks per group in the two-level scan of the bucket histogram
@@ -260,6 +263,21 @@ hipError_t launch_assign_direct(const float* X, uint32_t N, uint32_t d, const fl
                                 uint32_t* idx, float* dmin, const uint32_t* gate, uint32_t gate_limit,
                                 hipStream_t s, Profile* profile = nullptr);
 
+// Up to so many far vectors, 32, 64 and 128 of them share a workgroup: the first two give each of 256 compute units one, and 256 vectors
+// (d = 8), whose operand loads and start values serve twice the products (27.3 instead of 31.8 ms of the 29 M fit), take four rounds
+// to be worth it (2.8 M: 26.7 ms with 256 at any number, 25.5 with 128, 25.0 with this rule).
+constexpr uint32_t kFarFew1 = 32 * 256, kFarFew2 = 64 * 256, kFarFew4 = 4 * 128 * 256;
+// How many far vectors, neighbours in their list, share a window: those of a workgroup. 512 of them lie far apart, and so their windows held 64 % of the codebook
+// at d = 8 (29 M, K = 65536) and 10 % at d = 4 (11 M) where those of 256 and 128 with room for two octaves of shells hold 38 % and 6 % (fits of
+// 10 and 20 iterations 87.9 -> 81.2 and 12.98 -> 12.67 ms). 512 where the windows would need more room than there is, and for the fp32 variant, which
+// gives 512 to a workgroup.
+__device__ __forceinline__ uint32_t far_window_tile(const WsHeader* hdr, uint32_t d, uint32_t N)
+{
+    const uint32_t far = hdr->far_count;
+    if (hdr->x_not_f16 != 0 || far > N / 2) return kWinTile;
+    return far <= kFarFew1 ? 32u : (far <= kFarFew2 ? 64u : (d == 4 || far <= kFarFew4 ? 128u : 256u));
+}
+
 // Which inputs a gated kernel runs for (decided on the device from WsHeader::x_not_f16).
 // kGateNoHint (a flag on top of the three) additionally requires that the workspace holds no usable hint.
 enum Gate : int { kGateIfF16 = 0, kGateIfNotF16 = 1, kGateAlways = 2, kGateNoHint = 4 };
@@ -324,9 +342,7 @@ hipError_t launch_sort_centroids(const float* C, uint32_t N, uint32_t d, uint32_
 // the centroids as operands where they are; zero_sums: the cluster sums are cleared too
 hipError_t launch_pack_codebook(const float* C, uint32_t d, uint32_t K, const Workspace& w, bool zero_sums, hipStream_t s);
 hipError_t launch_key_starts(const uint32_t* hist, uint32_t* starts, uint32_t* cursor, uint32_t K, hipStream_t s);
-// n_dev: NULL, or where the device keeps the number of vectors (at most N)
-hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
-                          hipStream_t s, const uint32_t* n_dev = nullptr);
+hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess, hipStream_t s);
 hipError_t launch_gather_rows(const float* in, const uint32_t* ids, uint32_t n, uint32_t d, float* out, hipStream_t s);
 // by_cells: the vectors are grouped by cells
 hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool by_cells, hipStream_t s);
@@ -335,15 +351,15 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool 
 // vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order, and the codes change
 // places with w.idx_prev: at the end a next call can put them into the norm order, kHintByCells); launch_cells_centroids
 // orders the current centroids and makes their operands and the lists of the cells; launch_cells_near decides the near
-// vectors; launch_cells_compact leaves the far ones as a list of hdr->far_count entries in the arrays of far_view;
-// launch_cells_far decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
+// vectors; launch_cells_compact leaves the far ones as a list of hdr->far_count entries in the arrays of far_view, with their windows
+// (far_windows); launch_cells_far decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
                               bool first, hipStream_t s);
 enum Radii : int { kRadiiStay, kRadiiFollow, kRadiiJump };   // towards the lists' target lengths: not, a step, all the way (same centroids)
 hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s);
 hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded, hipStream_t s);
 hipError_t launch_cells_hints(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
-hipError_t launch_cells_compact(uint32_t N, uint32_t d, const Workspace& w, hipStream_t s);
+hipError_t launch_cells_compact(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_cells_far(uint32_t N, uint32_t d, uint32_t K, const Workspace& w, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t value, hipStream_t s);
 struct FarView {
@@ -352,6 +368,9 @@ struct FarView {
     uint32_t* idx;   // [N]     previous codes
     uint32_t* refine;  // [N]   those to be re-decided in direct form
 };
+// Windows of the far vectors, kFarWinStride entries for each far_window_tile of them: between groupings nobody uses that buffer of theirs
+// (at most N / 256 + 257 windows of 520 bytes in 4 N of the 1.5 M vectors or more of such a fit).
+inline uint2* far_windows(const Workspace& w) { return reinterpret_cast<uint2*>(w.vperm_tmp); }
 inline FarView far_view(const Workspace& w, uint32_t N, uint32_t d)   // far_bytes(N, d) bytes
 {
     FarView f;

@@ -51,16 +51,17 @@ __global__ __launch_bounds__(kThreads) void refine_kernel(const float* __restric
     }
     if (count > refine_cap) return;  // overflow is handled by the full direct pass
     const int lane = threadIdx.x & 63;
+    const uint32_t win_tile = out_pos != nullptr ? far_window_tile(hdr, D, N) : kWinTile, win_stride = out_pos != nullptr ? kFarWinStride : kWinStride;
     const int fpe = fixed_point_exp(hdr->absmax_bits, N);
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
         const uint32_t i = refine_list[e];
         float x[D];
         load_row<D>(X + size_t(i) * D, x);
-        const uint2* wl = windows != nullptr ? windows + size_t(i / kWinTile) * kWinStride : nullptr;
+        const uint2* wl = windows != nullptr ? windows + size_t(i / win_tile) * win_stride : nullptr;
         const uint32_t nruns = wl != nullptr ? wl[0].x : 1u;
-        // all runs of the list in one load (at most kWinSlots <= 64 of them, one per lane): a load per run inside the
+        // all runs of the list in one load (at most 64 of them, one per lane): a load per run inside the
         // loop below would put a trip to memory in front of every run
-        static_assert(kWinSlots <= 64, "one run per lane");
+        static_assert(kWinSlots <= 64 && kFarWinSlots <= 64, "one run per lane");
         uint2 my_run = make_uint2(0u, 0u);
         if (wl != nullptr && uint32_t(lane) < nruns) my_run = wl[1 + lane];
         unsigned long long best = ~0ull;
@@ -116,7 +117,7 @@ hipError_t launch_refine(const float* X, uint32_t N, uint32_t d, const float* C,
 {
     const float* rows = norm_ordered ? w.csorted : C;
     const uint32_t* row_ids = norm_ordered ? w.cperm : nullptr;
-    const uint2* windows = norm_ordered ? w.windows : nullptr;
+    const uint2* windows = norm_ordered ? (out_pos != nullptr ? far_windows(w) : w.windows) : nullptr;
     long long* sums = fix_sums ? w.sums : nullptr;
     uint32_t* counts = fix_sums ? w.counts : nullptr;
     WsPersist* persist = norm_ordered ? w.persist : nullptr;

@@ -25,18 +25,20 @@ __device__ __forceinline__ void take_score(float& best, float& second, float w)
     asm("v_min_f32 %0, %1, %2" : "=v"(best) : "v"(best), "v"(w));
 }
 
+// win_tile vectors (a multiple of those of a workgroup) share a window, those of two begin win_stride entries apart.
 // finish(i, mine, x, k, distance, safe), by whole waves: the decision for vector i, in the lane with `mine` set; the vectors of lanes n are
 // neighbours from a multiple of 32 on. LDS: x_best, x_second, x_grp of W * VT * 64, lds_norms (16-byte aligned) of W * 32 * kSetGroup entries.
 template <int D, int VT, int W, bool WINDOWED, typename Finish>
 __device__ __forceinline__ void score_sets(const float* __restrict__ X, const float* __restrict__ rows, const uint32_t* __restrict__ cperm,
                                            uint32_t N, uint32_t K, const char* __restrict__ packed, uint32_t ntiles, const uint2* __restrict__ windows,
+                                           uint32_t win_tile, uint32_t win_stride,
                                            uint32_t cmax_bits, float* x_best, float* x_second, uint32_t* x_grp, float* lds_norms, Finish finish)
 {
     using S = F16Shape<D>;
     constexpr int GT = kSetGroup, KM = S::KM;
     constexpr uint32_t kSet = 32 * VT;
     static_assert(GT == 2, "a lane of each half to a tile's norms");
-    static_assert(kWinSlots <= 64, "a lane to a run");
+    static_assert(kWinSlots <= 64 && kFarWinSlots <= 64, "a lane to a run");
     static_assert((!WINDOWED || kWinTile % kSet == 0) && VT <= W, "a set has one window, a wave finishes a tile");
     const int lane = threadIdx.x & 63, h = lane >> 5, n = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -62,7 +64,7 @@ __device__ __forceinline__ void score_sets(const float* __restrict__ X, const fl
         // run r ends in it and what turns a place in the sequence into a group. Tiles of a group beside the run are scored with it.
         uint32_t run_end = 0, shift = 0, total = (ntiles + GT - 1) / GT, r = 0;
         if constexpr (WINDOWED) {
-            const uint2* wl = windows + size_t(i0 / kWinTile) * kWinStride;
+            const uint2* wl = windows + size_t(i0 / win_tile) * win_stride;
             uint32_t g0 = 0, count = 0;
             if (uint32_t(lane) < wl[0].x) {
                 const uint2 run = wl[1 + lane];

@@ -326,13 +326,8 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
                                                           const float* __restrict__ C, uint32_t K,
                                                           const uint32_t* __restrict__ hint, const WsPersist* persist,
                                                           const uint32_t* __restrict__ ckey_starts, float guess,
-                                                          const WsHeader* __restrict__ hdr, uint2* __restrict__ win,
-                                                          const uint32_t* __restrict__ n_dev, unsigned long long* stages)
+                                                          const WsHeader* __restrict__ hdr, uint2* __restrict__ win)
 {
-    if (n_dev != nullptr) {
-        N = min(N, *n_dev);
-        if (blockIdx.x * kWinTile >= N) return;
-    }
     __shared__ float red[4][kThreads / 64];
     __shared__ uint2 runs[kWinSlots];
     const uint32_t quads = (K + kWinQuad - 1) / kWinQuad;
@@ -454,10 +449,7 @@ __global__ __launch_bounds__(kThreads) void window_kernel(const float* __restric
     }
     __syncthreads();
     if (threadIdx.x < merged_n) out[1 + threadIdx.x] = merged[threadIdx.x];
-    if (threadIdx.x == 0) {
-        out[0] = make_uint2(merged_n, merged_total);
-        if (n_dev != nullptr) atomicAdd(stages, static_cast<unsigned long long>(merged_total));  // statistics (few tiles)
-    }
+    if (threadIdx.x == 0) out[0] = make_uint2(merged_n, merged_total);
 }
 
 // Sum of the guessed windows' sizes (statistics only).
@@ -645,10 +637,10 @@ hipError_t launch_pack_codebook(const float* C, uint32_t d, uint32_t K, const Wo
 }
 
 template <int D>
-static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, float guess, hipStream_t s, const uint32_t* n_dev)
+static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, float guess, hipStream_t s)
 {
     hipLaunchKernelGGL(window_kernel<D>, dim3((N + kWinTile - 1) / kWinTile), dim3(kThreads), 0, s, w.xsorted, N, C, K, w.idx_sorted,
-                       w.persist, w.key_starts, guess, w.hdr, w.windows, n_dev, &w.hdr->window_stages);
+                       w.persist, w.key_starts, guess, w.hdr, w.windows);
     if (guess > 0.0f)   // those of the exact pass are counted by the refinement
         hipLaunchKernelGGL(window_stats_kernel, dim3(32), dim3(1024), 0, s, w.windows, (N + kWinTile - 1) / kWinTile, K, w.hdr);
 }
@@ -656,13 +648,12 @@ static void windows_t(const float* C, uint32_t N, uint32_t K, const Workspace& w
 // guess = 0: windows from the codes in w.idx_sorted (which must be valid codes of these vectors, however stale).
 // guess > 0: no codes needed - windows of relative half-width `guess` around every vector's own norm and
 // projection, for the bootstrap pass that produces the first codes; does nothing if the workspace holds a hint.
-hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess,
-                          hipStream_t s, const uint32_t* n_dev)
+hipError_t launch_windows(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, float guess, hipStream_t s)
 {
     switch (d) {
-        case 4: windows_t<4>(C, N, K, w, guess, s, n_dev); break;
-        case 8: windows_t<8>(C, N, K, w, guess, s, n_dev); break;
-        case 16: windows_t<16>(C, N, K, w, guess, s, n_dev); break;
+        case 4: windows_t<4>(C, N, K, w, guess, s); break;
+        case 8: windows_t<8>(C, N, K, w, guess, s); break;
+        case 16: windows_t<16>(C, N, K, w, guess, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -34,3 +34,28 @@ def test_far_vectors_have_the_codes_of_the_direct_form(N, d, K, share, least, mo
     print("far:", far, flush=True)
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert least <= far <= most
+
+
+@pytest.mark.parametrize("d,copies,seed", [(4, 131, 0), (8, 1092, 1)])
+def test_more_than_half_of_the_vectors_far(d, copies, seed):
+    """Every centroid many times over: no list has room for its cell's, so all vectors are far, 512 to a window, of one octave of
+    norms or many."""
+    import paper_2503_13089_amd as cc
+
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    K, N = 65500 // copies * copies, (3 << 19) + 1025
+    x = (torch.randn(N, d, device="cuda", generator=gen) * 0.02 * torch.exp(torch.randn(N, 1, device="cuda", generator=gen))).half().float()
+    c0 = x[torch.randperm(N, device="cuda", generator=gen)[:K // copies]].repeat(copies, 1).contiguous()
+    ws = torch.empty(cc.workspace_bytes(N, d, K), dtype=torch.uint8, device="cuda")
+    out = []
+    for mode in (0, 1):
+        c, idx, j = torch.empty_like(c0), torch.empty(N, dtype=torch.uint32, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+        print(f"all far N={N} d={d} K={K} mode={mode}", flush=True)
+        cc.kmeans_fit(x, K, 3, c0, c, idx, j, ws, assign_mode=mode)
+        torch.cuda.synchronize()
+        if mode == 0:
+            far = int(ws[64:68].view(torch.int32).item())
+        out.append((c, idx.view(torch.int32)))
+    print("far:", far, flush=True)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert far > N // 2
