@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreads) void cell_first_radius_kernel(const float
 // of the vectors in such cells: 0.3 to 0.5 instead of 2.9 tiles of 32 centroids scored per 512 vectors.)
 template <int D>
 __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restrict__ heads, uint32_t K, uint32_t slots, uint32_t item,
-                                                              uint32_t* __restrict__ item_cell, const float* __restrict__ X,
+                                                              uint4* __restrict__ items, const float* __restrict__ X,
                                                               const uint32_t* __restrict__ idx, const float* __restrict__ C,
                                                               float factor1, float factor2, int first_time)
 {
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void cell_items_kernel(CellHead* __restri
     const uint32_t s0 = heads[c].start, members = heads[c].members;
     const uint32_t first = s0 / item + c, end = c + 1 < K ? (s0 + members) / item + c + 1 : slots;
     const uint32_t used = first + (members + item - 1) / item;
-    for (uint32_t s = first + (threadIdx.x & 63); s < end; s += 64) item_cell[s] = s < used ? c : 0xffffffffu;
+    for (uint32_t s = first + (threadIdx.x & 63); s < end; s += 64) items[s] = make_uint4(s < used ? c : 0xffffffffu, s0, (s - first) * item, members);
     if (first_time || heads[c].n1 >= uint32_t(L::kTarget1 / 4)) return;
     float mean, most;
     cell_bounds<D>(X, idx, C, K, c, s0, min(members, 256u), mean, most);
@@ -560,7 +560,7 @@ struct NearArgs {
     const uint32_t* cperm;      // ... and their indices
     uint32_t K;
     CellHead* heads;
-    const uint32_t* item_cell;
+    const uint4* items;
     uint32_t slots;
     const uint16_t* lists;
     const uint32_t* rank;
@@ -589,22 +589,20 @@ __device__ __forceinline__ void or_bits(uint32_t* bits, uint32_t p0, unsigned lo
 
 __device__ __forceinline__ void or_bit(uint32_t* bits, uint32_t p) { atomicOr(bits + (p >> 5), 1u << (p & 31u)); }
 
-// What a work item is a part of: the vectors of a cell, or one of its queues.
-enum ItemOf : int { kMembers, kQueuedNear, kQueuedMid };
-// first: of the vectors (kMembers), else the place in the queue of the first of them.
-__device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, uint32_t item, ItemOf of, uint32_t& c, CellHead& head,
-                                          uint32_t& first, uint32_t& n)
+// A work item: `at`, the first of its vectors or of its places in a queue among those of cell c, which has `members` vectors from `start` on. One load says so, so that
+// all that follows from it, the cell's head among it, is requested at once: a wave waits for memory twice before it scores, not four times.
+struct NearItem {
+    uint32_t c, start, at, members;
+};
+__device__ __forceinline__ bool near_item(const NearArgs& a, uint32_t slot, NearItem& it)
 {
     if (slot >= a.slots) return false;
-    c = uint32_t(__builtin_amdgcn_readfirstlane(int(a.item_cell[slot])));
-    if (c >= a.K) return false;
-    head = a.heads[c];
-    const uint32_t at = (slot - (head.start / item + c)) * item;
-    first = of == kQueuedMid ? head.start + head.members - 1 - at : head.start + at;
-    const uint32_t have = of == kMembers ? head.members : (of == kQueuedMid ? head.mids : a.queued_near[c]);
-    if (at >= have) return false;
-    n = min(item, have - at);
-    return true;
+    const uint4 v = a.items[slot];
+    it.c = uint32_t(__builtin_amdgcn_readfirstlane(int(v.x)));
+    it.start = uint32_t(__builtin_amdgcn_readfirstlane(int(v.y)));
+    it.at = uint32_t(__builtin_amdgcn_readfirstlane(int(v.z)));
+    it.members = uint32_t(__builtin_amdgcn_readfirstlane(int(v.w)));
+    return it.c < a.K;
 }
 
 // t(x), enlarged by more than the rounding of the two distances (the roots are within 1 ulp, those of subnormal numbers zero)
@@ -618,36 +616,43 @@ __device__ __forceinline__ float rough_distance(const float (&x)[D], const float
     return __builtin_amdgcn_sqrtf(direct_sqdist<D>(x, c));
 }
 
-// ---- near vectors, d = 4: direct form over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
-// Direct-form distances are final: no guard band and no index recovery. Rows past the list are NaN and never win.
-// Bound: vector instructions, 17 per 64 (vector, entry) pairs by the counters where the distance, its comparison and two selects
-// are 11; 0.49 G pairs in 0.15 ms (lists of 43 entries, N = 11 M). A workgroup is one wave, as in the kernels for d = 8: two in five
-// items are empty or short, and in a workgroup of four the room of those waves waits for the longest (0.21 ms).
-// Tried: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest
-// t(x): a third fewer instructions in all, 0.20 ms.
-template <int D, int NV>
-__device__ __forceinline__ void scan_list(const float4* rows, uint32_t L, const float (&x)[4][D], float (&bd)[4], uint32_t (&bp)[4],
-                                          unsigned long long& ties)
+// ---- near vectors, d = 4: scores over the list, rows broadcast from LDS, one lane per vector (up to 4) ----------------
+// What is scored is ||c' - c||^2 - 2 (x - c).(c' - c), c the cell's centroid: four multiply-adds a pair, and numbers no larger than the cell, so
+// that fp32 tells all but a few candidates apart. Four entries of the list are a group; a group's minimum, with its number in the low 5 bits, goes into the running
+// best and second best. The best group's four are then compared in direct form; a vector whose second best comes within the guard band is decided in direct form over
+// the whole list, 64 entries at a time.
+// Guard band: let a = ||x - c||. c is on its own list, so the nearest centroid c* has ||x - c*|| <= a, and whatever rivals it ||c' - c|| <= 2 a. The differences
+// are rounded once (2^-24 of each), norm and products add up to 72 x 2^-24 a^2 in a score, direct-form distances are within 8 x 2^-24 a^2 of theirs: 160 x 2^-24 a^2
+// for two candidates, of which 200 are taken; a tag takes 2^-18 of a score. Scores among the subnormal numbers are within 1e-37, always.
+// Bound: vector instructions and, as much, LDS, which takes 8 clocks to give 64 lanes the same 16 bytes. Multiply-adds issue in 2 clocks, minima, compares and
+// selects in 4 (measured with 8 waves per SIMD), so this is 13 clocks a pair and 190 a vector where direct form over the list, a compare and two selects took 34 a
+// pair. N = 11 M, K = 65536 (lists of 43 entries) 0.147 -> 0.129 ms, 4.2 M, K = 4096 0.061 -> 0.045. A workgroup is one wave,
+// as in the kernels for d = 8: two in five items are empty or short, and in a workgroup of four the room of those waves waits for the longest. Three sets of 64 to an
+// item leave six waves to a SIMD, four leave four: 0.153. Rows that are loaded again after the scan for the sake of two more waves, 0.153.
+// Tried with the direct form: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest
+// t(x): a third fewer instructions in all, 0.20 ms where 0.15 were taken.
+constexpr uint32_t kScanGroup = 4;
+constexpr uint32_t kScanTag = 31;
+constexpr uint32_t kScanRoom = Lists<4>::kCap1 + kScanGroup;
+static_assert(Lists<4>::kCap1 <= (kScanTag + 1) * kScanGroup, "the number of a group fits its tag");
+template <int NV>
+__device__ __forceinline__ void scan_list(const float4* to, const float* norms, uint32_t groups, const float (&y)[NV][4], float (&best)[NV], float (&second)[NV])
 {
-    static_assert(D == 4, "one 16-byte row per centroid");
-    for (uint32_t e = 0; e < L; e += 2) {
-        float c[2][D];
+    for (uint32_t g = 0; g < groups; ++g) {
+        const float4 n4 = *reinterpret_cast<const float4*>(norms + g * kScanGroup);
+        const float n[kScanGroup] = {n4.x, n4.y, n4.z, n4.w};
+        float4 r[kScanGroup];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float4 t = rows[e + u];
-            c[u][0] = t.x; c[u][1] = t.y; c[u][2] = t.z; c[u][3] = t.w;
+        for (uint32_t u = 0; u < kScanGroup; ++u) r[u] = to[g * kScanGroup + u];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            float s[kScanGroup];
+#pragma unroll
+            for (uint32_t u = 0; u < kScanGroup; ++u)
+                s[u] = __builtin_fmaf(y[v][3], r[u].w, __builtin_fmaf(y[v][2], r[u].z, __builtin_fmaf(y[v][1], r[u].y, __builtin_fmaf(y[v][0], r[u].x, n[u]))));
+            const float m = __builtin_fminf(__builtin_fminf(__builtin_fminf(s[0], s[1]), s[2]), s[3]);
+            take_score(best[v], second[v], __uint_as_float((__float_as_uint(m) & ~kScanTag) | g));
         }
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const float d = direct_sqdist<D>(x[v], c[u]);
-                ties |= __ballot(d == bd[v]);
-                if (d < bd[v]) {
-                    bd[v] = d;
-                    bp[v] = e + u;
-                }
-            }
     }
 }
 
@@ -655,89 +660,145 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 {
     constexpr int D = 4;
     using L = Lists<D>;
-    __shared__ float4 rows[L::kCap + 2];
-    __shared__ uint32_t ids[L::kCap + 2];
+    __shared__ float4 rows[kScanRoom], to[kScanRoom];   // of the list's entries: the centroid, -2 (c' - c) ...
+    __shared__ __attribute__((aligned(16))) float norms[kScanRoom];   // ... ||c' - c||^2 ...
+    __shared__ __attribute__((aligned(16))) uint32_t ids[kScanRoom];  // ... and the index
     const int lane = threadIdx.x;
-    uint32_t c, first, n;
-    CellHead head;
-    if (!near_item(a, blockIdx.x, kCellItem, kMembers, c, head, first, n)) return;
+    NearItem it;
+    if (!near_item(a, blockIdx.x, it)) return;
+    const uint32_t c = it.c, first = it.start + it.at, n = min(kCellItem, it.members - it.at);
     // of this item, by place within it
     const float4* X = reinterpret_cast<const float4*>(a.X) + first;
     uint32_t* idx = a.idx + first;
     float* dmin = a.dmin != nullptr ? a.dmin + first : nullptr;
     const uint16_t* list = a.lists + size_t(c) * L::kCap;
-    // lists are complete unless they ran out of room
-    const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1;
-    const float R = usable ? head.r1 : -1.0f;
-    const uint32_t len = usable ? head.n1 : 0u;
-    const float qnan = __uint_as_float(0x7fc00000u);
-    for (uint32_t e = lane; e < len + 2; e += 64) {
-        float4 row = make_float4(qnan, qnan, qnan, qnan);
-        uint32_t id = 0;
-        if (e < len) {
-            const uint32_t pos = list[e];
-            row = reinterpret_cast<const float4*>(a.csorted)[pos];
-            id = a.cperm[pos];
-        }
-        rows[e] = row;
-        ids[e] = id;
-    }
-    wave_order();
+    const CellHead head = a.heads[c];
     float cc_row[D];
     load_row<D>(a.C + size_t(c) * D, cc_row);
-    const uint32_t nv = (n + 63) / 64;
-    float x[4][D], bd[4];
-    uint32_t bp[4], hint[4];
-    bool near[4];
+    static_assert(L::kCap == 128, "two entries of a list per lane");
+    const uint32_t listed[2] = {list[lane], list[64 + lane]};   // (past the list's end: whatever lies there)
     float tm = 0.0f;
+    auto sets = [&](auto of) {   // of 64 vectors
+        constexpr int NV = decltype(of)::value;
+        float x[NV][D], y[NV][D], best[NV], second[NV], centre[NV], ch[NV][D];
+        uint32_t hint[NV];
+        bool near[NV];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const uint32_t o = v * 64 + lane;
-        const uint32_t i = min(o, n - 1);
-        const float4 t4 = X[i];
-        x[v][0] = t4.x; x[v][1] = t4.y; x[v][2] = t4.z; x[v][3] = t4.w;
-        hint[v] = idx[i];
-        float ch[D];
-        load_row<D>(a.C + size_t(min(hint[v], a.K - 1)) * D, ch);
-        const float t = cell_bound(rough_distance<D>(x[v], cc_row), rough_distance<D>(x[v], ch));
-        near[v] = t <= R;
-        if (o < n) tm = __builtin_fmaxf(tm, t);
-        bd[v] = INFINITY;
-        bp[v] = 0;
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t i = min(uint32_t(v * 64 + lane), n - 1);
+            const float4 t4 = X[i];
+            x[v][0] = t4.x; x[v][1] = t4.y; x[v][2] = t4.z; x[v][3] = t4.w;
+            hint[v] = idx[i];
+        }
+        // lists are complete unless they ran out of room
+        const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1;
+        const float R = usable ? head.r1 : -1.0f;
+        const uint32_t len = usable ? head.n1 : 0u, groups = (len + kScanGroup - 1) / kScanGroup;
+        float4 row[2];
+        uint32_t id[2];
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
+            const float qnan = __uint_as_float(0x7fc00000u);   // past the list: never the nearest
+            row[q] = make_float4(qnan, qnan, qnan, qnan);
+            id[q] = 0;
+            if (q * 64 + lane < len) {
+                row[q] = reinterpret_cast<const float4*>(a.csorted)[listed[q]];
+                id[q] = a.cperm[listed[q]];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) load_row<D>(a.C + size_t(min(hint[v], a.K - 1)) * D, ch[v]);
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
+            const uint32_t e = q * 64 + lane;
+            if (e >= groups * kScanGroup) break;
+            const bool on = e < len;
+            const float r[D] = {row[q].x, row[q].y, row[q].z, row[q].w}, norm = direct_sqdist<D>(r, cc_row);
+            const float4 step = make_float4(-2.0f * (r[0] - cc_row[0]), -2.0f * (r[1] - cc_row[1]), -2.0f * (r[2] - cc_row[2]), -2.0f * (r[3] - cc_row[3]));
+            rows[e] = row[q];
+            to[e] = on ? step : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            norms[e] = on ? norm : 1e38f;
+            ids[e] = id[q];
+        }
+        wave_order();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) y[v][j] = x[v][j] - cc_row[j];
+            centre[v] = direct_sqdist<D>(x[v], cc_row);
+            const float t = cell_bound(__builtin_amdgcn_sqrtf(centre[v]), rough_distance<D>(x[v], ch[v]));
+            near[v] = t <= R;
+            if (uint32_t(v * 64 + lane) < n) tm = __builtin_fmaxf(tm, t);
+            best[v] = second[v] = 3e38f;
+        }
+        scan_list<NV>(to, norms, groups, y, best, second);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t o = v * 64 + lane, p = first + o;
+            const bool live = o < n;
+            uint32_t k = 0xffffffffu;
+            float bd = INFINITY;
+            if (groups != 0) {   // the best group in direct form: among equals the lowest index wins
+                const uint32_t e0 = min(__float_as_uint(best[v]) & kScanTag, groups - 1) * kScanGroup;
+                const uint4 i4 = *reinterpret_cast<const uint4*>(ids + e0);
+                const uint32_t id[kScanGroup] = {i4.x, i4.y, i4.z, i4.w};
+                float d[kScanGroup];
+#pragma unroll
+                for (uint32_t u = 0; u < kScanGroup; ++u) {
+                    const float4 t = rows[e0 + u];
+                    const float cr[D] = {t.x, t.y, t.z, t.w};
+                    d[u] = direct_sqdist<D>(x[v], cr);
+                }
+                bd = __builtin_fminf(__builtin_fminf(__builtin_fminf(d[0], d[1]), d[2]), d[3]);
+#pragma unroll
+                for (uint32_t u = 0; u < kScanGroup; ++u) k = d[u] == bd ? min(k, id[u]) : k;
+                const float band = 1.2e-5f * centre[v] + 3.814697265625e-06f * (__builtin_fabsf(best[v]) + __builtin_fabsf(second[v])) + 1e-37f;
+                unsigned long long todo = __ballot(live && near[v] && !(second[v] - best[v] > band));
+                while (todo != 0) {
+                    const int src = __ffsll(static_cast<long long>(todo)) - 1;
+                    todo &= todo - 1;
+                    float z[D];
+#pragma unroll
+                    for (int j = 0; j < D; ++j) z[j] = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(x[v][j])), src)));
+                    unsigned long long key = ~0ull;
+                    for (uint32_t e = lane; e < len; e += 64) {
+                        const float4 t = rows[e];
+                        const float cr[D] = {t.x, t.y, t.z, t.w};
+                        const unsigned long long w = (static_cast<unsigned long long>(__float_as_uint(direct_sqdist<D>(z, cr))) << 32) | ids[e];
+                        key = w < key ? w : key;
+                    }
+                    for (int off = 32; off > 0; off >>= 1) {
+                        const unsigned long long w = __shfl_xor(key, off, 64);
+                        key = w < key ? w : key;
+                    }
+                    if (lane == src) {
+                        k = uint32_t(key & 0xffffffffull);
+                        bd = __uint_as_float(uint32_t(key >> 32));
+                    }
+                }
+            }
+            if (live && near[v]) {
+                idx[o] = k;
+                if (dmin != nullptr) dmin[o] = bd;
+            }
+            if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
+            if (a.changed != nullptr) {
+                const bool moved = live && (!near[v] || k != hint[v]);
+                if (moved) a.prev_out[p] = hint[v];
+                or_bits(a.changed, first + v * 64, __ballot(moved), lane);
+            }
+        }
+    };
+    static_assert(kCellItem <= 4 * 64, "at most four sets");
+    switch ((n + 63) / 64) {
+        case 1: sets(std::integral_constant<int, 1>{}); break;
+        case 2: sets(std::integral_constant<int, 2>{}); break;
+        case 3: sets(std::integral_constant<int, 3>{}); break;
+        default:
+            if constexpr (kCellItem > 192) sets(std::integral_constant<int, 4>{});
     }
     for (int off = 32; off > 0; off >>= 1) tm = __builtin_fmaxf(tm, __shfl_xor(tm, off, 64));
     if (lane == 0) atomicMax(&a.heads[c].tmax, __float_as_uint(tm));
-    unsigned long long ties = 0;
-    switch (nv) {
-        case 1: scan_list<D, 1>(rows, len, x, bd, bp, ties); break;
-        case 2: scan_list<D, 2>(rows, len, x, bd, bp, ties); break;
-        case 3: scan_list<D, 3>(rows, len, x, bd, bp, ties); break;
-        default: scan_list<D, 4>(rows, len, x, bd, bp, ties); break;
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        if (uint32_t(v) >= nv) break;
-        const uint32_t o = v * 64 + lane, p = first + o;
-        const bool live = o < n;
-        uint32_t k = ids[bp[v]];
-        if (ties != 0) {  // some lane met an equal distance: among equals the lowest index wins
-            for (uint32_t e = 0; e < len; ++e) {
-                const float4 t = rows[e];
-                const float cr[D] = {t.x, t.y, t.z, t.w};
-                if (direct_sqdist<D>(x[v], cr) == bd[v]) k = min(k, ids[e]);
-            }
-        }
-        if (live && near[v]) {
-            idx[o] = k;
-            if (dmin != nullptr) dmin[o] = bd[v];
-        }
-        if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
-        if (a.changed != nullptr) {
-            const bool moved = live && (!near[v] || k != hint[v]);
-            if (moved) a.prev_out[p] = hint[v];
-            or_bits(a.changed, first + v * 64, __ballot(moved), lane);
-        }
-    }
 }
 
 // ---- near vectors, d = 8: matrix cores over the list -----------------------------------------------------------------
@@ -920,9 +981,10 @@ __global__ __launch_bounds__(kThreads) void near_sort_out_kernel(NearArgs a)
 {
     constexpr int D = 8;
     const int lane = threadIdx.x & 63;
-    uint32_t c, first, n;
-    CellHead head;
-    if (!near_item(a, blockIdx.x * kWaves + (threadIdx.x >> 6), kSetVectors, kMembers, c, head, first, n)) return;
+    NearItem it;
+    if (!near_item(a, blockIdx.x * kWaves + (threadIdx.x >> 6), it)) return;
+    const uint32_t c = it.c, first = it.start + it.at, n = min(kSetVectors, it.members - it.at);
+    const CellHead head = a.heads[c];
     const uint32_t p = first + min(uint32_t(lane), n - 1), hint = a.idx[p];
     float x[D];
     load_row<D>(a.X + size_t(p) * D, x);
@@ -944,9 +1006,14 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     constexpr int D = 8;
     using L = Lists<D>;
     const int lane = threadIdx.x, g = lane >> 4, n16 = lane & 15;
-    uint32_t c, first, n;
-    CellHead head;
-    if (!near_item(a, blockIdx.x, kSetVectors, MID ? kQueuedMid : (QUEUED ? kQueuedNear : kMembers), c, head, first, n)) return;
+    NearItem it;
+    if (!near_item(a, blockIdx.x, it)) return;
+    const uint32_t c = it.c;
+    const CellHead head = a.heads[c];
+    const uint32_t first = MID ? it.start + it.members - 1 - it.at : it.start + it.at;   // of the vectors, or of the places in the queue
+    const uint32_t have = MID ? head.mids : (QUEUED ? a.queued_near[c] : it.members);
+    if (it.at >= have) return;
+    const uint32_t n = min(kSetVectors, have - it.at);
     // lists are complete unless they ran out of room
     const bool usable = lists_exist(a.hdr) && head.n1 <= L::kCap1 && head.n1 > 0;
     const bool whole = usable && head.n2 <= L::kCap2;
@@ -1340,7 +1407,7 @@ hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K,
     hipLaunchKernelGGL(cell_starts_kernel, dim3((K + kThreads - 1) / kThreads), dim3(kThreads), 0, s, w.vkeys, N, K, w.cell_heads);
     const uint32_t item = item_of(D), slots = N / item + K;
     const float wider = D == 4 ? 1.0f : 1.28f;   // (kTarget2 / kTarget1)^(1/8)
-    hipLaunchKernelGGL(cell_items_kernel<D>, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.cell_heads, K, slots, item, w.cell_items,
+    hipLaunchKernelGGL(cell_items_kernel<D>, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.cell_heads, K, slots, item, cell_items(w),
                        w.xsorted, w.idx_sorted, C, factor, factor * wider, first ? 1 : 0);
     if (first) {
         hipLaunchKernelGGL(cell_first_radius_kernel<D>, dim3((K + kWaves - 1) / kWaves), dim3(kThreads), 0, s, w.xsorted, w.idx_sorted,
@@ -1377,7 +1444,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
 
 NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded)
 {
-    return NearArgs{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, w.cell_items, N / item_of(d) + K,
+    return NearArgs{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, cell_items(w), N / item_of(d) + K,
                     w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos,
                     w.cell_cursor, w.cperm_tmp, cells_bounded(N, d, K) ? reinterpret_cast<uint16_t*>(w.cell_order) /* idle between groupings */ : nullptr,
                     cells_bounded(N, d, K) && bounded, w.idx_sorted, track ? nullptr : w.dmin /* track: an iteration's */,

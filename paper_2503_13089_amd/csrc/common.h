@@ -15,7 +15,7 @@ size_t sort_hist_bytes(uint64_t n);
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K);
 // E-step by cells (cells.hip): room for the entries of a cell's list
 uint32_t cell_list_cap(uint32_t d);
-constexpr uint32_t kCellItem = 256;       // vectors of one wave (d = 4)
+constexpr uint32_t kCellItem = 192;       // vectors of one wave (d = 4)
 struct CellHead {
     uint32_t start, members;   // the cell's vectors
     uint32_t n1, n2;           // list entries within r1, between r1 and r2 (more than there is room for: not all stored)
@@ -133,7 +133,6 @@ struct Workspace {
     uint32_t* cell_cursor;     // [65536] next position of each key
     char* cell_flat;           // [K + 1] x 64 bytes: operand pieces of each ordered centroid (d = 8)
     char* cell_operands;       // one matrix-core operand per 32 ordered centroids, for the lists
-    uint32_t* cell_items;      // [N / 64 + K] cell of each work item
     uint16_t* cell_lists;      // [K][cap] positions in the norm order of the centroids (an E-step's own); NULL: no room for cells
     char* small_partials;      // small problems: one set of cluster sums per workgroup; NULL: no room
     uint32_t refine_cap;
@@ -243,7 +242,6 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K, si
         w.cell_cursor = reinterpret_cast<uint32_t*>(take(65536 * 4));
         w.cell_operands = take((size_t(K) + 31) / 32 * 1024);
         w.cell_flat = take((size_t(K) + 1) * 64);
-        w.cell_items = reinterpret_cast<uint32_t*>(take((size_t(N) / 64 + K) * 4));
         w.cell_lists = have >= off && p ? reinterpret_cast<uint16_t*>(p + lists_at) : nullptr;
         w.bytes = off;
     }
@@ -368,6 +366,9 @@ struct FarView {
     uint32_t* idx;   // [N]     previous codes
     uint32_t* refine;  // [N]   those to be re-decided in direct form
 };
+// Work items of the near vectors, N / kCellItem + K (d = 4) or N / 64 + K of them: the cell (none: ~0), its first vector, the item's place among its vectors and how
+// many these are, in one load. Where the sort by code had its second buffer (K <= N / 24: at most 0.92 N of 2 N bytes).
+inline uint4* cell_items(const Workspace& w) { return reinterpret_cast<uint4*>(w.vkeys_tmp); }
 // Windows of the far vectors, kFarWinStride entries for each far_window_tile of them: between groupings nobody uses that buffer of theirs
 // (at most N / 256 + 257 windows of 520 bytes in 4 N of the 1.5 M vectors or more of such a fit).
 inline uint2* far_windows(const Workspace& w) { return reinterpret_cast<uint2*>(w.vperm_tmp); }
