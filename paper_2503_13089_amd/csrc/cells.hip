@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
                                                                           uint32_t* __restrict__ hist, CellHead* __restrict__ heads,
                                                                           uint32_t* __restrict__ changed, uint32_t* __restrict__ far_bits, WsHeader* hdr,
                                                                           const float* __restrict__ csorted, const uint32_t* __restrict__ cinv,
-                                                                          float* __restrict__ drift)
+                                                                          uint16_t* __restrict__ moves)
 {
     using L = Lists<D>;
     const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
@@ -221,10 +221,10 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
         const uint32_t key = ordering_key<D>(c, __builtin_sqrtf(s), shell_base(hdr->absmax_bits, D), proj);
         keys[t] = uint16_t(key);
         atomicAdd(&hist[key], 1u);
-        if (drift != nullptr) {   // how far it can have moved since the E-step before
+        if (moves != nullptr) {   // how far it can have moved since the E-step before
             float before[D];
             load_row<D>(csorted + size_t(cinv[t]) * D, before);
-            drift[t] = __builtin_sqrtf(direct_sqdist<D>(c, before)) * 1.00001f + 3e-19f;
+            moves[t] = upper_half(__builtin_sqrtf(direct_sqdist<D>(c, before)) * 1.00001f + 3e-19f);
         }
         if (radii != kRadiiStay) {
             const CellHead h = heads[t];
@@ -265,8 +265,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
                                                               uint32_t* __restrict__ cperm, uint32_t* __restrict__ cinv,
                                                               float* __restrict__ csorted, char* __restrict__ packed,
                                                               char* __restrict__ operands, char* __restrict__ flat,
-                                                              const WsHeader* __restrict__ hdr, const float* __restrict__ drift,
-                                                              uint16_t* __restrict__ moves)
+                                                              const WsHeader* __restrict__ hdr)
 {
     using S = F16Shape<D>;
     static_assert(S::KM == 1, "one matrix instruction per tile");
@@ -282,7 +281,6 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         pos = atomicAdd(&cursor[keys[k]], 1u);
         cperm[pos] = k;
         cinv[k] = pos;
-        if (drift != nullptr) moves[pos] = upper_half(drift[k]);
 #pragma unroll
         for (int q = 0; q < D / 4; ++q)
             reinterpret_cast<float4*>(csorted + size_t(pos) * D)[q] = make_float4(c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]);
@@ -306,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
     }
     if (f16) put_f16_operand<D>(packed, pos, parts, g, scaled_norm);
     if (flat != nullptr && valid) {  // d = 8: the operand pieces of one centroid side by side, for the near vectors
-        f16x8* to = reinterpret_cast<f16x8*>(flat + size_t(pos) * 64);
+        f16x8* to = reinterpret_cast<f16x8*>(flat + size_t(k) * 64);
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             f16x8 v;
@@ -325,9 +323,10 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
             none[3] = f16x8{_Float16(60000.0f), o, o, o, o, o, o, o};
         }
     }
-    if (pos >= (K + 31) / 32 * 32) return;   // lists go tile by tile
-    const uint32_t q = pos & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
-    char* op = operands + size_t(pos >> 5) * 1024;
+    const uint32_t at = D == 4 ? pos : k;   // d = 8: lists take the whole codebook, and hold indices
+    if (at >= (K + 31) / 32 * 32) return;   // tile by tile
+    const uint32_t q = at & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
+    char* op = operands + size_t(at >> 5) * 1024;
     f16x8 lo, hi;
 #pragma unroll
     for (int j = 0; j < 8; ++j) lo[j] = j < D ? parts[j % D][0] : _Float16(0.0f);
@@ -555,9 +554,9 @@ __global__ __launch_bounds__(64 * kListWaves<D>, 4) void cell_lists_kernel(const
 struct NearArgs {
     const float* X;
     const float* C;             // centroids by index
-    const float* csorted;       // centroids in the norm order ...
-    const char* flat;           // ... their operand pieces (d = 8) ...
+    const float* csorted;       // d = 4: centroids in the norm order ...
     const uint32_t* cperm;      // ... and their indices
+    const char* flat;           // d = 8: operand pieces of the centroids, by index
     uint32_t K;
     CellHead* heads;
     const uint4* items;
@@ -805,11 +804,14 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
 // A wave takes up to 64 vectors of one cell and works alone. The operands of the list's centroids (64 bytes each, one cache
 // line) are laid out for v_mfma_f32_16x16x32_f16: 32 k slots hold the 24 products of d = 8 and sigma ||c||^2, so that scores
 // need no accumulator to start from; the wave gathers them through LDS. Four tiles of 16 centroids are folded
-// two and two row by row; a pair's minimum, with its row and pair in the low 5 bits, goes into the running best and second best: 32 vector
-// instructions per 1024 scores. The winner is then known up to 2 centroids: two direct-form distances. What the tag costs
-// in precision (2^-18 of a score) goes into the guard band, as does twice the accumulation bound (this instruction is
+// row by row: the minimum of the four scores of a row, with the row in the low 4 bits, goes into the running best and second best, 21 vector
+// instructions per 1024 scores. The winner is then known up to 4 centroids: as many direct-form distances. (Two by two it took 35 instructions and two distances: 29 M
+// vectors 13.6 + 13.5 ms a fit, now 13.2 + 12.6. Half of the requests to L2, which are what bounds it now, 0.3 per clock and compute unit, are operands of the lists, a
+// quarter those rows.) What the tag costs in precision (2^-19 of a score) goes into the guard band, as does twice the accumulation bound (this instruction is
 // within 4.5 x 2^-24 of the sum of its terms in tests/test_gpu_mfma_bound16.py; 16 is assumed); a vector whose second best
 // comes within the band is decided in direct form over the list, 64 centroids at a time.
+// Lists hold indices here, in the order of the codebook: nothing has to be looked up for the winner, and what a list that runs out of room in the first iteration keeps of
+// its ball is a fair share of it, where positions in the norm order left the ball's far side out (far vectors of the first two E-steps 7.6 -> 5.0 ms).
 // Vectors between r1 and r2 are queued by cell and scored over the whole list in a second launch (MID), 64 per wave.
 // Inputs that are no fp16 numbers take two operands: fp16 part and rest, 22 bits or more; the band grows accordingly.
 // Measured at N = 29 M, K = 65536 (list of 400, 1500 with the outer part): 1.9 ms per E-step that scores every vector, 0.9 to 1.9
@@ -821,7 +823,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kVT = 4;                    // tiles of 16 vectors per wave
 constexpr uint32_t kSetVectors = 16 * kVT;
 constexpr uint32_t kGroup = 64;           // list entries folded together: 4 tiles of 16
-constexpr uint32_t kTag = 31;
+constexpr uint32_t kTag = 15;
 
 struct Scores {
     float best[kVT], second[kVT];
@@ -867,13 +869,16 @@ __device__ __forceinline__ void score_group(const f16x8 (&a)[4], const f16x8 (&b
             r[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[t], b[vt], r[t], 0, 0, 0);
         }
         const float before = s.best[vt];
+        auto quad = [&](int i) {
+            // median with -inf = minimum of two: fminf on fresh matrix results costs two more instructions to quiet them (that of three does not)
+            const float m = __builtin_fminf(__builtin_fminf(__builtin_amdgcn_fmed3f(r[0][i], r[1][i], minus_inf), r[2][i]), r[3][i]);
+            return __uint_as_float((__float_as_uint(m) & ~kTag) | (row0 + i));
+        };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            // median with -inf = minimum of two: fminf on fresh matrix results costs two more instructions to quiet them
-            const uint32_t lo = __float_as_uint(__builtin_amdgcn_fmed3f(r[0][i], r[1][i], minus_inf));
-            const uint32_t hi = __float_as_uint(__builtin_amdgcn_fmed3f(r[2][i], r[3][i], minus_inf));
-            take_score(s.best[vt], s.second[vt], __uint_as_float((lo & ~kTag) | (row0 + i)));
-            take_score(s.best[vt], s.second[vt], __uint_as_float((hi & ~kTag) | (row0 + i + 16)));
+        for (int i = 0; i < 4; i += 2) {   // two at once: the second best of all is that of {best, u, v} or the second best so far
+            const float u = quad(i), v = quad(i + 1), middle = __builtin_amdgcn_fmed3f(s.best[vt], u, v);
+            asm("v_min_f32 %0, %1, %2" : "=v"(s.second[vt]) : "v"(s.second[vt]), "v"(middle));
+            s.best[vt] = __builtin_fminf(__builtin_fminf(s.best[vt], u), v);
         }
         s.grp[vt] = s.best[vt] < before ? group : s.grp[vt];
     }
@@ -887,10 +892,10 @@ __global__ __launch_bounds__(kMovedThreads) void cell_moved_kernel(const uint16_
                                                                    const WsHeader* __restrict__ hdr)
 {
     using L = Lists<8>;
-    extern __shared__ __attribute__((aligned(16))) uint16_t by_position[];
+    extern __shared__ __attribute__((aligned(16))) uint16_t by_index[];
     if (!lists_exist(hdr)) return;
     for (uint32_t i = threadIdx.x; i < (K + 7) / 8; i += kMovedThreads)   // (the buffer is a whole number of 256 bytes)
-        reinterpret_cast<uint4*>(by_position)[i] = reinterpret_cast<const uint4*>(moves)[i];
+        reinterpret_cast<uint4*>(by_index)[i] = reinterpret_cast<const uint4*>(moves)[i];
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63, waves = gridDim.x * (kMovedThreads / 64);
     for (uint32_t c = blockIdx.x * (kMovedThreads / 64) + (threadIdx.x >> 6); c < K; c += waves) {
@@ -903,8 +908,8 @@ __global__ __launch_bounds__(kMovedThreads) void cell_moved_kernel(const uint16_
                 const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                 for (uint32_t q = 0; q < 8; ++q) {
-                    const uint32_t pos = (w[q / 2] >> (16 * (q & 1))) & 0xffffu;
-                    if (e0 + q < n) m = max(m, uint32_t(by_position[pos]));
+                    const uint32_t id = (w[q / 2] >> (16 * (q & 1))) & 0xffffu;
+                    if (e0 + q < n) m = max(m, uint32_t(by_index[id]));
                 }
             }
             for (int off = 32; off > 0; off >>= 1) m = max(m, uint32_t(__shfl_xor(int(m), off, 64)));
@@ -1076,31 +1081,31 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         // accesses a load, one each clock of the kernel. 29 M vectors, K = 65536: 1.40 and 1.43 ms (near and between r1 and r2) -> 1.27 and
         // 1.27, 2.8 M 0.221 and 0.131 -> 0.204 and 0.112; of that, a half for one load of list entries per group in place of four.
         const uint32_t row = lane >> 2, from = (lane ^ (row + (row >> 2))) & 3u, to_row = 4 * n16 + ((g ^ (n16 + (n16 >> 2))) & 3);
-        uint32_t pos = 0;   // of entry `lane` of a group
+        uint32_t id = 0;   // of entry `lane` of a group
         f16x8 av[4];
-        auto positions = [&](uint32_t gr) {
+        auto entries = [&](uint32_t gr) {
             const uint32_t e = gr * kGroup + lane, at = entry(min(e, max(len, 1u) - 1u));
-            pos = e < len ? at : a.K;
+            id = e < len ? at : a.K;
         };
         auto gather = [&]() {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const char* operand = a.flat + size_t(uint32_t(__shfl(int(pos), 16 * t + int(row), 64))) * 64 + from * 16;
+                const char* operand = a.flat + size_t(uint32_t(__shfl(int(id), 16 * t + int(row), 64))) * 64 + from * 16;
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)operand, (__attribute__((address_space(3))) void*)(turn + t * 64), 16, 0,
                                                  0);
             }
         };
-        positions(0);
+        entries(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows have been read
         gather();
-        positions(1);
+        entries(1);
         for (uint32_t gr = 0; gr < groups; ++gr) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the operands have landed
 #pragma unroll
             for (int t = 0; t < 4; ++t) av[t] = turn[t * 64 + to_row];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and are read before the next ones land there
             gather();
-            positions(gr + 2);
+            entries(gr + 2);
             if (!f16) score_group<4, true>(av, b, low + lane, row0, gr, minus_inf, s);
             else if (tiles <= 2) score_group<2, false>(av, b, low, row0, gr, minus_inf, s);
             else score_group<4, false>(av, b, low, row0, gr, minus_inf, s);
@@ -1126,15 +1131,29 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         grp = g == t ? tg : grp;
     }
     // ---- the decision
-    const uint32_t tag = __float_as_uint(best) & kTag, e0 = grp * kGroup + (tag & 15u) + 2 * (tag & 16u);
-    const uint32_t p0 = entry(min(e0, len - 1)), p1 = entry(min(e0 + 16, len - 1));
-    float c0[D], c1[D];
-    load_row<D>(a.csorted + size_t(p0) * D, c0);
-    load_row<D>(a.csorted + size_t(p1) * D, c1);
-    const float d0 = direct_sqdist<D>(x, c0), d1 = direct_sqdist<D>(x, c1);
-    float d = __builtin_fminf(d0, d1);
-    uint32_t k = a.cperm[d0 <= d1 ? p0 : p1];
-    if (d0 == d1) k = min(k, a.cperm[p1]);
+    const uint32_t e0 = grp * kGroup + (__float_as_uint(best) & kTag);
+    uint32_t at[4];
+    float of[4];
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+        const uint32_t e = e0 + 16 * t;
+        at[t] = entry(min(e, len - 1));
+        float row[D];
+        load_row<D>(a.C + size_t(at[t]) * D, row);
+        of[t] = direct_sqdist<D>(x, row);
+        if (e >= len) of[t] = INFINITY;
+    }
+    float d = __builtin_fminf(__builtin_fminf(__builtin_fminf(of[0], of[1]), of[2]), of[3]);
+    float rival = INFINITY;   // the second of them
+    uint32_t k = a.K - 1;
+    bool seen = false;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const bool is = of[t] == d;
+        if (!is || seen) rival = __builtin_fminf(rival, of[t]);
+        k = is ? (seen ? min(k, at[t]) : at[t]) : k;
+        seen |= is;
+    }
     if constexpr (MODE == kHint) {
         if (on) a.idx[p] = k;
         return;
@@ -1142,7 +1161,7 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
     float xn = 0.0f;
 #pragma unroll
     for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
-    float slack = 3.814697265625e-06f * (__builtin_fabsf(best) + __builtin_fabsf(second));   // the tags: 2^-18
+    float slack = 1.9073486328125e-06f * (__builtin_fabsf(best) + __builtin_fabsf(second));   // the tags: 2^-19
     if (!f16) slack += 16.0f * sigma_cmax * (2.384185791015625e-07f * __builtin_sqrtf(xn) + 1.6e-07f);   // what x has beyond 22 bits
     const float delta = f16_guard_band<D, 3, true, 16>(x, d, sigma, sigma_cmax) + slack;
     const bool clear = (second - best) > delta;
@@ -1156,11 +1175,10 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         unsigned long long key = ~0ull;
 #pragma unroll 4
         for (uint32_t le = lane; le < len; le += 64) {
-            const uint32_t pos = entry(le);
+            const uint32_t id = entry(le);
             float c2[D];
-            load_row<D>(a.csorted + size_t(pos) * D, c2);
-            const unsigned long long v =
-                (static_cast<unsigned long long>(__float_as_uint(direct_sqdist<D>(y, c2))) << 32) | a.cperm[pos];
+            load_row<D>(a.C + size_t(id) * D, c2);
+            const unsigned long long v = (static_cast<unsigned long long>(__float_as_uint(direct_sqdist<D>(y, c2))) << 32) | id;
             key = v < key ? v : key;
         }
         for (int off = 32; off > 0; off >>= 1) {
@@ -1177,12 +1195,12 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         if (a.dmin != nullptr) a.dmin[p] = d;
     }
     if (on && a.bound != nullptr) {
-        // others: the partner of the winner's pair, and whatever scored no better than the second best pair. The band is the one of a
+        // others: the next of the winner's four, and whatever scored no better than the second best four. The band is the one of a
         // centroid twice as far as the winner, which is as much as is made of the scores of those beyond.
         float row[D];
         load_row<D>(a.C + size_t(c) * D, row);
         const float scored = (second - f16_guard_band<D, 3, true, 16>(x, 4.0f * d, sigma, sigma_cmax) - slack) / sigma + xn * 0.999999f;
-        const float sq = __builtin_fminf(__builtin_fminf(scored, 4.0f * d), __builtin_fmaxf(d0, d1));
+        const float sq = __builtin_fminf(__builtin_fminf(scored, 4.0f * d), rival);
         const float others = clear ? __builtin_sqrtf(__builtin_fmaxf(0.0f, sq)) * 0.99999f : 0.0f;
         a.bound[p] = lower_half(bound_of(others, MID ? r2 : r1, rough_distance<D>(x, row)));
     }
@@ -1421,18 +1439,16 @@ template <int D>
 hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s)
 {
     // buffers of the centroids' order by norm alone, which no E-step by cells asks for
-    float* drift = cells_bounded(N, D, K) && bounded ? reinterpret_cast<float*>(w.cperm_tmp) : nullptr;
-    uint16_t* moves = w.ckeys_tmp;
+    uint16_t* moves = cells_bounded(N, D, K) && bounded ? w.ckeys_tmp : nullptr;
     const uint32_t words = (N + 31) / 32, tiles = (K + 31) / 32, padded = w.packed_tiles * 32;
     hipLaunchKernelGGL(cell_keys_of_centroids_kernel<D>, dim3((std::max(K, words) + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K,
-                       words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr, w.csorted, w.cinv, drift);
+                       words, int(radii), w.ckeys, w.cell_hist, w.cell_heads, w.changed, w.far_bits, w.hdr, w.csorted, w.cinv, moves);
     if (hipError_t e = launch_key_starts(w.cell_hist, w.key_starts, w.cell_cursor, K, s); e != hipSuccess) return e;
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
-                       w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr,
-                       drift, moves);
+                       w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
     hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(64 * kListWaves<D>), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
                        w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist, w.cell_cursor);
-    if (drift != nullptr) {   // (by cell where the moves were by centroid: those are in their places now)
+    if (moves != nullptr) {
         const uint32_t lds = (K + 7) / 8 * 16;
         if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cell_moved_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 65536 * 2);
             e != hipSuccess) return e;
@@ -1444,7 +1460,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
 
 NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded)
 {
-    return NearArgs{w.xsorted, C, w.csorted, w.cell_flat, w.cperm, K, w.cell_heads, cell_items(w), N / item_of(d) + K,
+    return NearArgs{w.xsorted, C, w.csorted, w.cperm, w.cell_flat, K, w.cell_heads, cell_items(w), N / item_of(d) + K,
                     w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos,
                     w.cell_cursor, w.cperm_tmp, cells_bounded(N, d, K) ? reinterpret_cast<uint16_t*>(w.cell_order) /* idle between groupings */ : nullptr,
                     cells_bounded(N, d, K) && bounded, w.idx_sorted, track ? nullptr : w.dmin /* track: an iteration's */,

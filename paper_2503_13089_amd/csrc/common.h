@@ -110,7 +110,7 @@ struct Workspace {
     uint16_t* vkeys_tmp;       // [N]
     float* csorted;            // [K*d]  the centroids in ascending-norm order
     uint32_t* cperm;           // [K]    centroid index of the p-th centroid in norm order
-    uint32_t* cperm_tmp;       // [K]    rank of each centroid among those of its key; moves (cells)
+    uint32_t* cperm_tmp;       // [K]    rank of each centroid among those of its key; most moved of each list (cells)
     uint32_t* cinv;            // [K]    position of centroid k in norm order (inverse of cperm)
     uint16_t* ckeys;           // [K]
     uint16_t* ckeys_tmp;       // [K]    moves (cells)
@@ -131,9 +131,9 @@ struct Workspace {
     CellHead* cell_heads;      // [K]
     uint32_t* cell_hist;       // [65536] centroids per ordering key; zero between E-steps
     uint32_t* cell_cursor;     // [65536] next position of each key
-    char* cell_flat;           // [K + 1] x 64 bytes: operand pieces of each ordered centroid (d = 8)
-    char* cell_operands;       // one matrix-core operand per 32 ordered centroids, for the lists
-    uint16_t* cell_lists;      // [K][cap] positions in the norm order of the centroids (an E-step's own); NULL: no room for cells
+    char* cell_flat;           // [K + 1] x 64 bytes: operand pieces of each centroid (d = 8)
+    char* cell_operands;       // one matrix-core operand per 32 centroids (d = 4: ordered ones), for the lists
+    uint16_t* cell_lists;      // [K][cap] centroids (d = 4: positions in their norm order; an E-step's own); NULL: no room for cells
     char* small_partials;      // small problems: one set of cluster sums per workgroup; NULL: no room
     uint32_t refine_cap;
     uint32_t partial_slots;
