@@ -35,14 +35,16 @@ constexpr int kWaves = kThreads / 64;
 
 // A cell's list: the centroids within r1 of its centroid, then (d = 8) those between r1 and r2. Room in all for 4096 entries
 // where 1500 are aimed at: the vectors of a longer one are far. 29 M vectors, K = 65536, 10 iterations: room for 6144
-// 152.7 ms, 4096 153.4, 2560 157.5; 2.8 M vectors 28.4, 28.3 and 28.3 ms with 805, 537 and 335 MB of lists.
+// 152.7 ms, 4096 153.4, 2560 157.5; 2.8 M vectors 28.4, 28.3 and 28.3 ms with 805, 537 and 335 MB of lists. How many are aimed at, d = 4: 36 / 44 / 54 / 60 / 74 entries, 11 M,
+// K = 65536, 20 iterations 13.27 / 12.30 / 11.93 / 11.92 / 11.92 ms, 4.2 M, K = 4096 4.66 / 4.55 / 4.54 / 4.54 / 4.58; 2 M, K = 40000, 10 2.85 (44) / 2.80 (60). d = 8: 400 +
+// 1100 / 400 + 800 / 330 + 870 / 500 + 1000, 29 M, K = 65536 77.0 / 78.8 / 78.9 / 77.4, 2.8 M of 6, K = 65500 17.38 / 17.16 / 17.29 / 17.22.
 template <int D>
 struct Lists {
     static constexpr uint32_t kCap1 = D == 4 ? 128 : 1024;            // room for entries within r1 ...
     static constexpr uint32_t kCap2 = D == 4 ? 0 : 3072;              // ... and between r1 and r2
     static constexpr uint32_t kCap = kCap1 + kCap2;
-    static constexpr float kTarget1 = D == 4 ? 44.0f : 400.0f;        // entries within r1 / r2 that a list should have
-    static constexpr float kTarget2 = D == 4 ? 44.0f : 1500.0f;
+    static constexpr float kTarget1 = D == 4 ? 60.0f : 400.0f;        // entries within r1 / r2 that a list should have
+    static constexpr float kTarget2 = D == 4 ? 60.0f : 1500.0f;
 };
 
 }  // namespace
@@ -625,7 +627,7 @@ __device__ __forceinline__ float rough_distance(const float (&x)[D], const float
 // for two candidates, of which 200 are taken; a tag takes 2^-18 of a score. Scores among the subnormal numbers are within 1e-37, always.
 // Bound: vector instructions and, as much, LDS, which takes 8 clocks to give 64 lanes the same 16 bytes. Multiply-adds issue in 2 clocks, minima, compares and
 // selects in 4 (measured with 8 waves per SIMD), so this is 13 clocks a pair and 190 a vector where direct form over the list, a compare and two selects took 34 a
-// pair. N = 11 M, K = 65536 (lists of 43 entries) 0.147 -> 0.129 ms, 4.2 M, K = 4096 0.061 -> 0.045. A workgroup is one wave,
+// pair. N = 11 M, K = 65536 (lists of 43 entries; 60 are aimed at now) 0.147 -> 0.129 ms, 4.2 M, K = 4096 0.061 -> 0.045. A workgroup is one wave,
 // as in the kernels for d = 8: two in five items are empty or short, and in a workgroup of four the room of those waves waits for the longest. Three sets of 64 to an
 // item leave six waves to a SIMD, four leave four: 0.153. Rows that are loaded again after the scan for the sake of two more waves, 0.153.
 // Tried with the direct form: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest
