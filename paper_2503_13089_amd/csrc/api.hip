@@ -291,15 +291,15 @@ int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float*
 
 // Whether a fit by cells takes its first E-step by cells too, or by windows. At d = 8 those hold 66 % of the codebook (20 % with rows
 // of different scale), time that grows like N * K; the first way takes two more groupings and lists, time that grows like N and K * K. Windows / cells, ms,
-// K = 65536 unless said, the second pair with rows of different scale (0.3): N = 29 M, 10 iterations 149.5 / 120.2, 151.0 / 138.0 (with slower lists than now);
-// 15 M, 10 66.8 / 63.9; 5.4 M, 5 22.8 / 19.6, 10 31.9 / 32.0; 22 M, K = 16400, 5 36.2 / 32.5, 10 50.9 / 50.6; d = 7, 5.5 M, 5 18.7 / 14.8, 10
-// 24.8 / 23.0; d = 5, 15 M, K = 30000 18.0 / 17.1, 24.1 / 23.5. Below: 4.2 M, 5 18.9 / 16.9, 10 27.2 / 27.6 and 3 14.7 / 15.2; 27 M, K = 10000 38.9 / 37.9, 56.0 /
-// 57.9; d = 5, 5.5 M 9.2 / 9.2, 13.1 / 13.3. At d = 4 the windows take 1.5 of 18 ms and the fit is no faster without.
+// 10 iterations unless said, (s) with rows of different scale (0.3): d = 8: (N, K) = (4.1 M, 30000) 14.65 / 13.93, (4.1 M, 60000) (s) 23.65 / 22.47, (4.1 M, 65500) 3 iterations
+// 13.94 / 11.53 (s), 5 16.48 / 15.43 (s), (10 M, 17000) 21.96 / 21.02, (2 M, 60000) 20 28.16 / 28.00; d = 6, 20: (2.8 M, 65500) 17.39 / 17.25, (4.1 M, 35000) 15.61 / 15.02.
+// Below: d = 8: (4.1 M, 17000) 10.64 / 10.69, (5.6 M, 12000) 11.54 / 11.78, (1.6 M, 60000) 15.06 / 15.38, (1.6 M, 35000) 20 (s) 16.68 / 17.22; d = 7, 20: (1.8 M, 45000) 15.27 / 15.39;
+// d = 6, 20: (1.8 M, 35000) 9.87 / 9.99. d = 5: (4.1 M, 65500) 20 16.01 / 16.35, (15 M, 30000) 18.0 / 17.1. At d = 4 the windows take 1.4 of 12 ms.
 // Inputs that are no fp16 numbers have their far vectors scored on the fp32 matrix cores: d = 5, 15 M, K = 30000, 10 74.7 / 79.3, 22 M, K = 45000 127.1 / 136.3 (fp16
 // numbers 33.1 / 31.4); d = 6, 15 M, K = 30000 and with slower lists 109 / 88, d = 8 153 / 122.
 bool cells_from_first(uint64_t N, uint32_t d, uint32_t d_caller, uint32_t K)
 {
-    return d == 8 && K >= 16384 && N * K >= (d_caller == 5 ? 450000000000ull : 350000000000ull);
+    return d == 8 && K >= 16384 && N >= (1u << 21) && N * K >= (d_caller == 5 ? 450000000000ull : 120000000000ull);
 }
 
 // Iterations of a fit by cells that begin with grouping the vectors by their codes (anew): most codes change early, and a grouping costs

@@ -1,4 +1,4 @@
-"""Fits large enough (d = 8, K >= 16384, N * K >= 3.5e11, at d = 5 4.5e11) that the first E-step goes by cells too, grouped by the codes of a bootstrap and of one
+"""Fits large enough (d = 6 .. 8, K >= 16384, N >= 2^21, N * K >= 1.2e11; d = 5 4.5e11) that the first E-step goes by cells too, grouped by the codes of a bootstrap and of one
 look at the lists: codes and centroids are the bits of the same fit with every E-step over the whole codebook (Section 3.1: the
 codes are the argmin over all centroids), the objective is the sum of the same numbers in another order."""
 import pytest
@@ -35,7 +35,8 @@ def test_first_estep_by_cells_gives_the_bits_of_the_whole_codebook(d, kind):
     assert abs(j.item() - j_whole.item()) <= 2.0 ** -52 * N * j_whole.item()
 
 
-@pytest.mark.parametrize("N,d,K", [(5_344_129, 7, 65500), (5_340_456, 8, 65536), (21_362_305, 8, 16384), (11_250_013, 5, 40000), (6_870_000, 5, 65500)])
+@pytest.mark.parametrize("N,d,K", [(5_344_129, 7, 65500), (5_340_456, 8, 65536), (21_362_305, 8, 16384), (11_250_013, 5, 40000), (6_870_000, 5, 65500),
+                                   (2_097_152, 8, 57221), (7_324_219, 6, 16384), (2_097_151, 7, 60000)])
 def test_fits_at_the_line_have_the_bits_of_the_whole_codebook(N, d, K):
     import paper_2503_13089_amd as cc
 
