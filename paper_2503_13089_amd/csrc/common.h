@@ -597,6 +597,25 @@ __device__ __forceinline__ long long fixed_point_finite(float x, int e)
     return (v ^ s) - s;
 }
 
+// The same terms where they have at most 30 bits above a common unit, 2^(k - e): x in that unit is a whole number t, and the term t * 2^k. Multiplication, fraction, conversion
+// and two shifts, 18 clocks of a SIMD where fixed_point_finite takes 45. Non-finite numbers have no fraction of zero.
+struct ShortTerms {
+    float scale;   // 2^(e - k)
+    uint32_t k;    // 1 .. 31
+};
+__device__ __forceinline__ ShortTerms short_terms(uint32_t absmax_bits, int e)   // |x| < 2^(em + 1): |t| < 2^29
+{
+    const int em = int(absmax_bits >> 23) - 127, s = max(min(28 - em, e - 1), e - 31);
+    return {__uint_as_float(uint32_t(s + 127) << 23), uint32_t(e - s)};
+}
+// Bits other than zero: not a whole number
+__device__ __forceinline__ uint32_t not_whole(float t) { return __float_as_uint(__builtin_amdgcn_fractf(t)); }
+__device__ __forceinline__ unsigned long long short_term(float t, uint32_t k)
+{
+    const int v = int(t);
+    return static_cast<unsigned long long>(uint32_t(v) << k) | static_cast<unsigned long long>(uint32_t(v >> (32 - k))) << 32;
+}
+
 // The same for any input: a non-finite one (which the input scan flags in WsHeader::x_nonfinite) contributes nothing.
 __device__ __forceinline__ long long fixed_point_term(float x, int e)
 {

@@ -25,8 +25,9 @@
 // with rows).
 //
 // Bound, rows along: the passes over memory (chunk kernel 5.6 TB/s, 40 us for the gradient of 4096x11008, 55 for 11.3 M vectors of 4), then
-// 14 vector instructions per number for its fixed-point term (26 us) beside the records from memory (25 us) and the LDS atomics
-// (11 clocks a wave, 14 us). Slices of 2048 clusters at d = 4 then, half the partial sums of 4096. By entries: one row fetch per
+// the records from memory (25 us) beside the LDS atomics (11 clocks a wave, 14 us). A number's fixed-point term took 14 vector instructions (26 us); numbers of 16 bits have
+// at most 30 bits above a unit that nearly all share, which takes 6 (a wave's step that has another takes the 14): with that and the records of two steps under way
+// 11.3 M vectors of 4 99.7 -> 96.2 us a call, the gradient 77.1 -> 74.9. By entries, where rows come a line each, that was no faster. Slices of 2048 clusters at d = 4 then, half the partial sums of 4096. By entries: one row fetch per
 // vector from a different cache line each - the L1 fill rate - or, with few slices, the two passes over the rows.
 // By entries / rows along, us a call, fp32 vectors of 4; numbers of fp16 or bf16 / of neither: 2 M, K = 12000 46 / 39 / 38; 11.3 M, K = 65536 126 / 105 / 120;
 // 20 M, K = 8192 182 / 154 / 188, K = 65536 231 / 159 / 226. 16-bit gradients through an fp32 copy / rows along: 4096x11008 g = 6 344 / 143, g = 9 458 / 187.
@@ -582,7 +583,7 @@ __device__ __forceinline__ bool job_of_workgroup(uint32_t slices, uint32_t range
 // where the runs begin is loaded for 64 units at once, a lane each, and the records of the next step (kStep rows) before those of
 // this one are added.
 template <int D, int SRC, int RECORDS>
-__device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* cnt, int e, uint32_t slice, uint32_t slices,
+__device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* cnt, int e, ShortTerms st, uint32_t slice, uint32_t slices,
                                             uint32_t range, uint32_t ranges, uint32_t chunks, uint32_t sharers,
                                             const char* __restrict__ records, const uint32_t* __restrict__ starts)
 {
@@ -655,18 +656,31 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
         }
     };
     auto add_kind = [&](const Step& s, auto bf16) {
+        float x[U][n], t[U][n];
+        uint32_t fractions = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (u * R + which >= s.rows) continue;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < n; ++j) {
                 const uint32_t w = s.w[u][j / 2];
-                const float x = decltype(bf16)::value ? __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16)
-                                                      : float(__builtin_bit_cast(_Float16, uint16_t(j & 1 ? w >> 16 : w)));
-                atomicAdd(&mine[j * S::kPitch + s.cluster[u]], static_cast<unsigned long long>(fixed_point_finite(x, e)));
+                x[u][j] = decltype(bf16)::value ? __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16)
+                                                : float(__builtin_bit_cast(_Float16, uint16_t(j & 1 ? w >> 16 : w)));
+                t[u][j] = x[u][j] * st.scale;
+                fractions |= not_whole(t[u][j]);
             }
-            if (SRC == 0 && piece == 0) atomicAdd(&cnt[s.cluster[u]], 1u);
-        }
+        auto put = [&](auto shorts) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u * R + which >= s.rows) continue;
+#pragma unroll
+                for (int j = 0; j < n; ++j)
+                    atomicAdd(&mine[j * S::kPitch + s.cluster[u]],
+                              decltype(shorts)::value ? short_term(t[u][j], st.k) : static_cast<unsigned long long>(fixed_point_finite(x[u][j], e)));
+                if (SRC == 0 && piece == 0) atomicAdd(&cnt[s.cluster[u]], 1u);
+            }
+        };
+        if (__any(fractions != 0)) put(std::false_type{});
+        else put(std::true_type{});
     };
     auto add = [&](const Step& s) {
         if (SRC == 2 || (SRC == 0 && s.kind == kRowsBf16)) add_kind(s, std::true_type{});
@@ -675,16 +689,23 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
     end = 0;
     at = 0u - sharers * kStep;   // next() begins with a step
     if (!next()) return;
-    Step a, b;
+    Step a, b, c;   // two steps ahead (a step without rows adds nothing)
     load(a, true);
-    for (bool more = true; more;) {
-        more = next();
-        load(b, more);
+    bool more = next();
+    load(b, more);
+    do {
+        more = more && next();
+        load(c, more);
         add(a);
         more = more && next();
         load(a, more);
         add(b);
-    }
+        more = more && next();
+        load(b, more);
+        add(c);
+    } while (more);
+    add(a);
+    add(b);
 }
 
 // LISTED: by entry lists; otherwise (one slice) the codes themselves, in their order. RECORDS: by what record_chunk_kernel left (2: in wide slices).
@@ -749,7 +770,7 @@ __global__ __launch_bounds__(kThreads) void sliced_accumulate_kernel(const void*
     const bool finite = (flags & 2u) == 0;   // otherwise every number is looked at
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (RECORDS)
-        add_records<D, SRC, RECORDS>(sum, cnt, e, slice, slices, range, ranges, chunks, sharers,
+        add_records<D, SRC, RECORDS>(sum, cnt, e, short_terms(absmax, e), slice, slices, range, ranges, chunks, sharers,
                             reinterpret_cast<const char*>(entries), starts);
     uint32_t bad = 0;
     auto add_entries = [&](auto all_finite) {

@@ -105,3 +105,26 @@ def test_16_bit_gradients_on_either_side_of_2_24_numbers(dt, in_features, out_fe
     cc.layer_codebook_grad(G.to(dt), codes, K, gl, out, ws)
     want = torch.zeros(K, gl, dtype=torch.float64, device="cuda").index_add_(0, idx, G.view(n, gl))
     assert torch.equal(out.cpu(), want.float().cpu())
+
+
+@pytest.mark.parametrize("N,K,scale,least", [(300 * 3584 + 5, 8192, 0, 0), (300 * 3584, 5000, 0, 1e-9), (40000, 9000, 100, 0), (70001, 20000, -90, 0), (70001, 20000, -126, 0), (3_000_001, 65536, -20, 1e-13)])
+def test_terms_of_few_bits_and_others_side_by_side(N, K, scale, least):
+    """bf16 numbers of ordinary range, whose terms have at most 30 bits above a common unit, `least`: with a few among them that have not, over the
+    exponents where the scale of the sums meets its ends."""
+    rng = np.random.default_rng(N + K)
+    X = ((0.02 * rng.standard_normal((N, 4))).astype(np.float32).view(np.uint32) & 0xffff0000).view(np.float32)
+    if least:
+        some = rng.integers(0, N, 50)
+        X[some, rng.integers(0, 4, 50)] = ((least * rng.standard_normal(50)).astype(np.float32).view(np.uint32) & 0xffff0000).view(np.float32)
+    X = ((np.ldexp(X, scale)).astype(np.float32).view(np.uint32) & 0xffff0000).view(np.float32)
+    idx = rng.integers(0, K, size=N).astype(np.uint32)
+    prev = rng.standard_normal((K, 4)).astype(np.float32)
+    print(f"few bits N={N} K={K} scale={scale} least={least}", flush=True)
+    got, counts, stats = g.gpu_update(X, idx, prev)
+    terms = np.rint(np.ldexp(X.astype(np.float64), stats.fixed_point_exp)).astype(np.int64)
+    n = np.bincount(idx, minlength=K)
+    order = np.argsort(idx, kind="stable")
+    sums = np.zeros((K, 4), np.int64)
+    sums[n > 0] = np.add.reduceat(terms[order], np.concatenate(([0], np.cumsum(n)))[:-1][n > 0], axis=0)
+    want = np.where(n[:, None] > 0, np.ldexp(sums.astype(np.float64), -stats.fixed_point_exp) / np.maximum(n, 1)[:, None], prev)
+    assert np.array_equal(counts, n) and got.tobytes() == want.astype(np.float32).tobytes()
