@@ -365,8 +365,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     const uint32_t tile = direct ? job : whole + cut;
     const uint32_t mt = tile % m_tiles, nt = tile / m_tiles;
     const uint32_t m0 = mt * BM, n0 = nt * BN;
-    const uint32_t k_begin = direct ? 0u : split * k_per_split;
-    const uint32_t k_end = direct ? K : min(k_begin + k_per_split, K);
+    const uint32_t k_begin = uint32_t(__builtin_amdgcn_readfirstlane(int(direct ? 0u : split * k_per_split)));
+    const uint32_t k_end = uint32_t(__builtin_amdgcn_readfirstlane(int(direct ? K : min(k_begin + k_per_split, K))));
 
     // x: global -> registers -> LDS in 16-byte pieces, BK / 8 per row and slice; thread t takes piece t % PR of rows
     // t / PR + RP i. Rows past the edge are clamped (their results are never stored); a piece past k_end is read from
@@ -382,22 +382,36 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     constexpr int PR = BK / 8, RP = kGemmThreads / PR, NA = BM / RP;
     static_assert(NA == 2, "the wait counts below assume two pieces of x per thread and slice");
     const uint32_t prow = threadIdx.x / PR, pk = (threadIdx.x % PR) * 8;
-    const uint16_t* a_src[NA];
+    // Where a request goes is a buffer (the tile's rows of x, its column blocks of W), an offset of the lane's that does not change and one of the
+    // contraction's that is a scalar: with addresses made per request the loop had 30 vector instructions beside its 16 matrix instructions, which share the issue with
+    // them. What lies past a buffer's end reads as zero.
+    const uint32_t rows = min(uint32_t(BM), M - m0), block0 = n0 / 32, blocks = min(uint32_t(BN / 32), NB - block0);
+    auto buffer = [](const uint16_t* from, size_t bytes) {
+        const uint64_t at = reinterpret_cast<uint64_t>(from);
+        return u32x4{uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(at)))), uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(at >> 32) & 0xffffu))),
+                     uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(min(bytes, size_t(0x7fffffff)))))), 0x00020000u};
+    };
+    const u32x4 a_buffer = buffer(x + size_t(m0) * K, size_t(rows) * K * 2), b_buffer = buffer(wf + size_t(block0) * KB * kFragHalves, size_t(blocks) * KB * kFragHalves * 2);
+    uint32_t a_off[NA], b_off[2];   // bytes
 #pragma unroll
-    for (int i = 0; i < NA; ++i) a_src[i] = x + size_t(min(m0 + prow + RP * i, M - 1)) * K;
-    const uint16_t* b_src[2];
+    for (int i = 0; i < NA; ++i) a_off[i] = (min(prow + RP * i, rows - 1) * K + pk) * 2;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-        b_src[j] = wf + size_t(min(n0 / 32 + wn * 2 + j, NB - 1)) * KB * kFragHalves + frag_piece(l32, h) * 8;
-    auto request = [](u32x4& r, const uint16_t* p) { asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(r) : "v"(p)); };
-    auto a_addr = [&](int i, uint32_t k0) { return a_src[i] + (k0 + pk < k_end ? k0 + pk : K - 8); };
-    auto b_addr = [&](int j, uint32_t k) { return b_src[j] + size_t(min(k / 16, KB - 1)) * kFragHalves; };
+    for (int j = 0; j < 2; ++j) b_off[j] = (min(uint32_t(wn * 2 + j), blocks - 1) * KB * kFragHalves + frag_piece(l32, h) * 8) * 2;
+    auto request = [](u32x4& r, uint32_t off, const u32x4& from, uint32_t at) {
+        asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(r) : "v"(off), "s"(from), "s"(at));
+    };
+    auto request_a = [&](u32x4& r, int i, uint32_t k0) { request(r, a_off[i], a_buffer, k0 * 2); };
+    auto request_b = [&](u32x4& r, int j, uint32_t k) { request(r, b_off[j], b_buffer, min(k / 16, KB - 1) * (kFragHalves * 2)); };
 #define CC_GEMM_ARRIVED(younger, r) asm volatile("s_waitcnt vmcnt(" #younger ")" : "+v"((r)[0]), "+v"((r)[1]))
-    auto stash = [&](const u32x4 (&a)[NA], int buf, uint32_t k0) {
-        const uint32_t keep = k0 + pk < k_end ? 0xffffffffu : 0u;
+    auto stash = [&](u32x4 (&a)[NA], int buf, uint32_t k0) {
         uint16_t* As = lds + buf * kStageHalves;
+        if (k0 < k_end && k0 + BK > k_end) {   // a last slice that the contraction does not fill: zeros (past the end nobody reads)
+            const uint32_t keep = k0 + pk < k_end ? 0xffffffffu : 0u;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4*>(&As[(prow + RP * i) * LDT + pk]) = a[i] & keep;
+            for (int i = 0; i < NA; ++i) a[i] &= keep;
+        }
+#pragma unroll
+        for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4*>(&As[(prow + RP * i) * LDT + pk]) = a[i];
     };
     const uint16_t* a_lds = lds + (wm * 128 + l32) * LDT + 8 * h;
     auto read_frag = [&](u32x4& a, int i, int buf, int kk) {
@@ -442,13 +456,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
         CC_GEMM_STEP(acc[1][1] = mma<DT>(a0[1], bq[2 * (P)][1], acc[1][1]));                   \
         CC_GEMM_STEP(read_frag(a1[3], 3, P, 1));                                               \
         CC_GEMM_STEP(acc[2][0] = mma<DT>(a0[2], bq[2 * (P)][0], acc[2][0]));                   \
-        CC_GEMM_STEP(request(ar[P][0], a_addr(0, (k0) + 2 * BK)));                             \
+        CC_GEMM_STEP(request_a(ar[P][0], 0, (k0) + 2 * BK));                             \
         CC_GEMM_STEP(acc[2][1] = mma<DT>(a0[2], bq[2 * (P)][1], acc[2][1]));                   \
-        CC_GEMM_STEP(request(ar[P][1], a_addr(1, (k0) + 2 * BK)));                             \
+        CC_GEMM_STEP(request_a(ar[P][1], 1, (k0) + 2 * BK));                             \
         CC_GEMM_STEP(acc[3][0] = mma<DT>(a0[3], bq[2 * (P)][0], acc[3][0]));                   \
-        CC_GEMM_STEP(request(bq[(2 * (P) + 3) % 4][0], b_addr(0, (k0) + BK + 16)));            \
+        CC_GEMM_STEP(request_b(bq[(2 * (P) + 3) % 4][0], 0, (k0) + BK + 16));            \
         CC_GEMM_STEP(acc[3][1] = mma<DT>(a0[3], bq[2 * (P)][1], acc[3][1]));                   \
-        CC_GEMM_STEP(request(bq[(2 * (P) + 3) % 4][1], b_addr(1, (k0) + BK + 16)));            \
+        CC_GEMM_STEP(request_b(bq[(2 * (P) + 3) % 4][1], 1, (k0) + BK + 16));            \
         CC_GEMM_ARRIVED(8, ar[1 - (P)]);                                                       \
         stash(ar[1 - (P)], 1 - (P), (k0) + BK);                                                \
         __syncthreads();                                                                       \
@@ -465,22 +479,22 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
         CC_GEMM_STEP(acc[2][0] = mma<DT>(a1[2], bq[2 * (P) + 1][0], acc[2][0]));               \
         CC_GEMM_STEP(acc[2][1] = mma<DT>(a1[2], bq[2 * (P) + 1][1], acc[2][1]));               \
         CC_GEMM_STEP(acc[3][0] = mma<DT>(a1[3], bq[2 * (P) + 1][0], acc[3][0]));               \
-        CC_GEMM_STEP(request(bq[2 * (P)][0], b_addr(0, (k0) + 2 * BK)));                       \
+        CC_GEMM_STEP(request_b(bq[2 * (P)][0], 0, (k0) + 2 * BK));                       \
         CC_GEMM_STEP(acc[3][1] = mma<DT>(a1[3], bq[2 * (P) + 1][1], acc[3][1]));               \
-        CC_GEMM_STEP(request(bq[2 * (P)][1], b_addr(1, (k0) + 2 * BK)));                       \
+        CC_GEMM_STEP(request_b(bq[2 * (P)][1], 1, (k0) + 2 * BK));                       \
     } while (0)
 
     // before the first slice: the same requests in the same order, as far as they exist
-    request(ar[0][0], a_addr(0, k_begin));
-    request(ar[0][1], a_addr(1, k_begin));
-    request(bq[0][0], b_addr(0, k_begin));
-    request(bq[0][1], b_addr(1, k_begin));
-    request(ar[1][0], a_addr(0, k_begin + BK));
-    request(ar[1][1], a_addr(1, k_begin + BK));
-    request(bq[1][0], b_addr(0, k_begin + 16));
-    request(bq[1][1], b_addr(1, k_begin + 16));
-    request(bq[2][0], b_addr(0, k_begin + BK));
-    request(bq[2][1], b_addr(1, k_begin + BK));
+    request_a(ar[0][0], 0, k_begin);
+    request_a(ar[0][1], 1, k_begin);
+    request_b(bq[0][0], 0, k_begin);
+    request_b(bq[0][1], 1, k_begin);
+    request_a(ar[1][0], 0, k_begin + BK);
+    request_a(ar[1][1], 1, k_begin + BK);
+    request_b(bq[1][0], 0, k_begin + 16);
+    request_b(bq[1][1], 1, k_begin + 16);
+    request_b(bq[2][0], 0, k_begin + BK);
+    request_b(bq[2][1], 1, k_begin + BK);
     CC_GEMM_ARRIVED(8, ar[0]);
     stash(ar[0], 0, k_begin);
     __syncthreads();
