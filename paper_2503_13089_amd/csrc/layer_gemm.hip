@@ -369,22 +369,23 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     const uint32_t k_end = uint32_t(__builtin_amdgcn_readfirstlane(int(direct ? K : min(k_begin + k_per_split, K))));
 
     // x: global -> registers -> LDS in 16-byte pieces, BK / 8 per row and slice; thread t takes piece t % PR of rows
-    // t / PR + RP i. Rows past the edge are clamped (their results are never stored); a piece past k_end is read from
-    // the last valid piece of its row instead and goes to LDS as zeros (K and k_per_split are multiples of 8).
+    // t / PR + RP i. Rows past the edge are clamped (their results are never stored); a piece past k_end goes to LDS as
+    // zeros (K and k_per_split are multiples of 8).
     // W: this wave's two column blocks, fragments straight from memory; a block past the last one is clamped (its
     // columns are never stored), a fragment past the end of the contraction reads the last one (and is never used).
     //
     // The global loads of the main loop are written as instructions, with the waits on them placed by hand: the
     // compiler otherwise moves each request down to the slice that uses it, where its whole latency is exposed. The
     // memory counter retires loads in order, so a wait names how many younger requests may still be in flight. Every
-    // slice issues the same six requests, past the end of the contraction too (clamped addresses, results unused),
+    // slice issues the same six requests, past the end of the contraction too (clamped offsets, results unused),
     // which keeps those numbers the same for every slice.
     constexpr int PR = BK / 8, RP = kGemmThreads / PR, NA = BM / RP;
     static_assert(NA == 2, "the wait counts below assume two pieces of x per thread and slice");
     const uint32_t prow = threadIdx.x / PR, pk = (threadIdx.x % PR) * 8;
     // Where a request goes is a buffer (the tile's rows of x, its column blocks of W), an offset of the lane's that does not change and one of the
-    // contraction's that is a scalar: with addresses made per request the loop had 30 vector instructions beside its 16 matrix instructions, which share the issue with
-    // them. What lies past a buffer's end reads as zero.
+    // contraction's that is a scalar, clamped to the last piece: with addresses made per request the loop had 30 vector instructions beside its 16 matrix
+    // instructions, which share the issue with them (2048 x 4096 x 11008, bf16, a call 223 / 213 us; 4096^3 149 / 142). What lies past a buffer's end (the pieces
+    // beside the last one, in the last row) reads as zero. A buffer has at most 512 K bytes, 2^31 - 2^15 at the most in-features that the rebuild takes.
     const uint32_t rows = min(uint32_t(BM), M - m0), block0 = n0 / 32, blocks = min(uint32_t(BN / 32), NB - block0);
     auto buffer = [](const uint16_t* from, size_t bytes) {
         const uint64_t at = reinterpret_cast<uint64_t>(from);
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     auto request = [](u32x4& r, uint32_t off, const u32x4& from, uint32_t at) {
         asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(r) : "v"(off), "s"(from), "s"(at));
     };
-    auto request_a = [&](u32x4& r, int i, uint32_t k0) { request(r, a_off[i], a_buffer, k0 * 2); };
+    auto request_a = [&](u32x4& r, int i, uint32_t k0) { request(r, a_off[i], a_buffer, min(k0, K - 8) * 2); };
     auto request_b = [&](u32x4& r, int j, uint32_t k) { request(r, b_off[j], b_buffer, min(k / 16, KB - 1) * (kFragHalves * 2)); };
 #define CC_GEMM_ARRIVED(younger, r) asm volatile("s_waitcnt vmcnt(" #younger ")" : "+v"((r)[0]), "+v"((r)[1]))
     auto stash = [&](u32x4 (&a)[NA], int buf, uint32_t k0) {
