@@ -39,7 +39,9 @@ constexpr int kGemmThreads = 128 * WN;
 constexpr int BM = 256, BN = 64 * WN, BK = 32;
 constexpr int LDT = BK + 8;                 // halves per LDS row (20 words: the 16-byte reads of 16 lanes hit 16 bank quads)
 constexpr int kStageHalves = BM * LDT;
-constexpr uint32_t kGemmLdsBytes = 2 * kStageHalves * 2;   // 40,960 bytes
+constexpr int kOutPitch = 64 + 4;             // floats per LDS row of the epilogue: 32 rows of a wave's 64 columns
+constexpr uint32_t kGemmLdsBytes = 2 * WN * 32 * kOutPitch * 4;   // 69,632 bytes; the slices of x take 40,960
+static_assert(kGemmLdsBytes >= 2 * kStageHalves * 2, "room for two slices");
 constexpr int kFragHalves = 512;            // one B operand: 32 columns x 16 in-features
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -512,31 +514,59 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
 #undef CC_GEMM_STEP
 #undef CC_GEMM_ARRIVED
 
-    // ---- epilogue: accumulator register r of lane (l32, h) is row r % 4 + 8 (r / 4) + 4 h, column l32 of its tile
+    // ---- epilogue: accumulator register r of lane (l32, h) is row r % 4 + 8 (r / 4) + 4 h, column l32 of its tile. 32 rows of the wave at a time go through
+    // LDS, and from there as 16-byte pieces: stored from the registers, 2 bytes a lane, the tile took 128 store instructions a wave where these are 16 (2048 x 4096 x 11008, a call 213 / 202 us; 4096^3 142 / 134).
+    __syncthreads();   // the last slice has been read
     const float sc = (direct && scale != nullptr) ? *scale : 1.0f;
+    float bv[8];   // of this lane's columns
+    if (direct && bias != nullptr) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bv[e] = to_f32<DT>(bias[min(n0 + wn * 64 + 8 * (lane % 8) + e, N - 1)]);
+    }
     const uint32_t l_column = block_column(l32, g);
+    float* const out = reinterpret_cast<float*>(lds) + wave * (32 * kOutPitch);
     float* ptile = partial + (size_t(cut) * f + split) * (BM * BN);
+    typedef u32x4 u32x4_2 __attribute__((aligned(2)));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows before have been read
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t nl = wn * 64 + 32 * j + l_column, n = n0 + nl;
-            if (n >= N) continue;
-            const float bv = (direct && bias != nullptr) ? to_f32<DT>(bias[n]) : 0.0f;
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t ml = wm * 128 + 32 * i + (r & 3) + 8 * (r >> 2) + 4 * h, m = m0 + ml;
-                if (m >= M) continue;
-                if (direct) {
-                    float v = acc[i][j][r];
-                    if (scale != nullptr) v *= sc;
-                    if (bias != nullptr) v += bv;
-                    y[size_t(m) * N + n] = from_f32<DT>(v);
+            for (int r = 0; r < 16; ++r) out[((r & 3) + 8 * (r >> 2) + 4 * h) * kOutPitch + 32 * j + l_column] = acc[i][j][r];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // a wave's own: no barrier
+        if (direct) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {   // 8 rows of 8 pieces of 8 columns
+                const uint32_t row = 8 * t + lane / 8, nl = wn * 64 + 8 * (lane % 8), n = n0 + nl, m = m0 + wm * 128 + 32 * i + row;
+                const float4 lo = *reinterpret_cast<const float4*>(out + row * kOutPitch + 8 * (lane % 8)), hi = *reinterpret_cast<const float4*>(out + row * kOutPitch + 8 * (lane % 8) + 4);
+                float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                if (m >= M || n >= N) continue;
+                u32x4 piece;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (scale != nullptr) v[e] *= sc;
+                    if (bias != nullptr) v[e] += bv[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) piece[e] = uint32_t(from_f32<DT>(v[2 * e])) | uint32_t(from_f32<DT>(v[2 * e + 1])) << 16;
+                uint16_t* to = y + size_t(m) * N + n;
+                if (n + 8 <= N) {
+                    *reinterpret_cast<u32x4_2*>(to) = piece;
                 } else {
-                    ptile[ml * BN + nl] = acc[i][j][r];
+#pragma unroll
+                    for (int e = 0; e < 7; ++e)
+                        if (n + e < N) to[e] = uint16_t(piece[e / 2] >> (16 * (e % 2)));
                 }
             }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {   // 4 rows of 16 pieces of 4 columns; rows and columns past the edges nobody reads
+                const uint32_t row = 4 * t + lane / 16, ml = wm * 128 + 32 * i + row;
+                *reinterpret_cast<float4*>(ptile + ml * BN + wn * 64 + 4 * (lane % 16)) = *reinterpret_cast<const float4*>(out + row * kOutPitch + 4 * (lane % 16));
+            }
         }
+    }
 }
 
 // The tiles of the partial round: y = round(scale * (sum of the f slices, in order) + bias); scale may be NULL (= 1)
@@ -650,6 +680,8 @@ hipError_t launch_layer_gemm(const void* x, uint32_t M, const void* wf, int dtyp
                              const float* scale, const void* bias, void* y, float* partial, uint32_t group, hipStream_t s)
 {
     const GemmShape g = gemm_shape(M, in_features, out_features);
+    const auto kernel = dtype == 1 ? gemm_frag_kernel<1> : gemm_frag_kernel<2>;
+    if (const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(kGemmLdsBytes)); e != hipSuccess) return e;
     const dim3 grid(8 * ((g.whole + 7) / 8) + 8 * ((g.jobs - g.whole + 7) / 8));
     const uint16_t* xs = static_cast<const uint16_t*>(x);
     const uint16_t* ws = static_cast<const uint16_t*>(wf);
@@ -657,12 +689,8 @@ hipError_t launch_layer_gemm(const void* x, uint32_t M, const void* wf, int dtyp
     uint16_t* ys = static_cast<uint16_t*>(y);
     const uint32_t NB = (out_features + 31) / 32, KB = (in_features + 15) / 16;
     if (dtype != 1 && dtype != 2) return hipErrorInvalidValue;
-    if (dtype == 1)
-        hipLaunchKernelGGL(gemm_frag_kernel<1>, grid, dim3(kGemmThreads), kGemmLdsBytes, s, xs, ws, M, out_features, in_features, NB,
-                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs, group);
-    else
-        hipLaunchKernelGGL(gemm_frag_kernel<2>, grid, dim3(kGemmThreads), kGemmLdsBytes, s, xs, ws, M, out_features, in_features, NB,
-                           KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs, group);
+    hipLaunchKernelGGL(kernel, grid, dim3(kGemmThreads), kGemmLdsBytes, s, xs, ws, M, out_features, in_features, NB,
+                       KB, scale, bs, ys, partial, g.m_tiles, g.whole, g.f, g.k_per_split, g.jobs, group);
     if (g.cut_tiles > 0) {
         const dim3 fgrid(BM * BN / kThreads, g.cut_tiles);
         if (dtype == 1)
