@@ -46,3 +46,27 @@ def test_workspace_for_the_rebuilt_route_alone_is_enough(cc):
         assert bool(((y.double() - want).abs() <= 2.0 ** -8 * want.abs() + i * 2.0 ** -24 * size).all())
     with pytest.raises(cc.CCError):
         cc.layer_forward(x, book, codes, o, None, y, torch.empty(dense - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("out_features", [1, 7, 8, 65, 255, 259, 518])   # the last piece of 8 columns whole and of each kind of part
+@pytest.mark.parametrize("M,in_features", [(385, 8), (513, 40), (641, 1040)])   # whole tiles, one and 128 rows in the last; cut tiles
+def test_a_tile_is_stored_to_its_ends_and_no_further(cc, M, in_features, out_features, dt):
+    gen = torch.Generator(device="cuda").manual_seed(M + out_features)
+    K, g = 500, 4
+    codes = torch.randint(0, K, (cc.layer_num_codes(in_features, out_features, g),), device="cuda", generator=gen).to(torch.int16).view(torch.uint16)
+    book = (torch.randn(K, g, device="cuda", generator=gen) * 0.05).to(dt)
+    x = torch.randn(M, in_features, device="cuda", generator=gen).to(dt)
+    bias = torch.randn(out_features, device="cuda", generator=gen).to(dt)
+    w = torch.empty(in_features, out_features, dtype=dt, device="cuda")
+    cc.layer_weight(book, codes, in_features, out_features, w)
+    room = torch.full((M * out_features + 512,), 9.0, dtype=dt, device="cuda")
+    y = room[:M * out_features].view(M, out_features)
+    ws = torch.empty(cc.layer_forward_workspace_bytes(M, in_features, out_features), dtype=torch.uint8, device="cuda")
+    cc.layer_forward(x, book, codes, out_features, bias, y, ws)
+    want = x.double() @ w.double() + bias.double()
+    size = x.double().abs() @ w.double().abs() + bias.double().abs()
+    # exact products, in_features + 1 sums in fp32, one rounding
+    tol = (2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -11) * want.abs() + (in_features + 1) * 2.0 ** -24 * size + 2.0 ** -24
+    assert bool(((y.double() - want).abs() <= tol).all())
+    assert bool((room[M * out_features:] == 9.0).all())
