@@ -76,37 +76,32 @@ __global__ __launch_bounds__(kThreads) void pack_codebook_kernel(const float* __
 
 // ---------------------------------------------------------------------------------------------
 // WINDOWED = false: the whole packed codebook in stages of ST tiles. WINDOWED = true: the runs of the
-// workgroup's window list (stages of kStageTiles tiles, tiles outside a run skipped).
-template <int D, int VT, int ST, int GT, bool WINDOWED>
-__global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* __restrict__ X, uint32_t N,
-                                                               const float* __restrict__ C, uint32_t K,
-                                                               const float* __restrict__ packed, uint32_t ntiles,
-                                                               uint32_t* __restrict__ idx, float* __restrict__ dmin,
-                                                               WsHeader* hdr, uint32_t* __restrict__ refine_list,
-                                                               uint32_t refine_cap, int gate, long long* sums,
-                                                               uint32_t* counts, const uint2* __restrict__ windows,
-                                                               const uint32_t* __restrict__ cperm, int hint_only,
-                                                               uint32_t* __restrict__ prev_out,
-                                                               uint32_t* __restrict__ changed,
-                                                               const uint32_t* __restrict__ n_dev, const uint32_t* __restrict__ out_pos)
+// workgroup's window list (stages of kStageTiles tiles, tiles outside a run skipped). TURNS: n_dev vectors, at most N (windowed; far vectors of a fit by
+// cells), workgroups taking turns at them.
+template <int D, int VT, int ST, int GT, bool WINDOWED, bool TURNS>
+__device__ __forceinline__ void assign_mfma_sets(float4 (&lds)[2][ST * (64 * (D / 2) + 32) / 4], const float* __restrict__ X, uint32_t N,
+                                                 const float* __restrict__ C, uint32_t K,
+                                                 const float* __restrict__ packed, uint32_t ntiles,
+                                                 uint32_t* __restrict__ idx, float* __restrict__ dmin,
+                                                 WsHeader* hdr, uint32_t* __restrict__ refine_list,
+                                                 uint32_t refine_cap, long long* sums,
+                                                 uint32_t* counts, const uint2* __restrict__ windows,
+                                                 const uint32_t* __restrict__ cperm, int hint_only,
+                                                 uint32_t* __restrict__ prev_out,
+                                                 uint32_t* __restrict__ changed, const uint32_t* __restrict__ out_pos)
 {
     constexpr int KS = D / 2;                 // MFMA k-steps per tile
-    if (!gate_open(hdr, gate)) return;        // uniform over the grid
     constexpr int TF = 64 * KS + 32;          // floats per packed tile
     constexpr int STAGE_F4 = ST * TF / 4;     // float4 per LDS stage
     constexpr int NPF = (STAGE_F4 + kThreads - 1) / kThreads;
     static_assert(ST % GT == 0, "a tracking group must not straddle LDS stages");
     static_assert(!WINDOWED || ST == int(kStageTiles), "window runs never share a stage of kStageTiles tiles");
-    __shared__ float4 lds[2][STAGE_F4];
-
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int h = lane >> 5, n = lane & 31;
+    const uint32_t sets = TURNS ? (N + 4 * 32 * VT - 1) / (4 * 32 * VT) : gridDim.x;
+    for (uint32_t turn = blockIdx.x; turn < sets; turn += gridDim.x) {
     // a windowed launch starts with the last tiles of the norm order, whose windows are the widest (as in the fp16 kernel)
-    const uint32_t wg = WINDOWED ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
-    if (n_dev != nullptr) {  // fewer vectors than the grid was made for (uniform over the workgroup)
-        N = min(N, *n_dev);
-        if (wg * (4 * 32 * VT) >= N) return;
-    }
+    const uint32_t wg = WINDOWED ? sets - 1 - turn : turn;
     const uint32_t vbase = (wg * 4 + wave) * (32 * VT);
 
     // B operands: lane (n, h) supplies -2 * x_n[2 ks + h] for k-step ks
@@ -129,7 +124,7 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
     // ntiles is a multiple of ST (padding rows carry ||c||^2 = +inf), so every stage is whole
     const float4* P4 = reinterpret_cast<const float4*>(packed);
     // Stages to score: the whole packed codebook, or the runs of this workgroup's 512-vector tile.
-    const uint2* wl = WINDOWED ? windows + size_t((wg * (4 * 32 * VT)) / kWinTile) * (n_dev != nullptr ? kFarWinStride : kWinStride) : nullptr;
+    const uint2* wl = WINDOWED ? windows + (TURNS ? size_t(wg) * kFarWinStride : size_t((wg * (4 * 32 * VT)) / kWinTile) * kWinStride) : nullptr;
     const uint32_t nruns = WINDOWED ? wl[0].x : 1u;
     uint32_t run = 0;
     uint2 cur_run = WINDOWED ? wl[1] : make_uint2(0, ntiles);  // [first tile, end tile)
@@ -285,6 +280,38 @@ __global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* _
             if (lane == 0 && vbase + vt * 32 < N) changed[(vbase + vt * 32) >> 5] = uint32_t(m);
         }
     }
+    if constexpr (!TURNS) break;
+    }   // (the last barrier above is behind the last read of a stage)
+}
+
+template <int D, int VT, int ST, int GT, bool WINDOWED, bool TURNS>
+__global__ __launch_bounds__(kThreads, 2) void assign_mfma_kernel(const float* __restrict__ X, uint32_t N,
+                                                               const float* __restrict__ C, uint32_t K,
+                                                               const float* __restrict__ packed, uint32_t ntiles,
+                                                               uint32_t* __restrict__ idx, float* __restrict__ dmin,
+                                                               WsHeader* hdr, uint32_t* __restrict__ refine_list,
+                                                               uint32_t refine_cap, int gate, long long* sums,
+                                                               uint32_t* counts, const uint2* __restrict__ windows,
+                                                               const uint32_t* __restrict__ cperm, int hint_only,
+                                                               uint32_t* __restrict__ prev_out,
+                                                               uint32_t* __restrict__ changed,
+                                                               const uint32_t* __restrict__ n_dev, const uint32_t* __restrict__ out_pos)
+{
+    if (!gate_open(hdr, gate)) return;        // uniform over the grid
+    __shared__ float4 lds[2][ST * (64 * (D / 2) + 32) / 4];
+    if constexpr (TURNS) {
+        const uint32_t far = min(N, *n_dev);
+        if (far_window_tile(hdr, D, N) < kWinTile) {
+            assign_mfma_sets<D, 1, ST, GT, true, true>(lds, X, far, C, K, packed, ntiles, idx, dmin, hdr, refine_list, refine_cap, sums, counts, windows, cperm, hint_only,
+                                                       prev_out, changed, out_pos);
+        } else {
+            assign_mfma_sets<D, VT, ST, GT, true, true>(lds, X, far, C, K, packed, ntiles, idx, dmin, hdr, refine_list, refine_cap, sums, counts, windows, cperm, hint_only,
+                                                        prev_out, changed, out_pos);
+        }
+    } else {
+        assign_mfma_sets<D, VT, ST, GT, WINDOWED, false>(lds, X, N, C, K, packed, ntiles, idx, dmin, hdr, refine_list, refine_cap, sums, counts, windows, cperm, hint_only,
+                                                         prev_out, changed, out_pos);
+    }
 }
 
 template <int D, int VT, int ST>
@@ -298,11 +325,15 @@ static hipError_t launch_t(const EStep& e, const Workspace& w, hipStream_t s)
                            dim3(kThreads), 0, s, e.pack_rows, e.K, e.packed_tiles, static_cast<float*>(e.packed), w.hdr, e.gate);
     constexpr int VTW = VT * 128 > int(kWinTile) ? int(kWinTile) / 128 : VT;
     const uint32_t per_block = 4 * 32 * (e.windows != nullptr ? VTW : VT);
-    const auto kernel = e.windows != nullptr ? assign_mfma_kernel<D, VTW, int(kStageTiles), GT, true>
-                                             : assign_mfma_kernel<D, VT, ST, GT, false>;
+    auto kernel = e.windows != nullptr ? assign_mfma_kernel<D, VTW, int(kStageTiles), GT, true, false> : assign_mfma_kernel<D, VT, ST, GT, false, false>;
+    if constexpr (D <= 8)
+        if (e.n_dev != nullptr) kernel = assign_mfma_kernel<D, VTW, int(kStageTiles), GT, true, true>;
     {
         ProfileScope scope(e.profile, kProfEstepF32, s);
-        hipLaunchKernelGGL(kernel, dim3((e.N + per_block - 1) / per_block), dim3(kThreads), 0, s,
+        // A device-side count (far vectors: a few percent of N, none unless the inputs are no fp16 numbers) is met by a grid that takes turns: one for N is
+        // 22016 workgroups at 11 M, which find nothing to do in 6.5 us where these take 4.7.
+        const uint32_t all = (e.N + per_block - 1) / per_block;
+        hipLaunchKernelGGL(kernel, dim3(e.n_dev != nullptr ? std::min(all, 2048u) : all), dim3(kThreads), 0, s,
                            e.X, e.N, e.rows, e.K, static_cast<const float*>(e.packed), e.packed_tiles, e.idx, w.dmin, w.hdr,
                            w.refine_list, w.refine_cap, e.gate, e.accumulate ? w.sums : nullptr,
                            e.accumulate ? w.counts : nullptr, e.windows, e.row_ids, e.hint_only ? 1 : 0,

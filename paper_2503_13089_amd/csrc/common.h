@@ -267,12 +267,16 @@ hipError_t launch_assign_direct(const float* X, uint32_t N, uint32_t d, const fl
 constexpr uint32_t kFarFew1 = 32 * 256, kFarFew2 = 64 * 256, kFarFew4 = 4 * 128 * 256;
 // How many far vectors, neighbours in their list, share a window: those of a workgroup. 512 of them lie far apart, and so their windows held 64 % of the codebook
 // at d = 8 (29 M, K = 65536) and 10 % at d = 4 (11 M) where those of 256 and 128 with room for two octaves of shells hold 38 % and 6 % (fits of
-// 10 and 20 iterations 87.9 -> 81.2 and 12.98 -> 12.67 ms). 512 where the windows would need more room than there is, and for the fp32 variant, which
-// gives 512 to a workgroup.
+// 10 and 20 iterations 87.9 -> 81.2 and 12.98 -> 12.67 ms). 512 where the windows would need more room than there is.
+// Inputs that are no fp16 numbers, on the fp32 matrix cores: 128 to a workgroup up to 2^17 of them, else 512, whose tiles come through LDS for four times the
+// products. Fits of 10 iterations with 512 always / this rule, ms: (4 M, d = 4, K = 30000) 6.94 / 5.20, (16 M, 4, 65536) 19.7 / 17.6,
+// (2 M, 8, 8192) 10.9 / 10.0; up to 2^19 of them (4 M, 8, 30000) 32.0 / 30.0, (16 M, 4, 65536) 17.6 / 17.3, but (16 M, 8, 40000) 121 / 123.
+constexpr uint32_t kFarFewF32 = 1u << 17;
 __device__ __forceinline__ uint32_t far_window_tile(const WsHeader* hdr, uint32_t d, uint32_t N)
 {
     const uint32_t far = hdr->far_count;
-    if (hdr->x_not_f16 != 0 || far > N / 2) return kWinTile;
+    if (far > N / 2 || (hdr->x_not_f16 != 0 && far > kFarFewF32)) return kWinTile;
+    if (hdr->x_not_f16 != 0) return 128u;
     return far <= kFarFew1 ? 32u : (far <= kFarFew2 ? 64u : (d == 4 || far <= kFarFew4 ? 128u : 256u));
 }
 

@@ -59,3 +59,29 @@ def test_more_than_half_of_the_vectors_far(d, copies, seed):
     print("far:", far, flush=True)
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert far > N // 2
+
+
+@pytest.mark.parametrize("N,d,K,share,least,most", [
+    ((3 << 19) + 77, 4, 1055, 0.0001, 1, 2048), ((3 << 19) + 77, 4, 1055, 0.02, 8192, 131072), ((1 << 22) + 77, 4, 1055, 0.15, 131073, 1 << 20),
+    ((3 << 19) + 33, 8, 1025, 0.004, 1, 131072), ((1 << 21) + 33, 8, 1025, 0.15, 131073, 1 << 20)])
+def test_far_vectors_that_are_no_fp16_numbers(N, d, K, share, least, most):
+    """128 to a workgroup up to 2^17 of them, else 512; workgroups take turns."""
+    import paper_2503_13089_amd as cc
+
+    gen = torch.Generator(device="cuda").manual_seed(K + d)
+    c0 = torch.randn(K, d, device="cuda", generator=gen).mul_(0.05)
+    x = c0[torch.randint(0, K, (N,), device="cuda", generator=gen)] + 0.002 * torch.randn(N, d, device="cuda", generator=gen)
+    x[:int(share * N)] += 0.05 * torch.randn(int(share * N), d, device="cuda", generator=gen)
+    ws = torch.empty(cc.workspace_bytes(N, d, K), dtype=torch.uint8, device="cuda")
+    out = []
+    for mode in (0, 1):
+        c, idx, j = torch.empty_like(c0), torch.empty(N, dtype=torch.uint32, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+        print(f"far fp32 vectors N={N} d={d} K={K} share={share} mode={mode}", flush=True)
+        cc.kmeans_fit(x, K, 5, c0, c, idx, j, ws, assign_mode=mode)
+        torch.cuda.synchronize()
+        if mode == 0:
+            far = int(ws[64:68].view(torch.int32).item())
+        out.append((c, idx.view(torch.int32)))
+    print("far:", far, flush=True)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert least <= far <= most
