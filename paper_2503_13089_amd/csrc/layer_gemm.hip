@@ -574,9 +574,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
             }
         } else {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {   // 4 rows of 16 pieces of 4 columns; rows and columns past the edges nobody reads
+            for (int t = 0; t < 8; ++t) {   // 4 rows of 16 pieces of 4 columns; columns past the edge nobody reads
                 const uint32_t row = 4 * t + lane / 16, ml = wm * 128 + 32 * i + row;
-                *reinterpret_cast<float4*>(ptile + ml * BN + wn * 64 + 4 * (lane % 16)) = *reinterpret_cast<const float4*>(out + row * kOutPitch + 4 * (lane % 16));
+                if (m0 + ml < M) *reinterpret_cast<float4*>(ptile + ml * BN + wn * 64 + 4 * (lane % 16)) = *reinterpret_cast<const float4*>(out + row * kOutPitch + 4 * (lane % 16));
             }
         }
     }
