@@ -256,6 +256,18 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
     if (m > __builtin_nontemporal_load(&hdr->cmax_bits)) atomicMax(&hdr->cmax_bits, m);
 }
 
+// Where a centroid stands among the operands of the lists. d = 8: tiles come in pairs, whose results for a lane are made one six-bit number each, the pair's in turn, by one
+// instruction (score_bits); z, the place of its two bits in a word from the top, says which of the 2 x 8 results of that word it is.
+struct ListRow {
+    uint32_t tile, row;
+};
+__device__ __forceinline__ ListRow paired_row(uint32_t at)
+{
+    const uint32_t word = (at >> 5) & 1u, h = (at >> 4) & 1u, p = 15u - (at & 15u), in = p / 3u;   // p: from the bottom
+    const uint32_t turn = p % 3u == 2u ? in : (p % 3u == 1u ? 5u + in : 10u + in), reg = 8u * word + turn / 2u;
+    return {(at >> 6) * 2u + (turn & 1u), reg % 4u + 8u * (reg / 4u) + 4u * h};
+}
+
 // Every centroid to its place: permutation and inverse, ordered row, the operand row of the E-step's packed codebook
 // (assign_mfma_f16.hip) and the one of the lists: 8 product slots (the first fp16 part of each component) and
 // 8 for norm and threshold: sigma ||c||^2 in three parts against the multipliers 2^8, 2^-3, 2^-14 of the other side, and
@@ -326,9 +338,10 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
         }
     }
     const uint32_t at = D == 4 ? pos : k;   // d = 8: lists take the whole codebook, and hold indices
-    if (at >= (K + 31) / 32 * 32) return;   // tile by tile
-    const uint32_t q = at & 31u, m = 4 * (q >> 4) + (q & 3u) + 8 * ((q & 15u) >> 2);
-    char* op = operands + size_t(at >> 5) * 1024;
+    if (at >= list_tiles(D, K) * 32) return;   // tile by tile
+    const ListRow row = D == 4 ? ListRow{at >> 5, 4 * ((at & 31u) >> 4) + (at & 3u) + 8 * ((at & 15u) >> 2)} : paired_row(at);
+    const uint32_t m = row.row;
+    char* op = operands + size_t(row.tile) * 1024;
     f16x8 lo, hi;
 #pragma unroll
     for (int j = 0; j < 8; ++j) lo[j] = j < D ? parts[j % D][0] : _Float16(0.0f);
@@ -346,23 +359,41 @@ __global__ __launch_bounds__(kThreads) void cell_place_kernel(const float* __res
 // or less. The cells' counters are in LDS. Where in a list an entry lands depends on scheduling; no result does.
 // WINDOWED (d = 4): only the runs of the ordered codebook that the shells and cosines of sort.hip allow for the 32 cells;
 // at d = 8 a ball that is 1 % of the codebook touches most of them.
-// Bound: vector instructions, 16 for a tile's bits and as many again for its hits, and L2 (a KB of operands per product, 2 bytes per
-// entry written on their own: the channels are busy nine clocks of ten). K = 65536: 4.3 G pairs at d = 8 in 0.26 ms (lists of 2.8 M vectors) and 0.49
-// (29 M, the first lists are longer), 0.06 at d = 4 (11 M); 0.32, 0.79 and 0.08 with 4 waves to a workgroup, 4 tiles at a time and the inner shells first.
+// d = 8: sign and upper exponent bit of 32 results come out of one conversion to six-bit numbers (64 clocks; shifted into a word one by one they take 128) and
+// two selections per word. Vector instructions (16 a tile with those of its hits; 35 before, with 64-bit addresses and operands copied out of the way of
+// the next) take four fifths of the time, L2 most of the rest (a KB of operands per product, 2 bytes per entry written on their own). K = 65536: 4.3 G pairs at d = 8 in 0.22 ms
+// (lists of 2.8 M vectors; 0.26 before), 0.06 at d = 4 (11 M). Entries gathered in LDS and written in runs, between barriers every 8 or 16 pairs of tiles:
+// 0.28.
 // Two products per tile (64 cells to a workgroup) halve the loads and lose: 0.32 -> 0.39.
 constexpr float kListThrMax = 1.5e7f;     // what three fp16 parts against 2^8, 2^-3, 2^-14 can carry
 // Waves of a workgroup. With 4 the whole launch is on the chip at once and ends on the few workgroups of the outer shells, whose lists are the longest;
 // with 8 or 16 those start first and are shared by more.
 template <int D> constexpr int kListWaves = D == 4 ? 8 : 16;
+// Two bits of each of 2 x 16 results, sign and upper exponent bit (-2 or less after rounding to four of them: from -1.9375 on), as words of 16 pairs (paired_row).
+// The last statement keeps the result out of the operands' registers: written there, it destroys what has not been read yet, and the compiler does not know.
+__device__ __forceinline__ void score_bits(const f32x16& a, const f32x16& b, uint32_t (&word)[2])
+{
+    u32x6 v = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
+    asm volatile("" : "+v"(v) : "v"(a), "v"(b));
+    uint32_t m0 = 0x30c30c30u, m1 = 0x0c30c30cu;   // of a word of three; the third's are the rest
+    asm("" : "+s"(m0), "+s"(m1));   // two selections, which the compiler takes apart where it knows the masks, or what is asked of the word
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t rest = (v[3 * i + 1] & m1) | (v[3 * i + 2] & ~m1);
+        word[i] = (v[3 * i] & m0) | (rest & ~m0);
+        asm("" : "+v"(word[i]));
+    }
+}
 
 template <int D, bool WINDOWED>
-__global__ __launch_bounds__(64 * kListWaves<D>, 4) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
+__global__ __launch_bounds__(64 * kListWaves<D>, 8) void cell_lists_kernel(const float* __restrict__ csorted, const uint32_t* __restrict__ cperm,
                                                               uint32_t K, const char* __restrict__ operands, uint32_t ntiles,
                                                               const uint32_t* __restrict__ key_starts, CellHead* __restrict__ heads,
                                                               uint32_t N, WsHeader* hdr, uint16_t* __restrict__ lists,
                                                               uint32_t* __restrict__ hist, uint32_t* __restrict__ queued_near)
 {
     using L = Lists<D>;
+    static_assert(WINDOWED == (D == 4), "d = 8: the whole codebook, by pairs of tiles");
     __shared__ uint32_t cnt1[32], cnt2[32], cell_ids[32], all_inner[32];
     __shared__ uint2 queues[kListWaves<D>][128];   // per wave: fewer than 64 entries left over + at most 64 of one tile
     for (uint32_t i = blockIdx.x * (64 * kListWaves<D>) + threadIdx.x; i < 65536; i += gridDim.x * (64 * kListWaves<D>)) {
@@ -458,75 +489,96 @@ __global__ __launch_bounds__(64 * kListWaves<D>, 4) void cell_lists_kernel(const
     uint2* queue = queues[wave];
     uint32_t queued = 0;   // wave-uniform
     auto work_off = [&](uint32_t count) {   // the first `count` <= 64 entries
-        if (uint32_t(lane) < count) {
-            const uint2 q = queue[lane];
-            const uint32_t cell = q.y & 31u, first_pos = (q.y >> 6) * 32 + (q.y & 32u ? 16u : 0u);
-            const uint32_t all = L::kCap2 > 0 ? q.x & 0xaaaaaaaau : q.x << 16;
-            const uint32_t inner = L::kCap2 > 0 ? all & ((q.x << 1) | all_inner[cell]) : all, outer = all ^ inner;
-            const uint32_t n1 = __popc(inner), n2 = __popc(outer);
-            const uint32_t at1 = n1 ? atomicAdd(&cnt1[cell], n1) : 0u, at2 = n2 ? atomicAdd(&cnt2[cell], n2) : 0u;
-            auto put = [&](uint32_t mask, uint32_t at, uint32_t end) {   // in entries of the whole table
+        if (uint32_t(lane) >= count) return;
+        const uint2 q = queue[lane];
+        const uint32_t cell = q.y & 31u, first_pos = (q.y >> 6) * 32 + (q.y & 32u ? 16u : 0u);
+        if constexpr (D == 4) {
+            uint32_t mask = q.x << 16, at = atomicAdd(&cnt1[cell], uint32_t(__popc(mask)));
+            const uint32_t list = cell_ids[cell] * L::kCap, end = list + L::kCap1;
+            at += list;
+            while (mask != 0) {
+                const uint32_t bit = uint32_t(__builtin_clz(mask));
+                mask ^= 0x80000000u >> bit;
+                if (at < end) lists[at] = uint16_t(first_pos + bit);
+                ++at;
+            }
+        } else {
+            const uint32_t all = q.x & 0xaaaaaaaau, inner = all & ((q.x << 1) | all_inner[cell]), outer = all ^ inner;
+            const uint32_t n1 = __popc(inner), n2 = __popc(outer), at = cell_ids[cell] * L::kCap;
+            const uint32_t at1 = at + (n1 ? atomicAdd(&cnt1[cell], n1) : 0u), at2 = at + L::kCap1 + (n2 ? atomicAdd(&cnt2[cell], n2) : 0u);
+            auto put = [&](uint32_t mask, uint32_t at, uint32_t end) {   // in bytes of the whole table, 512 MB at most
                 while (mask != 0) {
                     const uint32_t bit = uint32_t(__builtin_clz(mask));
                     mask ^= 0x80000000u >> bit;
-                    if (at < end) lists[at] = uint16_t(first_pos + bit / (L::kCap2 > 0 ? 2 : 1));
-                    ++at;
+                    if (at < end) *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(lists) + at) = uint16_t(((first_pos << 16) | (bit << 15)) >> 16);
+                    at += 2;
                 }
             };
-            const uint32_t list = cell_ids[cell] * L::kCap;
-            put(inner, list + at1, list + L::kCap1);
-            if constexpr (L::kCap2 > 0) put(outer, list + L::kCap1 + at2, list + L::kCap);
+            put(inner, 2 * at1, 2 * (at + L::kCap1));
+            put(outer, 2 * at2, 2 * (at + L::kCap));
         }
     };
-    constexpr int U = D == 4 ? 1 : 2;           // tiles a wave takes at a time: at d = 4 a run has a few
-    constexpr uint32_t kStep = U * kListWaves<D>;
-    uint32_t next = 0;
-    for (uint32_t r = 0; r < nruns; ++r) {
-        const uint32_t r0 = max(uint32_t(__builtin_amdgcn_readlane(int(run.x), int(r))), next);  // a tile on the border of
-        const uint32_t t1 = uint32_t(__builtin_amdgcn_readlane(int(run.y), int(r)));             // two shells is visited once
-        if (r0 >= t1) continue;
-        next = t1;
-        uint32_t t = r0 + wave * U;
-        f16x8 a[U];
+    auto push = [&](uint32_t bits, uint32_t mask, uint32_t which) {   // 32 * which: the first of the rows
+        const unsigned long long hits = __ballot(mask != 0);
+        if (mask != 0)
+            (queue + queued)[__builtin_amdgcn_mbcnt_hi(uint32_t(hits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(hits), 0u))] = make_uint2(bits, (which << 6) | uint32_t(lane));
+        queued += uint32_t(__popcll(hits));
+        if (queued >= 64) {
+            wave_order();
+            work_off(64);
+            queued -= 64;
+            const uint2 rest = queue[64 + lane];
+            wave_order();
+            if (uint32_t(lane) < queued) queue[lane] = rest;
+            wave_order();
+        }
+    };
+    auto operand = [&](uint32_t t, f16x8* a, auto tiles) {   // neighbouring tiles
+        typedef const __attribute__((address_space(1))) char* Global;
+        Global tile = reinterpret_cast<Global>(reinterpret_cast<uintptr_t>(operands + size_t(t) * 1024));
+        uint32_t lane_at = lane * 16;
+        asm volatile("" : "+s"(tile), "+v"(lane_at));   // a scalar and 32 bits: else a 64-bit addition per request
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + u, t1 - 1)) * 1024 + uint32_t(lane * 16));
-        for (; t < t1; t += kStep) {
-            f16x8 an[U];
+        for (int u = 0; u < decltype(tiles)::value; ++u) a[u] = *reinterpret_cast<const __attribute__((address_space(1))) f16x8*>(tile + lane_at + 1024 * u);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Pair = std::integral_constant<int, 2>;
+    if constexpr (D == 4) {
+        uint32_t next = 0;
+        for (uint32_t r = 0; r < nruns; ++r) {
+            const uint32_t r0 = max(uint32_t(__builtin_amdgcn_readlane(int(run.x), int(r))), next);  // a tile on the border of
+            const uint32_t t1 = uint32_t(__builtin_amdgcn_readlane(int(run.y), int(r)));             // two shells is visited once
+            if (r0 >= t1) continue;
+            next = t1;
+            f16x8 a, an;
+            operand(min(r0 + wave, t1 - 1), &a, One{});
+            for (uint32_t t = r0 + wave; t < t1; t += kListWaves<D>) {   // one at a time: a run has a few
+                operand(min(t + kListWaves<D>, t1 - 1), &an, One{});
+                const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, zero, 0, 0, 0);
+                float m = INFINITY;
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                an[u] = *reinterpret_cast<const f16x8*>(operands + size_t(min(t + kStep + u, t1 - 1)) * 1024 + uint32_t(lane * 16));
+                for (int q = 0; q < 8; ++q) m = __builtin_fminf(__builtin_fminf(m, acc[2 * q]), acc[2 * q + 1]);
+                if (__any(m < 0.0f)) {
+                    uint32_t bits = 0;   // row 0 uppermost
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (t + u >= t1) break;
-                const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b, zero, 0, 0, 0);
-                if constexpr (WINDOWED) {
-                    float m = INFINITY;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) m = __builtin_fminf(__builtin_fminf(m, acc[2 * q]), acc[2 * q + 1]);
-                    if (!__any(m < 0.0f)) continue;
+                    for (int q = 0; q < 16; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(acc[q]), 31);
+                    push(bits, bits, t);
                 }
-                constexpr int kBits = L::kCap2 > 0 ? 2 : 1;   // of a row: within the (outer) radius, within r1
-                uint32_t bits = 0;   // row 0 uppermost
-#pragma unroll
-                for (int q = 0; q < 16; ++q) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(acc[q]), 32 - kBits);
-                const uint32_t mask = kBits == 2 ? bits & 0xaaaaaaaau : bits;
-                const unsigned long long hits = __ballot(mask != 0);
-                if (mask != 0)
-                    queue[__builtin_amdgcn_mbcnt_hi(uint32_t(hits >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(hits), queued))] =
-                        make_uint2(bits, ((t + u) << 6) | uint32_t(lane));
-                queued += uint32_t(__popcll(hits));
-                if (queued >= 64) {
-                    wave_order();
-                    work_off(64);
-                    queued -= 64;
-                    const uint2 rest = queue[64 + lane];
-                    wave_order();
-                    if (uint32_t(lane) < queued) queue[lane] = rest;
-                    wave_order();
-                }
+                a = an;
             }
+        }
+    } else {
+        const uint32_t pairs = ntiles / 2;
+        f16x8 a[2];
+        operand(2 * min(uint32_t(wave), pairs - 1), a, Pair{});
+        for (uint32_t t = wave; t < pairs; t += kListWaves<D>) {
+            f32x16 acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b, zero, 0, 0, 0), acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b, zero, 0, 0, 0);
+            asm volatile("" : "+v"(acc0), "+v"(acc1));   // requested before the products, the next operands would need registers of their own
+            operand(2 * min(t + kListWaves<D>, pairs - 1), a, Pair{});
+            uint32_t word[2];
+            score_bits(acc0, acc1, word);
 #pragma unroll
-            for (int u = 0; u < U; ++u) a[u] = an[u];
+            for (uint32_t u = 0; u < 2; ++u) push(word[u], word[u] & 0xaaaaaaaau, 2 * t + u);
         }
     }
     wave_order();
@@ -1448,7 +1500,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
     if (hipError_t e = launch_key_starts(w.cell_hist, w.key_starts, w.cell_cursor, K, s); e != hipSuccess) return e;
     hipLaunchKernelGGL(cell_place_kernel<D>, dim3((padded + kThreads - 1) / kThreads), dim3(kThreads), 0, s, C, K, padded, w.ckeys,
                        w.cell_cursor, w.cperm, w.cinv, w.csorted, reinterpret_cast<char*>(w.packed), w.cell_operands, D == 8 ? w.cell_flat : nullptr, w.hdr);
-    hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(64 * kListWaves<D>), 0, s, w.csorted, w.cperm, K, w.cell_operands, tiles,
+    hipLaunchKernelGGL((cell_lists_kernel<D, D == 4>), dim3(tiles), dim3(64 * kListWaves<D>), 0, s, w.csorted, w.cperm, K, w.cell_operands, list_tiles(D, K),
                        w.key_starts, w.cell_heads, N, w.hdr, w.cell_lists, w.cell_hist, w.cell_cursor);
     if (moves != nullptr) {
         const uint32_t lds = (K + 7) / 8 * 16;

@@ -15,6 +15,8 @@ size_t sort_hist_bytes(uint64_t n);
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K);
 // E-step by cells (cells.hip): room for the entries of a cell's list
 uint32_t cell_list_cap(uint32_t d);
+// Operands of 32 centroids for the lists; d = 8: whole pairs of them
+__host__ __device__ constexpr uint32_t list_tiles(uint32_t d, uint32_t K) { return d == 4 ? (K + 31) / 32 : (K + 63) / 64 * 2; }
 constexpr uint32_t kCellItem = 192;       // vectors of one wave (d = 4)
 struct CellHead {
     uint32_t start, members;   // the cell's vectors
@@ -240,7 +242,7 @@ inline Workspace carve(void* base, uint64_t N, uint32_t d_caller, uint32_t K, si
         w.cell_heads = reinterpret_cast<CellHead*>(take(size_t(K) * sizeof(CellHead)));
         w.cell_hist = reinterpret_cast<uint32_t*>(take(65536 * 4));
         w.cell_cursor = reinterpret_cast<uint32_t*>(take(65536 * 4));
-        w.cell_operands = take((size_t(K) + 31) / 32 * 1024);
+        w.cell_operands = take(size_t(list_tiles(d, K)) * 1024);
         w.cell_flat = take((size_t(K) + 1) * 64);
         w.cell_lists = have >= off && p ? reinterpret_cast<uint16_t*>(p + lists_at) : nullptr;
         w.bytes = off;

@@ -7,6 +7,7 @@ namespace cc {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
 
 constexpr float kUnit = 5.9604644775390625e-08f;  // 2^-24
 constexpr float kGuardSafety = 1.5f;
