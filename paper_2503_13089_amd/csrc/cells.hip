@@ -1135,35 +1135,42 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         // accesses a load, one each clock of the kernel. 29 M vectors, K = 65536: 1.40 and 1.43 ms (near and between r1 and r2) -> 1.27 and
         // 1.27, 2.8 M 0.221 and 0.131 -> 0.204 and 0.112; of that, a half for one load of list entries per group in place of four.
         const uint32_t row = lane >> 2, from = (lane ^ (row + (row >> 2))) & 3u, to_row = 4 * n16 + ((g ^ (n16 + (n16 >> 2))) & 3);
-        uint32_t id = 0;   // of entry `lane` of a group
+        uint32_t begins = 0;   // where the operand of entry `lane` of a group does: a scalar and 32 bits of address per request, 64-bit additions otherwise
         f16x8 av[4];
         auto entries = [&](uint32_t gr) {
             const uint32_t e = gr * kGroup + lane, at = entry(min(e, max(len, 1u) - 1u));
-            id = e < len ? at : a.K;
+            begins = (e < len ? at : a.K) * 64;
         };
         auto gather = [&]() {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const char* operand = a.flat + size_t(uint32_t(__shfl(int(id), 16 * t + int(row), 64))) * 64 + from * 16;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)operand, (__attribute__((address_space(3))) void*)(turn + t * 64), 16, 0,
-                                                 0);
+                uint32_t at = uint32_t(__shfl(int(begins), 16 * t + int(row), 64)) | from * 16;
+                asm volatile("" : "+v"(at));
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a.flat + at), (__attribute__((address_space(3))) void*)(turn + t * 64), 16, 0, 0);
             }
         };
-        entries(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows have been read
-        gather();
-        entries(1);
-        for (uint32_t gr = 0; gr < groups; ++gr) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the operands have landed
-#pragma unroll
-            for (int t = 0; t < 4; ++t) av[t] = turn[t * 64 + to_row];
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and are read before the next ones land there
+        // A loop for each number of tiles: one that chose in every group kept scores in other registers for each choice, 25 copies beside 80 instructions.
+        // Lists of 2.8 M vectors 188 / 179 us (three tiles of four where cells hold 43 vectors), bf16 layer of 4096^2 at g = 6 16.48 / 16.30 ms, 8192 x 28672 77.7 / 77.0.
+        auto score = [&](auto tiles, auto low_too) {
+            entries(0);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows have been read
             gather();
-            entries(gr + 2);
-            if (!f16) score_group<4, true>(av, b, low + lane, row0, gr, minus_inf, s);
-            else if (tiles <= 2) score_group<2, false>(av, b, low, row0, gr, minus_inf, s);
-            else score_group<4, false>(av, b, low, row0, gr, minus_inf, s);
-        }
+            entries(1);
+            for (uint32_t gr = 0; gr < groups; ++gr) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the operands have landed
+#pragma unroll
+                for (int t = 0; t < 4; ++t) av[t] = turn[t * 64 + to_row];
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // ... and are read before the next ones land there
+                gather();
+                entries(gr + 2);
+                score_group<decltype(tiles)::value, decltype(low_too)::value>(av, b, low + lane, row0, gr, minus_inf, s);
+            }
+        };
+        if (!f16) score(std::integral_constant<int, 4>{}, std::true_type{});
+        else if (tiles == 1) score(std::integral_constant<int, 1>{}, std::false_type{});
+        else if (tiles == 2) score(std::integral_constant<int, 2>{}, std::false_type{});
+        else if (tiles == 3) score(std::integral_constant<int, 3>{}, std::false_type{});
+        else score(std::integral_constant<int, 4>{}, std::false_type{});
     }
     // ---- best, second best and group over the four lanes that share a vector; lane (n16, g) takes vector n16 of tile g
     float best = 0.0f, second = 0.0f;
