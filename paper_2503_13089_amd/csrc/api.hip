@@ -309,11 +309,18 @@ bool cells_from_first(uint64_t N, uint32_t d, uint32_t d_caller, uint32_t K)
 // the benchmark's fit and the padded lengths; the three between would be 1 to 5 % faster with 1 alone.
 bool regroup_at(int32_t t, bool from_first) { return from_first ? t == 2 || t == 5 : t == 1 || t == 5; }
 
+bool last_grouping(int32_t t, int32_t iters, bool from_first)
+{
+    for (int32_t later = t + 1; later < iters && later <= 5; ++later)
+        if (regroup_at(later, from_first)) return false;
+    return true;
+}
+
 // First iteration of a fit by cells (d = 8). The bootstrap's codes are among the nearest few hundred of their vector's cell rather than
 // the nearest: one look at the cell's list makes most of them so, the vectors are grouped again, and the lengths of the lists
 // say what radii the exact ones take.
 int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32_t d_caller, float* C, uint32_t K, cc::Workspace& w,
-                         hipStream_t s)
+                         int32_t iters, hipStream_t s)
 {
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
@@ -325,7 +332,7 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
     if (int rc = run_bootstrap(cx, e, N, d, C, K, w, s)) return rc;
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, true, s), "assign (grouping by code)");
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, true, false, s), "assign (grouping by code)");
         CC_TRY_HIP(cc::launch_cells_centroids(C, N, d, K, w, cc::kRadiiStay, false, s), "assign (centroids and lists of the cells)");
     }
     {
@@ -334,7 +341,7 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
     }
     {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, false, s), "assign (grouping by code)");
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, false, last_grouping(0, iters, true), s), "assign (grouping by code)");
     }
     if (int rc = run_assign_cells(cx, N, d, C, K, w, cc::kRadiiJump, false, false, s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
@@ -347,11 +354,11 @@ int run_cells_first_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, 
 
 // Iteration t >= 1 of a fit by cells; the workspace holds the codes, sums and counts of the iteration before.
 int run_cells_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, uint32_t d_caller, float* C, uint32_t K, cc::Workspace& w,
-                   int32_t t, bool from_first, hipStream_t s)
+                   int32_t t, int32_t iters, bool from_first, hipStream_t s)
 {
     if (regroup_at(t, from_first)) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
-        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, t == 1, s), "assign (grouping by code)");
+        CC_TRY_HIP(cc::launch_cells_order(X, C, N, d, d_caller, K, w, t == 1, last_grouping(t, iters, from_first), s), "assign (grouping by code)");
     }
     if (int rc = run_assign_cells(cx, N, d, C, K, w, t == 1 && !from_first ? cc::kRadiiStay : cc::kRadiiFollow, true, !regroup_at(t, from_first), s)) return rc;
     cc::ProfileScope mstep_scope(cx.prof, cc::kProfMstep, s);
@@ -549,8 +556,8 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     const bool cells = pruned && iters >= 3 && w.cell_lists != nullptr, from_first = cells && cells_from_first(N, D, d, K);
     for (int32_t t = 0; t < iters; ++t) {
         if (cells && (t > 0 || from_first)) {
-            if (int rc = t == 0 ? run_cells_first_iter(cx, o.X, n, D, d, o.C_work, K, w, s)
-                                : run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, from_first, s))
+            if (int rc = t == 0 ? run_cells_first_iter(cx, o.X, n, D, d, o.C_work, K, w, iters, s)
+                                : run_cells_iter(cx, o.X, n, D, d, o.C_work, K, w, t, iters, from_first, s))
                 return rc;
             continue;
         }

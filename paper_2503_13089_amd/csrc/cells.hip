@@ -76,7 +76,9 @@ __global__ __launch_bounds__(kThreads) void cell_keys_kernel(const uint32_t* __r
 }
 
 // New position p holds what stood at order[p]. order is turned into the norm rank of every position (the position in
-// the norm order the fit began with: rank_old == NULL means that the old order is that one).
+// the norm order the fit began with: rank_old == NULL means that the old order is that one). position, the inverse, may be NULL: where the far vectors stand the near
+// kernels write in every E-step, and all of it only a later call asks for. 4-byte writes in random order were half of this kernel's time:
+// 29 M vectors 1070, 850 and 720 us / 560, 480 and 275 without, 11 M 355 / 200.
 __global__ __launch_bounds__(kThreads) void cell_apply_kernel(const uint16_t* __restrict__ sorted_keys, uint32_t N, uint32_t* order,
                                                               const uint32_t* __restrict__ rank_old,
                                                               const uint32_t* __restrict__ perm_old, uint32_t* __restrict__ perm_new,
@@ -87,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void cell_apply_kernel(const uint16_t* __
     const uint32_t q = order[p];
     const uint32_t r = rank_old != nullptr ? rank_old[q] : q;
     order[p] = r;
-    position[r] = p;
+    if (position != nullptr) position[r] = p;
     perm_new[p] = perm_old[q];
     idx[p] = sorted_keys[p];
 }
@@ -617,7 +619,8 @@ struct NearArgs {
     uint32_t slots;
     const uint16_t* lists;
     const uint32_t* rank;
-    uint32_t* far_bits;
+    uint32_t* far_bits;         // by norm rank
+    uint32_t* position;         // by norm rank: that of the far vectors
     uint32_t* queues;           // d = 8: positions of vectors to be scored, in their cell's places: those within r1 from its first on,
                                 // those between r1 and r2 from its last backwards
     uint32_t* queued_near;      // [K] how many of the former (the latter: CellHead::mids)
@@ -641,6 +644,13 @@ __device__ __forceinline__ void or_bits(uint32_t* bits, uint32_t p0, unsigned lo
 }
 
 __device__ __forceinline__ void or_bit(uint32_t* bits, uint32_t p) { atomicOr(bits + (p >> 5), 1u << (p & 31u)); }
+
+__device__ __forceinline__ void mark_far(const NearArgs& a, uint32_t p)
+{
+    const uint32_t r = a.rank[p];
+    or_bit(a.far_bits, r);
+    a.position[r] = p;
+}
 
 // A work item: `at`, the first of its vectors or of its places in a queue among those of cell c, which has `members` vectors from `start` on. One load says so, so that
 // all that follows from it, the cell's head among it, is requested at once: a wave waits for memory twice before it scores, not four times.
@@ -834,7 +844,7 @@ __global__ __launch_bounds__(64) void near_direct_kernel(NearArgs a)
                 idx[o] = k;
                 if (dmin != nullptr) dmin[o] = bd;
             }
-            if (live && !near[v]) or_bit(a.far_bits, a.rank[p]);
+            if (live && !near[v]) mark_far(a, p);
             if (a.changed != nullptr) {
                 const bool moved = live && (!near[v] || k != hint[v]);
                 if (moved) a.prev_out[p] = hint[v];
@@ -1025,7 +1035,7 @@ __device__ __forceinline__ bool sort_out(const NearArgs& a, uint32_t c, const Ce
         if (mid) a.queues[head.start + head.members - 1 - __builtin_amdgcn_mbcnt_hi(uint32_t(mids >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mids), at))] = p;
     }
     if (far) {
-        or_bit(a.far_bits, a.rank[p]);
+        mark_far(a, p);
         if (a.bound != nullptr) a.bound[p] = 0;
     }
     if (a.changed != nullptr) {
@@ -1472,14 +1482,14 @@ bool cells_bounded(uint64_t N, uint32_t d, uint32_t K) { return d == 8 && N >= 1
 uint32_t item_of(uint32_t d) { return d == 4 ? kCellItem : kSetVectors; }
 
 template <int D>
-hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K, Workspace& w, bool first, float factor, hipStream_t s)
+hipError_t cells_order_t(const float* X, const float* C, uint32_t N, uint32_t K, Workspace& w, bool first, bool last, float factor, hipStream_t s)
 {
     const dim3 per_vector((N + kThreads - 1) / kThreads);
     hipLaunchKernelGGL(cell_keys_kernel, per_vector, dim3(kThreads), 0, s, w.idx_sorted, N, w.vkeys, w.cell_order);
     if (hipError_t e = launch_sort_u16(w.vkeys, w.cell_order, w.vkeys_tmp, w.vperm_tmp, N, w.sort_hist, s); e != hipSuccess) return e;
     if (first) std::swap(w.idx_sorted, w.idx_prev);
     hipLaunchKernelGGL(cell_apply_kernel, per_vector, dim3(kThreads), 0, s, w.vkeys, N, w.cell_order, first ? nullptr : w.cell_rank,
-                       w.vperm, w.vperm_tmp, w.cell_position, w.idx_sorted);
+                       w.vperm, w.vperm_tmp, last ? w.cell_position : nullptr, w.idx_sorted);
     std::swap(w.vperm, w.vperm_tmp);
     std::swap(w.cell_rank, w.cell_order);
     if (hipError_t e = launch_gather_rows(X, w.vperm, N, D, w.xsorted, s); e != hipSuccess) return e;
@@ -1522,7 +1532,7 @@ hipError_t cells_centroids_t(const float* C, uint32_t N, uint32_t K, const Works
 NearArgs near_args(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded)
 {
     return NearArgs{w.xsorted, C, w.csorted, w.cperm, w.cell_flat, K, w.cell_heads, cell_items(w), N / item_of(d) + K,
-                    w.cell_lists, w.cell_rank, w.far_bits, far_view(w, N, d).pos,
+                    w.cell_lists, w.cell_rank, w.far_bits, w.cell_position, far_view(w, N, d).pos,
                     w.cell_cursor, w.cperm_tmp, cells_bounded(N, d, K) ? reinterpret_cast<uint16_t*>(w.cell_order) /* idle between groupings */ : nullptr,
                     cells_bounded(N, d, K) && bounded, w.idx_sorted, track ? nullptr : w.dmin /* track: an iteration's */,
                     track ? w.idx_prev : nullptr, track ? w.changed : nullptr, w.hdr};
@@ -1571,13 +1581,13 @@ void cells_far_t(uint32_t N, uint32_t K, const Workspace& w, hipStream_t s)
 }  // namespace
 
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
-                              bool first, hipStream_t s)
+                              bool first, bool last, hipStream_t s)
 {
     // first radius over mean t: n(R) grows like R^d from about 10 (d = 4) or 150 (d = 8) centroids at the mean
     const float factor = d_caller <= 4 ? 1.45f : (d_caller <= 6 ? 1.25f : 1.13f);
     switch (d) {
-        case 4: return cells_order_t<4>(X, C, N, K, w, first, factor, s);
-        case 8: return cells_order_t<8>(X, C, N, K, w, first, factor, s);
+        case 4: return cells_order_t<4>(X, C, N, K, w, first, last, factor, s);
+        case 8: return cells_order_t<8>(X, C, N, K, w, first, last, factor, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -128,7 +128,7 @@ struct Workspace {
     // E-step by cells
     uint32_t* cell_order;      // [N]    scratch of the grouping
     uint32_t* cell_rank;       // [N]    norm rank of the vector at each position
-    uint32_t* cell_position;   // [N]    inverse of cell_rank
+    uint32_t* cell_position;   // [N]    inverse of cell_rank: where the vector is far, and after the last grouping
     uint32_t* far_bits;        // [ceil(N/32)] by norm rank
     CellHead* cell_heads;      // [K]
     uint32_t* cell_hist;       // [65536] centroids per ordering key; zero between E-steps
@@ -353,12 +353,12 @@ hipError_t launch_unpermute(uint32_t N, uint32_t* idx, const Workspace& w, bool 
 
 // E-step by cells inside a fit (cells.hip), after a first E-step in the norm order. launch_cells_order groups the
 // vectors by their codes (w.idx_sorted; swaps buffers of w; `first`: they lie in the norm order, and the codes change
-// places with w.idx_prev: at the end a next call can put them into the norm order, kHintByCells); launch_cells_centroids
+// places with w.idx_prev: at the end a next call can put them into the norm order, kHintByCells; `last`: no grouping follows); launch_cells_centroids
 // orders the current centroids and makes their operands and the lists of the cells; launch_cells_near decides the near
 // vectors; launch_cells_compact leaves the far ones as a list of hdr->far_count entries in the arrays of far_view, with their windows
 // (far_windows); launch_cells_far decides those (fp16 inputs) within their windows, up to the entries it leaves on the refine list.
 hipError_t launch_cells_order(const float* X, const float* C, uint32_t N, uint32_t d, uint32_t d_caller, uint32_t K, Workspace& w,
-                              bool first, hipStream_t s);
+                              bool first, bool last, hipStream_t s);
 enum Radii : int { kRadiiStay, kRadiiFollow, kRadiiJump };   // towards the lists' target lengths: not, a step, all the way (same centroids)
 hipError_t launch_cells_centroids(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, Radii radii, bool bounded, hipStream_t s);
 hipError_t launch_cells_near(const float* C, uint32_t N, uint32_t d, uint32_t K, const Workspace& w, bool track, bool bounded, hipStream_t s);
