@@ -5,7 +5,8 @@
 // of the index recovery, and an iteration with it is eleven launches of 2 us each, most of them gated off.
 //
 // A workgroup of 8 waves holds the codebook (K rows and their norms, fp32) and the accumulators (64-bit fixed-point sums and counts) in
-// LDS. A lane scores V vectors, ||c||^2 - 2 x.c, four centroids at a time: d multiply-adds a pair, two minima, a compare, a select and best and second
+// LDS. A lane scores V vectors, ||c||^2 / 2 - x.c (the rows are staged as -c: a vector of which
+// twice is no finite number is scored, and added, as it is), four centroids at a time: d multiply-adds a pair, two minima, a compare, a select and best and second
 // best for four of them. The best four are then compared in direct form; a vector whose second best comes within the guard band of the
 // fp32 matrix cores, which do the same chain of multiply-adds (assign_mfma.hip), is decided in direct form over the codebook. Bound: multiply-adds issue in 2 clocks and
 // the rest in 4, so a pair takes 2 d + 6 clocks, and LDS takes 8 to give all lanes 16 bytes: 2 d + 2 a centroid and wave, which four vectors per lane share. Direct form
@@ -42,7 +43,17 @@ size_t lds_bytes(uint32_t d, uint32_t K, int V, int S, bool sums)
 // bytes of one workgroup's partial sums: [D][K] int64, then [K] counts, rounded to whole 64-bit words
 size_t partial_bytes(uint32_t d, uint32_t K) { return (size_t(K) * (d * 8 + 4) + 7) & ~size_t(7); }
 
-// The decision for a lane's vector x from the best four of its scores (`four`: the first of them), by whole waves; `on`: there is a vector.
+template <int D>
+__device__ __forceinline__ void load_opposite(const float* row, float (&c)[D])
+{
+    load_row<D>(row, c);
+#pragma unroll
+    for (int j = 0; j < D; ++j) c[j] = -c[j];
+}
+
+// The decision for a lane's vector x from the best four of its scores (`four`: the first of them), by whole waves; `on`: there is a vector. rows: the centroids' opposites.
+// Where a score that matters could have overflowed, or missed the start value, the band has: a centroid no farther than bd has partial sums of at most
+// 3 (||x||^2 + bd), and the sum that the band is made of is 18 times that bracket or more.
 template <int D>
 __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float best, float second, uint32_t four, const float* rows, uint32_t K,
                                              float& bd, uint32_t& bk)
@@ -51,7 +62,7 @@ __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float
 #pragma unroll
     for (uint32_t u = 0; u < kFour; ++u) {
         float c[D];
-        load_row<D>(rows + size_t(four + u) * D, c);
+        load_opposite<D>(rows + size_t(four + u) * D, c);
         d[u] = direct_sqdist<D>(x, c);   // NaN past K
     }
     bd = __builtin_fminf(__builtin_fminf(__builtin_fminf(d[0], d[1]), d[2]), d[3]);
@@ -61,7 +72,7 @@ __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float
     float xn = 0.0f;
 #pragma unroll
     for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
-    const float band = 1.5f * 2.0f * 5.9604644775390625e-08f * (float(5 * D + 2) * xn + float(4 * D + 2) * bd) + 1e-36f;
+    const float band = 1.5f * 5.9604644775390625e-08f * (float(5 * D + 2) * xn + float(4 * D + 2) * bd) + 1e-36f;
     unsigned long long todo = __ballot(on && !(second - best > band));   // NaN too
     const uint32_t lane = threadIdx.x & 63;
     while (todo != 0) {
@@ -73,7 +84,7 @@ __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float
         unsigned long long key = (0x7f800000ull << 32) | 0u;   // no distance is less than infinity: the first centroid
         for (uint32_t k = lane; k < K; k += 64) {
             float c[D];
-            load_row<D>(rows + size_t(k) * D, c);
+            load_opposite<D>(rows + size_t(k) * D, c);
             const float dist = direct_sqdist<D>(y, c);
             const unsigned long long v = (static_cast<unsigned long long>(__float_as_uint(dist)) << 32) | k;
             key = dist < INFINITY && v < key ? v : key;
@@ -97,8 +108,8 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const uint32_t padded = (K + kFour - 1) / kFour * kFour;
-    float* rows = reinterpret_cast<float*>(smem);                                                    // [padded][D], NaN past K
-    float* norms = rows + size_t(padded) * D;                                                        // [padded]
+    float* rows = reinterpret_cast<float*>(smem);                                                    // [padded][D], opposites unless DIRECT, NaN past K
+    float* norms = rows + size_t(padded) * D;                                                        // [padded], halves
     unsigned long long* sums = reinterpret_cast<unsigned long long*>(norms + padded);                // [D][K]
     uint32_t* counts = reinterpret_cast<uint32_t*>(sums + (SUMS ? size_t(K) * D : 0));               // [K]
     float2* met = reinterpret_cast<float2*>((reinterpret_cast<uintptr_t>(counts + (SUMS ? K : 0)) + 15) & ~uintptr_t(15));   // [kThreads V]
@@ -136,8 +147,11 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
         if constexpr (!DIRECT) {
             double norm = 0.0;
 #pragma unroll
-            for (int j = 0; j < D; ++j) norm += double(c[j]) * double(c[j]);
-            norms[k] = float(norm);
+            for (int j = 0; j < D; ++j) {
+                norm += double(c[j]) * double(c[j]);
+                c[j] = -c[j];
+            }
+            norms[k] = float(0.5 * norm);
         }
 #pragma unroll
         for (int q = 0; q < D / 4; ++q)
@@ -203,11 +217,10 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
         uint32_t four[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-#pragma unroll
-            for (int j = 0; j < D; ++j) x[v][j] *= -2.0f;
             best[v] = second[v] = 3e38f;
             four[v] = min(k_lo, padded - kFour);
         }
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): else the loop has a wait for each vector
         for (uint32_t k = k_lo; k < k_hi; k += kFour) {
             const float4 n4 = *reinterpret_cast<const float4*>(norms + k);
             const float n[kFour] = {n4.x, n4.y, n4.z, n4.w};
@@ -231,11 +244,7 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
         }
         if constexpr (S == 1) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) x[v][j] *= -0.5f;
-                finish(x[v], v0 + part * VW + v * 64 + lane, best[v], second[v], four[v]);
-            }
+            for (int v = 0; v < V; ++v) finish(x[v], v0 + part * VW + v * 64 + lane, best[v], second[v], four[v]);
         } else {
         __syncthreads();   // the exchange buffers of the step before have been read
 #pragma unroll
