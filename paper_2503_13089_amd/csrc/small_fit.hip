@@ -54,7 +54,7 @@ __device__ __forceinline__ void load_opposite(const float* row, float (&c)[D])
 // The decision for a lane's vector x from the best four of its scores (`four`: the first of them), by whole waves; `on`: there is a vector. rows: the centroids' opposites.
 // Where a score that matters could have overflowed, or missed the start value, the band has: a centroid no farther than bd has partial sums of at most
 // 3 (||x||^2 + bd), and the sum that the band is made of is 18 times that bracket or more.
-template <int D>
+template <int D, bool SPLIT>
 __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float best, float second, uint32_t four, const float* rows, uint32_t K,
                                              float& bd, uint32_t& bk)
 {
@@ -74,6 +74,25 @@ __device__ __forceinline__ void decide_small(const float (&x)[D], bool on, float
     for (int j = 0; j < D; ++j) xn = __builtin_fmaf(x[j], x[j], xn);
     const float band = 1.5f * 5.9604644775390625e-08f * (float(5 * D + 2) * xn + float(4 * D + 2) * bd) + 1e-36f;
     unsigned long long todo = __ballot(on && !(second - best > band));   // NaN too
+    // One by one, or the whole wave at once where that takes less: among vectors of few different values, whose centroids have doubles or lie equally near, scores decide
+    // little. Fits of 10 iterations of numbers of 2 bits, us, direct form for every pair / scores, one by one / now: (65536, 4, 256) 141 / 554 / 212, (4.2 M, 4, 140)
+    // 1822 / 8272 / 3008, (4 M, 8, 390) 7105 / 7590 / 7288, (1 M, 16, 250) 2217 / 1772 / 1654. (Scores left out where most vectors of the iteration before were undecided:
+    // 192, 2216, 7364, 2361, but 0.3 to 3 % more for everybody else.)
+    // On its own a vector takes as much as so many centroids of a whole wave; more where few of the waves decide, and hide less of each other's waits.
+    const uint32_t alone = SPLIT ? 16 + K / 24 : 8 + K / 48;
+    if (__builtin_expect(uint32_t(__popcll(todo)) * alone > K, 0)) {
+        todo = 0;
+        bd = INFINITY;
+        bk = 0;
+#pragma unroll 32 / D
+        for (uint32_t k = 0; k < K; ++k) {
+            float c[D];
+            load_opposite<D>(rows + size_t(k) * D, c);
+            const float dist = direct_sqdist<D>(x, c);
+            bk = dist < bd ? k : bk;
+            bd = dist < bd ? dist : bd;
+        }
+    }
     const uint32_t lane = threadIdx.x & 63;
     while (todo != 0) {
         const int src = __ffsll(static_cast<long long>(todo)) - 1;
@@ -160,7 +179,7 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
     auto finish = [&](const float (&x)[D], uint32_t i, float best, float second, uint32_t at) {
         float bd = best;
         uint32_t bk = at;
-        if constexpr (!DIRECT) decide_small<D>(x, i < hi, best, second, at, rows, K, bd, bk);
+        if constexpr (!DIRECT) decide_small<D, (S > 1)>(x, i < hi, best, second, at, rows, K, bd, bk);
         if (i >= hi) return;
         if constexpr (SUMS) {
 #pragma unroll

@@ -41,3 +41,15 @@ def test_numbers_that_doubled_would_overflow(N, d, K):
     assert (want[0].view(torch.float32).abs() > 2.0 ** 126).any()   # a mean holds it
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,d,K", SHAPES)
+@pytest.mark.parametrize("levels", [2, 4, 8, 16])
+def test_vectors_of_few_values(N, d, K, levels):
+    """Numbers of 1 to 4 bits: centroids have doubles or lie equally near, and scores leave all vectors of a wave undecided, some or few."""
+    gen = torch.Generator(device="cuda").manual_seed(N + d + K + levels)
+    x = torch.randn(N, d, device="cuda", generator=gen).mul_(levels / 8).round_().clamp_(-levels // 2, levels // 2 - 1).mul_(0.125)
+    c0 = x[torch.randperm(N, device="cuda", generator=gen)[:K]].contiguous()
+    print(f"few values N={N} d={d} K={K} {levels}", flush=True)
+    for a, b in zip(results(x, c0, 0), results(x, c0, 1)):
+        assert torch.equal(a, b)
