@@ -602,7 +602,7 @@ int cc_assign_ex(const float* vectors, uint64_t N, uint32_t d, const float* cent
     Operands o;
     if (int rc = enter(vectors, centroids, nullptr, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
-    const bool small = use_small(cx, N, K, 1, w) && cc::small_assign_pays(N, w.d, K);
+    const bool small = use_small(cx, N, K, 1, w);
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, w.d, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
