@@ -246,12 +246,12 @@ int run_assign(const Ctx& cx, const float* X, uint32_t N, uint32_t d, const floa
 // idx == NULL (only inside the fit loop, pruned path) skips the copy of the codes to input order.
 int run_lloyd_iter(const Ctx& cx, const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx,
                    double* inertia, uint32_t* counts, const cc::Workspace& w, bool pruned, bool have_hint, hipStream_t s,
-                   bool small, bool sums_follow = false)
+                   const cc::SmallCut* small, bool sums_follow = false)
 {
-    if (small) {
+    if (small != nullptr) {
         // codes and distances leave the kernel only where somebody reads them
         cc::ProfileScope scope(cx.prof, cc::kProfEstepDirect, s);
-        CC_TRY_HIP(cc::launch_small_iter(X, N, d, C, K, idx, inertia ? w.dmin : nullptr, counts, w, s), "iteration (small problem)");
+        CC_TRY_HIP(cc::launch_small_iter(X, N, d, C, K, *small, idx, inertia ? w.dmin : nullptr, counts, w, s), "iteration (small problem)");
     } else if (use_matrix_cores(cx, K)) {
         // sums_follow (inside a fit, pruned path, after an M-step by buckets of the same fit): the workspace holds the
         // integer sums and counts of the codes in w.idx_sorted. The E-step kernel then flags the vectors that leave
@@ -548,6 +548,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
     if (o.C_work != o.C_in)
         CC_TRY_HIP(cc::launch_copy_f32(o.C_in, o.C_work, size_t(K) * D, s), "centroid copy");
     const bool small = use_small(cx, N, K, iters, w);
+    const cc::SmallCut cut = small ? cc::small_cut(n, D, K, true) : cc::SmallCut{};
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, D, K, iters);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
@@ -566,7 +567,7 @@ int cc_kmeans_fit_ex(const float* vectors, uint64_t N, uint32_t d, uint32_t K, i
         // From the third iteration on the M-step only moves the vectors whose code changed (the first iterations move
         // too many for that to pay off). Where one pass by one slice will do, finding those takes as long as that pass.
         const bool sums_follow = pruned && w.bucket_ok && t >= 2 && !(cc::update_one_slice(D, K) && cc::update_sliced_applies(n, D, K, w));
-        if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, small, sums_follow))
+        if (int rc = run_lloyd_iter(cx, o.X, n, D, o.C_work, K, step_idx, nullptr, nullptr, w, pruned, t > 0, s, small ? &cut : nullptr, sums_follow))
             return rc;
     }
     if (cells) {
@@ -636,12 +637,13 @@ int cc_lloyd_iter_ex(const float* vectors, uint64_t N, uint32_t d, float* centro
     if (int rc = enter(vectors, centroids, centroids, uint32_t(N), d, K, w, s, o)) return rc;
     CC_TRY_HIP(cc::launch_scan_inputs(o.X, N * w.d, w.hdr, s), "input scan");
     const bool small = use_small(cx, N, K, 1, w);
+    const cc::SmallCut cut = small ? cc::small_cut(uint32_t(N), w.d, K, true) : cc::SmallCut{};
     const bool pruned = !small && use_matrix_cores(cx, K) && use_pruning(cx, N, w.d, K, 1);
     if (pruned) {
         cc::ProfileScope order_scope(cx.prof, cc::kProfOrder, s);
         CC_TRY_HIP(cc::launch_sort_vectors(o.X, uint32_t(N), w.d, K, w, false, s), "norm ordering");
     }
-    if (int rc = run_lloyd_iter(cx, o.X, uint32_t(N), w.d, o.C_work, K, idx, inertia, counts, w, pruned, false, s, small)) return rc;
+    if (int rc = run_lloyd_iter(cx, o.X, uint32_t(N), w.d, o.C_work, K, idx, inertia, counts, w, pruned, false, s, small ? &cut : nullptr)) return rc;
     return leave(centroids, d, K, w, s);
 }
 

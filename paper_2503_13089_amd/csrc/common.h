@@ -330,7 +330,13 @@ hipError_t launch_assign_mfma_f16(const EStep& e, uint32_t d, const Workspace& w
 // Small problems (small_fit.hip): E-step in direct form with the codebook and the cluster sums in LDS. One Lloyd
 // iteration (C updated in place; idx, dmin and counts may be NULL), and the E-step alone.
 bool small_problem(uint64_t N, uint32_t d, uint32_t K);
-hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx, float* dmin,
+struct SmallCut {           // how the vectors of an iteration are dealt out
+    uint32_t blocks, per_block;
+    int32_t slices, lane;   // ways to split the codebook; vectors of a lane
+    int32_t direct;         // every distance in direct form
+};
+SmallCut small_cut(uint32_t N, uint32_t d, uint32_t K, bool sums);   // sums: an iteration, else an E-step alone
+hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, const SmallCut& cut, uint32_t* idx, float* dmin,
                              uint32_t* counts, const Workspace& w, hipStream_t s);
 hipError_t launch_small_assign(const float* X, uint32_t N, uint32_t d, const float* C, uint32_t K, uint32_t* idx, float* dmin,
                                const Workspace& w, hipStream_t s);

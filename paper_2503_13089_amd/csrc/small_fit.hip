@@ -341,16 +341,10 @@ __global__ __launch_bounds__(kFinThreads) void small_means_kernel(const char* __
 // iterations, us, direct / scores: N = 65536, d = 4, K = 64 96.7 / 98.7, 110 111.1 / 110.8, 170 126.4 / 122.0; 32768, d = 8, K = 80 106.6 / 107.5, 140 125.4 / 122.8;
 // 65536, d = 8, K = 100 135.0 / 137.6, 200 168.3 / 163.1; 19200, d = 16, K = 90 138.6 / 141.5, 190 178.8 / 175.0.
 constexpr uint32_t kDirectMost = 112;
-struct Cut {
-    uint32_t blocks, per_block;
-    int slices, lane;   // ways to split the codebook; vectors of a lane
-    bool direct;        // every distance in direct form
-};
-
 // Workgroups of `per` groups of 64 vectors
-Cut cut_by(uint32_t groups, uint32_t per)
+SmallCut cut_by(uint32_t groups, uint32_t per)
 {
-    Cut c{};
+    SmallCut c{};
     c.per_block = per * 64;
     c.blocks = (groups + per - 1) / per;
     return c;
@@ -361,7 +355,7 @@ uint32_t least_per_block(uint32_t groups) { return (groups + kMaxBlocks - 1) / k
 
 // us of an iteration: scores, exchange and decisions on the vector ALUs (a compute unit with one workgroup issues four fifths of what one with two does),
 // and the workgroups' sums out and in again at 4.5 TB/s.
-double cost_of(const Cut& c, uint32_t d, uint32_t K, bool sums)
+double cost_of(const SmallCut& c, uint32_t d, uint32_t K, bool sums)
 {
     const uint32_t at_once = 8 / uint32_t(c.slices) * c.lane, steps = (c.per_block / 64 + at_once - 1) / at_once;   // groups of 64 vectors
     const double alu = c.lane * (c.direct ? 4.0 * d + 18.0 : 2.0 * d + 7.0), lds = 4.0 * (c.direct ? 2.0 * d : 2.0 * d + 2.0);   // a centroid and wave; four SIMDs share LDS
@@ -373,37 +367,10 @@ double cost_of(const Cut& c, uint32_t d, uint32_t K, bool sums)
     return 2.0 * rounds * (side_by_side ? 1.0 : 1.25) * (1.0 + idle) * steps * (scores + decisions) / 2200 + (sums ? double(c.blocks) * 2 * double(partial_bytes(d, K)) / 4.5e6 : 0.0);
 }
 
-// How the vectors are dealt out: the cheapest of as many workgroups as there may be, or fewer, of 2, 3 or 4 vectors to a lane and 8, 4, 2 or 1 ways to split the
-// codebook that a kernel exists for. Few groups to a workgroup leave none of the larger steps whole; steps that are split 8 ways fit any number.
-Cut cut_of(uint32_t N, uint32_t d, uint32_t K, bool sums)
-{
-    const uint32_t groups = (N + 63) / 64, least = least_per_block(groups);
-    Cut best{};
-    double best_cost = 1e300;
-    for (uint32_t per = least; per <= 2 * least + 1; per += std::max(1u, least / 16)) {
-        Cut c = cut_by(groups, per);
-        for (int lane = d == 16 ? 2 : 4; lane >= 1; --lane) {
-            if ((lane == 1) != (per == 1)) continue;
-            for (int slices = 8; slices >= (lane == 1 || lane == 3 ? 8 : 1); slices /= 2) {
-                c.lane = lane;
-                c.slices = slices;
-                c.direct = lane == 1 || (slices == 8 && lane != 3 && K <= kDirectMost);
-                const double cost = cost_of(c, d, K, sums);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = c;
-                }
-            }
-        }
-    }
-    return best;
-}
-
 template <int D, bool SUMS>
-hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K, uint32_t* idx, float* dmin, const Workspace& w,
+hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K, const SmallCut& c, uint32_t* idx, float* dmin, const Workspace& w,
                          hipStream_t s)
 {
-    const Cut c = cut_of(N, D, K, SUMS);
     const uint32_t lds = uint32_t(lds_bytes(D, K, c.lane, c.slices, SUMS)), stride = uint32_t(partial_bytes(D, K));
     auto launch = [&](auto kernel) {
         if (lds > 48 * 1024) {
@@ -437,12 +404,12 @@ hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K,
 }
 
 template <int D>
-hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K, uint32_t* idx, float* dmin, uint32_t* counts,
+hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K, const SmallCut& c, uint32_t* idx, float* dmin, uint32_t* counts,
                                const Workspace& w, hipStream_t s)
 {
-    if (hipError_t e = launch_iter_t<D, true>(X, N, C, K, idx, dmin, w, s); e != hipSuccess) return e;
+    if (hipError_t e = launch_iter_t<D, true>(X, N, C, K, c, idx, dmin, w, s); e != hipSuccess) return e;
     hipLaunchKernelGGL(small_means_kernel<D>, dim3((K * D + 15) / 16), dim3(kFinThreads), 0, s, w.small_partials,
-                       uint32_t(partial_bytes(D, K)), cut_of(N, D, K, true).blocks, C, counts, K, N, w.hdr);
+                       uint32_t(partial_bytes(D, K)), c.blocks, C, counts, K, N, w.hdr);
     return hipGetLastError();
 }
 
@@ -465,6 +432,32 @@ bool small_problem(uint64_t N, uint32_t d, uint32_t K)
     return true;
 }
 
+// How the vectors are dealt out: the cheapest of as many workgroups as there may be, or fewer, of 2, 3 or 4 vectors to a lane and 8, 4, 2 or 1 ways to split the
+// codebook that a kernel exists for. Few groups to a workgroup leave none of the larger steps whole; steps that are split 8 ways fit any number.
+SmallCut small_cut(uint32_t N, uint32_t d, uint32_t K, bool sums)
+{
+    const uint32_t groups = (N + 63) / 64, least = least_per_block(groups);
+    SmallCut best{};
+    double best_cost = 1e300;
+    for (uint32_t per = least; per <= 2 * least + 1; per += std::max(1u, least / 16)) {
+        SmallCut c = cut_by(groups, per);
+        for (int lane = d == 16 ? 2 : 4; lane >= 1; --lane) {
+            if ((lane == 1) != (per == 1)) continue;
+            for (int slices = 8; slices >= (lane == 1 || lane == 3 ? 8 : 1); slices /= 2) {
+                c.lane = lane;
+                c.slices = slices;
+                c.direct = lane == 1 || (slices == 8 && lane != 3 && K <= kDirectMost);
+                const double cost = cost_of(c, d, K, sums);
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best = c;
+                }
+            }
+        }
+    }
+    return best;
+}
+
 size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K)
 {
     if (!small_problem(N, d, K)) return 0;
@@ -472,13 +465,13 @@ size_t small_partials_bytes(uint64_t N, uint32_t d, uint32_t K)
     return size_t(cut_by(groups, least_per_block(groups)).blocks) * partial_bytes(d, K);
 }
 
-hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, uint32_t* idx, float* dmin,
+hipError_t launch_small_iter(const float* X, uint32_t N, uint32_t d, float* C, uint32_t K, const SmallCut& cut, uint32_t* idx, float* dmin,
                              uint32_t* counts, const Workspace& w, hipStream_t s)
 {
     switch (d) {
-        case 4: return launch_small_iter_t<4>(X, N, C, K, idx, dmin, counts, w, s);
-        case 8: return launch_small_iter_t<8>(X, N, C, K, idx, dmin, counts, w, s);
-        case 16: return launch_small_iter_t<16>(X, N, C, K, idx, dmin, counts, w, s);
+        case 4: return launch_small_iter_t<4>(X, N, C, K, cut, idx, dmin, counts, w, s);
+        case 8: return launch_small_iter_t<8>(X, N, C, K, cut, idx, dmin, counts, w, s);
+        case 16: return launch_small_iter_t<16>(X, N, C, K, cut, idx, dmin, counts, w, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -487,9 +480,9 @@ hipError_t launch_small_assign(const float* X, uint32_t N, uint32_t d, const flo
                                const Workspace& w, hipStream_t s)
 {
     switch (d) {
-        case 4: return launch_iter_t<4, false>(X, N, C, K, idx, dmin, w, s);
-        case 8: return launch_iter_t<8, false>(X, N, C, K, idx, dmin, w, s);
-        case 16: return launch_iter_t<16, false>(X, N, C, K, idx, dmin, w, s);
+        case 4: return launch_iter_t<4, false>(X, N, C, K, small_cut(N, d, K, false), idx, dmin, w, s);
+        case 8: return launch_iter_t<8, false>(X, N, C, K, small_cut(N, d, K, false), idx, dmin, w, s);
+        case 16: return launch_iter_t<16, false>(X, N, C, K, small_cut(N, d, K, false), idx, dmin, w, s);
         default: return hipErrorInvalidValue;
     }
 }
