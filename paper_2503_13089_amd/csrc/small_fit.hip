@@ -385,7 +385,9 @@ hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K,
         if (c.direct) return launch(small_iter_kernel<D, 2, 8, true, SUMS>);
         switch (c.slices) {
             case 1: return launch(small_iter_kernel<D, 2, 1, false, SUMS>);
-            case 2: return launch(small_iter_kernel<D, 2, 2, false, SUMS>);
+            case 2:
+                if constexpr (D == 16) return launch(small_iter_kernel<D, 2, 2, false, SUMS>);
+                return hipErrorInvalidValue;
             case 4: return launch(small_iter_kernel<D, 2, 4, false, SUMS>);
             default: return launch(small_iter_kernel<D, 2, 8, false, SUMS>);
         }
@@ -421,7 +423,8 @@ hipError_t launch_small_iter_t(const float* X, uint32_t N, float* C, uint32_t K,
 // 778 / 669, (300000, 700) 588 / 529, (270000, 800) 586 / 506, (400000, 800) 720 / 693, (131072, 900) 421 / 331, (140000, 1000) 454 / 427, (180000, 1000) 481 / 482, (500000,
 // 1000) 812 / 877, (90000, 1200) 402 / 370, (65536, 1300) 366 / 344, (131072, 1300) 440 / 486, (66000, 1490) 412 / 409; d = 8: (4 M, 450) 5936 / 4267, (4 M, 520) 6031 / 4838,
 // (1 M, 560) 1762 / 1436, (300000, 560) 774 / 682, (262144, 620) 706 / 616, (500000, 620) 1044 / 967, (140000, 700) 573 / 480, (200000, 700) 667 / 648, (300000, 700) 784 /
-// 795, (400000, 660) 928 / 945, (90000, 745) 517 / 398. d = 16: every codebook that fits.
+// 795, (400000, 660) 928 / 945, (90000, 745) 517 / 398. d = 16, every codebook that fits: (20000, 390) 598 / 277, (400000, 390) 1545 / 1185, (8 M, 390)
+// 22863 / 15195 (others 20405 / 15591), (1 M, 300) 2920 / 1760, (4 M, 250) 9796 / 5380, (4 M, 130) 9803 / 3381; and d = 8: (8 M, 570) 11907 / 10364.
 // An E-step alone, fp16 numbers, others: d = 8: (4 M, 390) 516 / 387, 506 / 424, (800000, 400) 137 / 118, 167 / 152, (300000, 500) 83 / 76, 117 / 100, (4 M, 570) 529 / 534,
 // 624 / 581; d = 4: (4 M, 280) 230 / 172, 284 / 202, (400000, 700) 75 / 71, 103 / 91, (130000, 900) 44 / 33, 59 / 39: the same lines.
 bool small_problem(uint64_t N, uint32_t d, uint32_t K)
@@ -444,6 +447,7 @@ SmallCut small_cut(uint32_t N, uint32_t d, uint32_t K, bool sums)
         for (int lane = d == 16 ? 2 : 4; lane >= 1; --lane) {
             if ((lane == 1) != (per == 1)) continue;
             for (int slices = 8; slices >= (lane == 1 || lane == 3 ? 8 : 1); slices /= 2) {
+                if (lane == 2 && slices == 2 && d != 16) continue;   // the cheapest for no size
                 c.lane = lane;
                 c.slices = slices;
                 c.direct = lane == 1 || (slices == 8 && lane != 3 && K <= kDirectMost);
