@@ -263,12 +263,26 @@ __global__ __launch_bounds__(kThreads) void cell_keys_of_centroids_kernel(const 
 struct ListRow {
     uint32_t tile, row;
 };
-__device__ __forceinline__ ListRow paired_row(uint32_t at)
+__host__ __device__ constexpr ListRow paired_row(uint32_t at)
 {
     const uint32_t word = (at >> 5) & 1u, h = (at >> 4) & 1u, p = 15u - (at & 15u), in = p / 3u;   // p: from the bottom
     const uint32_t turn = p % 3u == 2u ? in : (p % 3u == 1u ? 5u + in : 10u + in), reg = 8u * word + turn / 2u;
     return {(at >> 6) * 2u + (turn & 1u), reg % 4u + 8u * (reg / 4u) + 4u * h};
 }
+// Which bits of a word of three are sign and upper exponent bit of a number, 6 bits after the one before from bit 4 of the three on: the third's are the rest.
+constexpr uint32_t kPairs0 = 0x30c30c30u, kPairs1 = 0x0c30c30cu, kPairs2 = ~(kPairs0 | kPairs1);
+// Result i of tile u of a pair has the six bits from 12 i + 6 u on (of six words); paired_row has to send the centroid there that the word's place stands for.
+constexpr bool pairs_stand_where_the_rows_say()
+{
+    for (uint32_t at = 0; at < 64; ++at) {
+        const ListRow to = paired_row(at);
+        const uint32_t i = to.row % 4 + 4 * (to.row / 8), bit = 12 * i + 6 * to.tile + 4, of_three = bit % 96 / 32, in_word = bit % 32;
+        const uint32_t mask = of_three == 0 ? kPairs0 : (of_three == 1 ? kPairs1 : kPairs2);
+        if (to.tile > 1 || to.row / 4 % 2 != (at >> 4 & 1) || bit / 96 != at >> 5 || ((mask >> in_word) & 3u) != 3u || 30 - in_word != 2 * (at & 15)) return false;
+    }
+    return (kPairs0 & kPairs1) == 0 && kPairs2 == 0xc30c30c3u;
+}
+static_assert(pairs_stand_where_the_rows_say(), "bits of the lists");
 
 // Every centroid to its place: permutation and inverse, ordered row, the operand row of the E-step's packed codebook
 // (assign_mfma_f16.hip) and the one of the lists: 8 product slots (the first fp16 part of each component) and
@@ -377,7 +391,7 @@ __device__ __forceinline__ void score_bits(const f32x16& a, const f32x16& b, uin
 {
     u32x6 v = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
     asm volatile("" : "+v"(v) : "v"(a), "v"(b));
-    uint32_t m0 = 0x30c30c30u, m1 = 0x0c30c30cu;   // of a word of three; the third's are the rest
+    uint32_t m0 = kPairs0, m1 = kPairs1;
     asm("" : "+s"(m0), "+s"(m1));   // two selections, which the compiler takes apart where it knows the masks, or what is asked of the word
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
