@@ -33,7 +33,7 @@ if ROOT not in sys.path:
 FP32_PEAK_TFLOPS = 157.3   # MI355X fp32 vector = fp32 matrix peak
 F16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense fp16 matrix peak
 HBM_PEAK_GBS = 8000.0      # MI355X HBM3E
-VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4   # wave-instructions/s: 1024 SIMDs, one 64-lane VALU instruction per 4 cycles
+VALU_CLOCKS_PEAK = 1024 * 2.4e9  # clocks/s of 1024 SIMDs; a wave's multiply-add takes 2 of them, minima, compares and selects 4 (measured with 8 waves per SIMD)
 
 # HBM bytes per launch from rocprofv3 counter runs of `bench.py --only <kernel>` (FETCH_SIZE and WRITE_SIZE in KiB per
 # dispatch, averaged over the kernel's launches, each scaled by what the same counter reads for a plain device copy of
@@ -42,13 +42,13 @@ VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4   # wave-instructions/s: 1024 SIMDs, one 64-l
 # reads 44,300 KiB x 2 dispatches on FETCH_SIZE and writes 88,580 KiB x 2 on WRITE_SIZE).
 _KIB = 1024.0
 MEASURED_TRAFFIC_BYTES = {
-    ("cfg3_4096x11008_d4_k65536", "fit_estep_direct"): (180173 * 1.988 + 74734 * 0.994) * _KIB,   # near_direct_kernel, mean of 20 launches
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_direct"): (186360 * 1.988 + 72903 * 0.994) * _KIB,   # near_direct_kernel, mean of 20 launches
     # far_kernel (20 a fit) and assign_mfma_f16_kernel (2 a fit)
-    ("cfg3_4096x11008_d4_k65536", "fit_estep_f16"): ((20 * 15476 + 2 * 132275) * 1.988 + (20 * 10073 + 2 * 66374) * 0.994) / 22 * _KIB,
-    ("cfg3_4096x11008_d4_k65536", "estep_whole"): (283040 * 1.988 + 88480 * 0.994) * _KIB,
+    ("cfg3_4096x11008_d4_k65536", "fit_estep_f16"): ((20 * 11949 + 2 * 148718) * 1.988 + (20 * 3660 + 2 * 66372) * 0.994) / 22 * _KIB,
+    ("cfg3_4096x11008_d4_k65536", "estep_whole"): (269910 * 1.988 + 88477 * 0.994) * _KIB,
     # record_chunk_kernel, sliced_accumulate_kernel, sliced_finalize_kernel
-    ("cfg3_4096x11008_d4_k65536", "update"): ((110152 + 55902 + 11032) * 1.988 + (110685 + 18489 + 4185) * 0.994) * _KIB,
-    ("cfg3_4096x11008_d4_k65536", "decode"): (26120 * 1.988 + 176100 * 0.994) * _KIB,
+    ("cfg3_4096x11008_d4_k65536", "update"): ((110169 + 55753 + 11031) * 1.988 + (110681 + 18451 + 4048) * 0.994) * _KIB,
+    ("cfg3_4096x11008_d4_k65536", "decode"): (26124 * 1.988 + 176128 * 0.994) * _KIB,
 }
 
 
@@ -290,9 +290,9 @@ def main():
         n = prof_n[slot]
         ms_ = prof_ms[slot] / n
         if slot == "estep_direct" and by_lists:
-            pairs, kernel = in_lists * pairs_unit / n, "near_direct_kernel (vectors on the list of their cell, direct form)"
+            pairs, kernel = in_lists * pairs_unit / n, "near_direct_kernel (vectors on the list of their cell: fp32 scores, the best four in direct form)"
         elif slot == "estep_direct":
-            pairs, kernel = float(N) * K, "E-step in direct form on the vector ALUs (assign_direct_kernel, or small_iter_kernel with the sums)"
+            pairs, kernel = float(N) * K, "E-step on the vector ALUs (assign_direct_kernel in direct form, or small_iter_kernel with the sums)"
         else:
             scored_here = (scored - in_lists) if by_lists else scored
             pairs = scored_here * pairs_unit / n if total else float(N) * K
@@ -308,18 +308,18 @@ def main():
                                                                                 else ("alu", FP32_PEAK_TFLOPS))
         flop = 2.0 * d * pairs
         rate = flop / (ms_ * 1e-3) / 1e12
-        # wave-instructions that the form cannot do without: one v_min3_f32 per two scores of the matrix cores, or the
-        # distance, its comparison and two selects
-        instr = pairs * (2 * d + 3) / 64.0 if slot == "estep_direct" else pairs / 128.0
+        # clocks of a SIMD that the form cannot do without: one v_min3_f32 per two scores of the matrix cores; d multiply-adds a pair and, for four of them, two
+        # minima and three instructions that keep the best two (a compare and a select more where the number of the four is kept beside the score)
+        clocks = pairs / 64.0 * ((2 * d + (5 if by_lists else 6)) if slot == "estep_direct" else 2)
         return {"bound": bound, "kernel": kernel, "achieved": rate, "peak": peak, "unit": "TFLOP/s", "frac": rate / peak,
                 "traffic": MEASURED_TRAFFIC_BYTES.get((w.name, "fit_" + slot)) if by_lists else None,
                 "flop_per_launch": flop, "pairs_per_launch": pairs, "avg_ms": ms_, "launches_per_job": n / len(walls),
                 "ms_per_step_in_this_kernel": prof_ms[slot] / len(walls) / args.steps,
                 "work": "2 d flop per (vector, centroid) pair actually scored: scored stages x 32 centroids x 512 vectors, "
-                        "summed over the launches (cc_stats), not the whole N x K"}, instr / (ms_ * 1e-3)
+                        "summed over the launches (cc_stats), not the whole N x K"}, clocks / (ms_ * 1e-3)
 
     slot = max(slots, key=lambda k: prof_ms[k])
-    roofline, instr_rate = estep(slot)
+    roofline, clock_rate = estep(slot)
 
     def timed(fn, reps=3):
         fn()
@@ -377,7 +377,7 @@ def main():
             "frac": assign_flop / (whole_ms * 1e-3) / 1e12 / (F16_MFMA_PEAK_TFLOPS if mode in (0, 3) and K >= 128 else FP32_PEAK_TFLOPS),
             "issued_mfma_slot_frac": (2.0 * 16 * km * N * K / (whole_ms * 1e-3) / 1e12 / F16_MFMA_PEAK_TFLOPS
                                       if mode in (0, 3) and K >= 128 else None),
-            "valu_issue_frac": N * K / 128.0 / (whole_ms * 1e-3) / VALU_ISSUE_PEAK,
+            "valu_issue_frac": N * K / 64.0 * 2 / (whole_ms * 1e-3) / VALU_CLOCKS_PEAK,
             "fp32_peak_equivalent": assign_flop / (whole_ms * 1e-3) / 1e12 / FP32_PEAK_TFLOPS,
             "traffic": MEASURED_TRAFFIC_BYTES.get((w.name, "estep_whole")),
         },
@@ -402,16 +402,16 @@ def main():
                    "timing": "median wall time of %d repetitions of the job" % len(walls),
                    "job_wall_ms": {"median": wall * 1e3, "min": min(walls) * 1e3, "max": max(walls) * 1e3},
                    "arithmetic": ("scores from exact fp16 x fp16 products of the inputs with the centroids split into "
-                                  "fp16 parts, fp32 accumulation, fp32 direct-form distances for every decision; "
+                                  "fp16 parts, fp32 accumulation (fp32 products on the lists), fp32 direct-form distances for every decision; "
                                   "cluster sums in 64-bit fixed point" if mode in (0, 3) else "fp32"),
                    "assign_mode": mode, "final_objective": final_objective,
                    "scored_codebook_fraction": (scored / total if total else 1.0),
                    "refined_vectors_per_assign": refined / max(1, assigns)},
         # per launch, averaged over all launches of that kind in the timed fits
         "roofline": roofline,
-        # the same launches against the issue rate of the vector ALUs
-        "roofline_alu": {"bound": "alu", "kernel": roofline["kernel"], "achieved": instr_rate / 1e9,
-                         "peak": VALU_ISSUE_PEAK / 1e9, "unit": "G wave-instr/s", "frac": instr_rate / VALU_ISSUE_PEAK, "traffic": None},
+        # the same launches against the clocks that the vector ALUs have
+        "roofline_alu": {"bound": "alu", "kernel": roofline["kernel"], "achieved": clock_rate / 1e9,
+                         "peak": VALU_CLOCKS_PEAK / 1e9, "unit": "G SIMD clocks/s", "frac": clock_rate / VALU_CLOCKS_PEAK, "traffic": None},
         "standalone_lloyd_iter_ms": iter_ms,
         "kernels": kernels,
     }
@@ -420,7 +420,7 @@ def main():
                                              / F16_MFMA_PEAK_TFLOPS)
     if by_lists:
         for kind in ("estep_direct", "estep_f16"):
-            kernels["estep_lists" if kind == "estep_direct" else "estep_windows"] = dict(estep(kind)[0], valu_issue_frac=estep(kind)[1] / VALU_ISSUE_PEAK)
+            kernels["estep_lists" if kind == "estep_direct" else "estep_windows"] = dict(estep(kind)[0], valu_issue_frac=estep(kind)[1] / VALU_CLOCKS_PEAK)
     if layer is not None:
         line["layer_kernels"] = layer
     del ws, out, Xd
