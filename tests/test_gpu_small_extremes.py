@@ -53,3 +53,21 @@ def test_vectors_of_few_values(N, d, K, levels):
     print(f"few values N={N} d={d} K={K} {levels}", flush=True)
     for a, b in zip(results(x, c0, 0), results(x, c0, 1)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,d,K", SHAPES)
+@pytest.mark.parametrize("log2", [61, 62, 63, 64])
+def test_norms_that_overflow_beside_finite_distances(N, d, K, log2):
+    """Vectors and centroids of 2^60 to 2^66: some squared norms and some distances are finite, others not."""
+    gen = torch.Generator(device="cuda").manual_seed(N + d + K + log2)
+    x = torch.randn(N, d, device="cuda", generator=gen).mul_(2.0 ** log2)
+    c0 = x[torch.randperm(N, device="cuda", generator=gen)[:K]].contiguous()
+    c0[K // 2] = 0.0
+    # one coordinate each: a centroid at 1.9e19, whose square is no finite number, is the nearest of the vector at 1e19, not the one at the origin
+    x[:64] = 0.0
+    x[:64, 0] = 1.0e19
+    c0[K - 1] = 0.0
+    c0[K - 1, 0] = 1.9e19
+    print(f"norms N={N} d={d} K={K} 2^{log2}", flush=True)
+    for a, b in zip(results(x, c0, 0), results(x, c0, 1)):
+        assert torch.equal(a, b)
