@@ -94,7 +94,7 @@ bool use_pruning(const Ctx& cx, uint64_t N, uint32_t d, uint32_t K, int32_t iter
     return K >= 256 && N >= (1u << 19) && iters >= 5;
 }
 
-// Small problems: two launches per iteration, everything in direct form (small_fit.hip); a fit long and large enough for
+// Small problems: two launches per iteration (small_fit.hip); a fit long and large enough for
 // the windows is better off with them.
 bool use_small(const Ctx& cx, uint64_t N, uint32_t K, int32_t iters, const cc::Workspace& w)
 {

@@ -11,9 +11,9 @@
 // The other vectors ("far", 0.7 to 4 %) are collected in their norm order and go through a windowed matrix-core E-step, the
 // 32 to 256 neighbours of a workgroup to a window. A centroid left out is farther than the previous code by a margin that no fp32 comparison can bridge, so the
 // codes are the same bits as those of every other route, whatever the radius, however old the grouping.
-// Measured, kernels of a later E-step: N = 11 M, d = 4, K = 65536: lists 0.08 ms, near vectors 0.15, far ones 0.02 to collect and
-// 0.04 to 0.18 to score, refinement 0.02, the centroids' order 0.05 (1.2 ms by windows). N = 29 M, d = 8: 0.6, 2.7
-// to 3.6, 0.2, 1.6 to 2.4, 0.05 (53 ms). At 2.8 M, d = 8: 0.3, 0.33, 0.02, 0.05, 0.03.
+// Measured, kernels of an E-step, means over a fit: N = 11 M, d = 4, K = 65536: lists 0.07 ms, near vectors 0.14, far ones 0.02 to collect and
+// 0.03 to score, refinement 0.02, the centroids' order 0.03 (1.2 ms by windows). N = 29 M, d = 8: 0.47, 2.8, 0.12, 1.5, 0.06, 0.03
+// (53 ms). At 2.8 M, d = 8: 0.25, 0.30, 0.02, 0.05, 0.02, 0.03.
 //
 // The grouping is only renewed now and then: a vector that has moved to a neighbouring cell meanwhile still has a t(x)
 // against the cell it is stored with, just a larger one. The radius follows from what the last E-step saw: about
@@ -702,8 +702,8 @@ __device__ __forceinline__ float rough_distance(const float (&x)[D], const float
 // are rounded once (2^-24 of each), norm and products add up to 72 x 2^-24 a^2 in a score, direct-form distances are within 8 x 2^-24 a^2 of theirs: 160 x 2^-24 a^2
 // for two candidates, of which 200 are taken; a tag takes 2^-18 of a score. Scores among the subnormal numbers are within 1e-37, always.
 // Bound: vector instructions and, as much, LDS, which takes 8 clocks to give 64 lanes the same 16 bytes. Multiply-adds issue in 2 clocks, minima, compares and
-// selects in 4 (measured with 8 waves per SIMD), so this is 13 clocks a pair and 190 a vector where direct form over the list, a compare and two selects took 34 a
-// pair. N = 11 M, K = 65536 (lists of 43 entries; 60 are aimed at now) 0.147 -> 0.129 ms, 4.2 M, K = 4096 0.061 -> 0.045. A workgroup is one wave,
+// selects in 4 (measured with 8 waves per SIMD), so this is 13 clocks a pair where direct form over the list, a compare and two selects took 34; a set of 64
+// vectors takes 268 instructions beside its pairs (bounds, the best four, what is written), nearly as many as for them. N = 11 M, K = 65536 (lists of 43 entries; 60 are aimed at now) 0.147 -> 0.129 ms, 4.2 M, K = 4096 0.061 -> 0.045. A workgroup is one wave,
 // as in the kernels for d = 8: two in five items are empty or short, and in a workgroup of four the room of those waves waits for the longest. Three sets of 64 to an
 // item leave six waves to a SIMD, four leave four: 0.153. Rows that are loaded again after the scan for the sake of two more waves, 0.153.
 // Tried with the direct form: entries in the order of their distance and vectors in the order of t(x), each 64 looking only as far as their largest

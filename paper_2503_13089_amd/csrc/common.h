@@ -327,7 +327,7 @@ hipError_t launch_assign_mfma_f32(const EStep& e, uint32_t d, const Workspace& w
 // every product is exact, scored with the fp16 MFMA. Same outputs as the fp32 variant.
 hipError_t launch_assign_mfma_f16(const EStep& e, uint32_t d, const Workspace& w, hipStream_t s);
 
-// Small problems (small_fit.hip): E-step in direct form with the codebook and the cluster sums in LDS. One Lloyd
+// Small problems (small_fit.hip): E-step on the vector ALUs with the codebook and the cluster sums in LDS. One Lloyd
 // iteration (C updated in place; idx, dmin and counts may be NULL), and the E-step alone.
 bool small_problem(uint64_t N, uint32_t d, uint32_t K);
 struct SmallCut {           // how the vectors of an iteration are dealt out

@@ -20,8 +20,9 @@
 //      scheduling.
 //
 // Bound: the bf16 / fp16 matrix cores (2 M N K flop against 2.5 PFLOP/s). Measured at M = 2048, 4096 x 11008: the
-// product takes 189 us = 0.98 PFLOP/s. The same loop with every memory instruction taken out (matrix instructions
-// only) takes 130 us: under sustained matrix work the chip clocks near 1.7 GHz instead of 2.4, and the 344 tiles take
+// product takes 169 us = 1.09 PFLOP/s in the first calls of a run, 177 to 219 in later ones by the card's clock, 194 on the mean of 20
+// (0.95). The loop that it grew from took 189 us, and with every memory instruction taken out (matrix instructions
+// only) 130: under sustained matrix work the chip clocks near 1.7 GHz instead of 2.4, and the 344 tiles take
 // 1.5 rounds on 256 compute units where 1.34 would do - that, not 2.5 PFLOP/s, is the ceiling of this tile schedule.
 #include <algorithm>
 #include <type_traits>
@@ -410,7 +411,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
     const uint32_t prow = threadIdx.x / PR, pk = (threadIdx.x % PR) * 8;
     // Where a request goes is a buffer (the tile's rows of x, its column blocks of W), an offset of the lane's that does not change and one of the
     // contraction's that is a scalar, clamped to the last piece: with addresses made per request the loop had 30 vector instructions beside its 16 matrix
-    // instructions, which share the issue with them (2048 x 4096 x 11008, bf16, a call 223 / 213 us; 4096^3 149 / 142). What lies past a buffer's end (the pieces
+    // instructions, which share the issue with them (2048 x 4096 x 11008, bf16, a call 233 / 226 us; 4096^3 155 / 148). What lies past a buffer's end (the pieces
     // beside the last one, in the last row) reads as zero. A buffer has at most 512 K bytes, 2^31 - 2^15 at the most in-features that the rebuild takes.
     const uint32_t rows = min(uint32_t(BM), M - m0), block0 = n0 / 32, blocks = min(uint32_t(BN / 32), NB - block0);
     auto buffer = [](const uint16_t* from, size_t bytes) {
@@ -539,7 +540,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
 #undef CC_GEMM_ARRIVED
 
     // ---- epilogue: accumulator register r of lane (l32, h) is row r % 4 + 8 (r / 4) + 4 h, column l32 of its tile. 32 rows of the wave at a time go through
-    // LDS, and from there as 16-byte pieces: stored from the registers, 2 bytes a lane, the tile took 128 store instructions a wave where these are 16 (2048 x 4096 x 11008, a call 213 / 202 us; 4096^3 142 / 134).
+    // LDS, and from there as 16-byte pieces: stored from the registers, 2 bytes a lane, the tile took 128 store instructions a wave where these are 16 (2048 x 4096 x 11008, a call 226 / 219 us; 4096^3 148 / 142).
     __syncthreads();   // the last slice has been read
     const float sc = (direct && scale != nullptr) ? *scale : 1.0f;
     float bv[8];   // of this lane's columns
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_frag_kernel(
 }
 
 // The tiles of the partial round: y = round(scale * (sum of the f slices, in order) + bias); scale may be NULL (= 1).
-// Bound: memory. 8 elements a thread; with one it took 12.2 us for 88 tiles of 2 slices (46 MB), now 10.0.
+// Bound: memory. 8 elements a thread; with one it took 12.2 us for 88 tiles of 2 slices (46 MB), now 10.0 (a call 218.6 / 217.6).
 template <int DT>
 __global__ __launch_bounds__(kThreads) void gemm_finish_kernel(const float* __restrict__ partial, uint32_t M, uint32_t N,
                                                                uint32_t m_tiles, uint32_t whole, uint32_t f,

@@ -1,4 +1,4 @@
-"""Small problems take a form of their own (Section 3.1's iteration in two launches, direct form): at the edges of how it
+"""Small problems take a form of their own (Section 3.1's iteration in two launches): at the edges of how it
 deals the vectors out, every result has the bits of the direct-form kernels and of the fused matrix-core route."""
 import numpy as np
 import pytest
