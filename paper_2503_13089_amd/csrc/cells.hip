@@ -1175,6 +1175,7 @@ __global__ __launch_bounds__(64, 4) void near_mfma_kernel(NearArgs a)
         };
         // A loop for each number of tiles: one that chose in every group kept scores in other registers for each choice, 25 copies beside 80 instructions.
         // Lists of 2.8 M vectors 188 / 179 us (three tiles of four where cells hold 43 vectors), bf16 layer of 4096^2 at g = 6 16.48 / 16.30 ms, 8192 x 28672 77.7 / 77.0.
+        // (QUEUED: the loop of three tiles leaves a pair of registers in scratch memory while it runs, once per wave.)
         auto score = [&](auto tiles, auto low_too) {
             entries(0);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the rows have been read

@@ -222,7 +222,8 @@ __global__ __launch_bounds__(kThreads, kWaves / 4) void layer_forward_columns_ke
         const char* from = reinterpret_cast<const char*>(p.codes + size_t(base) * p.per_row);
         if constexpr (MT == 4) {
             // Sums of 64 rows leave no registers for eight 64-bit addresses: 24 bytes a lane went through scratch memory, whose loads wait for all the others. A scalar and
-            // 32 bits instead: M = 64, 4096 x 11008 36.8 -> 32.2 us, M = 200, 4096 x 4096 37.0 -> 32.2, 4 bits, M = 64, 4096 x 4096 22.0 -> 20.1. With fewer rows it is up to 6 % slower.
+            // 32 bits instead: M = 64, 4096 x 11008 36.8 -> 32.2 us, M = 200, 4096 x 4096 37.0 -> 32.2, 4 bits, M = 64, 4096 x 4096 22.0 -> 20.1
+            // (37 of its registers still go through scratch, 51 before; 8 and 16 bits none). With fewer rows it is up to 6 % slower.
             typedef const __attribute__((address_space(1))) char* Global;
             uint32_t off = lane_code;
             asm volatile("" : "+v"(off));

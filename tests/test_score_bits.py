@@ -22,3 +22,14 @@ def test_result_has_registers_of_its_own():
         to, a, b = [range(int(lo), int(hi) + 1) for lo, hi in zip(registers[::2], registers[1::2])]
         assert len(to) == 6 and len(a) == len(b) == 16
         assert not set(to) & (set(a) | set(b))
+
+
+@pytest.mark.parametrize("line,fine", [("v[0:5], v[6:21], v[22:37], 1.0", True), ("v[6:11], v[6:21], v[22:37], 1.0", False), ("v[36:41], v[6:21], v[22:37], 1.0", False),
+                                       ("v[0:5], a[6:21], v[22:37], 1.0", False)])
+def test_the_build_refuses_shared_registers(line, fine):
+    name = "v_cvt_scalef32_2xpk16_fp6_f32"
+    if fine:
+        build.check_early_results(name, f"\t{name} {line}\n")
+    else:
+        with pytest.raises(RuntimeError):
+            build.check_early_results(name, f"\t{name} {line}\n")
