@@ -314,12 +314,21 @@ __global__ __launch_bounds__(kFinThreads) void small_means_kernel(const char* __
     const uint32_t k = live ? t % K : 0u, j = live ? t / K : 0u;   // clusters vary fastest, as in the partial sums
     long long s = 0;
     uint32_t n = 0;
-#pragma unroll 8
-    for (uint32_t b = group; b < blocks; b += 16) {
-        const unsigned long long* ps = reinterpret_cast<const unsigned long long*>(partials + size_t(b) * partial_stride);
-        s += static_cast<long long>(ps[j * K + k]);
-        n += reinterpret_cast<const uint32_t*>(ps + size_t(K) * D)[k];
-    }
+    auto eight = [&](uint32_t b0, auto all) {   // requests under way together; past the last block too: one at a time the rest took a trip to memory each
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            const uint32_t b = b0 + 16 * u;
+            const bool in = decltype(all)::value || b < blocks;
+            const unsigned long long* ps = reinterpret_cast<const unsigned long long*>(partials + size_t(in ? b : b0) * partial_stride);
+            const unsigned long long part = ps[j * K + k];
+            const uint32_t members = reinterpret_cast<const uint32_t*>(ps + size_t(K) * D)[k];
+            s += in ? static_cast<long long>(part) : 0;
+            n += in ? members : 0u;
+        }
+    };
+    uint32_t b = group;
+    for (; b + 16 * 7 < blocks; b += 16 * 8) eight(b, std::true_type{});
+    if (b < blocks) eight(b, std::false_type{});
     red_s[threadIdx.x] = s;
     red_n[threadIdx.x] = n;
     __syncthreads();

@@ -71,3 +71,15 @@ def test_norms_that_overflow_beside_finite_distances(N, d, K, log2):
     print(f"norms N={N} d={d} K={K} 2^{log2}", flush=True)
     for a, b in zip(results(x, c0, 0), results(x, c0, 1)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("blocks", [1, 15, 16, 17, 112, 113, 127, 128, 129, 240, 241, 255, 256, 257, 511, 512])
+def test_sums_of_any_number_of_workgroups(blocks):
+    """Sixteen threads add the workgroups' sums of an entry, eight requests at a time: none is left out or counted twice, whatever their number (64 or 128 vectors each)."""
+    N, d, K = 64 * blocks, 4, 5
+    gen = torch.Generator(device="cuda").manual_seed(blocks)
+    x = torch.randn(N, d, device="cuda", generator=gen).mul_(0.02).half().float()
+    c0 = x[torch.randperm(N, device="cuda", generator=gen)[:K]].contiguous()
+    print(f"workgroups {blocks}", flush=True)
+    for a, b in zip(results(x, c0, 0), results(x, c0, 1)):
+        assert torch.equal(a, b)
