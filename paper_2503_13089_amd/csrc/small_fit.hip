@@ -196,7 +196,6 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
     for (uint32_t v0 = lo; v0 < hi; v0 += VS) {
         if (S == 1 || v0 != lo) load_vectors(v0);
         if constexpr (DIRECT) {   // distances in direct form, nothing to decide
-            static_assert(S > 1, "the waves meet");
             float bd[V];
             uint32_t bk[V];
 #pragma unroll
@@ -214,6 +213,11 @@ __global__ __launch_bounds__(kThreads, 4) void small_iter_kernel(const float* __
                     bk[v] = dist < bd[v] ? k : bk[v];
                     bd[v] = dist < bd[v] ? dist : bd[v];
                 }
+            }
+            if constexpr (S == 1) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) finish(x[v], v0 + part * VW + v * 64 + lane, bd[v], 0.0f, bk[v]);
+                continue;
             }
             __syncthreads();
 #pragma unroll
@@ -373,7 +377,10 @@ double cost_of(const SmallCut& c, uint32_t d, uint32_t K, bool sums)
     const uint32_t rounds = (c.blocks + 255) / 256;
     const bool side_by_side = rounds > 1 && lds_bytes(d, K, c.lane, c.slices, sums) <= 80 * 1024;
     const double idle = c.blocks < 256 ? 0.25 * (256 - c.blocks) / 256 : 0.0;   // fewer share what all wait for
-    return 2.0 * rounds * (side_by_side ? 1.0 : 1.25) * (1.0 + idle) * steps * (scores + decisions) / 2200 + (sums ? double(c.blocks) * 2 * double(partial_bytes(d, K)) / 4.5e6 : 0.0);
+    const double us = 2.0 * rounds * (side_by_side ? 1.0 : 1.25) * (1.0 + idle) * steps * (scores + decisions) / 2200;
+    if (!sums) return us;
+    const double meet = double(rounds) * (c.per_block / 64) * (d + 1) * 200.0 / K / 2200;   // additions of a wave that wait for each other: 3 clocks each for 64 / K of them
+    return us + meet + double(c.blocks) * 2 * double(partial_bytes(d, K)) / 4.5e6;
 }
 
 template <int D, bool SUMS>
@@ -391,9 +398,11 @@ hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K,
     };
     if (c.lane == 1) return launch(small_iter_kernel<D, 1, 8, true, SUMS>);
     if (c.lane == 2) {
-        if (c.direct) return launch(small_iter_kernel<D, 2, 8, true, SUMS>);
+        if (c.direct) return c.slices == 1 ? launch(small_iter_kernel<D, 2, 1, true, SUMS>) : launch(small_iter_kernel<D, 2, 8, true, SUMS>);
         switch (c.slices) {
-            case 1: return launch(small_iter_kernel<D, 2, 1, false, SUMS>);
+            case 1:
+                if constexpr (D != 8) return launch(small_iter_kernel<D, 2, 1, false, SUMS>);
+                return hipErrorInvalidValue;
             case 2:
                 if constexpr (D == 16) return launch(small_iter_kernel<D, 2, 2, false, SUMS>);
                 return hipErrorInvalidValue;
@@ -403,7 +412,7 @@ hipError_t launch_iter_t(const float* X, uint32_t N, const float* C, uint32_t K,
     }
     if constexpr (D < 16) {
         if (c.lane == 3) return launch(small_iter_kernel<D, 3, 8, false, SUMS>);
-        if (c.direct) return launch(small_iter_kernel<D, 4, 8, true, SUMS>);
+        if (c.direct) return c.slices == 1 ? launch(small_iter_kernel<D, 4, 1, true, SUMS>) : launch(small_iter_kernel<D, 4, 8, true, SUMS>);
         switch (c.slices) {
             case 1: return launch(small_iter_kernel<D, 4, 1, false, SUMS>);
             case 2: return launch(small_iter_kernel<D, 4, 2, false, SUMS>);
@@ -445,7 +454,10 @@ bool small_problem(uint64_t N, uint32_t d, uint32_t K)
 }
 
 // How the vectors are dealt out: the cheapest of as many workgroups as there may be, or fewer, of 2, 3 or 4 vectors to a lane and 8, 4, 2 or 1 ways to split the
-// codebook that a kernel exists for. Few groups to a workgroup leave none of the larger steps whole; steps that are split 8 ways fit any number.
+// codebook that a kernel exists for. A codebook that is not split goes in direct form where that costs less, up to 20 to 30 centroids: what a decision takes beside its
+// scores is 24 d + 420 clocks. With few of them the additions to the sums meet, and the fullest compute unit is what a call waits for. Fits of 10
+// iterations, us, scores alone and meetings not counted / now: (376704, 16, 4) 281 / 200, (590848, 8, 4) 251 / 190, (2.6 M, 8, 2) 770 / 610, (2.1 M, 8, 10) 428 / 368, (3.3 M, 4,
+// 3) 455 / 400, (417152, 8, 20) 194 / 171. Few groups to a workgroup leave none of the larger steps whole; steps that are split 8 ways fit any number.
 SmallCut small_cut(uint32_t N, uint32_t d, uint32_t K, bool sums)
 {
     const uint32_t groups = (N + 63) / 64, least = least_per_block(groups);
@@ -456,14 +468,18 @@ SmallCut small_cut(uint32_t N, uint32_t d, uint32_t K, bool sums)
         for (int lane = d == 16 ? 2 : 4; lane >= 1; --lane) {
             if ((lane == 1) != (per == 1)) continue;
             for (int slices = 8; slices >= (lane == 1 || lane == 3 ? 8 : 1); slices /= 2) {
-                if (lane == 2 && slices == 2 && d != 16) continue;   // the cheapest for no size
+                if (lane == 2 && slices == 2 && d != 16) continue;   // no size takes these
                 c.lane = lane;
                 c.slices = slices;
-                c.direct = lane == 1 || (slices == 8 && lane != 3 && K <= kDirectMost);
-                const double cost = cost_of(c, d, K, sums);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = c;
+                for (int form = 0; form < 2; ++form) {
+                    c.direct = lane == 1 || (slices == 8 && lane != 3 && K <= kDirectMost) || form == 1;
+                    if (form == 1 && slices != 1) break;   // not split: whichever costs less
+                    if (lane == 2 && d == 8 && slices == 1 && !c.direct) continue;   // no size
+                    const double cost = cost_of(c, d, K, sums);
+                    if (cost < best_cost) {
+                        best_cost = cost;
+                        best = c;
+                    }
                 }
             }
         }

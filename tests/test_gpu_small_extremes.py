@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # not split / split 8 ways, scores
-SHAPES = [(1048577, 4, 64), (20000, 4, 130), (65537, 8, 3), (20000, 8, 130), (1000001, 16, 250), (32769, 16, 130)]
+SHAPES = [(1048577, 4, 64), (20000, 4, 130), (65537, 8, 3), (300001, 8, 50), (20000, 8, 130), (1000001, 16, 250), (32769, 16, 130)]
 
 
 def results(x, c0, mode):

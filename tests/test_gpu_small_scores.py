@@ -10,7 +10,8 @@ torch = pytest.importorskip("torch")
 SHAPES = [(16384, 4, 1490), (1048577, 4, 64), (20000, 4, 130), (20000, 4, 111), (262145, 4, 700), (524288, 4, 64), (262145, 4, 113), (65537, 4, 111), (100001, 4, 899), (40000, 4, 3),
           (16384, 8, 575), (65537, 8, 3), (20000, 8, 700), (20000, 8, 111), (270001, 8, 575), (400003, 8, 574), (262145, 8, 64), (65537, 8, 113), (32769, 8, 2), (16384, 16, 299),
           (40000, 16, 1), (100001, 16, 113), (32769, 16, 130), (16384, 16, 390), (40000, 16, 64),
-          (50335, 4, 84), (293837, 4, 74), (50241, 8, 90), (265738, 8, 43), (65998, 8, 9), (49292, 8, 259), (114585, 16, 8)]
+          (50335, 4, 84), (293837, 4, 74), (50241, 8, 90), (265738, 8, 43), (65998, 8, 9), (49292, 8, 259), (114585, 16, 8),
+          (131202, 4, 68), (786486, 4, 5), (32914, 4, 24), (524748, 8, 4), (262239, 8, 3), (65642, 8, 25), (32797, 8, 23), (140583, 16, 41), (131137, 16, 43)]
 
 
 @pytest.mark.parametrize("N,d,K", SHAPES)
