@@ -689,6 +689,7 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
         else put(std::true_type{});
     };
     auto add = [&](const Step& s) {
+        if (kShort && s.rows == 0) return;   // nor a wait for its requests
         if (SRC == 2 || (SRC == 0 && s.kind == kRowsBf16)) add_kind(s, std::true_type{});
         else add_kind(s, std::false_type{});
     };
@@ -708,9 +709,15 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
         }
         return;
     }
-    Step c;   // two steps ahead (a step without rows adds nothing)
+    // Two steps ahead; a wave of one step asks for no other. Calls whose waves have a few steps, us, all steps asked for and added / now: 99468 vectors of 4, K = 10680 20.4 / 19.4,
+    // 250245, K = 4179 21.8 / 21.3, 16-bit gradient of 512 x 512 at K = 8000 15.9 / 15.3.
+    Step c;
     bool more = next();
-    load(b, more);
+    if (!more) {
+        add(a);
+        return;
+    }
+    load(b, true);
     do {
         more = more && next();
         load(c, more);

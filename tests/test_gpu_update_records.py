@@ -107,7 +107,8 @@ def test_16_bit_gradients_on_either_side_of_2_24_numbers(dt, in_features, out_fe
     assert torch.equal(out.cpu(), want.float().cpu())
 
 
-@pytest.mark.parametrize("N,K,scale,least", [(300 * 3584 + 5, 8192, 0, 0), (300 * 3584, 5000, 0, 1e-9), (40000, 9000, 100, 0), (70001, 20000, -90, 0), (70001, 20000, -126, 0), (3_000_001, 65536, -20, 1e-13)])
+@pytest.mark.parametrize("N,K,scale,least", [(300 * 3584 + 5, 8192, 0, 0), (300 * 3584, 5000, 0, 1e-9), (40000, 9000, 100, 0), (70001, 20000, -90, 0), (70001, 20000, -126, 0), (3_000_001, 65536, -20, 1e-13),
+                                               (32768, 30000, 0, 0), (33000, 6000, 0, 1e-9), (99468, 10680, 0, 0), (150001, 33000, 0, 0), (250245, 4179, 0, 1e-9)])   # few steps to a wave
 def test_terms_of_few_bits_and_others_side_by_side(N, K, scale, least):
     """bf16 numbers of ordinary range, whose terms have at most 30 bits above a common unit, `least`: with a few among them that have not, over the
     exponents where the scale of the sums meets its ends."""
