@@ -655,9 +655,6 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
             s.cluster[u] = reinterpret_cast<const uint16_t*>(base + kChunk * (2 * D))[i];
         }
     };
-    // Rows of 8 were no faster for terms of few bits and two steps under way: 16-bit gradients of 4096x11008 138.9 -> 139.7 us at g = 6, 82.8 -> 83.4 at g = 8; rows of 4
-    // 80.5 -> 78.5, of 9 183.3 -> 181.0.
-    constexpr bool kShort = D != 8;
     auto add_kind = [&](const Step& s, auto bf16) {
         float x[U][n], t[U][n];
         uint32_t fractions = 0;
@@ -668,10 +665,8 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
                 const uint32_t w = s.w[u][j / 2];
                 x[u][j] = decltype(bf16)::value ? __uint_as_float(j & 1 ? w & 0xffff0000u : w << 16)
                                                 : float(__builtin_bit_cast(_Float16, uint16_t(j & 1 ? w >> 16 : w)));
-                if constexpr (kShort) {
-                    t[u][j] = x[u][j] * st.scale;
-                    fractions |= not_whole(t[u][j]);
-                }
+                t[u][j] = x[u][j] * st.scale;
+                fractions |= not_whole(t[u][j]);
             }
         auto put = [&](auto shorts) {
 #pragma unroll
@@ -684,12 +679,11 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
                 if (SRC == 0 && piece == 0) atomicAdd(&cnt[s.cluster[u]], 1u);
             }
         };
-        if constexpr (!kShort) put(std::false_type{});
-        else if (__any(fractions != 0)) put(std::false_type{});
+        if (__any(fractions != 0)) put(std::false_type{});
         else put(std::true_type{});
     };
     auto add = [&](const Step& s) {
-        if (kShort && s.rows == 0) return;   // nor a wait for its requests
+        if (s.rows == 0) return;   // nor a wait for its requests
         if (SRC == 2 || (SRC == 0 && s.kind == kRowsBf16)) add_kind(s, std::true_type{});
         else add_kind(s, std::false_type{});
     };
@@ -698,17 +692,6 @@ __device__ __forceinline__ void add_records(unsigned long long* sum, uint32_t* c
     if (!next()) return;
     Step a, b;
     load(a, true);
-    if constexpr (!kShort) {
-        for (bool more = true; more;) {
-            more = next();
-            load(b, more);
-            add(a);
-            more = more && next();
-            load(a, more);
-            add(b);
-        }
-        return;
-    }
     // Two steps ahead; a wave of one step asks for no other. Calls whose waves have a few steps, us, all steps asked for and added / now: 99468 vectors of 4, K = 10680 20.4 / 19.4,
     // 250245, K = 4179 21.8 / 21.3, 16-bit gradient of 512 x 512 at K = 8000 15.9 / 15.3.
     Step c;
