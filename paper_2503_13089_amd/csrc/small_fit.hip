@@ -318,21 +318,31 @@ __global__ __launch_bounds__(kFinThreads) void small_means_kernel(const char* __
     const uint32_t k = live ? t % K : 0u, j = live ? t / K : 0u;   // clusters vary fastest, as in the partial sums
     long long s = 0;
     uint32_t n = 0;
-    auto eight = [&](uint32_t b0, auto all) {   // requests under way together; past the last block too: one at a time the rest took a trip to memory each
+    auto batch = [&](uint32_t first, auto most, auto all) {   // requests under way together; past the last block too: one at a time the rest took a trip to memory each
+        constexpr uint32_t n_of = decltype(most)::value;
+        unsigned long long part[n_of];
+        uint32_t members[n_of];
 #pragma unroll
-        for (uint32_t u = 0; u < 8; ++u) {
-            const uint32_t b = b0 + 16 * u;
-            const bool in = decltype(all)::value || b < blocks;
-            const unsigned long long* ps = reinterpret_cast<const unsigned long long*>(partials + size_t(in ? b : b0) * partial_stride);
-            const unsigned long long part = ps[j * K + k];
-            const uint32_t members = reinterpret_cast<const uint32_t*>(ps + size_t(K) * D)[k];
-            s += in ? static_cast<long long>(part) : 0;
-            n += in ? members : 0u;
+        for (uint32_t u = 0; u < n_of; ++u) {
+            const uint32_t b = first + group + 16 * u;
+            const unsigned long long* ps = reinterpret_cast<const unsigned long long*>(partials + size_t(decltype(all)::value || b < blocks ? b : 0u) * partial_stride);
+            part[u] = ps[j * K + k];
+            members[u] = reinterpret_cast<const uint32_t*>(ps + size_t(K) * D)[k];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < n_of; ++u) {
+            const bool in = decltype(all)::value || first + group + 16 * u < blocks;
+            s += in ? static_cast<long long>(part[u]) : 0;
+            n += in ? members[u] : 0u;
         }
     };
-    uint32_t b = group;
-    for (; b + 16 * 7 < blocks; b += 16 * 8) eight(b, std::true_type{});
-    if (b < blocks) eight(b, std::false_type{});
+    uint32_t first = 0;
+    for (; first + 16 * 8 <= blocks; first += 16 * 8) batch(first, std::integral_constant<uint32_t, 8>{}, std::true_type{});
+    const uint32_t rest = blocks - first;
+    if (rest > 16 * 4) batch(first, std::integral_constant<uint32_t, 8>{}, std::false_type{});
+    else if (rest > 16 * 2) batch(first, std::integral_constant<uint32_t, 4>{}, std::false_type{});
+    else if (rest > 16) batch(first, std::integral_constant<uint32_t, 2>{}, std::false_type{});
+    else if (rest > 0) batch(first, std::integral_constant<uint32_t, 1>{}, std::false_type{});
     red_s[threadIdx.x] = s;
     red_n[threadIdx.x] = n;
     __syncthreads();
